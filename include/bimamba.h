@@ -198,8 +198,8 @@ typedef struct bimamba_input_grads {
 } bimamba_input_grads;
 
 /* Gradients with respect to one direction's parameters: device pointers, fp32, contiguous, shaped like bimamba_params;
- * sums over batch and tokens, zeroed by the library first; the sum over the batch is formed with fp32 atomics, so
- * its last bits can differ between two calls with batch > 2.  dconv_b / ddt_bias may be NULL (not wanted). */
+ * sums over batch and tokens (overwritten, not accumulated into), formed in a fixed order: two calls on the same inputs
+ * give the same bits.  dconv_b / ddt_bias may be NULL (not wanted). */
 typedef struct bimamba_param_grads {
     float* dconv_w;
     float* dconv_b;
@@ -221,8 +221,7 @@ typedef struct bimamba_param_grads {
  * Supported: the selective-scan layout, i.e. n_heads == d_inner (Delta, A, D per channel), a_kind PER_HEAD_STATE,
  * d_kind PER_CHANNEL, conv_bc 0, d_state 4, 8 or 16; every other descriptor returns BIMAMBA_ERR_UNSUPPORTED.
  * Nothing may overlap: the gradient views among themselves, the inputs, dout.  (Not checked.)
- * The call enqueues kernels only (its accumulation targets are cleared by a fill kernel, not a memset node) and asks
- * the runtime nothing at first use, so it can be captured into a HIP graph as it is.
+ * The call enqueues kernels only (no memset nodes), so it can be captured into a HIP graph as it is.
  */
 int bimamba_bwd(const bimamba_desc* desc, const bimamba_params* pf, const bimamba_params* pb,
                 const bimamba_inputs* in_f, const bimamba_inputs* in_b, const bimamba_tensor* dout,
@@ -230,10 +229,9 @@ int bimamba_bwd(const bimamba_desc* desc, const bimamba_params* pf, const bimamb
                 const bimamba_param_grads* dpf, const bimamba_param_grads* dpb,
                 void* workspace, size_t workspace_bytes, void* hip_stream);
 
-/* Workspace of bimamba_bwd: fp32 B|C rows, the state entering every chunk of tokens for both directions
- * (2 * batch * ceil(L / chunk) * d_inner * d_state floats; chunk = 8 tokens, 16 for d_state 4, while the
- * call has at most as many waves as the device has SIMDs; beyond that 8 tokens, 4 for d_state 16), 12 bytes per (batch, token, channel) for the
- * values one direction leaves for the other to add, and the per-wave partial sums of dB and dC. */
+/* Workspace of bimamba_bwd: fp32 B|C rows, the state entering every chunk of 8 tokens for both directions (2 * batch *
+ * L / 8 * d_inner * d_state floats), the sums at the ends of the time segments a call is cut into, 12 bytes per (batch,
+ * token, channel) for the values one direction leaves for the other to add, and the per-wave partial sums of dB and dC. */
 size_t bimamba_bwd_workspace_bytes(const bimamba_desc* desc);
 
 /* Bytes of device scratch the two calls above need for this descriptor (0 on an invalid descriptor).  Pure host code. */

@@ -639,10 +639,9 @@ int bimamba_block_fwd_static(const bimamba_desc* desc, const bimamba_params* pf,
 // ---- gradients -------------------------------------------------------------------------------------------------
 namespace {
 struct BwdPlan {
-    bool dense;   // the two-waves-per-SIMD form of the kernels (shorter chunks for 16 states)
-    int chunk, nchunk;
+    int nseg, seg_len, seg_chunks, tiles;
     int tiles_per_group;
-    size_t off_bc[2], off_state, off_parked, off_part[2], total;
+    size_t off_bc[2], off_state, off_state_w, off_seg_h, off_seg_d, off_seg_w, off_params, off_parked, off_part[2], total;
 };
 
 int check_bwd_desc(const bimamba_desc* d)
@@ -658,16 +657,23 @@ int check_bwd_desc(const bimamba_desc* d)
 BwdPlan make_bwd_plan(const bimamba_desc* d)
 {
     BwdPlan p{};
-    p.dense = bm::bwd_dense(d->d_inner, d->batch);
-    p.chunk = bm::bwd_chunk_tokens(d->d_state, p.dense);
-    p.nchunk = d->seqlen > 0 ? (d->seqlen + p.chunk - 1) / p.chunk : 1;
+    bm::bwd_segments(d->d_inner, d->batch, d->seqlen, &p.nseg, &p.seg_len, &p.seg_chunks);
+    p.tiles = (d->d_inner + 63) / 64;
     const size_t bc = align_up((size_t)d->batch * d->seqlen * d->n_groups * 2 * d->d_state * sizeof(float), 256);
-    const size_t parked = align_up((size_t)d->batch * d->seqlen * d->d_inner * sizeof(Parked), 256);
+    // (the walk fetches parked rows two tokens ahead, past a sequence's ends: rows to spare on both sides)
+    constexpr int kSpareRows = 16;
+    const size_t parked = align_up(((size_t)d->batch * d->seqlen + 2 * kSpareRows) * d->d_inner * sizeof(Parked), 256);
+    const size_t segs = (size_t)2 * d->batch * p.nseg, row = (size_t)p.tiles * 64 * sizeof(float);   // (one float per chain)
     size_t off = 0;
     p.off_bc[0] = off; off += bc;
     p.off_bc[1] = off; off += bc;    // sized for separate activations
-    p.off_state = off; off += align_up((size_t)2 * d->batch * p.nchunk * d->d_inner * d->d_state * sizeof(float), 256);
-    p.off_parked = off; off += parked;
+    p.off_state = off; off += segs * p.seg_chunks * row * d->d_state;
+    p.off_state_w = off; off += segs * p.seg_chunks * row;
+    p.off_seg_h = off; off += segs * row * d->d_state;
+    p.off_seg_d = off; off += segs * row * d->d_state;
+    p.off_seg_w = off; off += 2 * segs * row;
+    p.off_params = off; off += segs * row * (d->d_state + bm::kBwdParams);
+    p.off_parked = off + (size_t)kSpareRows * d->d_inner * sizeof(Parked); off += parked;
     // per-wave partial sums of dB | dC: one slot per channel tile of a group and direction
     p.tiles_per_group = (d->d_inner / d->n_groups + 63) / 64;
     const size_t part = align_up((size_t)d->batch * d->seqlen * d->n_groups * p.tiles_per_group * 2 * d->d_state * sizeof(float), 256);
@@ -724,63 +730,59 @@ int bimamba_bwd(const bimamba_desc* d, const bimamba_params* pf, const bimamba_p
     const int GN = d->n_groups * d->d_state;
     const bool bf16 = d->io_dtype == BIMAMBA_BF16;
 
-    // parameter gradients are sums over the batch: zero them even for an empty call
-    for (const bimamba_param_grads* g : {dpf, dpb}) {
-        bm::launch_bwd_zero(g->dconv_w, (long long)d->d_inner * d->d_conv, st);
-        bm::launch_bwd_zero(g->dconv_b, d->d_inner, st);
-        bm::launch_bwd_zero(g->dA, (long long)d->d_inner * d->d_state, st);
-        bm::launch_bwd_zero(g->dD, d->d_inner, st);
-        bm::launch_bwd_zero(g->ddt_bias, d->d_inner, st);
+    bm::BwdSumArgs sum{};
+    sum.N = d->d_state; sum.Dn = d->d_inner; sum.K = d->d_conv;
+    for (int s = 0; s < 2; s++) {
+        const bimamba_param_grads* g = s == 0 ? dpf : dpb;
+        sum.dA[s] = g->dA; sum.dD[s] = g->dD; sum.dconv_w[s] = g->dconv_w; sum.dconv_b[s] = g->dconv_b; sum.ddt_bias[s] = g->ddt_bias;
     }
     if (live) {
-        const int nbuf = shared ? 1 : 2;
-        for (int s = 0; s < nbuf; s++) {
-            const bimamba_inputs* in = s == 0 ? in_f : in_b;
-            PrepArgs pa{};
-            pa.B = targ(in->B);
-            pa.C = targ(in->C);
-            pa.dst = reinterpret_cast<float*>(ws + plan.off_bc[s]);
-            pa.batch = d->batch; pa.L = d->seqlen; pa.G = d->n_groups; pa.N = d->d_state; pa.K = d->d_conv;
-            pa.Dn = d->d_inner; pa.tail_ch = d->d_inner; pa.conv_bc = 0; pa.dir = s == 0 ? 1 : -1;
-            const long long total = (long long)d->batch * d->seqlen * 2 * GN;
-            const dim3 grid((unsigned)((total + 255) / 256));
-            if (bf16) hipLaunchKernelGGL(prep_bc_kernel<IoBF16>, grid, dim3(256), 0, st, pa);
-            else hipLaunchKernelGGL(prep_bc_kernel<IoF32>, grid, dim3(256), 0, st, pa);
-        }
-        BwdArgs a{};
+        bm::BwdPrepArgs pa{};
+        bm::BwdArgs a{};
         for (int s = 0; s < 2; s++) {
             const bimamba_inputs* in = s == 0 ? in_f : in_b;
             const bimamba_params* p = s == 0 ? pf : pb;
-            const bimamba_param_grads* g = s == 0 ? dpf : dpb;
             const bimamba_input_grads* gi = (s == 0 || !din_b) ? din_f : din_b;
+            const int set = shared ? 0 : s;
+            pa.B[set] = targ(in->B); pa.C[set] = targ(in->C);
+            pa.dst[set] = reinterpret_cast<float*>(ws + plan.off_bc[set]);
             DirArgs& da = a.dir[s];
             da.x = targ(in->x); da.z = targ(in->z); da.dt = targ(in->dt);
-            da.bc = reinterpret_cast<const float*>(ws + plan.off_bc[shared ? 0 : s]);
+            da.bc = pa.dst[set];
             da.conv_w = p->conv_w; da.conv_b = p->conv_b; da.A = p->A; da.D = p->D; da.dt_bias = p->dt_bias;
             // shared activations: both directions' waves fill slots of one buffer (the two parts are adjacent)
-            a.bc_part[s] = reinterpret_cast<float*>(ws + plan.off_part[shared ? 0 : s]);
+            a.bc_part[s] = reinterpret_cast<float*>(ws + plan.off_part[set]);
             a.gdx[s] = targ(gi->dx); a.gdz[s] = targ(gi->dz); a.gddt[s] = targ(gi->ddt);
-            a.dA[s] = g->dA; a.dD[s] = g->dD; a.dconv_w[s] = g->dconv_w; a.dconv_b[s] = g->dconv_b; a.ddt_bias[s] = g->ddt_bias;
+            sum.part[set] = a.bc_part[s];
+            sum.dB[set] = gi->dB; sum.dC[set] = gi->dC;
         }
+        const int sets = shared ? 1 : 2;
+        pa.L = d->seqlen; pa.G = d->n_groups; pa.N = d->d_state;
+        pa.per_set = (long long)d->batch * d->seqlen * 2 * GN;
+        bm::launch_bwd_prep(bf16, pa, sets, st);
         a.dout = targ(*dout);
         a.state = reinterpret_cast<float*>(ws + plan.off_state);
-        a.parked = reinterpret_cast<Parked*>(ws + plan.off_parked);
-        a.L = d->seqlen; a.Dn = d->d_inner; a.G = d->n_groups; a.K = d->d_conv; a.nchunk = plan.nchunk;
+        a.state_w = reinterpret_cast<float*>(ws + plan.off_state_w);
+        a.seg_h = reinterpret_cast<float*>(ws + plan.off_seg_h);
+        a.seg_d = reinterpret_cast<float*>(ws + plan.off_seg_d);
+        a.seg_w = reinterpret_cast<float*>(ws + plan.off_seg_w);
+        a.param_part = reinterpret_cast<float*>(ws + plan.off_params);
+        a.parked = reinterpret_cast<bm::Parked*>(ws + plan.off_parked);
+        a.L = d->seqlen; a.Dn = d->d_inner; a.G = d->n_groups; a.K = d->d_conv;
+        a.nseg = plan.nseg; a.seg_len = plan.seg_len; a.seg_chunks = plan.seg_chunks; a.tiles = plan.tiles;
         a.dt_softplus = d->dt_softplus; a.separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
         a.park = shared;
+        a.try_progression = 1;
         a.bc_slots = plan.tiles_per_group * (shared ? 2 : 1);
         a.bc_slot_of_rev = shared ? plan.tiles_per_group : 0;
-        bm::launch_bwd(d->d_state, bf16, plan.dense, a, d->batch, st);
-        for (int s = 0; s < (shared ? 1 : 2); s++) {
-            const bimamba_input_grads* gi = s == 0 ? din_f : din_b;
-            BwdBcArgs ba{};
-            ba.part = a.bc_part[s];
-            ba.dB = gi->dB; ba.dC = gi->dC;
-            ba.rows = (long long)d->batch * d->seqlen * d->n_groups;
-            ba.slots = a.bc_slots; ba.N = d->d_state;
-            bm::launch_bwd_bc(ba, st);
-        }
+        bm::launch_bwd(d->d_state, bf16, a, d->batch, st);
+        sum.sets = sets; sum.slots = a.bc_slots;
+        sum.rows = (long long)d->batch * d->seqlen * d->n_groups;
+        sum.param_part = a.param_part;
+        sum.pitch = (long long)plan.tiles * 64;
+        sum.segs = d->batch * plan.nseg;
     }
+    bm::launch_bwd_sum(sum, st);   // an empty call's parameter gradients are zero
     const hipError_t now = hipPeekAtLastError();
     return (now == hipSuccess || now == pending) ? BIMAMBA_OK : BIMAMBA_ERR_HIP;
 }

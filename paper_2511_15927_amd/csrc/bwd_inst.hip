@@ -3,70 +3,125 @@
 #include "bwd_kernels.h"
 #include "launch.h"
 
+#include <atomic>
+
 namespace bm {
 
+// Raising a kernel's dynamic-LDS limit is idempotent; it is done once per (kernel, device).
+constexpr int kMaxDevices = 64;
+static bool first_use_on_current_device(std::atomic<bool>* seen)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return true;
+    return !seen[dev].exchange(true);
+}
+
 bool bwd_supported(int d_state) { return d_state == 4 || d_state == 8 || d_state == 16; }
-int bwd_chunk_tokens(int d_state, bool dense)
+
+// Time segments of a gradient call and their length.  The walk holds two waves per SIMD, so a call is cut until it has
+// four rounds of them: the last round, which may be nearly empty, is then a small part of the call, and the state pass has
+// twice the four waves per SIMD it holds.  Measured at 4, 6, 8, 12, 16 waves per SIMD (bf16): d_inner 4096, batch 8 x 8192
+// tokens 10.4 / 10.7 / 10.2 / 10.2 / 10.1 ms; 3104 channels, batch 22 x 1036: 3.4 / 3.1 / 3.05 / 3.0 / 3.0; 2512 channels,
+// batch 2 x 5813: 1.63 / 1.48 / 1.48 / 1.50 / 1.54.  A segment costs the dh sum of the state pass and three tokens walked
+// twice, so segments stay at 32 tokens or more.
+constexpr int kBwdWavesPerSimd = 8;
+constexpr int kBwdMinSegment = 32;
+void bwd_segments(int d_inner, int batch, int seqlen, int* nseg, int* seg_len, int* seg_chunks)
 {
-    if (dense) return d_state <= 4 ? kBwdChunk<4, true> : d_state <= 8 ? kBwdChunk<8, true> : kBwdChunk<16, true>;
-    return d_state <= 4 ? kBwdChunk<4, false> : d_state <= 8 ? kBwdChunk<8, false> : kBwdChunk<16, false>;
+    const long long waves = 2LL * ((d_inner + 63) / 64) * (batch > 0 ? batch : 1);
+    long long n = (4LL * cu_count() * kBwdWavesPerSimd + waves / 2) / waves;
+    if (n > seqlen / kBwdMinSegment) n = seqlen / kBwdMinSegment;
+    if (n < 1) n = 1;
+    if (n > 65535) n = 65535;
+    const long long len = ((seqlen + n - 1) / n + kBwdChunk - 1) / kBwdChunk * kBwdChunk;
+    *seg_len = (int)(len > 0 ? len : kBwdChunk);
+    *nseg = seqlen > 0 ? (seqlen + *seg_len - 1) / *seg_len : 1;
+    *seg_chunks = *seg_len / kBwdChunk;
 }
 
-// The dense form (two waves per SIMD) once the walk has more waves than the chip has SIMDs; see kBwdChunk.
-bool bwd_dense(int d_inner, int batch) { return 2LL * ((d_inner + 63) / 64) * batch > 4LL * cu_count(); }
-
-// Zeroes a float buffer (the accumulation targets of the atomics above); a kernel rather than a memset node so that
-// the call can be captured into a graph.
-__global__ __launch_bounds__(256) void bwd_zero_kernel(float* p, long long n)
+template <typename IO>
+__global__ __launch_bounds__(256) void bwd_prep_kernel(const BwdPrepArgs a)
 {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) p[i] = 0.0f;
+    using T = typename IO::T;
+    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= a.per_set) return;
+    const int set = blockIdx.y;
+    const int n = (int)(idx % a.N);
+    const int which = (int)(idx / a.N % 2);
+    const long long r = idx / (2 * a.N);          // (batch, token, group)
+    const int g = (int)(r % a.G), t = (int)(r / a.G % a.L), b = (int)(r / a.G / a.L);
+    const TensorArg& src = which ? a.C[set] : a.B[set];
+    a.dst[set][idx] = IO::ld((const T*)src.p + (size_t)b * src.sb + (long long)t * src.st + g * a.N + n);
 }
 
-__global__ __launch_bounds__(256) void bwd_bc_kernel(const BwdBcArgs a)
+void launch_bwd_prep(int io_bf16, const BwdPrepArgs& a, int sets, hipStream_t st)
 {
-    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    const dim3 grid((unsigned)((a.per_set + 255) / 256), (unsigned)sets);
+    if (io_bf16) hipLaunchKernelGGL(bwd_prep_kernel<IoBF16>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(bwd_prep_kernel<IoF32>, grid, dim3(256), 0, st, a);
+}
+
+__global__ __launch_bounds__(256) void bwd_sum_kernel(const BwdSumArgs a)
+{
+    long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     const int two_n = 2 * a.N;
-    if (i >= a.rows * two_n) return;
-    const long long r = i / two_n;
-    const int v = (int)(i % two_n);
-    const float* src = a.part + r * a.slots * two_n + v;
+    const long long per_set = a.rows * two_n;
+    if (i < a.sets * per_set) {
+        const int set = i >= per_set;
+        i -= set * per_set;
+        const long long r = i / two_n;
+        const int v = (int)(i % two_n);
+        const float* src = a.part[set] + r * a.slots * two_n + v;
+        float acc = 0.0f;
+        for (int k = 0; k < a.slots; k++) acc += src[(long long)k * two_n];
+        (v % 2 ? a.dC : a.dB)[set][r * a.N + v / 2] = acc;
+        return;
+    }
+    i -= a.sets * per_set;
+    const int values = a.N + kBwdParams;
+    if (i >= 2LL * values * a.Dn) return;
+    const int ch = (int)(i % a.Dn), v = (int)(i / a.Dn % values), s = (int)(i / a.Dn / values);
+    const float* src = a.param_part + ((size_t)s * a.segs * values + v) * a.pitch + ch;
     float acc = 0.0f;
-    for (int k = 0; k < a.slots; k++) acc += src[(long long)k * two_n];
-    if (v < a.N) a.dB[r * a.N + v] = acc;
-    else a.dC[r * a.N + v - a.N] = acc;
+    for (int k = 0; k < a.segs; k++) acc += src[(size_t)k * values * a.pitch];
+    if (v < a.N) a.dA[s][(size_t)ch * a.N + v] = acc;
+    else if (v == a.N) a.dD[s][ch] = acc;
+    else if (v < a.N + 5) {
+        const int tap = v - a.N - 1 - (4 - a.K);      // rows are tap positions with w[3] on the current token
+        if (tap >= 0) a.dconv_w[s][(size_t)ch * a.K + tap] = acc;
+    } else if (v == a.N + 5) {
+        if (a.dconv_b[s]) a.dconv_b[s][ch] = acc;
+    } else if (a.ddt_bias[s]) a.ddt_bias[s][ch] = acc;
 }
 
-void launch_bwd_bc(const BwdBcArgs& a, hipStream_t st)
+void launch_bwd_sum(const BwdSumArgs& a, hipStream_t st)
 {
-    const long long n = a.rows * 2 * a.N;
-    if (n <= 0) return;
-    hipLaunchKernelGGL(bwd_bc_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
-}
-
-template <int N, typename IO, bool DENSE>
-static void launch_pair(const BwdArgs& a, int batch, hipStream_t st)
-{
-    const dim3 grid((unsigned)(((a.Dn + 63) / 64 + 1) / 2), 1, (unsigned)batch);
-    constexpr int kStateTile = 64 / kBwdStateLanes<N>;    // channels per wave of the state pass
-    const dim3 state_grid((unsigned)(((a.Dn + kStateTile - 1) / kStateTile + 1) / 2), 1, (unsigned)batch);
-    hipLaunchKernelGGL((bwd_state_kernel<N, IO, DENSE>), state_grid, dim3(256), 0, st, a);
-    hipLaunchKernelGGL((bwd_kernel<N, IO, DENSE>), grid, dim3(256), 0, st, a);
+    const long long n = a.sets * a.rows * 2 * a.N + 2LL * (a.N + kBwdParams) * a.Dn;
+    hipLaunchKernelGGL(bwd_sum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, a);
 }
 
 template <int N, typename IO>
-static void launch_form(bool dense, const BwdArgs& a, int batch, hipStream_t st)
+static void launch_walks(const BwdArgs& a, int batch, hipStream_t st)
 {
-    if (dense) launch_pair<N, IO, true>(a, batch, st);
-    else launch_pair<N, IO, false>(a, batch, st);
+    const dim3 grid((unsigned)((a.tiles + 1) / 2), (unsigned)a.nseg, (unsigned)batch);
+    hipLaunchKernelGGL((bwd_state_kernel<N, IO>), grid, dim3(256), 0, st, a);
+    if (a.nseg > 1) {
+        const long long threads = 2LL * batch * a.tiles * 64 * N;
+        hipLaunchKernelGGL(bwd_carry_kernel<N>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a, batch);
+    }
+    static std::atomic<bool> lifted[kMaxDevices];
+    auto walk = bwd_kernel<N, IO>;
+    if (kBwdLdsBytes<N> > 64 * 1024 && first_use_on_current_device(lifted))
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(walk), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBwdLdsBytes<N>);
+    hipLaunchKernelGGL(walk, grid, dim3(256), kBwdLdsBytes<N>, st, a);
 }
 
-void launch_bwd(int d_state, int io_bf16, bool dense, const BwdArgs& a, int batch, hipStream_t st)
+void launch_bwd(int d_state, int io_bf16, const BwdArgs& a, int batch, hipStream_t st)
 {
-#define BM_BWD(n)                                                \
-    case n:                                                      \
-        if (io_bf16) launch_form<n, IoBF16>(dense, a, batch, st); \
-        else launch_form<n, IoF32>(dense, a, batch, st);          \
+#define BM_BWD(n)                                          \
+    case n:                                                \
+        if (io_bf16) launch_walks<n, IoBF16>(a, batch, st); \
+        else launch_walks<n, IoF32>(a, batch, st);          \
         break;
     switch (d_state) {
         BM_BWD(4)
@@ -75,12 +130,6 @@ void launch_bwd(int d_state, int io_bf16, bool dense, const BwdArgs& a, int batc
         default: break;
     }
 #undef BM_BWD
-}
-
-void launch_bwd_zero(float* p, long long n, hipStream_t st)
-{
-    if (!p || n <= 0) return;
-    hipLaunchKernelGGL(bwd_zero_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, n);
 }
 
 }  // namespace bm

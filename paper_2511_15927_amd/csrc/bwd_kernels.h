@@ -13,19 +13,27 @@
 //   dxc_t = D dy_t + sum_n dh_t[n] Delta_t B_t[n]    dpre_t = dxc_t silu'(pre_t)
 //   dx_t = sum_j w[K-1-j] dpre_{t + j steps}         dw[k] += dpre_t x_{t - (K-1-k) steps},  dcb += dpre_t
 //
-// Mapping: a lane is one (direction, batch, channel) chain, as in the forward sweep with one lane per chain (two
-// lanes per chain in the state pass for 8 and 16 states).  The backward recurrence needs the states in the reverse of
-// the order the forward recurrence makes them, so
-//   bwd_state_kernel  walks each chain forward and stores the state entering every chunk of kBwdChunk tokens;
-//   bwd_kernel        takes the chunks last to first: it recomputes a chunk's states from the stored one into
-//                     registers (kBwdChunk * N values per lane) and then walks the chunk backwards.
+// Mapping: a lane is one (direction, batch, channel) chain, as in the forward sweep with one lane per chain, and the
+// sequence is cut into segments that all walk at once, so that a call of any size brings the two waves per SIMD which
+// the walk's register budget allows (bwd_segments in bwd_inst.hip).  The backward recurrence needs the states in the
+// reverse of the order the forward recurrence makes them, so
+//   bwd_state_kernel  walks each segment forward from a zero state and stores the state entering every chunk of
+//                     kBwdChunk tokens, the Delta summed up to there, and the segment's end state.  On the way it also
+//                     sums what the segment's tokens contribute to the dh of the tokens before it:
+//                     sum_t exp(A W_t) C_t dy_t, W_t the Delta from the segment's start to t;
+//   bwd_carry_kernel  folds both across the segments (h in scan order, dh against it);
+//   bwd_kernel        takes a segment's chunks last to first, starting from the folded dh: it recomputes a chunk's
+//                     states from the stored one (plus the decayed state entering the segment) and then walks the chunk
+//                     backwards.  A token's dx takes dpre of the three tokens after it, which the next segment owns:
+//                     the walk starts with those three, for their dpre only.  For the same reason the dh sums run over
+//                     windows that start three tokens into their segment.
 // dB_t and dC_t are sums over the channels of a group: each wave adds its 64 channels with a reduce-scatter over its
-// lanes and stores the sums into its own slot of a partial buffer; bwd_bc_kernel adds the slots in a fixed order (no
-// atomics on activation gradients: the result does not depend on timing).  Parameter gradients are kept per lane and
-// added atomically once per chain (the sum over the batch).  When both directions read the same activations their
-// gradients of x, z and Delta have to be added: the two waves of a channel tile walk the tokens in opposite orders
-// and meet in the middle, as in the forward sweep; each parks its fp32 values for the half it reaches first and, past
-// one workgroup barrier, adds what the other parked to its own values for the other half and rounds once to the I/O dtype.
+// lanes and stores the sums into its own slot of a partial buffer.  Parameter gradients are kept per lane and stored
+// once per segment.  bwd_sum_kernel adds the slots of both in a fixed order (no atomics: the result does not depend on
+// timing).  When both directions read the same activations their gradients of x, z and Delta have to be added: the two
+// waves of a channel tile walk a segment's tokens in opposite orders and meet in its middle, as in the forward sweep;
+// each parks its fp32 values for the half it reaches first and, past one workgroup barrier, adds what the other parked
+// to its own values for the other half and rounds once to the I/O dtype.
 #pragma once
 #include "kernels.h"
 
@@ -39,27 +47,33 @@ struct Parked {
 struct BwdArgs {
     DirArgs dir[2];          // x, z, dt views, prepared fp32 B|C rows and parameters of each direction
     TensorArg dout;          // [batch][L][Dn] (ADD) or [batch][L][2 Dn] (SEPARATE), I/O dtype
-    float* state;            // [2][batch][nchunk][Dn][N]: the state entering each chunk (scan order)
+    // Workspace blocks of one wave: [..][tile][N / 4][64 lanes][4] floats for states, [..][tile][64 lanes] for sums.
+    float* state;            // [2][batch][nseg][seg_chunks] blocks: the state entering each chunk (scan order), from a zero
+                             // state at the segment's start
+    float* state_w;          // [2][batch][nseg][seg_chunks]: Delta summed from the segment's start to the chunk
+    float* seg_h;            // [2][batch][nseg] blocks: the segment's end state, then the state entering it
+    float* seg_d;            // [2][batch][nseg] blocks: the segment's dh sum, then the dh of the tokens after its window
+    float* seg_w;            // [2][2][batch][nseg]: Delta summed over the segment, over its dh window
+    float* param_part;       // [2][batch][nseg][N + 7][tiles * 64]: dA, dD, dconv_w, dconv_b, ddt_bias of a segment
     Parked* parked;          // [batch][L][Dn]: values of the direction that reaches a token first (park only)
     TensorArg gdx[2], gdz[2], gddt[2];   // the caller's gradient views per direction (equal when park)
     int park;                // both directions read the same activations: their gradients are added (see above)
-    float* bc_part[2];       // per direction: [batch][L][G][slots][2N] fp32 partial sums of dB | dC, one slot per wave
+    float* bc_part[2];       // per direction: [batch][L][G][slots][N][2] fp32 partial sums of dB and dC, one slot per wave
     int bc_slots;            // slots per group: channel tiles of a group (x 2 when both directions feed one buffer)
     int bc_slot_of_rev;      // slot offset of the reverse direction's waves (0 when it has a buffer of its own)
-    float* dA[2];            // [Dn][N]
-    float* dD[2];            // [Dn]
-    float* dconv_w[2];       // [Dn][K]
-    float* dconv_b[2];       // [Dn] or null
-    float* ddt_bias[2];      // [Dn] or null
-    int L, Dn, G, K, nchunk, dt_softplus, separate;
+    int L, Dn, G, K, dt_softplus, separate;
+    int nseg, seg_len, seg_chunks, tiles;
+    int try_progression;     // let each wave test whether its chains' A rows are arithmetic in n
 };
 
-// Tokens per chunk: (chunk + 1) * N state values per lane live in registers during the walk.  DENSE is the form for
-// launches with more waves than SIMDs: it has to leave room for a second wave on the SIMD (256 registers), which for 16
-// states means chunks of four tokens and twice the stored states (and eight instead of sixteen for 4).  Measured at d_inner 4096 and 64 K tokens: batch 8
-// (one wave per SIMD) 17.2 ms in the plain form, 18.8 ms in the dense one; batch 16 and 32: 17.2 against 13.7 ms.
-template <int N, bool DENSE>
-constexpr int kBwdChunk = DENSE ? (N <= 8 ? 8 : 4) : (N <= 4 ? 16 : 8);
+// Tokens per chunk: what bwd_kernel keeps of one chunk is a state per token, half of them in registers and, for 16
+// states, the other half in LDS, so that a wave fits 256 registers and a SIMD holds two.
+constexpr int kBwdChunk = 8;
+template <int N>
+constexpr int kBwdLdsTokens = N >= 16 ? 5 : 0;
+template <int N>
+constexpr size_t kBwdLdsBytes = (size_t)4 * kBwdLdsTokens<N> * 64 * N * sizeof(float);   // of a workgroup: two fit a CU
+constexpr int kBwdParams = 7;   // parameter gradients of a chain besides dA: dD, four taps, conv bias, Delta bias
 
 __device__ __forceinline__ float dsilu(float v)
 {
@@ -71,23 +85,21 @@ __device__ __forceinline__ float sigmoidf(float v) { return __builtin_amdgcn_rcp
 // Sums NV values per lane over the 64 lanes of the wave and leaves the total of value j in the lanes
 // j * (64 / NV) ... (j + 1) * (64 / NV) - 1 (returned by every lane: the total of value lane / (64 / NV)).
 // A reduce-scatter: each step halves the values a lane still carries.  The lane whose bit is clear keeps the first half
-// and receives its partner's first half, the other lane the second half, so NV - 1 + log2(64 / NV) adds do the work of
-// 6 * NV.  Partners: the other 32-lane half and the other row of 16 by the swap instructions of gfx950, then inside a
-// row by lane-permute operands (selection by lane group through their bank mask where the bit picks banks).
-template <int CTRL, int ROW_MASK, int BANK_MASK>
-__device__ __forceinline__ float lane_permuted(float old, float x)
-{
-    return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(x), CTRL, ROW_MASK, BANK_MASK, false));
-}
+// and receives its partner's first half, the other lane the second half, so about 2 NV instructions do the work of
+// 6 * NV adds.  Partners: the other 32-lane half and the other row of 16 by the swap instructions of gfx950, then inside a
+// row by lane-permute operands.  There both partners can form both sums, each an add with a permuted operand, and the
+// second one is written only where it is kept (bank masks pick lane groups of four): two instructions for a pair of
+// values where selecting first takes three.  (Inline assembly: the compiler does not form an add that keeps its old
+// result in some banks.  s_nop 1: a permuted operand must not have been written by the two instructions before.)
 template <int CTRL>
 __device__ __forceinline__ float from_partner(float x)
 {
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
 }
 template <int NV>
-__device__ __forceinline__ float wave_reduce_scatter(float (&v)[NV], int lane)
+__device__ __forceinline__ float wave_reduce_scatter(float (&v)[NV])
 {
-    static_assert(NV == 8 || NV == 16 || NV == 32, "8, 16 or 32 values per lane");
+    static_assert(NV == 4 || NV == 8 || NV == 16, "4, 8 or 16 values per lane");
     // lane bit 5: the other half of the wave
 #pragma unroll
     for (int i = 0; i < NV / 2; i++) {
@@ -100,437 +112,757 @@ __device__ __forceinline__ float wave_reduce_scatter(float (&v)[NV], int lane)
         const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[i]), __float_as_uint(v[NV / 4 + i]), false, false);
         v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
     }
-    // lane bit 3: banks 2 and 3 of a row keep the second half; the partner is 8 lanes away (row rotate by 8)
-#pragma unroll
-    for (int i = 0; i < NV / 8; i++) {
-        const float keep = lane_permuted<0xE4, 0xF, 0xC>(v[i], v[NV / 8 + i]);
-        const float send = lane_permuted<0xE4, 0xF, 0xC>(v[NV / 8 + i], v[i]);
-        v[i] = keep + from_partner<0x128>(send);
-    }
-    if constexpr (NV >= 16) {
-        // lane bit 2: banks 1 and 3; the partner is the mirror lane of the other bank of the half row
-#pragma unroll
-        for (int i = 0; i < NV / 16; i++) {
-            const float keep = lane_permuted<0xE4, 0xF, 0xA>(v[i], v[NV / 16 + i]);
-            const float send = lane_permuted<0xE4, 0xF, 0xA>(v[NV / 16 + i], v[i]);
-            v[i] = keep + from_partner<0x141>(send);
-        }
-    }
-    if constexpr (NV >= 32) {
-        // lane bit 1: inside a quad
-        const bool upper = (lane & 2) != 0;
-        const float keep = upper ? v[1] : v[0], send = upper ? v[0] : v[1];
-        v[0] = keep + from_partner<0x4E>(send);
+    float t = v[0];
+    if constexpr (NV == 16) {
+        // lane bit 3: banks 2 and 3 of a row keep the second half; the partner is 8 lanes away.  Lane bit 2: banks 1 and 3; the
+        // partner is the mirror lane of the other bank of the half row.
+        float a, b;
+        asm("s_nop 1\n\t"
+            "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %1, %3, %3 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %0, %4, %4 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+            "v_add_f32_dpp %1, %5, %5 row_ror:8 row_mask:0xf bank_mask:0xc\n\t"
+            "s_nop 0\n\t"
+            "v_add_f32_dpp %0, %0, %0 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+            "s_nop 0\n\t"
+            "v_add_f32_dpp %0, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa"
+            : "=&v"(a), "=&v"(b) : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]));
+        t = a;
+    } else if constexpr (NV == 8) {
+        asm("s_nop 1\n\t"
+            "v_add_f32_dpp %0, %1, %1 row_ror:8 row_mask:0xf bank_mask:0xf\n\t"
+            "v_add_f32_dpp %0, %2, %2 row_ror:8 row_mask:0xf bank_mask:0xc"
+            : "=&v"(t) : "v"(v[0]), "v"(v[1]));
     }
     // what is left of the lane index carries the same value: plain sums, quads first (the mirror needs equal quads)
-    float t = v[0];
-    t += from_partner<0xB1>(t);                              // quad_perm [1,0,3,2]
-    if constexpr (NV <= 16) t += from_partner<0x4E>(t);     // quad_perm [2,3,0,1]
+    t += from_partner<0xB1>(t);                             // quad_perm [1,0,3,2]
+    t += from_partner<0x4E>(t);                             // quad_perm [2,3,0,1]
     if constexpr (NV <= 8) t += from_partner<0x141>(t);     // row_half_mirror
+    if constexpr (NV <= 4) t += from_partner<0x128>(t);     // row_ror:8
     return t;
 }
 
-// The per-lane view of one chain shared by both kernels: constants, the scan-order token walk and the forward step.
+// The per-wave view of a (segment, direction, channel tile): places, constants and the scan-order token walk.
 template <int N, typename IO>
-struct BwdChain {
+struct BwdWave {
     using T = typename IO::T;
-    float a2[N];                 // A * log2(e)
-    float w4[4], cb, dval, dtb;  // conv taps (w4[3] on the current token), conv bias, D, Delta bias
-    const T *xb, *zb, *dtb_ptr;  // the lane's element of token 0 of this batch element
-    long long xs, zs, dts;       // token strides (elements)
-    const float* bc;             // prepared B|C rows of this batch element and group: row t at bc + t * bcs
-    long long bcs;
+    int s, b, seg, tile, lane, ch, grp;
+    bool exists, valid;          // the wave has a tile of its own; the lane has a channel of its own
+    int j0, j1;                  // the segment's scan positions [j0, j1); those outside [0, L) do not exist
+    int k0, k1;                  // its chunks [k0, k1) that hold tokens
     int L, dir;
+    float a2[N], d2;             // A * log2(e); with an arithmetic A the step between neighbouring states
+    float w4[4], cb, dval, dtb;  // conv taps (w4[3] on the current token), conv bias, D, Delta bias
 
-    __device__ __forceinline__ int token(int scan_index) const { return dir > 0 ? scan_index : L - 1 - scan_index; }
-    __device__ __forceinline__ float raw_x(int scan_index) const
-    {
-        return (scan_index >= 0 && scan_index < L) ? IO::cvt(xb[(long long)token(scan_index) * xs]) : 0.0f;
-    }
-    __device__ __forceinline__ float delta_of(float raw, bool softplus_dt) const { return softplus_dt ? softplus(raw + dtb) : raw; }
-    __device__ __forceinline__ uniform_ro_ptr row(int scan_index) const
-    {
-        return (uniform_ro_ptr)(bc + (long long)token(scan_index) * bcs);
-    }
-};
-
-// S lanes per chain: a wave's tile is 64 / S channels, lane l on channel l / S of it.
-template <int N, typename IO, int S = 1>
-__device__ __forceinline__ bool bwd_chain_setup(const BwdArgs& a, int w, BwdChain<N, IO>& c, int& s, int& b, int& ch, bool& valid)
-{
-    using T = typename IO::T;
-    constexpr int CPW = 64 / S;
-    s = w & 1;
-    b = blockIdx.z;
-    const int lane = threadIdx.x & 63;
-    int tile = (int)blockIdx.x * 2 + (w >> 1);
-    const bool exists = tile * CPW < a.Dn;               // the second tile of the last workgroup may not exist:
-    if (!exists) tile -= 1;                              // its waves shadow the first (they compute and store nothing)
-    valid = exists && tile * CPW + lane / S < a.Dn;
-    ch = min(tile * CPW + lane / S, a.Dn - 1);            // lanes past the last channel shadow it and contribute nothing
-    const DirArgs& da = a.dir[s];
-    const int grp = (tile * CPW) / (a.Dn / a.G);         // uniform: a tile never straddles two B/C groups
-#pragma unroll
-    for (int n = 0; n < N; n++) c.a2[n] = da.A[(size_t)ch * N + n] * kLog2e;
-#pragma unroll
-    for (int i = 0; i < 4; i++) c.w4[3 - i] = i < a.K ? da.conv_w[(size_t)ch * a.K + (a.K - 1 - i)] : 0.0f;
-    c.cb = da.conv_b ? da.conv_b[ch] : 0.0f;
-    c.dval = da.D[ch];
-    c.dtb = (a.dt_softplus && da.dt_bias) ? da.dt_bias[ch] : 0.0f;
-    c.xb = (const T*)da.x.p + (size_t)b * da.x.sb + ch;
-    c.zb = (const T*)da.z.p + (size_t)b * da.z.sb + ch;
-    c.dtb_ptr = (const T*)da.dt.p + (size_t)b * da.dt.sb + ch;
-    c.xs = da.x.st; c.zs = da.z.st; c.dts = da.dt.st;
-    c.bcs = (long long)a.G * 2 * N;
-    c.bc = da.bc + ((size_t)b * a.L * a.G + grp) * (2 * N);
-    c.L = a.L;
-    c.dir = s == 0 ? 1 : -1;
-    return exists;
-}
-
-// Lanes per chain of the state pass.  This pass has no sums across channels, so splitting the states of a chain over
-// two lanes costs only the repeated per-channel part (conv, SiLU, Delta: a third of the stream) and puts two waves on
-// every SIMD where one lane per chain leaves one, which issues an instruction only every seven cycles.
-template <int N>
-constexpr int kBwdStateLanes = N >= 8 ? 2 : 1;
-
-// grid (ceil(ceil(Dn / (64 / S)) / 2), 1, batch), block 256: waves 0 / 1 the forward / reverse chain of one channel
-// tile, waves 2 / 3 those of the next; S = kBwdStateLanes<N>, lane l of a wave holds states (l % S) * N / S ... of its chain.
-template <int N, typename IO, bool DENSE>
-__global__ __launch_bounds__(256, kBwdStateLanes<N>) void bwd_state_kernel(const BwdArgs a)
-{
-    constexpr int CT = kBwdChunk<N, DENSE>;
-    constexpr int S = kBwdStateLanes<N>;
-    constexpr int NS = N / S;
-    static_assert(NS % 4 == 0, "a lane's states are loaded and stored four at a time");
-    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    BwdChain<N, IO> c;
-    int s, b, ch;
-    bool valid;
-    if (!bwd_chain_setup<N, IO, S>(a, w, c, s, b, ch, valid)) return;
-    const bool sp = a.dt_softplus != 0;
-    const int part = (int)(threadIdx.x & 63) % S;        // which NS of the chain's states this lane holds
-    float a2[NS], h[NS];
-#pragma unroll
-    for (int n = 0; n < NS; n++) {
-        a2[n] = c.a2[n];
-#pragma unroll
-        for (int e = 1; e < S; e++) a2[n] = part == e ? c.a2[e * NS + n] : a2[n];
-        h[n] = 0.0f;
-    }
-    float x1 = 0.0f, x2 = 0.0f, x3 = 0.0f;   // raw x one, two, three tokens back in scan order
-    float* dst = a.state + (((size_t)s * gridDim.z + b) * a.nchunk * a.Dn + ch) * N + part * NS;
-    // A SIMD with one or two waves has little to hide a memory round trip behind: the activations of the next chunk
-    // are requested before the current chunk is worked through.  That includes the chunk's B rows: the same address
-    // in every lane of a part, but as scalar loads their round trips would lie open in front of every other token (a
-    // wave waits for all of its scalar loads at once, so none can be kept in flight across a use); as vector loads
-    // into the registers such a SIMD has to spare they arrive a chunk early.
-    typename IO::T xr[CT], dr[CT], xnext[CT], dnext[CT];
-    Float4 br[CT][NS / 4], bnext[CT][NS / 4];
-    unsigned in_vgpr = (unsigned)(part * NS * sizeof(float));
-    keep_narrow(in_vgpr);                                // an offset the compiler cannot prove uniform
-    auto request = [&](typename IO::T (&xq)[CT], typename IO::T (&dq)[CT], Float4 (&bq)[CT][NS / 4], int k) {
-#pragma unroll
-        for (int i = 0; i < CT; i++) {
-            const long long t = c.token(min(k * CT + i, a.L - 1));
-            xq[i] = c.xb[t * c.xs];
-            dq[i] = c.dtb_ptr[t * c.dts];
-            const Float4* row = (const Float4*)((const char*)(c.bc + t * c.bcs) + in_vgpr);
-#pragma unroll
-            for (int q = 0; q < NS / 4; q++) bq[i][q] = row[q];
-        }
-    };
-    request(xr, dr, br, 0);
-    for (int k = 0; k < a.nchunk; k++) {
-        if (valid) {
-#pragma unroll
-            for (int n = 0; n < NS; n++) dst[n] = h[n];
-        }
-        dst += (size_t)a.Dn * N;
-        if (k == a.nchunk - 1) break;    // the state after the last chunk feeds nothing
-        request(xnext, dnext, bnext, k + 1);
-#pragma unroll
-        for (int i = 0; i < CT; i++) {
-            if (k * CT + i >= a.L) break;
-            const float x0 = IO::cvt(xr[i]);
-            const float pre = fmaf(c.w4[0], x3, fmaf(c.w4[1], x2, fmaf(c.w4[2], x1, fmaf(c.w4[3], x0, c.cb))));
-            x3 = x2; x2 = x1; x1 = x0;
-            const float xc = silu(pre);
-            const float delta = c.delta_of(IO::cvt(dr[i]), sp);
-            const float u = delta * xc;
-#pragma unroll
-            for (int n = 0; n < NS; n++) h[n] = fmaf(fast_exp2(delta * a2[n]), h[n], u * br[i][n / 4][n % 4]);
-        }
-#pragma unroll
-        for (int i = 0; i < CT; i++) {
-            xr[i] = xnext[i];
-            dr[i] = dnext[i];
-#pragma unroll
-            for (int q = 0; q < NS / 4; q++) br[i][q] = bnext[i][q];
-        }
-    }
-}
-
-template <int N, typename IO, bool DENSE>
-__global__ __launch_bounds__(256, DENSE ? 2 : 1) void bwd_kernel(const BwdArgs a)
-{
-    using T = typename IO::T;
-    constexpr int CT = kBwdChunk<N, DENSE>;
-    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int lane = threadIdx.x & 63;
-    BwdChain<N, IO> c;
-    int s, b, ch;
-    bool valid;
-    // a wave without a tile of its own still runs (as a shadow of its neighbour): the barrier below counts four waves
-    const bool exists = bwd_chain_setup<N, IO>(a, w, c, s, b, ch, valid);
-    const bool sp = a.dt_softplus != 0;
-    const int my_tile = min((int)blockIdx.x * 2 + (w >> 1), (a.Dn + 63) / 64 - 1);
-    const int grp = my_tile * 64 / (a.Dn / a.G);
-    // Addresses: every tensor is walked through a wave-uniform byte pointer (kept in scalar registers and stepped by
-    // scalar adds) plus a byte offset of the lane that is fixed for the whole walk.  Per-lane pointers indexed by the
-    // token cost a few scalar multiplies per access, a fifth of this kernel's instructions when it was written that
-    // way.  (Forcing the stores into the scalar-base form as well, by keeping the lane offsets 32 bits wide in the
-    // blocks of the stores, was measured slower: the pointers then stay live in scalar registers up to each store and
-    // the B and C rows push them out into lanes of a vector register.)
-    const DirArgs& da = a.dir[s];
-    unsigned lo_t = (unsigned)(ch * sizeof(T));                              // x, z, dt, dout, dx, dz, ddt
-    unsigned lo_pk = (unsigned)(ch * sizeof(Parked));
-    unsigned lo_state = (unsigned)(ch * N * sizeof(float));
-    constexpr int kLanesPerValue = 64 / (2 * N);
-    unsigned lo_part = (unsigned)((lane / kLanesPerValue) * sizeof(float));
+    // A tensor walked token by token: a wave-uniform byte pointer; the lane's place in a row is a byte offset of its own.
     struct Walked {
         const char* base;    // token 0 of this batch element (and direction, where the tensor has one half per direction)
         int stride;          // bytes per token (the host bounds token strides at 2^26 elements, channels included)
     };
-    const Walked wx{(const char*)da.x.p + (size_t)b * da.x.sb * sizeof(T), (int)(da.x.st * (long long)sizeof(T))};
-    const Walked wdt{(const char*)da.dt.p + (size_t)b * da.dt.sb * sizeof(T), (int)(da.dt.st * (long long)sizeof(T))};
-    const Walked wz{(const char*)da.z.p + (size_t)b * da.z.sb * sizeof(T), (int)(da.z.st * (long long)sizeof(T))};
-    const Walked wg{(const char*)a.dout.p + ((size_t)b * a.dout.sb + (a.separate ? s * a.Dn : 0)) * sizeof(T),
-                    (int)(a.dout.st * (long long)sizeof(T))};
-    const Walked wodx{(const char*)a.gdx[s].p + (size_t)b * a.gdx[s].sb * sizeof(T), (int)(a.gdx[s].st * (long long)sizeof(T))};
-    const Walked wodz{(const char*)a.gdz[s].p + (size_t)b * a.gdz[s].sb * sizeof(T), (int)(a.gdz[s].st * (long long)sizeof(T))};
-    const Walked woddt{(const char*)a.gddt[s].p + (size_t)b * a.gddt[s].sb * sizeof(T), (int)(a.gddt[s].st * (long long)sizeof(T))};
-    const Walked wpk{(const char*)(a.parked + (size_t)b * a.L * a.Dn), a.Dn * (int)sizeof(Parked)};
-    // this wave's slot of the dB | dC partial sums: [batch][L][G][slots][2N]
-    const int tiles_per_group = (a.Dn / a.G + 63) / 64;
-    const int slot = my_tile % tiles_per_group + (s == 1 ? a.bc_slot_of_rev : 0);
-    const Walked wpart{(const char*)(a.bc_part[s] + (((size_t)b * a.L * a.G + grp) * a.bc_slots + slot) * (2 * N)),
-                       a.G * a.bc_slots * 2 * N * (int)sizeof(float)};
-    const Walked wrow{(const char*)c.bc, (int)(c.bcs * (long long)sizeof(float))};
-    const char* const state_base = (const char*)(a.state + ((size_t)s * gridDim.z + b) * a.nchunk * a.Dn * N);
-    const long long state_stride = (long long)a.Dn * N * (long long)sizeof(float);
-    auto at_scan = [&](const Walked& t, int scan_index) { return t.base + (long long)c.token(scan_index) * t.stride; };
-    // the per-token pointers start at the last token in scan order and move one token against it per step
-    const char* p_odx = at_scan(wodx, a.L - 1);
-    const char* p_odz = at_scan(wodz, a.L - 1);
-    const char* p_oddt = at_scan(woddt, a.L - 1);
-    const char* p_pk = at_scan(wpk, a.L - 1);
-    const char* p_part = at_scan(wpart, a.L - 1);
-    const char* p_row = at_scan(wrow, a.L - 1);
-    const int s_odx = c.dir * wodx.stride, s_odz = c.dir * wodz.stride, s_oddt = c.dir * woddt.stride;
-    const int s_pk = c.dir * wpk.stride, s_part = c.dir * wpart.stride, s_row = c.dir * wrow.stride;
-    const int s_x = c.dir * wx.stride, s_dt = c.dir * wdt.stride, s_z = c.dir * wz.stride, s_g = c.dir * wg.stride;
+    Walked x, z, dt, g, row;
 
-    // In scan order both waves walk j = L-1 .. 0 and park j >= jm: tokens [L/2, L) for the forward direction's wave,
-    // [0, L/2) for the reverse one's.  The other wave's values for j < jm are fetched two tokens ahead (q0, q1): a
-    // load issued where its value is needed would stall the one wave this SIMD holds for a memory round trip.
-    const int jm = a.park ? (s == 0 ? a.L / 2 : a.L - a.L / 2) : a.L;
-    float q0[3] = {0.0f, 0.0f, 0.0f}, q1[3] = {0.0f, 0.0f, 0.0f};
-    auto fetch_parked = [&](float (&q)[3], const char* row) {
-        const Parked v = *(const Parked*)(row + lo_pk);
-        q[0] = v.dx; q[1] = v.dz; q[2] = v.ddt;
-    };
-    // the barrier is a workgroup-scope release / acquire: past it, what the other wave of the tile parked is visible
-    auto meet = [&]() {
-        __syncthreads();
-        if (jm >= 1) fetch_parked(q0, at_scan(wpk, jm - 1));
-        if (jm >= 2) fetch_parked(q1, at_scan(wpk, jm - 2));
-    };
-    if (a.park && jm >= a.L) meet();                     // a one-token call: the reverse direction's wave parks nothing
-
-    float dh[N], gA[N];
-#pragma unroll
-    for (int n = 0; n < N; n++) dh[n] = gA[n] = 0.0f;
-    float gD = 0.0f, gcb = 0.0f, gbias = 0.0f, gw[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-    float dp1 = 0.0f, dp2 = 0.0f, dp3 = 0.0f;   // dpre of the tokens one, two, three steps later in scan order
-
-    // as in the state pass: the next chunk's activations are requested before this chunk is worked through
-    T xr[CT], dr[CT], zr[CT], gr[CT], xnext[CT], dnext[CT], znext[CT], gnext[CT];
-    T xprev[3] = {};                                     // raw x of the three tokens before the chunk in xr
-    float hnext[N];                                      // the state entering the next chunk to be walked
-    auto request_state = [&](int k) {
-        const float* src = (const float*)(state_base + k * state_stride + lo_state);
-#pragma unroll
-        for (int n = 0; n < N; n++) hnext[n] = src[n];
-    };
-    {   // the chunk walked first is the only one that can be short: its missing tokens repeat the last one
-        const int k = a.nchunk - 1;
-#pragma unroll
-        for (int i = 0; i < CT; i++) {
-            const int j = min(k * CT + i, a.L - 1);
-            xr[i] = *(const T*)(at_scan(wx, j) + lo_t);
-            dr[i] = *(const T*)(at_scan(wdt, j) + lo_t);
-            zr[i] = *(const T*)(at_scan(wz, j) + lo_t);
-            gr[i] = *(const T*)(at_scan(wg, j) + lo_t);
-        }
-        if (k > 0) {
-#pragma unroll
-            for (int e = 0; e < 3; e++) xprev[e] = *(const T*)(at_scan(wx, k * CT - 3 + e) + lo_t);
-        }
-        request_state(k);
+    __device__ __forceinline__ int token(int j) const { return dir > 0 ? j : L - 1 - j; }
+    __device__ __forceinline__ const char* at(const Walked& t, int j) const { return t.base + (long long)token(j) * t.stride; }
+    __device__ __forceinline__ int step(const Walked& t) const { return dir * t.stride; }   // bytes from one scan position to the next
+    // block `i` of a [2][batch][nseg]... workspace array, in waves
+    __device__ __forceinline__ size_t place(const BwdArgs& a, int per_seg, int i) const
+    {
+        return ((((size_t)s * gridDim.z + b) * a.nseg + seg) * per_seg + i) * a.tiles + tile;
     }
-    for (int k = a.nchunk - 1; k >= 0; k--) {
-        const int first = k * CT;                                   // scan index of the chunk's first token
-        const int count = min(CT, a.L - first);
-        keep_narrow(lo_t);
-        keep_narrow(lo_pk);
-        keep_narrow(lo_state);
-        keep_narrow(lo_part);
-        float xraw[CT + 3];
+};
+
+template <int N, typename IO>
+__device__ __forceinline__ void bwd_wave_setup(const BwdArgs& a, BwdWave<N, IO>& w)
+{
+    using T = typename IO::T;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    w.s = wave & 1;
+    w.b = blockIdx.z;
+    w.seg = blockIdx.y;
+    w.lane = threadIdx.x & 63;
+    w.tile = (int)blockIdx.x * 2 + (wave >> 1);
+    w.exists = w.tile < a.tiles;                         // the second tile of the last workgroup may not exist:
+    if (!w.exists) w.tile -= 1;                          // its waves shadow the first (they compute and store nothing)
+    w.valid = w.exists && w.tile * 64 + w.lane < a.Dn;
+    w.ch = min(w.tile * 64 + w.lane, a.Dn - 1);          // lanes past the last channel shadow it and contribute nothing
+    // uniform: a tile never straddles two B/C groups (divisions run on the vector ALU: back to a scalar register at once,
+    // or everything addressed through the quotient stays there)
+    w.grp = __builtin_amdgcn_readfirstlane(w.tile * 64 / (a.Dn / a.G));
+    w.L = a.L;
+    w.dir = w.s == 0 ? 1 : -1;
+    // every segment is seg_chunks whole chunks, so that the chunks of both directions hold the same tokens: the last one
+    // may reach past the sequence (scan positions from L on in the forward direction, below 0 in the reverse one)
+    const int t0 = w.seg * a.seg_len;
+    w.j0 = w.s == 0 ? t0 : a.L - t0 - a.seg_len;
+    w.j1 = w.j0 + a.seg_len;
+    w.k0 = w.j0 < 0 ? -w.j0 / kBwdChunk : 0;
+    w.k1 = min(a.seg_chunks, (a.L - w.j0 + kBwdChunk - 1) / kBwdChunk);
+    const DirArgs& da = a.dir[w.s];
 #pragma unroll
-        for (int e = 0; e < 3; e++) xraw[e] = k > 0 ? IO::cvt(xprev[e]) : 0.0f;
-        float hs[CT + 1][N];   // hs[i] = the state entering token i of the chunk
+    for (int n = 0; n < N; n++) w.a2[n] = da.A[(size_t)w.ch * N + n] * kLog2e;
+    w.d2 = (da.A[(size_t)w.ch * N + 1] - da.A[(size_t)w.ch * N]) * kLog2e;
 #pragma unroll
-        for (int n = 0; n < N; n++) hs[0][n] = hnext[n];
-        float xc[CT], delta[CT], pre[CT];
-        // forward over the chunk, keeping every state
-        const char* fwd_row = at_scan(wrow, first);
+    for (int i = 0; i < 4; i++) w.w4[3 - i] = i < a.K ? da.conv_w[(size_t)w.ch * a.K + (a.K - 1 - i)] : 0.0f;
+    w.cb = da.conv_b ? da.conv_b[w.ch] : 0.0f;
+    w.dval = da.D[w.ch];
+    w.dtb = (a.dt_softplus && da.dt_bias) ? da.dt_bias[w.ch] : 0.0f;
+    auto walked = [&](const TensorArg& t, int off) {
+        return typename BwdWave<N, IO>::Walked{(const char*)t.p + ((size_t)w.b * t.sb + off) * sizeof(T), (int)(t.st * (long long)sizeof(T))};
+    };
+    w.x = walked(da.x, 0);
+    w.z = walked(da.z, 0);
+    w.dt = walked(da.dt, 0);
+    w.g = walked(a.dout, a.separate ? w.s * a.Dn : 0);
+    w.row = {(const char*)(da.bc + ((size_t)w.b * a.L * a.G + w.grp) * (2 * N)), a.G * 2 * N * (int)sizeof(float)};
+}
+
+// Whether the A rows of all of the wave's chains are arithmetic in n (see sweep_kernel: bf16 I/O only).
+template <int N, typename IO>
+__device__ __forceinline__ bool bwd_progression(const BwdArgs& a, const BwdWave<N, IO>& w)
+{
+    if (!kProgressionEligible<N, IO> || !a.try_progression) return false;
+    const float* row = a.dir[w.s].A + (size_t)w.ch * N;
+    const float first = row[0], step = row[1] - row[0];
+    bool ok = true;
 #pragma unroll
-        for (int i = 0; i < CT; i++) {
-            xraw[i + 3] = IO::cvt(xr[i]);
-            pre[i] = fmaf(c.w4[0], xraw[i], fmaf(c.w4[1], xraw[i + 1], fmaf(c.w4[2], xraw[i + 2], fmaf(c.w4[3], xraw[i + 3], c.cb))));
-            xc[i] = silu(pre[i]);
-            delta[i] = c.delta_of(IO::cvt(dr[i]), sp);
-            if (i < count) {
-                const float u = delta[i] * xc[i];
-                uniform_ro_ptr row = (uniform_ro_ptr)fwd_row;
+    for (int n = 0; n < N; n++) ok &= row[n] == fmaf((float)n, step, first);
+    return __all(ok);
+}
+
+// f(n, scale * exp(v A[n])) for all n.
+template <int N, int AKIND, typename IO, typename F>
+__device__ __forceinline__ void for_each_decay(const BwdWave<N, IO>& w, float v, float scale, F f)
+{
+    if constexpr (AKIND == kAPerState) {
 #pragma unroll
-                for (int n = 0; n < N; n++) hs[i + 1][n] = fmaf(fast_exp2(delta[i] * c.a2[n]), hs[i][n], u * row[n]);
-            } else {
+        for (int n = 0; n < N; n++) f(n, scale * fast_exp2(v * w.a2[n]));
+    } else {
+        float an = scale * fast_exp2(v * w.a2[0]);
+        const float ratio = fast_exp2(v * w.d2);
 #pragma unroll
-                for (int n = 0; n < N; n++) hs[i + 1][n] = hs[i][n];
-            }
-            fwd_row += s_row;
-        }
-        // backward over the chunk, last token first
-#pragma unroll
-        for (int i = CT - 1; i >= 0; i--) {
-            // Half way through the walk the states of the chunk's later tokens are dead: their registers take the
-            // next chunk (whole: one scalar step per tensor and token), its entering state and the three x before it.
-            if (i == CT / 2 - 1 && k > 0) {
-                const char* nx = at_scan(wx, first - CT);
-                const char* nd = at_scan(wdt, first - CT);
-                const char* nz = at_scan(wz, first - CT);
-                const char* ng = at_scan(wg, first - CT);
-                if (k > 1) {
-#pragma unroll
-                    for (int e = 0; e < 3; e++) xprev[e] = *(const T*)(nx - (3 - e) * (long long)s_x + lo_t);
-                }
-#pragma unroll
-                for (int e = 0; e < CT; e++) {
-                    xnext[e] = *(const T*)(nx + lo_t);
-                    dnext[e] = *(const T*)(nd + lo_t);
-                    znext[e] = *(const T*)(nz + lo_t);
-                    gnext[e] = *(const T*)(ng + lo_t);
-                    nx += s_x; nd += s_dt; nz += s_z; ng += s_g;
-                }
-                request_state(k - 1);
-            }
-            if (i >= count) continue;
-            uniform_ro_ptr row = (uniform_ro_ptr)p_row;
-            const float zv = IO::cvt(zr[i]);
-            const float dg = valid ? IO::cvt(gr[i]) : 0.0f;          // shadow lanes add nothing to the sums below
-            float y = c.dval * xc[i];
-#pragma unroll
-            for (int n = 0; n < N; n++) y = fmaf(row[N + n], hs[i + 1][n], y);
-            const float dz = dg * y * dsilu(zv);
-            const float dy = dg * silu(zv);
-            gD = fmaf(dy, xc[i], gD);
-            const float u_over = delta[i] * xc[i];
-            float bc_terms[2 * N];                                   // this channel's terms of dB_t (first N) and dC_t
-            // sum_n dh[n] B[n] serves both dDelta (times xc) and dxc (times Delta); sum_n (dh h_prev a)[n] a2[n] is
-            // dDelta's decay part up to the factor ln 2 (A = a2 ln 2)
-            float dh_dot_b = 0.0f, decay_part = 0.0f;
-#pragma unroll
-            for (int n = 0; n < N; n++) {
-                const float an = fast_exp2(delta[i] * c.a2[n]);
-                dh[n] = fmaf(row[N + n], dy, dh[n]);
-                bc_terms[n] = dh[n] * u_over;
-                bc_terms[N + n] = dy * hs[i + 1][n];
-                const float da = dh[n] * hs[i][n] * an;              // dh * h_prev * a
-                gA[n] = fmaf(da, delta[i], gA[n]);
-                decay_part = fmaf(da, c.a2[n], decay_part);
-                dh_dot_b = fmaf(dh[n], row[n], dh_dot_b);
-                dh[n] *= an;
-            }
-            const float ddelta = fmaf(decay_part, kLn2, dh_dot_b * xc[i]);
-            const float dxc = fmaf(c.dval, dy, dh_dot_b * delta[i]);
-            {
-                // the wave's 64 channels summed: value j ends up in lanes j * kLanesPerValue ..., one of which stores it
-                const float total = wave_reduce_scatter<2 * N>(bc_terms, lane);
-                if (exists && lane % kLanesPerValue == 0) *(float*)(const_cast<char*>(p_part) + lo_part) = total;
-            }
-            float ddt = ddelta;
-            if (sp) {
-                ddt *= sigmoidf(IO::cvt(dr[i]) + c.dtb);
-                gbias += ddt;
-            }
-            const float dpre = dxc * dsilu(pre[i]);
-            gcb += dpre;
-            gw[3] = fmaf(dpre, xraw[i + 3], gw[3]);
-            gw[2] = fmaf(dpre, xraw[i + 2], gw[2]);
-            gw[1] = fmaf(dpre, xraw[i + 1], gw[1]);
-            gw[0] = fmaf(dpre, xraw[i], gw[0]);
-            const float dxv = fmaf(c.w4[3], dpre, fmaf(c.w4[2], dp1, fmaf(c.w4[1], dp2, c.w4[0] * dp3)));
-            dp3 = dp2; dp2 = dp1; dp1 = dpre;
-            const int j = first + i;
-            if (j >= jm) {                                // never taken unless a.park
-                if (valid) *(Parked*)(const_cast<char*>(p_pk) + lo_pk) = Parked{dxv, dz, ddt};
-                if (j == jm) meet();
-            } else {
-                const float px = q0[0], pz = q0[1], pd = q0[2];
-#pragma unroll
-                for (int e = 0; e < 3; e++) q0[e] = q1[e];
-                if (a.park && j >= 2) fetch_parked(q1, p_pk - 2 * (long long)s_pk);
-                if (valid) {
-                    IO::st((T*)(const_cast<char*>(p_odx) + lo_t), dxv + px);
-                    IO::st((T*)(const_cast<char*>(p_odz) + lo_t), dz + pz);
-                    IO::st((T*)(const_cast<char*>(p_oddt) + lo_t), ddt + pd);
-                }
-            }
-            p_odx -= s_odx; p_odz -= s_odz; p_oddt -= s_oddt;
-            p_pk -= s_pk; p_part -= s_part; p_row -= s_row;
-        }
-#pragma unroll
-        for (int i = 0; i < CT; i++) {
-            xr[i] = xnext[i];
-            dr[i] = dnext[i];
-            zr[i] = znext[i];
-            gr[i] = gnext[i];
+        for (int n = 0; n < N; n++) {
+            f(n, an);
+            if (n + 1 < N) an *= ratio;
         }
     }
-    if (valid) {
-        const int K = a.K;
+}
+template <int N, int AKIND, typename IO, typename F>
+__device__ __forceinline__ void for_each_decay(const BwdWave<N, IO>& w, float v, F f)
+{
+    for_each_decay<N, AKIND>(w, v, 1.0f, f);
+}
+
+// Two raw values of a token, kept in one register where the I/O dtype allows it.
+template <typename IO>
+struct RawPair {
+    float a, b;
+    __device__ __forceinline__ void set(float va, float vb) { a = va; b = vb; }
+    __device__ __forceinline__ float first() const { return a; }
+    __device__ __forceinline__ float second() const { return b; }
+    __device__ __forceinline__ void clear_first() { a = 0.0f; }
+    __device__ __forceinline__ void clear_second() { b = 0.0f; }
+    __device__ __forceinline__ void opaque() {}
+};
+template <>
+struct RawPair<IoBF16> {
+    unsigned v;
+    __device__ __forceinline__ void set(unsigned short va, unsigned short vb) { v = (unsigned)va | ((unsigned)vb << 16); opaque(); }
+    __device__ __forceinline__ float first() const { return __uint_as_float(v << 16); }
+    __device__ __forceinline__ float second() const { return __uint_as_float(v & 0xffff0000u); }
+    __device__ __forceinline__ void clear_first() { v &= 0xffff0000u; }
+    __device__ __forceinline__ void clear_second() { v &= 0xffffu; }
+    __device__ __forceinline__ void opaque() { asm volatile("" : "+v"(v)); }   // unpacked where used, not kept unpacked
+};
+
+// Has a value computed where it stands.  Left alone the compiler moves sums that are used much later (and what only a
+// conditional store needs) down the token's blocks and keeps their operands alive instead: more registers than there are.
+__device__ __forceinline__ void settle(float& v) { asm volatile("" : "+v"(v)); }
+
+template <int N>
+__device__ __forceinline__ void store_block(float* dst, const float (&v)[N], int lane)
+{
 #pragma unroll
-        for (int n = 0; n < N; n++) unsafeAtomicAdd(a.dA[s] + (size_t)ch * N + n, gA[n]);
-        unsafeAtomicAdd(a.dD[s] + ch, gD);
+    for (int q = 0; q < N / 4; q++)
+        *reinterpret_cast<float4*>(dst + (q * 64 + lane) * 4) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+}
+template <int N>
+__device__ __forceinline__ void load_block(const float* src, float (&v)[N], int lane)
+{
 #pragma unroll
-        for (int i = 0; i < 4; i++)
-            if (i < K) unsafeAtomicAdd(a.dconv_w[s] + (size_t)ch * K + (K - 1 - i), gw[3 - i]);
-        if (a.dconv_b[s]) unsafeAtomicAdd(a.dconv_b[s] + ch, gcb);
-        if (a.ddt_bias[s] && sp) unsafeAtomicAdd(a.ddt_bias[s] + ch, gbias);
+    for (int q = 0; q < N / 4; q++) {
+        const float4 t = *reinterpret_cast<const float4*>(src + (q * 64 + lane) * 4);
+        v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
     }
 }
 
-// dB and dC from the per-wave partial sums: one thread per (batch, token, group, value) adds its slots in a fixed order.
-struct BwdBcArgs {
-    const float* part;   // [batch][L][G][slots][2N]
-    float* dB;           // [batch][L][G][N]
-    float* dC;
-    long long rows;      // batch * L * G
-    int slots, N;
+// The walk of bwd_state_kernel.  WITH_D: the dh sum is wanted (some segment precedes this one in scan order).
+template <int N, typename IO, int AKIND, bool WITH_D>
+__device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N, IO>& w)
+{
+    using T = typename IO::T;
+    constexpr int CT = kBwdChunk;
+    const bool sp = a.dt_softplus != 0;
+    const bool end_wanted = w.j1 < a.L;                   // some segment follows in scan order
+    unsigned lo = (unsigned)(w.ch * sizeof(T));
+    float h[N], ds[WITH_D ? N : 1];
+#pragma unroll
+    for (int n = 0; n < N; n++) h[n] = 0.0f;
+    if constexpr (WITH_D) {
+#pragma unroll
+        for (int n = 0; n < N; n++) ds[n] = 0.0f;
+    }
+    float wsum = 0.0f, dsum = 0.0f;
+    float xh[3];                                          // raw x one, two, three tokens back in scan order
+#pragma unroll
+    for (int e = 0; e < 3; e++) xh[e] = w.j0 - 1 - e >= 0 ? IO::cvt(*(const T*)(w.at(w.x, max(w.j0 - 1 - e, 0)) + lo)) : 0.0f;
+    // The next chunk's activations are requested before the current chunk is worked through (positions outside the
+    // sequence repeat its nearest token).
+    auto inside = [&](int j) { return min(max(j, 0), a.L - 1); };
+    T xn[CT], dn[CT], zn[WITH_D ? CT : 1], gn[WITH_D ? CT : 1];
+    const int sx = w.step(w.x), sd = w.step(w.dt), sz = w.step(w.z), sg = w.step(w.g);
+    auto request = [&](int k) {
+        const int first = w.j0 + k * CT;
+        keep_narrow(lo);
+        const char *px = w.at(w.x, inside(first)), *pd = w.at(w.dt, inside(first)), *pz = w.at(w.z, inside(first)), *pg = w.at(w.g, inside(first));
+#pragma unroll
+        for (int i = 0; i < CT; i++) {
+            xn[i] = *(const T*)(px + lo);
+            dn[i] = *(const T*)(pd + lo);
+            const bool m = first + i >= 0 && first + i + 1 < a.L;
+            px += m ? sx : 0; pd += m ? sd : 0;
+            if constexpr (WITH_D) {
+                zn[i] = *(const T*)(pz + lo);
+                gn[i] = *(const T*)(pg + lo);
+                pz += m ? sz : 0; pg += m ? sg : 0;
+            }
+        }
+    };
+    auto add_to_d = [&](float delta, float z, float dg, uniform_ro_ptr row) {
+        dsum += delta;
+        for_each_decay<N, AKIND>(w, dsum, dg * silu(z), [&](int n, float c) { ds[WITH_D ? n : 0] = fmaf(c, row[N + n], ds[WITH_D ? n : 0]); });
+    };
+    request(w.k0);
+    float* dst = a.state + w.place(a, a.seg_chunks, w.k0) * (64 * N);
+    float* dst_w = a.state_w + w.place(a, a.seg_chunks, w.k0) * 64 + w.lane;
+    for (int k = w.k0; k < w.k1; k++) {
+        const int first = w.j0 + k * CT;
+        if (w.exists) {
+            store_block<N>(dst, h, w.lane);
+            *dst_w = wsum;
+        }
+        dst += (size_t)a.tiles * 64 * N;
+        dst_w += (size_t)a.tiles * 64;
+        if (k == w.k1 - 1 && !end_wanted && !WITH_D) return;    // what is left feeds nothing
+        float x[CT], delta[CT];
+        RawPair<IO> zg[WITH_D ? CT : 1];
+#pragma unroll
+        for (int i = 0; i < CT; i++) {
+            x[i] = IO::cvt(xn[i]);
+            delta[i] = IO::cvt(dn[i]);
+            if constexpr (WITH_D) zg[i].set(zn[i], w.valid ? gn[i] : T(0));
+        }
+        request(min(k + 1, w.k1 - 1));
+        if (sp) {
+#pragma unroll
+            for (int i = 0; i < CT; i++) delta[i] = softplus(delta[i] + w.dtb);
+        }
+        if (first < 0 || first + CT > a.L) {              // tokens that do not exist change nothing
+#pragma unroll
+            for (int i = 0; i < CT; i++) {
+                if (first + i < 0 || first + i >= a.L) {
+                    x[i] = delta[i] = 0.0f;
+                    if constexpr (WITH_D) zg[i].clear_second();
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < CT; i++) {
+            const float pre = fmaf(w.w4[0], xh[2], fmaf(w.w4[1], xh[1], fmaf(w.w4[2], xh[0], fmaf(w.w4[3], x[i], w.cb))));
+            xh[2] = xh[1]; xh[1] = xh[0]; xh[0] = x[i];
+            wsum += delta[i];
+            const float u = delta[i] * silu(pre);
+            uniform_ro_ptr row = (uniform_ro_ptr)w.at(w.row, inside(first + i));
+            for_each_decay<N, AKIND>(w, delta[i], [&](int n, float an) { h[n] = fmaf(an, h[n], u * row[n]); });
+            if constexpr (WITH_D) {
+                const bool in_window = i >= 3 || k > 0;   // (a segment that something precedes starts inside the sequence: k0 = 0)
+                add_to_d(in_window ? delta[i] : 0.0f, zg[i].first(), in_window ? zg[i].second() : 0.0f, row);
+            }
+        }
+    }
+    if constexpr (WITH_D) {
+        // the window reaches three tokens into the segments that follow
+        for (int j = max(w.j1, w.j0 + 3); j < min(w.j1 + 3, a.L); j++) {
+            float delta = IO::cvt(*(const T*)(w.at(w.dt, j) + lo));
+            if (sp) delta = softplus(delta + w.dtb);
+            const float dg = w.valid ? IO::cvt(*(const T*)(w.at(w.g, j) + lo)) : 0.0f;
+            add_to_d(delta, IO::cvt(*(const T*)(w.at(w.z, j) + lo)), dg, (uniform_ro_ptr)w.at(w.row, j));
+        }
+    }
+    if (w.exists) {
+        store_block<N>(a.seg_h + w.place(a, 1, 0) * (64 * N), h, w.lane);
+        a.seg_w[w.place(a, 1, 0) * 64 + w.lane] = wsum;
+        if constexpr (WITH_D) {
+            const size_t half = (size_t)2 * gridDim.z * a.nseg * a.tiles * 64;
+            store_block<N>(a.seg_d + w.place(a, 1, 0) * (64 * N), ds, w.lane);
+            a.seg_w[half + w.place(a, 1, 0) * 64 + w.lane] = dsum;
+        }
+    }
+}
+
+// grid (ceil(tiles / 2), nseg, batch), block 256: waves 0 / 1 the forward / reverse chains of one channel tile, waves
+// 2 / 3 those of the next.
+template <int N, typename IO>
+__global__ __launch_bounds__(256, 4) void bwd_state_kernel(const BwdArgs a)
+{
+    BwdWave<N, IO> w;
+    bwd_wave_setup<N, IO>(a, w);
+    if (!w.exists) return;
+    const bool with_d = w.j0 > 0;
+    if (bwd_progression<N, IO>(a, w)) {
+        if constexpr (kProgressionEligible<N, IO>) {
+            if (with_d) bwd_state_walk<N, IO, kAProgression, true>(a, w);
+            else bwd_state_walk<N, IO, kAProgression, false>(a, w);
+        }
+        return;
+    }
+    if (with_d) bwd_state_walk<N, IO, kAPerState, true>(a, w);
+    else bwd_state_walk<N, IO, kAPerState, false>(a, w);
+}
+
+// One thread per (direction, batch, tile, N / 4, lane, 4): the state entering each segment in scan order, and against
+// it the dh of the tokens after each segment's window:
+//   h_next = exp(A sum Delta) h + S,   D_before = exp(A sum Delta over the window) D + S_d.
+template <int N>
+__global__ __launch_bounds__(256) void bwd_carry_kernel(const BwdArgs a, int batch)
+{
+    constexpr int kAhead = 8;
+    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    const long long per_seg = (long long)a.tiles * 64 * N;
+    if (idx >= 2 * batch * per_seg) return;
+    const long long e = idx % per_seg;                    // element of one segment's blocks
+    const int b = (int)(idx / per_seg % batch), s = (int)(idx / per_seg / batch);
+    const int lane = (int)(e / 4 % 64), tile = (int)(e / (64 * N));
+    const int n = (int)(e / 256 % (N / 4)) * 4 + (int)(e % 4);
+    const float a2 = a.dir[s].A[(size_t)min(tile * 64 + lane, a.Dn - 1) * N + n] * kLog2e;
+    const size_t seg0 = ((size_t)s * batch + b) * a.nseg;
+    const size_t half = (size_t)2 * batch * a.nseg * a.tiles * 64;
+    auto seg_of = [&](int i) { return s == 0 ? i : a.nseg - 1 - i; };   // i: scan order
+    float h = 0.0f;
+    for (int i0 = 0; i0 < a.nseg; i0 += kAhead) {
+        float end[kAhead], sw[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; j++) {
+            const size_t at = seg0 + seg_of(min(i0 + j, max(a.nseg - 2, 0)));      // nothing needs the last segment's end
+            end[j] = a.seg_h[at * per_seg + e];
+            sw[j] = a.seg_w[(at * a.tiles + tile) * 64 + lane];
+        }
+#pragma unroll
+        for (int j = 0; j < kAhead; j++) {
+            if (i0 + j < a.nseg) {
+                a.seg_h[(seg0 + seg_of(i0 + j)) * per_seg + e] = h;
+                h = fmaf(fast_exp2(sw[j] * a2), h, end[j]);
+            }
+        }
+    }
+    float d = 0.0f;
+    for (int i0 = a.nseg - 1; i0 >= 0; i0 -= kAhead) {
+        float sum[kAhead], sw[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; j++) {
+            const size_t at = seg0 + seg_of(max(i0 - j, min(1, a.nseg - 1)));      // nothing needs the first segment's sum
+            sum[j] = a.seg_d[at * per_seg + e];
+            sw[j] = a.seg_w[half + (at * a.tiles + tile) * 64 + lane];
+        }
+#pragma unroll
+        for (int j = 0; j < kAhead; j++) {
+            if (i0 - j >= 0) {
+                a.seg_d[(seg0 + seg_of(i0 - j)) * per_seg + e] = d;
+                d = fmaf(fast_exp2(sw[j] * a2), d, sum[j]);
+            }
+        }
+    }
+}
+
+// What becomes of a chunk's dx, dz and dDelta: parked for the other direction, added to what it parked, or stored alone.
+enum { kBwdPark = 0, kBwdAdd = 1, kBwdAlone = 2 };
+
+// One wave's walk over its segment.  Every chunk has kBwdChunk tokens: where the sequence ends inside the last segment's
+// tokens, the missing ones are walked as tokens with Delta = 0 and dout = 0, which change nothing and are not stored.
+template <int N, typename IO, int AKIND>
+struct BwdWalk {
+    using T = typename IO::T;
+    using Wave = BwdWave<N, IO>;
+    using Walked = typename Wave::Walked;
+    static constexpr int CT = kBwdChunk, LT = kBwdLdsTokens<N>;
+    static constexpr int kLanesPerState = 64 / N;
+
+    const BwdArgs& a;
+    const Wave& w;
+    float* const lds;
+    bool sp;
+    unsigned lo_t, lo_pk, lo_part;                       // the lane's byte offset into a row: I/O dtype, parked records, partial sums
+    Walked odx, odz, oddt, pk, part;
+    float dh[N], gA[N];
+    float gD, gcb, gbias, gw[4];
+    float dp1, dp2, dp3;                                 // dpre of the tokens one, two, three steps later in scan order
+    float q[2][3];                                       // what the other direction parked for the next two tokens
+    // the next chunk to be walked, requested half a chunk early
+    T xnext[CT], dnext[CT], znext[CT], gnext[CT];
+    T xbefore[3];                                        // raw x of the three tokens before it
+    float hnext[N], wnext;                               // the state entering it (from zero at the segment's start), and the Delta up to there
+
+    __device__ __forceinline__ BwdWalk(const BwdArgs& a_, const Wave& w_, float* lds_) : a(a_), w(w_), lds(lds_) {}
+
+    __device__ __forceinline__ bool carried() const { return w.j0 > 0; }   // the segment starts from a state of its own
+    __device__ __forceinline__ float delta_of(float raw) const { return sp ? softplus(raw + w.dtb) : raw; }
+    __device__ __forceinline__ int inside(int j) const { return min(max(j, 0), a.L - 1); }
+    __device__ __forceinline__ bool exists(int j) const { return j >= 0 && j < a.L; }
+    __device__ __forceinline__ bool moves(int j) const { return j >= 0 && j + 1 < a.L; }   // inside(j + 1) != inside(j)
+
+    __device__ __forceinline__ void request(int k)
+    {
+        // (positions outside the sequence repeat its nearest token: one stepped pointer per tensor, no second form of the
+        // loads, whose addresses the compiler would merge in vector registers)
+        const int first = w.j0 + k * CT;
+        keep_narrow(lo_t);
+        const int sx = w.step(w.x), sd = w.step(w.dt), sz = w.step(w.z), sg = w.step(w.g);
+        const char *px = w.at(w.x, inside(first - 3)), *pd = w.at(w.dt, inside(first)), *pz = w.at(w.z, inside(first)),
+                   *pg = w.at(w.g, inside(first));
+#pragma unroll
+        for (int e = 0; e < 3; e++) {
+            xbefore[e] = *(const T*)(px + lo_t);
+            px += moves(first - 3 + e) ? sx : 0;
+        }
+#pragma unroll
+        for (int i = 0; i < CT; i++) {
+            xnext[i] = *(const T*)(px + lo_t);
+            dnext[i] = *(const T*)(pd + lo_t);
+            znext[i] = *(const T*)(pz + lo_t);
+            gnext[i] = *(const T*)(pg + lo_t);
+            const bool m = moves(first + i);
+            px += m ? sx : 0; pd += m ? sd : 0; pz += m ? sz : 0; pg += m ? sg : 0;
+        }
+        load_block<N>(a.state + w.place(a, a.seg_chunks, k) * (64 * N), hnext, w.lane);
+        wnext = a.state_w[w.place(a, a.seg_chunks, k) * 64 + w.lane];
+    }
+
+    __device__ __forceinline__ void fetch_parked(float (&v)[3], const char* row)
+    {
+        const Parked r = *(const Parked*)(row + lo_pk);
+        v[0] = r.dx; v[1] = r.dz; v[2] = r.ddt;
+    }
+
+    // dh of the tokens after the segment's window, then the (up to) three tokens between the segment's end and there, for
+    // their dpre
+    __device__ __forceinline__ void start_from_next_segment()
+    {
+        load_block<N>(a.seg_d + w.place(a, 1, 0) * (64 * N), dh, w.lane);
+        T xe[6], de[3], ze[3], ge[3];
+#pragma unroll
+        for (int e = 0; e < 6; e++) xe[e] = *(const T*)(w.at(w.x, inside(w.j1 - 3 + e)) + lo_t);
+#pragma unroll
+        for (int e = 0; e < 3; e++) {
+            const int j = inside(w.j1 + e);
+            de[e] = *(const T*)(w.at(w.dt, j) + lo_t);
+            ze[e] = *(const T*)(w.at(w.z, j) + lo_t);
+            ge[e] = *(const T*)(w.at(w.g, j) + lo_t);
+        }
+#pragma unroll
+        for (int e = 2; e >= 0; e--) {
+            if (w.j1 + e < a.L) {
+                uniform_ro_ptr row = (uniform_ro_ptr)w.at(w.row, w.j1 + e);
+                float pre = w.cb;
+#pragma unroll
+                for (int i = 0; i < 4; i++)
+                    if (w.j1 + e - 3 + i >= 0) pre = fmaf(w.w4[i], IO::cvt(xe[e + i]), pre);
+                const float delta = delta_of(IO::cvt(de[e]));
+                const float dy = (w.valid ? IO::cvt(ge[e]) : 0.0f) * silu(IO::cvt(ze[e]));
+                float dh_dot_b = 0.0f;
+                for_each_decay<N, AKIND>(w, delta, [&](int n, float an) {
+                    dh[n] = fmaf(row[N + n], dy, dh[n]);
+                    dh_dot_b = fmaf(dh[n], row[n], dh_dot_b);
+                    dh[n] *= an;
+                });
+                dp3 = dp2; dp2 = dp1;
+                dp1 = fmaf(w.dval, dy, dh_dot_b * delta) * dsilu(pre);
+            }
+        }
+    }
+
+    template <int MODE>
+    __device__ __forceinline__ void chunk(int k)
+    {
+        const int first = w.j0 + k * CT;                            // scan position of the chunk's first token
+        // x and Delta, z and dout of the chunk's tokens; xd[0 .. 2]: x of the three tokens before it
+        RawPair<IO> xd[CT + 3], zg[CT];
+#pragma unroll
+        for (int e = 0; e < 3; e++) xd[e].set(xbefore[e], T(0));
+#pragma unroll
+        for (int i = 0; i < CT; i++) {
+            xd[i + 3].set(xnext[i], dnext[i]);
+            zg[i].set(znext[i], w.valid ? gnext[i] : T(0));         // (shadow lanes add nothing to the sums below)
+        }
+        const bool at_an_end = first < 3 || first + CT > a.L;
+        if (at_an_end) {
+#pragma unroll
+            for (int e = 0; e < CT + 3; e++)
+                if (!exists(first - 3 + e)) {
+                    xd[e].clear_first();
+                    if (e >= 3) zg[e >= 3 ? e - 3 : 0].clear_second();
+                }
+        }
+        // the state entering the chunk: the stored one plus what is left of the state entering the segment
+        float h[N];
+#pragma unroll
+        for (int n = 0; n < N; n++) h[n] = hnext[n];
+        if (carried()) {
+            float hseg[N];
+            load_block<N>(a.seg_h + w.place(a, 1, 0) * (64 * N), hseg, w.lane);
+            for_each_decay<N, AKIND>(w, wnext, [&](int n, float c) { h[n] = fmaf(c, hseg[n], h[n]); });
+        }
+        float delta[CT], xc[CT], sig[CT];   // Delta, conv + SiLU output, sigmoid of the conv output
+#pragma unroll
+        for (int i = 0; i < CT; i++) delta[i] = xd[i + 3].second();
+        if (sp) {
+#pragma unroll
+            for (int i = 0; i < CT; i++) delta[i] = softplus(delta[i] + w.dtb);
+        }
+        if (at_an_end) {
+#pragma unroll
+            for (int i = 0; i < CT; i++) delta[i] = exists(first + i) ? delta[i] : 0.0f;
+        }
+        // forward over the chunk, keeping every state: hs[i] enters token i; those of the first LT tokens wait in LDS
+        float hs[CT + 1][N];
+        {
+            float x1 = xd[2].first(), x2 = xd[1].first(), x3 = xd[0].first();
+#pragma unroll
+            for (int i = 0; i < CT; i++) {
+                if (i < LT) store_block<N>(lds + i * 64 * N, h, w.lane);
+                else {
+#pragma unroll
+                    for (int n = 0; n < N; n++) hs[i][n] = h[n];
+                }
+                const float x0 = xd[i + 3].first();
+                const float pre = fmaf(w.w4[0], x3, fmaf(w.w4[1], x2, fmaf(w.w4[2], x1, fmaf(w.w4[3], x0, w.cb))));
+                x3 = x2; x2 = x1; x1 = x0;
+                sig[i] = sigmoidf(pre);
+                xc[i] = pre * sig[i];
+                const float u = delta[i] * xc[i];
+                uniform_ro_ptr row = (uniform_ro_ptr)w.at(w.row, inside(first + i));
+                for_each_decay<N, AKIND>(w, delta[i], [&](int n, float an) { h[n] = fmaf(an, h[n], u * row[n]); });
+            }
+        }
+#pragma unroll
+        for (int n = 0; n < N; n++) hs[CT][n] = h[n];
+        // backward over the chunk, last token first; xw: x of the token at hand and the three before it
+        float xw[4];
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+            xd[CT - 1 + e].opaque();
+            xw[e] = xd[CT - 1 + e].first();
+        }
+#pragma unroll
+        for (int i = CT - 1; i >= 0; i--) {
+            const int j = first + i;
+            const bool there = exists(j);
+            // Half way through the walk the states of the chunk's later tokens are dead: their registers take the
+            // next chunk, its entering state and the three x before it.  (Also after the last chunk, when nothing uses it:
+            // under a condition the old values would stay live beside the states.)
+            if (i == CT / 2 - 1) request(max(k - 1, w.k0));
+            if (i < LT) load_block<N>(lds + i * 64 * N, hs[i], w.lane);
+            uniform_ro_ptr row = (uniform_ro_ptr)w.at(w.row, inside(j));
+            float y = w.dval * xc[i];
+#pragma unroll
+            for (int n = 0; n < N; n++) y = fmaf(row[N + n], hs[i + 1][n], y);
+            const float zv = zg[i].first(), dg = zg[i].second();
+            const float z_sig = sigmoidf(zv), z_silu = zv * z_sig;
+            float dzv = dg * y * fmaf(z_silu, 1.0f - z_sig, z_sig);
+            settle(dzv);
+            const float dy = dg * z_silu;
+            gD = fmaf(dy, xc[i], gD);
+            const float u = delta[i] * xc[i];
+            // this channel's terms of dC_t, summed over the wave's channels: value n in lanes n * kLanesPerState ...
+            float terms[N];
+#pragma unroll
+            for (int n = 0; n < N; n++) terms[n] = dy * hs[i + 1][n];
+            float dc_total = wave_reduce_scatter<N>(terms);
+            settle(dc_total);
+            // (formed again: kept from the forward half, a chunk's decays would take as many registers as its states)
+            float dlt = delta[i];
+            asm volatile("" : "+v"(dlt));
+            // sum_n dh[n] B[n] serves both dDelta (times xc) and dxc (times Delta); sum_n (dh h_prev a)[n] a2[n] is
+            // dDelta's decay part up to the factor ln 2 (A = a2 ln 2)
+            float dh_dot_b = 0.0f, decay_part = 0.0f;
+            for_each_decay<N, AKIND>(w, dlt, [&](int n, float an) {
+                dh[n] = fmaf(row[N + n], dy, dh[n]);
+                terms[n] = dh[n] * u;                                // of dB_t
+                dh_dot_b = fmaf(dh[n], row[n], dh_dot_b);
+                dh[n] *= an;
+                const float da = dh[n] * hs[i][n];                   // dh * a * h_prev
+                gA[n] = fmaf(da, dlt, gA[n]);
+                decay_part = fmaf(da, w.a2[n], decay_part);
+            });
+#pragma unroll
+            for (int n = 0; n < N; n++) {
+                settle(gA[n]);
+                settle(dh[n]);
+            }
+            float ddt = fmaf(decay_part, kLn2, dh_dot_b * xc[i]);
+            float dxc = fmaf(w.dval, dy, dh_dot_b * dlt);
+            settle(ddt);
+            settle(dxc);
+            settle(gD);
+            {
+                // the two totals of a state side by side: the first half of its lanes has dB_t[n], the second dC_t[n]
+                const float db_total = wave_reduce_scatter<N>(terms);
+                const bool second = (w.lane & (kLanesPerState / 2)) != 0;
+                keep_narrow(lo_part);
+                if (there && w.exists && w.lane % (kLanesPerState / 2) == 0)
+                    *(float*)(const_cast<char*>(w.at(part, j)) + lo_part) = second ? dc_total : db_total;
+            }
+            if (sp) {
+                ddt *= sigmoidf(xd[i + 3].second() + w.dtb);
+                gbias += there ? ddt : 0.0f;
+            }
+            const float dpre = dxc * fmaf(xc[i], 1.0f - sig[i], sig[i]);
+            gcb += dpre;
+#pragma unroll
+            for (int e = 0; e < 4; e++) gw[e] = fmaf(dpre, xw[e], gw[e]);
+            float dxv = fmaf(w.w4[3], dpre, fmaf(w.w4[2], dp1, fmaf(w.w4[1], dp2, w.w4[0] * dp3)));
+            settle(dxv);
+            settle(gcb);
+#pragma unroll
+            for (int e = 0; e < 4; e++) settle(gw[e]);
+            dp3 = dp2; dp2 = dp1; dp1 = dpre;
+            xw[3] = xw[2]; xw[2] = xw[1]; xw[1] = xw[0];
+            if (i > 0) {
+                xd[i - 1].opaque();
+                xw[0] = xd[i - 1].first();
+            }
+            if constexpr (MODE == kBwdAdd) {
+                dxv += q[i & 1][0]; dzv += q[i & 1][1]; ddt += q[i & 1][2];
+                fetch_parked(q[i & 1], w.at(pk, j - 2));            // (the buffer has rows to spare on both sides)
+            }
+            keep_narrow(lo_t);
+            keep_narrow(lo_pk);
+            if (there && w.valid) {
+                if constexpr (MODE == kBwdPark) {
+                    *(Parked*)(const_cast<char*>(w.at(pk, j)) + lo_pk) = Parked{dxv, dzv, ddt};
+                } else {
+                    IO::st((T*)(const_cast<char*>(w.at(odx, j)) + lo_t), dxv);
+                    IO::st((T*)(const_cast<char*>(w.at(odz, j)) + lo_t), dzv);
+                    IO::st((T*)(const_cast<char*>(w.at(oddt, j)) + lo_t), ddt);
+                }
+            }
+            // (convergent: keeps the compiler from copying the loop's exit test into both sides of the branch above, which
+            // would make the loop counter, and with it every row address, a per-lane value)
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+
+    template <int MODE>
+    __device__ __forceinline__ void chunks(int from, int to)   // from, from - 1 ... to
+    {
+        for (int k = from; k >= to; k--) chunk<MODE>(k);
+    }
+
+    __device__ __forceinline__ void run()
+    {
+        sp = a.dt_softplus != 0;
+        lo_t = (unsigned)(w.ch * sizeof(T));
+        lo_pk = (unsigned)(w.ch * sizeof(Parked));
+        lo_part = (unsigned)((w.lane / (kLanesPerState / 2)) * sizeof(float));
+        auto view = [&](const TensorArg& t) {
+            return Walked{(const char*)t.p + (size_t)w.b * t.sb * sizeof(T), (int)(t.st * (long long)sizeof(T))};
+        };
+        odx = view(a.gdx[w.s]);
+        odz = view(a.gdz[w.s]);
+        oddt = view(a.gddt[w.s]);
+        pk = Walked{(const char*)(a.parked + (size_t)w.b * a.L * a.Dn), a.Dn * (int)sizeof(Parked)};
+        // this wave's slot of the dB and dC partial sums: [batch][L][G][slots][N][2]
+        const int tiles_per_group = (a.Dn / a.G + 63) / 64;
+        const int slot = __builtin_amdgcn_readfirstlane(w.tile % tiles_per_group) + (w.s == 1 ? a.bc_slot_of_rev : 0);
+        part = Walked{(const char*)(a.bc_part[w.s] + (((size_t)w.b * a.L * a.G + w.grp) * a.bc_slots + slot) * (2 * N)),
+                      a.G * a.bc_slots * 2 * N * (int)sizeof(float)};
+#pragma unroll
+        for (int n = 0; n < N; n++) dh[n] = gA[n] = 0.0f;
+        gD = gcb = gbias = dp1 = dp2 = dp3 = 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; e++) gw[e] = 0.0f;
+        if (w.j1 < a.L) start_from_next_segment();
+        if (!a.park) {
+            request(w.k1 - 1);
+            chunks<kBwdAlone>(w.k1 - 1, w.k0);
+        } else {
+            // The two waves of a tile walk the segment's tokens in opposite orders.  The forward direction's wave parks the
+            // later half, the reverse one's the earlier half; the barrier is a workgroup-scope release / acquire: past it,
+            // what the other wave parked is visible.  It is fetched two tokens ahead.
+            const int to = w.s == 0 ? a.seg_chunks / 2 : a.seg_chunks - a.seg_chunks / 2;
+            request(w.k1 - 1);
+            chunks<kBwdPark>(w.k1 - 1, max(to, w.k0));
+            __syncthreads();
+            const int from = min(to, w.k1) - 1, j = w.j0 + from * CT + CT - 1;
+            if (from >= w.k0) {
+                fetch_parked(q[1], w.at(pk, j));
+                fetch_parked(q[0], w.at(pk, j - 1));
+            }
+            chunks<kBwdAdd>(from, w.k0);
+        }
+        if (w.exists) {
+            // this segment's share of the parameter gradients: rows dA[0..N), dD, dconv_w[4] (w[3] on the current token), dconv_b, ddt_bias
+            const size_t pitch = (size_t)a.tiles * 64;
+            float* dst = a.param_part + ((((size_t)w.s * gridDim.z + w.b) * a.nseg + w.seg) * (N + kBwdParams)) * pitch + w.tile * 64 + w.lane;
+#pragma unroll
+            for (int n = 0; n < N; n++) dst[n * pitch] = gA[n];
+            dst[N * pitch] = gD;
+#pragma unroll
+            for (int i = 0; i < 4; i++) dst[(N + 1 + i) * pitch] = gw[i];
+            dst[(N + 5) * pitch] = gcb;
+            dst[(N + 6) * pitch] = gbias;
+        }
+    }
 };
 
-__global__ __launch_bounds__(256) void bwd_bc_kernel(const BwdBcArgs a);
+template <int N, typename IO>
+__global__ __launch_bounds__(256, 2) void bwd_kernel(const BwdArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) float lds_all[];   // kBwdLdsBytes<N>
+    BwdWave<N, IO> w;
+    bwd_wave_setup<N, IO>(a, w);
+    // (a wave without a tile of its own still runs, as a shadow of its neighbour: the meeting barrier counts four waves)
+    float* lds = lds_all + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) * (kBwdLdsTokens<N> * 64 * N);
+    if (bwd_progression<N, IO>(a, w)) {
+        if constexpr (kProgressionEligible<N, IO>) BwdWalk<N, IO, kAProgression>(a, w, lds).run();
+        return;
+    }
+    BwdWalk<N, IO, kAPerState>(a, w, lds).run();
+}
+
+// Prepared fp32 B | C rows of one or two sets of activations (prep_bc_kernel without the conv), both in one launch.
+struct BwdPrepArgs {
+    TensorArg B[2], C[2];
+    float* dst[2];       // [batch][L][G][2N]
+    int L, G, N;
+    long long per_set;   // batch * L * G * 2N
+};
+
+// What the walk left in slots, added in a fixed order: dB and dC from the per-wave partial sums (one thread per (batch,
+// token, group, value)), then the parameter gradients from the per-segment ones.
+struct BwdSumArgs {
+    const float* part[2];   // per set of activations: [batch][L][G][slots][N][2]
+    float* dB[2];           // [batch][L][G][N]
+    float* dC[2];
+    int sets, slots, N;
+    long long rows;         // batch * L * G
+    const float* param_part;   // [2][segs][N + 7][pitch]
+    long long pitch;
+    int segs;               // batch * nseg (0: the gradients are zero)
+    float* dA[2];
+    float* dD[2];
+    float* dconv_w[2];
+    float* dconv_b[2];      // or null
+    float* ddt_bias[2];     // or null
+    int Dn, K;
+};
 
 }  // namespace bm

@@ -37,11 +37,11 @@ void launch_ssd_duo(int d_state, int headdim, const SsdStatePair& sp, int batch,
 void launch_ssd_state(int d_state, int headdim, const SsdStatePair& sp, int subs, int batch, hipStream_t st);
 
 struct BwdArgs;
-struct BwdBcArgs;
-void launch_bwd_bc(const BwdBcArgs& a, hipStream_t st);
+struct BwdPrepArgs;
+struct BwdSumArgs;
 bool bwd_supported(int d_state);
-int bwd_chunk_tokens(int d_state, bool dense);
-bool bwd_dense(int d_inner, int batch);
-void launch_bwd(int d_state, int io_bf16, bool dense, const BwdArgs& a, int batch, hipStream_t st);
-void launch_bwd_zero(float* p, long long n, hipStream_t st);
+void bwd_segments(int d_inner, int batch, int seqlen, int* nseg, int* seg_len, int* seg_chunks);
+void launch_bwd_prep(int io_bf16, const BwdPrepArgs& a, int sets, hipStream_t st);
+void launch_bwd(int d_state, int io_bf16, const BwdArgs& a, int batch, hipStream_t st);
+void launch_bwd_sum(const BwdSumArgs& a, hipStream_t st);
 }  // namespace bm

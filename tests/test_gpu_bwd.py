@@ -228,6 +228,16 @@ def test_column_slices_with_their_own_token_strides(gpu, oracle, untied):
             assert float(wide[..., lo:hi].abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("untied", [False, True])
+@pytest.mark.parametrize("L", [31, 63, 64, 65, 66, 67, 71, 127, 129, 130, 131, 193, 259, 517])
+def test_lengths_around_the_time_segments(gpu, oracle, L, untied):
+    """A small call is cut into time segments of whole chunks, 32 tokens or more: lengths at which the last segment is
+    empty but for one to three tokens (the conv window and the dh window reach past it), odd chunk counts on either side
+    of the meeting point, both decay forms, every conv width."""
+    cfg = synth.mixer_cfg(2, L, 72, d_state=(16, 8, 4)[L % 3], d_conv=1 + L % 4, io="bf16", dt_softplus=L % 2)
+    run_case(gpu, oracle, cfg, 40 + L, untied=untied, random_a=bool(L & 2))
+
+
 @pytest.mark.parametrize("N", [4, 8, 16])
 @pytest.mark.parametrize("L", [1, 5, 37, 70])
 def test_more_waves_than_simds_takes_the_dense_form(gpu, oracle, N, L):
