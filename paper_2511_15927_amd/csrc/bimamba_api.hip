@@ -3,6 +3,7 @@
 #include "kernels.h"
 #include "launch.h"
 #include "bwd_kernels.h"
+#include "row_kernels.h"
 #include "ssd_kernels.h"
 
 #include <hip/hip_runtime.h>
@@ -430,6 +431,37 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
     char* ws = static_cast<char*>(workspace);
 
     if (d->batch > 0 && d->seqlen > 0) {
+        RowForm row;
+        const bool whole_call = !plan.ssd && !d->conv_bc && d->time_chunks == 0 && d->state_split == 0 &&
+                                row_form(d->batch, d->seqlen, d->d_inner, d->d_state, &row);
+        if (whole_call) {
+            // a short call with few chains: everything in one launch, the commit of the conv tail included
+            RowArgs ra{};
+            for (int s = 0; s < 2; s++) {
+                const bimamba_inputs* in = s == 0 ? in_f : in_b;
+                const bimamba_params* p = s == 0 ? pf : pb;
+                DirArgs& da = ra.dir[s];
+                da.x = targ(in->x); da.z = targ(in->z); da.dt = targ(in->dt);
+                da.Braw = targ(in->B); da.Craw = targ(in->C);
+                da.conv_w = p->conv_w; da.conv_b = p->conv_b; da.A = p->A; da.D = p->D; da.dt_bias = p->dt_bias;
+            }
+            ra.out = out->ptr; ra.out_sb = out->stride_batch; ra.out_st = out->stride_token;
+            if (block_variant) {
+                ra.h_in = h_in; ra.h_out = h_out;
+                ra.tail_in = tail_in; ra.tail_out = d->d_conv > 1 ? tail_out : nullptr;
+                tail_out = nullptr;
+            }
+            ra.L = d->seqlen; ra.Dn = d->d_inner; ra.P = d->d_inner / d->n_heads; ra.HG = d->n_heads / d->n_groups;
+            ra.G = d->n_groups; ra.N = d->d_state; ra.K = d->d_conv;
+            ra.dt_softplus = d->dt_softplus; ra.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD;
+            ra.a_scalar = d->a_kind == BIMAMBA_A_SCALAR_PER_HEAD; ra.separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
+            ra.same_z = same_tensor(in_f->z, in_b->z);
+            ra.same_bc = same_tensor(in_f->B, in_b->B) && same_tensor(in_f->C, in_b->C);
+            ra.tw = row.tw; ra.tw_log2 = row.tw == 4 ? 2 : row.tw == 2 ? 1 : 0; ra.nseg = row.nseg; ra.seg_len = row.seg_len;
+            if (probe_start) (void)hipEventRecord(probe_start, st);
+            launch_row(d->io_dtype == BIMAMBA_BF16, ra, d->batch, st);
+            if (probe_stop) (void)hipEventRecord(probe_stop, st);
+        } else {
         // 1. fp32 B|C rows per direction (the chunked path prepares its own operand tiles from the raw rows)
         const bool one_launch = short_call(d, plan);
         const int nbuf = (plan.ssd || one_launch) ? 0 : plan.two_bc ? 2 : 1;
@@ -557,6 +589,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
         ca.h_in = sa.h_in; ca.h_out = sa.h_out;
         ca.batch = d->batch; ca.nseg = plan.nseg; ca.Dn = d->d_inner; ca.P = sa.P;
         launch_scan(d, plan.split, one_launch, sa, ca, st, probe_start, probe_stop);
+        }
         }
     } else if (block_variant && d->batch > 0 && h_out && h_out != h_in) {
         // empty block: the state passes through unchanged

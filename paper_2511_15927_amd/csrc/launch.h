@@ -25,6 +25,14 @@ BM_DECLARE_SCAN(128, 1)
 BM_DECLARE_SCAN(128, 4)
 #undef BM_DECLARE_SCAN
 
+// The one-row-per-chain form of short calls (row_kernels.h): whether a call takes it, and its shape.
+struct RowForm {
+    int tw, nseg, seg_len;
+};
+struct RowArgs;
+bool row_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f);
+void launch_row(int io_bf16, const RowArgs& a, int batch, hipStream_t st);
+
 struct SsdPrepPair;
 struct SsdArgs;
 struct SsdCarryArgs;

@@ -1,0 +1,60 @@
+// Choice and launch of the one-row-per-chain form (row_kernels.h).
+#include "row_kernels.h"
+#include "launch.h"
+
+#include <atomic>
+
+namespace bm {
+
+// The row form spends about twice the vector work of the sweep on a chain and token and wins where the sweep's two to four
+// launches and its 100 instructions per dependent token are what a call waits for.  Measured against them (bf16,
+// d_inner 4096 unless stated, us, sweep / row): 1 x 32 tokens 14.1 / 6.8, 4 x 32 14.9 / 13.7, 8 x 32 17.7 / 24.1; 2 x 64
+// 18.8 / 12.5, 4 x 64 19.6 / 21.2; 1 x 128 26.6 / 16.9, 2 x 128 27.4 / 27.5; 1 x 256 49.6 / 38.2, d_inner 512 48.6 / 11.6.
+constexpr long long kRowMaxChains = 16384, kRowMaxElements = 3LL << 18, kRowMaxElementsLong = 1LL << 20;
+constexpr int kRowLongTokens = 128;
+constexpr size_t kRowLdsBytes = 160 * 1024;
+
+bool row_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f)
+{
+    if (d_state > 16 || seqlen < 1 || seqlen > kRowMaxTokens) return false;
+    const long long chains = (long long)batch * d_inner;
+    if (chains > kRowMaxChains || chains * seqlen > (seqlen > kRowLongTokens ? kRowMaxElementsLong : kRowMaxElements)) return false;
+    const long long tiles = (long long)batch * ((d_inner + 3) / 4);
+    const int groups = (seqlen + kRowTokens - 1) / kRowTokens;
+    // Time segments of two groups or more while that leaves the chip at most four waves per SIMD (a segment walked twice
+    // costs 1.6 times the work); then as many channel tiles beside each other as keep every CU busy.
+    int nseg = 1;
+    while (nseg < kRowMaxWaves / 2 && groups >= 4 * nseg && tiles * 4 * nseg <= 16LL * cu_count()) nseg *= 2;
+    f->seg_len = (groups + nseg - 1) / nseg * kRowTokens;
+    f->nseg = (seqlen + f->seg_len - 1) / f->seg_len;
+    f->tw = 1;
+    auto fits = [&](int tw) { return RowLds(seqlen, 2, tw, f->nseg, f->seg_len).total * sizeof(float) <= kRowLdsBytes; };
+    while (f->tw < 4 && 2 * f->nseg * f->tw * 2 <= kRowMaxWaves && tiles >= 2LL * f->tw * cu_count() && fits(2 * f->tw)) f->tw *= 2;
+    return fits(f->tw);
+}
+
+static size_t lds_bytes(const RowArgs& a) { return (size_t)RowLds(a.L, a.same_bc ? 1 : 2, a.tw, a.nseg, a.seg_len).total * sizeof(float); }
+
+template <typename IO>
+static void launch_io(const RowArgs& a, int batch, hipStream_t st)
+{
+    constexpr int kMaxDevices = 64;
+    static std::atomic<bool> seen[kMaxDevices];
+    auto kernel = row_kernel<IO>;
+    const size_t lds = lds_bytes(a);
+    if (lds > 64 * 1024) {   // raising the limit is idempotent; done once per device
+        int dev = 0;
+        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices || !seen[dev].exchange(true))
+            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    }
+    const dim3 grid((unsigned)((a.Dn + 4 * a.tw - 1) / (4 * a.tw)), 1, (unsigned)batch);
+    hipLaunchKernelGGL(kernel, grid, dim3((unsigned)(128 * a.nseg * a.tw)), lds, st, a);
+}
+
+void launch_row(int io_bf16, const RowArgs& a, int batch, hipStream_t st)
+{
+    if (io_bf16) launch_io<IoBF16>(a, batch, st);
+    else launch_io<IoF32>(a, batch, st);
+}
+
+}  // namespace bm

@@ -1,0 +1,52 @@
+"""GPU parity of the one-launch form of short calls with few chains (a row of 16 lanes per chain): lengths around its groups
+of 16 tokens and its time segments, state counts below the row's width, ragged channel tiles, both entry points."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import assert_close, rel_l2, to_np
+from paper_2511_15927_amd import synth
+from test_gpu_block import params
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def gpu():
+    import gpu_util
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    return gpu_util
+
+
+@pytest.mark.parametrize("L", [1, 2, 15, 16, 17, 31, 33, 48, 64, 65, 100, 127, 129, 200, 255, 256])
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+def test_lengths(gpu, oracle, L, io):
+    """Full-sequence and block calls over both dtypes, every conv width, shared and separate activations."""
+    k = L % 4
+    cfg = synth.mixer_cfg(2, L, (72, 3, 130, 257)[k], d_state=(16, 8, 4, 16)[k], d_conv=1 + (L // 2) % 4, io=io,
+                          dt_softplus=L % 2, combine=(L // 3) % 2)
+    pf, pb = params(cfg, L, random_a=bool(L & 4))
+    inp = synth.make_inputs(cfg, L)
+    inp_b = synth.make_inputs(cfg, L + 500) if L % 3 == 0 else None
+    both = (to_np(pf), to_np(pb), to_np(inp), None if inp_b is None else to_np(inp_b))
+    assert_close(gpu.gpu_fwd(cfg, pf, pb, inp, inp_b), oracle.bimamba_fwd(cfg, *both), gpu.TOL[io])
+    g = torch.Generator().manual_seed(L)
+    h0 = (0.2 * torch.randn(2, cfg["d_inner"], cfg["d_state"], generator=g)).float()
+    K = cfg["d_conv"]
+    tail0 = synth.round_io(torch.randn(2, K - 1, cfg["d_inner"], generator=g), io) if K > 1 else None
+    ref, h_ref, t_ref = oracle.bimamba_block_fwd(cfg, *both, h_in=h0.numpy(), tail_in=None if tail0 is None else tail0.numpy())
+    got, h_got, t_got = gpu.gpu_block_fwd(cfg, pf, pb, inp, inp_b, h_in=h0, tail_in=tail0)
+    assert_close(got, ref, gpu.TOL[io])
+    assert rel_l2(h_got, h_ref) < 1e-5
+    if K > 1:
+        assert np.array_equal(t_got, t_ref)
+
+
+@pytest.mark.parametrize("L", [31, 128])
+def test_heads_groups_and_scalar_decay(gpu, oracle, L):
+    """Heads of several channels, two B/C groups, a scalar decay and a skip weight per head."""
+    for a_kind in (0, 1):
+        cfg = synth.mixer_cfg(1, L, 256, d_state=16, n_heads=32, n_groups=2, a_kind=a_kind, d_kind=1, io="f32")
+        pf, pb = synth.make_params(cfg, L, 0), synth.make_params(cfg, L, 1)
+        inp = synth.make_inputs(cfg, L)
+        assert_close(gpu.gpu_fwd(cfg, pf, pb, inp), oracle.bimamba_fwd(cfg, to_np(pf), to_np(pb), to_np(inp)), gpu.TOL["f32"])
