@@ -261,14 +261,16 @@ Plan make_plan(const bimamba_desc* d, bool inputs_shared)
     p.ssd_parts = p.ssd_subs = p.ssd_part_subs = 1;
     p.ssd_part_chunks = p.ssd_sub_chunks = p.ssd_chunks;
     if (p.ssd) {
-        const long long items = (long long)d->n_heads * d->batch;
+        // (directions with an output half of their own share a launch: twice the items in flight)
+        const long long items = (long long)d->n_heads * d->batch * (d->combine == BIMAMBA_COMBINE_SEPARATE ? 2 : 1);
         const int cus = cu_count();
         long long parts = items > 0 ? cus / items : 1;
         if (parts > p.ssd_chunks / 8) parts = p.ssd_chunks / 8;
         if (parts > 16) parts = 16;
         if (parts >= 2) {
             const int part_chunks = (int)((p.ssd_chunks + parts - 1) / parts);
-            const long long subs_wanted = (4LL * cus + 2 * items - 1) / (2 * items);
+            const long long items_both = 2LL * d->n_heads * d->batch;
+            const long long subs_wanted = (4LL * cus + items_both - 1) / items_both;
             long long k = (subs_wanted + parts - 1) / parts;
             if (k > part_chunks / 4) k = part_chunks / 4;
             if (k < 1) k = 1;
@@ -556,7 +558,15 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                 for (int s = 0; s < 2; s++) sp.dir[s] = scan_args(s);
                 launch_ssd_duo(d->d_state, d->d_inner / d->n_heads, sp, d->batch, st);
             } else {
-                for (int s = 1; s >= 0; s--) launch_ssd_scan(d->d_state, d->d_inner / d->n_heads, scan_args(s), d->batch, st);
+                const int head_width = d->d_inner / d->n_heads;
+                SsdStatePair sp;
+                sp.dir[1] = scan_args(1);
+                if (!separate) {   // (the forward direction adds what the reverse one parked)
+                    sp.dir[0] = sp.dir[1];
+                    launch_ssd_scan(d->d_state, head_width, sp, 1, d->batch, st);
+                }
+                sp.dir[0] = scan_args(0);
+                launch_ssd_scan(d->d_state, head_width, sp, separate ? 2 : 1, d->batch, st);
             }
             if (probe_stop) (void)hipEventRecord(probe_stop, st);
         } else {

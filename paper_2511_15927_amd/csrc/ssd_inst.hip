@@ -28,38 +28,40 @@ static void prep_variant(const SsdPrepPair& pa, int nchunk, int batch, hipStream
 }
 
 template <int N, int P, bool SINGLE, int GROUPS, bool PARTS>
-static void scan_variant(const SsdArgs& sa, int batch, hipStream_t st)
+static void scan_variant(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     static std::atomic<bool> seen[kMaxDevices];
     constexpr size_t lds = SsdLds<N, P, SINGLE>::bytes();
     auto kernel = ssd_kernel<N, P, SINGLE, GROUPS, PARTS>;
     if (first_use_on_current_device(seen))
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    const unsigned parts = !PARTS ? 1u : (unsigned)sa.parts;   // blockIdx.y is the time part
-    hipLaunchKernelGGL(kernel, dim3((unsigned)sa.H, parts, (unsigned)batch), dim3(4 * P + 256 * GROUPS), lds, st, sa);
+    const unsigned parts = !PARTS ? 1u : (unsigned)sp.dir[0].parts;   // blockIdx.y is the time part of a direction
+    hipLaunchKernelGGL(kernel, dim3((unsigned)sp.dir[0].H, parts * (unsigned)dirs, (unsigned)batch), dim3(4 * P + 256 * GROUPS), lds, st, sp);
 }
 
-template <int N, int P>
-static void wide_variant(const SsdArgs& sa, int batch, hipStream_t st)
+template <int N, int P, int DIRS>
+static void wide_variant(const SsdStatePair& sp, int batch, hipStream_t st)
 {
     static std::atomic<bool> seen[kMaxDevices];
     constexpr size_t lds = SsdLds<N, P, false>::bytes();
-    auto kernel = ssd_wide_kernel<N, P>;
+    auto kernel = ssd_wide_kernel<N, P, DIRS>;
     if (first_use_on_current_device(seen))
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)sa.H, 1, (unsigned)batch), dim3(SsdWide<N, P>::kThreads), lds, st, sa);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)sp.dir[0].H, (unsigned)DIRS, (unsigned)batch), dim3(SsdWide<N, P>::kThreads), lds, st, sp);
 }
 
 // Long calls that leave at least half of the CUs empty (batch 1 or 2) split the producers into two groups, which
 // shortens the per-chunk chain of each workgroup (-4 to -9 %); with the chip full the extra waves only compete for
 // issue slots (+4 to +7 %), so those keep one group.  (Calls of a single chunk go to launch_ssd_duo.)
 template <int N, int P>
-static void scan_one(const SsdArgs& sa, int batch, hipStream_t st)
+static void scan_one(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    if (sa.wide) wide_variant<N, P>(sa, batch, st);
-    else if (sa.parts > 1) scan_variant<N, P, false, 1, true>(sa, batch, st);
-    else if (2LL * sa.H * batch <= cu_count()) scan_variant<N, P, false, 2, false>(sa, batch, st);
-    else scan_variant<N, P, false, 1, false>(sa, batch, st);
+    const SsdArgs& sa = sp.dir[0];
+    if (sa.wide && dirs == 2) wide_variant<N, P, 2>(sp, batch, st);
+    else if (sa.wide) wide_variant<N, P, 1>(sp, batch, st);
+    else if (sa.parts > 1) scan_variant<N, P, false, 1, true>(sp, dirs, batch, st);
+    else if (2LL * dirs * sa.H * batch <= cu_count()) scan_variant<N, P, false, 2, false>(sp, dirs, batch, st);
+    else scan_variant<N, P, false, 1, false>(sp, dirs, batch, st);
 }
 
 bool ssd_supported(int d_state, int headdim) { return (d_state == 64 || d_state == 128) && (headdim == 32 || headdim == 64); }
@@ -116,12 +118,15 @@ void launch_ssd_state(int d_state, int headdim, const SsdStatePair& sp, int subs
     else if (d_state == 64 && headdim == 32) hipLaunchKernelGGL((ssd_state_kernel<64, 32>), grid, dim3(256), 0, st, sp);
 }
 
-void launch_ssd_scan(int d_state, int headdim, const SsdArgs& sa, int batch, hipStream_t st)
+// dirs 1: the direction sp.dir[0]; dirs 2: both in one launch, for calls whose directions write halves of their own.  A
+// workgroup holds a CU (158 KB of LDS) and a call's time is its longest chain of chunks, so two launches that each leave
+// CUs empty take twice as long as one: 120 heads x 32, N 128, 1 x 1024 tokens 72.2 -> 38.1 us a call.
+void launch_ssd_scan(int d_state, int headdim, const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    if (d_state == 128 && headdim == 64) scan_one<128, 64>(sa, batch, st);
-    else if (d_state == 128 && headdim == 32) scan_one<128, 32>(sa, batch, st);
-    else if (d_state == 64 && headdim == 64) scan_one<64, 64>(sa, batch, st);
-    else if (d_state == 64 && headdim == 32) scan_one<64, 32>(sa, batch, st);
+    if (d_state == 128 && headdim == 64) scan_one<128, 64>(sp, dirs, batch, st);
+    else if (d_state == 128 && headdim == 32) scan_one<128, 32>(sp, dirs, batch, st);
+    else if (d_state == 64 && headdim == 64) scan_one<64, 64>(sp, dirs, batch, st);
+    else if (d_state == 64 && headdim == 32) scan_one<64, 32>(sp, dirs, batch, st);
 }
 
 }  // namespace bm

@@ -217,7 +217,7 @@ struct SsdArgs {
     int dir, mode, out_ch_off, dt_softplus, d_per_head;
     int wide;             // run on ssd_wide_kernel (ssd_wide.h): both directions of a call agree, the parked result is bf16
     // Time parts (calls with too few (batch, head) items to fill the chip): the chunks are dealt to `parts` workgroups
-    // per item, part_chunks each, in scan order (blockIdx.y).  A part is part_subs sub-parts of sub_chunks chunks;
+    // per item, part_chunks each, in scan order.  A part is part_subs sub-parts of sub_chunks chunks;
     // ssd_state_kernel leaves every sub-part's end state from a zero start and the product of its chunk decays (all
     // but the scan-last one), ssd_carry_kernel turns those into the state entering each sub-part, and the output launch
     // starts part p from the entry state of sub-part p * part_subs.
@@ -516,7 +516,7 @@ __global__ __launch_bounds__(256, 4) void ssd_state_kernel(const SsdStatePair bo
 // PG = 2 splits the producers into two groups of four waves: one builds the score operand and stages the tiles, the
 // other runs conv + SiLU (both run the short scan for themselves).  A producer wave's chain of dependent stages per
 // chunk is then about half as long, which is what sets the chunk period of long calls; the CU holds twelve waves.
-// PARTS compiles the time parts in (chunk range and entry state per blockIdx.y); without it the kernel walks every
+// PARTS compiles the time parts in (chunk range and entry state per time_part); without it the kernel walks every
 // chunk of its item and carries none of that bookkeeping through its loops.
 // DUO (single-chunk calls only): both directions of a (batch, head) item in one workgroup, see ssd_duo_kernel.
 // kDuoFirst is the direction that would park its result in global memory: it leaves it in LDS, one row per token.
@@ -536,7 +536,7 @@ struct SsdDuoLds {
 };
 
 template <int N, int P, bool SINGLE, int PG, bool PARTS, int DUO>
-__device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, float (&parked)[16])
+__device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, float (&parked)[16])
 {
     static_assert(PG == 1 || (PG == 2 && !SINGLE), "one or two producer groups; the single-chunk form keeps one");
     static_assert(!PARTS || (!SINGLE && PG == 1), "time parts come with one producer group and more than one chunk");
@@ -585,7 +585,6 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, float (&parked)[16
     const size_t Lpad = (size_t)a.nchunk * kQ;
     // this workgroup's chunks [c_first, c_stop) and the states it starts from / leaves
     constexpr bool in_parts = PARTS;
-    const int time_part = in_parts ? (int)blockIdx.y : 0;   // (`part` names the parked partial in the consumers)
     const int c_first = in_parts ? time_part * a.part_chunks : 0;
     const int c_stop = in_parts ? min(a.nchunk, c_first + a.part_chunks) : a.nchunk;
     const size_t part_elems = (size_t)gridDim.z * a.Dn * N;
@@ -1057,10 +1056,14 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, float (&parked)[16
 }
 
 template <int N, int P, bool SINGLE = false, int PG = 1, bool PARTS = false>
-__global__ __launch_bounds__(4 * P + 256 * PG, SINGLE ? 4 : 1) void ssd_kernel(const SsdArgs a)
+__global__ __launch_bounds__(4 * P + 256 * PG, SINGLE ? 4 : 1) void ssd_kernel(const SsdStatePair launch)
 {
     float none[16];
-    ssd_walk<N, P, SINGLE, PG, PARTS, kDuoNone>(a, none);
+    // blockIdx.y: the time part, counted through the direction(s) of the launch
+    int part = blockIdx.y, second = 0;
+    const int parts = PARTS ? launch.dir[0].parts : 1;
+    if (part >= parts) { second = 1; part -= parts; }
+    ssd_walk<N, P, SINGLE, PG, PARTS, kDuoNone>(launch.dir[second], part, none);
 }
 
 // Single-chunk calls (block-diffusion steps), both directions of a (batch, head) item in one workgroup: the reverse
@@ -1076,7 +1079,7 @@ __global__ __launch_bounds__(4 * P + 256, 4) void ssd_duo_kernel(const SsdStateP
     float parked[16];
 #pragma unroll
     for (int r = 0; r < 16; r++) parked[r] = 0.0f;
-    ssd_walk<N, P, true, 1, false, kDuoFirst>(both.dir[1], parked);
+    ssd_walk<N, P, true, 1, false, kDuoFirst>(both.dir[1], 0, parked);
     const int tid = threadIdx.x;
     if (tid < 4 * P && both.dir[1].mode != kSsdFinalOnly) {   // consumer waves, same places as in ssd_walk
         extern __shared__ __attribute__((aligned(16))) unsigned char ssd_lds[];
@@ -1095,7 +1098,7 @@ __global__ __launch_bounds__(4 * P + 256, 4) void ssd_duo_kernel(const SsdStateP
         }
     }
     lds_barrier();
-    ssd_walk<N, P, true, 1, false, kDuoSecond>(both.dir[0], parked);
+    ssd_walk<N, P, true, 1, false, kDuoSecond>(both.dir[0], 0, parked);
 }
 
 }  // namespace bm

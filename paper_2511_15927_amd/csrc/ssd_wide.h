@@ -12,7 +12,7 @@
 // arithmetic), and the result one direction parks for the other crosses global memory as bf16: in the paper's
 // precision (bf16 autocast, App. A) each direction's output is a bf16 tensor before the two are added (eq. 6).
 //
-// Multi-chunk calls without time parts only; z / out token strides up to 2^24 elements (the host checks).
+// grid (H, directions, batch).  Multi-chunk calls without time parts only; z / out token strides up to 2^24 elements (the host checks).
 #pragma once
 #include "ssd_kernels.h"
 
@@ -25,9 +25,12 @@ struct SsdWide {
     static constexpr int kThreads = 64 * (kYWaves + kHWaves + kProdWaves);
 };
 
-template <int N, int P>
-__global__ __launch_bounds__((SsdWide<N, P>::kThreads)) void ssd_wide_kernel(const SsdArgs a)
+// DIRS: one launch per direction (dir[0]) or both at once (see launch_ssd_scan); compiled apart, since selecting the arguments
+// at run time cost the launches of one direction 0.5 %.
+template <int N, int P, int DIRS>
+__global__ __launch_bounds__((SsdWide<N, P>::kThreads)) void ssd_wide_kernel(const SsdStatePair launch)
 {
+    const SsdArgs& a = launch.dir[DIRS == 1 ? 0 : blockIdx.y];
     using Lds = SsdLds<N, P, false>;
     using W = SsdWide<N, P>;
     constexpr int kPB = W::kPB, kNB = W::kNB;
@@ -503,8 +506,11 @@ __global__ __launch_bounds__((SsdWide<N, P>::kThreads)) void ssd_wide_kernel(con
             lds_barrier();
         }
     };
+    if constexpr (DIRS == 2) {
+        walk(std::integral_constant<int, kSsdFinalOnly>{});
+        return;
+    }
     switch (a.mode) {
-        case kSsdFinalOnly: walk(std::integral_constant<int, kSsdFinalOnly>{}); break;
         case kSsdPartial: walk(std::integral_constant<int, kSsdPartial>{}); break;
         case kSsdPartialRaw: walk(std::integral_constant<int, kSsdPartialRaw>{}); break;
         case kSsdFinalAdd: walk(std::integral_constant<int, kSsdFinalAdd>{}); break;

@@ -244,3 +244,30 @@ def test_ssd_block_call_at_benchmark_size_sampled(gpu, oracle):
     assert_close(out[..., sel], ref, gpu.TOL["bf16"])
     assert rel_l2(h[:, sel, :], h_ref[:, sel, :]) < 1e-2
     assert np.array_equal(tail, t_ref)
+
+
+@pytest.mark.parametrize("L,batch,heads,headdim,N", [(65, 1, 3, 64, 128), (130, 3, 8, 32, 64), (1100, 2, 4, 64, 64), (1157, 1, 5, 32, 128)])
+@pytest.mark.parametrize("wide_z", [False, True])
+def test_ssd_both_directions_in_one_launch(gpu, oracle, L, batch, heads, headdim, N, wide_z):
+    """Output halves kept apart, activations per direction: both directions walk in one launch, with and without time
+    parts; a z token stride beyond 2^24 elements takes the eight-wave form of the walk."""
+    from paper_2511_15927_amd import binding as bd
+    cfg = synth.m2_cfg(batch, L, heads * headdim, headdim=headdim, d_state=N, combine=synth.COMBINE_SEPARATE)
+    pf, pb, inp = case(cfg, 2100 + L)
+    inp_b = synth.make_inputs(cfg, 2600 + L)
+    ref = oracle.bimamba_fwd(cfg, to_np(pf), to_np(pb), to_np(inp), to_np(inp_b))
+    if not wide_z:
+        assert_close(gpu.gpu_fwd(cfg, pf, pb, inp, inp_b), ref, gpu.TOL["bf16"])
+        return
+    if L > 200 or batch > 1:
+        pytest.skip("one small call is enough for the strided view")
+    stride = (1 << 24) + 2
+    desc = bd.make_desc(cfg)
+    dpf, dpb, dinp, dinp_b = bd.to_device(pf), bd.to_device(pb), bd.to_device(inp, cfg), bd.to_device(inp_b, cfg)
+    z = torch.empty((L - 1) * stride + cfg["d_inner"], dtype=torch.bfloat16, device="cuda").as_strided((1, L, cfg["d_inner"]), (0, stride, 1))
+    z.copy_(dinp["z"])
+    dinp["z"] = z
+    out, ws = bd.alloc_out(cfg), bd.alloc_workspace(desc)
+    bd.bimamba_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp), bd.make_inputs(dinp_b), bd.make_tensor(out), ws)
+    torch.cuda.synchronize()
+    assert_close(out.float().cpu().numpy().reshape(ref.shape), ref, gpu.TOL["bf16"])
