@@ -61,6 +61,22 @@ void launch_bwd_prep(int io_bf16, const BwdPrepArgs& a, int sets, hipStream_t st
     else hipLaunchKernelGGL(bwd_prep_kernel<IoF32>, grid, dim3(256), 0, st, a);
 }
 
+// src[0], src[step], ... added in order.  The sum is one chain but its addresses are not: sixteen values are requested at a
+// time (the addition of one at a time waited out a memory round trip per two or three values).
+__device__ __forceinline__ float sum_in_order(const float* src, long long step, int count)
+{
+    constexpr int kAhead = 16;
+    float acc = 0.0f;
+    for (int k0 = 0; k0 < count; k0 += kAhead) {
+        float v[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; j++) v[j] = src[(long long)min(k0 + j, count - 1) * step];
+#pragma unroll
+        for (int j = 0; j < kAhead; j++) acc += k0 + j < count ? v[j] : 0.0f;
+    }
+    return acc;
+}
+
 __global__ __launch_bounds__(256) void bwd_sum_kernel(const BwdSumArgs a)
 {
     long long i = (long long)blockIdx.x * 256 + threadIdx.x;
@@ -72,8 +88,7 @@ __global__ __launch_bounds__(256) void bwd_sum_kernel(const BwdSumArgs a)
         const long long r = i / two_n;
         const int v = (int)(i % two_n);
         const float* src = a.part[set] + r * a.slots * two_n + v;
-        float acc = 0.0f;
-        for (int k = 0; k < a.slots; k++) acc += src[(long long)k * two_n];
+        const float acc = sum_in_order(src, two_n, a.slots);
         (v % 2 ? a.dC : a.dB)[set][r * a.N + v / 2] = acc;
         return;
     }
@@ -82,8 +97,7 @@ __global__ __launch_bounds__(256) void bwd_sum_kernel(const BwdSumArgs a)
     if (i >= 2LL * values * a.Dn) return;
     const int ch = (int)(i % a.Dn), v = (int)(i / a.Dn % values), s = (int)(i / a.Dn / values);
     const float* src = a.param_part + ((size_t)s * a.segs * values + v) * a.pitch + ch;
-    float acc = 0.0f;
-    for (int k = 0; k < a.segs; k++) acc += src[(size_t)k * values * a.pitch];
+    const float acc = sum_in_order(src, values * a.pitch, a.segs);
     if (v < a.N) a.dA[s][(size_t)ch * a.N + v] = acc;
     else if (v == a.N) a.dD[s][ch] = acc;
     else if (v < a.N + 5) {
@@ -107,7 +121,7 @@ static void launch_walks(const BwdArgs& a, int batch, hipStream_t st)
     hipLaunchKernelGGL((bwd_state_kernel<N, IO>), grid, dim3(256), 0, st, a);
     if (a.nseg > 1) {
         const long long threads = 2LL * batch * a.tiles * 64 * N;
-        hipLaunchKernelGGL(bwd_carry_kernel<N>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st, a, batch);
+        hipLaunchKernelGGL(bwd_carry_kernel<N>, dim3((unsigned)((threads + 255) / 256), 2), dim3(256), 0, st, a, batch);
     }
     static std::atomic<bool> lifted[kMaxDevices];
     auto walk = bwd_kernel<N, IO>;

@@ -432,6 +432,7 @@ __global__ __launch_bounds__(256, 4) void bwd_state_kernel(const BwdArgs a)
 // One thread per (direction, batch, tile, N / 4, lane, 4): the state entering each segment in scan order, and against
 // it the dh of the tokens after each segment's window:
 //   h_next = exp(A sum Delta) h + S,   D_before = exp(A sum Delta over the window) D + S_d.
+// blockIdx.y: the h fold, the dh fold.  Either waits for its rounds of loads more than it computes, so they run beside each other.
 template <int N>
 __global__ __launch_bounds__(256) void bwd_carry_kernel(const BwdArgs a, int batch)
 {
@@ -447,22 +448,25 @@ __global__ __launch_bounds__(256) void bwd_carry_kernel(const BwdArgs a, int bat
     const size_t seg0 = ((size_t)s * batch + b) * a.nseg;
     const size_t half = (size_t)2 * batch * a.nseg * a.tiles * 64;
     auto seg_of = [&](int i) { return s == 0 ? i : a.nseg - 1 - i; };   // i: scan order
-    float h = 0.0f;
-    for (int i0 = 0; i0 < a.nseg; i0 += kAhead) {
-        float end[kAhead], sw[kAhead];
+    if (blockIdx.y == 0) {
+        float h = 0.0f;
+        for (int i0 = 0; i0 < a.nseg; i0 += kAhead) {
+            float end[kAhead], sw[kAhead];
 #pragma unroll
-        for (int j = 0; j < kAhead; j++) {
-            const size_t at = seg0 + seg_of(min(i0 + j, max(a.nseg - 2, 0)));      // nothing needs the last segment's end
-            end[j] = a.seg_h[at * per_seg + e];
-            sw[j] = a.seg_w[(at * a.tiles + tile) * 64 + lane];
-        }
+            for (int j = 0; j < kAhead; j++) {
+                const size_t at = seg0 + seg_of(min(i0 + j, max(a.nseg - 2, 0)));      // nothing needs the last segment's end
+                end[j] = a.seg_h[at * per_seg + e];
+                sw[j] = a.seg_w[(at * a.tiles + tile) * 64 + lane];
+            }
 #pragma unroll
-        for (int j = 0; j < kAhead; j++) {
-            if (i0 + j < a.nseg) {
-                a.seg_h[(seg0 + seg_of(i0 + j)) * per_seg + e] = h;
-                h = fmaf(fast_exp2(sw[j] * a2), h, end[j]);
+            for (int j = 0; j < kAhead; j++) {
+                if (i0 + j < a.nseg) {
+                    a.seg_h[(seg0 + seg_of(i0 + j)) * per_seg + e] = h;
+                    h = fmaf(fast_exp2(sw[j] * a2), h, end[j]);
+                }
             }
         }
+        return;
     }
     float d = 0.0f;
     for (int i0 = a.nseg - 1; i0 >= 0; i0 -= kAhead) {
