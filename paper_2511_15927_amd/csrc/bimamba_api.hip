@@ -586,6 +586,10 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
         sa.h_in = block_variant ? h_in : nullptr;
         sa.h_out = block_variant ? h_out : nullptr;
         sa.tail_in = block_variant ? tail_in : nullptr;
+        if (block_variant && tail_out && plan.nseg == 1 && d->d_conv > 1 && !d->conv_bc) {
+            sa.tail_out = tail_out;   // one segment: its forward walk ends with the tail in registers
+            tail_out = nullptr;
+        }
         sa.carry = reinterpret_cast<float*>(ws + plan.off_carry);
         sa.sumdt = reinterpret_cast<float*>(ws + plan.off_sumdt);
         sa.L = d->seqlen; sa.Dn = d->d_inner; sa.P = d->d_inner / d->n_heads; sa.HG = d->n_heads / d->n_groups;

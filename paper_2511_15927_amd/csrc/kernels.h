@@ -55,6 +55,7 @@ struct SweepArgs {
     const float* h_in;    // [batch][Dn][N] or null
     float* h_out;         // or null; written by the sweep only when nseg == 1
     const void* tail_in;  // io dtype [batch][K-1][tail_ch] or null
+    void* tail_out;       // or null; written by the sweep only when nseg == 1, and its x channels only
     float* carry;         // [2][batch][nseg][Dn][N]: segment end states (summary) then segment start states (carry)
     float* sumdt;         // [2][batch][nseg][Dn]
     int L, Dn, P, HG, G, K, nseg, seg_len, tail_ch;
@@ -113,6 +114,14 @@ template <typename IO>
 __device__ __forceinline__ typename IO::T io_value(float v)
 {
     if constexpr (sizeof(typename IO::T) == 2) return IO::round(v);
+    else return v;
+}
+
+// The I/O dtype value a raw input was converted from.
+template <typename IO>
+__device__ __forceinline__ typename IO::T io_bits(float v)
+{
+    if constexpr (sizeof(typename IO::T) == 2) return (unsigned short)(__float_as_uint(v) >> 16);
     else return v;
 }
 
@@ -1206,10 +1215,24 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, float* lds_all, c
         if (a.raw_partial) run_range<N, S, AKIND, IO, kModeFinalAddRaw, TILE, BCSRC>(a, c, len - n_first, sp, lds, lane);
         else run_range<N, S, AKIND, IO, kModeFinalAdd, TILE, BCSRC>(a, c, len - n_first, sp, lds, lane);
     }
-    if (s == 0 && a.nseg == 1 && a.h_out) {
-        float* dst = a.h_out + ((size_t)b * a.Dn + ch) * N + sub * NS;
+    if (a.nseg == 1 && (a.h_out || a.tail_out)) {
+        // Waves past the last tile shadow it: all have read h_in and tail_in, which the commit may overwrite, before any
+        // of them gets here (with the halves apart no barrier came before).
+        if (a.separate) __syncthreads();
+        if (s == 0 && a.h_out) {
+            float* dst = a.h_out + ((size_t)b * a.Dn + ch) * N + sub * NS;
 #pragma unroll
-        for (int n = 0; n < NS; n++) dst[n] = c.h[n];
+            for (int n = 0; n < NS; n++) dst[n] = c.h[n];
+        }
+        // The conv window left by the forward walk is the tail: raw tokens, so cutting the fp32 form back to the I/O
+        // dtype restores their bits.  A launch of its own for it cost 4.0 us and its gap: 26.4 -> 23.8 us for a 32-token
+        // block step that commits (batch 16, d_inner 4096).
+        if (s == 0 && a.tail_out && sub == 0) {
+            T* dst = (T*)a.tail_out + (size_t)b * (a.K - 1) * a.tail_ch + ch;
+#pragma unroll
+            for (int i = 0; i < 3; i++)
+                if (i < a.K - 1) dst[(size_t)(a.K - 2 - i) * a.tail_ch] = io_bits<IO>(c.xh[i]);
+        }
     }
 }
 
