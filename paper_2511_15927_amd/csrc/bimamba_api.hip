@@ -467,10 +467,11 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
         // 1. fp32 B|C rows per direction (the chunked path prepares its own operand tiles from the raw rows)
         const bool one_launch = short_call(d, plan);
         const int nbuf = (plan.ssd || one_launch) ? 0 : plan.two_bc ? 2 : 1;
+        PrepPair prep{};
         for (int s = 0; s < nbuf; s++) {
             const bimamba_inputs* in = s == 0 ? in_f : in_b;
             const bimamba_params* p = s == 0 ? pf : pb;
-            PrepArgs pa{};
+            PrepArgs& pa = prep.dir[s];
             pa.B = targ(in->B);
             pa.C = targ(in->C);
             pa.conv_w = p->conv_w;
@@ -479,10 +480,12 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
             pa.dst = reinterpret_cast<float*>(ws + plan.off_bc[s]);
             pa.batch = d->batch; pa.L = d->seqlen; pa.G = d->n_groups; pa.N = d->d_state; pa.K = d->d_conv;
             pa.Dn = d->d_inner; pa.tail_ch = tail_ch; pa.conv_bc = d->conv_bc; pa.dir = s == 0 ? 1 : -1;
+        }
+        if (nbuf > 0) {
             const long long total = (long long)d->batch * d->seqlen * 2 * GN;
-            const dim3 grid((unsigned)((total + 255) / 256));
-            if (d->io_dtype == BIMAMBA_BF16) hipLaunchKernelGGL(prep_bc_kernel<IoBF16>, grid, dim3(256), 0, st, pa);
-            else hipLaunchKernelGGL(prep_bc_kernel<IoF32>, grid, dim3(256), 0, st, pa);
+            const dim3 grid((unsigned)((total + 255) / 256), (unsigned)nbuf);
+            if (d->io_dtype == BIMAMBA_BF16) hipLaunchKernelGGL(prep_bc_kernel<IoBF16>, grid, dim3(256), 0, st, prep);
+            else hipLaunchKernelGGL(prep_bc_kernel<IoF32>, grid, dim3(256), 0, st, prep);
         }
         if (plan.ssd) {
             // 2'. chunked matrix-core path: per-direction operand tiles, then the reverse scan parks its result and the
