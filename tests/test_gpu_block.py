@@ -247,3 +247,36 @@ def test_first_call_in_a_process_captured_into_a_graph(layout):
     assert res["eager_equals_replay"], res
     for rep in res["replays"]:
         assert rep["out"] < 2e-2 and rep["h"] < (1e-5 if layout == "selective" else 1e-2) and rep["tail_equal"], res
+
+
+@pytest.mark.parametrize("L", [1, 2, 3, 7, 41])
+@pytest.mark.parametrize("split,N,K,io", [(1, 16, 4, "bf16"), (2, 16, 3, "bf16"), (4, 16, 4, "f32"), (1, 32, 2, "f32"), (4, 64, 4, "bf16")])
+def test_tail_committed_by_the_sweep(gpu, oracle, L, split, N, K, io):
+    """One-segment sweeps store the conv tail themselves: calls shorter and longer than the tail, with and without one to
+    start from, an odd number of channel tiles, the halves added and kept apart, committed in place; and the same call cut
+    into segments, which leaves the tail to its own launch."""
+    from paper_2511_15927_amd import binding as bd
+    cfg = synth.mixer_cfg(2, L, 64 + 3 * (64 // split) // 2, d_state=N, d_conv=K, io=io, combine=L % 2)
+    pf, pb = params(cfg, 77 + L)
+    inp = synth.make_inputs(cfg, 78 + L)
+    g = torch.Generator().manual_seed(79 + L)
+    h0 = (0.2 * torch.randn(2, cfg["d_inner"], N, generator=g)).float()
+    tail0 = synth.round_io(torch.randn(2, K - 1, cfg["d_inner"], generator=g), io) if L != 2 else None
+    ref, h_ref, t_ref = oracle.bimamba_block_fwd(cfg, to_np(pf), to_np(pb), to_np(inp), h_in=h0.numpy(),
+                                                 tail_in=None if tail0 is None else tail0.numpy())
+    for chunks in (1, 2):
+        got, h, t = gpu.gpu_block_fwd(cfg, pf, pb, inp, h_in=h0, tail_in=tail0, state_split=split, time_chunks=chunks)
+        assert_close(got.reshape(ref.shape), ref, gpu.TOL[io])
+        assert rel_l2(h, h_ref) < 1e-5
+        assert np.array_equal(t, t_ref)
+    if tail0 is None:
+        return
+    desc = bd.make_desc(cfg, state_split=split, time_chunks=1)
+    dh, dt = h0.cuda(), tail0.to(device="cuda", dtype=bd.io_dtype(cfg))
+    out = bd.alloc_out(cfg)
+    dpf, dpb, dinp, ws = bd.to_device(pf), bd.to_device(pb), bd.to_device(inp, cfg), bd.alloc_workspace(desc, 1)
+    bd.bimamba_block_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp), None, dh, dt, dh, dt,
+                         bd.make_tensor(out), ws)
+    torch.cuda.synchronize()
+    assert_close(out.float().cpu().numpy().reshape(ref.shape), ref, gpu.TOL[io])
+    assert np.array_equal(dt.float().cpu().numpy().astype(np.float64), t_ref)
