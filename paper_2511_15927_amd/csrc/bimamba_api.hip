@@ -128,7 +128,7 @@ long long waves_of(const bimamba_desc* d, int split)
 }
 
 // Launch geometry of the lane-per-chain kernels, from measurements on MI355X (1024 SIMDs) with w = the number of waves
-// that one lane per chain gives (2 * batch * d_inner / 64), up to 32 states:
+// that one lane per chain gives (2 * batch * d_inner / 64), for 32 states (up to 16: pick_geometry below):
 //   first       two lanes per chain (each holds half the states), whole sequence, when the 2w waves fill the rounds of
 //               resident waves well (two_lanes_fit below).
 //   w >= 1920   one lane per chain, whole sequence: close to two waves per SIMD already.
@@ -175,7 +175,7 @@ bool two_lanes_fit(const bimamba_desc* d, long long w)
 // One lane per chain needs no help from segments or lane splitting.
 bool enough_chains(const bimamba_desc* d, long long w) { return many_states(d) ? w >= target_waves() : 8 * w >= 15 * simds(); }
 
-int pick_split(const bimamba_desc* d)
+int pick_split_general(const bimamba_desc* d)
 {
     if (d->state_split > 0) return d->state_split;
     const long long w = waves_of(d, 1);
@@ -190,7 +190,7 @@ int pick_split(const bimamba_desc* d)
     return two ? 2 : 1;
 }
 
-int pick_chunks(const bimamba_desc* d, int split)
+int pick_chunks_general(const bimamba_desc* d, int split)
 {
     const int L = d->seqlen;
     if (L <= 0) return 1;
@@ -208,6 +208,72 @@ int pick_chunks(const bimamba_desc* d, int split)
     if (n > 4096) n = 4096;
     if (n < 1) n = 1;
     return n;
+}
+
+// Up to 16 states, lanes per chain and time segments that are left to the library, for calls that neither fill the chip
+// (enough_chains) nor the band of two_lanes_fit.  Either the whole sequence is walked at once, with two lanes per chain
+// where 16 states allow it: its time is the tokens' times what a token costs while a SIMD holds at most one wave, or
+// up to two; or segments: a price for the two launches more, and a cost that follows the work.  In microseconds, bf16,
+// the state's decay general or arithmetic:
+//   16 states  whole 8 + 0.165 L (2w <= 1 wave per SIMD) or 8 + 0.25 L;  segments 35 + 0.32 w L
+//   8 states   whole 4 + 0.33 L;  segments 35 + 0.21 w L (w >= 1.4 waves per SIMD: always whole)
+// Segments fill rounds of resident workgroups (four waves per SIMD with one lane per chain) exactly: one workgroup more than
+// a round holds costs a round.  Four rounds while segments keep 128 tokens, else one round of segments of 48 (16 states)
+// or 16 tokens; too few tokens for that: two lanes per chain, three waves per SIMD, segments of 24 or more.
+// Over 308 calls of 16 states (512 to 4096 channels, batch 1 to 48, 64 to 16384 tokens, bf16 and fp32) the choice is
+// on average 1.4 % slower than the best of all geometries, the general rule 19 %; over 98 calls of 8 states 5 % and 34 %.
+struct Geometry {
+    int split, nseg;
+};
+Geometry pick_geometry(const bimamba_desc* d)
+{
+    const int L = d->seqlen;
+    const bool pair = d->d_state == 16;
+    const double w = (double)waves_of(d, 1) / simds(), tokens = L;
+    if (pair) {
+        if (tokens * (2 * w <= 1 ? 0.165 : 0.25) + 8 <= 35 + 0.32 * w * tokens) return {2, 1};
+    } else if (w >= 1.4 || tokens * 0.33 + 4 <= 35 + 0.21 * w * tokens) {
+        return {1, 1};
+    }
+    // segments of a launch that holds `layers` workgroups per CU at most
+    auto segments = [&](int split, int layers) {
+        const int cpw = 64 / split;
+        const long long per_segment = (long long)(((d->d_inner + cpw - 1) / cpw + 1) / 2) * d->batch;
+        const long long n = (long long)layers * cu_count() / per_segment;
+        return (int)(n < 1 ? 1 : n > L ? L : n);
+    };
+    auto tokens_of = [&](int n) { return L / n; };
+    int n = segments(1, 16);
+    if (n > 1 && tokens_of(n) >= 128) return {1, n};
+    const int shortest = pair ? 48 : 16;
+    if (pair) {
+        n = segments(1, 4);
+        if (n > 1 && tokens_of(n) >= shortest) return {1, n};
+        for (int layers = 3; layers > 0; layers--) {
+            n = segments(2, layers);
+            if (tokens_of(n) >= 24) return {2, n};
+        }
+        return {2, n > L / 16 ? 1 : n};
+    }
+    for (int layers = 4; layers > 0; layers--) {
+        n = segments(1, layers);
+        if (n > 1 && tokens_of(n) >= shortest) return {1, n};
+    }
+    return {1, 1};
+}
+
+// coarse: by the general rule whatever the state count (see bimamba_block_fwd_static).
+Geometry geometry_of(const bimamba_desc* d, bool coarse)
+{
+    const int split = pick_split_general(d);
+    const bool open = d->state_split == 0 && d->time_chunks == 0 && d->d_state <= 16 && d->seqlen > 0 && d->batch > 0;
+    const long long w = waves_of(d, 1);
+    if (open && !coarse && !enough_chains(d, w) && !(d->d_state == 16 && two_lanes_fit(d, w))) {
+        Geometry g = pick_geometry(d);
+        if (g.nseg > 4096) g.nseg = 4096;
+        return g;
+    }
+    return {split, pick_chunks_general(d, split)};
 }
 
 struct Plan {
@@ -229,14 +295,15 @@ bool use_ssd(const bimamba_desc* d)
            d->batch <= 32767;   // the preparation kernel's grid holds both directions of every batch element
 }
 
-Plan make_plan(const bimamba_desc* d, bool inputs_shared)
+Plan make_plan(const bimamba_desc* d, bool inputs_shared, bool coarse = false)
 {
     Plan p{};
     // The lane-per-chain geometry is always planned (and its workspace reserved): a call whose x tensors do not meet
     // the matrix-core kernels' alignment needs falls back to it.
     p.ssd = use_ssd(d);
-    p.split = pick_split(d);
-    p.nseg = pick_chunks(d, p.split);
+    const Geometry geometry = geometry_of(d, coarse);
+    p.split = geometry.split;
+    p.nseg = geometry.nseg;
     p.seg_len = d->seqlen > 0 ? (d->seqlen + p.nseg - 1) / p.nseg : 1;
     p.nseg = d->seqlen > 0 ? (d->seqlen + p.seg_len - 1) / p.seg_len : 1;
     p.two_bc = d->conv_bc || !inputs_shared;
@@ -383,7 +450,7 @@ void launch_scan(const bimamba_desc* d, int split, int short_call, const SweepAr
 
 int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* pb, const bimamba_inputs* in_f,
         const bimamba_inputs* in_b, const float* h_in, const void* tail_in, float* h_out, void* tail_out,
-        const bimamba_tensor* out, void* workspace, size_t workspace_bytes, void* hip_stream, bool block_variant)
+        const bimamba_tensor* out, void* workspace, size_t workspace_bytes, void* hip_stream, bool block_variant, bool coarse = false)
 {
     const hipEvent_t probe_start = g_probe_start, probe_stop = g_probe_stop;
     g_probe_start = g_probe_stop = nullptr;
@@ -401,7 +468,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
     if (!is_aligned(h_in, 4) || !is_aligned(h_out, 4) || !is_aligned(tail_in, elem) || !is_aligned(tail_out, elem))
         return BIMAMBA_ERR_MISALIGNED;
     const bool shared = same_inputs(in_f, in_b);
-    Plan plan = make_plan(d, shared);
+    Plan plan = make_plan(d, shared, coarse);
     // the chunked kernels read x two channels at a time and the carried state four states at a time
     if (plan.ssd && !(pairs_readable(in_f->x) && pairs_readable(in_b->x) && is_aligned(h_in, 16) && is_aligned(h_out, 16)))
         plan.ssd = false;
@@ -679,11 +746,13 @@ int bimamba_block_fwd_static(const bimamba_desc* desc, const bimamba_params* pf,
 {
     int rc = check_desc(desc);
     if (rc) return rc;
-    if (make_plan(desc, false).total > (size_t)BIMAMBA_STATIC_SCRATCH_BYTES) return BIMAMBA_ERR_SCRATCH_EXCEEDED;
+    // The limit is stated for the general rule's segments; a call that fits only with those gets them.
+    if (make_plan(desc, false, true).total > (size_t)BIMAMBA_STATIC_SCRATCH_BYTES) return BIMAMBA_ERR_SCRATCH_EXCEEDED;
+    const bool coarse = make_plan(desc, false).total > (size_t)BIMAMBA_STATIC_SCRATCH_BYTES;
     void* ws = nullptr;
     if ((rc = static_scratch(&ws))) return rc;
     return run(desc, pf, pb, in_f, in_b, h_in, tail_in, h_out, tail_out, out, ws, BIMAMBA_STATIC_SCRATCH_BYTES, hip_stream,
-               true);
+               true, coarse);
 }
 
 // ---- gradients -------------------------------------------------------------------------------------------------
