@@ -656,8 +656,8 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
         sa.h_in = block_variant ? h_in : nullptr;
         sa.h_out = block_variant ? h_out : nullptr;
         sa.tail_in = block_variant ? tail_in : nullptr;
-        if (block_variant && tail_out && plan.nseg == 1 && d->d_conv > 1 && !d->conv_bc) {
-            sa.tail_out = tail_out;   // one segment: its forward walk ends with the tail in registers
+        if (block_variant && one_launch && d->d_conv > 1) {
+            sa.tail_out = tail_out;   // the forward walk of a short call ends with the tail in registers
             tail_out = nullptr;
         }
         sa.carry = reinterpret_cast<float*>(ws + plan.off_carry);

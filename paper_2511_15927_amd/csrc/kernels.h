@@ -55,7 +55,6 @@ struct SweepArgs {
     const float* h_in;    // [batch][Dn][N] or null
     float* h_out;         // or null; written by the sweep only when nseg == 1
     const void* tail_in;  // io dtype [batch][K-1][tail_ch] or null
-    void* tail_out;       // or null; written by the sweep only when nseg == 1, and its x channels only
     float* carry;         // [2][batch][nseg][Dn][N]: segment end states (summary) then segment start states (carry)
     float* sumdt;         // [2][batch][nseg][Dn]
     int L, Dn, P, HG, G, K, nseg, seg_len, tail_ch;
@@ -64,6 +63,7 @@ struct SweepArgs {
     int try_progression;  // let each wave test whether its chains' A rows are arithmetic in n (see sweep_kernel)
     int layer_wgs;        // workgroups the dispatcher places before a CU gets its next one (the CU count); set by the launcher
     int turn_mask;        // 0: leave wave priorities alone; 1 / 3: two / up to four waves share a SIMD and take turns
+    void* tail_out;       // or null; written by the short form of the sweep (kBcStaged)
 };
 
 // Buffer resource of a raw (untyped, unstrided) range starting at a wave-uniform address.  An access adds a
@@ -1215,19 +1215,21 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, float* lds_all, c
         if (a.raw_partial) run_range<N, S, AKIND, IO, kModeFinalAddRaw, TILE, BCSRC>(a, c, len - n_first, sp, lds, lane);
         else run_range<N, S, AKIND, IO, kModeFinalAdd, TILE, BCSRC>(a, c, len - n_first, sp, lds, lane);
     }
-    if (a.nseg == 1 && (a.h_out || a.tail_out)) {
-        // Waves past the last tile shadow it: all have read h_in and tail_in, which the commit may overwrite, before any
-        // of them gets here (with the halves apart no barrier came before).
-        if (a.separate) __syncthreads();
-        if (s == 0 && a.h_out) {
-            float* dst = a.h_out + ((size_t)b * a.Dn + ch) * N + sub * NS;
+    // Waves past the last tile shadow it: all have read h_in and tail_in, which the commit of a short call may overwrite
+    // right away, before any of them gets here (with the halves apart no barrier came before).
+    if constexpr (BCSRC == kBcStaged)
+        if (a.separate && (a.h_out || a.tail_out)) __syncthreads();
+    if (s == 0 && a.nseg == 1 && a.h_out) {
+        float* dst = a.h_out + ((size_t)b * a.Dn + ch) * N + sub * NS;
 #pragma unroll
-            for (int n = 0; n < NS; n++) dst[n] = c.h[n];
-        }
-        // The conv window left by the forward walk is the tail: raw tokens, so cutting the fp32 form back to the I/O
-        // dtype restores their bits.  A launch of its own for it cost 4.0 us and its gap: 26.4 -> 23.8 us for a 32-token
-        // block step that commits (batch 16, d_inner 4096).
-        if (s == 0 && a.tail_out && sub == 0) {
+        for (int n = 0; n < NS; n++) dst[n] = c.h[n];
+    }
+    // Short calls commit the conv tail too: it is the window the forward walk leaves, raw tokens, so cutting the fp32 form
+    // back to the I/O dtype restores their bits.  A launch of its own for it cost 4.0 us: 26.4 -> 23.8 us for a 32-token
+    // block step that commits (batch 16, d_inner 4096).  Only here: the window kept alive through the end of the long walks,
+    // or read again behind them, cost those 0.5 % (8 x 2048 and 8 x 8192 tokens).
+    if constexpr (BCSRC == kBcStaged) {
+        if (s == 0 && a.tail_out) {
             T* dst = (T*)a.tail_out + (size_t)b * (a.K - 1) * a.tail_ch + ch;
 #pragma unroll
             for (int i = 0; i < 3; i++)

@@ -47,7 +47,9 @@ static void wide_variant(const SsdStatePair& sp, int batch, hipStream_t st)
     auto kernel = ssd_wide_kernel<N, P, DIRS>;
     if (first_use_on_current_device(seen))
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)sp.dir[0].H, (unsigned)DIRS, (unsigned)batch), dim3(SsdWide<N, P>::kThreads), lds, st, sp);
+    const dim3 grid((unsigned)sp.dir[0].H, (unsigned)DIRS, (unsigned)batch), block(SsdWide<N, P>::kThreads);
+    if constexpr (DIRS == 1) hipLaunchKernelGGL(kernel, grid, block, lds, st, sp.dir[0]);
+    else hipLaunchKernelGGL(kernel, grid, block, lds, st, sp);
 }
 
 // Long calls that leave at least half of the CUs empty (batch 1 or 2) split the producers into two groups, which

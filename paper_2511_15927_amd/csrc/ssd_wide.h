@@ -25,12 +25,15 @@ struct SsdWide {
     static constexpr int kThreads = 64 * (kYWaves + kHWaves + kProdWaves);
 };
 
-// DIRS: one launch per direction (dir[0]) or both at once (see launch_ssd_scan); compiled apart, since selecting the arguments
+// DIRS: one launch per direction or both at once (see launch_ssd_scan); compiled apart, since selecting the arguments
 // at run time cost the launches of one direction 0.5 %.
 template <int N, int P, int DIRS>
-__global__ __launch_bounds__((SsdWide<N, P>::kThreads)) void ssd_wide_kernel(const SsdStatePair launch)
+__global__ __launch_bounds__((SsdWide<N, P>::kThreads)) void ssd_wide_kernel(const std::conditional_t<DIRS == 1, SsdArgs, SsdStatePair> launch)
 {
-    const SsdArgs& a = launch.dir[DIRS == 1 ? 0 : blockIdx.y];
+    const SsdArgs& a = [&]() -> const SsdArgs& {
+        if constexpr (DIRS == 1) return launch;
+        else return launch.dir[blockIdx.y];
+    }();
     using Lds = SsdLds<N, P, false>;
     using W = SsdWide<N, P>;
     constexpr int kPB = W::kPB, kNB = W::kNB;

@@ -252,9 +252,9 @@ def test_first_call_in_a_process_captured_into_a_graph(layout):
 @pytest.mark.parametrize("L", [1, 2, 3, 7, 41])
 @pytest.mark.parametrize("split,N,K,io", [(1, 16, 4, "bf16"), (2, 16, 3, "bf16"), (4, 16, 4, "f32"), (1, 32, 2, "f32"), (4, 64, 4, "bf16")])
 def test_tail_committed_by_the_sweep(gpu, oracle, L, split, N, K, io):
-    """One-segment sweeps store the conv tail themselves: calls shorter and longer than the tail, with and without one to
-    start from, an odd number of channel tiles, the halves added and kept apart, committed in place; and the same call cut
-    into segments, which leaves the tail to its own launch."""
+    """The short form of the sweep (one lane per chain, up to 16 states) stores the conv tail itself: calls shorter and longer
+    than the tail, with and without one to start from, an odd number of channel tiles, the halves added and kept apart,
+    committed in place; other forms and calls cut into segments leave the tail to its own launch."""
     from paper_2511_15927_amd import binding as bd
     cfg = synth.mixer_cfg(2, L, 64 + 3 * (64 // split) // 2, d_state=N, d_conv=K, io=io, combine=L % 2)
     pf, pb = params(cfg, 77 + L)

@@ -285,3 +285,25 @@ def test_output_as_a_column_slice_of_the_inputs_buffer(gpu, oracle):
     assert torch.equal(big[:, :, keep], before[:, :, keep])
     clash = big[:, :, Dn // 2:Dn // 2 + Dn]                       # straddles z and x
     assert bd.bimamba_fwd(*args, bd.make_tensor(clash), ws, check=False) == -8
+
+
+@pytest.mark.parametrize("batch,L,Dn,N,io", [
+    (1, 257, 512, 16, "f32"),        # too short to cut: two lanes per chain, whole
+    (2, 777, 320, 16, "bf16"),       # two lanes per chain, segments of 24 tokens or more, a ragged last one
+    (1, 2051, 640, 16, "f32"),       # the same with a few tokens more than whole segments
+    (1, 3001, 1024, 16, "bf16"),     # one round of one-lane segments
+    (4, 8191, 192, 16, "bf16"),      # four rounds
+    (3, 900, 3072, 16, "f32"),       # whole: two waves per SIMD at most
+    (1, 300, 512, 8, "f32"), (2, 530, 640, 8, "bf16"), (1, 1601, 456, 4, "f32")])   # no lane splitting below 16 states
+@pytest.mark.parametrize("combine", [0, 1])
+def test_geometry_left_to_the_library(gpu, oracle, batch, L, Dn, N, io, combine):
+    """Every kind of geometry the cost rule picks, against the oracle, and against one segment with one lane per chain."""
+    cfg = synth.mixer_cfg(batch, L, Dn, d_state=N, io=io, combine=combine)
+    pf, pb = synth.make_params(cfg, L, 0), synth.make_params(cfg, L, 1)
+    if L % 2:
+        pf["A"], pb["A"] = synth.random_A(cfg, L), synth.random_A(cfg, L + 1)
+    inp = synth.make_inputs(cfg, L)
+    sel = sorted(np.random.default_rng(L).choice(Dn, size=24, replace=False).tolist())
+    ref = oracle.bimamba_fwd(cfg, to_np(pf), to_np(pb), to_np(inp), sel=sel)
+    assert_close(gpu.gpu_fwd(cfg, pf, pb, inp)[..., sel], ref, gpu.TOL[io])
+    assert_close(gpu.gpu_fwd(cfg, pf, pb, inp, state_split=1, time_chunks=1)[..., sel], ref, gpu.TOL[io])
