@@ -228,7 +228,7 @@ def bwd_bench(args, torch, bd, shapes, synth):
                    "workspace_bytes": int(ws.numel())},
         "roofline": {"bound": "alu", "achieved": ach, "peak": PEAK_FP32_VECTOR_TFLOPS, "unit": "TFLOP/s",
                      "frac": ach / PEAK_FP32_VECTOR_TFLOPS, "algorithmic_flops": flops, "traffic": None,
-                     "kernel": "bwd_state_kernel + bwd_kernel + bwd_bc_kernel (whole call)", "kernel_ms": ms,
+                     "kernel": "bwd_state_kernel + bwd_kernel + bwd_sum_kernel (whole call)", "kernel_ms": ms,
                      "frac_of_unpacked_fp32_peak": ach / PEAK_FP32_UNPACKED_TFLOPS},
         "hbm": {"achieved": nbytes / (ms * 1e-3) / 1e9, "peak": PEAK_HBM_GBPS, "unit": "GB/s",
                 "frac": nbytes / (ms * 1e-3) / 1e9 / PEAK_HBM_GBPS, "algorithmic_bytes": nbytes},
