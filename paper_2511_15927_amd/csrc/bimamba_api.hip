@@ -262,7 +262,7 @@ Geometry pick_geometry(const bimamba_desc* d)
     return {1, 1};
 }
 
-// coarse: by the general rule whatever the state count (see bimamba_block_fwd_static).
+// coarse: by the general rule whatever the state count (see make_plan).
 Geometry geometry_of(const bimamba_desc* d, bool coarse)
 {
     const int split = pick_split_general(d);
@@ -295,7 +295,7 @@ bool use_ssd(const bimamba_desc* d)
            d->batch <= 32767;   // the preparation kernel's grid holds both directions of every batch element
 }
 
-Plan make_plan(const bimamba_desc* d, bool inputs_shared, bool coarse = false)
+Plan plan_of(const bimamba_desc* d, bool inputs_shared, bool coarse)
 {
     Plan p{};
     // The lane-per-chain geometry is always planned (and its workspace reserved): a call whose x tensors do not meet
@@ -367,6 +367,16 @@ Plan make_plan(const bimamba_desc* d, bool inputs_shared, bool coarse = false)
     }
     p.total = off;
     return p;
+}
+
+// The plan of a call, the same for every entry point.  Segments by cost can be more than the general rule's and so can their
+// states; a call that fits the fixed scratch of bimamba_block_fwd_static only with the general rule's gets those.
+// (Decided on the size for separate activations: a call must not plan more than bimamba_workspace_bytes said.)
+Plan make_plan(const bimamba_desc* d, bool inputs_shared)
+{
+    constexpr size_t kScratch = BIMAMBA_STATIC_SCRATCH_BYTES;
+    const bool coarse = plan_of(d, false, false).total > kScratch && plan_of(d, false, true).total <= kScratch;
+    return plan_of(d, inputs_shared, coarse);
 }
 
 constexpr int64_t kMaxTokenStride = 1 << 26;  // elements
@@ -450,7 +460,7 @@ void launch_scan(const bimamba_desc* d, int split, int short_call, const SweepAr
 
 int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* pb, const bimamba_inputs* in_f,
         const bimamba_inputs* in_b, const float* h_in, const void* tail_in, float* h_out, void* tail_out,
-        const bimamba_tensor* out, void* workspace, size_t workspace_bytes, void* hip_stream, bool block_variant, bool coarse = false)
+        const bimamba_tensor* out, void* workspace, size_t workspace_bytes, void* hip_stream, bool block_variant)
 {
     const hipEvent_t probe_start = g_probe_start, probe_stop = g_probe_stop;
     g_probe_start = g_probe_stop = nullptr;
@@ -468,7 +478,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
     if (!is_aligned(h_in, 4) || !is_aligned(h_out, 4) || !is_aligned(tail_in, elem) || !is_aligned(tail_out, elem))
         return BIMAMBA_ERR_MISALIGNED;
     const bool shared = same_inputs(in_f, in_b);
-    Plan plan = make_plan(d, shared, coarse);
+    Plan plan = make_plan(d, shared);
     // the chunked kernels read x two channels at a time and the carried state four states at a time
     if (plan.ssd && !(pairs_readable(in_f->x) && pairs_readable(in_b->x) && is_aligned(h_in, 16) && is_aligned(h_out, 16)))
         plan.ssd = false;
@@ -746,13 +756,11 @@ int bimamba_block_fwd_static(const bimamba_desc* desc, const bimamba_params* pf,
 {
     int rc = check_desc(desc);
     if (rc) return rc;
-    // The limit is stated for the general rule's segments; a call that fits only with those gets them.
-    if (make_plan(desc, false, true).total > (size_t)BIMAMBA_STATIC_SCRATCH_BYTES) return BIMAMBA_ERR_SCRATCH_EXCEEDED;
-    const bool coarse = make_plan(desc, false).total > (size_t)BIMAMBA_STATIC_SCRATCH_BYTES;
+    if (make_plan(desc, false).total > (size_t)BIMAMBA_STATIC_SCRATCH_BYTES) return BIMAMBA_ERR_SCRATCH_EXCEEDED;
     void* ws = nullptr;
     if ((rc = static_scratch(&ws))) return rc;
     return run(desc, pf, pb, in_f, in_b, h_in, tail_in, h_out, tail_out, out, ws, BIMAMBA_STATIC_SCRATCH_BYTES, hip_stream,
-               true, coarse);
+               true);
 }
 
 // ---- gradients -------------------------------------------------------------------------------------------------
