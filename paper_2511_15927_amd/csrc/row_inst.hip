@@ -10,15 +10,19 @@ namespace bm {
 // launches and its 100 instructions per dependent token are what a call waits for.  Measured against them (bf16,
 // d_inner 4096 unless stated, us, sweep / row): 1 x 32 tokens 14.1 / 6.8, 4 x 32 14.9 / 13.7, 8 x 32 17.7 / 24.1; 2 x 64
 // 18.8 / 12.5, 4 x 64 19.6 / 21.2; 1 x 128 26.6 / 16.9, 2 x 128 27.4 / 27.5; 1 x 256 49.6 / 38.2, d_inner 512 48.6 / 11.6.
+// Beyond 192 tokens against the sweep as pick_geometry plans it (1 x 212 tokens, 2688 channels 28.2 / 32.6; 1 x 220, 4112
+// channels 37.1 / 56.4; 1 x 256, 4096 34.6 / 37.8; 1 x 255, 3280 37.0 / 36.2) the line lies at 0.4 M channel tokens.
 constexpr long long kRowMaxChains = 16384, kRowMaxElements = 3LL << 18, kRowMaxElementsLong = 1LL << 20;
-constexpr int kRowLongTokens = 128;
+constexpr long long kRowMaxElementsLongest = 3LL << 17;
+constexpr int kRowLongTokens = 128, kRowLongestTokens = 192;
 constexpr size_t kRowLdsBytes = 160 * 1024;
 
 bool row_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f)
 {
     if (d_state > 16 || seqlen < 1 || seqlen > kRowMaxTokens) return false;
     const long long chains = (long long)batch * d_inner;
-    if (chains > kRowMaxChains || chains * seqlen > (seqlen > kRowLongTokens ? kRowMaxElementsLong : kRowMaxElements)) return false;
+    const long long most = seqlen > kRowLongestTokens ? kRowMaxElementsLongest : seqlen > kRowLongTokens ? kRowMaxElementsLong : kRowMaxElements;
+    if (chains > kRowMaxChains || chains * seqlen > most) return false;
     const long long tiles = (long long)batch * ((d_inner + 3) / 4);
     const int groups = (seqlen + kRowTokens - 1) / kRowTokens;
     // Time segments of two groups or more while that leaves the chip at most four waves per SIMD (a segment walked twice
