@@ -899,7 +899,6 @@ int bimamba_bwd(const bimamba_desc* d, const bimamba_params* pf, const bimamba_p
         a.nseg = plan.nseg; a.seg_len = plan.seg_len; a.seg_chunks = plan.seg_chunks; a.tiles = plan.tiles;
         a.dt_softplus = d->dt_softplus; a.separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
         a.park = shared;
-        a.try_progression = 1;
         a.bc_slots = plan.tiles_per_group * (shared ? 2 : 1);
         a.bc_slot_of_rev = shared ? plan.tiles_per_group : 0;
         bm::launch_bwd(d->d_state, bf16, a, d->batch, st);

@@ -21,9 +21,9 @@ bool bwd_supported(int d_state) { return d_state == 4 || d_state == 8 || d_state
 // Time segments of a gradient call and their length.  The walk holds two waves per SIMD, so a call is cut until it has
 // four rounds of them: the last round, which may be nearly empty, is then a small part of the call, and the state pass has
 // twice the four waves per SIMD it holds.  Measured at 4, 6, 8, 12, 16 waves per SIMD (bf16): d_inner 4096, batch 8 x 8192
-// tokens 10.4 / 10.7 / 10.2 / 10.2 / 10.1 ms; 3104 channels, batch 22 x 1036: 3.4 / 3.1 / 3.05 / 3.0 / 3.0; 2512 channels,
-// batch 2 x 5813: 1.63 / 1.48 / 1.48 / 1.50 / 1.54.  A segment costs the dh sum of the state pass and three tokens walked
-// twice, so segments stay at 32 tokens or more.
+// tokens 11.7 / 11.5 / 11.3 / 11.0 / 10.9 ms; 3104 channels, batch 22 x 1036: 3.55 / 3.31 / 3.20 / 3.02 / 3.16; 2512
+// channels, batch 2 x 5813: 1.57 / 1.38 / 1.39 / 1.36 / 1.36.  A segment costs the dh sum of the state pass and three tokens
+// walked twice, so segments stay at 32 tokens or more.
 constexpr int kBwdWavesPerSimd = 8;
 constexpr int kBwdMinSegment = 32;
 void bwd_segments(int d_inner, int batch, int seqlen, int* nseg, int* seg_len, int* seg_chunks)

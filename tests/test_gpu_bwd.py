@@ -2,7 +2,7 @@
 gradients, which are themselves pinned by finite differences and automatic differentiation (test_oracle_bwd_pins.py).
 
 Tolerances: a gradient tensor is compared in relative L2 over the whole tensor; fp32 I/O 2e-5 (fp32 arithmetic, sums of
-up to L * batch terms formed with atomics in arbitrary order), bf16 I/O 2e-2 for the tensors that are rounded to bf16
+up to L * batch terms formed in a fixed order), bf16 I/O 2e-2 for the tensors that are rounded to bf16
 (dx, dz, ddt) and 2e-5 for the fp32 ones (dB, dC and the parameter gradients see the same fp32 arithmetic in both modes).
 """
 import numpy as np
@@ -244,6 +244,78 @@ def test_more_waves_than_simds_takes_the_dense_form(gpu, oracle, N, L):
     """Batch 9 at d_inner 4096 is 1152 waves for 1024 SIMDs: the kernels built for two waves per SIMD (shorter chunks
     for 4 and 16 states) and the plan that sizes their stored states; every channel compared."""
     run_case(gpu, oracle, synth.mixer_cfg(9, L, 4096, d_state=N, io="bf16" if L % 2 else "f32"), 900 + N + L)
+
+
+def device_call(cfg, weights, acts, dout):
+    """bimamba_bwd on tensors that are on the GPU already, both directions reading the same activations."""
+    Bt, L, Dn, N, K = (cfg[k] for k in ("batch", "seqlen", "d_inner", "d_state", "d_conv"))
+    io = bd.io_dtype(cfg)
+    empty = lambda *s, dtype=torch.float32: torch.full(s, float("nan"), dtype=dtype, device="cuda")
+    gi = dict(dx=empty(Bt, L, Dn, dtype=io), dz=empty(Bt, L, Dn, dtype=io), ddt=empty(Bt, L, Dn, dtype=io),
+              dB=empty(Bt, L, 1, N), dC=empty(Bt, L, 1, N))
+    qs = [dict(dconv_w=empty(Dn, K), dconv_b=empty(Dn), dA=empty(Dn, N), dD=empty(Dn), ddt_bias=empty(Dn)) for _ in range(2)]
+    desc = bd.make_desc(cfg)
+    dev = [bd.to_device(w) for w in weights]
+    ws = torch.empty(bd.bimamba_bwd_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    bd.bimamba_bwd(desc, bd.make_params(dev[0]), bd.make_params(dev[1]), bd.make_inputs(acts), None, bd.make_tensor(dout),
+                   bd.make_input_grads(gi), None, bd.make_param_grads(qs[0]), bd.make_param_grads(qs[1]), ws)
+    torch.cuda.synchronize()
+    return gi, qs
+
+
+@pytest.mark.parametrize("N", [4, 8, 16])
+def test_a_channel_does_not_feel_its_neighbours_decay_rates(gpu, N):
+    """A channel's gradients depend on its own A row alone: with the rows of the other channels of its wave arithmetic in n
+    (as at initialisation) or not (as training leaves them), its fp32 gradients have the same bits, i.e. there is no second,
+    less exact form of the decay factors for waves whose rows are all arithmetic."""
+    cfg = synth.mixer_cfg(2, 150, 128, d_state=N, io="bf16", dt_softplus=1)
+    pf, pb = params(cfg, 5, random_a=False)
+    acts = bd.to_device(synth.make_inputs(cfg, 5), cfg)
+    dout = torch.randn(2, 150, 128, generator=torch.Generator().manual_seed(6)).to("cuda", torch.bfloat16)
+    before = device_call(cfg, (pf, pb), acts, dout)
+    touched = [5, 70]                    # one channel of each wave
+    for p in (pf, pb):
+        p["A"][touched] = p["A"][touched] * torch.linspace(0.8, 1.3, N)
+    after = device_call(cfg, (pf, pb), acts, dout)
+    keep = [c for c in range(128) if c not in touched]
+    for k in ("dx", "dz", "ddt"):
+        assert torch.equal(before[0][k][..., keep], after[0][k][..., keep]), k
+    for s in range(2):
+        for k in before[1][s]:
+            assert torch.equal(before[1][s][k][keep], after[1][s][k][keep]), (s, k)
+        assert not torch.equal(before[1][s]["dA"][touched], after[1][s]["dA"][touched])
+
+
+@pytest.mark.parametrize("io,random_a", [("bf16", False), ("bf16", True), ("f32", True)])
+def test_long_time_segments(gpu, oracle, io, random_a):
+    """8 x 8192 tokens of 4096 channels: segments of 1024 tokens, whose dh sums decay over far larger sums of Delta than
+    those of small calls.  dout is zero but for eight channels, so that the sums over channels are theirs alone and the
+    oracle needs only them."""
+    Bt, L, Dn = 8, 8192, 4096
+    cfg = synth.mixer_cfg(Bt, L, Dn, io=io)
+    weights = params(cfg, 15, random_a=random_a)
+    sel = [0, 63, 64, 130, 1000, 2047, 4000, 4095]
+    g = torch.Generator(device="cuda").manual_seed(16)
+    dtype = bd.io_dtype(cfg)
+    normal = lambda n: torch.randn(Bt, L, n, device="cuda", generator=g).to(dtype)
+    acts = dict(x=normal(Dn), z=normal(Dn), B=normal(16), C=normal(16))
+    acts["dt"] = torch.nn.functional.softplus(0.5 * torch.randn(Bt, L, Dn, device="cuda", generator=g) +
+                                              synth.dt_shift(cfg, 15).cuda()).to(dtype)
+    dout = torch.zeros(Bt, L, Dn, dtype=dtype, device="cuda")
+    dout[..., sel] = normal(len(sel))
+    gi, qs = device_call(cfg, weights, acts, dout)
+    host = lambda t: t.float().cpu().numpy().astype(np.float64)
+    got_in = {k: host(v[..., sel]) if k in ("dx", "dz", "ddt") else host(v) for k, v in gi.items()}
+    got_par = [{k: host(v[sel]) for k, v in q.items()} for q in qs]
+    for k in ("dx", "dz", "ddt"):        # the other channels' gradients are zero
+        others = gi[k].clone()
+        others[..., sel] = 0
+        assert not bool(others.any()), k
+    inp = {k: host(v[..., sel]) if k in ("x", "z", "dt") else host(v).reshape(Bt, L, 1, 16) for k, v in acts.items()}
+    small = synth.mixer_cfg(Bt, L, len(sel), io=io)
+    cut = [{k: None if v is None else to_np({k: v})[k][sel] for k, v in w.items()} for w in weights]
+    ref = oracle.bimamba_bwd(small, cut[0], cut[1], inp, None, host(dout[..., sel]))
+    compare(small, (got_in, None, *got_par), ref)
 
 
 def test_empty_call_zeroes_the_parameter_gradients(gpu, oracle):
