@@ -538,7 +538,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
             ra.same_bc = same_tensor(in_f->B, in_b->B) && same_tensor(in_f->C, in_b->C);
             ra.tw = row.tw; ra.tw_log2 = row.tw == 4 ? 2 : row.tw == 2 ? 1 : 0; ra.nseg = row.nseg; ra.seg_len = row.seg_len;
             if (probe_start) (void)hipEventRecord(probe_start, st);
-            launch_row(d->io_dtype == BIMAMBA_BF16, ra, d->batch, st);
+            if (launch_row(d->io_dtype == BIMAMBA_BF16, ra, d->batch, st) != hipSuccess) return BIMAMBA_ERR_HIP;
             if (probe_stop) (void)hipEventRecord(probe_stop, st);
         } else {
         // 1. fp32 B|C rows per direction (the chunked path prepares its own operand tiles from the raw rows)
@@ -901,7 +901,7 @@ int bimamba_bwd(const bimamba_desc* d, const bimamba_params* pf, const bimamba_p
         a.park = shared;
         a.bc_slots = plan.tiles_per_group * (shared ? 2 : 1);
         a.bc_slot_of_rev = shared ? plan.tiles_per_group : 0;
-        bm::launch_bwd(d->d_state, bf16, a, d->batch, st);
+        if (bm::launch_bwd(d->d_state, bf16, a, d->batch, st) != hipSuccess) return BIMAMBA_ERR_HIP;
         sum.sets = sets; sum.slots = a.bc_slots;
         sum.rows = (long long)d->batch * d->seqlen * d->n_groups;
         sum.param_part = a.param_part;

@@ -3,18 +3,7 @@
 #include "bwd_kernels.h"
 #include "launch.h"
 
-#include <atomic>
-
 namespace bm {
-
-// Raising a kernel's dynamic-LDS limit is idempotent; it is done once per (kernel, device).
-constexpr int kMaxDevices = 64;
-static bool first_use_on_current_device(std::atomic<bool>* seen)
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return true;
-    return !seen[dev].exchange(true);
-}
 
 bool bwd_supported(int d_state) { return d_state == 4 || d_state == 8 || d_state == 16; }
 
@@ -115,33 +104,33 @@ void launch_bwd_sum(const BwdSumArgs& a, hipStream_t st)
 }
 
 template <int N, typename IO>
-static void launch_walks(const BwdArgs& a, int batch, hipStream_t st)
+static hipError_t launch_walks(const BwdArgs& a, int batch, hipStream_t st)
 {
+    auto walk = bwd_kernel<N, IO>;
+    if (kBwdLdsBytes<N> > 64 * 1024) {
+        static LdsLimit limit;
+        const hipError_t err = limit.raise(reinterpret_cast<const void*>(walk), kBwdLdsBytes<N>);
+        if (err != hipSuccess) return err;
+    }
     const dim3 grid((unsigned)((a.tiles + 1) / 2), (unsigned)a.nseg, (unsigned)batch);
     hipLaunchKernelGGL((bwd_state_kernel<N, IO>), grid, dim3(256), 0, st, a);
     if (a.nseg > 1) {
         const long long threads = 2LL * batch * a.tiles * 64 * N;
         hipLaunchKernelGGL(bwd_carry_kernel<N>, dim3((unsigned)((threads + 255) / 256), 2), dim3(256), 0, st, a, batch);
     }
-    static std::atomic<bool> lifted[kMaxDevices];
-    auto walk = bwd_kernel<N, IO>;
-    if (kBwdLdsBytes<N> > 64 * 1024 && first_use_on_current_device(lifted))
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(walk), hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBwdLdsBytes<N>);
     hipLaunchKernelGGL(walk, grid, dim3(256), kBwdLdsBytes<N>, st, a);
+    return hipSuccess;
 }
 
-void launch_bwd(int d_state, int io_bf16, const BwdArgs& a, int batch, hipStream_t st)
+hipError_t launch_bwd(int d_state, int io_bf16, const BwdArgs& a, int batch, hipStream_t st)
 {
-#define BM_BWD(n)                                          \
-    case n:                                                \
-        if (io_bf16) launch_walks<n, IoBF16>(a, batch, st); \
-        else launch_walks<n, IoF32>(a, batch, st);          \
-        break;
+#define BM_BWD(n) \
+    case n: return io_bf16 ? launch_walks<n, IoBF16>(a, batch, st) : launch_walks<n, IoF32>(a, batch, st);
     switch (d_state) {
         BM_BWD(4)
         BM_BWD(8)
         BM_BWD(16)
-        default: break;
+        default: return hipErrorInvalidValue;
     }
 #undef BM_BWD
 }

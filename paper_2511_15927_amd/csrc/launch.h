@@ -2,7 +2,29 @@
 #pragma once
 #include "kernels.h"
 
+#include <atomic>
+
 namespace bm {
+// A launch with more than 64 KB of dynamic LDS is refused until its kernel's limit has been raised, once per device.  The flag
+// is published after the limit is up: a thread that finds it unset raises the limit itself (that is idempotent) instead of
+// launching under one that another thread is still raising.  A failure is the caller's to report; the next call tries again.
+class LdsLimit {
+public:
+    hipError_t raise(const void* kernel, size_t bytes)
+    {
+        int dev = -1;
+        const bool known = hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices;
+        if (known && raised_[dev].load(std::memory_order_acquire)) return hipSuccess;
+        const hipError_t err = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+        if (err == hipSuccess && known) raised_[dev].store(true, std::memory_order_release);
+        return err;
+    }
+
+private:
+    static constexpr int kMaxDevices = 64;
+    std::atomic<bool> raised_[kMaxDevices] = {};
+};
+
 // Compute units of the current device (256 when no device answers), asked once per device; defined in bimamba_api.hip
 // and used by the host-side plan and by every launcher, so that all of them size a launch for the same chip.
 int cu_count();
@@ -31,7 +53,7 @@ struct RowForm {
 };
 struct RowArgs;
 bool row_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f);
-void launch_row(int io_bf16, const RowArgs& a, int batch, hipStream_t st);
+hipError_t launch_row(int io_bf16, const RowArgs& a, int batch, hipStream_t st);   // (an error: nothing was launched)
 
 struct SsdPrepPair;
 struct SsdArgs;
@@ -50,6 +72,6 @@ struct BwdSumArgs;
 bool bwd_supported(int d_state);
 void bwd_segments(int d_inner, int batch, int seqlen, int* nseg, int* seg_len, int* seg_chunks);
 void launch_bwd_prep(int io_bf16, const BwdPrepArgs& a, int sets, hipStream_t st);
-void launch_bwd(int d_state, int io_bf16, const BwdArgs& a, int batch, hipStream_t st);
+hipError_t launch_bwd(int d_state, int io_bf16, const BwdArgs& a, int batch, hipStream_t st);   // (an error: nothing was launched)
 void launch_bwd_sum(const BwdSumArgs& a, hipStream_t st);
 }  // namespace bm

@@ -2,8 +2,6 @@
 #include "row_kernels.h"
 #include "launch.h"
 
-#include <atomic>
-
 namespace bm {
 
 // The row form spends about twice the vector work of the sweep on a chain and token and wins where the sweep's two to four
@@ -40,25 +38,23 @@ bool row_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f)
 static size_t lds_bytes(const RowArgs& a) { return (size_t)RowLds(a.L, a.same_bc ? 1 : 2, a.tw, a.nseg, a.seg_len).total * sizeof(float); }
 
 template <typename IO>
-static void launch_io(const RowArgs& a, int batch, hipStream_t st)
+static hipError_t launch_io(const RowArgs& a, int batch, hipStream_t st)
 {
-    constexpr int kMaxDevices = 64;
-    static std::atomic<bool> seen[kMaxDevices];
+    static LdsLimit limit;
     auto kernel = row_kernel<IO>;
     const size_t lds = lds_bytes(a);
-    if (lds > 64 * 1024) {   // raising the limit is idempotent; done once per device
-        int dev = 0;
-        if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices || !seen[dev].exchange(true))
-            (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (lds > 64 * 1024) {
+        const hipError_t err = limit.raise(reinterpret_cast<const void*>(kernel), kRowLdsBytes);
+        if (err != hipSuccess) return err;
     }
     const dim3 grid((unsigned)((a.Dn + 4 * a.tw - 1) / (4 * a.tw)), 1, (unsigned)batch);
     hipLaunchKernelGGL(kernel, grid, dim3((unsigned)(128 * a.nseg * a.tw)), lds, st, a);
+    return hipSuccess;
 }
 
-void launch_row(int io_bf16, const RowArgs& a, int batch, hipStream_t st)
+hipError_t launch_row(int io_bf16, const RowArgs& a, int batch, hipStream_t st)
 {
-    if (io_bf16) launch_io<IoBF16>(a, batch, st);
-    else launch_io<IoF32>(a, batch, st);
+    return io_bf16 ? launch_io<IoBF16>(a, batch, st) : launch_io<IoF32>(a, batch, st);
 }
 
 }  // namespace bm
