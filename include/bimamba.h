@@ -235,10 +235,12 @@ int bimamba_bwd(const bimamba_desc* desc, const bimamba_params* pf, const bimamb
  * token, channel) for the values one direction leaves for the other to add, and the per-wave partial sums of dB and dC. */
 size_t bimamba_bwd_workspace_bytes(const bimamba_desc* desc);
 
-/* Bytes of device scratch the two calls above need for this descriptor (0 on an invalid descriptor).  Pure host code. */
+/* Bytes of device scratch bimamba_fwd (block_variant 0) or bimamba_block_fwd (1) needs for this descriptor (0 on an invalid
+ * descriptor).  The two differ where a block call is held to segments that fit BIMAMBA_STATIC_SCRATCH_BYTES; the larger of
+ * them serves both.  Pure host code. */
 size_t bimamba_workspace_bytes(const bimamba_desc* desc, int block_variant);
 
-/* Number of pieces the library would cut the time axis into for this descriptor, each piece scanned by its own
+/* Number of pieces bimamba_fwd would cut the time axis into for this descriptor, each piece scanned by its own
  * workgroups and joined through a carry pass (>= 1; 0 on an invalid descriptor): the time segments of the
  * lane-per-chain kernels, or the time parts of the chunked matrix-core kernels, which are 1 unless a call has so
  * few (batch, head) pairs that they would leave half of the chip empty.  Pure host code. */

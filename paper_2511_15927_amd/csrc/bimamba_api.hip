@@ -369,14 +369,18 @@ Plan plan_of(const bimamba_desc* d, bool inputs_shared, bool coarse)
     return p;
 }
 
-// The plan of a call, the same for every entry point.  Segments by cost can be more than the general rule's and so can their
-// states; a call that fits the fixed scratch of bimamba_block_fwd_static only with the general rule's gets those.
+// The plan of a call that brings `bytes` of workspace.  Segments by cost can be more than the general rule's and so can their
+// states.  A block call that fits the fixed scratch of bimamba_block_fwd_static only with the general rule's gets those from
+// both block entry points, whose results are bit-identical; bimamba_fwd has no such twin and takes them only where the
+// caller's workspace, sized for the block call of the same shape, holds no more.
 // (Decided on the size for separate activations: a call must not plan more than bimamba_workspace_bytes said.)
-Plan make_plan(const bimamba_desc* d, bool inputs_shared)
+Plan make_plan(const bimamba_desc* d, bool inputs_shared, bool block_variant, size_t bytes)
 {
     constexpr size_t kScratch = BIMAMBA_STATIC_SCRATCH_BYTES;
-    const bool coarse = plan_of(d, false, false).total > kScratch && plan_of(d, false, true).total <= kScratch;
-    return plan_of(d, inputs_shared, coarse);
+    const Plan fine = plan_of(d, inputs_shared, false);
+    if (!block_variant && bytes >= fine.total) return fine;
+    const bool fits_coarse_only = plan_of(d, false, false).total > kScratch && plan_of(d, false, true).total <= kScratch;
+    return fits_coarse_only ? plan_of(d, inputs_shared, true) : fine;
 }
 
 constexpr int64_t kMaxTokenStride = 1 << 26;  // elements
@@ -478,7 +482,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
     if (!is_aligned(h_in, 4) || !is_aligned(h_out, 4) || !is_aligned(tail_in, elem) || !is_aligned(tail_out, elem))
         return BIMAMBA_ERR_MISALIGNED;
     const bool shared = same_inputs(in_f, in_b);
-    Plan plan = make_plan(d, shared);
+    Plan plan = make_plan(d, shared, block_variant, workspace_bytes);
     // the chunked kernels read x two channels at a time and the carried state four states at a time
     if (plan.ssd && !(pairs_readable(in_f->x) && pairs_readable(in_b->x) && is_aligned(h_in, 16) && is_aligned(h_out, 16)))
         plan.ssd = false;
@@ -756,7 +760,7 @@ int bimamba_block_fwd_static(const bimamba_desc* desc, const bimamba_params* pf,
 {
     int rc = check_desc(desc);
     if (rc) return rc;
-    if (make_plan(desc, false).total > (size_t)BIMAMBA_STATIC_SCRATCH_BYTES) return BIMAMBA_ERR_SCRATCH_EXCEEDED;
+    if (make_plan(desc, false, true, SIZE_MAX).total > (size_t)BIMAMBA_STATIC_SCRATCH_BYTES) return BIMAMBA_ERR_SCRATCH_EXCEEDED;
     void* ws = nullptr;
     if ((rc = static_scratch(&ws))) return rc;
     return run(desc, pf, pb, in_f, in_b, h_in, tail_in, h_out, tail_out, out, ws, BIMAMBA_STATIC_SCRATCH_BYTES, hip_stream,
@@ -921,16 +925,15 @@ size_t bimamba_bwd_workspace_bytes(const bimamba_desc* desc)
 
 size_t bimamba_workspace_bytes(const bimamba_desc* desc, int block_variant)
 {
-    (void)block_variant;
     if (check_desc(desc)) return 0;
     // sized for the larger case (the two directions reading different activations)
-    return make_plan(desc, false).total;
+    return make_plan(desc, false, block_variant != 0, SIZE_MAX).total;
 }
 
 int bimamba_time_chunks(const bimamba_desc* desc)
 {
     if (check_desc(desc)) return 0;
-    const Plan p = make_plan(desc, true);
+    const Plan p = make_plan(desc, true, false, SIZE_MAX);
     return p.ssd ? p.ssd_parts : p.nseg;
 }
 

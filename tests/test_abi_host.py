@@ -141,6 +141,17 @@ def test_workspace_and_chunk_planning():
     assert bd.bimamba_workspace_bytes(d1) % 256 == 0
 
 
+@pytest.mark.parametrize("batch,L,Dn", [(4, 1931, 1600), (7, 635, 2944), (5, 4345, 512)])
+def test_full_sequence_calls_are_not_planned_for_the_static_scratch(batch, L, Dn):
+    """Calls whose segments by cost need a little more than the fixed scratch of the static block entry point: the block
+    variant is held to segments that fit it, a full-sequence call is not.  Its segments are those of the same call without a
+    partial buffer, which fits the scratch anyway."""
+    add, sep = (bd.make_desc(synth.mixer_cfg(batch, L, Dn, combine=c)) for c in (0, 1))
+    assert bd.bimamba_workspace_bytes(sep, 0) == bd.bimamba_workspace_bytes(sep, 1) < bd.STATIC_SCRATCH_BYTES
+    assert bd.bimamba_workspace_bytes(add, 1) <= bd.STATIC_SCRATCH_BYTES < bd.bimamba_workspace_bytes(add, 0)
+    assert bd.bimamba_time_chunks(add) == bd.bimamba_time_chunks(sep)
+
+
 def test_time_parts_of_the_matrix_core_path():
     # 64 heads: batch 1 leaves 3/4 of the CUs empty -> 4 parts; batch 2 -> 2; batch 4 fills the chip -> 1.
     parts = {b: bd.bimamba_time_chunks(bd.make_desc(synth.m2_cfg(b, 8192, 4096))) for b in (1, 2, 3, 4, 8)}

@@ -4,6 +4,7 @@ committed conv tail must be bit-identical.  Two calls in a row share the buffer,
 import pytest
 import torch
 
+from helpers import assert_close
 from paper_2511_15927_amd import synth
 
 pytestmark = pytest.mark.gpu
@@ -72,9 +73,20 @@ def test_static_scratch_rejects_calls_beyond_its_size():
 @pytest.mark.parametrize("batch,L,Dn", [(4, 1931, 1600), (7, 635, 2944), (5, 4345, 512)])
 def test_static_scratch_takes_what_the_general_rule_fits(batch, L, Dn):
     """Calls whose segments by cost would need a little more than the scratch: planned with the general rule's segments, by
-    both entry points, instead of being refused by one."""
+    both entry points, instead of being refused by one.  A full-sequence call with a workspace of that size runs too."""
     from paper_2511_15927_amd import binding as bd
     assert torch.cuda.is_available(), "these tests need the MI355X"
     cfg = synth.mixer_cfg(batch, L, Dn)
     assert 0.9 * bd.STATIC_SCRATCH_BYTES < bd.bimamba_workspace_bytes(bd.make_desc(cfg), 1) <= bd.STATIC_SCRATCH_BYTES
     both_ways(bd, cfg, 61)
+    desc = bd.make_desc(cfg)
+    small, full = bd.alloc_workspace(desc, 1), bd.alloc_workspace(desc, 0)
+    assert small.numel() < full.numel()
+    dpf, dpb = bd.to_device(synth.make_params(cfg, 61, 0)), bd.to_device(synth.make_params(cfg, 61, 1))
+    dinp, res = bd.to_device(synth.make_inputs(cfg, 61), cfg), []
+    for ws in (small, full):
+        out = bd.alloc_out(cfg).fill_(float("nan"))
+        bd.bimamba_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp), None, bd.make_tensor(out), ws)
+        torch.cuda.synchronize()
+        res.append(out.float().cpu().numpy())
+    assert_close(res[0], res[1], 2 ** -8)    # both round the same fp32 value, give or take its last bits, to bf16
