@@ -8,7 +8,9 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <cstdlib>
 
 // Device memory of bimamba_block_fwd_static, the entry point for callers that cannot allocate: one copy per GPU, held
@@ -219,9 +221,15 @@ int pick_chunks_general(const bimamba_desc* d, int split)
 //   8 states   whole 4 + 0.33 L;  segments 35 + 0.21 w L (w >= 1.4 waves per SIMD: always whole)
 // Segments fill rounds of resident workgroups (four waves per SIMD with one lane per chain) exactly: one workgroup more than
 // a round holds costs a round.  Four rounds while segments keep 128 tokens, else one round of segments of 48 (16 states)
-// or 16 tokens; too few tokens for that: two lanes per chain, three waves per SIMD, segments of 24 or more.
-// Over 308 calls of 16 states (512 to 4096 channels, batch 1 to 48, 64 to 16384 tokens, bf16 and fp32) the choice is
-// on average 1.4 % slower than the best of all geometries, the general rule 19 %; over 98 calls of 8 states 5 % and 34 %.
+// or 16 tokens; too few tokens for that: two lanes per chain, three waves per SIMD, segments of 24 or more.  The carry folds
+// the segments one after the other, so the shortest segment grows with the root of the sequence, and a call too narrow to
+// fill one workgroup per CU even with those gets no more of them (1 x 1928 tokens of 256 channels, 8 states: whole 519 us,
+// 15 segments 83, 84 segments 36; 1 x 16384 tokens of 64 channels: 1024 segments 128, 128 segments 94, 256 segments 72).
+// Over 491 calls (8 and 16 states, 512 to 4096 channels, batch 1 to 48, 64 to 16384 tokens, bf16 and fp32) the choice is on
+// average 2.0 % slower than the best of twenty geometries with 16 states and 4.4 % with 8, the general rule 25 % and 31 %.
+// Beside the general rule alone, 240 calls of 256 to 4096 channels, decays per state or per head, bf16 or fp32: 24 to 30 %
+// less time with 4 states, 24 to 32 % with 8, 14 to 20 % with 16, the worst call 20 % more; 240 calls of 16 to 2048 channels
+// at batch 1 to 8: 41 to 46 % less, the worst 1 % more.
 struct Geometry {
     int split, nseg;
 };
@@ -243,23 +251,26 @@ Geometry pick_geometry(const bimamba_desc* d)
         return (int)(n < 1 ? 1 : n > L ? L : n);
     };
     auto tokens_of = [&](int n) { return L / n; };
+    const double root = (pair ? 0.65 : 0.5) * std::sqrt(tokens);
     int n = segments(1, 16);
     if (n > 1 && tokens_of(n) >= 128) return {1, n};
-    const int shortest = pair ? 48 : 16;
+    auto at_most = [&](int n, double shortest) { return std::min(n, std::max(1, (int)(tokens / shortest))); };
     if (pair) {
         n = segments(1, 4);
-        if (n > 1 && tokens_of(n) >= shortest) return {1, n};
-        for (int layers = 3; layers > 0; layers--) {
+        if (n > 1 && tokens_of(n) >= std::max(48.0, root)) return {1, n};
+        const double shortest = std::max(24.0, root);
+        for (int layers = 3; layers > 1; layers--) {
             n = segments(2, layers);
-            if (tokens_of(n) >= 24) return {2, n};
+            if (tokens_of(n) >= shortest) return {2, n};
         }
-        return {2, n > L / 16 ? 1 : n};
+        return {2, at_most(segments(2, 1), std::max(16.0, root))};
     }
-    for (int layers = 4; layers > 0; layers--) {
+    const double shortest = std::max(16.0, root);
+    for (int layers = 4; layers > 1; layers--) {
         n = segments(1, layers);
         if (n > 1 && tokens_of(n) >= shortest) return {1, n};
     }
-    return {1, 1};
+    return {1, at_most(segments(1, 1), shortest)};
 }
 
 // coarse: by the general rule whatever the state count (see make_plan).

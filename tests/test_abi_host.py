@@ -152,6 +152,16 @@ def test_full_sequence_calls_are_not_planned_for_the_static_scratch(batch, L, Dn
     assert bd.bimamba_time_chunks(add) == bd.bimamba_time_chunks(sep)
 
 
+@pytest.mark.parametrize("N", [4, 8, 16])
+@pytest.mark.parametrize("batch,L,Dn", [(1, 300, 64), (3, 600, 128), (1, 1928, 256), (2, 6000, 256), (1, 16384, 64), (1, 32768, 16)])
+def test_narrow_sequences_are_cut_into_segments(batch, L, Dn, N):
+    """Calls with too few chains to fill the chip, however short the segments: they are cut all the same, into segments of at
+    least half the root of the sequence (the carry folds them one after the other), not walked whole."""
+    n = bd.bimamba_time_chunks(bd.make_desc(synth.mixer_cfg(batch, L, Dn, d_state=N)))
+    assert 8 <= n <= 2 * L ** 0.5, n
+    assert 16 <= L // n
+
+
 def test_time_parts_of_the_matrix_core_path():
     # 64 heads: batch 1 leaves 3/4 of the CUs empty -> 4 parts; batch 2 -> 2; batch 4 fills the chip -> 1.
     parts = {b: bd.bimamba_time_chunks(bd.make_desc(synth.m2_cfg(b, 8192, 4096))) for b in (1, 2, 3, 4, 8)}
