@@ -457,6 +457,13 @@ bool short_call(const bimamba_desc* d, const Plan& plan)
            d->seqlen <= kShortCallTokens;
 }
 
+// A short call with few chains takes the one-row-per-chain form: everything in one launch.
+bool row_call(const bimamba_desc* d, const Plan& plan, RowForm* row)
+{
+    return !plan.ssd && !d->conv_bc && d->time_chunks == 0 && d->state_split == 0 &&
+           row_form(d->batch, d->seqlen, d->d_inner, d->d_state, row);
+}
+
 void launch_scan(const bimamba_desc* d, int split, int short_call, const SweepArgs& sa, const CarryArgs& ca,
                  hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
@@ -526,10 +533,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
 
     if (d->batch > 0 && d->seqlen > 0) {
         RowForm row;
-        const bool whole_call = !plan.ssd && !d->conv_bc && d->time_chunks == 0 && d->state_split == 0 &&
-                                row_form(d->batch, d->seqlen, d->d_inner, d->d_state, &row);
-        if (whole_call) {
-            // a short call with few chains: everything in one launch, the commit of the conv tail included
+        if (row_call(d, plan, &row)) {   // the commit of the conv tail is part of the launch too
             RowArgs ra{};
             for (int s = 0; s < 2; s++) {
                 const bimamba_inputs* in = s == 0 ? in_f : in_b;
@@ -945,7 +949,8 @@ int bimamba_time_chunks(const bimamba_desc* desc)
 {
     if (check_desc(desc)) return 0;
     const Plan p = make_plan(desc, true, false, SIZE_MAX);
-    return p.ssd ? p.ssd_parts : p.nseg;
+    RowForm row;
+    return p.ssd ? p.ssd_parts : row_call(desc, p, &row) ? 1 : p.nseg;
 }
 
 void bimamba_profile_next_call(void* ev_start, void* ev_stop)

@@ -131,6 +131,7 @@ def test_workspace_and_chunk_planning():
     assert bd.bimamba_time_chunks(bd.make_desc(synth.CONFIGS["cfg3_block"])) == 1
     assert bd.bimamba_time_chunks(bd.make_desc(synth.mixer_cfg(1, 100, 64, time_chunks=7))) == 7
     assert bd.bimamba_time_chunks(bd.make_desc(synth.mixer_cfg(1, 5, 64, time_chunks=7))) == 5
+    assert bd.bimamba_time_chunks(bd.make_desc(synth.mixer_cfg(1, 256, 512))) == 1     # one launch, no segments across workgroups
     # batch sweep at d_inner 4096 (w = 128 waves per batch element with one lane per chain): whole sequence with two
     # lanes per chain from 1.7 to 5 waves per SIMD (batch 7-20), with one lane per chain above, time segments below
     chunks = {b: bd.bimamba_time_chunks(bd.make_desc(synth.mixer_cfg(b, 8192, 4096))) for b in (1, 4, 6, 7, 8, 12, 16, 20, 21, 24, 64)}
