@@ -8,19 +8,28 @@ namespace bm {
 // launches and its 100 instructions per dependent token are what a call waits for.  Measured against them (bf16,
 // d_inner 4096 unless stated, us, sweep / row): 1 x 32 tokens 14.1 / 6.8, 4 x 32 14.9 / 13.7, 8 x 32 17.7 / 24.1; 2 x 64
 // 18.8 / 12.5, 4 x 64 19.6 / 21.2; 1 x 128 26.6 / 16.9, 2 x 128 27.4 / 27.5; 1 x 256 49.6 / 38.2, d_inner 512 48.6 / 11.6.
-// Beyond 192 tokens against the sweep as pick_geometry plans it (1 x 212 tokens, 2688 channels 28.2 / 32.6; 1 x 220, 4112
-// channels 37.1 / 56.4; 1 x 256, 4096 34.6 / 37.8; 1 x 255, 3280 37.0 / 36.2) the line lies at 0.4 M channel tokens.
-constexpr long long kRowMaxChains = 16384, kRowMaxElements = 3LL << 18, kRowMaxElementsLong = 1LL << 20;
+// Against the sweep as pick_geometry plans it, 1000 calls inside the limits (4, 8 and 16 states, decays per state or per
+// head, bf16 and fp32, which differ little), time of the row form over the sweep's, by chains (batch * d_inner):
+//   beyond 12288 chains   4 states 1.2 to 1.4 up to 24 tokens, 1.0 to 1.3 beyond; 8 states 1.1 to 1.3 up to 24 tokens, 0.9 to
+//                         1.0 beyond; 16 states 0.75 to 1.0: not taken with 4 states, with 8 from 25 tokens on
+//   129 to 192 tokens     with 4 / 8 / 16 states up to 4096 chains 0.65 / 0.56 / 0.51, beyond them 1.14 / 0.94 / 0.94: 4 states
+//                         stop at 0.75 M channel tokens, the others at 1 M
+//   193 to 256 tokens     up to 0.4 M channel tokens 0.56 / 0.48 / 0.50, the worst call 0.81; beyond (bf16, 16 states) 1 x 212
+//                         tokens of 2688 channels 28.2 us / 32.6, 1 x 220 of 4112 37.1 / 56.4, 1 x 256 of 4096 34.6 / 37.8
+constexpr long long kRowMaxChains = 16384, kRowMaxChainsFew = 3LL << 12, kRowMaxElements = 3LL << 18, kRowMaxElementsLong = 1LL << 20;
 constexpr long long kRowMaxElementsLongest = 3LL << 17;
-constexpr int kRowLongTokens = 128, kRowLongestTokens = 192;
+constexpr int kRowFewTokens = 24, kRowLongTokens = 128, kRowLongestTokens = 192;
 constexpr size_t kRowLdsBytes = 160 * 1024;
 
 bool row_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f)
 {
     if (d_state > 16 || seqlen < 1 || seqlen > kRowMaxTokens) return false;
     const long long chains = (long long)batch * d_inner;
-    const long long most = seqlen > kRowLongestTokens ? kRowMaxElementsLongest : seqlen > kRowLongTokens ? kRowMaxElementsLong : kRowMaxElements;
-    if (chains > kRowMaxChains || chains * seqlen > most) return false;
+    const long long most = seqlen > kRowLongestTokens                 ? kRowMaxElementsLongest
+                           : seqlen > kRowLongTokens && d_state >= 8 ? kRowMaxElementsLong
+                                                                     : kRowMaxElements;
+    const long long most_chains = d_state < 8 || (d_state < 16 && seqlen <= kRowFewTokens) ? kRowMaxChainsFew : kRowMaxChains;
+    if (chains > most_chains || chains * seqlen > most) return false;
     const long long tiles = (long long)batch * ((d_inner + 3) / 4);
     const int groups = (seqlen + kRowTokens - 1) / kRowTokens;
     // Time segments of two groups or more while that leaves the chip at most four waves per SIMD (a segment walked twice

@@ -132,6 +132,9 @@ def test_workspace_and_chunk_planning():
     assert bd.bimamba_time_chunks(bd.make_desc(synth.mixer_cfg(1, 100, 64, time_chunks=7))) == 7
     assert bd.bimamba_time_chunks(bd.make_desc(synth.mixer_cfg(1, 5, 64, time_chunks=7))) == 5
     assert bd.bimamba_time_chunks(bd.make_desc(synth.mixer_cfg(1, 256, 512))) == 1     # one launch, no segments across workgroups
+    # (the one-launch form costs 4 states as much as 16, the segments do not: beyond 0.75 M channel tokens they are cut)
+    short = {n: bd.bimamba_time_chunks(bd.make_desc(synth.mixer_cfg(2, 181, 2864, d_state=n))) for n in (4, 8, 16)}
+    assert short[4] > 1 and short[8] == short[16] == 1, short
     # batch sweep at d_inner 4096 (w = 128 waves per batch element with one lane per chain): whole sequence with two
     # lanes per chain from 1.7 to 5 waves per SIMD (batch 7-20), with one lane per chain above, time segments below
     chunks = {b: bd.bimamba_time_chunks(bd.make_desc(synth.mixer_cfg(b, 8192, 4096))) for b in (1, 4, 6, 7, 8, 12, 16, 20, 21, 24, 64)}
