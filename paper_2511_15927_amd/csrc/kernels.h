@@ -1215,10 +1215,9 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, float* lds_all, c
         if (a.raw_partial) run_range<N, S, AKIND, IO, kModeFinalAddRaw, TILE, BCSRC>(a, c, len - n_first, sp, lds, lane);
         else run_range<N, S, AKIND, IO, kModeFinalAdd, TILE, BCSRC>(a, c, len - n_first, sp, lds, lane);
     }
-    // Waves past the last tile shadow it: all have read h_in and tail_in, which the commit of a short call may overwrite
-    // right away, before any of them gets here (with the halves apart no barrier came before).
-    if constexpr (BCSRC == kBcStaged)
-        if (a.separate && (a.h_out || a.tail_out)) __syncthreads();
+    // Waves past the last tile shadow it: all have read h_in (and tail_in, which a short call's commit overwrites too) before
+    // any of them commits over it.  With the halves apart no barrier came before; the carry of segments has its own commit.
+    if (a.separate && a.nseg == 1 && (a.h_out || a.tail_out)) __syncthreads();
     if (s == 0 && a.nseg == 1 && a.h_out) {
         float* dst = a.h_out + ((size_t)b * a.Dn + ch) * N + sub * NS;
 #pragma unroll
