@@ -19,7 +19,9 @@ def main(layout):
     from helpers import rel_l2, to_np
     from paper_2511_15927_amd import binding as bd
     from paper_2511_15927_amd import synth
-    cfg = synth.mixer_cfg(3, 32, 200, d_state=8) if layout == "selective" else synth.m2_cfg(3, 40, 128, headdim=32, d_state=64)
+    cfg = {"selective": synth.mixer_cfg(3, 256, 200, d_state=8),                          # more than 64 KB of LDS in one launch
+           "selective_sweep": synth.mixer_cfg(3, 32, 200, d_state=8, time_chunks=1),      # the sweep's occupancy query
+           "mamba2": synth.m2_cfg(3, 40, 128, headdim=32, d_state=64)}[layout]
     N, K, Bt, Dn = cfg["d_state"], cfg["d_conv"], cfg["batch"], cfg["d_inner"]
     pf, pb, inp = synth.make_params(cfg, 5, 0), synth.make_params(cfg, 5, 1), synth.make_inputs(cfg, 5)
     g = torch.Generator().manual_seed(9)

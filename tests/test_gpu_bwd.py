@@ -120,10 +120,9 @@ def test_random_descriptor(gpu, oracle, seed):
 
 
 def test_gradient_call_replayed_from_a_hip_graph(gpu):
-    """bimamba_bwd captured into a HIP graph (it clears its accumulation targets with kernels, not memset nodes):
-    every replay, with eager work and synchronisation between replays and fresh contents in the static buffers, must
-    equal the eager call on the same contents: bit for bit for the activation gradients (fixed summation order), to
-    rounding for the parameter gradients (their sum over the batch is formed with atomics)."""
+    """bimamba_bwd captured into a HIP graph (it enqueues kernels only): every replay, with eager work and synchronisation
+    between replays and fresh contents in the static buffers, must equal the eager call on the same contents bit for bit
+    (every sum has a fixed order)."""
     cfg = synth.mixer_cfg(3, 45, 200, io="bf16")
     Bt, L, Dn, N, K = 3, 45, 200, cfg["d_state"], cfg["d_conv"]
     pf, pb = params(cfg, 5)
@@ -155,7 +154,6 @@ def test_gradient_call_replayed_from_a_hip_graph(gpu):
     with torch.cuda.graph(graph):
         call()
     outs = list(gi.values()) + list(qf.values()) + list(qb.values())
-    n_exact = len(gi)
     for rep in range(3):
         fresh = bd.to_device(synth.make_inputs(cfg, 70 + rep), cfg)
         for k in static_in:
@@ -170,12 +168,7 @@ def test_gradient_call_replayed_from_a_hip_graph(gpu):
         graph.replay()
         torch.cuda.synchronize()
         for i, (got, ref) in enumerate(zip(outs, want)):
-            if i < n_exact:
-                assert torch.equal(got, ref), (rep, i)
-            elif not bool(ref.any()):
-                assert not bool(got.any()), (rep, i)      # e.g. the Delta bias without softplus
-            else:
-                assert rel_all(got.cpu().numpy(), ref.cpu().numpy()) < 1e-6, (rep, i)
+            assert torch.equal(got, ref), (rep, i)
 
 
 @pytest.mark.parametrize("untied", [False, True])
@@ -240,9 +233,9 @@ def test_lengths_around_the_time_segments(gpu, oracle, L, untied):
 
 @pytest.mark.parametrize("N", [4, 8, 16])
 @pytest.mark.parametrize("L", [1, 5, 37, 70])
-def test_more_waves_than_simds_takes_the_dense_form(gpu, oracle, N, L):
-    """Batch 9 at d_inner 4096 is 1152 waves for 1024 SIMDs: the kernels built for two waves per SIMD (shorter chunks
-    for 4 and 16 states) and the plan that sizes their stored states; every channel compared."""
+def test_more_waves_than_simds(gpu, oracle, N, L):
+    """Batch 9 at d_inner 4096 is 1152 waves for 1024 SIMDs, in one or two time segments, and the plan that sizes their
+    stored states; every channel compared."""
     run_case(gpu, oracle, synth.mixer_cfg(9, L, 4096, d_state=N, io="bf16" if L % 2 else "f32"), 900 + N + L)
 
 

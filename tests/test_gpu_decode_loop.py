@@ -12,17 +12,17 @@ from paper_2511_15927_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("layout,G,static", [("selective", 32, False), ("selective", 64, True), ("mamba2", 32, False),
-                                             ("mamba2", 128, False)])
+@pytest.mark.parametrize("layout,G,static", [("selective", 32, False), ("selective", 64, True), ("selective_sweep", 32, False),
+                                             ("selective_sweep", 96, True), ("mamba2", 32, False), ("mamba2", 128, False)])
 def test_decode_loop_graph_matches_oracle_layer_by_layer(oracle, layout, G, static):
     from paper_2511_15927_amd import binding as bd
     from paper_2511_15927_amd.decode import BlockDecodeLoop
     assert torch.cuda.is_available(), "these tests need the MI355X"
     n_layers, n_steps, n_blocks = 3, 2, 3
-    if layout == "selective":
-        cfg, h_tol = synth.mixer_cfg(2, G, 192), 1e-5
-    else:
+    if layout == "mamba2":
         cfg, h_tol = synth.m2_cfg(2, G, 128, headdim=32, d_state=64), 1e-2
+    else:
+        cfg, h_tol = synth.mixer_cfg(2, G, 192, time_chunks=int(layout == "selective_sweep")), 1e-5
     Bt, Dn, N, K = cfg["batch"], cfg["d_inner"], cfg["d_state"], cfg["d_conv"]
     params = [(synth.make_params(cfg, 3000 + l, 0), synth.make_params(cfg, 3000 + l, 1)) for l in range(n_layers)]
     loop = BlockDecodeLoop(cfg, params, n_steps, keep_layer_outputs=True, static_scratch=static)

@@ -30,11 +30,13 @@ def check_fwd(gpu, oracle, cfg, seed, random_a=False, untied=False, sel=None, **
     pf, pb, inp = case(cfg, seed, random_a)
     inp_b = synth.make_inputs(cfg, seed + 500) if untied else None
     c = dict(cfg, **override)
-    got = gpu.gpu_fwd(c, pf, pb, inp, inp_b)
     ref = oracle.bimamba_fwd(c, to_np(pf), to_np(pb), to_np(inp), None if inp_b is None else to_np(inp_b), sel=sel)
-    if sel is not None:
-        got = got[..., sel]
-    return assert_close(got, ref, gpu.TOL[c["io"]], c)
+    runs = [c]
+    if c["d_state"] <= 16 and c["seqlen"] <= 256 and c["time_chunks"] == c["state_split"] == 0:
+        runs.append(dict(c, time_chunks=1))      # the sweep, where a call left to the library may take the one-launch form
+    for r in runs:
+        got = gpu.gpu_fwd(r, pf, pb, inp, inp_b)
+        assert_close(got if sel is None else got[..., sel], ref, gpu.TOL[c["io"]], r)
 
 
 def test_cfg0_tiny_fp32(gpu, oracle):
@@ -111,10 +113,12 @@ def test_lanes_per_chain(gpu, oracle, N, split):
     check_fwd(gpu, oracle, sep, 970 + N + split, random_a=True, untied=True)
 
 
-def test_strided_views_of_one_projection(gpu, oracle):
-    """x, z, dt, B, C as column slices of one [Bt, L, D_in] buffer (channel stride 1, token stride D_in)."""
+@pytest.mark.parametrize("kw", [{}, dict(state_split=1, time_chunks=1), dict(state_split=2, time_chunks=1), dict(time_chunks=3)])
+def test_strided_views_of_one_projection(gpu, oracle, kw):
+    """x, z, dt, B, C as column slices of one [Bt, L, D_in] buffer (channel stride 1, token stride D_in), on the form the
+    library picks and on those of the sweep: one launch, lanes split, time segments."""
     from paper_2511_15927_amd import binding as bd
-    cfg = synth.mixer_cfg(2, 45, 96, io="bf16")
+    cfg = synth.mixer_cfg(2, 45, 96, io="bf16", **kw)
     pf, pb, inp = case(cfg, 700)
     Dn, N = 96, 16
     widths = dict(z=Dn, x=Dn, B=N, C=N, dt=Dn)
@@ -257,11 +261,12 @@ def test_launch_geometries_of_the_batch_sweep(gpu, oracle, batch, L):
     check_fwd(gpu, oracle, cfg, 1800 + batch, sel=sampled(16, 4096, batch))
 
 
-def test_output_as_a_column_slice_of_the_inputs_buffer(gpu, oracle):
+@pytest.mark.parametrize("kw", [{}, dict(state_split=1, time_chunks=1), dict(state_split=2, time_chunks=1)])
+def test_output_as_a_column_slice_of_the_inputs_buffer(gpu, oracle, kw):
     """out may live in the same buffer as the inputs as long as its columns stay apart from theirs (same strides): the
     host's overlap check accepts it and no input column is disturbed; an out that runs into z is refused."""
     from paper_2511_15927_amd import binding as bd
-    cfg = synth.mixer_cfg(2, 45, 96, io="bf16")
+    cfg = synth.mixer_cfg(2, 45, 96, io="bf16", **kw)
     pf, pb, inp = case(cfg, 710)
     Dn, N = 96, 16
     widths = dict(z=Dn, x=Dn, B=N, C=N, dt=Dn, out=Dn)
@@ -288,7 +293,9 @@ def test_output_as_a_column_slice_of_the_inputs_buffer(gpu, oracle):
 
 
 @pytest.mark.parametrize("batch,L,Dn,N,io", [
-    (1, 257, 512, 16, "f32"),        # too short to cut: two lanes per chain, whole
+    (5, 170, 1600, 16, "f32"),       # too short to cut: two lanes per chain, whole
+    (1, 257, 512, 16, "f32"), (1, 1101, 72, 16, "bf16"), (2, 9001, 40, 16, "bf16"),    # too narrow for a round of segments
+    (1, 1928, 200, 8, "bf16"), (2, 700, 40, 4, "f32"), (1, 5003, 64, 8, "f32"),
     (2, 777, 320, 16, "bf16"),       # two lanes per chain, segments of 24 tokens or more, a ragged last one
     (1, 2051, 640, 16, "f32"),       # the same with a few tokens more than whole segments
     (1, 3001, 1024, 16, "bf16"),     # one round of one-lane segments

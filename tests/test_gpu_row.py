@@ -50,3 +50,41 @@ def test_heads_groups_and_scalar_decay(gpu, oracle, L):
         pf, pb = synth.make_params(cfg, L, 0), synth.make_params(cfg, L, 1)
         inp = synth.make_inputs(cfg, L)
         assert_close(gpu.gpu_fwd(cfg, pf, pb, inp), oracle.bimamba_fwd(cfg, to_np(pf), to_np(pb), to_np(inp)), gpu.TOL["f32"])
+
+
+@pytest.mark.parametrize("batch,L,Dn,N,K", [
+    (1, 31, 2050, 16, 4),        # two tiles of four channels in a workgroup
+    (3, 16, 1366, 8, 3),         # four, a ragged last workgroup of six channels
+    (1, 32, 4100, 16, 4),        # four, a last workgroup of one tile
+    (2, 64, 2045, 16, 2),        # four, two time segments
+    (1, 100, 3001, 4, 4),        # two, two segments
+    (1, 128, 2046, 16, 4),       # two, four segments
+    (2, 17, 8000, 16, 1)])       # four
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+def test_several_channel_tiles_in_a_workgroup(gpu, oracle, batch, L, Dn, N, K, io):
+    """Calls of 2048 chains or more put two or four channel tiles into a workgroup: full-sequence calls with the directions
+    added and kept apart, shared and separate activations, and a block call committed in place."""
+    from paper_2511_15927_amd import binding as bd
+    assert bd.bimamba_time_chunks(bd.make_desc(synth.mixer_cfg(batch, L, Dn, d_state=N))) == 1
+    for combine in (0, 1):
+        cfg = synth.mixer_cfg(batch, L, Dn, d_state=N, d_conv=K, io=io, dt_softplus=combine, combine=combine)
+        pf, pb = params(cfg, Dn + combine, random_a=bool(combine))
+        inp = synth.make_inputs(cfg, Dn)
+        inp_b = synth.make_inputs(cfg, Dn + 500) if combine else None
+        both = (to_np(pf), to_np(pb), to_np(inp), None if inp_b is None else to_np(inp_b))
+        assert_close(gpu.gpu_fwd(cfg, pf, pb, inp, inp_b), oracle.bimamba_fwd(cfg, *both), gpu.TOL[io])
+        g = torch.Generator().manual_seed(L)
+        h0 = (0.2 * torch.randn(batch, Dn, N, generator=g)).float()
+        tail0 = synth.round_io(torch.randn(batch, K - 1, Dn, generator=g), io) if K > 1 else None
+        ref, h_ref, t_ref = oracle.bimamba_block_fwd(cfg, *both, h_in=h0.numpy(), tail_in=None if tail0 is None else tail0.numpy())
+        desc, out, ws = bd.make_desc(cfg), bd.alloc_out(cfg), bd.alloc_workspace(bd.make_desc(cfg), 1)
+        dh, dt = h0.cuda(), None if tail0 is None else tail0.to(device="cuda", dtype=bd.io_dtype(cfg))
+        dpf, dpb, dinp = bd.to_device(pf), bd.to_device(pb), bd.to_device(inp, cfg)
+        dinp_b = None if inp_b is None else bd.to_device(inp_b, cfg)
+        bd.bimamba_block_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp),
+                             None if dinp_b is None else bd.make_inputs(dinp_b), dh, dt, dh, dt, bd.make_tensor(out), ws)
+        torch.cuda.synchronize()
+        assert_close(out.float().cpu().numpy().reshape(ref.shape), ref, gpu.TOL[io])
+        assert rel_l2(dh.cpu().numpy(), h_ref) < 1e-5
+        if K > 1:
+            assert np.array_equal(dt.float().cpu().numpy().astype(np.float64), t_ref)

@@ -40,12 +40,14 @@ def both_ways(bd, cfg, seed):
     assert torch.equal(o0, o1) and torch.equal(h0, h1) and torch.equal(t0, t1), cfg
 
 
-@pytest.mark.parametrize("layout", ["selective", "mamba2"])
+@pytest.mark.parametrize("layout", ["selective", "selective_sweep", "mamba2"])
 def test_static_scratch_block_step_equals_workspace_call(layout):
     from paper_2511_15927_amd import binding as bd
     assert torch.cuda.is_available(), "these tests need the MI355X"
     if layout == "selective":
-        first, second = synth.mixer_cfg(4, 96, 1024), synth.mixer_cfg(2, 32, 320)     # 96 tokens: prepared B|C rows + partial
+        first, second = synth.mixer_cfg(4, 96, 1024), synth.mixer_cfg(2, 32, 320)     # one launch, nothing in scratch
+    elif layout == "selective_sweep":      # 96 tokens: prepared B|C rows + partial
+        first, second = synth.mixer_cfg(4, 96, 1024, time_chunks=1), synth.mixer_cfg(2, 32, 320, time_chunks=1)
     else:
         first, second = synth.m2_cfg(4, 130, 512, headdim=64, d_state=128), synth.m2_cfg(3, 32, 256, headdim=32, d_state=64)
     assert 0 < bd.bimamba_workspace_bytes(bd.make_desc(second), 1) < bd.bimamba_workspace_bytes(bd.make_desc(first), 1)
