@@ -1217,7 +1217,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, float* lds_all, c
     }
     // Waves past the last tile shadow it: all have read h_in (and tail_in, which a short call's commit overwrites too) before
     // any of them commits over it.  With the halves apart no barrier came before; the carry of segments has its own commit.
-    if (a.separate && a.nseg == 1 && (a.h_out || a.tail_out)) __syncthreads();
+    if (a.separate && (BCSRC == kBcStaged || a.nseg == 1) && (a.h_out || a.tail_out)) __syncthreads();   // (short calls: one segment)
     if (s == 0 && a.nseg == 1 && a.h_out) {
         float* dst = a.h_out + ((size_t)b * a.Dn + ch) * N + sub * NS;
 #pragma unroll
