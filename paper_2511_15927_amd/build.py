@@ -10,6 +10,8 @@ OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libbimamba.so")
 # (d_state, lanes per chain) pairs the scan kernels are instantiated for
 VARIANTS = ((4, 1), (8, 1), (16, 1), (16, 2), (16, 4), (32, 1), (32, 2), (32, 4), (64, 1), (64, 4), (128, 1), (128, 4))
+# (d_state, head width) pairs of the many-wave chunk walk
+SSD_WIDE = ((64, 32), (64, 64), (128, 32), (128, 64))
 # packed fp32 VALU forms are switched off for every kernel in this library
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC", "-Xclang", "-target-feature", "-Xclang",
          "-packed-fp32-ops", "-Wall", "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"),
@@ -48,6 +50,9 @@ def build(force: bool = True, jobs: int = 8):
         units.append((os.path.join(CSRC, "scan_inst.hip"), os.path.join(OBJ, "scan_n%d_s%d.o" % (n, s)),
                       ["-DBM_N=%d" % n, "-DBM_S=%d" % s]))
     units.append((os.path.join(CSRC, "ssd_inst.hip"), os.path.join(OBJ, "ssd_inst.o"), []))
+    for n, p in SSD_WIDE:
+        units.append((os.path.join(CSRC, "ssd_wide_inst.hip"), os.path.join(OBJ, "ssd_wide_n%d_p%d.o" % (n, p)),
+                      ["-DBM_N=%d" % n, "-DBM_P=%d" % p]))
     units.append((os.path.join(CSRC, "bwd_inst.hip"), os.path.join(OBJ, "bwd_inst.o"), []))
     units.append((os.path.join(CSRC, "row_inst.hip"), os.path.join(OBJ, "row_inst.o"), []))
     newest = max(os.path.getmtime(p) for p in sources())

@@ -588,6 +588,12 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
             // forward scan adds, gates and stores (or each writes its own half)
             const bool separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
             const bool raw = !separate && same_tensor(in_f->z, in_b->z);
+            // calls of several chunks that need no time parts walk sixteen waves wide (the row offsets of a chunk's
+            // gate / output rows are 32-bit there) unless BIMAMBA_NO_WIDE is set
+            constexpr int64_t kMaxWideStride = 1 << 24;
+            const bool wide = plan.ssd_parts == 1 && plan.ssd_chunks >= 2 && in_f->z.stride_token <= kMaxWideStride &&
+                              in_b->z.stride_token <= kMaxWideStride && out->stride_token <= kMaxWideStride &&
+                              !getenv("BIMAMBA_NO_WIDE");
             SsdPrepPair pp{};
             for (int s = 0; s < 2; s++) {
                 SsdPrepArgs& pa = pp.dir[s];
@@ -601,6 +607,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                 pa.b_t = reinterpret_cast<__bf16*>(ws + plan.off_bt[s]);
                 pa.score_op = reinterpret_cast<float*>(ws + plan.off_score[s]);
                 pa.L = d->seqlen; pa.G = d->n_groups; pa.dir = s == 0 ? 1 : -1;
+                pa.wide = wide;
             }
             launch_ssd_prep(d->d_state, pp, plan.ssd_chunks, d->batch, st);
             if (probe_start) (void)hipEventRecord(probe_start, st);
@@ -629,12 +636,8 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                                    : s == 1 ? (raw ? kSsdPartialRaw : kSsdPartial) : (raw ? kSsdFinalAddRaw : kSsdFinalAdd);
                 sa.out_ch_off = separate ? s * d->d_inner : 0;
                 sa.dt_softplus = d->dt_softplus; sa.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD;
-                // calls of several chunks that need no time parts walk sixteen waves wide (the row offsets of a chunk's
-                // gate / output rows are 32-bit there) unless BIMAMBA_NO_WIDE is set
-                constexpr int64_t kMaxWideStride = 1 << 24;
-                sa.wide = plan.ssd_parts == 1 && plan.ssd_chunks >= 2 && in_f->z.stride_token <= kMaxWideStride &&
-                          in_b->z.stride_token <= kMaxWideStride && out->stride_token <= kMaxWideStride &&
-                          !getenv("BIMAMBA_NO_WIDE");
+                sa.wide = wide;
+                sa.pairs = pairs_readable(in->z) && pairs_readable(*out);
                 return sa;
             };
             if (plan.ssd_parts > 1) {

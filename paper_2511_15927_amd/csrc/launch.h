@@ -25,6 +25,15 @@ private:
     std::atomic<bool> raised_[kMaxDevices] = {};
 };
 
+// For the kernels whose limit is raised without a check: idempotent, done once per (kernel, device).
+constexpr int kMaxSeenDevices = 64;
+inline bool first_use_on_current_device(std::atomic<bool>* seen)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxSeenDevices) return true;
+    return !seen[dev].exchange(true);
+}
+
 // Compute units of the current device (256 when no device answers), asked once per device; defined in bimamba_api.hip
 // and used by the host-side plan and by every launcher, so that all of them size a launch for the same chip.
 int cu_count();
@@ -62,6 +71,11 @@ struct SsdStatePair;
 bool ssd_supported(int d_state, int headdim);
 void launch_ssd_prep(int d_state, const SsdPrepPair& pa, int nchunk, int batch, hipStream_t st);
 void launch_ssd_scan(int d_state, int headdim, const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
+// (the many-wave form of the scan; defined in ssd_wide_inst.hip, one object per (d_state, head width))
+void launch_ssd_wide_n128_p64(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
+void launch_ssd_wide_n128_p32(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
+void launch_ssd_wide_n64_p64(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
+void launch_ssd_wide_n64_p32(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
 void launch_ssd_carry(int d_state, const SsdCarryArgs& ca, hipStream_t st);
 void launch_ssd_duo(int d_state, int headdim, const SsdStatePair& sp, int batch, hipStream_t st);
 void launch_ssd_state(int d_state, int headdim, const SsdStatePair& sp, int subs, int batch, hipStream_t st);

@@ -1,25 +1,15 @@
 // Instantiations and launchers of the chunked Mamba-2 kernels (d_state in {64, 128}, head width in {32, 64}).
 #include "ssd_kernels.h"
-#include "ssd_wide.h"
 #include "launch.h"
 
 #include <atomic>
 
 namespace bm {
 
-// Raising a kernel's dynamic-LDS limit is idempotent; it is done once per (kernel, device).
-constexpr int kMaxDevices = 64;
-static bool first_use_on_current_device(std::atomic<bool>* seen)
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return true;
-    return !seen[dev].exchange(true);
-}
-
 template <int N, int THREADS>
 static void prep_variant(const SsdPrepPair& pa, int nchunk, int batch, hipStream_t st)
 {
-    static std::atomic<bool> seen[kMaxDevices];
+    static std::atomic<bool> seen[kMaxSeenDevices];
     constexpr size_t lds = ssd_prep_lds_bytes<N, THREADS>();
     auto kernel = ssd_prep_kernel<N, THREADS>;
     if (first_use_on_current_device(seen))
@@ -30,7 +20,7 @@ static void prep_variant(const SsdPrepPair& pa, int nchunk, int batch, hipStream
 template <int N, int P, bool SINGLE, int GROUPS, bool PARTS>
 static void scan_variant(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    static std::atomic<bool> seen[kMaxDevices];
+    static std::atomic<bool> seen[kMaxSeenDevices];
     constexpr size_t lds = SsdLds<N, P, SINGLE>::bytes();
     auto kernel = ssd_kernel<N, P, SINGLE, GROUPS, PARTS>;
     if (first_use_on_current_device(seen))
@@ -39,17 +29,13 @@ static void scan_variant(const SsdStatePair& sp, int dirs, int batch, hipStream_
     hipLaunchKernelGGL(kernel, dim3((unsigned)sp.dir[0].H, parts * (unsigned)dirs, (unsigned)batch), dim3(4 * P + 256 * GROUPS), lds, st, sp);
 }
 
-template <int N, int P, int DIRS>
-static void wide_variant(const SsdStatePair& sp, int batch, hipStream_t st)
+template <int N, int P>
+static void launch_ssd_wide(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    static std::atomic<bool> seen[kMaxDevices];
-    constexpr size_t lds = SsdLds<N, P, false>::bytes();
-    auto kernel = ssd_wide_kernel<N, P, DIRS>;
-    if (first_use_on_current_device(seen))
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    const dim3 grid((unsigned)sp.dir[0].H, (unsigned)DIRS, (unsigned)batch), block(SsdWide<N, P>::kThreads);
-    if constexpr (DIRS == 1) hipLaunchKernelGGL(kernel, grid, block, lds, st, sp.dir[0]);
-    else hipLaunchKernelGGL(kernel, grid, block, lds, st, sp);
+    if constexpr (N == 128 && P == 64) launch_ssd_wide_n128_p64(sp, dirs, batch, st);
+    else if constexpr (N == 128) launch_ssd_wide_n128_p32(sp, dirs, batch, st);
+    else if constexpr (P == 64) launch_ssd_wide_n64_p64(sp, dirs, batch, st);
+    else launch_ssd_wide_n64_p32(sp, dirs, batch, st);
 }
 
 // Long calls that leave at least half of the CUs empty (batch 1 or 2) split the producers into two groups, which
@@ -59,8 +45,7 @@ template <int N, int P>
 static void scan_one(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     const SsdArgs& sa = sp.dir[0];
-    if (sa.wide && dirs == 2) wide_variant<N, P, 2>(sp, batch, st);
-    else if (sa.wide) wide_variant<N, P, 1>(sp, batch, st);
+    if (sa.wide) launch_ssd_wide<N, P>(sp, dirs, batch, st);
     else if (sa.parts > 1) scan_variant<N, P, false, 1, true>(sp, dirs, batch, st);
     else if (2LL * dirs * sa.H * batch <= cu_count()) scan_variant<N, P, false, 2, false>(sp, dirs, batch, st);
     else scan_variant<N, P, false, 1, false>(sp, dirs, batch, st);
@@ -92,7 +77,7 @@ void launch_ssd_carry(int d_state, const SsdCarryArgs& ca, hipStream_t st)
 template <int N, int P>
 static void duo_one(const SsdStatePair& sp, int batch, hipStream_t st)
 {
-    static std::atomic<bool> seen[kMaxDevices];
+    static std::atomic<bool> seen[kMaxSeenDevices];
     constexpr size_t lds = SsdDuoLds<N, P>::bytes();
     auto kernel = ssd_duo_kernel<N, P>;
     if (first_use_on_current_device(seen))

@@ -29,6 +29,7 @@ namespace bm {
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
 constexpr int kQ = 64;     // chunk length
 constexpr int kPadK = 8;   // bf16 elements of row padding in LDS tiles (keeps 16-byte alignment, spreads banks)
@@ -44,6 +45,7 @@ struct SsdPrepArgs {
     float* score_op;   // [batch][nchunk][G][kScoreOp]: B_j . C_i for j, i in the chunk, MFMA operand order (see the kernel)
     int L, G, K, Dn, tail_ch, conv_bc;
     int dir;           // +1: scan position tau is token tau; -1: token L-1-tau
+    int wide;          // operand tiles in the order of ssd_wide_kernel (ssd_wide.h)
 };
 
 struct SsdPrepPair {
@@ -126,6 +128,24 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
     }
     __syncthreads();
     const size_t Lpad = (size_t)nchunk * kQ;
+    const size_t tile = ((size_t)b * nchunk + c) * a.G + g;
+    if (a.wide) {
+        // operand tiles of ssd_wide_kernel, one 16-byte piece per lane of an MFMA operand: C as [row block of 16][32
+        // states][lane] with the states in the order the state's accumulators publish them, B^T as [32 states][16 positions][lane]
+        for (int idx = tid; idx < kQ * N / 8; idx += THREADS) {
+            const int ln = idx % 64, f = idx / 64;
+            const int i = (f / (N / 32)) * 16 + ln % 16, n0 = (f % (N / 32)) * 32 + 16 * ((ln / 16) % 2) + 4 * (ln / 32);
+            const int n2 = (f / 4) * 32 + ln % 32, j0 = (f % 4) * 16 + 8 * (ln / 32);
+            bf16x8 cv, bv;
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                cv[e] = (__bf16)sC[i][n0 + 8 * (e / 4) + e % 4];
+                bv[e] = (__bf16)sB[j0 + e][n2];
+            }
+            *reinterpret_cast<bf16x8*>(&a.c_rows[(tile * kQ * N / 8 + idx) * 8]) = cv;
+            *reinterpret_cast<bf16x8*>(&a.b_t[(tile * kQ * N / 8 + idx) * 8]) = bv;
+        }
+    } else
     // bf16 C rows and the transposed bf16 B tile, written as 16-byte pieces (8 states of a row, 8 positions of a state)
     for (int idx = tid; idx < kQ * N / 8; idx += THREADS) {
         const int j = idx / (N / 8), n8 = idx % (N / 8);
@@ -188,7 +208,18 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
             }
         }
     }
-    if (blk < 3 && kpart == 0) {
+    if (blk < 3 && kpart == 0 && a.wide) {
+        // [block][16 rows i][lane][8]: slot 4t + e of lane l holds row i = l%16 of column j = 16t + 4(l/16) + e; zero above the diagonal
+        float* const dst = a.score_op + tile * kScoreOp;
+#pragma unroll
+        for (int q = 0; q < 4; q++) {
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; e++) v[e] = blk != 1 && 8 * q + 4 * (lane / 32) + e > lane % 32 ? 0.0f : acc[4 * q + e];
+            const int sl = (2 * (q % 2) + lane / 32) * 16 + lane % 16;
+            *reinterpret_cast<float4*>(dst + ((blk * 2 + (lane / 16) % 2) * 64 + sl) * 8 + 4 * (q / 2)) = make_float4(v[0], v[1], v[2], v[3]);
+        }
+    } else if (blk < 3 && kpart == 0) {
         float* dst = a.score_op + (((size_t)b * nchunk + c) * a.G + g) * kScoreOp + ((size_t)(blk * 2) * 64 + lane) * 8;
 #pragma unroll
         for (int kb = 0; kb < 2; kb++) {
@@ -216,6 +247,7 @@ struct SsdArgs {
     int L, Dn, H, HG, G, K, tail_ch, nchunk;
     int dir, mode, out_ch_off, dt_softplus, d_per_head;
     int wide;             // run on ssd_wide_kernel (ssd_wide.h): both directions of a call agree, the parked result is bf16
+    int pairs;            // wide: z and out can be accessed as aligned channel pairs
     // Time parts (calls with too few (batch, head) items to fill the chip): the chunks are dealt to `parts` workgroups
     // per item, part_chunks each, in scan order.  A part is part_subs sub-parts of sub_chunks chunks;
     // ssd_state_kernel leaves every sub-part's end state from a zero start and the product of its chunk decays (all

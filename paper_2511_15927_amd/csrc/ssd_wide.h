@@ -1,56 +1,76 @@
-// The chunk walk of ssd_kernels.h for calls that fill the chip, as sixteen short instruction streams instead of eight.
+// The chunk walk of ssd_kernels.h for calls that fill the chip, dealt to short instruction streams of up to sixteen waves.
 //
 // A wave issues at most one instruction every six to seven cycles whatever the instruction is, while a SIMD's vector
-// ALU accepts a 64-lane instruction every four, so a workgroup is as fast as its longest per-chunk instruction stream,
-// not as its total work.  ssd_kernel deals a chunk to four consumer and four producer waves; here the same work goes to
-//   y waves   (P/16): the intra-chunk product, the inter-chunk product C H and the epilogue of a 32 x 32 output block;
-//   h waves   (N/32): the state update of one row block of H (all channel blocks, so one B^T operand serves them all),
-//                     its decay and the bf16 operand copy of the new state;
-//   producers (8):    four build the masked, decayed score operand and stage the C / B^T tiles, four run conv + SiLU.
-// Tiles, double buffering and the one barrier per chunk are those of ssd_kernel.  The epilogue addresses the rows of a
-// chunk through raw buffer ranges (a constant lane offset per row group plus a scalar row offset: no vector address
-// arithmetic), and the result one direction parks for the other crosses global memory as bf16: in the paper's
-// precision (bf16 autocast, App. A) each direction's output is a bf16 tensor before the two are added (eq. 6).
+// ALU accepts a 64-lane instruction every four, so a workgroup is as fast as its longest instruction stream, not as its
+// total work.  A workgroup walks the chunks of one head, or of two heads of a group in turn (HEADS = 2); a period is one
+// (chunk, head), and its work is
+//   y waves     (two sets of P/16): the intra-chunk product, the inter-chunk product C H and the epilogue of a 32 x 32 output
+//               block each.  The sets take the periods in turn: a set runs a period's matrix products while its tiles are in
+//               LDS and its epilogue (gate, combine, stores) a period later, while the other set multiplies;
+//   state waves (4): the state update, whose B^T operand comes straight from global memory in operand order, the bf16 operand
+//               copy of the new state, and the masked, decayed score operand of the next period.  Each of them scans every fourth
+//               period's Delta, two periods ahead, for all waves;
+//   conv waves  (4): conv + SiLU of x for the next period.
+// One LDS barrier per period.
 //
-// grid (H, directions, batch).  Multi-chunk calls without time parts only; z / out token strides up to 2^24 elements (the host checks).
+// What bounds it is the bytes a CU takes in: with all global accesses but the first ones removed a launch at batch 8 x 8192
+// tokens of 64 heads x 64, 128 states takes 0.28 ms, with them 0.50 (reverse) and 0.69 (forward), and the tiles that every
+// head of a group reads again (C 16 KB, B^T 16, scores 12 per chunk, all from L2) cost more than x, z and the output.  Hence two heads
+// to a workgroup, which share them, where that leaves no CU idle: 0.43 and 0.51 ms.
+//
+// Layouts.  The y waves multiply with the 16x16x32 MFMA (operand A lane l: row l%16, eight contraction slots of group l/16;
+// accumulator register r: row 4*(l/16) + r, column l%16): two row tiles by two column tiles, where column tile ct holds
+// channels 2*(l%16) + ct, so that a lane owns adjacent channels and moves 4-byte pairs of z, of the parked result and of the
+// output.  The state update uses the 32x32x16 MFMA with the same channel order, column j = channel 2*(j%16) + j/16.
+// Contraction over positions: slot 4t + e of group g is position 16t + 4g + e of a 32-position block, which makes a
+// lane's own output rows its slots of the xc operand (the skip term reads no LDS).  Contraction over states: slot 4u + e of group
+// g is state 16*(g%2) + 8u + 4*(g/2) + e of a 32-state block, the order in which the state's accumulators publish it.
+//
+// The result one direction parks for the other crosses global memory as bf16: in the paper's precision (bf16 autocast,
+// App. A) each direction's output is a bf16 tensor before the two are added (eq. 6).
+//
+// grid (H / HEADS, directions, batch).  Multi-chunk calls without time parts only; z / out token strides up to 2^24 elements (the host checks).
 #pragma once
 #include "ssd_kernels.h"
 
 namespace bm {
 
-template <int N, int P>
+template <int N, int P, int HEADS>
 struct SsdWide {
     static constexpr int kPB = P / 32, kNB = N / 32;
-    static constexpr int kYWaves = 2 * kPB, kHWaves = kNB, kProdWaves = 8;
-    static constexpr int kThreads = 64 * (kYWaves + kHWaves + kProdWaves);
+    static constexpr int kYWaves = 2 * kPB;                  // of one set
+    static constexpr int kThreads = 64 * (2 * kYWaves + 8);
+    // LDS: two buffers of xc, xw (operand order) and of the score operand, two of the state operand (the chunks of one head in
+    // turn, or one for each of two heads), of C where two heads share it, four slots of tables
+    static constexpr int kX = kQ * P, kM = 3 * 2 * 64 * 8, kTile = 2 * kX + kM, kHT = N * P;
+    static constexpr int kTable = 4 * kQ + 4, kSlots = 4;    // e_i, f_j Delta_j, end-of-chunk weight, exp(l_i); separable flag
+    static constexpr int kC = HEADS == 2 ? kQ * N : 0;
+    static constexpr size_t bytes() { return 2 * (size_t)(kTile + kHT + kC) * sizeof(__bf16) + (size_t)kSlots * kTable * sizeof(float); }
 };
 
-// DIRS: one launch per direction or both at once (see launch_ssd_scan); compiled apart, since selecting the arguments
-// at run time cost the launches of one direction 0.5 %.
-template <int N, int P, int DIRS>
-__global__ __launch_bounds__((SsdWide<N, P>::kThreads)) void ssd_wide_kernel(const std::conditional_t<DIRS == 1, SsdArgs, SsdStatePair> launch)
+// MODE: the output mode, compiled apart (the registers of one mode are not held through another's loop); kSsdFinalOnly walks
+// both directions in one launch (see launch_ssd_scan), the others one.
+template <int N, int P, int HEADS, int MODE>
+__global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_kernel(const std::conditional_t<(MODE > 0), SsdArgs, SsdStatePair> launch)
 {
+    // (the parameter's type names no enumerator: those of an unnamed enumeration are spelt differently in a kernel's host and device name)
+    static_assert(kSsdFinalOnly == 0);
     const SsdArgs& a = [&]() -> const SsdArgs& {
-        if constexpr (DIRS == 1) return launch;
+        if constexpr (MODE != kSsdFinalOnly) return launch;
         else return launch.dir[blockIdx.y];
     }();
-    using Lds = SsdLds<N, P, false>;
-    using W = SsdWide<N, P>;
+    using W = SsdWide<N, P, HEADS>;
     constexpr int kPB = W::kPB, kNB = W::kNB;
-    constexpr int kProdThreads = 256;
-    constexpr int kRowC = Lds::kRowC, kRowT = Lds::kRowT;
-    constexpr int kCopy = kQ * N / 8 / kProdThreads;
-    constexpr int kHS = 2 * 3 * 2 * 64 / kProdThreads;
     using T = unsigned short;
     extern __shared__ __attribute__((aligned(16))) unsigned char ssd_lds[];
     __bf16* const tiles = reinterpret_cast<__bf16*>(ssd_lds);
-    __bf16* const sHT = tiles + Lds::kBufs * Lds::kTileElems;
-    float* const scal = reinterpret_cast<float*>(sHT + Lds::kBufs * Lds::kHT);
-    auto sC = [&](int buf) { return tiles + buf * Lds::kTileElems; };
-    auto sBT = [&](int buf) { return tiles + buf * Lds::kTileElems + Lds::kC; };
-    auto sXc = [&](int buf) { return tiles + buf * Lds::kTileElems + Lds::kC + Lds::kBT; };
-    auto sXw = [&](int buf) { return tiles + buf * Lds::kTileElems + Lds::kC + Lds::kBT + Lds::kX; };
-    auto sM = [&](int buf) { return tiles + buf * Lds::kTileElems + Lds::kC + Lds::kBT + 2 * Lds::kX; };
+    __bf16* const sHT = tiles + 2 * W::kTile;
+    __bf16* const sC = sHT + 2 * W::kHT;
+    float* const tables = reinterpret_cast<float*>(sC + 2 * W::kC);
+    auto sXc = [&](int buf) { return tiles + buf * W::kTile; };
+    auto sXw = [&](int buf) { return tiles + buf * W::kTile + W::kX; };
+    auto sM = [&](int buf) { return tiles + buf * W::kTile + 2 * W::kX; };
+    auto table = [&](int p) { return tables + (p & (W::kSlots - 1)) * W::kTable; };
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -64,460 +84,526 @@ __global__ __launch_bounds__((SsdWide<N, P>::kThreads)) void ssd_wide_kernel(con
             b = (int)(item / gridDim.x);
         }
     }
+    head *= HEADS;                          // the workgroup's first; two heads are of one group (the host checks)
     const int grp = head / a.HG;
     const int ch0 = head * P;
-    const size_t Lpad = (size_t)a.nchunk * kQ;
-    const int nchunk = a.nchunk;
+    const int nchunk = a.nchunk, periods = nchunk * HEADS;   // period p: chunk p / HEADS, head p % HEADS
     const int last = a.L - 1;
     auto token_of = [&](int tau) { return a.dir > 0 ? tau : last - tau; };
-    const int cl = lane & 31, half = lane >> 5;
+    // the prepared tiles of (chunk c, this group)
+    auto tile_of = [&](int c) { return ((size_t)b * nchunk + c) * a.G + grp; };
 
-    if (wave >= W::kYWaves + W::kHWaves) {
-        // ------------------------------------------------------------------ producers (two groups of four waves)
-        constexpr int kCP = P / 2;
-        constexpr int kPos = kQ * kCP / kProdThreads;
-        const int pw = wave - (W::kYWaves + W::kHWaves);
-        const int group = pw >> 2, pwave = pw & 3;
-        const int ptid = tid - 64 * (W::kYWaves + W::kHWaves) - kProdThreads * group;
-        const bool do_score = group == 0;
+    if (wave >= 2 * W::kYWaves + 4) {
+        // ------------------------------------------------------------------ conv waves
+        constexpr int kCP = P / 2;                  // channel pairs of the head
+        constexpr int kPos = kQ * kCP / 256;        // chunk positions per thread (8 or 4)
+        const int ptid = tid - 64 * (2 * W::kYWaves + 4);
         const int cp = ptid % kCP, tg = ptid / kCP;
-        float* const pw_l2 = scal + Lds::kBufs * kQ + pwave * 3 * kQ;   // wave i of both groups shares slot i: each writes only what it reads
-        float* const pw_dl = pw_l2 + kQ;
-        float* const pw_wgt = pw_dl + kQ;
-        const float a2 = a.A[head] * kLog2e;
-        const float dtb = (a.dt_softplus && a.dt_bias) ? a.dt_bias[head] : 0.0f;
-        float w4[2][4], cbias[2];
+        float w4[HEADS][2][4], cbias[HEADS][2];
 #pragma unroll
-        for (int h2 = 0; h2 < 2; h2++) {
+        for (int hd = 0; hd < HEADS; hd++)
 #pragma unroll
-            for (int i = 0; i < 4; i++)
-                w4[h2][3 - i] = i < a.K ? a.conv_w[(size_t)(ch0 + 2 * cp + h2) * a.K + (a.K - 1 - i)] : 0.0f;
-            cbias[h2] = a.conv_b ? a.conv_b[ch0 + 2 * cp + h2] : 0.0f;
-        }
+            for (int h2 = 0; h2 < 2; h2++) {
+                const int ch = ch0 + hd * P + 2 * cp + h2;
+#pragma unroll
+                for (int i = 0; i < 4; i++) w4[hd][h2][3 - i] = i < a.K ? a.conv_w[(size_t)ch * a.K + (a.K - 1 - i)] : 0.0f;
+                cbias[hd][h2] = a.conv_b ? a.conv_b[ch] : 0.0f;
+            }
         const T* xb = (const T*)a.x.p + (size_t)b * a.x.sb + ch0 + 2 * cp;
-        const T* dtp = (const T*)a.dt.p + (size_t)b * a.dt.sb + head;
         const long long xstep = a.dir * a.x.st;
         const auto edge_chunk = [&](int c) { return c == 0 || c * kQ + kQ - 1 > last; };
-        T dtraw;
-        auto issue_dt = [&](int c) { dtraw = dtp[(long long)token_of(min(c * kQ + lane, last)) * a.dt.st]; };
-        // Delta and the inclusive cumulative log2-decay of position `lane` of chunk c (every producer wave runs the short
-        // scan for itself); re-requests Delta for chunk cn
-        auto scan_chunk = [&](int c, int cn, float& dl, float& l2) {
-            dl = IoBF16::cvt(dtraw);
-            issue_dt(cn);
-            if (a.dt_softplus) dl = softplus(dl + dtb);
-            if (c * kQ + lane > last) dl = 0.0f;
-            l2 = wave_inclusive_sum(dl * a2);
+        unsigned xraw[kPos + 3];
+        auto issue_x = [&](int c, int hd) {
+            const int tau0 = c * kQ + kPos * tg - 3;
+            const T* const xh = xb + hd * P;
+            if (!edge_chunk(c)) {
+                const T* xp = xh + (long long)token_of(tau0) * a.x.st;
+#pragma unroll
+                for (int q = 0; q < kPos + 3; q++) xraw[q] = *reinterpret_cast<const unsigned*>(xp + q * xstep);
+            } else {
+#pragma unroll
+                for (int q = 0; q < kPos + 3; q++)
+                    xraw[q] = *reinterpret_cast<const unsigned*>(xh + (long long)token_of(min(max(tau0 + q, 0), last)) * a.x.st);
+            }
         };
-        // The two groups are separate code paths (not branches inside one loop) so that each keeps only its own
-        // prefetch registers live.  Either way: chunk c's tiles go into buffer c & 1 from what was requested for it,
-        // and every stage re-requests its inputs for chunk cn the moment it has consumed them.
-        if (do_score) {
-            unsigned c_src[kCopy], b_src[kCopy], c_dst[kCopy], b_dst[kCopy];
+        // this thread's pieces of the operand tiles (elements): its kPos positions of channels 2cp, 2cp + 1
+        const int pblk = cp / 16, pos0 = kPos * tg;
+        unsigned xc_at[kPos / 4], xw_at;
 #pragma unroll
-            for (int i = 0; i < kCopy; i++) {
-                const int idx = i * kProdThreads + ptid;
-                c_src[i] = (unsigned)(idx / (N / 8)) * a.G * N + (idx % (N / 8)) * 8;
-                b_src[i] = (idx / (kQ / 8)) * kQ + (idx % (kQ / 8)) * 8;
-                c_dst[i] = (idx / (N / 8)) * kRowC + (idx % (N / 8)) * 8;
-                b_dst[i] = (idx / (kQ / 8)) * kRowT + (idx % (kQ / 8)) * 8;
+        for (int u = 0; u < kPos / 4; u++) {
+            const int pos = pos0 + 4 * u;   // slot 4t of group g in 32-position block pos/32
+            xc_at[u] = (unsigned)((((pos / 32) * kPB + pblk) * 2 * 64 + ((pos % 16) / 4) * 16 + cp % 16) * 8 + 4 * ((pos % 32) / 16));
+        }
+        xw_at = (unsigned)((((pos0 / 16) * kPB + pblk) * 64 + ((pos0 % 16) / 8) * 32 + cp % 16) * 8 + pos0 % 8);
+        // conv + SiLU of period (c, hd) into its tile buffer; requests x of the period after it the moment its registers are free
+        auto finish = [&](int c, auto head_c) {
+            constexpr int hd = decltype(head_c)::value, hn = (hd + 1) % HEADS;
+            const int p = c * HEADS + hd, cn = min(hn == 0 ? c + 1 : c, nchunk - 1);
+            float xr[2][kPos + 3];
+#pragma unroll
+            for (int q = 0; q < kPos + 3; q++) {
+                xr[0][q] = __uint_as_float(xraw[q] << 16);
+                xr[1][q] = __uint_as_float(xraw[q] & 0xffff0000u);
             }
-            bf16x8 ctile[kCopy], btile[kCopy];
-            float4 gt[kHS];
-            auto issue_score = [&](int c) {
-                const float4* sc = reinterpret_cast<const float4*>(a.score_op + (((size_t)b * nchunk + c) * a.G + grp) * kScoreOp);
-#pragma unroll
-                for (int m = 0; m < kHS; m++) gt[m] = sc[m * kProdThreads + ptid];
-            };
-            auto issue_tiles = [&](int c) {
-                const __bf16* csrc = a.c_rows + (((size_t)b * Lpad + (size_t)c * kQ) * a.G + grp) * N;
-                const __bf16* bsrc = a.b_t + ((((size_t)b * nchunk + c) * a.G + grp) * N) * kQ;
-#pragma unroll
-                for (int i = 0; i < kCopy; i++) {
-                    ctile[i] = *reinterpret_cast<const bf16x8*>(csrc + c_src[i]);
-                    btile[i] = *reinterpret_cast<const bf16x8*>(bsrc + b_src[i]);
-                }
-            };
-            auto finish = [&](int c, int buf, int cn) {
-                float dl, l2;
-                scan_chunk(c, cn, dl, l2);
-                // separable decay exp(l_i - l_j) = e_i f_j around the chunk's middle unless the chunk decays too fast
-                const float l2_end = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), 63));
-                const float l2_first = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), 0));
-                const float l2_mid = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), kQ / 2 - 1));
-                const bool separable = l2_first - l2_end <= 100.0f;
-                if (separable) {
-                    pw_l2[lane] = fast_exp2(l2 - l2_mid);
-                    pw_dl[lane] = fast_exp2(l2_mid - l2) * dl;
-                } else {
-                    pw_l2[lane] = l2;
-                    pw_dl[lane] = dl;
-                }
-                if (pwave == 0) scal[buf * kQ + lane] = fast_exp2(l2);
-                __builtin_amdgcn_wave_barrier();
-                float sv[kHS][4];
-#pragma unroll
-                for (int m = 0; m < kHS; m++) { sv[m][0] = gt[m].x; sv[m][1] = gt[m].y; sv[m][2] = gt[m].z; sv[m][3] = gt[m].w; }
-                asm volatile("" ::: "memory");
-                issue_score(cn);
-#pragma unroll
-                for (int m = 0; m < kHS; m++) {
-                    const int hs = m * kProdThreads + ptid;
-                    const int bp = hs / 256, kb = (hs / 128) % 2, sl = (hs / 2) % 64, hi = hs % 2;
-                    const int iblk = bp > 0, jblk = bp > 1;
-                    const int i = iblk * 32 + sl % 32;
-                    const int jb = jblk * 32 + 16 * kb + 8 * hi + 4 * (sl / 32);
-                    const bool diagonal = iblk == jblk;
-                    const float l2i = pw_l2[i];
-                    const float4 da = *reinterpret_cast<const float4*>(&pw_dl[jb]);
-                    const float dj[4] = {da.x, da.y, da.z, da.w};
-                    bf16x4 v;
-                    if (separable) {
-#pragma unroll
-                        for (int e = 0; e < 4; e++) {
-                            const float val = sv[m][e] * l2i * dj[e];
-                            v[e] = (__bf16)((diagonal && jb + e > i) ? 0.0f : val);
-                        }
-                    } else {
-                        const float4 la = *reinterpret_cast<const float4*>(&pw_l2[jb]);
-                        const float lj[4] = {la.x, la.y, la.z, la.w};
-#pragma unroll
-                        for (int e = 0; e < 4; e++) {
-                            const float val = sv[m][e] * fast_exp2(l2i - lj[e]) * dj[e];
-                            v[e] = (__bf16)((diagonal && jb + e > i) ? 0.0f : val);
-                        }
-                    }
-                    *reinterpret_cast<bf16x4*>(&sM(buf)[(((iblk * 2 + jblk) * 2 + kb) * 64 + sl) * 8 + 4 * hi]) = v;
-                }
-#pragma unroll
-                for (int i = 0; i < kCopy; i++) {
-                    *reinterpret_cast<bf16x8*>(&sC(buf)[c_dst[i]]) = ctile[i];
-                    *reinterpret_cast<bf16x8*>(&sBT(buf)[b_dst[i]]) = btile[i];
-                }
-                asm volatile("" ::: "memory");
-                issue_tiles(cn);
-                __builtin_amdgcn_wave_barrier();   // the next chunk's scan results overwrite the tables only after these reads
-            };
-            issue_dt(0);
-            issue_score(0);
-            issue_tiles(0);
-            finish(0, 0, min(1, nchunk - 1));
-            lds_barrier();
-            for (int c = 0; c < nchunk; c++) {
-                if (c + 1 < nchunk) finish(c + 1, (c + 1) & 1, min(c + 2, nchunk - 1));
-                lds_barrier();
-            }
-        } else {
-            unsigned xraw[kPos + 3];
-            auto issue_x = [&](int c) {
-                const int tau0 = c * kQ + kPos * tg - 3;
-                if (!edge_chunk(c)) {
-                    const T* xp = xb + (long long)token_of(tau0) * a.x.st;
-#pragma unroll
-                    for (int q = 0; q < kPos + 3; q++) xraw[q] = *reinterpret_cast<const unsigned*>(xp + q * xstep);
-                } else {
-#pragma unroll
-                    for (int q = 0; q < kPos + 3; q++)
-                        xraw[q] = *reinterpret_cast<const unsigned*>(xb + (long long)token_of(min(max(tau0 + q, 0), last)) * a.x.st);
-                }
-            };
-            auto finish = [&](int c, int buf, int cn) {
-                float dl, l2;
-                scan_chunk(c, cn, dl, l2);
-                const float l2_end = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), 63));
-                pw_wgt[lane] = fast_exp2(l2_end - l2) * dl;
-                __builtin_amdgcn_wave_barrier();
-                float xr[2][kPos + 3];
+            asm volatile("" ::: "memory");
+            issue_x(cn, hn);
+            if (edge_chunk(c)) {
 #pragma unroll
                 for (int q = 0; q < kPos + 3; q++) {
-                    xr[0][q] = __uint_as_float(xraw[q] << 16);
-                    xr[1][q] = __uint_as_float(xraw[q] & 0xffff0000u);
+                    const int tau = c * kQ + kPos * tg + q - 3;
+                    if (tau < 0 || tau > last) xr[0][q] = xr[1][q] = 0.0f;
                 }
-                asm volatile("" ::: "memory");
-                issue_x(cn);
-                if (edge_chunk(c)) {
+                if (c == 0 && a.dir > 0 && a.tail_in && tg == 0 && a.K > 1) {
+                    T cached[3][2];
 #pragma unroll
-                    for (int q = 0; q < kPos + 3; q++) {
-                        const int tau = c * kQ + kPos * tg + q - 3;
-                        if (tau < 0 || tau > last) xr[0][q] = xr[1][q] = 0.0f;
+                    for (int q = 0; q < 3; q++) {   // 3 - q tokens before the block; a tap beyond the conv width has a zero weight
+                        const T* tp = (const T*)a.tail_in + ((size_t)b * (a.K - 1) + max(a.K - 1 - (3 - q), 0)) * a.tail_ch + ch0 + hd * P + 2 * cp;
+                        cached[q][0] = tp[0];
+                        cached[q][1] = tp[1];
                     }
-                    if (c == 0 && a.dir > 0 && a.tail_in && tg == 0 && a.K > 1) {
-                        T cached[3][2];
 #pragma unroll
-                        for (int q = 0; q < 3; q++) {   // 3 - q tokens before the block; a tap beyond the conv width has a zero weight
-                            const T* tp = (const T*)a.tail_in + ((size_t)b * (a.K - 1) + max(a.K - 1 - (3 - q), 0)) * a.tail_ch + ch0 + 2 * cp;
-                            cached[q][0] = tp[0];
-                            cached[q][1] = tp[1];
-                        }
-#pragma unroll
-                        for (int q = 0; q < 3; q++) {
-                            if (3 - q <= a.K - 1) {
-                                xr[0][q] = IoBF16::cvt(cached[q][0]);
-                                xr[1][q] = IoBF16::cvt(cached[q][1]);
-                            }
+                    for (int q = 0; q < 3; q++) {
+                        if (3 - q <= a.K - 1) {
+                            xr[0][q] = IoBF16::cvt(cached[q][0]);
+                            xr[1][q] = IoBF16::cvt(cached[q][1]);
                         }
                     }
                 }
-                float wq[kPos];
+            }
+            const float* const wgt = table(p) + 2 * kQ + pos0;
+            float wq[kPos];
 #pragma unroll
-                for (int q = 0; q < kPos; q += 4) {
-                    const float4 w = *reinterpret_cast<const float4*>(&pw_wgt[kPos * tg + q]);
-                    wq[q] = w.x; wq[q + 1] = w.y; wq[q + 2] = w.z; wq[q + 3] = w.w;
+            for (int q = 0; q < kPos; q += 4) {
+                const float4 w = *reinterpret_cast<const float4*>(wgt + q);
+                wq[q] = w.x; wq[q + 1] = w.y; wq[q + 2] = w.z; wq[q + 3] = w.w;
+            }
+            const int buf = p & 1;
+#pragma unroll
+            for (int h2 = 0; h2 < 2; h2++) {
+                typedef __attribute__((__vector_size__(kPos * sizeof(__bf16)))) __bf16 bf16run;
+                bf16run vw;
+                bf16x4 vx[kPos / 4];
+#pragma unroll
+                for (int q = 0; q < kPos; q++) {
+                    float pre = cbias[hd][h2];
+                    pre = fmaf(w4[hd][h2][0], xr[h2][q], pre);
+                    pre = fmaf(w4[hd][h2][1], xr[h2][q + 1], pre);
+                    pre = fmaf(w4[hd][h2][2], xr[h2][q + 2], pre);
+                    pre = fmaf(w4[hd][h2][3], xr[h2][q + 3], pre);
+                    const float xc = silu(pre);
+                    vx[q / 4][q % 4] = (__bf16)xc;
+                    vw[q] = (__bf16)(xc * wq[q]);
                 }
 #pragma unroll
-                for (int h2 = 0; h2 < 2; h2++) {
-                    typedef __attribute__((__vector_size__(kPos * sizeof(__bf16)))) __bf16 bf16run;
-                    bf16run vx, vw;
+                for (int u = 0; u < kPos / 4; u++) *reinterpret_cast<bf16x4*>(&sXc(buf)[xc_at[u] + h2 * 64 * 8]) = vx[u];
+                *reinterpret_cast<bf16run*>(&sXw(buf)[xw_at + h2 * 16 * 8]) = vw;
+            }
+        };
+        // C of a chunk to LDS for two heads: requested two periods before it is written
+        constexpr int kCopy = HEADS == 2 ? kQ * N / 8 / 256 : 1;
+        bf16x8 ctile[kCopy];
+        auto issue_c = [&](int c) {
+            const bf16x8* src = reinterpret_cast<const bf16x8*>(a.c_rows + tile_of(c) * N * kQ) + ptid;
 #pragma unroll
-                    for (int q = 0; q < kPos; q++) {
-                        float pre = cbias[h2];
-                        pre = fmaf(w4[h2][0], xr[h2][q], pre);
-                        pre = fmaf(w4[h2][1], xr[h2][q + 1], pre);
-                        pre = fmaf(w4[h2][2], xr[h2][q + 2], pre);
-                        pre = fmaf(w4[h2][3], xr[h2][q + 3], pre);
-                        const float xc = silu(pre);
-                        vx[q] = (__bf16)xc;
-                        vw[q] = (__bf16)(xc * wq[q]);
-                    }
-                    *reinterpret_cast<bf16run*>(&sXc(buf)[(2 * cp + h2) * kRowT + kPos * tg]) = vx;
-                    *reinterpret_cast<bf16run*>(&sXw(buf)[(2 * cp + h2) * kRowT + kPos * tg]) = vw;
+            for (int i = 0; i < kCopy; i++) ctile[i] = src[i * 256];
+        };
+        auto put_c = [&](int c) {
+            bf16x8* dst = reinterpret_cast<bf16x8*>(sC + (c & 1) * W::kC) + ptid;
+#pragma unroll
+            for (int i = 0; i < kCopy; i++) dst[i * 256] = ctile[i];
+        };
+        using Head0 = std::integral_constant<int, 0>;
+        using Head1 = std::integral_constant<int, HEADS - 1>;
+        if constexpr (HEADS == 2) issue_c(0);
+        issue_x(0, 0);
+        lds_barrier();   // the tables of the first two periods
+        if constexpr (HEADS == 2) {
+            put_c(0);
+            asm volatile("" ::: "memory");
+            issue_c(1);
+        }
+        finish(0, Head0{});
+        lds_barrier();
+        for (int c = 0; c < nchunk; c++) {
+            if constexpr (HEADS == 2) {
+                if (c + 1 < nchunk) {   // (the slot's last readers were in the period before this one)
+                    put_c(c + 1);
+                    asm volatile("" ::: "memory");
+                    issue_c(min(c + 2, nchunk - 1));
                 }
-                __builtin_amdgcn_wave_barrier();
-            };
-            issue_dt(0);
-            issue_x(0);
-            finish(0, 0, min(1, nchunk - 1));
+                finish(c, Head1{});
+                lds_barrier();
+            }
+            if (c + 1 < nchunk) finish(c + 1, Head0{});
             lds_barrier();
-            for (int c = 0; c < nchunk; c++) {
-                if (c + 1 < nchunk) finish(c + 1, (c + 1) & 1, min(c + 2, nchunk - 1));
+        }
+        return;
+    }
+
+    if (wave >= 2 * W::kYWaves) {
+        // ------------------------------------------------------------------ state waves
+        constexpr int kBlocks = kNB * kPB, kOwn = (kBlocks + 3) / 4;   // 32 x 32 blocks of H; of one wave: one row of blocks
+        const int sw = wave - 2 * W::kYWaves, ptid = tid - 64 * 2 * W::kYWaves;
+        const bool owner = kOwn * sw < kBlocks;
+        const int nblk = kOwn * sw / kPB, pblk0 = kOwn * sw % kPB;
+        const int cl = lane & 31, half = lane >> 5;
+        const int ch_of_lane = ch0 + 2 * (cl % 16) + cl / 16;          // + 32 per channel block
+        // a wave scans every fourth period: always the same head's
+        const int scan_head = head + sw % HEADS;
+        const float a2 = a.A[scan_head] * kLog2e;
+        const float dtb = (a.dt_softplus && a.dt_bias) ? a.dt_bias[scan_head] : 0.0f;
+        const T* dtp = (const T*)a.dt.p + (size_t)b * a.dt.sb + scan_head;
+        T dtraw;
+        auto issue_dt = [&](int p) { dtraw = dtp[(long long)token_of(min(p / HEADS * kQ + lane, last)) * a.dt.st]; };
+        // Delta and the inclusive cumulative log2-decay of a period, and what the waves read of them
+        auto scan = [&](int p) {
+            const int c = p / HEADS;
+            float dl = IoBF16::cvt(dtraw);
+            issue_dt(p + 4);   // (clamped to the sequence)
+            if (a.dt_softplus) dl = softplus(dl + dtb);
+            if (c * kQ + lane > last) dl = 0.0f;
+            const float l2 = wave_inclusive_sum(dl * a2);
+            const float l2_end = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), 63));
+            // separable decay exp(l_i - l_j) = e_i f_j around the chunk's middle unless the chunk decays too fast
+            const float l2_first = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), 0));
+            const float l2_mid = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), kQ / 2 - 1));
+            const bool separable = l2_first - l2_end <= 100.0f;
+            float* const t = table(p);
+            t[lane] = separable ? fast_exp2(l2 - l2_mid) : l2;
+            t[kQ + lane] = separable ? fast_exp2(l2_mid - l2) * dl : dl;
+            t[2 * kQ + lane] = fast_exp2(l2_end - l2) * dl;
+            t[3 * kQ + lane] = fast_exp2(l2);
+            if (lane == 0) t[4 * kQ] = separable ? 1.0f : 0.0f;
+        };
+        float4 gt[3];
+        auto issue_score = [&](int c, int m) {
+            gt[m] = reinterpret_cast<const float4*>(a.score_op + tile_of(c) * kScoreOp)[m * 256 + ptid];
+        };
+        bf16x8 bt[4];
+        auto issue_bt = [&](int c) {
+            const bf16x8* src = reinterpret_cast<const bf16x8*>(a.b_t + tile_of(c) * N * kQ) + (owner ? nblk * 4 * 64 : 0) + lane;
+#pragma unroll
+            for (int kb = 0; kb < 4; kb++) bt[kb] = src[kb * 64];
+        };
+        // (B_j . C_i) exp(l_i - l_j) Delta_j of a period, for the blocks (i, j) = (0, 0), (1, 0), (1, 1) of 32 x 32: this
+        // thread holds row i of four adjacent columns j in each.  The prepared scores are zero above the diagonal.
+        const int i32 = (ptid / 128) * 16 + (ptid / 2) % 16, j32 = 16 * (ptid % 2) + 4 * ((ptid / 32) % 4);
+        auto score = [&](int p, int cn) {   // cn: the chunk whose scores to request then, -1: they are needed again
+            const float* const t = table(p);
+            const bool separable = __builtin_amdgcn_readfirstlane(__float_as_int(t[4 * kQ])) != 0;
+            const float li[2] = {t[i32], t[32 + i32]};
+            // (block by block, each one's scores requested again as soon as they are used: the state leaves few registers)
+#pragma unroll
+            for (int m = 0; m < 3; m++) {
+                const float4 d4 = *reinterpret_cast<const float4*>(t + kQ + 32 * (m > 1) + j32);
+                const float dj[4] = {d4.x, d4.y, d4.z, d4.w}, sv[4] = {gt[m].x, gt[m].y, gt[m].z, gt[m].w};
+                bf16x4 v;
+                if (separable) {
+#pragma unroll
+                    for (int e = 0; e < 4; e++) v[e] = (__bf16)(sv[e] * li[m > 0] * dj[e]);
+                } else {
+                    const float4 l4 = *reinterpret_cast<const float4*>(t + 32 * (m > 1) + j32);
+                    const float lj[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        const float val = sv[e] * fast_exp2(li[m > 0] - lj[e]) * dj[e];
+                        v[e] = (__bf16)((m != 1 && j32 + e > i32) ? 0.0f : val);
+                    }
+                }
+                *reinterpret_cast<bf16x4*>(&sM(p & 1)[(m * 256 + ptid) * 4]) = v;
+                asm volatile("" ::: "memory");
+                if (cn >= 0) issue_score(cn, m);
+            }
+        };
+        f32x16 hacc[HEADS][kOwn];
+#pragma unroll
+        for (int hd = 0; hd < HEADS; hd++)
+#pragma unroll
+            for (int o = 0; o < kOwn; o++) {
+#pragma unroll
+                for (int r = 0; r < 16; r++) hacc[hd][o][r] = 0.0f;
+                if (a.h_in && owner) {   // registers 4q .. 4q+3: four adjacent states of the lane's channel
+                    const float* hrow = a.h_in + ((size_t)b * a.Dn + ch_of_lane + hd * P + (pblk0 + o) * 32) * N + nblk * 32 + 4 * half;
+#pragma unroll
+                    for (int q = 0; q < 4; q++) {
+                        const float4 v = *reinterpret_cast<const float4*>(hrow + 8 * q);
+                        hacc[hd][o][4 * q] = v.x; hacc[hd][o][4 * q + 1] = v.y; hacc[hd][o][4 * q + 2] = v.z; hacc[hd][o][4 * q + 3] = v.w;
+                    }
+                }
+            }
+        auto publish_state = [&](auto head_c, int which) {
+            constexpr int hd = decltype(head_c)::value;
+            if (!owner) return;
+#pragma unroll
+            for (int o = 0; o < kOwn; o++) {
+#pragma unroll
+                for (int u = 0; u < 2; u++) {
+                    bf16x8 v;
+#pragma unroll
+                    for (int e = 0; e < 8; e++) v[e] = (__bf16)hacc[hd][o][8 * u + e];
+                    *reinterpret_cast<bf16x8*>(&sHT[which * W::kHT + (((nblk * kPB + pblk0 + o) * 2 + cl / 16) * 64 + (2 * half + u) * 16 + cl % 16) * 8]) = v;
+                }
+            }
+        };
+        auto update = [&](auto head_c, int c) {
+            constexpr int hd = decltype(head_c)::value;
+            const int p = c * HEADS + hd;
+            // the state after the last chunk matters only if it is committed
+            if (!owner || (c + 1 >= nchunk && a.h_out == nullptr)) return;
+            const float decay_q = table(p)[3 * kQ + kQ - 1];
+            const bf16x8* xw = reinterpret_cast<const bf16x8*>(sXw(p & 1)) + lane;
+#pragma unroll
+            for (int o = 0; o < kOwn; o++)
+#pragma unroll
+                for (int r = 0; r < 16; r++) hacc[hd][o][r] *= decay_q;
+#pragma unroll
+            for (int kb = 0; kb < 4; kb++) {
+                // (two heads' states leave no registers for operands that wait)
+                if (HEADS == 2 && kb % 2 == 0) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int o = 0; o < kOwn; o++)
+                    hacc[hd][o] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bt[kb], xw[(kb * kPB + pblk0 + o) * 64], hacc[hd][o], 0, 0, 0);
+            }
+            if (HEADS == 2) __builtin_amdgcn_sched_barrier(0);
+        };
+        auto scan_ahead = [&](int p) { if (((p + 2) & 3) == sw) scan(p + 2); };
+        using Head0 = std::integral_constant<int, 0>;
+        using Head1 = std::integral_constant<int, HEADS - 1>;
+        issue_dt(sw);
+#pragma unroll
+        for (int m = 0; m < 3; m++) issue_score(0, m);
+        issue_bt(0);
+        if (sw < 2) scan(sw);
+        lds_barrier();   // the tables of the first two periods
+        score(0, HEADS == 1 ? 1 : -1);
+        publish_state(Head0{}, 0);
+        if constexpr (HEADS == 2) publish_state(Head1{}, 1);
+        lds_barrier();
+        for (int c = 0; c < nchunk; c++) {
+            const int cn = min(c + 1, nchunk - 1);
+            if constexpr (HEADS == 1) {
+                scan_ahead(c);
+                update(Head0{}, c);
+                asm volatile("" ::: "memory");
+                issue_bt(cn);
+                if (c + 1 < nchunk) {
+                    score(c + 1, min(c + 2, nchunk - 1));
+                    publish_state(Head0{}, (c + 1) & 1);   // (the chunk's own copy is still being read)
+                }
+                lds_barrier();
+            } else {
+                // a head's new state is published in the other head's period, when nothing reads its copy
+                scan_ahead(2 * c);
+                if (c > 0) publish_state(Head1{}, 1);
+                update(Head0{}, c);
+                score(2 * c + 1, cn);
+                lds_barrier();
+                scan_ahead(2 * c + 1);
+                publish_state(Head0{}, 0);
+                update(Head1{}, c);
+                asm volatile("" ::: "memory");
+                issue_bt(cn);
+                if (c + 1 < nchunk) score(2 * c + 2, -1);
                 lds_barrier();
             }
         }
-        return;
-    }
-
-    if (wave >= W::kYWaves) {
-        // ------------------------------------------------------------------ h waves: row block nblk of the state
-        const int nblk = wave - W::kYWaves;
-        f32x16 hacc[kPB];
+        if (a.h_out && owner) {
 #pragma unroll
-        for (int pb = 0; pb < kPB; pb++) {
+            for (int hd = 0; hd < HEADS; hd++)
 #pragma unroll
-            for (int r = 0; r < 16; r++) hacc[pb][r] = 0.0f;
-            if (a.h_in) {   // registers 4q .. 4q+3: four adjacent states of channel pb*32 + cl
-                const float* hrow = a.h_in + ((size_t)b * a.Dn + ch0 + pb * 32 + cl) * N + nblk * 32 + 4 * half;
+                for (int o = 0; o < kOwn; o++) {
+                    float* hrow = a.h_out + ((size_t)b * a.Dn + ch_of_lane + hd * P + (pblk0 + o) * 32) * N + nblk * 32 + 4 * half;
 #pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    const float4 v = *reinterpret_cast<const float4*>(hrow + 8 * q);
-                    hacc[pb][4 * q] = v.x; hacc[pb][4 * q + 1] = v.y; hacc[pb][4 * q + 2] = v.z; hacc[pb][4 * q + 3] = v.w;
+                    for (int q = 0; q < 4; q++)
+                        *reinterpret_cast<float4*>(hrow + 8 * q) =
+                            make_float4(hacc[hd][o][4 * q], hacc[hd][o][4 * q + 1], hacc[hd][o][4 * q + 2], hacc[hd][o][4 * q + 3]);
                 }
-            }
-        }
-        auto publish_state = [&](int which) {
-#pragma unroll
-            for (int pb = 0; pb < kPB; pb++) {
-#pragma unroll
-                for (int kb = 0; kb < 2; kb++) {
-                    bf16x8 v;
-#pragma unroll
-                    for (int e = 0; e < 8; e++) v[e] = (__bf16)hacc[pb][8 * kb + e];
-                    *reinterpret_cast<bf16x8*>(&sHT[which * Lds::kHT + (((nblk * kPB + pb) * 2 + kb) * 64 + lane) * 8]) = v;
-                }
-            }
-        };
-        publish_state(0);
-        lds_barrier();
-        for (int c = 0; c < nchunk; c++) {
-            const int buf = c & 1;
-            if (c + 1 < nchunk || a.h_out != nullptr) {   // the state after the last chunk matters only if it is committed
-                const float decay_q = scal[buf * kQ + kQ - 1];
-                const __bf16* b_t = sBT(buf);
-                const __bf16* xw_t = sXw(buf);
-#pragma unroll
-                for (int pb = 0; pb < kPB; pb++)
-#pragma unroll
-                    for (int r = 0; r < 16; r++) hacc[pb][r] *= decay_q;
-#pragma unroll
-                for (int kb = 0; kb < 4; kb++) {
-                    const bf16x8 ab = *reinterpret_cast<const bf16x8*>(&b_t[(nblk * 32 + cl) * kRowT + 16 * kb + 8 * half]);
-#pragma unroll
-                    for (int pb = 0; pb < kPB; pb++) {
-                        const bf16x8 bw = *reinterpret_cast<const bf16x8*>(&xw_t[(pb * 32 + cl) * kRowT + 16 * kb + 8 * half]);
-                        hacc[pb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ab, bw, hacc[pb], 0, 0, 0);
-                    }
-                }
-            }
-            if (c + 1 < nchunk) publish_state(buf ^ 1);
-            lds_barrier();
-        }
-        if (a.h_out) {
-#pragma unroll
-            for (int pb = 0; pb < kPB; pb++) {
-                float* hrow = a.h_out + ((size_t)b * a.Dn + ch0 + pb * 32 + cl) * N + nblk * 32 + 4 * half;
-#pragma unroll
-                for (int q = 0; q < 4; q++)
-                    *reinterpret_cast<float4*>(hrow + 8 * q) =
-                        make_float4(hacc[pb][4 * q], hacc[pb][4 * q + 1], hacc[pb][4 * q + 2], hacc[pb][4 * q + 3]);
-            }
         }
         return;
     }
 
-    // ---------------------------------------------------------------------- y waves: one 32 x 32 block of the output
-    auto walk = [&](auto mode_c) {
-        constexpr int kMode = decltype(mode_c)::value;
-        constexpr bool need_z = kMode != kSsdPartialRaw;
-        constexpr bool need_p = kMode == kSsdFinalAdd || kMode == kSsdFinalAddRaw;
-        constexpr bool parks = kMode == kSsdPartialRaw || kMode == kSsdPartial;
-        const int iblk = wave / kPB, pblk = wave % kPB;
-        const int po = pblk * 32 + cl;
-        const int icol = iblk * 32 + cl;
-        const int i0 = iblk * 32 + 4 * half;
-        auto row_k = [](int r) { return 8 * (r / 4) + (r % 4); };
-        const float dval = a.D[a.d_per_head ? head : ch0 + po];
-        // rows of a chunk that lies inside the sequence, relative to the chunk's lowest-address token: the row of
-        // accumulator register 4q + e is group[q] (in the lane offset) plus step[e] (a scalar offset), see the header
-        const int fwd = a.dir > 0;
-        const unsigned zs = (unsigned)a.z.st * 2u, os = (unsigned)a.out_st * 2u, ps = (unsigned)a.Dn * 2u;
-        unsigned zoff[4], ooff[4], poff[4];
+    // ---------------------------------------------------------------------- y waves: one 32 x 32 block of every other period's output
+    constexpr bool need_z = MODE != kSsdPartialRaw;
+    constexpr bool need_p = MODE == kSsdFinalAdd || MODE == kSsdFinalAddRaw;
+    constexpr bool parks = MODE == kSsdPartialRaw || MODE == kSsdPartial;
+    const int set = wave / W::kYWaves, iblk = (wave / kPB) % 2, pblk = wave % kPB;
+    const int col = lane & 15, g4 = lane >> 4;
+    const int po = pblk * 32 + 2 * col;        // this lane's channel pair
+    const int i0 = iblk * 32 + 4 * g4;         // output row of row tile 0, register 0
+    const int my_head = head + (HEADS == 2 ? set : 0), my_ch0 = my_head * P;
+    const float dval[2] = {a.D[a.d_per_head ? my_head : my_ch0 + po], a.D[a.d_per_head ? my_head : my_ch0 + po + 1]};
+    // rows of a chunk that lies inside the sequence, relative to the chunk's lowest-address token: row 16 rt + r of
+    // the lane is group[rt] (in the lane offset) plus step[r] (a scalar offset): no vector address arithmetic
+    const int fwd = a.dir > 0;
+    const unsigned zs = (unsigned)a.z.st * 2u, os = (unsigned)a.out_st * 2u, ps = (unsigned)a.Dn * 2u;
+    unsigned zoff[2], ooff[2], poff[2];
 #pragma unroll
-        for (int q = 0; q < 4; q++) {
-            const unsigned rows = (unsigned)(fwd ? iblk * 32 + 8 * q + 4 * half : 56 - iblk * 32 - 8 * q + 4 * (1 - half));
-            zoff[q] = rows * zs + 2u * (unsigned)po;
-            ooff[q] = rows * os + 2u * (unsigned)po;
-            poff[q] = rows * ps + 2u * (unsigned)po;
-        }
-        // (scalar registers by construction: left to the compiler the direction select lands in vector registers and
-        // every access loops over the lanes to read its offset back)
-        int zstep[4], ostep[4], pstep[4];
+    for (int rt = 0; rt < 2; rt++) {
+        const unsigned rows = (unsigned)(fwd ? i0 + 16 * rt : kQ - 4 - i0 - 16 * rt);
+        zoff[rt] = rows * zs + 2u * (unsigned)po;
+        ooff[rt] = rows * os + 2u * (unsigned)po;
+        poff[rt] = rows * ps + 2u * (unsigned)po;
+    }
+    // (scalar registers by construction: left to the compiler the direction select lands in vector registers and
+    // every access loops over the lanes to read its offset back)
+    int zstep[4], ostep[4], pstep[4];
 #pragma unroll
-        for (int e = 0; e < 4; e++) {
-            const int m = fwd ? e : 3 - e;
-            zstep[e] = __builtin_amdgcn_readfirstlane(m * (int)zs);
-            ostep[e] = __builtin_amdgcn_readfirstlane(m * (int)os);
-            pstep[e] = __builtin_amdgcn_readfirstlane(m * (int)ps);
-        }
-        const T* const zhead = (const T*)a.z.p + (size_t)b * a.z.sb + ch0;
-        const T* const phead = (const T*)a.partial + (size_t)b * a.L * a.Dn + ch0;   // the parked result is bf16
-        T* const ohead = (T*)a.out + (size_t)b * a.out_sb + a.out_ch_off + ch0;
-        auto chunk_low_token = [&](int c) { return (long long)(fwd ? c * kQ : last - (c * kQ + kQ - 1)); };
+    for (int e = 0; e < 4; e++) {
+        const int m = fwd ? e : 3 - e;
+        zstep[e] = __builtin_amdgcn_readfirstlane(m * (int)zs);
+        ostep[e] = __builtin_amdgcn_readfirstlane(m * (int)os);
+        pstep[e] = __builtin_amdgcn_readfirstlane(m * (int)ps);
+    }
+    const T* const zhead = (const T*)a.z.p + (size_t)b * a.z.sb + my_ch0;
+    T* const phead = (T*)a.partial + (size_t)b * a.L * a.Dn + my_ch0;   // the parked result is bf16
+    T* const ohead = (T*)a.out + (size_t)b * a.out_sb + a.out_ch_off + my_ch0;
+    auto chunk_low_token = [&](int c) { return (long long)(fwd ? c * kQ : last - (c * kQ + kQ - 1)); };
+    // (channel pairs of z and out are 4-byte pieces where the host found them aligned)
+    auto inside = [&](int c) { return c * kQ + kQ - 1 <= last && a.pairs; };
+    auto token_at = [&](int c, int k) { return (long long)token_of(min(c * kQ + i0 + 16 * (k / 4) + k % 4, last)); };
 
-        T zraw[16], praw[16];
-        auto issue_gate = [&](int c) {
-            if (c * kQ + kQ - 1 <= last) {
-                const long long t0 = chunk_low_token(c);
-                const Rsrc zr = raw_range(zhead + t0 * a.z.st), pr = raw_range(phead + t0 * a.Dn);
+    unsigned zraw[8], praw[8];   // register k: row 16 (k / 4) + k % 4 of the lane, a channel pair
+    auto issue_z = [&](int c) {
+        if constexpr (!need_z) return;
+        if (inside(c)) {
+            const Rsrc zr = raw_range(zhead + chunk_low_token(c) * a.z.st);
 #pragma unroll
-                for (int r = 0; r < 16; r++) {
-                    if constexpr (need_z) zraw[r] = IoBF16::ld_raw(zr, zoff[r / 4], zstep[r % 4]);
-                    if constexpr (need_p) praw[r] = IoBF16::ld_raw(pr, poff[r / 4], pstep[r % 4]);
-                }
-            } else {
-                const int tau0 = c * kQ + i0;
+            for (int k = 0; k < 8; k++) zraw[k] = __builtin_amdgcn_raw_buffer_load_b32(zr, zoff[k / 4], zstep[k % 4], 0);
+        } else {
 #pragma unroll
-                for (int r = 0; r < 16; r++) {
-                    const long long t = token_of(min(tau0 + row_k(r), last));
-                    if constexpr (need_z) zraw[r] = zhead[t * a.z.st + po];
-                    if constexpr (need_p) praw[r] = phead[t * a.Dn + po];
-                }
+            for (int k = 0; k < 8; k++) {
+                const T* zp = zhead + token_at(c, k) * a.z.st + po;
+                zraw[k] = (unsigned)zp[0] | ((unsigned)zp[1] << 16);
             }
-        };
-        bool state_nonzero = a.h_in != nullptr;
-        issue_gate(0);
-        lds_barrier();
-        for (int c = 0; c < nchunk; c++) {
-            const int buf = c & 1;
-            const float* el = scal + buf * kQ;
-            const __bf16* xc_t = sXc(buf);
-            f32x16 y1 = {0}, y2 = {0};
-#pragma unroll
-            for (int jblk = 0; jblk < 2; jblk++) {
-                if (jblk > iblk) break;
-#pragma unroll
-                for (int kb = 0; kb < 2; kb++) {
-                    const bf16x8 am = *reinterpret_cast<const bf16x8*>(&sM(buf)[(((iblk * 2 + jblk) * 2 + kb) * 64 + lane) * 8]);
-                    bf16x8 bx;
-#pragma unroll
-                    for (int jj = 0; jj < 2; jj++) {
-                        const bf16x4 v = *reinterpret_cast<const bf16x4*>(&xc_t[po * kRowT + jblk * 32 + 16 * kb + 8 * jj + 4 * half]);
-#pragma unroll
-                        for (int e = 0; e < 4; e++) bx[4 * jj + e] = v[e];
-                    }
-                    y1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bx, y1, 0, 0, 0);
-                }
-            }
-            if (state_nonzero) {
-                const __bf16* c_t = sC(buf);
-                const __bf16* h_t = sHT + buf * Lds::kHT;
-#pragma unroll
-                for (int nb = 0; nb < kNB; nb++) {
-#pragma unroll
-                    for (int kb = 0; kb < 2; kb++) {
-                        bf16x8 ac;
-#pragma unroll
-                        for (int jj = 0; jj < 2; jj++) {
-                            const bf16x4 v = *reinterpret_cast<const bf16x4*>(&c_t[icol * kRowC + nb * 32 + 16 * kb + 8 * jj + 4 * half]);
-#pragma unroll
-                            for (int e = 0; e < 4; e++) ac[4 * jj + e] = v[e];
-                        }
-                        const bf16x8 bh = *reinterpret_cast<const bf16x8*>(&h_t[(((nb * kPB + pblk) * 2 + kb) * 64 + lane) * 8]);
-                        y2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ac, bh, y2, 0, 0, 0);
-                    }
-                }
-            }
-            // epilogue: inter-chunk term, skip term, gate, combine; all 16 results first, then the stores
-            float res[16];
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const float4 e4 = *reinterpret_cast<const float4*>(&el[i0 + 8 * q]);
-                const bf16x4 x4 = *reinterpret_cast<const bf16x4*>(&xc_t[po * kRowT + i0 + 8 * q]);
-                const float ev[4] = {e4.x, e4.y, e4.z, e4.w};
-#pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const int r = 4 * q + e;
-                    const float y = y1[r] + ev[e] * y2[r] + dval * (float)x4[e];
-                    if constexpr (!need_z) res[r] = y;
-                    else {
-                        const float zg = silu(IoBF16::cvt(zraw[r]));
-                        const float pv = need_p ? IoBF16::cvt(praw[r]) : 0.0f;
-                        res[r] = kMode == kSsdFinalAddRaw ? (y + pv) * zg : need_p ? y * zg + pv : y * zg;
-                    }
-                }
-            }
-            if (c * kQ + kQ - 1 <= last) {
-                const long long t0 = chunk_low_token(c);
-                const Rsrc orr = raw_range(parks ? (T*)phead + t0 * a.Dn : ohead + t0 * a.out_st);
-#pragma unroll
-                for (int r = 0; r < 16; r++) {
-                    if constexpr (parks) IoBF16::st_raw(orr, poff[r / 4], pstep[r % 4], res[r]);
-                    else IoBF16::st_raw(orr, ooff[r / 4], ostep[r % 4], res[r]);
-                }
-            } else {
-                const int tau0 = c * kQ + i0;
-#pragma unroll
-                for (int r = 0; r < 16; r++) {
-                    const int tau = tau0 + row_k(r);
-                    if (tau <= last) {
-                        const long long t = token_of(tau);
-                        if constexpr (parks) IoBF16::st((T*)phead + t * a.Dn + po, res[r]);
-                        else IoBF16::st(ohead + t * a.out_st + po, res[r]);
-                    }
-                }
-            }
-            if (c + 1 < nchunk) issue_gate(c + 1);
-            state_nonzero = true;
-            lds_barrier();
         }
     };
-    if constexpr (DIRS == 2) {
-        walk(std::integral_constant<int, kSsdFinalOnly>{});
-        return;
-    }
-    switch (a.mode) {
-        case kSsdPartial: walk(std::integral_constant<int, kSsdPartial>{}); break;
-        case kSsdPartialRaw: walk(std::integral_constant<int, kSsdPartialRaw>{}); break;
-        case kSsdFinalAdd: walk(std::integral_constant<int, kSsdFinalAdd>{}); break;
-        default: walk(std::integral_constant<int, kSsdFinalAddRaw>{}); break;
+    auto issue_p = [&](int c) {
+        if constexpr (!need_p) return;
+        if (inside(c)) {
+            const Rsrc pr = raw_range(phead + chunk_low_token(c) * a.Dn);
+#pragma unroll
+            for (int k = 0; k < 8; k++) praw[k] = __builtin_amdgcn_raw_buffer_load_b32(pr, poff[k / 4], pstep[k % 4], 0);
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; k++) praw[k] = *reinterpret_cast<const unsigned*>(phead + token_at(c, k) * a.Dn + po);
+        }
+    };
+    bf16x8 cf[HEADS == 1 ? kNB : 1][2];   // one head: C operand straight from global memory, [32 states][row tile]
+    auto issue_c = [&](int c) {
+        if constexpr (HEADS == 2) return;
+        const bf16x8* src = reinterpret_cast<const bf16x8*>(a.c_rows + tile_of(c) * N * kQ) + iblk * 2 * kNB * 64 + lane;
+#pragma unroll
+        for (int nb = 0; nb < kNB; nb++)
+#pragma unroll
+            for (int rt = 0; rt < 2; rt++) cf[HEADS == 1 ? nb : 0][rt] = src[(rt * kNB + nb) * 64];
+    };
+    auto lo = [](unsigned v) { return __uint_as_float(v << 16); };
+    auto hi = [](unsigned v) { return __uint_as_float(v & 0xffff0000u); };
+
+    const int mine = HEADS == 2 ? 0 : min(set, nchunk - 1);
+    issue_c(mine);
+    issue_z(mine);
+    issue_p(mine);
+    lds_barrier();
+    lds_barrier();
+    if (set == 1) lds_barrier();   // period 0 belongs to the other set
+    const int buf = set;           // of the set's tiles and of its state operand
+    for (int p = set; p < periods; p += 2) {
+        const int c = p / HEADS, cn = p + 2 < periods ? (p + 2) / HEADS : c;
+        f32x4 y1[2][2], y2[2][2];
+#pragma unroll
+        for (int rt = 0; rt < 2; rt++)
+#pragma unroll
+            for (int ct = 0; ct < 2; ct++) y1[rt][ct] = y2[rt][ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        if (c > 0 || a.h_in != nullptr) {
+            const bf16x8* c_t = reinterpret_cast<const bf16x8*>(sC + (c & 1) * W::kC) + iblk * 2 * kNB * 64 + lane;
+            const bf16x8* h_t = reinterpret_cast<const bf16x8*>(sHT + buf * W::kHT) + pblk * 2 * 64 + lane;
+#pragma unroll
+            for (int nb = 0; nb < kNB; nb++)
+#pragma unroll
+                for (int ct = 0; ct < 2; ct++) {
+                    const bf16x8 bh = h_t[(nb * kPB * 2 + ct) * 64];
+#pragma unroll
+                    for (int rt = 0; rt < 2; rt++) {
+                        const bf16x8 ac = HEADS == 1 ? cf[HEADS == 1 ? nb : 0][rt] : c_t[(rt * kNB + nb) * 64];
+                        y2[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ac, bh, y2[rt][ct], 0, 0, 0);
+                    }
+                }
+        }
+        bf16x8 bx[2];        // after the loop: the diagonal block's
+#pragma unroll
+        for (int jblk = 0; jblk < 2; jblk++) {
+            if (jblk > iblk) break;
+            const bf16x8* m_t = reinterpret_cast<const bf16x8*>(sM(buf)) + (iblk + jblk) * 2 * 64 + lane;
+            const bf16x8* x_t = reinterpret_cast<const bf16x8*>(sXc(buf)) + (jblk * kPB + pblk) * 2 * 64 + lane;
+            bf16x8 am[2];
+#pragma unroll
+            for (int k = 0; k < 2; k++) { am[k] = m_t[k * 64]; bx[k] = x_t[k * 64]; }
+#pragma unroll
+            for (int rt = 0; rt < 2; rt++)
+#pragma unroll
+                for (int ct = 0; ct < 2; ct++) y1[rt][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(am[rt], bx[ct], y1[rt][ct], 0, 0, 0);
+        }
+        asm volatile("" ::: "memory");
+        issue_c(cn);
+        // inter-chunk and skip term
+        float y[8][2];
+        const float* const e_l = table(p) + 3 * kQ + i0;
+#pragma unroll
+        for (int rt = 0; rt < 2; rt++) {
+            const float4 v = *reinterpret_cast<const float4*>(e_l + 16 * rt);
+            const float el[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int r = 0; r < 4; r++)
+#pragma unroll
+                for (int ct = 0; ct < 2; ct++)
+                    y[4 * rt + r][ct] = y1[rt][ct][r] + el[r] * y2[rt][ct][r] + dval[ct] * (float)bx[ct][4 * rt + r];
+        }
+        lds_barrier();
+        // epilogue: gate, combine, round, a channel pair at a time
+        unsigned res[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) {
+            float v[2];
+#pragma unroll
+            for (int ct = 0; ct < 2; ct++) {
+                const float pv = need_p ? (ct == 0 ? lo(praw[k]) : hi(praw[k])) : 0.0f;
+                if constexpr (!need_z) v[ct] = y[k][ct];
+                else {
+                    const float zg = silu(ct == 0 ? lo(zraw[k]) : hi(zraw[k]));
+                    v[ct] = MODE == kSsdFinalAddRaw ? (y[k][ct] + pv) * zg : need_p ? y[k][ct] * zg + pv : y[k][ct] * zg;
+                }
+            }
+            typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+            const bf16x2 pair = {(__bf16)v[0], (__bf16)v[1]};
+            res[k] = __builtin_bit_cast(unsigned, pair);
+        }
+        if (inside(c)) {
+            const long long t0 = chunk_low_token(c);
+            const Rsrc orr = raw_range(parks ? phead + t0 * a.Dn : ohead + t0 * a.out_st);
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                if constexpr (parks) __builtin_amdgcn_raw_buffer_store_b32(res[k], orr, poff[k / 4], pstep[k % 4], 0);
+                else __builtin_amdgcn_raw_buffer_store_b32(res[k], orr, ooff[k / 4], ostep[k % 4], 0);
+            }
+        } else {
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                const int tau = c * kQ + i0 + 16 * (k / 4) + k % 4;
+                if (tau <= last) {
+                    const long long t = token_of(tau);
+                    if constexpr (parks) *reinterpret_cast<unsigned*>(phead + t * a.Dn + po) = res[k];
+                    else {
+                        T* const o = ohead + t * a.out_st + po;
+                        o[0] = (T)res[k];
+                        o[1] = (T)(res[k] >> 16);
+                    }
+                }
+            }
+        }
+        issue_z(cn);
+        issue_p(cn);
+        if (p + 1 < periods) lds_barrier();   // (the other set's period)
     }
 }
 

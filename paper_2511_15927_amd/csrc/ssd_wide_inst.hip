@@ -1,0 +1,45 @@
+// Launcher of the many-wave chunk walk (ssd_wide.h) for one (BM_N, BM_P), set on the command line.
+#include "ssd_wide.h"
+#include "launch.h"
+
+#include <atomic>
+
+namespace bm {
+
+template <int HEADS, int MODE>
+static void variant(const SsdStatePair& sp, int batch, hipStream_t st)
+{
+    static std::atomic<bool> seen[kMaxSeenDevices];
+    using W = SsdWide<BM_N, BM_P, HEADS>;
+    auto kernel = ssd_wide_kernel<BM_N, BM_P, HEADS, MODE>;
+    if (first_use_on_current_device(seen))
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)W::bytes());
+    const dim3 grid((unsigned)(sp.dir[0].H / HEADS), MODE == kSsdFinalOnly ? 2u : 1u, (unsigned)batch), block(W::kThreads);
+    if constexpr (MODE == kSsdFinalOnly) hipLaunchKernelGGL(kernel, grid, block, W::bytes(), st, sp);
+    else hipLaunchKernelGGL(kernel, grid, block, W::bytes(), st, sp.dir[0]);
+}
+
+template <int HEADS>
+static void launch(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
+{
+    if (dirs == 2) return variant<HEADS, kSsdFinalOnly>(sp, batch, st);
+    switch (sp.dir[0].mode) {
+        case kSsdPartial: return variant<HEADS, kSsdPartial>(sp, batch, st);
+        case kSsdPartialRaw: return variant<HEADS, kSsdPartialRaw>(sp, batch, st);
+        case kSsdFinalAdd: return variant<HEADS, kSsdFinalAdd>(sp, batch, st);
+        default: return variant<HEADS, kSsdFinalAddRaw>(sp, batch, st);
+    }
+}
+
+#define BM_NAME2(n, p) launch_ssd_wide_n##n##_p##p
+#define BM_NAME(n, p) BM_NAME2(n, p)
+
+// Two heads to a workgroup once one head each would not fit the chip at once: they share the tiles of their group.
+void BM_NAME(BM_N, BM_P)(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
+{
+    const SsdArgs& sa = sp.dir[0];
+    if (sa.HG % 2 == 0 && (long long)sa.H * batch * dirs > cu_count()) launch<2>(sp, dirs, batch, st);
+    else launch<1>(sp, dirs, batch, st);
+}
+
+}  // namespace bm

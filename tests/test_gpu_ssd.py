@@ -271,3 +271,54 @@ def test_ssd_both_directions_in_one_launch(gpu, oracle, L, batch, heads, headdim
     bd.bimamba_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp), bd.make_inputs(dinp_b), bd.make_tensor(out), ws)
     torch.cuda.synchronize()
     assert_close(out.float().cpu().numpy().reshape(ref.shape), ref, gpu.TOL["bf16"])
+
+
+@pytest.mark.parametrize("N,P", [(128, 64), (128, 32), (64, 64), (64, 32)])
+@pytest.mark.parametrize("L,heads,groups,kw", [
+    (65, 130, 1, {}),                              # two chunks, the second of one token; two heads to a workgroup
+    (200, 132, 2, dict(d_conv=3)),                 # four chunks, two groups
+    (130, 131, 1, dict(d_kind=0)),                 # three chunks, an odd head count: one head to a workgroup
+])
+def test_ssd_wide_forms(gpu, oracle, N, P, L, heads, groups, kw):
+    """Enough (batch, head) items for the many-wave walk in both of its forms, as a block call from a cached state and tail
+    (the state and the tail are committed), with the parked result gated and ungated, and with output halves kept apart."""
+    cfg = synth.m2_cfg(2, L, heads * P, headdim=P, d_state=N, n_groups=groups, **kw)
+    pf, pb, inp = case(cfg, 3100 + L + N + P)
+    g = torch.Generator().manual_seed(L + P)
+    K, Dn = cfg["d_conv"], cfg["d_inner"]
+    h0 = (0.2 * torch.randn(2, Dn, N, generator=g)).float()
+    tail0 = synth.round_io(torch.randn(2, K - 1, synth.conv_channels(cfg), generator=g), "bf16")
+    sel = sorted(np.random.default_rng(L).choice(Dn, size=40, replace=False).tolist() + [0, Dn - 1])
+    inp_b = dict(inp, z=synth.make_inputs(cfg, 3200 + L)["z"])
+    for combine, other in ((0, None), (0, inp_b), (1, inp_b)):
+        c = dict(cfg, combine=combine)
+        ref, h_ref, t_ref = oracle.bimamba_block_fwd(c, to_np(pf), to_np(pb), to_np(inp), None if other is None else to_np(other),
+                                                     h_in=h0.numpy(), tail_in=tail0.numpy(), sel=sel)
+        out, h, tail = gpu.gpu_block_fwd(c, pf, pb, inp, other, h_in=h0, tail_in=tail0)
+        assert_close(out[..., sel], ref, gpu.TOL["bf16"], (combine, other is not None))
+        assert rel_l2(h[:, sel, :], h_ref[:, sel, :]) < 1e-2
+        assert np.array_equal(tail, t_ref)
+
+
+@pytest.mark.parametrize("heads", [4, 260])
+def test_ssd_wide_fast_decay_and_odd_pitch(gpu, oracle, heads):
+    """Chunks that decay by more than 2^100 (per-element decay factors), and z and out that are not aligned channel pairs."""
+    from paper_2511_15927_amd import binding as bd
+    cfg = synth.m2_cfg(1, 150, heads * 32, headdim=32, d_state=64)
+    pf, pb, inp = case(cfg, 3300)
+    for p in (pf, pb):
+        p["A"] = p["A"] * torch.where(torch.arange(heads) % 2 == 0, 40.0, 1.0)
+    ref = oracle.bimamba_fwd(cfg, to_np(pf), to_np(pb), to_np(inp))
+    assert_close(gpu.gpu_fwd(cfg, pf, pb, inp), ref, gpu.TOL["bf16"])
+    Dn = cfg["d_inner"]
+    dinp = bd.to_device(inp, cfg)
+    z = torch.empty(1, 150, Dn + 3, dtype=torch.bfloat16, device="cuda")[:, :, 1:1 + Dn]
+    z.copy_(dinp["z"])
+    dinp["z"] = z
+    big = torch.zeros(1, 150, Dn + 5, dtype=torch.bfloat16, device="cuda")
+    out = big[:, :, 2:2 + Dn]
+    desc, dpf, dpb = bd.make_desc(cfg), bd.to_device(pf), bd.to_device(pb)
+    bd.bimamba_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp), None, bd.make_tensor(out), bd.alloc_workspace(desc))
+    torch.cuda.synchronize()
+    assert_close(out.float().cpu().numpy(), ref, gpu.TOL["bf16"])
+    assert torch.all(big[:, :, :2] == 0) and torch.all(big[:, :, 2 + Dn:] == 0)
