@@ -112,8 +112,8 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
         const T* xb = (const T*)a.x.p + (size_t)b * a.x.sb + ch0 + 2 * cp;
         const long long xstep = a.dir * a.x.st;
         const auto edge_chunk = [&](int c) { return c == 0 || c * kQ + kQ - 1 > last; };
-        unsigned xraw[kPos + 3];
-        auto issue_x = [&](int c, int hd) {
+        unsigned xraw[2][kPos + 3];   // of the periods of either parity, requested two periods ahead
+        auto issue_x = [&](int c, int hd, unsigned (&xraw)[kPos + 3]) {
             const int tau0 = c * kQ + kPos * tg - 3;
             const T* const xh = xb + hd * P;
             if (!edge_chunk(c)) {
@@ -135,18 +135,19 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
             xc_at[u] = (unsigned)((((pos / 32) * kPB + pblk) * 2 * 64 + ((pos % 16) / 4) * 16 + cp % 16) * 8 + 4 * ((pos % 32) / 16));
         }
         xw_at = (unsigned)((((pos0 / 16) * kPB + pblk) * 64 + ((pos0 % 16) / 8) * 32 + cp % 16) * 8 + pos0 % 8);
-        // conv + SiLU of period (c, hd) into its tile buffer; requests x of the period after it the moment its registers are free
-        auto finish = [&](int c, auto head_c) {
-            constexpr int hd = decltype(head_c)::value, hn = (hd + 1) % HEADS;
-            const int p = c * HEADS + hd, cn = min(hn == 0 ? c + 1 : c, nchunk - 1);
+        // conv + SiLU of period p (of parity odd) into its tile buffer; requests x of period p + 2 the moment its registers are free
+        auto finish = [&](int p, auto odd_c) {
+            constexpr int odd = decltype(odd_c)::value, hd = odd % HEADS;
+            const int c = p / HEADS, cn = min((p + 2) / HEADS, nchunk - 1);
+            unsigned(&xraw_p)[kPos + 3] = xraw[odd];
             float xr[2][kPos + 3];
 #pragma unroll
             for (int q = 0; q < kPos + 3; q++) {
-                xr[0][q] = __uint_as_float(xraw[q] << 16);
-                xr[1][q] = __uint_as_float(xraw[q] & 0xffff0000u);
+                xr[0][q] = __uint_as_float(xraw_p[q] << 16);
+                xr[1][q] = __uint_as_float(xraw_p[q] & 0xffff0000u);
             }
             asm volatile("" ::: "memory");
-            issue_x(cn, hn);
+            issue_x(cn, hd, xraw_p);
             if (edge_chunk(c)) {
 #pragma unroll
                 for (int q = 0; q < kPos + 3; q++) {
@@ -212,29 +213,32 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
 #pragma unroll
             for (int i = 0; i < kCopy; i++) dst[i * 256] = ctile[i];
         };
-        using Head0 = std::integral_constant<int, 0>;
-        using Head1 = std::integral_constant<int, HEADS - 1>;
+        using Even = std::integral_constant<int, 0>;
+        using Odd = std::integral_constant<int, 1>;
         if constexpr (HEADS == 2) issue_c(0);
-        issue_x(0, 0);
+        issue_x(0, 0, xraw[0]);
+        issue_x(min(1 / HEADS, nchunk - 1), HEADS - 1, xraw[1]);
         lds_barrier();   // the tables of the first two periods
         if constexpr (HEADS == 2) {
             put_c(0);
             asm volatile("" ::: "memory");
             issue_c(1);
         }
-        finish(0, Head0{});
+        finish(0, Even{});
         lds_barrier();
-        for (int c = 0; c < nchunk; c++) {
+        for (int p = 0; p < periods; p += 2) {
             if constexpr (HEADS == 2) {
+                const int c = p / 2;
                 if (c + 1 < nchunk) {   // (the slot's last readers were in the period before this one)
                     put_c(c + 1);
                     asm volatile("" ::: "memory");
                     issue_c(min(c + 2, nchunk - 1));
                 }
-                finish(c, Head1{});
-                lds_barrier();
             }
-            if (c + 1 < nchunk) finish(c + 1, Head0{});
+            if (p + 1 < periods) finish(p + 1, Odd{});
+            lds_barrier();
+            if (HEADS == 1 && p + 1 >= periods) break;
+            if (p + 2 < periods) finish(p + 2, Even{});
             lds_barrier();
         }
         return;
