@@ -637,7 +637,6 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                 sa.out_ch_off = separate ? s * d->d_inner : 0;
                 sa.dt_softplus = d->dt_softplus; sa.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD;
                 sa.wide = wide;
-                sa.pairs = pairs_readable(in->z) && pairs_readable(*out);
                 return sa;
             };
             if (plan.ssd_parts > 1) {

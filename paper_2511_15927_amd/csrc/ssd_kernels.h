@@ -31,6 +31,9 @@ typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
 
+// A channel pair at any 2-byte aligned place (global accesses need no more than that here).
+typedef unsigned __attribute__((aligned(2))) bf16_pair;
+
 constexpr int kQ = 64;     // chunk length
 constexpr int kPadK = 8;   // bf16 elements of row padding in LDS tiles (keeps 16-byte alignment, spreads banks)
 constexpr int kScoreOp = 3 * 2 * 64 * 8;   // floats of one chunk's score tile: 3 lower-triangular 32x32 blocks
@@ -247,7 +250,6 @@ struct SsdArgs {
     int L, Dn, H, HG, G, K, tail_ch, nchunk;
     int dir, mode, out_ch_off, dt_softplus, d_per_head;
     int wide;             // run on ssd_wide_kernel (ssd_wide.h): both directions of a call agree, the parked result is bf16
-    int pairs;            // wide: z and out can be accessed as aligned channel pairs
     // Time parts (calls with too few (batch, head) items to fill the chip): the chunks are dealt to `parts` workgroups
     // per item, part_chunks each, in scan order.  A part is part_subs sub-parts of sub_chunks chunks;
     // ssd_state_kernel leaves every sub-part's end state from a zero start and the product of its chunk decays (all

@@ -20,8 +20,8 @@
 //
 // Layouts.  The y waves multiply with the 16x16x32 MFMA (operand A lane l: row l%16, eight contraction slots of group l/16;
 // accumulator register r: row 4*(l/16) + r, column l%16): two row tiles by two column tiles, where column tile ct holds
-// channels 2*(l%16) + ct, so that a lane owns adjacent channels and moves 4-byte pairs of z, of the parked result and of the
-// output.  The state update uses the 32x32x16 MFMA with the same channel order, column j = channel 2*(j%16) + j/16.
+// channels 2*(l%16) + ct, so that a lane owns adjacent channels and moves 4-byte pairs (of any alignment) of z, of the parked
+// result and of the output.  The state update uses the 32x32x16 MFMA with the same channel order, column j = channel 2*(j%16) + j/16.
 // Contraction over positions: slot 4t + e of group g is position 16t + 4g + e of a 32-position block, which makes a
 // lane's own output rows its slots of the xc operand (the skip term reads no LDS).  Contraction over states: slot 4u + e of group
 // g is state 16*(g%2) + 8u + 4*(g/2) + e of a 32-state block, the order in which the state's accumulators publish it.
@@ -462,8 +462,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
     T* const phead = (T*)a.partial + (size_t)b * a.L * a.Dn + my_ch0;   // the parked result is bf16
     T* const ohead = (T*)a.out + (size_t)b * a.out_sb + a.out_ch_off + my_ch0;
     auto chunk_low_token = [&](int c) { return (long long)(fwd ? c * kQ : last - (c * kQ + kQ - 1)); };
-    // (channel pairs of z and out are 4-byte pieces where the host found them aligned)
-    auto inside = [&](int c) { return c * kQ + kQ - 1 <= last && a.pairs; };
+    auto inside = [&](int c) { return c * kQ + kQ - 1 <= last; };
     auto token_at = [&](int c, int k) { return (long long)token_of(min(c * kQ + i0 + 16 * (k / 4) + k % 4, last)); };
 
     unsigned zraw[8], praw[8];   // register k: row 16 (k / 4) + k % 4 of the lane, a channel pair
@@ -477,7 +476,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
 #pragma unroll
             for (int k = 0; k < 8; k++) {
                 const T* zp = zhead + token_at(c, k) * a.z.st + po;
-                zraw[k] = (unsigned)zp[0] | ((unsigned)zp[1] << 16);
+                zraw[k] = *reinterpret_cast<const bf16_pair*>(zp);
             }
         }
     };
@@ -599,8 +598,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
                     if constexpr (parks) *reinterpret_cast<unsigned*>(phead + t * a.Dn + po) = res[k];
                     else {
                         T* const o = ohead + t * a.out_st + po;
-                        o[0] = (T)res[k];
-                        o[1] = (T)(res[k] >> 16);
+                        *reinterpret_cast<bf16_pair*>(o) = res[k];
                     }
                 }
             }
