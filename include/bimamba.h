@@ -188,6 +188,30 @@ int bimamba_block_fwd_static(const bimamba_desc* desc, const bimamba_params* pf,
                              const float* h_in, const void* tail_in, float* h_out, void* tail_out,
                              const bimamba_tensor* out, void* hip_stream);
 
+/* One layer of a stack: its parameters, its cached state fp32 [batch, d_inner, d_state] (NULL = zero, not committed) and its
+ * conv tail, io_dtype [batch, d_conv-1, d_inner] (NULL = zeros, not committed). */
+typedef struct bimamba_stack_layer {
+    bimamba_params f, b;
+    float* h;
+    void* tail;
+} bimamba_stack_layer;
+
+/*
+ * All denoising steps of a block through a stack of layers that feed each other, in one launch: for every step, layer 0 reads the
+ * step's x, layer l + 1 reads layer l's output, all of them the step's z, dt, B and C; every call is bimamba_block_fwd's with
+ * COMBINE_ADD, starts from its layer's cached state and tail, and the last step commits both in place.
+ *   table       host array of n_layers bimamba_stack_layer, then n_steps bimamba_inputs, then n_steps * n_layers pointers: where
+ *               layer l of step s (place s * n_layers + l) leaves its output, io_dtype [batch, seqlen, d_inner] contiguous, or
+ *               NULL (not wanted).
+ *   table_dev   a copy of it in device memory, 8-byte aligned; it stays until the work has run.
+ * Outputs must not overlap any step's inputs.  Only for descriptors bimamba_block_stack_form answers 1 to: few enough chains that
+ * a workgroup takes a few channels through the whole stack, since channels are mixed nowhere.  Nothing is allocated, no scratch is
+ * used.
+ */
+int bimamba_block_stack(const bimamba_desc* desc, int n_layers, int n_steps, const void* table, const void* table_dev,
+                        void* hip_stream);
+int bimamba_block_stack_form(const bimamba_desc* desc);
+
 /* Gradients with respect to the activations one direction read.  dx, dz [batch, L, d_inner] and ddt [batch, L, n_heads]
  * are views in io_dtype like the inputs (written, one rounding each); dB, dC are contiguous fp32
  * [batch, L, n_groups, d_state] device arrays (sums over the channels of a group, formed in fp32 in a fixed order;

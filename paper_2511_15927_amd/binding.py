@@ -21,7 +21,7 @@ STATUS = {0: "BIMAMBA_OK", -1: "BIMAMBA_ERR_NULL_POINTER", -2: "BIMAMBA_ERR_BAD_
           -7: "BIMAMBA_ERR_SCRATCH_EXCEEDED", -8: "BIMAMBA_ERR_ALIAS"}
 STATIC_SCRATCH_BYTES = 64 << 20
 
-EXPORTS = ("bimamba_fwd", "bimamba_block_fwd", "bimamba_block_fwd_static", "bimamba_bwd", "bimamba_workspace_bytes",
+EXPORTS = ("bimamba_fwd", "bimamba_block_fwd", "bimamba_block_fwd_static", "bimamba_block_stack", "bimamba_block_stack_form", "bimamba_bwd", "bimamba_workspace_bytes",
            "bimamba_bwd_workspace_bytes", "bimamba_time_chunks", "bimamba_profile_next_call", "bimamba_status_string",
            "bimamba_version")
 
@@ -42,6 +42,10 @@ class Tensor(C.Structure):
 
 class Inputs(C.Structure):
     _fields_ = [(n, Tensor) for n in ("x", "z", "dt", "B", "C")]
+
+
+class StackLayer(C.Structure):
+    _fields_ = [("f", Params), ("b", Params), ("h", C.c_void_p), ("tail", C.c_void_p)]
 
 
 class InputGrads(C.Structure):
@@ -81,6 +85,10 @@ def lib():
         L.bimamba_block_fwd_static.argtypes = [C.POINTER(Desc), C.POINTER(Params), C.POINTER(Params), C.POINTER(Inputs),
                                                C.POINTER(Inputs), C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p,
                                                C.POINTER(Tensor), C.c_void_p]
+        L.bimamba_block_stack.restype = C.c_int
+        L.bimamba_block_stack.argtypes = [C.POINTER(Desc), C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p]
+        L.bimamba_block_stack_form.restype = C.c_int
+        L.bimamba_block_stack_form.argtypes = [C.POINTER(Desc)]
         L.bimamba_bwd.restype = C.c_int
         L.bimamba_bwd.argtypes = [C.POINTER(Desc), C.POINTER(Params), C.POINTER(Params), C.POINTER(Inputs),
                                   C.POINTER(Inputs), C.POINTER(Tensor), C.POINTER(InputGrads), C.POINTER(InputGrads),
@@ -230,6 +238,26 @@ def bimamba_block_fwd_static(desc, pf, pb, in_f, in_b, h_in, tail_in, h_out, tai
                                         _ptr(tail_out), C.byref(out), _stream_ptr(stream))
     if check and rc != 0:
         raise BimambaError(rc, "bimamba_block_fwd_static")
+    return rc
+
+
+def bimamba_block_stack_form(desc):
+    return int(lib().bimamba_block_stack_form(C.byref(desc)))
+
+
+def make_stack_table(layers, steps, outs):
+    """layers: StackLayer structs; steps: Inputs structs; outs: one output tensor or None per (step, layer), layers fastest.
+    Returns the table's bytes."""
+    assert len(outs) == len(layers) * len(steps)
+    return b"".join(bytes(s) for s in list(layers) + list(steps)) + bytes((C.c_void_p * len(outs))(*[0 if o is None else o.data_ptr() for o in outs]))
+
+
+def bimamba_block_stack(desc, n_layers, n_steps, table, table_dev, stream=None, check=True):
+    """Enqueue all steps of a block through the stack.  table: make_stack_table's bytes; table_dev: a uint8 device tensor
+    holding the same."""
+    rc = lib().bimamba_block_stack(C.byref(desc), n_layers, n_steps, table, C.c_void_p(table_dev.data_ptr()), _stream_ptr(stream))
+    if check and rc != 0:
+        raise BimambaError(rc, "bimamba_block_stack")
     return rc
 
 

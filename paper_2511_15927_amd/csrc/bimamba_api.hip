@@ -4,6 +4,7 @@
 #include "launch.h"
 #include "bwd_kernels.h"
 #include "row_kernels.h"
+#include "stack_kernels.h"
 #include "ssd_kernels.h"
 
 #include <hip/hip_runtime.h>
@@ -732,6 +733,62 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
     return now == hipSuccess || now == pending ? BIMAMBA_OK : BIMAMBA_ERR_HIP;
 }
 
+// Whether a descriptor can take a stack of layers in one launch, and in which shape.
+bool stack_call(const bimamba_desc* d, RowForm* row)
+{
+    return !use_ssd(d) && !d->conv_bc && d->time_chunks == 0 && d->state_split == 0 && d->combine == BIMAMBA_COMBINE_ADD &&
+           d->batch > 0 && stack_form(d->batch, d->seqlen, d->d_inner, d->d_state, row);
+}
+
+int run_stack(const bimamba_desc* d, int n_layers, int n_steps, const void* table, const void* table_dev, void* hip_stream)
+{
+    int rc = check_desc(d);
+    if (rc) return rc;
+    if (n_layers < 0 || n_steps < 0) return BIMAMBA_ERR_BAD_SHAPE;
+    RowForm row;
+    if (!stack_call(d, &row)) return BIMAMBA_ERR_UNSUPPORTED;
+    if (n_layers == 0 || n_steps == 0) return BIMAMBA_OK;
+    if (!table || !table_dev) return BIMAMBA_ERR_NULL_POINTER;
+    if (!is_aligned(table, 8) || !is_aligned(table_dev, 8)) return BIMAMBA_ERR_MISALIGNED;
+    const size_t elem = d->io_dtype == BIMAMBA_BF16 ? 2 : 4;
+    const auto* layers = static_cast<const bimamba_stack_layer*>(table);
+    const auto* steps = reinterpret_cast<const bimamba_inputs*>(layers + n_layers);
+    const auto* outs = reinterpret_cast<void* const*>(steps + n_steps);
+    for (int l = 0; l < n_layers; l++) {
+        if ((rc = check_params(&layers[l].f)) || (rc = check_params(&layers[l].b))) return rc;
+        if (!is_aligned(layers[l].h, 4) || !is_aligned(layers[l].tail, elem)) return BIMAMBA_ERR_MISALIGNED;
+    }
+    for (int s = 0; s < n_steps; s++)
+        if ((rc = check_inputs(&steps[s], d, elem))) return rc;
+    const int gn = d->n_groups * d->d_state;
+    for (int i = 0; i < n_steps * n_layers; i++) {
+        if (!outs[i]) continue;
+        if (!is_aligned(outs[i], elem)) return BIMAMBA_ERR_MISALIGNED;
+        const bimamba_tensor o{outs[i], (int64_t)d->seqlen * d->d_inner, d->d_inner};
+        for (int s = 0; s < n_steps; s++) {
+            const bimamba_inputs& in = steps[s];
+            if (may_overlap(o, d->d_inner, in.x, d->d_inner, elem, d) || may_overlap(o, d->d_inner, in.z, d->d_inner, elem, d) ||
+                may_overlap(o, d->d_inner, in.dt, d->n_heads, elem, d) || may_overlap(o, d->d_inner, in.B, gn, elem, d) ||
+                may_overlap(o, d->d_inner, in.C, gn, elem, d))
+                return BIMAMBA_ERR_ALIAS;
+        }
+    }
+    const hipError_t pending = hipPeekAtLastError();
+    StackArgs sa{};
+    sa.layers = static_cast<const bimamba_stack_layer*>(table_dev);
+    sa.steps = reinterpret_cast<const bimamba_inputs*>(sa.layers + n_layers);
+    sa.outs = reinterpret_cast<void* const*>(sa.steps + n_steps);
+    sa.n_layers = n_layers; sa.n_steps = n_steps;
+    sa.L = d->seqlen; sa.Dn = d->d_inner; sa.P = d->d_inner / d->n_heads; sa.HG = d->n_heads / d->n_groups;
+    sa.G = d->n_groups; sa.N = d->d_state; sa.K = d->d_conv;
+    sa.dt_softplus = d->dt_softplus; sa.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD;
+    sa.a_scalar = d->a_kind == BIMAMBA_A_SCALAR_PER_HEAD;
+    sa.tw = row.tw; sa.tw_log2 = row.tw == 4 ? 2 : row.tw == 2 ? 1 : 0; sa.nseg = row.nseg; sa.seg_len = row.seg_len;
+    if (launch_stack(d->io_dtype == BIMAMBA_BF16, sa, d->batch, reinterpret_cast<hipStream_t>(hip_stream)) != hipSuccess) return BIMAMBA_ERR_HIP;
+    const hipError_t now = hipPeekAtLastError();
+    return now == hipSuccess || now == pending ? BIMAMBA_OK : BIMAMBA_ERR_HIP;
+}
+
 constexpr int kMaxScratchDevices = 64;
 std::atomic<void*> g_scratch_addr[kMaxScratchDevices];   // per device: each GPU holds its own copy of the array
 
@@ -945,6 +1002,17 @@ size_t bimamba_workspace_bytes(const bimamba_desc* desc, int block_variant)
     if (check_desc(desc)) return 0;
     // sized for the larger case (the two directions reading different activations)
     return make_plan(desc, false, block_variant != 0, SIZE_MAX).total;
+}
+
+int bimamba_block_stack(const bimamba_desc* desc, int n_layers, int n_steps, const void* table, const void* table_dev, void* hip_stream)
+{
+    return run_stack(desc, n_layers, n_steps, table, table_dev, hip_stream);
+}
+
+int bimamba_block_stack_form(const bimamba_desc* desc)
+{
+    RowForm row;
+    return check_desc(desc) == BIMAMBA_OK && stack_call(desc, &row);
 }
 
 int bimamba_time_chunks(const bimamba_desc* desc)

@@ -62,6 +62,9 @@ struct RowForm {
 };
 struct RowArgs;
 bool row_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f);
+bool stack_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f);      // the same for a stack of layers (stack_kernels.h)
+struct StackArgs;
+hipError_t launch_stack(int io_bf16, const StackArgs& a, int batch, hipStream_t st);
 hipError_t launch_row(int io_bf16, const RowArgs& a, int batch, hipStream_t st);   // (an error: nothing was launched)
 
 struct SsdPrepPair;

@@ -117,6 +117,37 @@ __device__ __forceinline__ float row_reduce_scatter(float (&p)[16], int n)
     return b0 ? q1 : q0;
 }
 
+// The recurrence of a wave's four chains over `groups` groups of sixteen tokens, from state h: (u, Delta, D xc) of the tokens from
+// `ud` (STRIDE floats a group), B|C rows of the call from `bc` (in token order: a group's are sixteen constant offsets from its
+// lowest-address one).  sink(j, y) takes the output of scan position j + n.
+template <bool OUTPUT, int DIR, int STRIDE, typename Sink>
+__device__ __forceinline__ void row_walk(float& h, float a2, const float* ud, const float2* bc, int groups, int j0, int last, int lane, int n,
+                                         Sink&& sink)
+{
+    for (int g = 0; g < groups; g++) {
+        const float u = ud[g * STRIDE + lane], delta = ud[g * STRIDE + 64 + lane];
+        float p[16];
+        const int j = j0 + g * kRowTokens;
+        const float2* const rows = bc + (DIR > 0 ? j : last - j - (kRowTokens - 1)) * 16;
+        auto token = [&](auto ic) {
+            constexpr int i = decltype(ic)::value;
+            const float2 row = rows[(DIR > 0 ? i : kRowTokens - 1 - i) * 16];
+            const float an = fast_exp2(row_lane<i>(delta) * a2);
+            h = fmaf(an, h, row_lane<i>(u) * row.x);
+            if (OUTPUT) p[i] = row.y * h;
+        };
+        token(std::integral_constant<int, 0>{}); token(std::integral_constant<int, 1>{});
+        token(std::integral_constant<int, 2>{}); token(std::integral_constant<int, 3>{});
+        token(std::integral_constant<int, 4>{}); token(std::integral_constant<int, 5>{});
+        token(std::integral_constant<int, 6>{}); token(std::integral_constant<int, 7>{});
+        token(std::integral_constant<int, 8>{}); token(std::integral_constant<int, 9>{});
+        token(std::integral_constant<int, 10>{}); token(std::integral_constant<int, 11>{});
+        token(std::integral_constant<int, 12>{}); token(std::integral_constant<int, 13>{});
+        token(std::integral_constant<int, 14>{}); token(std::integral_constant<int, 15>{});
+        if constexpr (OUTPUT) sink(j, row_reduce_scatter(p, n) + ud[g * STRIDE + 128 + lane]);
+    }
+}
+
 // grid (ceil(Dn / (4 tw)), 1, batch), block 128 * nseg * tw, dynamic LDS RowLds::total floats.
 template <typename IO>
 __global__ __launch_bounds__(64 * kRowMaxWaves, 1) void row_kernel(const RowArgs a)
@@ -232,36 +263,14 @@ __global__ __launch_bounds__(64 * kRowMaxWaves, 1) void row_kernel(const RowArgs
     asm volatile("" : "+v"(h));                          // (h_in has arrived before any wave can reach its store to an aliased h_out)
     __syncthreads();                                     // B|C rows
 
-    // The recurrence over the segment.  The rows of a group are sixteen constant offsets from its lowest-address one.
+    // the recurrence over the segment
     const float2* const bc = reinterpret_cast<const float2*>(row_lds + lds.bc) + ((a.same_bc ? 0 : s) * set_rows + kRowTokens) * 16 + n;
     auto walk = [&](auto with_output, auto direction) {
         constexpr bool kOutput = decltype(with_output)::value;
         constexpr int kDir = decltype(direction)::value;
-        for (int g = 0; g < groups; g++) {
-            const float u = ud[g * 192 + lane], delta = ud[g * 192 + 64 + lane];
-            float p[16];
-            const int j = j0 + g * kRowTokens;
-            const float2* const rows = bc + (kDir > 0 ? j : last - j - (kRowTokens - 1)) * 16;
-            auto token = [&](auto ic) {
-                constexpr int i = decltype(ic)::value;
-                const float2 row = rows[(kDir > 0 ? i : kRowTokens - 1 - i) * 16];
-                const float an = fast_exp2(row_lane<i>(delta) * a2);
-                h = fmaf(an, h, row_lane<i>(u) * row.x);
-                if (kOutput) p[i] = row.y * h;
-            };
-            token(std::integral_constant<int, 0>{}); token(std::integral_constant<int, 1>{});
-            token(std::integral_constant<int, 2>{}); token(std::integral_constant<int, 3>{});
-            token(std::integral_constant<int, 4>{}); token(std::integral_constant<int, 5>{});
-            token(std::integral_constant<int, 6>{}); token(std::integral_constant<int, 7>{});
-            token(std::integral_constant<int, 8>{}); token(std::integral_constant<int, 9>{});
-            token(std::integral_constant<int, 10>{}); token(std::integral_constant<int, 11>{});
-            token(std::integral_constant<int, 12>{}); token(std::integral_constant<int, 13>{});
-            token(std::integral_constant<int, 14>{}); token(std::integral_constant<int, 15>{});
-            if constexpr (kOutput) {
-                const float y = row_reduce_scatter(p, n) + ud[g * 192 + 128 + lane];
-                if (j + n < j1) row_lds[lds.y + (s * a.L + token_of(j + n)) * width + tile * 4 + (lane >> 4)] = y;
-            }
-        }
+        row_walk<kOutput, kDir, 192>(h, a2, ud, bc, groups, j0, last, lane, n, [&](int j, float y) {
+            if (j + n < j1) row_lds[lds.y + (s * a.L + token_of(j + n)) * width + tile * 4 + (lane >> 4)] = y;
+        });
     };
     using Up = std::integral_constant<int, 1>;
     using Down = std::integral_constant<int, -1>;

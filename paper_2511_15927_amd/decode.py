@@ -10,11 +10,10 @@ layer l+1's x; z, dt, B, C of a step are shared by the layers; parameters are pe
 
 The n_steps x n_layers calls of a block are captured ONCE into a HIP graph (torch.cuda.CUDAGraph: stream capture of
 the library's launches, which contain no memset nodes) and replayed per block; the caller refreshes the static step
-inputs between replays.  Why there is no kernel that keeps h on chip across the steps of a block: step s + 1 of a layer
-consumes what the whole network made of step s (in the paper's model through the projections and MLPs, here through
-the 23 other layers), so between two steps of one layer every other layer has to run; the state of all layers
-(n_layers x batch x d_inner x d_state fp32, 100 MB at batch 16) exceeds what registers and LDS hold, so it lives in
-HBM/L2 between calls and a call reads it once (4 MB per layer call against 8 MB of activations).
+inputs between replays.  Nothing on this path mixes channels, so with few enough chains the whole block is one launch in which a
+workgroup takes a few channels through every layer of every step (bimamba_block_stack; at batch 1, 24 layers x 8 steps of 32
+tokens 1.44 -> 0.55 ms).  Otherwise the state of all layers (n_layers x batch x d_inner x d_state fp32, 100 MB at batch 16)
+lives in HBM/L2 between calls and a call reads it once (4 MB per layer call against 8 MB of activations).
 """
 import torch
 
@@ -49,6 +48,9 @@ class BlockDecodeLoop:
         self.static_scratch = static_scratch
         self.ws = None if static_scratch else bd.alloc_workspace(self.desc, 1, device=device)
         self._graph = None
+        # few enough chains: the whole block is one launch (bimamba_block_stack), whose table of pointers sits on the device
+        self._one_launch = self.n_layers > 0 and self.n_steps > 0 and bd.bimamba_block_stack_form(self.desc) == 1
+        self._table, self._table_dev = None, None
 
     def layer_output(self, step, layer):
         assert self.keep
@@ -72,8 +74,28 @@ class BlockDecodeLoop:
         else:
             bd.bimamba_block_fwd(*a, self.ws, stream=stream)
 
+    def _stack_table(self):
+        """The pointers bimamba_block_stack works from, on the host and on the device; uploaded anew (into memory of its own: a
+        captured block keeps its copy) when one of them has changed."""
+        has_tail = self.tail[0].shape[1] > 0
+        layers = [bd.StackLayer(pf, pb, h.data_ptr(), t.data_ptr() if has_tail else None)
+                  for (pf, pb), h, t in zip(self._params, self.h, self.tail)]
+        steps = [bd.make_inputs(s) for s in self.step_inputs]
+        outs = [self.out[s] if l == self.n_layers - 1 else self._act[s * self.n_layers + l] if self.keep else None
+                for s in range(self.n_steps) for l in range(self.n_layers)]
+        table = bd.make_stack_table(layers, steps, outs)
+        if table != self._table:
+            self._table_dev = torch.frombuffer(bytearray(table), dtype=torch.uint8).to(self.out[0].device)
+            torch.cuda.synchronize()
+            self._table = table
+        return self._table, self._table_dev
+
     def run_block_eager(self, stream=None):
-        """All steps of one block, launch by launch; the last step commits every layer's state and conv tail in place."""
+        """All steps of one block, call by call (in one launch where the library can); the last step commits every layer's
+        state and conv tail in place."""
+        if self._one_launch:
+            bd.bimamba_block_stack(self.desc, self.n_layers, self.n_steps, *self._stack_table(), stream=stream)
+            return
         for step in range(self.n_steps):
             commit = step == self.n_steps - 1
             x = self.step_inputs[step]["x"]
@@ -99,6 +121,7 @@ class BlockDecodeLoop:
         self._graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(self._graph):
             self.run_block_eager()
+        self._graph_table = self._table_dev   # (the captured launch reads it)
         # the capture itself does not run the kernels: the cache is untouched
         return self
 

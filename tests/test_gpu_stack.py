@@ -1,0 +1,73 @@
+"""GPU parity of a stack of layers in one launch (bimamba_block_stack through BlockDecodeLoop): every layer's output of every
+step and the committed caches against the fp64 oracle fed that layer's own input, at block lengths around the groups of 16
+tokens and the outputs a thread holds, for every conv width, state counts below a row's width, ragged channel tiles."""
+import numpy as np
+import pytest
+import torch
+
+from helpers import assert_close, rel_l2, to_np
+from paper_2511_15927_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("batch,L,Dn,N,K,io,layers,kw", [
+    (1, 1, 72, 16, 4, "f32", 2, {}),                               # a block shorter than the conv tail
+    (2, 2, 5, 4, 3, "bf16", 3, dict(dt_softplus=1)),
+    (2, 16, 130, 8, 1, "f32", 1, {}),                              # no tail; one layer
+    (1, 17, 257, 16, 2, "bf16", 2, dict(dt_softplus=1)),
+    (3, 33, 1366, 16, 4, "f32", 2, {}),                            # several tiles of four channels in a workgroup, a ragged last one
+    (1, 32, 4098, 16, 4, "bf16", 3, {}),
+    (2, 64, 2045, 16, 4, "bf16", 2, dict(dt_softplus=1)),          # two outputs a thread or two time segments
+    (1, 65, 515, 8, 3, "f32", 2, {}),
+    (1, 100, 4096, 16, 4, "bf16", 2, {}),                          # four outputs a thread
+    (1, 128, 256, 16, 4, "f32", 2, dict(n_heads=32, n_groups=2, d_kind=1)),
+    (1, 200, 64, 16, 4, "f32", 2, dict(n_heads=4, a_kind=1)),
+])
+def test_stack_matches_oracle_layer_by_layer(oracle, batch, L, Dn, N, K, io, layers, kw):
+    from paper_2511_15927_amd import binding as bd
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    cfg = synth.mixer_cfg(batch, L, Dn, d_state=N, d_conv=K, io=io, **kw)
+    assert bd.bimamba_block_stack_form(bd.make_desc(cfg)) == 1
+    steps = 2
+    params = [(synth.make_params(cfg, 70 + l, 0), synth.make_params(cfg, 70 + l, 1)) for l in range(layers)]
+    loop = BlockDecodeLoop(cfg, params, steps, keep_layer_outputs=True)
+    g = torch.Generator().manual_seed(L)
+    h_ref, tail_ref = [], []
+    for l in range(layers):
+        h0 = (0.2 * torch.randn(batch, Dn, N, generator=g)).float()
+        t0 = synth.round_io(torch.randn(batch, K - 1, Dn, generator=g), io)
+        loop.h[l].copy_(h0)
+        loop.tail[l].copy_(t0)
+        h_ref.append(h0.numpy().astype(np.float64))
+        tail_ref.append(t0.numpy().astype(np.float64))
+    loop.capture()
+    tol = 1e-5 if io == "f32" else 2e-2
+    for block in range(2):      # the second one starts from what the first one committed
+        inputs = [synth.make_inputs(cfg, 80 + 10 * block + s) for s in range(steps)]
+        for s in range(steps):
+            loop.set_step_inputs(s, inputs[s])
+        loop.run_block()
+        torch.cuda.synchronize()
+        for s in range(steps):
+            for l in range(layers):
+                x = inputs[s]["x"].numpy() if l == 0 else loop.layer_output(s, l - 1).float().cpu().numpy()
+                ref, h_new, t_new = oracle.bimamba_block_fwd(cfg, to_np(params[l][0]), to_np(params[l][1]), dict(to_np(inputs[s]), x=x),
+                                                             h_in=h_ref[l], tail_in=tail_ref[l] if K > 1 else None)
+                assert_close(loop.layer_output(s, l).float().cpu().numpy(), ref, tol, (block, s, l))
+                if s == steps - 1:
+                    h_ref[l] = h_new
+                    if K > 1:
+                        tail_ref[l] = t_new
+        for l in range(layers):
+            assert rel_l2(loop.h[l].cpu().numpy(), h_ref[l]) < 1e-5, (block, l)
+            if K > 1:
+                assert np.array_equal(loop.tail[l].float().cpu().numpy().astype(np.float64), tail_ref[l]), (block, l)
+
+
+def test_stack_refuses_what_it_cannot_take(oracle):
+    from paper_2511_15927_amd import binding as bd
+    small = synth.mixer_cfg(1, 32, 64)
+    for over in (dict(time_chunks=1), dict(state_split=2), dict(combine=1), dict(d_state=32), dict(seqlen=257)):
+        assert bd.bimamba_block_stack_form(bd.make_desc(dict(small, **over))) == 0, over
+    assert bd.bimamba_block_stack_form(bd.make_desc(synth.m2_cfg(1, 32, 64, headdim=32, d_state=64))) == 0
