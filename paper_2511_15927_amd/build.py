@@ -35,7 +35,7 @@ def newest_dep(src, newest_all):
     """Modification time an object must beat: its source and the headers that source includes."""
     text = open(src).read()
     deps = [src, os.path.join(ROOT, "include", "bimamba.h")]
-    for h in ("kernels.h", "launch.h", "ssd_kernels.h", "ssd_wide.h", "bwd_kernels.h", "row_kernels.h", "stack_kernels.h"):
+    for h in ("kernels.h", "launch.h", "ssd_kernels.h", "ssd_wide.h", "ssd_block.h", "bwd_kernels.h", "row_kernels.h", "stack_kernels.h"):
         if h in text or (h == "kernels.h"):
             deps.append(os.path.join(CSRC, h))
     return max(os.path.getmtime(p) for p in deps)
@@ -50,6 +50,7 @@ def build(force: bool = True, jobs: int = 8):
         units.append((os.path.join(CSRC, "scan_inst.hip"), os.path.join(OBJ, "scan_n%d_s%d.o" % (n, s)),
                       ["-DBM_N=%d" % n, "-DBM_S=%d" % s]))
     units.append((os.path.join(CSRC, "ssd_inst.hip"), os.path.join(OBJ, "ssd_inst.o"), []))
+    units.append((os.path.join(CSRC, "ssd_block_inst.hip"), os.path.join(OBJ, "ssd_block_inst.o"), []))
     for n, p in SSD_WIDE:
         units.append((os.path.join(CSRC, "ssd_wide_inst.hip"), os.path.join(OBJ, "ssd_wide_n%d_p%d.o" % (n, p)),
                       ["-DBM_N=%d" % n, "-DBM_P=%d" % p]))

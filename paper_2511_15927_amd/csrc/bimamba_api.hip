@@ -5,6 +5,7 @@
 #include "bwd_kernels.h"
 #include "row_kernels.h"
 #include "stack_kernels.h"
+#include "ssd_block.h"
 #include "ssd_kernels.h"
 
 #include <hip/hip_runtime.h>
@@ -584,7 +585,35 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
             if (d->io_dtype == BIMAMBA_BF16) hipLaunchKernelGGL(prep_bc_kernel<IoBF16>, grid, dim3(256), 0, st, prep);
             else hipLaunchKernelGGL(prep_bc_kernel<IoF32>, grid, dim3(256), 0, st, prep);
         }
-        if (plan.ssd) {
+        if (plan.ssd && plan.ssd_chunks == 1) {
+            // 2''. one chunk: its operands, then both directions of every (batch, head) item at once
+            SsdBlockArgs ba{};
+            for (int s = 0; s < 2; s++) {
+                const bimamba_inputs* in = s == 0 ? in_f : in_b;
+                const bimamba_params* p = s == 0 ? pf : pb;
+                SsdBlockDir& bd = ba.dir[s];
+                bd.x = targ(in->x); bd.z = targ(in->z); bd.dt = targ(in->dt); bd.B = targ(in->B); bd.C = targ(in->C);
+                bd.conv_w = p->conv_w; bd.conv_b = p->conv_b; bd.A = p->A; bd.D = p->D; bd.dt_bias = p->dt_bias;
+                ba.score[s] = reinterpret_cast<float*>(ws + plan.off_score[s]);
+            }
+            ba.c_op = reinterpret_cast<__bf16*>(ws + plan.off_crows[0]);
+            ba.b_op = reinterpret_cast<__bf16*>(ws + plan.off_bt[0]);
+            ba.out = out->ptr; ba.out_sb = out->stride_batch; ba.out_st = out->stride_token;
+            if (block_variant) {
+                ba.h_in = h_in; ba.h_out = h_out;
+                ba.tail_in = tail_in; ba.tail_out = d->d_conv > 1 ? tail_out : nullptr;
+                tail_out = nullptr;
+            }
+            ba.batch = d->batch; ba.L = d->seqlen; ba.Dn = d->d_inner; ba.H = d->n_heads; ba.P = d->d_inner / d->n_heads;
+            ba.HG = d->n_heads / d->n_groups; ba.G = d->n_groups; ba.K = d->d_conv; ba.tail_ch = tail_ch;
+            ba.dt_softplus = d->dt_softplus; ba.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD; ba.conv_bc = d->conv_bc;
+            ba.separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
+            ba.shared = same_tensor(in_f->x, in_b->x) && same_tensor(in_f->z, in_b->z);
+            launch_ssd_block_prep(d->d_state, ba, st);
+            if (probe_start) (void)hipEventRecord(probe_start, st);
+            launch_ssd_block(d->d_state, ba, st);
+            if (probe_stop) (void)hipEventRecord(probe_stop, st);
+        } else if (plan.ssd) {
             // 2'. chunked matrix-core path: per-direction operand tiles, then the reverse scan parks its result and the
             // forward scan adds, gates and stores (or each writes its own half)
             const bool separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
@@ -655,11 +684,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                 ca.parts = plan.ssd_subs;
                 launch_ssd_carry(d->d_state, ca, st);
             }
-            if (plan.ssd_chunks == 1) {
-                SsdStatePair sp;
-                for (int s = 0; s < 2; s++) sp.dir[s] = scan_args(s);
-                launch_ssd_duo(d->d_state, d->d_inner / d->n_heads, sp, d->batch, st);
-            } else {
+            {
                 const int head_width = d->d_inner / d->n_heads;
                 SsdStatePair sp;
                 sp.dir[1] = scan_args(1);

@@ -80,7 +80,9 @@ void launch_ssd_wide_n128_p32(const SsdStatePair& sp, int dirs, int batch, hipSt
 void launch_ssd_wide_n64_p64(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
 void launch_ssd_wide_n64_p32(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
 void launch_ssd_carry(int d_state, const SsdCarryArgs& ca, hipStream_t st);
-void launch_ssd_duo(int d_state, int headdim, const SsdStatePair& sp, int batch, hipStream_t st);
+struct SsdBlockArgs;
+void launch_ssd_block_prep(int d_state, const SsdBlockArgs& a, hipStream_t st);   // (calls of one chunk: ssd_block.h)
+void launch_ssd_block(int d_state, const SsdBlockArgs& a, hipStream_t st);
 void launch_ssd_state(int d_state, int headdim, const SsdStatePair& sp, int subs, int batch, hipStream_t st);
 
 struct BwdArgs;

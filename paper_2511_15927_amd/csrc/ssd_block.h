@@ -1,0 +1,565 @@
+// Mamba-2 calls of up to 64 tokens (block-diffusion steps), both directions, without a barrier.
+//
+// Such a call is 1500 vector instructions and 46 KB of memory traffic an item (batch, head) at 32 tokens of 64 channels: what it
+// costs is the length of its chains of loads and phases.  Here a wave owns 16 channels over the whole block and does all phases
+// for them: it requests everything it reads at its start, scans Delta (both directions in one pass over the two halves of the wave at
+// 32 tokens), forms the masked, decayed score operands, the conv + SiLU of its channels right in operand layout and the bf16 operand
+// of its entry state, and multiplies.  Four waves share x, z and the output, which cross global memory in whole rows of 64 channels
+// through LDS, and the score operands of a head, made by its waves in shares (with 2-byte accesses and operands of each wave's own
+// a call of 16 x 32 tokens, 64 heads x 64, 128 states took 26.2 us, most of it address and tag cycles; 18.8 now, the bytes alone
+// 9).  The score tiles and operands that all heads of a group share come from ssd_block_prep_kernel, one workgroup per (direction,
+// group, batch element).  (Before: a workgroup an item with producer and consumer waves, one direction after the other, 39.9.)
+//
+// Both directions work in token order: the reverse direction's operands hold j >= i.  MFMA 16x16x32: operand A lane l holds row
+// l%16, B column l%16, eight contraction slots of group g = l/16; accumulator register r of lane l is row 4g + r, column l%16.
+// Positions fill the slots of a 32-token block in order (slot e of group g is token 8g + e: a lane convolves a run of eight);
+// states as 4t + e of group g = state 16t + 4g + e, the accumulator's own order, so that the state loaded once (16-byte
+// pieces) is both operand and accumulator of the update.  The skip term's xc in accumulator layout is a product with the
+// identity, which is exact.
+#pragma once
+#include "ssd_kernels.h"
+
+namespace bm {
+
+struct SsdBlockDir {
+    TensorArg x, z, dt, B, C;
+    const float *conv_w, *conv_b, *A, *D, *dt_bias;
+};
+
+struct SsdBlockArgs {
+    SsdBlockDir dir[2];   // forward, reverse
+    // operands shared by the heads of a group, per (batch, group): C of the forward direction [32 states][16 rows][lane][8], its
+    // B^T [16 states][32 tokens][lane][8], both directions' scores [32 x 32 block][16 rows][lane][8]
+    __bf16 *c_op, *b_op;
+    float* score[2];
+    void* out;
+    long long out_sb, out_st;
+    const float* h_in;    // [batch][Dn][N] or null
+    float* h_out;         // or null; may alias h_in
+    const void* tail_in;  // bf16 [batch][K-1][tail_ch] or null
+    void* tail_out;       // or null; may alias tail_in: x's part is written by whoever reads it there, B's and C's by the preparation
+    int batch, L, Dn, H, P, HG, G, K, tail_ch;
+    int dt_softplus, d_per_head, conv_bc, separate;
+    int shared;           // both directions read the same x and the same z
+};
+
+// Eight channels of one token.
+typedef unsigned __attribute__((ext_vector_type(4), aligned(2))) Piece;
+
+// 32 x 32 score blocks of a call: the causal (forward) or anti-causal (reverse) ones of BLOCKS x BLOCKS.
+template <int BLOCKS>
+constexpr int ssd_block_scores() { return BLOCKS == 1 ? 1 : 3; }
+
+template <int N, int BLOCKS>
+constexpr size_t ssd_block_prep_lds() { return 2 * (size_t)(32 * BLOCKS) * (N + 1) * sizeof(float) + 12 * 64 * 4 * sizeof(float); }
+
+// grid (G, 2, batch), block 1024, dynamic LDS ssd_block_prep_lds<N, BLOCKS>().  B and C of one direction after conv + SiLU as fp32
+// in LDS, then the operands.  Scores are formed as in ssd_prep_kernel: operands split into a bf16 head and remainder, three products.
+template <int N, int BLOCKS>
+__global__ __launch_bounds__(1024) void ssd_block_prep_kernel(const SsdBlockArgs a)
+{
+    using T = unsigned short;
+    constexpr int kTok = 32 * BLOCKS;
+    extern __shared__ __attribute__((aligned(16))) unsigned char ssd_block_lds[];
+    float(*sB)[N + 1] = reinterpret_cast<float(*)[N + 1]>(ssd_block_lds);
+    float(*sC)[N + 1] = sB + kTok;
+    float* const sums = reinterpret_cast<float*>(sC + kTok);   // [12][64][4]
+    const int g = blockIdx.x, s = blockIdx.y, b = blockIdx.z, tid = threadIdx.x, last = a.L - 1;
+    const SsdBlockDir& d = a.dir[s];
+    {
+        constexpr int kCols = 2 * N, kParts = 1024 / kCols, kLen = kTok / kParts;
+        const int col = tid % kCols, part = tid / kCols;   // one column of B|C, tokens part*kLen ..
+        const int which = col / N, n = col % N;
+        const TensorArg& src = which ? d.C : d.B;
+        const T* base = (const T*)src.p + (size_t)b * src.sb + g * N + n;
+        const int row = a.Dn + which * a.G * N + g * N + n;   // this column's conv channel
+        const int t0 = part * kLen - (s == 0 ? 3 : 0);        // first token of the run and its halo (behind it in scan order)
+        T raw[kLen + 3];
+#pragma unroll
+        for (int q = 0; q < kLen + 3; q++) raw[q] = base[(long long)min(max(t0 + q, 0), last) * src.st];
+        float w4[4] = {0.0f, 0.0f, 0.0f, 0.0f}, bias = 0.0f;   // w4[3] on the current position
+        if (a.conv_bc) {
+#pragma unroll
+            for (int i = 0; i < 4; i++) w4[3 - i] = i < a.K ? d.conv_w[(size_t)row * a.K + (a.K - 1 - i)] : 0.0f;
+            bias = d.conv_b ? d.conv_b[row] : 0.0f;
+        }
+        float xr[kLen + 3];
+#pragma unroll
+        for (int q = 0; q < kLen + 3; q++) xr[q] = (t0 + q >= 0 && t0 + q <= last) ? IoBF16::cvt(raw[q]) : 0.0f;
+        if (s == 0 && part == 0 && a.tail_in && a.conv_bc && a.K > 1) {
+            T cached[3];
+#pragma unroll
+            for (int q = 0; q < 3; q++)   // 3 - q tokens before the block, from clamped rows (a tap beyond the conv width has a zero weight)
+                cached[q] = ((const T*)a.tail_in)[((size_t)b * (a.K - 1) + max(a.K - 1 - (3 - q), 0)) * a.tail_ch + row];
+#pragma unroll
+            for (int q = 0; q < 3; q++)
+                if (3 - q <= a.K - 1) xr[q] = IoBF16::cvt(cached[q]);
+        }
+        if (s == 0 && part == 0 && a.tail_out && a.conv_bc) {   // the last K - 1 raw tokens of (tail_in || block)
+            T last_raw[3];
+#pragma unroll
+            for (int q = 0; q < 3; q++) last_raw[q] = base[(long long)max(a.L - 3 + q, 0) * src.st];
+#pragma unroll
+            for (int q = 0; q < 3; q++) {
+                const int n_out = q - 3 + (a.K - 1), pos = a.L - 3 + q;   // row of the tail, token of the block (negative: of tail_in)
+                T v = last_raw[q];
+                if (pos < 0) {   // (xr[0 .. 2] hold the tokens before the block)
+                    v = 0;
+#pragma unroll
+                    for (int e = 0; e < 3; e++)
+                        if (pos + 3 == e) v = io_bits<IoBF16>(xr[e]);
+                }
+                if (n_out >= 0) ((T*)a.tail_out)[((size_t)b * (a.K - 1) + n_out) * a.tail_ch + row] = v;
+            }
+        }
+        float(*dst)[N + 1] = which ? sC : sB;
+#pragma unroll
+        for (int i = 0; i < kLen; i++) {
+            const int t = part * kLen + i;
+            float v = xr[s == 0 ? i + 3 : i];
+            if (a.conv_bc) {
+                float pre = bias;
+#pragma unroll
+                for (int k = 0; k < 4; k++) pre = fmaf(w4[k], xr[s == 0 ? i + k : i + 3 - k], pre);
+                v = silu(pre);
+            }
+            dst[t][n] = t > last ? 0.0f : v;
+        }
+    }
+    __syncthreads();
+    const size_t item = (size_t)b * a.G + g;
+    if (s == 0 && a.h_in) {
+        for (int idx = tid; idx < kTok * N / 8; idx += 1024) {
+            const int ln = idx % 64, f = idx / 64, i = (f % (2 * BLOCKS)) * 16 + ln % 16, n0 = (f / (2 * BLOCKS)) * 32 + 4 * (ln / 16);
+            bf16x8 v;
+#pragma unroll
+            for (int e = 0; e < 8; e++) v[e] = (__bf16)sC[i][n0 + 16 * (e / 4) + e % 4];
+            *reinterpret_cast<bf16x8*>(&a.c_op[(item * (kTok * N / 8) + idx) * 8]) = v;
+        }
+    }
+    if (s == 0 && a.h_out) {
+        for (int idx = tid; idx < kTok * N / 8; idx += 1024) {
+            const int ln = idx % 64, f = idx / 64, n = (f / BLOCKS) * 16 + ln % 16, j0 = (f % BLOCKS) * 32 + 8 * (ln / 16);
+            bf16x8 v;
+#pragma unroll
+            for (int e = 0; e < 8; e++) v[e] = (__bf16)sB[j0 + e][n];
+            *reinterpret_cast<bf16x8*>(&a.b_op[(item * (kTok * N / 8) + idx) * 8]) = v;
+        }
+    }
+    // 16 x 16 tiles (rows j, columns i): at 32 tokens four waves share a tile's contraction and add up through LDS
+    const int wave = tid / 64, lane = tid % 64, g4 = lane / 16, c16 = lane % 16;
+    constexpr int kSplit = BLOCKS == 1 ? 4 : 1, kSteps = N / 32 / kSplit > 0 ? N / 32 / kSplit : 1;
+    const int tile = wave / kSplit, kpart = wave % kSplit;
+    const int it = tile / (2 * BLOCKS), jt = tile % (2 * BLOCKS);
+    const bool wanted = s == 0 ? jt / 2 <= it / 2 : jt / 2 >= it / 2;   // of a 32 x 32 block that is kept
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (wanted && kpart * kSteps < N / 32) {
+#pragma unroll
+        for (int ks = 0; ks < kSteps; ks++) {
+            const int k0 = (kpart * kSteps + ks) * 32 + 8 * g4;
+            bf16x8 ah, al, bh, bl;
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                const float bv = sB[jt * 16 + c16][k0 + e], cv = sC[it * 16 + c16][k0 + e];
+                ah[e] = (__bf16)bv;
+                al[e] = (__bf16)(bv - (float)ah[e]);
+                bh[e] = (__bf16)cv;
+                bl[e] = (__bf16)(cv - (float)bh[e]);
+            }
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, acc, 0, 0, 0);
+        }
+    }
+    if constexpr (kSplit > 1) {
+        const int slot = tile * 3 + kpart - 1;
+        if (kpart > 0) *reinterpret_cast<f32x4*>(&sums[(slot * 64 + lane) * 4]) = acc;
+        __syncthreads();
+        if (kpart > 0) return;
+#pragma unroll
+        for (int o = 0; o < 3; o++) {
+            const f32x4 v = *reinterpret_cast<const f32x4*>(&sums[((tile * 3 + o) * 64 + lane) * 4]);
+#pragma unroll
+            for (int r = 0; r < 4; r++) acc[r] += v[r];
+        }
+    }
+    if (!wanted) return;
+    const int i = it * 16 + c16, j0 = jt * 16 + 4 * g4;
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+        if (s == 0 ? j0 + r > i : j0 + r < i) acc[r] = 0.0f;
+    // block (i, j) of the kept ones: forward (0,0), (1,0), (1,1); reverse (0,0), (0,1), (1,1)
+    const int block = it / 2 + jt / 2;
+    float* const dst = a.score[s] + item * (ssd_block_scores<BLOCKS>() * 1024) +
+                       ((block * 2 + it % 2) * 64 + (2 * (jt % 2) + g4 / 2) * 16 + c16) * 8 + 4 * (g4 % 2);
+    *reinterpret_cast<f32x4*>(dst) = acc;
+}
+
+// Prefix sums inside the two halves of a wave.
+__device__ __forceinline__ float half_wave_inclusive_sum(float v)
+{
+#define BM_DPP_ADD(ctrl, rows) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, rows, 0xF, false))
+    BM_DPP_ADD(0x111, 0xF);
+    BM_DPP_ADD(0x112, 0xF);
+    BM_DPP_ADD(0x114, 0xF);
+    BM_DPP_ADD(0x118, 0xF);
+    BM_DPP_ADD(0x142, 0xA);
+#undef BM_DPP_ADD
+    return v;
+}
+__device__ __forceinline__ float lane_value(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
+
+// grid (ceil(Dn / 64), 1, batch), block 256: wave w owns channels 16 (4 blockIdx.x + w) .. of one batch element.  COMMIT: h_out is
+// written; SHARED: both directions read the same x and the same z (the registers of the other cases are not held here).
+template <int N, int BLOCKS, bool COMMIT, bool SHARED>
+__global__ __launch_bounds__(256, BLOCKS == 1 ? 4 : COMMIT ? 2 : 3) void ssd_block_kernel(const SsdBlockArgs a)
+{
+    using T = unsigned short;
+    constexpr int kTok = 32 * BLOCKS, kRT = 2 * BLOCKS, kNB = N / 32, kScores = ssd_block_scores<BLOCKS>();
+    // wave-private tables by token: forward e_i, f_j Delta_j, exp(l_i), end weight; reverse e_i, f_j Delta_j
+    __shared__ __attribute__((aligned(16))) float s_tab[4][6][kTok];
+    // raw x by row (row r: token r - 3; zeros outside the block and its cached tail), and the outputs before the gate
+    constexpr int kRows = kTok + 6, kXPitch = 68, kYPitch = 68;
+    // and the score operands, made once per head: [head of the workgroup][direction, block, 16 rows][lane].  With 64 tokens the
+    // outputs lie over x and the operands.
+    constexpr int kXBytes = (SHARED ? 1 : 2) * kRows * kXPitch * (int)sizeof(T), kUnits = 2 * kScores * 2;
+    constexpr int kMAt = (kXBytes + 15) / 16 * 16, kMBytes = 2 * kUnits * 64 * 16, kYBytes = 2 * kTok * kYPitch * 4;
+    constexpr int kYAt = BLOCKS == 1 ? kMAt + kMBytes : 0, kAll = BLOCKS == 1 ? kYAt + kYBytes : kMAt + kMBytes > kYBytes ? kMAt + kMBytes : kYBytes;
+    __shared__ __attribute__((aligned(16))) unsigned char s_all[kAll];
+    auto* const s_x = reinterpret_cast<T(*)[kRows][kXPitch]>(s_all);
+    auto* const s_m = reinterpret_cast<bf16x8*>(s_all + kMAt);
+    auto* const s_y = reinterpret_cast<float(*)[kTok][kYPitch]>(s_all + kYAt);
+    const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // workgroups dealt to the XCDs batch-major: the heads of a batch element share its operands
+    int wg = blockIdx.x, b = blockIdx.z;
+    {
+        const unsigned total = gridDim.x * gridDim.z, id = blockIdx.x + gridDim.x * blockIdx.z;
+        if (total % 8 == 0) {
+            const unsigned item = (id % 8) * (total / 8) + id / 8;
+            wg = (int)(item % gridDim.x);
+            b = (int)(item / gridDim.x);
+        }
+    }
+    const int wg_ch0 = wg * 64;
+    // (waves past the last channel shadow the last tile: they join the barriers and store nothing)
+    const bool active = wg_ch0 + wave * 16 < a.Dn;
+    const int ch0 = active ? wg_ch0 + wave * 16 : a.Dn - 16;
+    const int head = ch0 / a.P, grp = head / a.HG, ch = ch0 + c16, last = a.L - 1;
+    const size_t item = (size_t)b * a.G + grp;
+    float(*const tab)[kTok] = s_tab[wave];
+
+    // ---- everything the wave reads
+    T dtraw[BLOCKS];
+    float a2, dtb = 0.0f;
+    {
+        // 32 tokens: the lower half of the wave scans the forward direction, the upper half the reverse one, each in its order
+        const int s = BLOCKS == 1 ? lane >> 5 : 0;
+        const SsdBlockDir& df = a.dir[0];
+        const SsdBlockDir& db = a.dir[1];
+        if constexpr (BLOCKS == 1) {
+            const T* const dp = s == 0 ? (const T*)df.dt.p + (size_t)b * df.dt.sb : (const T*)db.dt.p + (size_t)b * db.dt.sb;
+            const int t = s == 0 ? lane : kTok - 1 - (lane - 32);
+            dtraw[0] = dp[min(t, last) * (s == 0 ? df.dt.st : db.dt.st) + head];
+            a2 = (s == 0 ? df.A : db.A)[head] * kLog2e;
+            const float* const bias = s == 0 ? df.dt_bias : db.dt_bias;
+            if (a.dt_softplus && bias) dtb = bias[head];
+        } else {
+            dtraw[0] = ((const T*)df.dt.p + (size_t)b * df.dt.sb)[min(lane, last) * df.dt.st + head];
+            dtraw[BLOCKS - 1] = ((const T*)db.dt.p + (size_t)b * db.dt.sb)[min(kTok - 1 - lane, last) * db.dt.st + head];
+            a2 = 0.0f;
+        }
+    }
+    // x and z in pieces of eight channels (any alignment: global accesses need no more than the elements')
+    constexpr int kXPieces = (kRows * 8 + 255) / 256;
+    constexpr bool kTwoX = !SHARED;
+    Piece xraw[kTwoX ? 2 : 1][kXPieces], zraw[kTwoX ? 2 : 1][BLOCKS];
+    const int pc = 8 * (tid & 7);                          // this thread's channels within the workgroup's 64
+    const bool piece_there = wg_ch0 + pc < a.Dn;
+    const int piece_ch = piece_there ? wg_ch0 + pc : a.Dn - 8;
+#pragma unroll
+    for (int s = 0; s < (kTwoX ? 2 : 1); s++)
+#pragma unroll
+        for (int k = 0; k < kXPieces; k++) {
+            const int t = (tid >> 3) + 32 * k - 3;
+            const bool tail = s == 0 && t < 0 && a.tail_in && -t <= a.K - 1;
+            const T* const src = tail ? (const T*)a.tail_in + ((size_t)b * (a.K - 1) + (a.K - 1 + t)) * a.tail_ch
+                                      : (const T*)a.dir[s].x.p + (size_t)b * a.dir[s].x.sb + (long long)min(max(t, 0), last) * a.dir[s].x.st;
+            xraw[s][k] = *reinterpret_cast<const Piece*>(src + piece_ch);
+            if ((t < 0 && !tail) || t > last) xraw[s][k] = Piece{0, 0, 0, 0};
+        }
+    float w4[2][4], cb[2], dval[2];
+#pragma unroll
+    for (int s = 0; s < 2; s++) {
+        const SsdBlockDir& d = a.dir[s];
+        if (a.K == 4) {
+            typedef float __attribute__((ext_vector_type(4), aligned(4))) Taps;
+            const Taps w = *reinterpret_cast<const Taps*>(d.conv_w + (size_t)ch * 4);
+#pragma unroll
+            for (int i = 0; i < 4; i++) w4[s][i] = w[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; i++) {
+                const float w = d.conv_w[(size_t)ch * a.K + max(a.K - 1 - i, 0)];
+                w4[s][3 - i] = i < a.K ? w : 0.0f;
+            }
+        }
+        cb[s] = d.conv_b ? d.conv_b[ch] : 0.0f;
+        dval[s] = d.D[a.d_per_head ? head : ch];
+    }
+    f32x4 h[kNB][2];   // states 32 nb + 16 t + 4 g4 + r of channel ch
+    const size_t h_at = ((size_t)b * a.Dn + ch) * N + 4 * g4;
+#pragma unroll
+    for (int nb = 0; nb < kNB; nb++)
+#pragma unroll
+        for (int t = 0; t < 2; t++) {
+            h[nb][t] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            if (a.h_in) h[nb][t] = *reinterpret_cast<const f32x4*>(a.h_in + h_at + 32 * nb + 16 * t);
+        }
+    // scores: the waves of a head deal its units (direction, block, 16 rows) among themselves
+    const int head_waves = a.P / 16, hw = wave % head_waves;
+    bf16x8* const m_ops = s_m + (wave / head_waves) * (kUnits * 64) + lane;
+    f32x4 sc[kUnits / 2][2];
+#pragma unroll
+    for (int k = 0; k < kUnits / 2; k++) {
+        const int u = hw + k * head_waves, us = u / (2 * kScores), v = u - us * (2 * kScores);
+        if (u < kUnits) {
+            const float* const src = (us == 0 ? a.score[0] : a.score[1]) + item * (kScores * 1024) + (v * 64 + lane) * 8;
+            sc[k][0] = *reinterpret_cast<const f32x4*>(src);
+            sc[k][1] = *reinterpret_cast<const f32x4*>(src + 4);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < (kTwoX ? 2 : 1); s++)
+#pragma unroll
+        for (int k = 0; k < BLOCKS; k++)
+            zraw[s][k] = *reinterpret_cast<const Piece*>((const T*)a.dir[s].z.p + (size_t)b * a.dir[s].z.sb +
+                                                         (long long)min((tid >> 3) + 32 * k, last) * a.dir[s].z.st + piece_ch);
+#pragma unroll
+    for (int s = 0; s < (kTwoX ? 2 : 1); s++)
+#pragma unroll
+        for (int k = 0; k < kXPieces; k++) {
+            const int r = (tid >> 3) + 32 * k;
+            uint2* const dst = reinterpret_cast<uint2*>(&s_x[s][r < kRows ? r : 0][pc]);
+            if (r < kRows) {
+                dst[0] = make_uint2(xraw[s][k][0], xraw[s][k][1]);
+                dst[1] = make_uint2(xraw[s][k][2], xraw[s][k][3]);
+            }
+        }
+
+    // ---- Delta, the cumulative decays and the tables
+    bool separable[2];
+    float decay_q = 1.0f;
+    {
+        // separable decay exp(l_i - l_j) = e_i f_j around the block's middle unless it decays too fast (as in ssd_walk)
+        if constexpr (BLOCKS == 1) {
+            const int s = lane >> 5, t = s == 0 ? lane : kTok - 1 - (lane - 32);
+            float dl = IoBF16::cvt(dtraw[0]);
+            if (a.dt_softplus) dl = softplus(dl + dtb);
+            if (t > last) dl = 0.0f;
+            const float l2 = half_wave_inclusive_sum(dl * a2);
+            const float endf = lane_value(l2, 31), endr = lane_value(l2, 63);
+            separable[0] = lane_value(l2, 0) - endf <= 100.0f;
+            separable[1] = lane_value(l2, 32) - endr <= 100.0f;
+            const float mid = s == 0 ? lane_value(l2, 15) : lane_value(l2, 47), end = s == 0 ? endf : endr;
+            const bool sep = s == 0 ? separable[0] : separable[1];
+            float* const row = tab[s == 0 ? 0 : 4] + t;
+            row[0] = sep ? fast_exp2(l2 - mid) : l2;
+            row[kTok] = sep ? fast_exp2(mid - l2) * dl : dl;
+            if (s == 0) {
+                row[2 * kTok] = fast_exp2(l2);
+                row[3 * kTok] = fast_exp2(end - l2) * dl;
+            }
+            decay_q = fast_exp2(endf);
+        } else {
+#pragma unroll
+            for (int s = 0; s < 2; s++) {
+                const int t = s == 0 ? lane : kTok - 1 - lane;
+                float dl = IoBF16::cvt(dtraw[s == 0 ? 0 : BLOCKS - 1]);
+                if (a.dt_softplus) dl = softplus(dl + (a.dir[s].dt_bias ? a.dir[s].dt_bias[head] : 0.0f));
+                if (t > last) dl = 0.0f;
+                const float l2 = wave_inclusive_sum(dl * (a.dir[s].A[head] * kLog2e));
+                const float mid = lane_value(l2, 31), end = lane_value(l2, 63);
+                separable[s] = lane_value(l2, 0) - end <= 100.0f;
+                float* const row = tab[s == 0 ? 0 : 4] + t;
+                row[0] = separable[s] ? fast_exp2(l2 - mid) : l2;
+                row[kTok] = separable[s] ? fast_exp2(mid - l2) * dl : dl;
+                if (s == 0) {
+                    row[2 * kTok] = fast_exp2(l2);
+                    row[3 * kTok] = fast_exp2(end - l2) * dl;
+                    decay_q = fast_exp2(end);
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+
+    // ---- the head's masked, decayed score operands
+#pragma unroll
+    for (int k = 0; k < kUnits / 2; k++) {
+        const int u = hw + k * head_waves, us = u / (2 * kScores), v = u - us * (2 * kScores), m = v / 2;
+        if (u < kUnits) {
+            // block (i, j) of the kept ones: forward (0,0), (1,0), (1,1); reverse (0,0), (0,1), (1,1)
+            const int ib = us == 0 ? (m > 0) : (m > 1), jb = m - ib, i = ib * 32 + 16 * (v % 2) + c16, j0 = jb * 32 + 8 * g4;
+            const float* const te = tab[us == 0 ? 0 : 4];
+            const float* const tf = te + kTok;
+            const float ei = te[i];
+            bf16x8 op;
+#pragma unroll
+            for (int h2 = 0; h2 < 2; h2++) {
+                const f32x4 sv = sc[k][h2];
+                const float4 f4 = *reinterpret_cast<const float4*>(&tf[j0 + 4 * h2]);
+                const float fj[4] = {f4.x, f4.y, f4.z, f4.w};
+                if (us == 0 ? separable[0] : separable[1]) {
+#pragma unroll
+                    for (int e = 0; e < 4; e++) op[4 * h2 + e] = (__bf16)(sv[e] * ei * fj[e]);
+                } else {
+                    const float4 l4 = *reinterpret_cast<const float4*>(&te[j0 + 4 * h2]);
+                    const float lj[4] = {l4.x, l4.y, l4.z, l4.w};
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        const int j = j0 + 4 * h2 + e;
+                        const float val = sv[e] * fast_exp2(ei - lj[e]) * fj[e];
+                        op[4 * h2 + e] = (__bf16)((us == 0 ? j > i : j < i) ? 0.0f : val);
+                    }
+                }
+            }
+            m_ops[u * 64] = op;
+        }
+    }
+
+    // ---- inter-block term of the forward direction: exp(l_i) C_i H
+    f32x4 y[2][kRT];
+#pragma unroll
+    for (int rt = 0; rt < kRT; rt++) y[0][rt] = y[1][rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (a.h_in) {
+        const bf16x8* const c_op = reinterpret_cast<const bf16x8*>(a.c_op) + item * (kTok * N / 8) + lane;
+#pragma unroll
+        for (int nb = 0; nb < kNB; nb++) {
+            bf16x8 hb;
+#pragma unroll
+            for (int e = 0; e < 8; e++) hb[e] = (__bf16)h[nb][e / 4][e % 4];
+#pragma unroll
+            for (int rt = 0; rt < kRT; rt++)
+                y[0][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c_op[(nb * kRT + rt) * 64], hb, y[0][rt], 0, 0, 0);
+        }
+#pragma unroll
+        for (int rt = 0; rt < kRT; rt++) {
+            const float4 e4 = *reinterpret_cast<const float4*>(&tab[2][16 * rt + 4 * g4]);
+            y[0][rt][0] *= e4.x; y[0][rt][1] *= e4.y; y[0][rt][2] *= e4.z; y[0][rt][3] *= e4.w;
+        }
+    }
+
+    __syncthreads();                                       // x and the score operands
+    // ---- conv + SiLU of the lane's runs, as contraction operands, and (forward) weighted to the block's end
+    bf16x8 xc[2][BLOCKS], xw[BLOCKS];
+#pragma unroll
+    for (int s = 0; s < 2; s++)
+#pragma unroll
+        for (int blk = 0; blk < BLOCKS; blk++) {
+            const int t0 = blk * 32 + 8 * g4;
+            float xr[11];   // forward: tokens t0 - 3 ..; reverse: tokens t0 ..
+#pragma unroll
+            for (int q = 0; q < 11; q++) xr[q] = IoBF16::cvt(s_x[kTwoX ? s : 0][t0 + q + 3 * s][wave * 16 + c16]);
+            const float4 wa = *reinterpret_cast<const float4*>(&tab[3][t0]), wb = *reinterpret_cast<const float4*>(&tab[3][t0 + 4]);
+            const float wq[8] = {wa.x, wa.y, wa.z, wa.w, wb.x, wb.y, wb.z, wb.w};
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                float pre = cb[s];
+#pragma unroll
+                for (int k = 0; k < 4; k++) pre = fmaf(w4[s][k], xr[s == 0 ? e + k : e + 3 - k], pre);
+                const float v = silu(pre);
+                xc[s][blk][e] = (__bf16)v;
+                if (COMMIT && s == 0) xw[blk][e] = (__bf16)(v * wq[e]);
+            }
+        }
+
+    // ---- x's part of the committed tail: the last K - 1 raw tokens of (tail_in || block)
+    if (a.tail_out && (tid >> 3) < a.K - 1 && piece_there) {
+        const int n = tid >> 3;
+        const uint2* const src = reinterpret_cast<const uint2*>(&s_x[0][a.L - (a.K - 1) + n + 3][pc]);
+        const uint2 lo = src[0], hi = src[1];
+        *reinterpret_cast<Piece*>((T*)a.tail_out + ((size_t)b * (a.K - 1) + n) * a.tail_ch + piece_ch) = Piece{lo.x, lo.y, hi.x, hi.y};
+    }
+
+    // ---- intra-block products with the scores, and the skip term
+#pragma unroll
+    for (int s = 0; s < 2; s++) {
+#pragma unroll
+        for (int rt = 0; rt < kRT; rt++) {
+            const int ib = rt / 2;
+#pragma unroll
+            for (int jb = s == 0 ? 0 : ib; jb < (s == 0 ? ib + 1 : BLOCKS); jb++)
+                y[s][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(m_ops[((s * kScores + ib + jb) * 2 + rt % 2) * 64], xc[s][jb], y[s][rt], 0, 0, 0);
+            bf16x8 one;    // rows of the identity
+#pragma unroll
+            for (int e = 0; e < 8; e++) one[e] = (__bf16)(8 * g4 + e == 16 * (rt % 2) + c16 ? 1.0f : 0.0f);
+            const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+            const f32x4 xa = __builtin_amdgcn_mfma_f32_16x16x32_bf16(one, xc[s][ib], zero, 0, 0, 0);
+#pragma unroll
+            for (int r = 0; r < 4; r++) y[s][rt][r] += dval[s] * xa[r];
+        }
+    }
+
+    // ---- the committed state
+    if constexpr (COMMIT) {
+        const bf16x8* const b_op = reinterpret_cast<const bf16x8*>(a.b_op) + item * (kTok * N / 8) + lane;
+#pragma unroll
+        for (int nb = 0; nb < kNB; nb++)
+#pragma unroll
+            for (int t = 0; t < 2; t++) {
+                f32x4 v = h[nb][t];
+#pragma unroll
+                for (int r = 0; r < 4; r++) v[r] *= decay_q;
+#pragma unroll
+                for (int blk = 0; blk < BLOCKS; blk++)
+                    v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b_op[((2 * nb + t) * BLOCKS + blk) * 64], xw[blk], v, 0, 0, 0);
+                if (active) *reinterpret_cast<f32x4*>(a.h_out + h_at + 32 * nb + 16 * t) = v;
+            }
+    }
+
+    // ---- gate, combine, round: a token's eight channels per thread
+    const bool one_y = SHARED && !a.separate;
+    if constexpr (BLOCKS > 1) __syncthreads();             // (x and the operands have been read)
+#pragma unroll
+    for (int rt = 0; rt < kRT; rt++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int t = 16 * rt + 4 * g4 + r, c = wave * 16 + c16;
+            if (one_y) s_y[0][t][c] = y[0][rt][r] + y[1][rt][r];
+            else {
+                s_y[0][t][c] = y[0][rt][r];
+                s_y[1][t][c] = y[1][rt][r];
+            }
+        }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < BLOCKS; k++) {
+        const int t = (tid >> 3) + 32 * k;
+        if (t > last || !piece_there) continue;
+        T* const o = (T*)a.out + (size_t)b * a.out_sb + (long long)t * a.out_st + piece_ch;
+        Piece res[2];
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            float v[2][2];
+#pragma unroll
+            for (int e = 0; e < 2; e++) {
+                auto part = [e](unsigned p) { return __uint_as_float(e == 0 ? p << 16 : p & 0xffff0000u); };
+                const float zf = silu(part(zraw[0][k][i])), yf = s_y[0][t][pc + 2 * i + e];
+                if (one_y) v[0][e] = yf * zf;
+                else {
+                    const float zb = SHARED ? zf : silu(part(zraw[kTwoX ? 1 : 0][k][i])), yb = s_y[1][t][pc + 2 * i + e];
+                    v[0][e] = a.separate ? yf * zf : fmaf(yf, zf, yb * zb);
+                    v[1][e] = yb * zb;
+                }
+            }
+            typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+#pragma unroll
+            for (int h2 = 0; h2 < 2; h2++) res[h2][i] = __builtin_bit_cast(unsigned, bf16x2{(__bf16)v[h2][0], (__bf16)v[h2][1]});
+        }
+        *reinterpret_cast<Piece*>(o) = res[0];
+        if (a.separate) *reinterpret_cast<Piece*>(o + a.Dn) = res[1];
+    }
+}
+
+}  // namespace bm

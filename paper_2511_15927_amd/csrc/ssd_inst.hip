@@ -74,26 +74,6 @@ void launch_ssd_carry(int d_state, const SsdCarryArgs& ca, hipStream_t st)
     else hipLaunchKernelGGL(ssd_carry_kernel<64>, grid, dim3(256), 0, st, ca);
 }
 
-template <int N, int P>
-static void duo_one(const SsdStatePair& sp, int batch, hipStream_t st)
-{
-    static std::atomic<bool> seen[kMaxSeenDevices];
-    constexpr size_t lds = SsdDuoLds<N, P>::bytes();
-    auto kernel = ssd_duo_kernel<N, P>;
-    if (first_use_on_current_device(seen))
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)sp.dir[0].H, 1, (unsigned)batch), dim3(4 * P + 256), lds, st, sp);
-}
-
-// A call of one chunk: both directions of every (batch, head) item in one workgroup.
-void launch_ssd_duo(int d_state, int headdim, const SsdStatePair& sp, int batch, hipStream_t st)
-{
-    if (d_state == 128 && headdim == 64) duo_one<128, 64>(sp, batch, st);
-    else if (d_state == 128 && headdim == 32) duo_one<128, 32>(sp, batch, st);
-    else if (d_state == 64 && headdim == 64) duo_one<64, 64>(sp, batch, st);
-    else if (d_state == 64 && headdim == 32) duo_one<64, 32>(sp, batch, st);
-}
-
 // Both directions in one launch; nothing to do for the sub-part scanned last (no part starts after it).
 void launch_ssd_state(int d_state, int headdim, const SsdStatePair& sp, int subs, int batch, hipStream_t st)
 {

@@ -322,3 +322,51 @@ def test_ssd_wide_fast_decay_and_odd_pitch(gpu, oracle, heads):
     torch.cuda.synchronize()
     assert_close(out.float().cpu().numpy(), ref, gpu.TOL["bf16"])
     assert torch.all(big[:, :, :2] == 0) and torch.all(big[:, :, 2 + Dn:] == 0)
+
+
+@pytest.mark.parametrize("L", [1, 3, 31, 32, 33, 63, 64])
+@pytest.mark.parametrize("N,P,heads,groups,kw", [
+    (128, 64, 3, 1, {}),
+    (128, 32, 3, 1, dict(d_conv=2)),                  # a last workgroup of half its channels
+    (64, 32, 5, 1, dict(d_kind=0, d_conv=1)),
+    (64, 64, 4, 2, dict(conv_bc=0, dt_softplus=0)),
+])
+def test_ssd_one_chunk_calls(gpu, oracle, L, N, P, heads, groups, kw):
+    """Block steps around the 32-token blocks: from a cached state and tail and from none, committed in place, shared and separate
+    activations, both combines; a decay too fast for separable factors; views at odd places."""
+    from paper_2511_15927_amd import binding as bd
+    cfg = synth.m2_cfg(2, L, heads * P, headdim=P, d_state=N, n_groups=groups, **kw)
+    pf, pb, inp = case(cfg, 3400 + L + N + P)
+    for p in (pf, pb):
+        p["A"] = p["A"] * torch.where(torch.arange(heads) % 3 == 1, 60.0, 1.0)
+    other = synth.make_inputs(cfg, 3500 + L)
+    K, Dn, ch = cfg["d_conv"], cfg["d_inner"], synth.conv_channels(cfg)
+    g = torch.Generator().manual_seed(L + P)
+    h0 = (0.2 * torch.randn(2, Dn, N, generator=g)).float()
+    tail0 = synth.round_io(torch.randn(2, K - 1, ch, generator=g), "bf16") if K > 1 else None
+    for combine, in_b, start in ((0, None, True), (0, other, True), (1, other, False), (1, dict(inp, z=other["z"]), True)):
+        c = dict(cfg, combine=combine)
+        ref, h_ref, t_ref = oracle.bimamba_block_fwd(c, to_np(pf), to_np(pb), to_np(inp), None if in_b is None else to_np(in_b),
+                                                     h_in=h0.numpy() if start else None, tail_in=tail0.numpy() if start and K > 1 else None)
+        out, h, tail = gpu.gpu_block_fwd(c, pf, pb, inp, in_b, h_in=h0 if start else None, tail_in=tail0 if start else None)
+        assert_close(out, ref, gpu.TOL["bf16"], (combine, in_b is not None))
+        assert rel_l2(h, h_ref) < 1e-2
+        if K > 1:
+            assert np.array_equal(tail, t_ref)
+    # in place, from columns of wider buffers
+    ref, h_ref, t_ref = oracle.bimamba_block_fwd(cfg, to_np(pf), to_np(pb), to_np(inp), h_in=h0.numpy(), tail_in=tail0.numpy() if K > 1 else None)
+    dinp, desc, dpf, dpb = bd.to_device(inp, cfg), bd.make_desc(cfg), bd.to_device(pf), bd.to_device(pb)
+    for k, off in (("x", 2), ("z", 3)):
+        wide = torch.full((2, L, Dn + 6), 7.0, dtype=torch.bfloat16, device="cuda")[:, :, off:off + Dn]
+        wide.copy_(dinp[k])
+        dinp[k] = wide
+    big = torch.zeros(2, L, Dn + 3, dtype=torch.bfloat16, device="cuda")
+    h, tail = h0.cuda(), tail0.to(torch.bfloat16).cuda() if K > 1 else None
+    bd.bimamba_block_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp), None, h, tail, h, tail,
+                         bd.make_tensor(big[:, :, 1:1 + Dn]), bd.alloc_workspace(desc, 1))
+    torch.cuda.synchronize()
+    if K > 1:
+        assert np.array_equal(tail.float().cpu().numpy(), t_ref)
+    assert_close(big[:, :, 1:1 + Dn].float().cpu().numpy(), ref, gpu.TOL["bf16"])
+    assert rel_l2(h.cpu().numpy(), h_ref) < 1e-2
+    assert torch.all(big[:, :, :1] == 0) and torch.all(big[:, :, 1 + Dn:] == 0)
