@@ -147,7 +147,12 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
                 xr[1][q] = __uint_as_float(xraw_p[q] & 0xffff0000u);
             }
             asm volatile("" ::: "memory");
-            issue_x(cn, hd, xraw_p);
+            // (two heads' rows are neighbours in memory and are requested together: 0.5 % at 64 heads x 64)
+            if constexpr (HEADS == 1) issue_x(cn, hd, xraw_p);
+            else if constexpr (odd == 1) {
+                issue_x(cn, 0, xraw[0]);
+                issue_x(cn, 1, xraw[1]);
+            }
             if (edge_chunk(c)) {
 #pragma unroll
                 for (int q = 0; q < kPos + 3; q++) {
