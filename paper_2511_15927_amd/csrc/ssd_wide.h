@@ -95,6 +95,8 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
 
     if (wave >= 2 * W::kYWaves + 4) {
         // ------------------------------------------------------------------ conv waves
+        // (the conv and state waves' streams are what a period waits for: they go before the y waves on their SIMD)
+        __builtin_amdgcn_s_setprio(1);
         constexpr int kCP = P / 2;                  // channel pairs of the head
         constexpr int kPos = kQ * kCP / 256;        // chunk positions per thread (8 or 4)
         const int ptid = tid - 64 * (2 * W::kYWaves + 4);
@@ -251,6 +253,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
 
     if (wave >= 2 * W::kYWaves) {
         // ------------------------------------------------------------------ state waves
+        __builtin_amdgcn_s_setprio(1);
         constexpr int kBlocks = kNB * kPB, kOwn = (kBlocks + 3) / 4;   // 32 x 32 blocks of H; of one wave: one row of blocks
         const int sw = wave - 2 * W::kYWaves, ptid = tid - 64 * 2 * W::kYWaves;
         const bool owner = kOwn * sw < kBlocks;
@@ -264,14 +267,18 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
         const T* dtp = (const T*)a.dt.p + (size_t)b * a.dt.sb + scan_head;
         T dtraw;
         auto issue_dt = [&](int p) { dtraw = dtp[(long long)token_of(min(p / HEADS * kQ + lane, last)) * a.dt.st]; };
-        // Delta and the inclusive cumulative log2-decay of a period, and what the waves read of them
-        auto scan = [&](int p) {
-            const int c = p / HEADS;
-            float dl = IoBF16::cvt(dtraw);
+        // A period's scan: Delta; the inclusive cumulative log2-decay; what the waves read of them.  With two heads a wave does these
+        // in successive periods (whole, it lengthens one wave's stream in every period: 0.8 % at 8 x 8192 tokens); with one head's
+        // shorter periods the branches cost more than that (2 % at 1 x 1024).
+        float dl = 0.0f, l2 = 0.0f;
+        auto scan_delta = [&](int p) {
+            dl = IoBF16::cvt(dtraw);
             issue_dt(p + 4);   // (clamped to the sequence)
             if (a.dt_softplus) dl = softplus(dl + dtb);
-            if (c * kQ + lane > last) dl = 0.0f;
-            const float l2 = wave_inclusive_sum(dl * a2);
+            if (p / HEADS * kQ + lane > last) dl = 0.0f;
+        };
+        auto scan_decay = [&]() { l2 = wave_inclusive_sum(dl * a2); };
+        auto scan_tables = [&](int p) {
             const float l2_end = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), 63));
             // separable decay exp(l_i - l_j) = e_i f_j around the chunk's middle unless the chunk decays too fast
             const float l2_first = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), 0));
@@ -375,14 +382,31 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
             }
             if (HEADS == 2) __builtin_amdgcn_sched_barrier(0);
         };
-        auto scan_ahead = [&](int p) { if (((p + 2) & 3) == sw) scan(p + 2); };
+        // tables of period p + 2 in period p, by wave (p + 2) % 4
+        auto scan_ahead = [&](int p) {
+            const int ahead = (sw - p) & 3;
+            if constexpr (HEADS == 1) {
+                if (ahead != 2) return;
+                scan_delta(p + 2);
+                scan_decay();
+                scan_tables(p + 2);
+            } else {
+                if (ahead == 2) scan_tables(p + 2);
+                else if (ahead == 3) scan_decay();
+                else if (ahead == 0) scan_delta(p + 4);
+            }
+        };
         using Head0 = std::integral_constant<int, 0>;
         using Head1 = std::integral_constant<int, HEADS - 1>;
         issue_dt(sw);
 #pragma unroll
         for (int m = 0; m < 3; m++) issue_score(0, m);
         issue_bt(0);
-        if (sw < 2) scan(sw);
+        if (HEADS == 2 || sw < 2) {
+            scan_delta(sw);
+            scan_decay();
+        }
+        if (sw < 2) scan_tables(sw);
         lds_barrier();   // the tables of the first two periods
         score(0, HEADS == 1 ? 1 : -1);
         publish_state(Head0{}, 0);
