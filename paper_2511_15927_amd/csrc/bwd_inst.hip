@@ -7,25 +7,37 @@ namespace bm {
 
 bool bwd_supported(int d_state) { return d_state == 4 || d_state == 8 || d_state == 16; }
 
-// Time segments of a gradient call and their length.  The walk holds two waves per SIMD, so a call is cut until it has
-// four rounds of them: the last round, which may be nearly empty, is then a small part of the call, and the state pass has
-// twice the four waves per SIMD it holds.  Measured at 4, 6, 8, 12, 16 waves per SIMD (bf16): d_inner 4096, batch 8 x 8192
-// tokens 11.7 / 11.5 / 11.3 / 11.0 / 10.9 ms; 3104 channels, batch 22 x 1036: 3.55 / 3.31 / 3.20 / 3.02 / 3.16; 2512
-// channels, batch 2 x 5813: 1.57 / 1.38 / 1.39 / 1.36 / 1.36.  A segment costs the dh sum of the state pass and three tokens
-// walked twice, so segments stay at 32 tokens or more.
-constexpr int kBwdWavesPerSimd = 8;
-constexpr int kBwdMinSegment = 32;
+// Time segments of a gradient call and their length: the cheapest by two cost lines.  Workgroups take their segments in rounds of
+// what the chip holds (the walk two per CU, the state pass four); a round takes a segment's tokens, plus 15 tokens' time for
+// what a segment starts and ends with, and the last one, in which the CUs finish unevenly, a quarter of a round more.  Cutting a
+// call at all adds the dh sums to the state pass, 0.3 of the walk's time a token.  Fitted on 44 calls of random size (1 to 32 x 128
+// to 8192 tokens of 512 to 4096 channels, 8 and 16 states, bf16 and fp32), each timed with up to 14 numbers of segments: the choice
+// costs 0.7 % more than the best one on average, 6 % at worst; a fixed eight waves per SIMD, at 32 tokens or more, 11 %.
 void bwd_segments(int d_inner, int batch, int seqlen, int* nseg, int* seg_len, int* seg_chunks)
 {
-    const long long waves = 2LL * ((d_inner + 63) / 64) * (batch > 0 ? batch : 1);
-    long long n = (4LL * cu_count() * kBwdWavesPerSimd + waves / 2) / waves;
-    if (n > seqlen / kBwdMinSegment) n = seqlen / kBwdMinSegment;
-    if (n < 1) n = 1;
-    if (n > 65535) n = 65535;
-    const long long len = ((seqlen + n - 1) / n + kBwdChunk - 1) / kBwdChunk * kBwdChunk;
-    *seg_len = (int)(len > 0 ? len : kBwdChunk);
+    constexpr double kEnds = 15.0, kLastRound = 0.25, kDhSums = 0.3;
+    constexpr int kMaxRounds = 16;                       // (the sums of a segment take workspace)
+    const long long per_segment = (long long)(((d_inner + 63) / 64 + 1) / 2) * (batch > 0 ? batch : 1);
+    auto rounds = [&](long long workgroups, int per_cu) {
+        const long long resident = (long long)per_cu * cu_count();
+        return 2 * workgroups <= resident ? 1.0 : (double)((workgroups + resident - 1) / resident) + kLastRound;
+    };
+    const int all = seqlen > 0 ? (seqlen + kBwdChunk - 1) / kBwdChunk : 1;
+    int best = all;
+    double least = rounds(per_segment, 2) * all * kBwdChunk;
+    for (int n = 2; 2 * n <= all && n <= 65535 && n * per_segment <= 2LL * kMaxRounds * cu_count(); n++) {
+        const int chunks = (all + n - 1) / n;
+        if ((all + chunks - 1) / chunks != n) continue;   // as many segments of this length as a smaller n has
+        const double tokens = chunks * kBwdChunk;
+        const double cost = rounds(n * per_segment, 2) * (tokens + kEnds) + kDhSums * rounds(n * per_segment, 4) * tokens;
+        if (cost < least) {
+            least = cost;
+            best = chunks;
+        }
+    }
+    *seg_chunks = best;
+    *seg_len = best * kBwdChunk;
     *nseg = seqlen > 0 ? (seqlen + *seg_len - 1) / *seg_len : 1;
-    *seg_chunks = *seg_len / kBwdChunk;
 }
 
 template <typename IO>
