@@ -179,15 +179,23 @@ bool two_lanes_fit(const bimamba_desc* d, long long w)
 // One lane per chain needs no help from segments or lane splitting.
 bool enough_chains(const bimamba_desc* d, long long w) { return many_states(d) ? w >= target_waves() : 8 * w >= 15 * simds(); }
 
+// Whether one lane per chain, the whole call in one launch (short_kernel), is the choice for a call that allows it: up to
+// 64 tokens and 16 states, no conv on B and C.  Against the other geometries (bf16, 16 states, 4 / 16 / 32 / 64 tokens, us, other -> one
+// launch): 20480 chains (batch * d_inner) 14.4 / 15.0 / 18.8 / 26.1 -> 8.8 / 10.1 / 14.3 / 22.6, 57344 chains 17.6 / 23.9 / 32.1 / 45.4 ->
+// 8.5 / 12.7 / 18.2 / 29.8, 262144 chains x 64 118 -> 97; general decays, fp32, halves apart alike.  Only while two lanes per chain make at most
+// one wave per SIMD (16384 chains) do more than 32 tokens favour them: 64 tokens 22.3 / 22.0 (one launch / two lanes), fp32 26.4 / 23.7,
+// halves apart 23.1 / 20.6.  (Fewer chains yet: the row form.)
+bool one_launch_fits(const bimamba_desc* d, long long w)
+{
+    return d->d_state <= 16 && !d->conv_bc && d->seqlen <= kShortCallTokens && (d->d_state < 16 || d->seqlen <= 32 || 2 * w > simds());
+}
+
 int pick_split_general(const bimamba_desc* d)
 {
     if (d->state_split > 0) return d->state_split;
     const long long w = waves_of(d, 1);
     const bool two = split_supported(d->d_state, 2), four = d->d_state >= 64 && split_supported(d->d_state, 4);
-    // (calls of a few dozen tokens that can run as one launch with one lane per chain keep it, see short_call below:
-    // 32-token block steps at batch 16, d_inner 4096 take 23 us that way against 28 us with two lanes and a preparation launch)
-    const bool one_launch_form = d->d_state <= 16 && !d->conv_bc && d->seqlen <= kShortCallTokens && enough_chains(d, w);
-    if (!many_states(d) && two && d->time_chunks <= 1 && !one_launch_form && two_lanes_fit(d, w)) return 2;
+    if (!many_states(d) && two && d->time_chunks <= 1 && !one_launch_fits(d, w) && two_lanes_fit(d, w)) return 2;
     if (enough_chains(d, w)) return 1;
     if (many_states(d)) return w >= target_waves() / 2 && two ? 2 : four ? 4 : two ? 2 : 1;
     if (d->time_chunks == 0 && w * segments_for(d, w) >= target_waves()) return 1;
@@ -281,6 +289,7 @@ Geometry geometry_of(const bimamba_desc* d, bool coarse)
     const int split = pick_split_general(d);
     const bool open = d->state_split == 0 && d->time_chunks == 0 && d->d_state <= 16 && d->seqlen > 0 && d->batch > 0;
     const long long w = waves_of(d, 1);
+    if (open && one_launch_fits(d, w)) return {1, 1};
     if (open && !coarse && !enough_chains(d, w) && !(d->d_state == 16 && two_lanes_fit(d, w))) {
         Geometry g = pick_geometry(d);
         if (g.nseg > 4096) g.nseg = 4096;
@@ -724,6 +733,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
         sa.dt_softplus = d->dt_softplus; sa.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD;
         sa.separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
         sa.raw_partial = !sa.separate && same_tensor(in_f->z, in_b->z);
+        sa.same_bc = same_tensor(in_f->B, in_b->B) && same_tensor(in_f->C, in_b->C);
         sa.try_progression = 1;
         CarryArgs ca{};
         ca.carry = sa.carry; ca.sumdt = sa.sumdt; ca.A[0] = pf->A; ca.A[1] = pb->A;

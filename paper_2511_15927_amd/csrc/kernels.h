@@ -59,11 +59,12 @@ struct SweepArgs {
     float* sumdt;         // [2][batch][nseg][Dn]
     int L, Dn, P, HG, G, K, nseg, seg_len, tail_ch;
     int dt_softplus, d_per_head, separate;
+    int same_bc;          // both directions read the same B and C (the short form asks)
     int raw_partial;      // both directions gate with the same z: park y ungated and gate once at the final store
     int try_progression;  // let each wave test whether its chains' A rows are arithmetic in n (see sweep_kernel)
     int layer_wgs;        // workgroups the dispatcher places before a CU gets its next one (the CU count); set by the launcher
     int turn_mask;        // 0: leave wave priorities alone; 1 / 3: two / up to four waves share a SIMD and take turns
-    void* tail_out;       // or null; written by the short form of the sweep (kBcStaged)
+    void* tail_out;       // or null; written by the short form
 };
 
 // Buffer resource of a raw (untyped, unstrided) range starting at a wave-uniform address.  An access adds a
@@ -163,10 +164,7 @@ __device__ __forceinline__ float chain_lane_value(float v)
 }
 
 enum { kSweep = 0, kSummary = 1 };
-// Where a token's B|C row comes from: the fp32 rows prep_bc_kernel prepared, or (short calls, one lane per chain, no
-// conv on B and C) a copy of the caller's rows that each wave converts into LDS itself at kernel start, which saves
-// the preparation launch when a call is a few dozen tokens long.
-enum { kBcPrepared = 0, kBcStaged = 1 };
+// Calls of up to this many tokens, up to 16 states, no conv on B and C and one lane per chain run in one launch (short_kernels.h).
 constexpr int kShortCallTokens = 64;
 // How the decay exp(Delta A[h, n]) is formed: one exponential per state; one per token for a scalar A per head; or, when
 // A is an arithmetic progression in n (detected on the device), two exponentials per token, a_n = a_first r^n.
@@ -233,7 +231,6 @@ struct Chain {
     long long xs, zs, dts, os, ps, bcs;
     unsigned ch_io, head_io, ch_f32;  // the lane's byte offset into a row: channel / head in the I/O dtype, channel in fp32
     unsigned sub;                   // slice index (lane % S)
-    int tok, tstep;                 // kBcStaged: current token and its signed step (rows are indexed by token in LDS)
 };
 
 template <typename IO, int TILE>
@@ -425,7 +422,6 @@ __device__ __forceinline__ void token_step(Chain<N, S, AKIND, IO>& c, typename I
         }
     }
     c.bcrow += c.bcs;
-    c.tok += c.tstep;
 }
 
 template <int N, int S, int AKIND, typename IO>
@@ -766,7 +762,6 @@ __device__ __forceinline__ int run_tiles_dealt(const SweepArgs& a, Chain<N, S, A
     for (int m = 0; m < 3; m++) c.xh[m] = chain_lane_pick<S>(hist[m / S], (S - 1 - m % S));
     advance_rows(c, done);
     c.bcrow += done * c.bcs;
-    c.tok += done * c.tstep;
     return done;
 }
 
@@ -774,22 +769,21 @@ __device__ __forceinline__ int run_tiles_dealt(const SweepArgs& a, Chain<N, S, A
 template <int N, int S, int TILE>
 constexpr int kStagedTile = kDealtTokens<N, S> && kDealtTile<N, S> > TILE ? kDealtTile<N, S> : TILE;
 
-template <int N, int S, int AKIND, typename IO, int MODE, int TILE, int BCSRC = kBcPrepared>
+template <int N, int S, int AKIND, typename IO, int MODE, int TILE>
 __device__ __forceinline__ void run_range(const SweepArgs& a, Chain<N, S, AKIND, IO>& c, int count, bool softplus_dt, float* lds,
                                           int lane)
 {
-    static_assert(BCSRC == kBcPrepared || (S == 1 && N <= 16), "staged rows exist for one lane per chain, <= 16 states");
     constexpr int NS = N / S;
     constexpr int kRowF4 = 2 * N / 4;              // float4s per B|C row
     constexpr int kStage = (TILE * kRowF4 + 63) / 64;  // float4s each lane moves per staged tile
     // With the shallow tile (many waves per SIMD) token_step refills the one scalar row itself; with the deep tile
     // (two or three waves per SIMD, less cover for a scalar load) the next token's row is requested a whole token
     // ahead into a second set of registers.
-    constexpr bool kRefill = kBcScalarAhead<N, S> && BCSRC == kBcPrepared && TILE == 4;
+    constexpr bool kRefill = kBcScalarAhead<N, S> && TILE == 4;
     using Tile = RawTile<IO, TILE>;
     if (count <= 0) return;
     int done = 0;
-    if constexpr (kDealtTokens<N, S> && MODE != kModeNoOutput && BCSRC == kBcPrepared) {
+    if constexpr (kDealtTokens<N, S> && MODE != kModeNoOutput) {
         done = run_tiles_dealt<N, S, AKIND, IO, MODE>(a, c, count, softplus_dt, lds, lane);
     } else if (count >= TILE) {
         Tile nxt;
@@ -819,8 +813,6 @@ __device__ __forceinline__ void run_range(const SweepArgs& a, Chain<N, S, AKIND,
             stage_load(0);
             stage_store(0);
             load_bc_lds<N, S>(lds, 0, c.sub, row);
-        } else if constexpr (BCSRC == kBcStaged) {
-            load_bc_lds<N, 1>(lds, c.tok, 0, row);
         } else if constexpr (kBcScalarAhead<N, S>) {
             load_bc_scalar<N>(c.bcrow, row);
         }
@@ -873,12 +865,10 @@ __device__ __forceinline__ void run_range(const SweepArgs& a, Chain<N, S, AKIND,
                 BcRow<NS> row_next;
                 if constexpr (S > 1) {
                     if (i + 1 < TILE) load_bc_lds<N, S>(tile_bc, i + 1, c.sub, row_next);
-                } else if constexpr (BCSRC == kBcStaged) {
-                    load_bc_lds<N, 1>(lds, done + i + 1 < count ? c.tok + c.tstep : c.tok, 0, row_next);
                 }
                 // never read past the walk's last token: the row after it may lie outside the buffer
                 const float* next = kBcScalarAhead<N, S> ? (done + i + 1 < count ? c.bcrow + c.bcs : c.bcrow) : nullptr;
-                if constexpr (kBcScalarAhead<N, S> && BCSRC == kBcPrepared && !kRefill) {
+                if constexpr (kBcScalarAhead<N, S> && !kRefill) {
                     load_bc_scalar<N>(next, row_next);
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -886,8 +876,6 @@ __device__ __forceinline__ void run_range(const SweepArgs& a, Chain<N, S, AKIND,
                                                   TileSink<IO, TILE>{to, tpk, c.ch_io, c.ch_f32, i});
                 if constexpr (S > 1) {
                     if (i + 1 < TILE) row = row_next;
-                } else if constexpr (BCSRC == kBcStaged) {
-                    row = row_next;
                 } else if constexpr (kBcScalarAhead<N, S> && !kRefill) {
                     __builtin_amdgcn_sched_barrier(0);
                     row = row_next;
@@ -910,7 +898,6 @@ __device__ __forceinline__ void run_range(const SweepArgs& a, Chain<N, S, AKIND,
         if (mode_reads_partial(MODE)) part = *lane_elem(c.prow, c.ch_f32);
         BcRow<NS> row;
         if constexpr (S > 1) load_bc_direct<N, S>(c.bcrow, c.sub, row);
-        else if constexpr (BCSRC == kBcStaged) load_bc_lds<N, 1>(lds, c.tok, 0, row);
         else if constexpr (kBcScalarAhead<N, S>) load_bc_scalar<N>(c.bcrow, row);
         float delta = IO::cvt(dr);
         if (softplus_dt) delta = softplus(delta + c.dtb);
@@ -1063,7 +1050,7 @@ __device__ __forceinline__ int tile_of_wave(int w, int Dn)
 }
 
 // grid (ceil(ceil(Dn / (64/S)) / 2), nseg, batch), block 256.
-template <int N, int S, int AKIND, typename IO, int KIND, int TILE, int BCSRC = kBcPrepared>
+template <int N, int S, int AKIND, typename IO, int KIND, int TILE>
 __device__ __forceinline__ void sweep_body(const SweepArgs& a, float* lds_all, const int w)
 {
     const int s = w & 1;
@@ -1071,7 +1058,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, float* lds_all, c
     constexpr int NS = N / S;
     constexpr int kCpw = 64 / S;  // channels per wave
     const int lane = threadIdx.x & 63;
-    float* lds = lds_all + (BCSRC == kBcStaged ? w * (kShortCallTokens * 2 * N) : S > 1 ? w * (2 * kStagedTile<N, S, TILE> * 2 * N) : 0);
+    float* lds = lds_all + (S > 1 ? w * (2 * kStagedTile<N, S, TILE> * 2 * N) : 0);
     const DirArgs& da = a.dir[s];
     const int b = blockIdx.z, seg = blockIdx.y;
     // Lanes past the last channel shadow channel Dn-1: they load the same inputs, compute the same values and
@@ -1168,30 +1155,6 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, float* lds_all, c
     c.orow = (T*)a.out + (size_t)b * a.out_sb + (long long)tstart * a.out_st + (a.separate ? s * a.Dn : 0);
     c.prow = a.partial + ((size_t)b * a.L + tstart) * a.Dn;
     c.bcrow = da.bc + (((size_t)b * a.L + tstart) * a.G + grp) * (2 * N);
-    c.tok = tstart;
-    c.tstep = step;
-    if constexpr (BCSRC == kBcStaged) {
-        // this wave's own fp32 copy of its direction's B|C rows of the whole (short) call, indexed by token
-        const T* bsrc = (const T*)da.Braw.p + (size_t)b * da.Braw.sb + grp * N;
-        const T* csrc = (const T*)da.Craw.p + (size_t)b * da.Craw.sb + grp * N;
-        // every load is requested before the first value is used: the call is too short to wait for them one by one
-        constexpr int kPerLane = kShortCallTokens * 2 * N / 64;
-        const int count = a.L * 2 * N;
-        T raw[kPerLane];
-#pragma unroll
-        for (int j = 0; j < kPerLane; j++) {
-            if (j * 64 >= count) break;
-            const int idx = min(j * 64 + lane, count - 1);
-            const int t = idx / (2 * N), col = idx % (2 * N);
-            raw[j] = col < N ? bsrc[(long long)t * da.Braw.st + col] : csrc[(long long)t * da.Craw.st + col - N];
-        }
-#pragma unroll
-        for (int j = 0; j < kPerLane; j++) {
-            if (j * 64 >= count) break;
-            if (j * 64 + lane < count) lds[j * 64 + lane] = IO::cvt(raw[j]);
-        }
-        __builtin_amdgcn_wave_barrier();  // read back by other lanes of this wave only; LDS keeps wave order
-    }
     const bool sp = a.dt_softplus != 0;
 
     if (KIND == kSummary) {
@@ -1205,36 +1168,26 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, float* lds_all, c
     }
 
     if (a.separate) {
-        run_range<N, S, AKIND, IO, kModeFinalOnly, TILE, BCSRC>(a, c, len, sp, lds, lane);
+        run_range<N, S, AKIND, IO, kModeFinalOnly, TILE>(a, c, len, sp, lds, lane);
     } else {
         // forward parks [t0, m), reverse parks [m, t1); then each finishes the other's half
         const int n_first = s == 0 ? (len + 1) / 2 : len / 2;
-        if (a.raw_partial) run_range<N, S, AKIND, IO, kModePartialRaw, TILE, BCSRC>(a, c, n_first, sp, lds, lane);
-        else run_range<N, S, AKIND, IO, kModePartial, TILE, BCSRC>(a, c, n_first, sp, lds, lane);
+        if (a.raw_partial) run_range<N, S, AKIND, IO, kModePartialRaw, TILE>(a, c, n_first, sp, lds, lane);
+        else run_range<N, S, AKIND, IO, kModePartial, TILE>(a, c, n_first, sp, lds, lane);
         __syncthreads();  // workgroup-scope release/acquire: the other wave's partials are visible from here on
-        if (a.raw_partial) run_range<N, S, AKIND, IO, kModeFinalAddRaw, TILE, BCSRC>(a, c, len - n_first, sp, lds, lane);
-        else run_range<N, S, AKIND, IO, kModeFinalAdd, TILE, BCSRC>(a, c, len - n_first, sp, lds, lane);
+        if (a.raw_partial) run_range<N, S, AKIND, IO, kModeFinalAddRaw, TILE>(a, c, len - n_first, sp, lds, lane);
+        else run_range<N, S, AKIND, IO, kModeFinalAdd, TILE>(a, c, len - n_first, sp, lds, lane);
     }
-    // Waves past the last tile shadow it: all have read h_in (and tail_in, which a short call's commit overwrites too) before
-    // any of them commits over it.  With the halves apart no barrier came before; the carry of segments has its own commit.
-    if (a.separate && (BCSRC == kBcStaged || a.nseg == 1) && (a.h_out || a.tail_out)) __syncthreads();   // (short calls: one segment)
+    // Waves past the last tile shadow it: all have read h_in before any of them commits over it.  With the halves apart no
+    // barrier came before; the carry of segments has its own commit.
+    if (a.separate && a.nseg == 1 && a.h_out) __syncthreads();
     if (s == 0 && a.nseg == 1 && a.h_out) {
         float* dst = a.h_out + ((size_t)b * a.Dn + ch) * N + sub * NS;
 #pragma unroll
         for (int n = 0; n < NS; n++) dst[n] = c.h[n];
     }
-    // Short calls commit the conv tail too: it is the window the forward walk leaves, raw tokens, so cutting the fp32 form
-    // back to the I/O dtype restores their bits.  A launch of its own for it cost 4.0 us: 26.4 -> 23.8 us for a 32-token
-    // block step that commits (batch 16, d_inner 4096).  Only here: the window kept alive through the end of the long walks,
-    // or read again behind them, cost those 0.5 % (8 x 2048 and 8 x 8192 tokens).
-    if constexpr (BCSRC == kBcStaged) {
-        if (s == 0 && a.tail_out) {
-            T* dst = (T*)a.tail_out + (size_t)b * (a.K - 1) * a.tail_ch + ch;
-#pragma unroll
-            for (int i = 0; i < 3; i++)
-                if (i < a.K - 1) dst[(size_t)(a.K - 2 - i) * a.tail_ch] = io_bits<IO>(c.xh[i]);
-        }
-    }
+    // (The conv tail is not committed here: the window kept alive through the end of the long walks, or read again behind them,
+    // cost those 0.5 %, 8 x 2048 and 8 x 8192 tokens; its own launch costs 4 us.)
 }
 
 // The progression form of the decay is used for bf16 I/O and up to 32 states (its rounding error grows with the state
@@ -1248,12 +1201,10 @@ constexpr bool kProgressionEligible = (N >= 2 && N <= 32 && sizeof(typename IO::
 template <int N, int S, int KIND>
 constexpr int kSweepMinWaves = KIND == kSweep && kDealtTokens<N, S> ? (S == 4 ? 4 : 3) : 1;
 
-template <int N, int S, int AKIND, typename IO, int KIND, int TILE, int BCSRC = kBcPrepared>
+template <int N, int S, int AKIND, typename IO, int KIND, int TILE>
 __global__ __launch_bounds__(256, (kSweepMinWaves<N, S, KIND>)) void sweep_kernel(const SweepArgs a)
 {
-    __shared__ __attribute__((aligned(16))) float lds_all[BCSRC == kBcStaged ? 4 * kShortCallTokens * 2 * N
-                                                          : S > 1            ? 4 * 2 * kStagedTile<N, S, TILE> * 2 * N
-                                                                             : 4];
+    __shared__ __attribute__((aligned(16))) float lds_all[S > 1 ? 4 * 2 * kStagedTile<N, S, TILE> * 2 * N : 4];
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if constexpr (AKIND == kAPerState && kProgressionEligible<N, IO>) {
         // Every lane checks its own chain's A row: A[h, n] == fma(n, A[h, 1] - A[h, 0], A[h, 0]) for all n.  The wave takes
@@ -1266,12 +1217,12 @@ __global__ __launch_bounds__(256, (kSweepMinWaves<N, S, KIND>)) void sweep_kerne
 #pragma unroll
             for (int n = 0; n < N; n++) ok &= row[n] == fmaf((float)n, step, first);
             if (__all(ok)) {
-                sweep_body<N, S, kAProgression, IO, KIND, TILE, BCSRC>(a, lds_all, w);
+                sweep_body<N, S, kAProgression, IO, KIND, TILE>(a, lds_all, w);
                 return;
             }
         }
     }
-    sweep_body<N, S, AKIND, IO, KIND, TILE, BCSRC>(a, lds_all, w);
+    sweep_body<N, S, AKIND, IO, KIND, TILE>(a, lds_all, w);
 }
 
 // Stitch time segments: carry[s][b][seg] holds each segment's end state from a zero start (summary pass); replace it

@@ -10,15 +10,19 @@ namespace bm {
 // 18.8 / 12.5, 4 x 64 19.6 / 21.2; 1 x 128 26.6 / 16.9, 2 x 128 27.4 / 27.5; 1 x 256 49.6 / 38.2, d_inner 512 48.6 / 11.6.
 // Against the sweep as pick_geometry plans it, 1000 calls inside the limits (4, 8 and 16 states, decays per state or per
 // head, bf16 and fp32, which differ little), time of the row form over the sweep's, by chains (batch * d_inner):
-//   beyond 12288 chains   4 states 1.2 to 1.4 up to 24 tokens, 1.0 to 1.3 beyond; 8 states 1.1 to 1.3 up to 24 tokens, 0.9 to
-//                         1.0 beyond; 16 states 0.75 to 1.0: not taken with 4 states, with 8 from 25 tokens on
+//   beyond 12288 chains   65 tokens and more: 4 states 1.0 to 1.3, 8 states 0.9 to 1.0, 16 states 0.75 to 1.0: not taken with 4
 //   129 to 192 tokens     with 4 / 8 / 16 states up to 4096 chains 0.65 / 0.56 / 0.51, beyond them 1.14 / 0.94 / 0.94: 4 states
 //                         stop at 0.75 M channel tokens, the others at 1 M
 //   193 to 256 tokens     up to 0.4 M channel tokens 0.56 / 0.48 / 0.50, the worst call 0.81; beyond (bf16, 16 states) 1 x 212
 //                         tokens of 2688 channels 28.2 us / 32.6, 1 x 220 of 4112 37.1 / 56.4, 1 x 256 of 4096 34.6 / 37.8
+// Up to 64 tokens the other side is short_kernel, one launch too (short / row, us; 4, 16, 32 and 64 tokens, bf16):
+//   16 states  12288 chains  8.4/8.7  9.9/9.6 14.1/11.6 22.0/17.3;  16384 chains  8.5/10.4 10.0/12.2 14.4/15.0
+//   8 states    8192 chains  8.7/9.2  8.2/8.4 11.2/9.7  16.8/13.5;  12288 chains  9.1/9.6  9.3/10.0 11.3/11.5 16.9/17.3
+//   4 states    8192 chains  8.3/8.4  8.4/8.8  9.7/9.4  14.4/13.3;  12288 chains  8.6/8.9  8.6/9.6   9.8/11.5 14.5/17.1
+constexpr long long kRowMaxChainsShort = 3LL << 12, kRowMaxChainsShortFew = 8192;   // up to 64 tokens: 16 states, fewer
 constexpr long long kRowMaxChains = 16384, kRowMaxChainsFew = 3LL << 12, kRowMaxElements = 3LL << 18, kRowMaxElementsLong = 1LL << 20;
 constexpr long long kRowMaxElementsLongest = 3LL << 17;
-constexpr int kRowFewTokens = 24, kRowLongTokens = 128, kRowLongestTokens = 192;
+constexpr int kRowLongTokens = 128, kRowLongestTokens = 192;
 constexpr size_t kRowLdsBytes = 160 * 1024;
 
 bool row_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f)
@@ -28,7 +32,9 @@ bool row_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f)
     const long long most = seqlen > kRowLongestTokens                 ? kRowMaxElementsLongest
                            : seqlen > kRowLongTokens && d_state >= 8 ? kRowMaxElementsLong
                                                                      : kRowMaxElements;
-    const long long most_chains = d_state < 8 || (d_state < 16 && seqlen <= kRowFewTokens) ? kRowMaxChainsFew : kRowMaxChains;
+    const long long most_chains = seqlen <= kShortCallTokens ? (d_state < 16 ? kRowMaxChainsShortFew : kRowMaxChainsShort)
+                                  : d_state < 8              ? kRowMaxChainsFew
+                                                             : kRowMaxChains;
     if (chains > most_chains || chains * seqlen > most) return false;
     const long long tiles = (long long)batch * ((d_inner + 3) / 4);
     const int groups = (seqlen + kRowTokens - 1) / kRowTokens;

@@ -1,8 +1,10 @@
 // Instantiations of the scan kernels for one d_state (BM_N) and one lanes-per-chain factor (BM_S), compiled once per
 // supported pair so the translation units build in parallel.
 #include "kernels.h"
+#include "short_kernels.h"
 #include "launch.h"
 
+#include <algorithm>
 #include <atomic>
 
 #if !defined(BM_N) || !defined(BM_S)
@@ -75,19 +77,21 @@ static SweepArgs with_turns(const SweepArgs& sa, const dim3& grid, int resident)
 
 static long long rounds(long long per_cu, int resident) { return (per_cu + resident - 1) / resident; }
 
-// Bytes of dynamic LDS to ask for so that the launch spreads evenly (0: nothing to gain).
+// Bytes of dynamic LDS to ask for so that the launch spreads evenly (the `need` bytes the kernel uses: nothing to gain).
 template <typename Kernel>
-static unsigned spread_lds(Kernel kernel, KernelFit* fit, const dim3& grid)
+static unsigned spread_lds(Kernel kernel, KernelFit* fit, const dim3& grid, int need = 0)
 {
-    const int dev = current_device(), resident = fit->ask(kernel, dev);
-    if (dev < 0) return 0;
+    const int dev = current_device();
+    int resident = fit->ask(kernel, dev);
+    if (dev < 0) return (unsigned)need;
+    if (need > 0) resident = std::min(resident, kLdsPerCu / need);
     const long long per_cu = workgroups_per_cu(grid), n = rounds(per_cu, resident);
     const int cap = (int)((per_cu + n - 1) / n);
-    if (cap >= resident) return 0;
+    if (cap >= resident) return (unsigned)need;
     // between the largest slice of which cap + 1 fit and the largest of which cap fit
     const int slice = (kLdsPerCu / cap + kLdsPerCu / (cap + 1)) / 2 / 256 * 256;
     const int extra = slice - fit->static_lds[dev].load(std::memory_order_relaxed);
-    if (extra < 0 || (slice > 64 * 1024 && !fit->lifted[dev].load(std::memory_order_relaxed))) return 0;
+    if (extra < need || (slice > 64 * 1024 && !fit->lifted[dev].load(std::memory_order_relaxed))) return (unsigned)need;
     return (unsigned)extra;
 }
 
@@ -120,6 +124,21 @@ struct Tiled {
     }
 };
 
+#if BM_S == 1 && BM_N <= 16
+template <int AKIND, int KIND, typename IO>
+static void launch_short(const SweepArgs& sa, int batch, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    static KernelFit fit;
+    const auto kernel = short_kernel<BM_N, AKIND, KIND, IO>;
+    const dim3 grid((unsigned)(((sa.Dn + 63) / 64 + 1) / 2), 1, (unsigned)batch);
+    const int need = ShortLds(sa.L, BM_N, !sa.same_bc, sa.G > 1, KIND == kShortSeparate).total * (int)sizeof(float);
+    const unsigned lds = spread_lds(kernel, &fit, grid, need);
+    if (ev_start) (void)hipEventRecord(ev_start, st);
+    hipLaunchKernelGGL(kernel, grid, dim3(kBlock), lds, st, sa);
+    if (ev_stop) (void)hipEventRecord(ev_stop, st);
+}
+#endif
+
 // One lane per chain and up to 32 states come with two prefetch depths: the deep tile hides memory latency when a
 // SIMD holds few waves, the shallow one needs fewer registers, so more waves are resident at once.  The shallow tile
 // is taken when it gets the launch through in fewer rounds of resident workgroups.
@@ -128,14 +147,10 @@ static void launch_one(const SweepArgs& sa, const CarryArgs& ca, int batch, int 
                        hipEvent_t ev_start, hipEvent_t ev_stop)
 {
 #if BM_S == 1 && BM_N <= 16
-    if (short_call) {   // one launch: the kernel converts the caller's B and C rows itself (see kBcStaged)
-        const dim3 grid((unsigned)(((sa.Dn + 63) / 64 + 1) / 2), 1, (unsigned)batch);
-        static KernelFit fit_short;
-        auto sweep = sweep_kernel<BM_N, BM_S, AKIND, IO, kSweep, 8, kBcStaged>;
-        const unsigned lds = spread_lds(sweep, &fit_short, grid);
-        if (ev_start) (void)hipEventRecord(ev_start, st);
-        hipLaunchKernelGGL(sweep, grid, dim3(kBlock), lds, st, with_turns(sa, grid, fit_short.ask(sweep, current_device())));
-        if (ev_stop) (void)hipEventRecord(ev_stop, st);
+    if (short_call) {
+        if (sa.separate) launch_short<AKIND, kShortSeparate, IO>(sa, batch, st, ev_start, ev_stop);
+        else if (sa.raw_partial) launch_short<AKIND, kShortAddRaw, IO>(sa, batch, st, ev_start, ev_stop);
+        else launch_short<AKIND, kShortAdd, IO>(sa, batch, st, ev_start, ev_stop);
         return;
     }
 #endif

@@ -284,3 +284,36 @@ def test_tail_committed_by_the_sweep(gpu, oracle, L, split, N, K, io):
     torch.cuda.synchronize()
     assert_close(out.float().cpu().numpy().reshape(ref.shape), ref, gpu.TOL[io])
     assert np.array_equal(dt.float().cpu().numpy().astype(np.float64), t_ref)
+
+
+@pytest.mark.parametrize("L", [1, 2, 8, 15, 16, 17, 33, 63, 64])
+@pytest.mark.parametrize("N,io,a_kind,own", [(16, "bf16", 0, ""), (16, "f32", 0, "z"), (16, "bf16", 1, "BC"), (8, "bf16", 0, "xzBC"), (4, "f32", 1, "BC")])
+def test_one_launch_short_calls(gpu, oracle, L, N, io, a_kind, own):
+    """Calls of up to 64 tokens, one lane per chain, in one launch: around the tiles of eight tokens and the meeting of the
+    directions; B/C groups whose border lies inside a workgroup; the reverse direction with `own` tensors for some of its inputs
+    (gated together or apart, one copy of B and C rows or two); general and arithmetic decays, decays per head; halves apart;
+    states and tails committed in place."""
+    from paper_2511_15927_amd import binding as bd
+    cfg = synth.mixer_cfg(2, L, 192, d_state=N, n_heads=192 if L % 2 else 96, n_groups=3, io=io, a_kind=a_kind, dt_softplus=L // 2 % 2,
+                          combine=int(L in (2, 15, 64)))
+    if a_kind == 0 and L % 4 != 1:
+        pf, pb = params(cfg, 60 + L)
+    else:
+        pf, pb = synth.make_params(cfg, 60 + L, 0), synth.make_params(cfg, 60 + L, 1)
+    inp, other = synth.make_inputs(cfg, 61 + L), synth.make_inputs(cfg, 62 + L)
+    inp_b = {k: other[k] if k in own else v for k, v in inp.items()}
+    g = torch.Generator().manual_seed(63 + L)
+    h0 = (0.2 * torch.randn(2, 192, N, generator=g)).float()
+    tail0 = synth.round_io(torch.randn(2, 3, 192, generator=g), io)
+    ref, h_ref, t_ref = oracle.bimamba_block_fwd(cfg, to_np(pf), to_np(pb), to_np(inp), to_np(inp_b), h_in=h0.numpy(), tail_in=tail0.numpy())
+    desc = bd.make_desc(cfg, state_split=1, time_chunks=1)
+    dev_f, dev_o = bd.to_device(inp, cfg), bd.to_device(other, cfg)
+    dev_b = {k: dev_o[k] if k in own else v for k, v in dev_f.items()}
+    dh, dt = h0.cuda(), tail0.to(device="cuda", dtype=bd.io_dtype(cfg))
+    out, dpf, dpb, ws = bd.alloc_out(cfg), bd.to_device(pf), bd.to_device(pb), bd.alloc_workspace(desc, 1)
+    bd.bimamba_block_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dev_f), bd.make_inputs(dev_b), dh, dt, dh, dt,
+                         bd.make_tensor(out), ws)
+    torch.cuda.synchronize()
+    assert_close(out.float().cpu().numpy().reshape(ref.shape), ref, gpu.TOL[io])
+    assert rel_l2(dh.cpu().numpy(), h_ref) < 1e-5
+    assert np.array_equal(dt.float().cpu().numpy().astype(np.float64), t_ref)
