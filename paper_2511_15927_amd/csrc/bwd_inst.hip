@@ -3,6 +3,8 @@
 #include "bwd_kernels.h"
 #include "launch.h"
 
+#include <algorithm>
+
 namespace bm {
 
 bool bwd_supported(int d_state) { return d_state == 4 || d_state == 8 || d_state == 16; }
@@ -13,25 +15,34 @@ bool bwd_supported(int d_state) { return d_state == 4 || d_state == 8 || d_state
 // call at all adds the dh sums to the state pass, 0.3 of the walk's time a token.  Fitted on 44 calls of random size (1 to 32 x 128
 // to 8192 tokens of 512 to 4096 channels, 8 and 16 states, bf16 and fp32), each timed with up to 14 numbers of segments: the choice
 // costs 0.7 % more than the best one on average, 6 % at worst; a fixed eight waves per SIMD, at 32 tokens or more, 11 %.
+// That number of segments is the least there are, though: every token rounds the dh it hands on, so dDelta's error grows over a segment
+// (fp32, 4 x 2048 x 1024: 2.5e-7 against 64 bits with 32 tokens, 3.3e-7 with 64), and 3 % of the time, by the cost lines, buy its staying.
 void bwd_segments(int d_inner, int batch, int seqlen, int* nseg, int* seg_len, int* seg_chunks)
 {
     constexpr double kEnds = 15.0, kLastRound = 0.25, kDhSums = 0.3;
     constexpr int kMaxRounds = 16;                       // (the sums of a segment take workspace)
-    const long long per_segment = (long long)(((d_inner + 63) / 64 + 1) / 2) * (batch > 0 ? batch : 1);
+    constexpr int kLeastWavesPerSimd = 8, kLeastTokens = 32;
+    const int all = seqlen > 0 ? (seqlen + kBwdChunk - 1) / kBwdChunk : 1;
+    const long long tiles = (long long)((d_inner + 63) / 64), per_segment = (tiles + 1) / 2 * (batch > 0 ? batch : 1);
+    const long long waves = 2 * tiles * (batch > 0 ? batch : 1);
+    const long long fewest = std::clamp((4LL * cu_count() * kLeastWavesPerSimd + waves / 2) / waves, 1LL, std::max(1LL, (long long)seqlen / kLeastTokens));
+    const int longest = (int)((all + fewest - 1) / fewest);   // chunks
     auto rounds = [&](long long workgroups, int per_cu) {
         const long long resident = (long long)per_cu * cu_count();
         return 2 * workgroups <= resident ? 1.0 : (double)((workgroups + resident - 1) / resident) + kLastRound;
     };
-    const int all = seqlen > 0 ? (seqlen + kBwdChunk - 1) / kBwdChunk : 1;
-    int best = all;
-    double least = rounds(per_segment, 2) * all * kBwdChunk;
-    for (int n = 2; 2 * n <= all && n <= 65535 && n * per_segment <= 2LL * kMaxRounds * cu_count(); n++) {
-        const int chunks = (all + n - 1) / n;
-        if ((all + chunks - 1) / chunks != n) continue;   // as many segments of this length as a smaller n has
+    auto cost = [&](long long n, int chunks) {
         const double tokens = chunks * kBwdChunk;
-        const double cost = rounds(n * per_segment, 2) * (tokens + kEnds) + kDhSums * rounds(n * per_segment, 4) * tokens;
-        if (cost < least) {
-            least = cost;
+        if (n == 1) return rounds(per_segment, 2) * tokens;
+        return rounds(n * per_segment, 2) * (tokens + kEnds) + kDhSums * rounds(n * per_segment, 4) * tokens;
+    };
+    int best = longest;
+    double least = cost((all + longest - 1) / longest, longest);
+    for (long long n = fewest + 1; 2 * n <= all && n <= 65535 && n * per_segment <= 2LL * kMaxRounds * cu_count(); n++) {
+        const int chunks = (int)((all + n - 1) / n);
+        if ((all + chunks - 1) / chunks != n) continue;   // as many segments of this length as a smaller n has
+        if (const double c = cost(n, chunks); c < least) {
+            least = c;
             best = chunks;
         }
     }
