@@ -81,14 +81,15 @@ __device__ __forceinline__ float dsilu(float v)
 }
 __device__ __forceinline__ float sigmoidf(float v) { return __builtin_amdgcn_rcpf(1.0f + fast_exp2(-kLog2e * v)); }
 
-// Sums NV values per lane over the 64 lanes of the wave and leaves the total of value j in the lanes
+// Sums scale * v[j], NV values per lane, over the 64 lanes of the wave and leaves the total of value j in the lanes
 // j * (64 / NV) ... (j + 1) * (64 / NV) - 1 (returned by every lane: the total of value lane / (64 / NV)).
 // A reduce-scatter: each step halves the values a lane still carries.  The lane whose bit is clear keeps the first half
 // and receives its partner's first half, the other lane the second half, so about 2 NV instructions do the work of
 // 6 * NV adds.  Partners: the other 32-lane half and the other row of 16 by the swap instructions of gfx950, then inside a
 // row by lane-permute operands.  There both partners can form both sums, each an add with a permuted operand, and the
 // second one is written only where it is kept (bank masks pick lane groups of four): two instructions for a pair of
-// values where selecting first takes three.  (Inline assembly: the compiler does not form an add that keeps its old
+// values where selecting first takes three.  The products are formed after the first exchange, with both partners' scales at
+// hand: a multiplication and a multiply-add for a pair of values, not two multiplications and an add.  (Inline assembly: the compiler does not form an add that keeps its old
 // result in some banks.  s_nop 1: a permuted operand must not have been written by the two instructions before.)
 template <int CTRL>
 __device__ __forceinline__ float from_partner(float x)
@@ -96,14 +97,15 @@ __device__ __forceinline__ float from_partner(float x)
     return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), CTRL, 0xF, 0xF, true));
 }
 template <int NV>
-__device__ __forceinline__ float wave_reduce_scatter(float (&v)[NV])
+__device__ __forceinline__ float wave_reduce_scatter(float (&v)[NV], float scale)
 {
     static_assert(NV == 4 || NV == 8 || NV == 16, "4, 8 or 16 values per lane");
     // lane bit 5: the other half of the wave
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(scale), __float_as_uint(scale), false, false);
 #pragma unroll
     for (int i = 0; i < NV / 2; i++) {
         const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v[i]), __float_as_uint(v[NV / 2 + i]), false, false);
-        v[i] = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        v[i] = fmaf(__uint_as_float(r[1]), __uint_as_float(s[1]), __uint_as_float(r[0]) * __uint_as_float(s[0]));
     }
     // lane bit 4: the neighbouring row of 16
 #pragma unroll
@@ -683,8 +685,8 @@ struct BwdWalk {
             // this channel's terms of dC_t, summed over the wave's channels: value n in lanes n * kLanesPerState ...
             float terms[N];
 #pragma unroll
-            for (int n = 0; n < N; n++) terms[n] = dy * hs[i + 1][n];
-            float dc_total = wave_reduce_scatter<N>(terms);
+            for (int n = 0; n < N; n++) terms[n] = hs[i + 1][n];
+            float dc_total = wave_reduce_scatter<N>(terms, dy);
             settle(dc_total);
             // (formed again: kept from the forward half, a chunk's decays would take as many registers as its states)
             float dlt = delta[i];
@@ -695,7 +697,7 @@ struct BwdWalk {
             float dot[2] = {0.0f, 0.0f}, decay[2] = {0.0f, 0.0f};
             for_each_decay<N>(w, dlt, [&](int n, float an) {
                 dh[n] = fmaf(row[N + n], dy, dh[n]);
-                terms[n] = dh[n] * u;                                // of dB_t
+                terms[n] = dh[n];                                    // of dB_t, times u
                 dot[n & 1] = fmaf(dh[n], row[n], dot[n & 1]);
                 dh[n] *= an;
                 const float da = dh[n] * hs[i][n];                   // dh * a * h_prev
@@ -715,7 +717,7 @@ struct BwdWalk {
             settle(gD);
             {
                 // the two totals of a state side by side: the first half of its lanes has dB_t[n], the second dC_t[n]
-                const float db_total = wave_reduce_scatter<N>(terms);
+                const float db_total = wave_reduce_scatter<N>(terms, u);
                 const bool second = (w.lane & (kLanesPerState / 2)) != 0;
                 keep_narrow(lo_part);
                 if (there && w.exists && w.lane % (kLanesPerState / 2) == 0)
