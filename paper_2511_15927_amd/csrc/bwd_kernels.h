@@ -518,30 +518,30 @@ struct BwdWalk {
     __device__ __forceinline__ float delta_of(float raw) const { return sp ? softplus(raw + w.dtb) : raw; }
     __device__ __forceinline__ int inside(int j) const { return min(max(j, 0), a.L - 1); }
     __device__ __forceinline__ bool exists(int j) const { return j >= 0 && j < a.L; }
-    __device__ __forceinline__ bool moves(int j) const { return j >= 0 && j + 1 < a.L; }   // inside(j + 1) != inside(j)
 
     __device__ __forceinline__ void request(int k)
     {
-        // (positions outside the sequence repeat its nearest token: one stepped pointer per tensor, no second form of the
-        // loads, whose addresses the compiler would merge in vector registers)
+        // (positions outside the sequence repeat its nearest token; rows as offsets from the chunk's lowest one, which the load
+        // instruction adds: a scalar multiplication a row)
         const int first = w.j0 + k * CT;
         keep_narrow(lo_t);
-        const int sx = w.step(w.x), sd = w.step(w.dt), sz = w.step(w.z), sg = w.step(w.g);
-        const char *px = w.at(w.x, inside(first - 3)), *pd = w.at(w.dt, inside(first)), *pz = w.at(w.z, inside(first)),
-                   *pg = w.at(w.g, inside(first));
+        const int ja = inside(first - 3), jb = inside(first + CT - 1), low = w.dir > 0 ? ja : a.L - 1 - jb;
+        auto range_of = [&](const Walked& t) { return raw_range(t.base + (long long)low * t.stride); };
+        const Rsrc rx = range_of(w.x), rd = range_of(w.dt), rz = range_of(w.z), rg = range_of(w.g);
 #pragma unroll
-        for (int e = 0; e < 3; e++) {
-            xbefore[e] = *(const T*)(px + lo_t);
-            px += moves(first - 3 + e) ? sx : 0;
-        }
-#pragma unroll
-        for (int i = 0; i < CT; i++) {
-            xnext[i] = *(const T*)(px + lo_t);
-            dnext[i] = *(const T*)(pd + lo_t);
-            znext[i] = *(const T*)(pz + lo_t);
-            gnext[i] = *(const T*)(pg + lo_t);
-            const bool m = moves(first + i);
-            px += m ? sx : 0; pd += m ? sd : 0; pz += m ? sz : 0; pg += m ? sg : 0;
+        for (int e = 0; e < CT + 3; e++) {
+            const int j = inside(first - 3 + e);
+            const unsigned row = (unsigned)(w.dir > 0 ? j - ja : jb - j);
+            auto load = [&](const Rsrc& r, const Walked& t) { return IO::ld_raw(r, lo_t, (int)(row * (unsigned)t.stride)); };
+            if (e < 3) {
+                xbefore[e < 3 ? e : 0] = load(rx, w.x);
+            } else {
+                const int i = e >= 3 ? e - 3 : 0;
+                xnext[i] = load(rx, w.x);
+                dnext[i] = load(rd, w.dt);
+                znext[i] = load(rz, w.z);
+                gnext[i] = load(rg, w.g);
+            }
         }
         load_block<N>(a.state + w.place(a, a.seg_chunks, k) * (64 * N), hnext, w.lane);
         wnext = a.state_w[w.place(a, a.seg_chunks, k) * 64 + w.lane];
