@@ -319,12 +319,23 @@ __device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N
             }
         }
     };
-    auto add_to_d = [&](int n, float an, float dy, uniform_ro_ptr row) {
+    auto add_to_d = [&](int n, float an, float dy, float c) {
         const int i = WITH_D ? n : 0;
         pd[i] *= an;
-        ds[i] = fmaf(pd[i], dy * row[N + n], ds[i]);
+        ds[i] = fmaf(pd[i], dy * c, ds[i]);
+    };
+    // a token's B and C, requested as soon as the values of the token before have had their last use
+    // (8 x 8192 tokens of 4096 channels, the whole call 9.70 -> 9.50 ms, 4 x 771 x 1536 261 -> 257 us)
+    float row[WITH_D ? 2 * N : N];
+    auto request_row = [&](int j) {
+        uniform_ro_ptr from = (uniform_ro_ptr)w.at(w.row, inside(j));
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int n = 0; n < (WITH_D ? 2 * N : N); n++) row[n] = from[n];
+        __builtin_amdgcn_sched_barrier(0);
     };
     request(w.k0 * kSteps);
+    request_row(w.j0 + w.k0 * kBwdChunk);
     float* dst = a.state + w.place(a, a.seg_chunks, w.k0) * (64 * N);
     float* dst_w = a.state_w + w.place(a, a.seg_chunks, w.k0) * 64 + w.lane;
     for (int k = w.k0 * kSteps; k < w.k1 * kSteps; k++) {
@@ -367,14 +378,17 @@ __device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N
             xh[2] = xh[1]; xh[1] = xh[0]; xh[0] = x[i];
             wsum += delta[i];
             const float u = delta[i] * silu(pre);
-            uniform_ro_ptr row = (uniform_ro_ptr)w.at(w.row, inside(first + i));
             // (a segment that something precedes starts inside the sequence, k0 = 0, and its first three tokens are not in its window)
             const bool in_window = i >= 3 || k > 0;
             const float dy = WITH_D && in_window ? zg[WITH_D ? i : 0].second() * silu(zg[WITH_D ? i : 0].first()) : 0.0f;
             for_each_decay<N>(w, delta[i], [&](int n, float an) {
                 h[n] = fmaf(an, h[n], u * row[n]);
-                if constexpr (WITH_D) add_to_d(n, an, dy, row);
+                if constexpr (WITH_D) add_to_d(n, an, dy, row[WITH_D ? N + n : 0]);
             });
+            if constexpr (!WITH_D) {
+#pragma unroll
+                for (int n = 0; n < N; n++) settle(h[n]);
+            }
             if constexpr (WITH_D) {
 #pragma unroll
                 for (int n = 0; n < N; n++) {   // (a token at a time: more at once than the registers hold)
@@ -388,6 +402,7 @@ __device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N
                     for (int n = 0; n < N; n++) pd[n] = 1.0f;
                 }
             }
+            request_row(first + i + 1);
         }
     }
     if constexpr (WITH_D) {
@@ -397,9 +412,9 @@ __device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N
             if (sp) delta = softplus(delta + w.dtb);
             const float dg = w.valid ? IO::cvt(*(const T*)(w.at(w.g, j) + lo)) : 0.0f;
             const float dy = dg * silu(IO::cvt(*(const T*)(w.at(w.z, j) + lo)));
-            uniform_ro_ptr row = (uniform_ro_ptr)w.at(w.row, j);
+            uniform_ro_ptr c = (uniform_ro_ptr)w.at(w.row, j) + N;
             dsum += delta;
-            for_each_decay<N>(w, delta, [&](int n, float an) { add_to_d(n, an, dy, row); });
+            for_each_decay<N>(w, delta, [&](int n, float an) { add_to_d(n, an, dy, c[n]); });
         }
     }
     if (w.exists) {
