@@ -27,6 +27,7 @@
 namespace bm {
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
 typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4;
@@ -55,112 +56,167 @@ struct SsdPrepPair {
     SsdPrepArgs dir[2];   // forward, reverse: one launch prepares both
 };
 
-// (the wide form adds the partial score accumulators of the waves that share a block: [12][64][16] floats)
+// LDS of ssd_prep_kernel: the chunk's B and C rows after the conv, each value as a bf16 head and the bf16 rest of it.  (The wide
+// form adds the partial score accumulators of the waves that share a block: [12][64][16] floats.)
+constexpr int kPrepPad = 8;
 template <int N, int THREADS>
 constexpr size_t ssd_prep_lds_bytes()
 {
-    return 2 * (size_t)kQ * (N + 1) * sizeof(float) + (THREADS > 256 ? 12 * 64 * 16 * sizeof(float) : 0);
+    return 4 * (size_t)kQ * (N + kPrepPad) * sizeof(__bf16) + (THREADS > 256 ? 12 * 64 * 16 * sizeof(float) : 0);
 }
 
 // grid (nchunk, G, 2 * batch), block THREADS (256 or 1024), dynamic LDS ssd_prep_lds_bytes<N, THREADS>();
-// blockIdx.z / batch selects the direction.  Reads the raw B and C rows of one chunk
-// (plus the conv halo), applies the short conv + SiLU along the scan direction when they pass through it, and
-// keeps the fp32 result in LDS for the three outputs.  The wide form is for launches of few workgroups (block
-// calls, short sequences), whose duration is one workgroup's chain of phases: sixteen waves shorten every phase.
+// blockIdx.z / batch selects the direction.  Reads the raw B and C rows of one chunk (plus the conv halo), two columns a
+// thread, applies the short conv + SiLU along the scan direction when they pass through it, and leaves the result in LDS split the
+// way the score product takes it, so that every operand below is read in pieces of eight or sixteen bytes (fp32 columns, read
+// one by one and split by every wave that needs them: 61.4 us for 8 x 8192 tokens, N 128; this: 41.5; 1 x 1024 tokens, sixteen waves,
+// 9.3 -> 7.5).  B^T pieces of the wide
+// operand order are a column's consecutive positions: they go out from registers.  The wide form is for launches of few
+// workgroups (block calls, short sequences), whose duration is one workgroup's chain of phases: sixteen waves shorten every phase.
 template <int N, int THREADS = 256>
 __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair both)
 {
     static_assert(THREADS == 256 || THREADS == 1024, "four or sixteen waves");
     using T = unsigned short;
+    constexpr int kRow = N + kPrepPad;
     const int batch = gridDim.z / 2;
     const SsdPrepArgs& a = both.dir[blockIdx.z / batch];
     extern __shared__ __attribute__((aligned(16))) unsigned char ssd_prep_lds[];
-    float(*sB)[N + 1] = reinterpret_cast<float(*)[N + 1]>(ssd_prep_lds);
-    float(*sC)[N + 1] = sB + kQ;
+    __bf16(*const split)[kQ][kRow] = reinterpret_cast<__bf16(*)[kQ][kRow]>(ssd_prep_lds);   // B head, B rest, C head, C rest
     const int c = blockIdx.x, g = blockIdx.y, b = blockIdx.z % batch, tid = threadIdx.x;
     const int nchunk = gridDim.x;
-    {
-        constexpr int kCols = 2 * N, kParts = THREADS / kCols, kLen = kQ / kParts;
-        const int col = tid % kCols, seg = tid / kCols;   // one column of B|C, positions seg*kLen .. of the chunk
-        const int which = col / N, n = col % N;
-        const TensorArg& src = which ? a.C : a.B;
-        const T* base = (const T*)src.p + (size_t)b * src.sb + g * N + n;
-        const int last = a.L - 1;
-        const int row = a.Dn + which * a.G * N + g * N + n;   // this column's conv channel
-        float w4[4] = {0.0f, 0.0f, 0.0f, 0.0f}, bias = 0.0f;   // w4[3] on the current position
-        if (a.conv_bc) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) w4[3 - i] = i < a.K ? a.conv_w[(size_t)row * a.K + (a.K - 1 - i)] : 0.0f;
-            bias = a.conv_b ? a.conv_b[row] : 0.0f;
-        }
-        const int tau0 = c * kQ + seg * kLen - 3;
-        T raw[kLen + 3];
-#pragma unroll
-        for (int q = 0; q < kLen + 3; q++) {
-            const int tau = min(max(tau0 + q, 0), last);
-            raw[q] = base[(long long)(a.dir > 0 ? tau : last - tau) * src.st];
-        }
-        float xr[kLen + 3];
-#pragma unroll
-        for (int q = 0; q < kLen + 3; q++) xr[q] = (tau0 + q >= 0 && tau0 + q <= last) ? IoBF16::cvt(raw[q]) : 0.0f;
-        if (c == 0 && seg == 0 && a.dir > 0 && a.tail_in && a.conv_bc && a.K > 1) {
-            // requested together from clamped rows (a tap beyond the conv width has a zero weight)
-            T cached[3];
-#pragma unroll
-            for (int q = 0; q < 3; q++)   // 3 - q tokens before the block
-                cached[q] = ((const T*)a.tail_in)[((size_t)b * (a.K - 1) + max(a.K - 1 - (3 - q), 0)) * a.tail_ch + row];
-#pragma unroll
-            for (int q = 0; q < 3; q++)
-                if (3 - q <= a.K - 1) xr[q] = IoBF16::cvt(cached[q]);
-        }
-        float(*dstm)[N + 1] = which ? sC : sB;
-#pragma unroll
-        for (int i = 0; i < kLen; i++) {
-            float v = xr[i + 3];
-            if (a.conv_bc) {
-                float pre = bias;
-                pre = fmaf(w4[0], xr[i], pre);
-                pre = fmaf(w4[1], xr[i + 1], pre);
-                pre = fmaf(w4[2], xr[i + 2], pre);
-                pre = fmaf(w4[3], xr[i + 3], pre);
-                v = silu(pre);
-            }
-            if (tau0 + 3 + i > last) v = 0.0f;
-            dstm[seg * kLen + i][n] = v;
-        }
-    }
-    __syncthreads();
     const size_t Lpad = (size_t)nchunk * kQ;
     const size_t tile = ((size_t)b * nchunk + c) * a.G + g;
+    constexpr int kParts = THREADS / N, kLen = kQ / kParts;   // positions of a thread
+    constexpr bool kFromRegisters = kLen >= 8;
+    {
+        const int seg = __builtin_amdgcn_readfirstlane(tid / N), n = 2 * (tid % (N / 2));   // columns n, n + 1 of B or C
+        int which = tid % N / (N / 2);
+        if constexpr (N == 128) which = __builtin_amdgcn_readfirstlane(which);   // rows at wave-uniform addresses
+        const TensorArg& src = which ? a.C : a.B;
+        const T* const base = (const T*)src.p + (size_t)b * src.sb + g * N;
+        const int last = a.L - 1;
+        const int row = a.Dn + which * a.G * N + g * N + n;   // the first column's conv channel
+        const int tau0 = c * kQ + seg * kLen - 3;
+        bf16_pair raw[kLen + 3];
+        {   // (positions outside the sequence repeat its nearest row)
+            const int first = min(max(tau0, 0), last);
+            const T* at = base + (long long)(a.dir > 0 ? first : last - first) * src.st;
+            const long long step = a.dir > 0 ? src.st : -src.st;
+#pragma unroll
+            for (int q = 0; q < kLen + 3; q++) {
+                raw[q] = *(const bf16_pair*)(at + n);
+                at += (tau0 + q >= 0) & (tau0 + q < last) ? step : 0;
+            }
+        }
+        const bool from_tail = c == 0 && seg == 0 && a.dir > 0 && a.tail_in && a.conv_bc && a.K > 1;
+        if (from_tail) {
+            // requested together from clamped rows (a tap beyond the conv width has a zero weight)
+#pragma unroll
+            for (int q = 0; q < 3; q++)   // 3 - q tokens before the block
+                raw[q] = *(const bf16_pair*)((const T*)a.tail_in + ((size_t)b * (a.K - 1) + max(a.K - 1 - (3 - q), 0)) * a.tail_ch + row);
+        }
+        float w4[2][4], bias[2] = {0.0f, 0.0f};   // w4[.][3] on the current position
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+#pragma unroll
+            for (int i = 0; i < 4; i++) w4[q][i] = 0.0f;
+        if (a.conv_bc) {
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                const float* const taps = a.conv_w + (size_t)(row + q) * a.K;
+                if (a.K == 4) {   // a column's taps in one load: sixteen waves asking tap by tap are what the small form waits for
+                    typedef __attribute__((__vector_size__(16), __aligned__(4))) float taps4;
+                    const taps4 v = *(const taps4*)taps;
+#pragma unroll
+                    for (int i = 0; i < 4; i++) w4[q][i] = v[i];
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 3; i++) w4[q][3 - i] = taps[max(a.K - 1 - i, 0)];
+                }
+            }
+            if (a.conv_b) {
+                const float2 v = make_float2(a.conv_b[row], a.conv_b[row + 1]);
+                bias[0] = v.x;
+                bias[1] = v.y;
+            }
+        }
+        // positions before the sequence (or the cached tail) and past its end are zeros
+        const int front = from_tail ? 4 - a.K : max(-tau0, 0), end = last - tau0;
+#pragma unroll
+        for (int q = 0; q < kLen + 3; q++) raw[q] = (q >= 3 || q >= front) & (q <= end) ? raw[q] : 0u;
+        auto column = [&](int q, int k) -> float { return __uint_as_float(k ? raw[q] & 0xffff0000u : raw[q] << 16); };
+#pragma unroll
+        for (int q = 0; q < 2; q++)
+#pragma unroll
+            for (int i = 1; i < 4; i++) w4[q][3 - i] = i < a.K ? w4[q][3 - i] : 0.0f;
+        bf16x8 piece[2];
+        auto rows = [&](auto conv) {
+#pragma unroll
+            for (int i = 0; i < kLen; i++) {
+                __bf16 head[2], rest[2];
+#pragma unroll
+                for (int k = 0; k < 2; k++) {
+                    float v = column(i + 3, k);
+                    if constexpr (decltype(conv)::value) {
+                        float pre = bias[k];
+                        pre = fmaf(w4[k][0], column(i, k), pre);
+                        pre = fmaf(w4[k][1], column(i + 1, k), pre);
+                        pre = fmaf(w4[k][2], column(i + 2, k), pre);
+                        pre = fmaf(w4[k][3], column(i + 3, k), pre);
+                        v = silu(pre);
+                    }
+                    v = i + 3 <= end ? v : 0.0f;
+                    head[k] = (__bf16)v;
+                    rest[k] = (__bf16)(v - (float)head[k]);
+                    if constexpr (kFromRegisters) piece[k][i % 8] = head[k];
+                }
+                const int r = seg * kLen + i;
+                *reinterpret_cast<bf16x2*>(&split[2 * which][r][n]) = bf16x2{head[0], head[1]};
+                *reinterpret_cast<bf16x2*>(&split[2 * which + 1][r][n]) = bf16x2{rest[0], rest[1]};
+                if constexpr (kFromRegisters) {
+                    if (i % 8 == 7 && a.wide && which == 0) {
+                        // B^T as [32 states][16 positions][lane]: lane l holds state l%32, positions 8 (l/32) .. + 7
+                        const int j0 = r - 7;
+#pragma unroll
+                        for (int k = 0; k < 2; k++) {
+                            const int idx = ((n / 32) * 4 + j0 / 16) * 64 + (j0 / 8) % 2 * 32 + n % 32 + k;
+                            *reinterpret_cast<bf16x8*>(&a.b_t[(tile * kQ * N / 8 + idx) * 8]) = piece[k];
+                        }
+                    }
+                }
+            }
+        };
+        if (a.conv_bc) rows(std::true_type{});
+        else rows(std::false_type{});
+    }
+    __syncthreads();
+    auto b_column = [&](int n, int j0) {   // eight positions of a state
+        bf16x8 v;
+#pragma unroll
+        for (int e = 0; e < 8; e++) v[e] = split[0][j0 + e][n];
+        return v;
+    };
     if (a.wide) {
-        // operand tiles of ssd_wide_kernel, one 16-byte piece per lane of an MFMA operand: C as [row block of 16][32
-        // states][lane] with the states in the order the state's accumulators publish them, B^T as [32 states][16 positions][lane]
+        // C as [row block of 16][32 states][lane of an MFMA operand], with the states in the order the state's accumulators publish them
         for (int idx = tid; idx < kQ * N / 8; idx += THREADS) {
             const int ln = idx % 64, f = idx / 64;
             const int i = (f / (N / 32)) * 16 + ln % 16, n0 = (f % (N / 32)) * 32 + 16 * ((ln / 16) % 2) + 4 * (ln / 32);
-            const int n2 = (f / 4) * 32 + ln % 32, j0 = (f % 4) * 16 + 8 * (ln / 32);
-            bf16x8 cv, bv;
-#pragma unroll
-            for (int e = 0; e < 8; e++) {
-                cv[e] = (__bf16)sC[i][n0 + 8 * (e / 4) + e % 4];
-                bv[e] = (__bf16)sB[j0 + e][n2];
+            const bf16x4 lo = *reinterpret_cast<const bf16x4*>(&split[2][i][n0]), hi = *reinterpret_cast<const bf16x4*>(&split[2][i][n0 + 8]);
+            *reinterpret_cast<bf16x8*>(&a.c_rows[(tile * kQ * N / 8 + idx) * 8]) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            if constexpr (!kFromRegisters) {
+                const int n2 = (f / 4) * 32 + ln % 32, j0 = (f % 4) * 16 + 8 * (ln / 32);
+                *reinterpret_cast<bf16x8*>(&a.b_t[(tile * kQ * N / 8 + idx) * 8]) = b_column(n2, j0);
             }
-            *reinterpret_cast<bf16x8*>(&a.c_rows[(tile * kQ * N / 8 + idx) * 8]) = cv;
-            *reinterpret_cast<bf16x8*>(&a.b_t[(tile * kQ * N / 8 + idx) * 8]) = bv;
         }
     } else
     // bf16 C rows and the transposed bf16 B tile, written as 16-byte pieces (8 states of a row, 8 positions of a state)
     for (int idx = tid; idx < kQ * N / 8; idx += THREADS) {
         const int j = idx / (N / 8), n8 = idx % (N / 8);
         const int n2 = idx / (kQ / 8), j8 = idx % (kQ / 8);
-        bf16x8 cv, bv;
-#pragma unroll
-        for (int e = 0; e < 8; e++) {
-            cv[e] = (__bf16)sC[j][8 * n8 + e];
-            bv[e] = (__bf16)sB[8 * j8 + e][n2];
-        }
-        *reinterpret_cast<bf16x8*>(&a.c_rows[(((size_t)b * Lpad + c * kQ + j) * a.G + g) * N + 8 * n8]) = cv;
-        *reinterpret_cast<bf16x8*>(&a.b_t[((((size_t)b * nchunk + c) * a.G + g) * N + n2) * kQ + 8 * j8]) = bv;
+        *reinterpret_cast<bf16x8*>(&a.c_rows[(((size_t)b * Lpad + c * kQ + j) * a.G + g) * N + 8 * n8]) =
+            *reinterpret_cast<const bf16x8*>(&split[2][j][8 * n8]);
+        *reinterpret_cast<bf16x8*>(&a.b_t[((((size_t)b * nchunk + c) * a.G + g) * N + n2) * kQ + 8 * j8]) = b_column(n2, 8 * j8);
     }
     // Score tile B_j . C_i on the matrix cores, one 32 x 32 block per wave; only the three blocks on or below the
     // diagonal are kept.  Each fp32 operand is split into a bf16 head and a bf16 remainder and the three significant
@@ -178,22 +234,16 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
         const int iblk = blk > 0, jblk = blk > 1;
         const int rj = jblk * 32 + lane % 32, ri = iblk * 32 + lane % 32, koff = 8 * (lane / 32);
         for (int ks = kpart * kSteps; ks < (kpart + 1) * kSteps; ks++) {
-            bf16x8 ah, al, bh, bl;
-#pragma unroll
-            for (int e = 0; e < 8; e++) {
-                const float bv = sB[rj][16 * ks + koff + e], cv = sC[ri][16 * ks + koff + e];
-                ah[e] = (__bf16)bv;
-                al[e] = (__bf16)(bv - (float)ah[e]);
-                bh[e] = (__bf16)cv;
-                bl[e] = (__bf16)(cv - (float)bh[e]);
-            }
+            const int k0 = 16 * ks + koff;
+            const bf16x8 ah = *reinterpret_cast<const bf16x8*>(&split[0][rj][k0]), al = *reinterpret_cast<const bf16x8*>(&split[1][rj][k0]);
+            const bf16x8 bh = *reinterpret_cast<const bf16x8*>(&split[2][ri][k0]), bl = *reinterpret_cast<const bf16x8*>(&split[3][ri][k0]);
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
         }
     }
     if constexpr (kSplit > 1) {
-        float* const sums = reinterpret_cast<float*>(sC + kQ);   // [12][64][16]
+        float* const sums = reinterpret_cast<float*>(split + 4);   // [12][64][16]
         if (blk < 3 && kpart > 0) {
 #pragma unroll
             for (int q = 0; q < 4; q++)
