@@ -188,8 +188,7 @@ __global__ __launch_bounds__(64 * kRowMaxWaves, 1) void row_kernel(const RowArgs
         else if (tail && j >= -(a.K - 1)) before = IO::cvt(from_tail);
     }
     float w4[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++) w4[3 - i] = i < a.K ? da.conv_w[(size_t)ch * a.K + (a.K - 1 - i)] : 0.0f;
+    load_taps(da.conv_w + (size_t)ch * a.K, a.K, w4);
     const float cb = da.conv_b ? da.conv_b[ch] : 0.0f;
     const float dval = da.D[a.d_per_head ? head : ch];
     const float dtb = (a.dt_softplus && da.dt_bias) ? da.dt_bias[head] : 0.0f;

@@ -115,8 +115,7 @@ __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
         if (two_sets) stage_set(1, 1);
     }
     float w4[4], h[N], a2[AKIND == kAPerState ? N : 1], d2 = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 4; i++) w4[3 - i] = i < a.K ? da.conv_w[(size_t)ch * a.K + (a.K - 1 - i)] : 0.0f;
+    load_taps(da.conv_w + (size_t)ch * a.K, a.K, w4);
     const float cb = da.conv_b ? da.conv_b[ch] : 0.0f;
     const float dval = da.D[a.d_per_head ? head : ch];
     const float dtb = (a.dt_softplus && da.dt_bias) ? da.dt_bias[head] : 0.0f;

@@ -79,8 +79,7 @@ __global__ __launch_bounds__(1024) void ssd_block_prep_kernel(const SsdBlockArgs
         for (int q = 0; q < kLen + 3; q++) raw[q] = base[(long long)min(max(t0 + q, 0), last) * src.st];
         float w4[4] = {0.0f, 0.0f, 0.0f, 0.0f}, bias = 0.0f;   // w4[3] on the current position
         if (a.conv_bc) {
-#pragma unroll
-            for (int i = 0; i < 4; i++) w4[3 - i] = i < a.K ? d.conv_w[(size_t)row * a.K + (a.K - 1 - i)] : 0.0f;
+            load_taps(d.conv_w + (size_t)row * a.K, a.K, w4);
             bias = d.conv_b ? d.conv_b[row] : 0.0f;
         }
         float xr[kLen + 3];
@@ -292,18 +291,7 @@ __global__ __launch_bounds__(256, BLOCKS == 1 ? 4 : COMMIT ? 2 : 3) void ssd_blo
 #pragma unroll
     for (int s = 0; s < 2; s++) {
         const SsdBlockDir& d = a.dir[s];
-        if (a.K == 4) {
-            typedef float __attribute__((ext_vector_type(4), aligned(4))) Taps;
-            const Taps w = *reinterpret_cast<const Taps*>(d.conv_w + (size_t)ch * 4);
-#pragma unroll
-            for (int i = 0; i < 4; i++) w4[s][i] = w[i];
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const float w = d.conv_w[(size_t)ch * a.K + max(a.K - 1 - i, 0)];
-                w4[s][3 - i] = i < a.K ? w : 0.0f;
-            }
-        }
+        load_taps(d.conv_w + (size_t)ch * a.K, a.K, w4[s]);
         cb[s] = d.conv_b ? d.conv_b[ch] : 0.0f;
         dval[s] = d.D[a.d_per_head ? head : ch];
     }

@@ -70,9 +70,8 @@ constexpr size_t ssd_prep_lds_bytes()
 // thread, applies the short conv + SiLU along the scan direction when they pass through it, and leaves the result in LDS split the
 // way the score product takes it, so that every operand below is read in pieces of eight or sixteen bytes (fp32 columns, read
 // one by one and split by every wave that needs them: 61.4 us for 8 x 8192 tokens, N 128; this: 41.5; 1 x 1024 tokens, sixteen waves,
-// 9.3 -> 7.5).  B^T pieces of the wide
-// operand order are a column's consecutive positions: they go out from registers.  The wide form is for launches of few
-// workgroups (block calls, short sequences), whose duration is one workgroup's chain of phases: sixteen waves shorten every phase.
+// 9.3 -> 7.5).  B^T pieces of the wide operand order are a column's consecutive positions: they go out from registers.  The form
+// of sixteen waves is for launches of few workgroups (short sequences), whose duration is one workgroup's chain of phases.
 template <int N, int THREADS = 256>
 __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair both)
 {
@@ -123,22 +122,10 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
             for (int i = 0; i < 4; i++) w4[q][i] = 0.0f;
         if (a.conv_bc) {
 #pragma unroll
-            for (int q = 0; q < 2; q++) {
-                const float* const taps = a.conv_w + (size_t)(row + q) * a.K;
-                if (a.K == 4) {   // a column's taps in one load: sixteen waves asking tap by tap are what the small form waits for
-                    typedef __attribute__((__vector_size__(16), __aligned__(4))) float taps4;
-                    const taps4 v = *(const taps4*)taps;
-#pragma unroll
-                    for (int i = 0; i < 4; i++) w4[q][i] = v[i];
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 3; i++) w4[q][3 - i] = taps[max(a.K - 1 - i, 0)];
-                }
-            }
+            for (int q = 0; q < 2; q++) load_taps(a.conv_w + (size_t)(row + q) * a.K, a.K, w4[q]);
             if (a.conv_b) {
-                const float2 v = make_float2(a.conv_b[row], a.conv_b[row + 1]);
-                bias[0] = v.x;
-                bias[1] = v.y;
+                bias[0] = a.conv_b[row];
+                bias[1] = a.conv_b[row + 1];
             }
         }
         // positions before the sequence (or the cached tail) and past its end are zeros
@@ -146,10 +133,6 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
 #pragma unroll
         for (int q = 0; q < kLen + 3; q++) raw[q] = (q >= 3 || q >= front) & (q <= end) ? raw[q] : 0u;
         auto column = [&](int q, int k) -> float { return __uint_as_float(k ? raw[q] & 0xffff0000u : raw[q] << 16); };
-#pragma unroll
-        for (int q = 0; q < 2; q++)
-#pragma unroll
-            for (int i = 1; i < 4; i++) w4[q][3 - i] = i < a.K ? w4[q][3 - i] : 0.0f;
         bf16x8 piece[2];
         auto rows = [&](auto conv) {
 #pragma unroll

@@ -107,8 +107,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
 #pragma unroll
             for (int h2 = 0; h2 < 2; h2++) {
                 const int ch = ch0 + hd * P + 2 * cp + h2;
-#pragma unroll
-                for (int i = 0; i < 4; i++) w4[hd][h2][3 - i] = i < a.K ? a.conv_w[(size_t)ch * a.K + (a.K - 1 - i)] : 0.0f;
+                load_taps(a.conv_w + (size_t)ch * a.K, a.K, w4[hd][h2]);
                 cbias[hd][h2] = a.conv_b ? a.conv_b[ch] : 0.0f;
             }
         const T* xb = (const T*)a.x.p + (size_t)b * a.x.sb + ch0 + 2 * cp;

@@ -96,11 +96,7 @@ __global__ __launch_bounds__(64 * kRowMaxWaves, 1) void stack_kernel(const Stack
     const unsigned state_at = ((unsigned)b * a.Dn + ch) * a.N + min(n, a.N - 1);
     auto request = [&](const Places& p) {
         Layer v;
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const float w = p.conv_w[conv_at + max(a.K - 1 - i, 0)];
-            v.w4[3 - i] = i < a.K ? w : 0.0f;
-        }
+        load_taps(p.conv_w + conv_at, a.K, v.w4);
         v.cb = v.dtb = v.h = 0.0f;
         v.tail = 0;
         v.dval = p.D[skip_at];
