@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 from paper_2511_15927_amd import binding as bd
 from paper_2511_15927_amd import synth
@@ -212,3 +213,28 @@ def test_status_strings():
     for code in range(0, -9, -1):
         assert lib.bimamba_status_string(code).decode() not in ("", "unknown status")
     assert lib.bimamba_status_string(-99).decode() == "unknown status"
+
+
+@pytest.mark.parametrize("kind", ["same", "strided", "other_dtype", "own", "grad"])
+def test_step_inputs_refreshed_together_or_one_by_one(kind):
+    """A step's tensors are refreshed in one go where they are of the buffer's kind, one by one otherwise: the same values at odd sizes."""
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    cfg = synth.mixer_cfg(2, 3, 5, d_state=4)
+    layer = (synth.make_params(cfg, 1, 0), synth.make_params(cfg, 1, 1))
+    loop = BlockDecodeLoop(cfg, [layer], 2, device="cpu")
+    want = {k: v.to(torch.bfloat16) for k, v in synth.make_inputs(cfg, 3).items()}
+    given = dict(want)
+    if kind == "strided":
+        given["x"] = want["x"].transpose(0, 1).contiguous().transpose(0, 1)
+    elif kind == "other_dtype":
+        given["z"] = want["z"].float()
+    elif kind == "own":
+        loop.set_step_inputs(0, want)
+        given = dict(loop.step_inputs[0])
+    elif kind == "grad":
+        given["dt"] = want["dt"].clone().requires_grad_()
+    with torch.no_grad():
+        loop.set_step_inputs(0, given)
+    for k, v in want.items():
+        assert torch.equal(loop.step_inputs[0][k], v.reshape(loop.step_inputs[0][k].shape)), k
+    assert all(t.count_nonzero() == 0 for t in loop.step_inputs[1].values())
