@@ -17,16 +17,16 @@ static void prep_variant(const SsdPrepPair& pa, int nchunk, int batch, hipStream
     hipLaunchKernelGGL(kernel, dim3((unsigned)nchunk, (unsigned)pa.dir[0].G, 2u * (unsigned)batch), dim3(THREADS), lds, st, pa);
 }
 
-template <int N, int P, bool SINGLE, int GROUPS, bool PARTS>
+template <int N, int P, bool PARTS>
 static void scan_variant(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     static std::atomic<bool> seen[kMaxSeenDevices];
-    constexpr size_t lds = SsdLds<N, P, SINGLE>::bytes();
-    auto kernel = ssd_kernel<N, P, SINGLE, GROUPS, PARTS>;
+    constexpr size_t lds = SsdLds<N, P>::bytes();
+    auto kernel = ssd_kernel<N, P, PARTS>;
     if (first_use_on_current_device(seen))
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     const unsigned parts = !PARTS ? 1u : (unsigned)sp.dir[0].parts;   // blockIdx.y is the time part of a direction
-    hipLaunchKernelGGL(kernel, dim3((unsigned)sp.dir[0].H, parts * (unsigned)dirs, (unsigned)batch), dim3(4 * P + 256 * GROUPS), lds, st, sp);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)sp.dir[0].H, parts * (unsigned)dirs, (unsigned)batch), dim3(4 * P + 256), lds, st, sp);
 }
 
 template <int N, int P>
@@ -38,17 +38,13 @@ static void launch_ssd_wide(const SsdStatePair& sp, int dirs, int batch, hipStre
     else launch_ssd_wide_n64_p32(sp, dirs, batch, st);
 }
 
-// Long calls that leave at least half of the CUs empty (batch 1 or 2) split the producers into two groups, which
-// shortens the per-chunk chain of each workgroup (-4 to -9 %); with the chip full the extra waves only compete for
-// issue slots (+4 to +7 %), so those keep one group.  (Calls of a single chunk go to launch_ssd_duo.)
 template <int N, int P>
 static void scan_one(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     const SsdArgs& sa = sp.dir[0];
     if (sa.wide) launch_ssd_wide<N, P>(sp, dirs, batch, st);
-    else if (sa.parts > 1) scan_variant<N, P, false, 1, true>(sp, dirs, batch, st);
-    else if (2LL * dirs * sa.H * batch <= cu_count()) scan_variant<N, P, false, 2, false>(sp, dirs, batch, st);
-    else scan_variant<N, P, false, 1, false>(sp, dirs, batch, st);
+    else if (sa.parts > 1) scan_variant<N, P, true>(sp, dirs, batch, st);
+    else scan_variant<N, P, false>(sp, dirs, batch, st);
 }
 
 bool ssd_supported(int d_state, int headdim) { return (d_state == 64 || d_state == 128) && (headdim == 32 || headdim == 64); }
@@ -86,8 +82,8 @@ void launch_ssd_state(int d_state, int headdim, const SsdStatePair& sp, int subs
 }
 
 // dirs 1: the direction sp.dir[0]; dirs 2: both in one launch, for calls whose directions write halves of their own.  A
-// workgroup holds a CU (158 KB of LDS) and a call's time is its longest chain of chunks, so two launches that each leave
-// CUs empty take twice as long as one: 120 heads x 32, N 128, 1 x 1024 tokens 72.2 -> 38.1 us a call.
+// workgroup holds a CU and a call's time is its longest chain of chunks, so two launches that each leave CUs empty take
+// twice as long as one: 120 heads x 32, N 128, 1 x 1024 tokens 72.2 -> 38.1 us a call.
 void launch_ssd_scan(int d_state, int headdim, const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     if (d_state == 128 && headdim == 64) scan_one<128, 64>(sp, dirs, batch, st);

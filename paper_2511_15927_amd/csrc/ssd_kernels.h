@@ -11,9 +11,9 @@
 // score tile C B^T, the bf16 C rows and the transposed bf16 B tile.
 //
 // Kernels in this file: ssd_prep_kernel (above); ssd_kernel, the chunk walk of one direction (ssd_walk), with
-// variants for two producer groups and for time parts; ssd_state_kernel and ssd_carry_kernel, which find the state
-// entering each time part when a call has too few (batch, head) items to fill the chip; ssd_duo_kernel, both
-// directions of a single-chunk call (a block-diffusion step) in one workgroup.
+// a variant for time parts; ssd_state_kernel and ssd_carry_kernel, which find the state
+// entering each time part when a call has too few (batch, head) items to fill the chip.  Calls of one chunk run on ssd_block.h,
+// whole calls of several on ssd_wide.h; the walk here is for time parts and for rows too far apart for 32-bit offsets.
 //
 // Lane layouts of the 32x32x16 MFMA (checked on hardware): operand A lane l holds row l%32, k = 8*(l/32)..+7;
 // operand B lane l holds column l%32, same k; accumulator register r of lane l is row 8*(r/4) + 4*(l/32) + r%4,
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
 #pragma unroll
             for (int q = 0; q < kLen + 3; q++) {
                 raw[q] = *(const bf16_pair*)(at + n);
-                at += (tau0 + q >= 0) & (tau0 + q < last) ? step : 0;
+                at += ((tau0 + q >= 0) & (tau0 + q < last)) ? step : 0;
             }
         }
         const bool from_tail = c == 0 && seg == 0 && a.dir > 0 && a.tail_in && a.conv_bc && a.K > 1;
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
         // positions before the sequence (or the cached tail) and past its end are zeros
         const int front = from_tail ? 4 - a.K : max(-tau0, 0), end = last - tau0;
 #pragma unroll
-        for (int q = 0; q < kLen + 3; q++) raw[q] = (q >= 3 || q >= front) & (q <= end) ? raw[q] : 0u;
+        for (int q = 0; q < kLen + 3; q++) raw[q] = ((q >= 3 || q >= front) & (q <= end)) ? raw[q] : 0u;
         auto column = [&](int q, int k) -> float { return __uint_as_float(k ? raw[q] & 0xffff0000u : raw[q] << 16); };
         bf16x8 piece[2];
         auto rows = [&](auto conv) {
@@ -324,10 +324,8 @@ __global__ __launch_bounds__(256) void ssd_carry_kernel(const SsdCarryArgs a)
 }
 
 // LDS of ssd_kernel: two buffers of per-chunk tiles (filled by the producer waves one chunk ahead of the consumer
-// waves) and two copies of the state in MFMA operand form.  SINGLE (calls of one chunk, i.e. block-diffusion steps):
-// one of each and one set of scan tables shared by the producer waves (they all write the same values), which brings
-// the workgroup under half a CU's LDS so that two workgroups overlap their load-compute-store chains on a CU.
-template <int N, int P, bool SINGLE = false>
+// waves) and two copies of the state in MFMA operand form.
+template <int N, int P>
 struct SsdLds {
     static constexpr int kRowC = N + kPadK, kRowT = kQ + kPadK;
     static constexpr int kC = kQ * kRowC;    // C rows of the chunk               [kQ][kRowC] bf16
@@ -337,8 +335,8 @@ struct SsdLds {
     static constexpr int kTileElems = kC + kBT + 2 * kX + kM;
     static constexpr int kHT = (N / 32) * (P / 32) * 2 * 64 * 8;   // state operand copy, bf16
     static constexpr int kProducerWaves = 4;
-    static constexpr int kBufs = SINGLE ? 1 : 2;
-    static constexpr int kScanTables = SINGLE ? 1 : kProducerWaves;
+    static constexpr int kBufs = 2;
+    static constexpr int kScanTables = kProducerWaves;
     // + exp(l_i) per buffer, + per scan table: cumulative log2 decay, Delta, end-of-chunk weight of each position
     static constexpr size_t bytes() { return (size_t)(kBufs * kTileElems + kBufs * kHT) * sizeof(__bf16) + (kBufs + 3 * kScanTables) * kQ * sizeof(float); }
 };
@@ -579,38 +577,13 @@ __global__ __launch_bounds__(256, 4) void ssd_state_kernel(const SsdStatePair bo
 // chunk ahead they compute Delta and the cumulative decay, build the masked decayed score operand, run conv + SiLU,
 // and stage the C / B^T tiles, with the global loads of the chunk after that already in flight.  One LDS barrier per
 // chunk.  (The producers' per-head work does not shrink with the head width, so their count does not either.)
-// Block: 4*P + 256*PG threads.
-// PG = 2 splits the producers into two groups of four waves: one builds the score operand and stages the tiles, the
-// other runs conv + SiLU (both run the short scan for themselves).  A producer wave's chain of dependent stages per
-// chunk is then about half as long, which is what sets the chunk period of long calls; the CU holds twelve waves.
+// Block: 4*P + 256 threads.
 // PARTS compiles the time parts in (chunk range and entry state per time_part); without it the kernel walks every
 // chunk of its item and carries none of that bookkeeping through its loops.
-// DUO (single-chunk calls only): both directions of a (batch, head) item in one workgroup, see ssd_duo_kernel.
-// kDuoFirst is the direction that would park its result in global memory: it leaves it in LDS, one row per token.
-// kDuoSecond is the direction that would read the parked result back: it takes it from `parked`, which its caller
-// filled from LDS (register r: token i0 + row_k(r) of the thread's channel).
-enum { kDuoNone = 0, kDuoFirst = 1, kDuoSecond = 2 };
-
-// Where the first direction of a pair leaves its [kQ][P] fp32 result for the second: over the state operand copy
-// when that is large enough (the first direction starts from a zero state and never reads it), else behind the
-// scan tables.
-template <int N, int P>
-struct SsdDuoLds {
-    using Lds = SsdLds<N, P, true>;
-    static constexpr size_t kParkBytes = (size_t)kQ * P * sizeof(float);
-    static constexpr bool kParkOverState = (size_t)Lds::kHT * sizeof(__bf16) >= kParkBytes;
-    static constexpr size_t bytes() { return Lds::bytes() + (kParkOverState ? 0 : kParkBytes); }
-};
-
-template <int N, int P, bool SINGLE, int PG, bool PARTS, int DUO>
-__device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, float (&parked)[16])
+template <int N, int P, bool PARTS>
+__device__ __forceinline__ void ssd_walk(const SsdArgs& a, int time_part)
 {
-    static_assert(PG == 1 || (PG == 2 && !SINGLE), "one or two producer groups; the single-chunk form keeps one");
-    static_assert(!PARTS || (!SINGLE && PG == 1), "time parts come with one producer group and more than one chunk");
-    static_assert(DUO == kDuoNone || SINGLE, "both directions in one workgroup: single-chunk calls only");
-    using Lds = SsdLds<N, P, SINGLE>;
-    SsdArgs a = a_in;
-    if (SINGLE) a.nchunk = 1;   // known at compile time: the chunk pipeline below folds away
+    using Lds = SsdLds<N, P>;
     constexpr int kPB = P / 32;       // channel blocks
     constexpr int kNB = N / 32;       // state blocks
     constexpr int kHB = kNB / 2;      // state blocks owned per consumer wave
@@ -624,8 +597,6 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, flo
     __bf16* const tiles = reinterpret_cast<__bf16*>(ssd_lds);
     __bf16* const sHT = tiles + Lds::kBufs * Lds::kTileElems;
     float* const scal = reinterpret_cast<float*>(sHT + Lds::kBufs * Lds::kHT);   // [kBufs][kQ]: exp(l_i), decay from the chunk start
-    float* const park = SsdDuoLds<N, P>::kParkOverState ? reinterpret_cast<float*>(sHT)
-                                                        : scal + (Lds::kBufs + 3 * Lds::kScanTables) * kQ;   // DUO only
     auto sC = [&](int buf) { return tiles + buf * Lds::kTileElems; };
     auto sBT = [&](int buf) { return tiles + buf * Lds::kTileElems + Lds::kC; };
     auto sXc = [&](int buf) { return tiles + buf * Lds::kTileElems + Lds::kC + Lds::kBT; };
@@ -664,13 +635,11 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, flo
         // ------------------------------------------------------------------ producers
         constexpr int kCP = P / 2;                 // channel pairs of the head
         constexpr int kPos = kQ * kCP / kProdThreads;   // chunk positions per thread in the conv role (8 or 4)
-        const int ptid = (tid - kConsThreads) % kProdThreads;    // index within the wave's group
-        const int pwave = (wave - kConsThreads / 64) % 4;
-        const int group = (wave - kConsThreads / 64) / 4;
-        const bool do_score = PG == 1 || group == 0, do_conv = PG == 1 || group == 1;
+        const int ptid = tid - kConsThreads;
+        const int pwave = wave - kConsThreads / 64;
         const int cp = ptid % kCP, tg = ptid / kCP;   // conv role: channels 2cp, 2cp+1; positions kPos*tg .. of each chunk
-        // wave-private, written and read by this wave only (SINGLE: one copy, every wave writes the same values)
-        float* const pw_l2 = scal + Lds::kBufs * kQ + (SINGLE ? 0 : pwave) * 3 * kQ;
+        // wave-private, written and read by this wave only
+        float* const pw_l2 = scal + Lds::kBufs * kQ + pwave * 3 * kQ;
         float* const pw_dl = pw_l2 + kQ;
         float* const pw_wgt = pw_dl + kQ;
         const float a2 = a.A[head] * kLog2e;
@@ -741,7 +710,7 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, flo
             // Delta, inclusive cumulative log2-decay and end-of-chunk weight of position `lane` (every producer wave
             // computes them for itself; the first one publishes exp(l) for the consumers)
             float dl = IoBF16::cvt(dtraw);
-            if (!SINGLE) issue_dt(cn);
+            issue_dt(cn);
             if (a.dt_softplus) dl = softplus(dl + dtb);
             if (c * kQ + lane > last) dl = 0.0f;
             const float l2 = wave_inclusive_sum(dl * a2);
@@ -753,132 +722,121 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, flo
             const float l2_first = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), 0));
             const float l2_mid = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), kQ / 2 - 1));
             const bool separable = l2_first - l2_end <= 100.0f;
-            // (with two groups, wave i of each group shares slot i of the tables and writes only what its role reads)
-            if (do_score) {
-                if (separable) {
-                    pw_l2[lane] = fast_exp2(l2 - l2_mid);          // e_i
-                    pw_dl[lane] = fast_exp2(l2_mid - l2) * dl;     // f_j Delta_j
-                } else {
-                    pw_l2[lane] = l2;
-                    pw_dl[lane] = dl;
-                }
-                if (pwave == 0) scal[buf * kQ + lane] = fast_exp2(l2);
+            if (separable) {
+                pw_l2[lane] = fast_exp2(l2 - l2_mid);          // e_i
+                pw_dl[lane] = fast_exp2(l2_mid - l2) * dl;     // f_j Delta_j
+            } else {
+                pw_l2[lane] = l2;
+                pw_dl[lane] = dl;
             }
-            if (do_conv) pw_wgt[lane] = fast_exp2(l2_end - l2) * dl;
+            if (pwave == 0) scal[buf * kQ + lane] = fast_exp2(l2);
+            pw_wgt[lane] = fast_exp2(l2_end - l2) * dl;
             __builtin_amdgcn_wave_barrier();
-            if (do_score) {
-                // masked score operand: (B_j . C_i) exp(l_i - l_j) Delta_j for j <= i, else 0
-                float sv[kHS][4];
+            // masked score operand: (B_j . C_i) exp(l_i - l_j) Delta_j for j <= i, else 0
+            float sv[kHS][4];
 #pragma unroll
-                for (int m = 0; m < kHS; m++) { sv[m][0] = gt[m].x; sv[m][1] = gt[m].y; sv[m][2] = gt[m].z; sv[m][3] = gt[m].w; }
-                asm volatile("" ::: "memory");   // the re-issue below must not move above the reads of gt
-                if (!SINGLE) issue_score(cn);
+            for (int m = 0; m < kHS; m++) { sv[m][0] = gt[m].x; sv[m][1] = gt[m].y; sv[m][2] = gt[m].z; sv[m][3] = gt[m].w; }
+            asm volatile("" ::: "memory");   // the re-issue below must not move above the reads of gt
+            issue_score(cn);
 #pragma unroll
-                for (int m = 0; m < kHS; m++) {
-                    const int hs = m * kProdThreads + ptid;
-                    const int bp = hs / 256, kb = (hs / 128) % 2, sl = (hs / 2) % 64, hi = hs % 2;
-                    const int iblk = bp > 0, jblk = bp > 1;
-                    const int i = iblk * 32 + sl % 32;
-                    const int jb = jblk * 32 + 16 * kb + 8 * hi + 4 * (sl / 32);
-                    const bool diagonal = iblk == jblk;    // only the diagonal blocks hold elements with j > i
-                    const float l2i = pw_l2[i];
-                    const float4 da = *reinterpret_cast<const float4*>(&pw_dl[jb]);
-                    const float dj[4] = {da.x, da.y, da.z, da.w};
-                    bf16x4 v;
-                    if (separable) {
+            for (int m = 0; m < kHS; m++) {
+                const int hs = m * kProdThreads + ptid;
+                const int bp = hs / 256, kb = (hs / 128) % 2, sl = (hs / 2) % 64, hi = hs % 2;
+                const int iblk = bp > 0, jblk = bp > 1;
+                const int i = iblk * 32 + sl % 32;
+                const int jb = jblk * 32 + 16 * kb + 8 * hi + 4 * (sl / 32);
+                const bool diagonal = iblk == jblk;    // only the diagonal blocks hold elements with j > i
+                const float l2i = pw_l2[i];
+                const float4 da = *reinterpret_cast<const float4*>(&pw_dl[jb]);
+                const float dj[4] = {da.x, da.y, da.z, da.w};
+                bf16x4 v;
+                if (separable) {
 #pragma unroll
-                        for (int e = 0; e < 4; e++) {
-                            const float val = sv[m][e] * l2i * dj[e];
-                            v[e] = (__bf16)((diagonal && jb + e > i) ? 0.0f : val);
-                        }
-                    } else {
-                        const float4 la = *reinterpret_cast<const float4*>(&pw_l2[jb]);
-                        const float lj[4] = {la.x, la.y, la.z, la.w};
-#pragma unroll
-                        for (int e = 0; e < 4; e++) {
-                            const float val = sv[m][e] * fast_exp2(l2i - lj[e]) * dj[e];
-                            v[e] = (__bf16)((diagonal && jb + e > i) ? 0.0f : val);
-                        }
+                    for (int e = 0; e < 4; e++) {
+                        const float val = sv[m][e] * l2i * dj[e];
+                        v[e] = (__bf16)((diagonal && jb + e > i) ? 0.0f : val);
                     }
-                    *reinterpret_cast<bf16x4*>(&sM(buf)[(((iblk * 2 + jblk) * 2 + kb) * 64 + sl) * 8 + 4 * hi]) = v;
+                } else {
+                    const float4 la = *reinterpret_cast<const float4*>(&pw_l2[jb]);
+                    const float lj[4] = {la.x, la.y, la.z, la.w};
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        const float val = sv[m][e] * fast_exp2(l2i - lj[e]) * dj[e];
+                        v[e] = (__bf16)((diagonal && jb + e > i) ? 0.0f : val);
+                    }
                 }
+                *reinterpret_cast<bf16x4*>(&sM(buf)[(((iblk * 2 + jblk) * 2 + kb) * 64 + sl) * 8 + 4 * hi]) = v;
             }
-            if (do_conv) {
-                // conv + SiLU of two channels at kPos positions
-                float xr[2][kPos + 3];
+            // conv + SiLU of two channels at kPos positions
+            float xr[2][kPos + 3];
+#pragma unroll
+            for (int q = 0; q < kPos + 3; q++) {
+                xr[0][q] = __uint_as_float(xraw[q] << 16);
+                xr[1][q] = __uint_as_float(xraw[q] & 0xffff0000u);
+            }
+            asm volatile("" ::: "memory");
+            issue_x(cn);
+            if (edge_chunk(c)) {
 #pragma unroll
                 for (int q = 0; q < kPos + 3; q++) {
-                    xr[0][q] = __uint_as_float(xraw[q] << 16);
-                    xr[1][q] = __uint_as_float(xraw[q] & 0xffff0000u);
+                    const int tau = c * kQ + kPos * tg + q - 3;
+                    if (tau < 0 || tau > last) xr[0][q] = xr[1][q] = 0.0f;
                 }
-                asm volatile("" ::: "memory");
-                if (!SINGLE) issue_x(cn);
-                if (edge_chunk(c)) {
+                if (c == 0 && a.dir > 0 && a.tail_in && tg == 0 && a.K > 1) {
+                    // requested together from clamped rows (a tap beyond the conv width has a zero weight)
+                    T cached[3][2];
 #pragma unroll
-                    for (int q = 0; q < kPos + 3; q++) {
-                        const int tau = c * kQ + kPos * tg + q - 3;
-                        if (tau < 0 || tau > last) xr[0][q] = xr[1][q] = 0.0f;
+                    for (int q = 0; q < 3; q++) {   // 3 - q tokens before the block
+                        const T* tp = (const T*)a.tail_in + ((size_t)b * (a.K - 1) + max(a.K - 1 - (3 - q), 0)) * a.tail_ch + ch0 + 2 * cp;
+                        cached[q][0] = tp[0];
+                        cached[q][1] = tp[1];
                     }
-                    if (c == 0 && a.dir > 0 && a.tail_in && tg == 0 && a.K > 1) {
-                        // requested together from clamped rows (a tap beyond the conv width has a zero weight)
-                        T cached[3][2];
 #pragma unroll
-                        for (int q = 0; q < 3; q++) {   // 3 - q tokens before the block
-                            const T* tp = (const T*)a.tail_in + ((size_t)b * (a.K - 1) + max(a.K - 1 - (3 - q), 0)) * a.tail_ch + ch0 + 2 * cp;
-                            cached[q][0] = tp[0];
-                            cached[q][1] = tp[1];
-                        }
-#pragma unroll
-                        for (int q = 0; q < 3; q++) {
-                            if (3 - q <= a.K - 1) {
-                                xr[0][q] = IoBF16::cvt(cached[q][0]);
-                                xr[1][q] = IoBF16::cvt(cached[q][1]);
-                            }
+                    for (int q = 0; q < 3; q++) {
+                        if (3 - q <= a.K - 1) {
+                            xr[0][q] = IoBF16::cvt(cached[q][0]);
+                            xr[1][q] = IoBF16::cvt(cached[q][1]);
                         }
                     }
                 }
-                float wq[kPos];
-#pragma unroll
-                for (int q = 0; q < kPos; q += 4) {
-                    const float4 w = *reinterpret_cast<const float4*>(&pw_wgt[kPos * tg + q]);
-                    wq[q] = w.x; wq[q + 1] = w.y; wq[q + 2] = w.z; wq[q + 3] = w.w;
-                }
-#pragma unroll
-                for (int h2 = 0; h2 < 2; h2++) {
-                    typedef __attribute__((__vector_size__(kPos * sizeof(__bf16)))) __bf16 bf16run;
-                    bf16run vx, vw;
-#pragma unroll
-                    for (int q = 0; q < kPos; q++) {
-                        float pre = cbias[h2];
-                        pre = fmaf(w4[h2][0], xr[h2][q], pre);
-                        pre = fmaf(w4[h2][1], xr[h2][q + 1], pre);
-                        pre = fmaf(w4[h2][2], xr[h2][q + 2], pre);
-                        pre = fmaf(w4[h2][3], xr[h2][q + 3], pre);
-                        const float xc = silu(pre);
-                        vx[q] = (__bf16)xc;
-                        vw[q] = (__bf16)(xc * wq[q]);
-                    }
-                    *reinterpret_cast<bf16run*>(&sXc(buf)[(2 * cp + h2) * kRowT + kPos * tg]) = vx;
-                    *reinterpret_cast<bf16run*>(&sXw(buf)[(2 * cp + h2) * kRowT + kPos * tg]) = vw;
-                }
             }
-            if (do_score) {
+            float wq[kPos];
 #pragma unroll
-                for (int i = 0; i < kCopy; i++) {
-                    *reinterpret_cast<bf16x8*>(&sC(buf)[c_dst[i]]) = ctile[i];
-                    *reinterpret_cast<bf16x8*>(&sBT(buf)[b_dst[i]]) = btile[i];
-                }
-                asm volatile("" ::: "memory");
-                if (!SINGLE) issue_tiles(cn);
+            for (int q = 0; q < kPos; q += 4) {
+                const float4 w = *reinterpret_cast<const float4*>(&pw_wgt[kPos * tg + q]);
+                wq[q] = w.x; wq[q + 1] = w.y; wq[q + 2] = w.z; wq[q + 3] = w.w;
             }
+#pragma unroll
+            for (int h2 = 0; h2 < 2; h2++) {
+                typedef __attribute__((__vector_size__(kPos * sizeof(__bf16)))) __bf16 bf16run;
+                bf16run vx, vw;
+#pragma unroll
+                for (int q = 0; q < kPos; q++) {
+                    float pre = cbias[h2];
+                    pre = fmaf(w4[h2][0], xr[h2][q], pre);
+                    pre = fmaf(w4[h2][1], xr[h2][q + 1], pre);
+                    pre = fmaf(w4[h2][2], xr[h2][q + 2], pre);
+                    pre = fmaf(w4[h2][3], xr[h2][q + 3], pre);
+                    const float xc = silu(pre);
+                    vx[q] = (__bf16)xc;
+                    vw[q] = (__bf16)(xc * wq[q]);
+                }
+                *reinterpret_cast<bf16run*>(&sXc(buf)[(2 * cp + h2) * kRowT + kPos * tg]) = vx;
+                *reinterpret_cast<bf16run*>(&sXw(buf)[(2 * cp + h2) * kRowT + kPos * tg]) = vw;
+            }
+#pragma unroll
+            for (int i = 0; i < kCopy; i++) {
+                *reinterpret_cast<bf16x8*>(&sC(buf)[c_dst[i]]) = ctile[i];
+                *reinterpret_cast<bf16x8*>(&sBT(buf)[b_dst[i]]) = btile[i];
+            }
+            asm volatile("" ::: "memory");
+            issue_tiles(cn);
             __builtin_amdgcn_wave_barrier();   // the next chunk's scan results overwrite pw_* only after these reads
         };
         issue_dt(c_first);
-        if (do_score) {
-            issue_score(c_first);
-            issue_tiles(c_first);
-        }
-        if (do_conv) issue_x(c_first);
+        issue_score(c_first);
+        issue_tiles(c_first);
+        issue_x(c_first);
         finish(c_first, 0, min(c_first + 1, c_stop - 1));
         lds_barrier();
         for (int c = c_first; c < c_stop; c++) {
@@ -896,7 +854,6 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, flo
         constexpr int kMode = decltype(mode_c)::value;
         constexpr bool need_z = kMode != kSsdPartialRaw;
         constexpr bool adds_parked = kMode == kSsdFinalAdd || kMode == kSsdFinalAddRaw;
-        constexpr bool need_p = adds_parked && DUO != kDuoSecond;   // read back from global memory
         constexpr bool parks = kMode == kSsdPartialRaw || kMode == kSsdPartial;
         const int iblk = wave / kPB, pblk = wave % kPB;
         const int cl = lane & 31, half = lane >> 5;
@@ -944,10 +901,6 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, flo
         // chunk clamps every position instead.
         T zraw[16];
         float part[16];
-        if constexpr (DUO == kDuoSecond && adds_parked) {
-#pragma unroll
-            for (int r = 0; r < 16; r++) part[r] = parked[r];
-        }
         auto issue_gate = [&](int c) {
             const int tau0 = c * kQ + i0;
             if (c * kQ + kQ - 1 <= last) {
@@ -957,14 +910,14 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, flo
 #pragma unroll
                 for (int r = 0; r < 16; r++) {
                     if constexpr (need_z) zraw[r] = zp[row_k(r) * zstep];
-                    if constexpr (need_p) part[r] = pp[row_k(r) * pstep];
+                    if constexpr (adds_parked) part[r] = pp[row_k(r) * pstep];
                 }
             } else {
 #pragma unroll
                 for (int r = 0; r < 16; r++) {
                     const long long t = token_of(min(tau0 + row_k(r), last));
                     if constexpr (need_z) zraw[r] = zb[t * a.z.st];
-                    if constexpr (need_p) part[r] = pbase[t * a.Dn];
+                    if constexpr (adds_parked) part[r] = pbase[t * a.Dn];
                 }
             }
         };
@@ -1062,8 +1015,7 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, flo
                         T* op = obase + t0 * a.out_st;
 #pragma unroll
                         for (int r = 0; r < 16; r++) {
-                            if constexpr (parks && DUO == kDuoFirst) park[((int)t0 + row_k(r) * a.dir) * P + po] = res[r];
-                            else if constexpr (parks) pp[row_k(r) * pstep] = res[r];
+                            if constexpr (parks) pp[row_k(r) * pstep] = res[r];
                             else IoBF16::st(op + row_k(r) * ostep, res[r]);
                         }
                     } else {
@@ -1072,8 +1024,7 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, flo
                             const int tau = tau0 + row_k(r);
                             if (tau <= last) {
                                 const long long t = token_of(tau);
-                                if constexpr (parks && DUO == kDuoFirst) park[(int)t * P + po] = res[r];
-                                else if constexpr (parks) pbase[t * a.Dn] = res[r];
+                                if constexpr (parks) pbase[t * a.Dn] = res[r];
                                 else IoBF16::st(obase + t * a.out_st, res[r]);
                             }
                         }
@@ -1099,73 +1050,23 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a_in, int time_part, flo
             }
         }
     };
-    if constexpr (DUO == kDuoFirst) {   // the direction that parks (or stores its own half of a two-part output)
-        switch (a.mode) {
-            case kSsdFinalOnly: walk(std::integral_constant<int, kSsdFinalOnly>{}); break;
-            case kSsdPartial: walk(std::integral_constant<int, kSsdPartial>{}); break;
-            default: walk(std::integral_constant<int, kSsdPartialRaw>{}); break;
-        }
-    } else if constexpr (DUO == kDuoSecond) {
-        switch (a.mode) {
-            case kSsdFinalOnly: walk(std::integral_constant<int, kSsdFinalOnly>{}); break;
-            case kSsdFinalAdd: walk(std::integral_constant<int, kSsdFinalAdd>{}); break;
-            default: walk(std::integral_constant<int, kSsdFinalAddRaw>{}); break;
-        }
-    } else {
-        switch (a.mode) {
-            case kSsdFinalOnly: walk(std::integral_constant<int, kSsdFinalOnly>{}); break;
-            case kSsdPartial: walk(std::integral_constant<int, kSsdPartial>{}); break;
-            case kSsdPartialRaw: walk(std::integral_constant<int, kSsdPartialRaw>{}); break;
-            case kSsdFinalAdd: walk(std::integral_constant<int, kSsdFinalAdd>{}); break;
-            default: walk(std::integral_constant<int, kSsdFinalAddRaw>{}); break;
-        }
+    switch (a.mode) {
+        case kSsdFinalOnly: walk(std::integral_constant<int, kSsdFinalOnly>{}); break;
+        case kSsdPartial: walk(std::integral_constant<int, kSsdPartial>{}); break;
+        case kSsdPartialRaw: walk(std::integral_constant<int, kSsdPartialRaw>{}); break;
+        case kSsdFinalAdd: walk(std::integral_constant<int, kSsdFinalAdd>{}); break;
+        default: walk(std::integral_constant<int, kSsdFinalAddRaw>{}); break;
     }
 }
 
-template <int N, int P, bool SINGLE = false, int PG = 1, bool PARTS = false>
-__global__ __launch_bounds__(4 * P + 256 * PG, SINGLE ? 4 : 1) void ssd_kernel(const SsdStatePair launch)
+template <int N, int P, bool PARTS>
+__global__ __launch_bounds__(4 * P + 256, 1) void ssd_kernel(const SsdStatePair launch)
 {
-    float none[16];
     // blockIdx.y: the time part, counted through the direction(s) of the launch
     int part = blockIdx.y, second = 0;
     const int parts = PARTS ? launch.dir[0].parts : 1;
     if (part >= parts) { second = 1; part -= parts; }
-    ssd_walk<N, P, SINGLE, PG, PARTS, kDuoNone>(launch.dir[second], part, none);
-}
-
-// Single-chunk calls (block-diffusion steps), both directions of a (batch, head) item in one workgroup: the reverse
-// direction runs first and leaves its result in LDS instead of parking it in global memory, the forward direction
-// picks it up, so the call is one scan launch instead of two, x's rows are fetched from HBM once and the partial
-// never leaves the chip.  grid (H, 1, batch), block 4*P + 256, dynamic LDS SsdDuoLds<N, P>::bytes().  Between the
-// directions every consumer thread takes the 16 parked values of its (token, channel) places into registers, then a
-// barrier lets the forward direction overwrite the tiles and the state operand copy.
-template <int N, int P>
-__global__ __launch_bounds__(4 * P + 256, 4) void ssd_duo_kernel(const SsdStatePair both)
-{
-    using Lds = SsdLds<N, P, true>;
-    float parked[16];
-#pragma unroll
-    for (int r = 0; r < 16; r++) parked[r] = 0.0f;
-    ssd_walk<N, P, true, 1, false, kDuoFirst>(both.dir[1], 0, parked);
-    const int tid = threadIdx.x;
-    if (tid < 4 * P && both.dir[1].mode != kSsdFinalOnly) {   // consumer waves, same places as in ssd_walk
-        extern __shared__ __attribute__((aligned(16))) unsigned char ssd_lds[];
-        __bf16* const sHT = reinterpret_cast<__bf16*>(ssd_lds) + Lds::kTileElems;
-        const float* const park = SsdDuoLds<N, P>::kParkOverState
-                                      ? reinterpret_cast<const float*>(sHT)
-                                      : reinterpret_cast<const float*>(sHT + Lds::kHT) + (1 + 3) * kQ;
-        const int wave = tid >> 6, lane = tid & 63;
-        const int iblk = wave / (P / 32), pblk = wave % (P / 32);
-        const int po = pblk * 32 + (lane & 31), i0 = iblk * 32 + 4 * (lane >> 5);
-        const int last = both.dir[0].L - 1;
-#pragma unroll
-        for (int r = 0; r < 16; r++) {
-            const int t = i0 + 8 * (r / 4) + (r % 4);
-            parked[r] = t <= last ? park[t * P + po] : 0.0f;
-        }
-    }
-    lds_barrier();
-    ssd_walk<N, P, true, 1, false, kDuoSecond>(both.dir[0], 0, parked);
+    ssd_walk<N, P, PARTS>(launch.dir[second], part);
 }
 
 }  // namespace bm
