@@ -347,10 +347,10 @@ def main():
     roofline = {"bound": "alu", "achieved": ach_tflops, "peak": PEAK_FP32_VECTOR_TFLOPS, "unit": "TFLOP/s",
                 "frac": ach_tflops / PEAK_FP32_VECTOR_TFLOPS, "algorithmic_flops": flops}
     if ssd:
-        # the chunked matrix-core kernels: one launch per direction, both inside the probed interval
-        # one time part and several chunks: the sixteen-wave form; otherwise the eight-wave form (+ state and carry kernels)
-        form = "ssd_wide_kernel" if bd.bimamba_time_chunks(desc) == 1 and cfg["seqlen"] > 64 else "ssd_kernel"
-        kernel = "%s<N=%d,P=%d> (two launches, one per direction)" % (form, cfg["d_state"], cfg["d_inner"] // cfg["n_heads"])
+        # the chunked matrix-core kernels, inside the probed interval: one launch per direction (with time parts the state and carry
+        # kernels before them), or one for both where a call is a single chunk
+        form, launches = ("ssd_wide_kernel", "two launches, one per direction") if cfg["seqlen"] > 64 else ("ssd_block_kernel", "one launch")
+        kernel = "%s<N=%d,P=%d> (%s)" % (form, cfg["d_state"], cfg["d_inner"] // cfg["n_heads"], launches)
         mflops = shapes.ssd_matrix_flops(cfg)
         ach = mflops / (kernel_ms * 1e-3) / 1e12
         roofline = {"bound": "mfma", "achieved": ach, "peak": PEAK_BF16_MFMA_TFLOPS, "unit": "TFLOP/s",

@@ -515,10 +515,13 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
     // the chunked kernels read x two channels at a time and the carried state four states at a time
     if (plan.ssd && !(pairs_readable(in_f->x) && pairs_readable(in_b->x) && is_aligned(h_in, 16) && is_aligned(h_out, 16)))
         plan.ssd = false;
-    // the state pass of the time parts addresses the 67 token rows of a chunk with 32-bit byte offsets
-    constexpr int64_t kMaxPartsTokenStride = 1 << 24;
+    // the many-wave walk addresses a chunk's gate and output rows with 32-bit byte offsets, the state pass of the time parts
+    // its rows of x; parts come with both
+    constexpr int64_t kMaxWideStride = 1 << 24;
+    const bool wide = plan.ssd && plan.ssd_chunks >= 2 && in_f->z.stride_token <= kMaxWideStride &&
+                      in_b->z.stride_token <= kMaxWideStride && out->stride_token <= kMaxWideStride && !getenv("BIMAMBA_NO_WIDE");
     if (plan.ssd && plan.ssd_parts > 1 &&
-        (in_f->x.stride_token > kMaxPartsTokenStride || in_b->x.stride_token > kMaxPartsTokenStride)) {
+        (!wide || in_f->x.stride_token > kMaxWideStride || in_b->x.stride_token > kMaxWideStride)) {
         plan.ssd_parts = plan.ssd_subs = plan.ssd_part_subs = 1;
         plan.ssd_part_chunks = plan.ssd_sub_chunks = plan.ssd_chunks;
     }
@@ -627,12 +630,6 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
             // forward scan adds, gates and stores (or each writes its own half)
             const bool separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
             const bool raw = !separate && same_tensor(in_f->z, in_b->z);
-            // calls of several chunks that need no time parts walk sixteen waves wide (the row offsets of a chunk's
-            // gate / output rows are 32-bit there) unless BIMAMBA_NO_WIDE is set
-            constexpr int64_t kMaxWideStride = 1 << 24;
-            const bool wide = plan.ssd_parts == 1 && plan.ssd_chunks >= 2 && in_f->z.stride_token <= kMaxWideStride &&
-                              in_b->z.stride_token <= kMaxWideStride && out->stride_token <= kMaxWideStride &&
-                              !getenv("BIMAMBA_NO_WIDE");
             SsdPrepPair pp{};
             for (int s = 0; s < 2; s++) {
                 SsdPrepArgs& pa = pp.dir[s];

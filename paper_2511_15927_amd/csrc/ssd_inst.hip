@@ -17,16 +17,15 @@ static void prep_variant(const SsdPrepPair& pa, int nchunk, int batch, hipStream
     hipLaunchKernelGGL(kernel, dim3((unsigned)nchunk, (unsigned)pa.dir[0].G, 2u * (unsigned)batch), dim3(THREADS), lds, st, pa);
 }
 
-template <int N, int P, bool PARTS>
+template <int N, int P>
 static void scan_variant(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     static std::atomic<bool> seen[kMaxSeenDevices];
     constexpr size_t lds = SsdLds<N, P>::bytes();
-    auto kernel = ssd_kernel<N, P, PARTS>;
+    auto kernel = ssd_kernel<N, P>;
     if (first_use_on_current_device(seen))
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    const unsigned parts = !PARTS ? 1u : (unsigned)sp.dir[0].parts;   // blockIdx.y is the time part of a direction
-    hipLaunchKernelGGL(kernel, dim3((unsigned)sp.dir[0].H, parts * (unsigned)dirs, (unsigned)batch), dim3(4 * P + 256), lds, st, sp);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)sp.dir[0].H, (unsigned)dirs, (unsigned)batch), dim3(4 * P + 256), lds, st, sp);
 }
 
 template <int N, int P>
@@ -43,8 +42,7 @@ static void scan_one(const SsdStatePair& sp, int dirs, int batch, hipStream_t st
 {
     const SsdArgs& sa = sp.dir[0];
     if (sa.wide) launch_ssd_wide<N, P>(sp, dirs, batch, st);
-    else if (sa.parts > 1) scan_variant<N, P, true>(sp, dirs, batch, st);
-    else scan_variant<N, P, false>(sp, dirs, batch, st);
+    else scan_variant<N, P>(sp, dirs, batch, st);
 }
 
 bool ssd_supported(int d_state, int headdim) { return (d_state == 64 || d_state == 128) && (headdim == 32 || headdim == 64); }

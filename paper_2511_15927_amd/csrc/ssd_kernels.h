@@ -10,10 +10,9 @@
 // rounded to bf16.  ssd_prep_kernel builds, once per (direction, batch, chunk, group) and shared by all heads, the
 // score tile C B^T, the bf16 C rows and the transposed bf16 B tile.
 //
-// Kernels in this file: ssd_prep_kernel (above); ssd_kernel, the chunk walk of one direction (ssd_walk), with
-// a variant for time parts; ssd_state_kernel and ssd_carry_kernel, which find the state
+// Kernels in this file: ssd_prep_kernel (above); ssd_kernel, the chunk walk of one direction (ssd_walk); ssd_state_kernel and ssd_carry_kernel, which find the state
 // entering each time part when a call has too few (batch, head) items to fill the chip.  Calls of one chunk run on ssd_block.h,
-// whole calls of several on ssd_wide.h; the walk here is for time parts and for rows too far apart for 32-bit offsets.
+// calls of several on ssd_wide.h; the walk here is for rows too far apart for 32-bit offsets.
 //
 // Lane layouts of the 32x32x16 MFMA (checked on hardware): operand A lane l holds row l%32, k = 8*(l/32)..+7;
 // operand B lane l holds column l%32, same k; accumulator register r of lane l is row 8*(r/4) + 4*(l/32) + r%4,
@@ -470,17 +469,16 @@ __global__ __launch_bounds__(256, 4) void ssd_state_kernel(const SsdStatePair bo
         for (int q = 0; q < kPos + 3; q++) xraw[q] = xnext[q];
         float dl = IoBF16::cvt(dtraw);
         issue_dt(cn);
-        // this wave's B^T operands straight from the prepared tile (rows of kQ positions), used after the barrier.
+        // this wave's B^T operands straight from the prepared tile (whole pieces in lane order), used after the barrier
         bf16x8 ab[kLoadB][4];
         {
-            const __bf16* bsrc = a.b_t + ((((size_t)b * a.nchunk + c) * a.G + grp) * N) * kQ;
+            const bf16x8* bsrc = reinterpret_cast<const bf16x8*>(a.b_t + ((((size_t)b * a.nchunk + c) * a.G + grp) * N) * kQ) + lane;
 #pragma unroll
             for (int o = 0; o < kLoadB; o++) {
                 const int id = kOwn * wave + o, nblk = id / kPB;
                 if (kBlocks % 4 == 0 || id < kBlocks) {
 #pragma unroll
-                    for (int kb = 0; kb < 4; kb++)
-                        ab[o][kb] = *reinterpret_cast<const bf16x8*>(bsrc + (nblk * 32 + cl) * kQ + 16 * kb + 8 * half);
+                    for (int kb = 0; kb < 4; kb++) ab[o][kb] = bsrc[(nblk * 4 + kb) * 64];
                 }
             }
         }
@@ -578,10 +576,8 @@ __global__ __launch_bounds__(256, 4) void ssd_state_kernel(const SsdStatePair bo
 // and stage the C / B^T tiles, with the global loads of the chunk after that already in flight.  One LDS barrier per
 // chunk.  (The producers' per-head work does not shrink with the head width, so their count does not either.)
 // Block: 4*P + 256 threads.
-// PARTS compiles the time parts in (chunk range and entry state per time_part); without it the kernel walks every
-// chunk of its item and carries none of that bookkeeping through its loops.
-template <int N, int P, bool PARTS>
-__device__ __forceinline__ void ssd_walk(const SsdArgs& a, int time_part)
+template <int N, int P>
+__device__ __forceinline__ void ssd_walk(const SsdArgs& a)
 {
     using Lds = SsdLds<N, P>;
     constexpr int kPB = P / 32;       // channel blocks
@@ -622,12 +618,10 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a, int time_part)
     const int ch0 = head * P;
     const size_t Lpad = (size_t)a.nchunk * kQ;
     // this workgroup's chunks [c_first, c_stop) and the states it starts from / leaves
-    constexpr bool in_parts = PARTS;
-    const int c_first = in_parts ? time_part * a.part_chunks : 0;
-    const int c_stop = in_parts ? min(a.nchunk, c_first + a.part_chunks) : a.nchunk;
-    const size_t part_elems = (size_t)gridDim.z * a.Dn * N;
-    const float* const state_in = in_parts ? a.part_state + (size_t)time_part * a.part_subs * part_elems : a.h_in;
-    float* const state_out = (time_part == (in_parts ? a.parts : 1) - 1) ? a.h_out : nullptr;
+    constexpr int c_first = 0;
+    const int c_stop = a.nchunk;
+    const float* const state_in = a.h_in;
+    float* const state_out = a.h_out;
     const int last = a.L - 1;
     auto token_of = [&](int tau) { return a.dir > 0 ? tau : last - tau; };   // scan position -> token index
 
@@ -1059,14 +1053,10 @@ __device__ __forceinline__ void ssd_walk(const SsdArgs& a, int time_part)
     }
 }
 
-template <int N, int P, bool PARTS>
+template <int N, int P>
 __global__ __launch_bounds__(4 * P + 256, 1) void ssd_kernel(const SsdStatePair launch)
 {
-    // blockIdx.y: the time part, counted through the direction(s) of the launch
-    int part = blockIdx.y, second = 0;
-    const int parts = PARTS ? launch.dir[0].parts : 1;
-    if (part >= parts) { second = 1; part -= parts; }
-    ssd_walk<N, P, PARTS>(launch.dir[second], part);
+    ssd_walk<N, P>(launch.dir[blockIdx.y]);   // blockIdx.y: the direction, where a launch has both
 }
 
 }  // namespace bm

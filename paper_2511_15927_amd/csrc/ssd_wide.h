@@ -50,14 +50,18 @@ struct SsdWide {
 
 // MODE: the output mode, compiled apart (the registers of one mode are not held through another's loop); kSsdFinalOnly walks
 // both directions in one launch (see launch_ssd_scan), the others one.
-template <int N, int P, int HEADS, int MODE>
+// PARTS: the launch deals every item's chunks to several workgroups in scan order (blockIdx.y: the part, then the direction), each from
+// the state that ssd_state_kernel and ssd_carry_kernel left for it, and what one direction parks for the other stays fp32.
+// Against the eight-wave walk of ssd_kernels.h, calls of 64 heads x 64, N 128: 1 x 32768 tokens 953 -> 890 us, 1 x 8192 279 -> 255, 2 x 8192
+// 476 -> 440, 1 x 2048 103 -> 90; 64 heads x 32, N 64, 1 x 16384 340 -> 258.
+template <int N, int P, int HEADS, int MODE, bool PARTS>
 __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_kernel(const std::conditional_t<(MODE > 0), SsdArgs, SsdStatePair> launch)
 {
     // (the parameter's type names no enumerator: those of an unnamed enumeration are spelt differently in a kernel's host and device name)
     static_assert(kSsdFinalOnly == 0);
     const SsdArgs& a = [&]() -> const SsdArgs& {
         if constexpr (MODE != kSsdFinalOnly) return launch;
-        else return launch.dir[blockIdx.y];
+        else return launch.dir[PARTS ? (int)blockIdx.y >= launch.dir[0].parts : blockIdx.y];
     }();
     using W = SsdWide<N, P, HEADS>;
     constexpr int kPB = W::kPB, kNB = W::kNB;
@@ -87,11 +91,15 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
     head *= HEADS;                          // the workgroup's first; two heads are of one group (the host checks)
     const int grp = head / a.HG;
     const int ch0 = head * P;
-    const int nchunk = a.nchunk, periods = nchunk * HEADS;   // period p: chunk p / HEADS, head p % HEADS
+    // this workgroup's chunks [c0, c0 + nchunk), below by their place in it; period p: chunk p / HEADS, head p % HEADS
+    const int part = !PARTS ? 0 : (int)blockIdx.y - ((int)blockIdx.y >= a.parts ? a.parts : 0), c0 = !PARTS ? 0 : part * a.part_chunks;
+    const int nchunk = !PARTS ? a.nchunk : min(a.nchunk - c0, a.part_chunks), periods = nchunk * HEADS, q0 = c0 * kQ;
+    const float* const state_in = !PARTS ? a.h_in : a.part_state + (size_t)part * a.part_subs * gridDim.z * a.Dn * N;
+    float* const state_out = !PARTS || part == a.parts - 1 ? a.h_out : nullptr;
     const int last = a.L - 1;
     auto token_of = [&](int tau) { return a.dir > 0 ? tau : last - tau; };
     // the prepared tiles of (chunk c, this group)
-    auto tile_of = [&](int c) { return ((size_t)b * nchunk + c) * a.G + grp; };
+    auto tile_of = [&](int c) { return ((size_t)b * a.nchunk + c0 + c) * a.G + grp; };
 
     if (wave >= 2 * W::kYWaves + 4) {
         // ------------------------------------------------------------------ conv waves
@@ -112,10 +120,10 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
             }
         const T* xb = (const T*)a.x.p + (size_t)b * a.x.sb + ch0 + 2 * cp;
         const long long xstep = a.dir * a.x.st;
-        const auto edge_chunk = [&](int c) { return c == 0 || c * kQ + kQ - 1 > last; };
+        const auto edge_chunk = [&](int c) { return c0 + c == 0 || q0 + c * kQ + kQ - 1 > last; };
         unsigned xraw[2][kPos + 3];   // of the periods of either parity, requested two periods ahead
         auto issue_x = [&](int c, int hd, unsigned (&xraw)[kPos + 3]) {
-            const int tau0 = c * kQ + kPos * tg - 3;
+            const int tau0 = q0 + c * kQ + kPos * tg - 3;
             const T* const xh = xb + hd * P;
             if (!edge_chunk(c)) {
                 const T* xp = xh + (long long)token_of(tau0) * a.x.st;
@@ -157,10 +165,10 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
             if (edge_chunk(c)) {
 #pragma unroll
                 for (int q = 0; q < kPos + 3; q++) {
-                    const int tau = c * kQ + kPos * tg + q - 3;
+                    const int tau = q0 + c * kQ + kPos * tg + q - 3;
                     if (tau < 0 || tau > last) xr[0][q] = xr[1][q] = 0.0f;
                 }
-                if (c == 0 && a.dir > 0 && a.tail_in && tg == 0 && a.K > 1) {
+                if (c0 + c == 0 && a.dir > 0 && a.tail_in && tg == 0 && a.K > 1) {
                     T cached[3][2];
 #pragma unroll
                     for (int q = 0; q < 3; q++) {   // 3 - q tokens before the block; a tap beyond the conv width has a zero weight
@@ -265,7 +273,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
         const float dtb = (a.dt_softplus && a.dt_bias) ? a.dt_bias[scan_head] : 0.0f;
         const T* dtp = (const T*)a.dt.p + (size_t)b * a.dt.sb + scan_head;
         T dtraw;
-        auto issue_dt = [&](int p) { dtraw = dtp[(long long)token_of(min(p / HEADS * kQ + lane, last)) * a.dt.st]; };
+        auto issue_dt = [&](int p) { dtraw = dtp[(long long)token_of(min(q0 + p / HEADS * kQ + lane, last)) * a.dt.st]; };
         // A period's scan: Delta; the inclusive cumulative log2-decay; what the waves read of them.  With two heads a wave does these
         // in successive periods (whole, it lengthens one wave's stream in every period: 0.8 % at 8 x 8192 tokens); with one head's
         // shorter periods the branches cost more than that (2 % at 1 x 1024).
@@ -274,7 +282,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
             dl = IoBF16::cvt(dtraw);
             issue_dt(p + 4);   // (clamped to the sequence)
             if (a.dt_softplus) dl = softplus(dl + dtb);
-            if (p / HEADS * kQ + lane > last) dl = 0.0f;
+            if (q0 + p / HEADS * kQ + lane > last) dl = 0.0f;
         };
         auto scan_decay = [&]() { l2 = wave_inclusive_sum(dl * a2); };
         auto scan_tables = [&](int p) {
@@ -337,8 +345,8 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
             for (int o = 0; o < kOwn; o++) {
 #pragma unroll
                 for (int r = 0; r < 16; r++) hacc[hd][o][r] = 0.0f;
-                if (a.h_in && owner) {   // registers 4q .. 4q+3: four adjacent states of the lane's channel
-                    const float* hrow = a.h_in + ((size_t)b * a.Dn + ch_of_lane + hd * P + (pblk0 + o) * 32) * N + nblk * 32 + 4 * half;
+                if (state_in && owner) {   // registers 4q .. 4q+3: four adjacent states of the lane's channel
+                    const float* hrow = state_in + ((size_t)b * a.Dn + ch_of_lane + hd * P + (pblk0 + o) * 32) * N + nblk * 32 + 4 * half;
 #pragma unroll
                     for (int q = 0; q < 4; q++) {
                         const float4 v = *reinterpret_cast<const float4*>(hrow + 8 * q);
@@ -364,7 +372,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
             constexpr int hd = decltype(head_c)::value;
             const int p = c * HEADS + hd;
             // the state after the last chunk matters only if it is committed
-            if (!owner || (c + 1 >= nchunk && a.h_out == nullptr)) return;
+            if (!owner || (c + 1 >= nchunk && state_out == nullptr)) return;
             const float decay_q = table(p)[3 * kQ + kQ - 1];
             const bf16x8* xw = reinterpret_cast<const bf16x8*>(sXw(p & 1)) + lane;
 #pragma unroll
@@ -439,12 +447,12 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
                 lds_barrier();
             }
         }
-        if (a.h_out && owner) {
+        if (state_out && owner) {
 #pragma unroll
             for (int hd = 0; hd < HEADS; hd++)
 #pragma unroll
                 for (int o = 0; o < kOwn; o++) {
-                    float* hrow = a.h_out + ((size_t)b * a.Dn + ch_of_lane + hd * P + (pblk0 + o) * 32) * N + nblk * 32 + 4 * half;
+                    float* hrow = state_out + ((size_t)b * a.Dn + ch_of_lane + hd * P + (pblk0 + o) * 32) * N + nblk * 32 + 4 * half;
 #pragma unroll
                     for (int q = 0; q < 4; q++)
                         *reinterpret_cast<float4*>(hrow + 8 * q) =
@@ -467,14 +475,16 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
     // rows of a chunk that lies inside the sequence, relative to the chunk's lowest-address token: row 16 rt + r of
     // the lane is group[rt] (in the lane offset) plus step[r] (a scalar offset): no vector address arithmetic
     const int fwd = a.dir > 0;
-    const unsigned zs = (unsigned)a.z.st * 2u, os = (unsigned)a.out_st * 2u, ps = (unsigned)a.Dn * 2u;
+    const unsigned zs = (unsigned)a.z.st * 2u, os = (unsigned)a.out_st * 2u;
+    using Park = std::conditional_t<PARTS, float, T>;   // what one direction leaves for the other: bf16 where a call is walked whole
+    const unsigned ps = (unsigned)a.Dn * (unsigned)sizeof(Park);
     unsigned zoff[2], ooff[2], poff[2];
 #pragma unroll
     for (int rt = 0; rt < 2; rt++) {
         const unsigned rows = (unsigned)(fwd ? i0 + 16 * rt : kQ - 4 - i0 - 16 * rt);
         zoff[rt] = rows * zs + 2u * (unsigned)po;
         ooff[rt] = rows * os + 2u * (unsigned)po;
-        poff[rt] = rows * ps + 2u * (unsigned)po;
+        poff[rt] = rows * ps + (unsigned)sizeof(Park) * (unsigned)po;
     }
     // (scalar registers by construction: left to the compiler the direction select lands in vector registers and
     // every access loops over the lanes to read its offset back)
@@ -487,13 +497,16 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
         pstep[e] = __builtin_amdgcn_readfirstlane(m * (int)ps);
     }
     const T* const zhead = (const T*)a.z.p + (size_t)b * a.z.sb + my_ch0;
-    T* const phead = (T*)a.partial + (size_t)b * a.L * a.Dn + my_ch0;   // the parked result is bf16
+    Park* const phead = (Park*)a.partial + (size_t)b * a.L * a.Dn + my_ch0;
     T* const ohead = (T*)a.out + (size_t)b * a.out_sb + a.out_ch_off + my_ch0;
-    auto chunk_low_token = [&](int c) { return (long long)(fwd ? c * kQ : last - (c * kQ + kQ - 1)); };
-    auto inside = [&](int c) { return c * kQ + kQ - 1 <= last; };
-    auto token_at = [&](int c, int k) { return (long long)token_of(min(c * kQ + i0 + 16 * (k / 4) + k % 4, last)); };
+    auto chunk_low_token = [&](int c) { return (long long)(fwd ? q0 + c * kQ : last - (q0 + c * kQ + kQ - 1)); };
+    auto inside = [&](int c) { return q0 + c * kQ + kQ - 1 <= last; };
+    auto token_at = [&](int c, int k) { return (long long)token_of(min(q0 + c * kQ + i0 + 16 * (k / 4) + k % 4, last)); };
 
-    unsigned zraw[8], praw[8];   // register k: row 16 (k / 4) + k % 4 of the lane, a channel pair
+    typedef unsigned __attribute__((ext_vector_type(2))) uint2v;
+    using ParkPair = std::conditional_t<PARTS, uint2v, unsigned>;
+    unsigned zraw[8];   // register k: row 16 (k / 4) + k % 4 of the lane, a channel pair
+    ParkPair praw[8];
     auto issue_z = [&](int c) {
         if constexpr (!need_z) return;
         if (inside(c)) {
@@ -513,10 +526,13 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
         if (inside(c)) {
             const Rsrc pr = raw_range(phead + chunk_low_token(c) * a.Dn);
 #pragma unroll
-            for (int k = 0; k < 8; k++) praw[k] = __builtin_amdgcn_raw_buffer_load_b32(pr, poff[k / 4], pstep[k % 4], 0);
+            for (int k = 0; k < 8; k++) {
+                if constexpr (PARTS) praw[k] = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(pr, poff[k / 4], pstep[k % 4], 0));
+                else praw[k] = __builtin_amdgcn_raw_buffer_load_b32(pr, poff[k / 4], pstep[k % 4], 0);
+            }
         } else {
 #pragma unroll
-            for (int k = 0; k < 8; k++) praw[k] = *reinterpret_cast<const unsigned*>(phead + token_at(c, k) * a.Dn + po);
+            for (int k = 0; k < 8; k++) praw[k] = *reinterpret_cast<const ParkPair*>(phead + token_at(c, k) * a.Dn + po);
         }
     };
     bf16x8 cf[HEADS == 1 ? kNB : 1][2];   // one head: C operand straight from global memory, [32 states][row tile]
@@ -546,7 +562,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
         for (int rt = 0; rt < 2; rt++)
 #pragma unroll
             for (int ct = 0; ct < 2; ct++) y1[rt][ct] = y2[rt][ct] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        if (c > 0 || a.h_in != nullptr) {
+        if (c > 0 || state_in != nullptr) {
             const bf16x8* c_t = reinterpret_cast<const bf16x8*>(sC + (c & 1) * W::kC) + iblk * 2 * kNB * 64 + lane;
             const bf16x8* h_t = reinterpret_cast<const bf16x8*>(sHT + buf * W::kHT) + pblk * 2 * 64 + lane;
 #pragma unroll
@@ -592,38 +608,45 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
         }
         lds_barrier();
         // epilogue: gate, combine, round, a channel pair at a time
-        unsigned res[8];
+        using Result = std::conditional_t<parks, ParkPair, unsigned>;
+        Result res[8];
 #pragma unroll
         for (int k = 0; k < 8; k++) {
             float v[2];
 #pragma unroll
             for (int ct = 0; ct < 2; ct++) {
-                const float pv = need_p ? (ct == 0 ? lo(praw[k]) : hi(praw[k])) : 0.0f;
+                float pv = 0.0f;
+                if constexpr (need_p && PARTS) pv = __uint_as_float(praw[k][ct]);
+                else if constexpr (need_p) pv = ct == 0 ? lo(praw[k]) : hi(praw[k]);
                 if constexpr (!need_z) v[ct] = y[k][ct];
                 else {
                     const float zg = silu(ct == 0 ? lo(zraw[k]) : hi(zraw[k]));
                     v[ct] = MODE == kSsdFinalAddRaw ? (y[k][ct] + pv) * zg : need_p ? y[k][ct] * zg + pv : y[k][ct] * zg;
                 }
             }
-            typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
-            const bf16x2 pair = {(__bf16)v[0], (__bf16)v[1]};
-            res[k] = __builtin_bit_cast(unsigned, pair);
+            if constexpr (parks && PARTS) {
+                res[k] = Result{__float_as_uint(v[0]), __float_as_uint(v[1])};
+            } else {
+                const bf16x2 pair = {(__bf16)v[0], (__bf16)v[1]};
+                res[k] = __builtin_bit_cast(unsigned, pair);
+            }
         }
         if (inside(c)) {
             const long long t0 = chunk_low_token(c);
-            const Rsrc orr = raw_range(parks ? phead + t0 * a.Dn : ohead + t0 * a.out_st);
+            const Rsrc orr = raw_range(parks ? (const void*)(phead + t0 * a.Dn) : (const void*)(ohead + t0 * a.out_st));
 #pragma unroll
             for (int k = 0; k < 8; k++) {
-                if constexpr (parks) __builtin_amdgcn_raw_buffer_store_b32(res[k], orr, poff[k / 4], pstep[k % 4], 0);
+                if constexpr (parks && PARTS) __builtin_amdgcn_raw_buffer_store_b64(res[k], orr, poff[k / 4], pstep[k % 4], 0);
+                else if constexpr (parks) __builtin_amdgcn_raw_buffer_store_b32(res[k], orr, poff[k / 4], pstep[k % 4], 0);
                 else __builtin_amdgcn_raw_buffer_store_b32(res[k], orr, ooff[k / 4], ostep[k % 4], 0);
             }
         } else {
 #pragma unroll
             for (int k = 0; k < 8; k++) {
-                const int tau = c * kQ + i0 + 16 * (k / 4) + k % 4;
+                const int tau = q0 + c * kQ + i0 + 16 * (k / 4) + k % 4;
                 if (tau <= last) {
                     const long long t = token_of(tau);
-                    if constexpr (parks) *reinterpret_cast<unsigned*>(phead + t * a.Dn + po) = res[k];
+                    if constexpr (parks) *reinterpret_cast<Result*>(phead + t * a.Dn + po) = res[k];
                     else {
                         T* const o = ohead + t * a.out_st + po;
                         *reinterpret_cast<bf16_pair*>(o) = res[k];

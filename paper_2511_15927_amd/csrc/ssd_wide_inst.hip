@@ -6,28 +6,29 @@
 
 namespace bm {
 
-template <int HEADS, int MODE>
+template <int HEADS, int MODE, bool PARTS>
 static void variant(const SsdStatePair& sp, int batch, hipStream_t st)
 {
     static std::atomic<bool> seen[kMaxSeenDevices];
     using W = SsdWide<BM_N, BM_P, HEADS>;
-    auto kernel = ssd_wide_kernel<BM_N, BM_P, HEADS, MODE>;
+    auto kernel = ssd_wide_kernel<BM_N, BM_P, HEADS, MODE, PARTS>;
     if (first_use_on_current_device(seen))
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)W::bytes());
-    const dim3 grid((unsigned)(sp.dir[0].H / HEADS), MODE == kSsdFinalOnly ? 2u : 1u, (unsigned)batch), block(W::kThreads);
+    const unsigned parts = PARTS ? (unsigned)sp.dir[0].parts : 1u;
+    const dim3 grid((unsigned)(sp.dir[0].H / HEADS), MODE == kSsdFinalOnly ? 2u * parts : parts, (unsigned)batch), block(W::kThreads);
     if constexpr (MODE == kSsdFinalOnly) hipLaunchKernelGGL(kernel, grid, block, W::bytes(), st, sp);
     else hipLaunchKernelGGL(kernel, grid, block, W::bytes(), st, sp.dir[0]);
 }
 
-template <int HEADS>
+template <int HEADS, bool PARTS>
 static void launch(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    if (dirs == 2) return variant<HEADS, kSsdFinalOnly>(sp, batch, st);
+    if (dirs == 2) return variant<HEADS, kSsdFinalOnly, PARTS>(sp, batch, st);
     switch (sp.dir[0].mode) {
-        case kSsdPartial: return variant<HEADS, kSsdPartial>(sp, batch, st);
-        case kSsdPartialRaw: return variant<HEADS, kSsdPartialRaw>(sp, batch, st);
-        case kSsdFinalAdd: return variant<HEADS, kSsdFinalAdd>(sp, batch, st);
-        default: return variant<HEADS, kSsdFinalAddRaw>(sp, batch, st);
+        case kSsdPartial: return variant<HEADS, kSsdPartial, PARTS>(sp, batch, st);
+        case kSsdPartialRaw: return variant<HEADS, kSsdPartialRaw, PARTS>(sp, batch, st);
+        case kSsdFinalAdd: return variant<HEADS, kSsdFinalAdd, PARTS>(sp, batch, st);
+        default: return variant<HEADS, kSsdFinalAddRaw, PARTS>(sp, batch, st);
     }
 }
 
@@ -38,8 +39,9 @@ static void launch(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 void BM_NAME(BM_N, BM_P)(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     const SsdArgs& sa = sp.dir[0];
-    if (sa.HG % 2 == 0 && (long long)sa.H * batch * dirs > cu_count()) launch<2>(sp, dirs, batch, st);
-    else launch<1>(sp, dirs, batch, st);
+    if (sa.parts > 1) launch<1, true>(sp, dirs, batch, st);
+    else if (sa.HG % 2 == 0 && (long long)sa.H * batch * dirs > cu_count()) launch<2, false>(sp, dirs, batch, st);
+    else launch<1, false>(sp, dirs, batch, st);
 }
 
 }  // namespace bm

@@ -213,6 +213,41 @@ def test_ssd_time_parts_with_a_wide_x_stride(gpu, oracle, token_stride):
     assert_close(got, ref, gpu.TOL["bf16"])
 
 
+@pytest.mark.parametrize("N,headdim,combine,own", [(128, 64, 0, False), (128, 32, 0, True), (64, 32, 1, False), (64, 64, 0, True)])
+def test_ssd_time_parts_down_to_one_short_chunk(gpu, oracle, N, headdim, combine, own):
+    """41 chunks in parts of ten, the last part one chunk of five tokens: every head width, z shared (gated once, behind the sum) and
+    the reverse direction's own, the halves added and kept apart."""
+    from paper_2511_15927_amd import binding as bd
+    cfg = synth.m2_cfg(1, 2565, 256, headdim=headdim, d_state=N, combine=combine)
+    assert bd.bimamba_time_chunks(bd.make_desc(cfg)) == 5
+    pf, pb, inp = case(cfg, 2565 + N)
+    other = synth.make_inputs(cfg, 2566) if own else None
+    ref = oracle.bimamba_fwd(cfg, to_np(pf), to_np(pb), to_np(inp), None if other is None else to_np(other))
+    assert_close(gpu.gpu_fwd(cfg, pf, pb, inp, other), ref, gpu.TOL["bf16"])
+
+
+def test_ssd_rows_too_far_apart_for_time_parts(gpu, oracle):
+    """z as a view with a token stride beyond 2^24 elements: the call runs without parts and without the many-wave walk."""
+    from paper_2511_15927_amd import binding as bd
+    L, token_stride = 1030, (1 << 24) + 2
+    cfg = synth.m2_cfg(1, L, 256, headdim=64, d_state=64)
+    pf, pb, inp = case(cfg, 4243)
+    ref = oracle.bimamba_fwd(cfg, to_np(pf), to_np(pb), to_np(inp))
+    desc = bd.make_desc(cfg)
+    dpf, dpb, dinp = bd.to_device(pf), bd.to_device(pb), bd.to_device(inp, cfg)
+    big = torch.empty((L - 1) * token_stride + 256, dtype=torch.bfloat16, device="cuda")
+    wide = big.as_strided((1, L, 256), (0, token_stride, 1))
+    wide.copy_(dinp["z"])
+    dinp["z"] = wide
+    out, ws = bd.alloc_out(cfg), bd.alloc_workspace(desc)
+    bd.bimamba_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp), None, bd.make_tensor(out), ws)
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy()
+    del big, wide, dinp
+    torch.cuda.empty_cache()
+    assert_close(got, ref, gpu.TOL["bf16"])
+
+
 @pytest.mark.parametrize("name,batch", [("cfg2_m2", 1), ("headline_m2", 1), ("headline_m2", 2)])
 def test_ssd_time_parts_at_benchmark_size_sampled(gpu, oracle, name, batch):
     """The time-part path (state pass over sub-parts, carry, concurrent output pass) at the benchmark's own sizes, in the
