@@ -64,13 +64,19 @@ def read_profile(kernel_key):
         return {}, None, None
     # the dominant kernel of the step: the one with the longest dispatch
     kernel = max(ours, key=lambda k: ours[k].get("DURATION_NS_UNDER_PMC", 0.0))
-    return dict(shared, **ours[kernel]), kernel, os.path.relpath(path, ROOT)
+    counters = dict(shared, **ours[kernel])
+    # bytes of a step: of all forms of that kernel (the chunked path launches one per direction)
+    for key in ("FETCH_BYTES_PER_LAUNCH", "WRITE_BYTES_PER_LAUNCH"):
+        forms = [c[key] for k, c in ours.items() if k.split("<")[0] == kernel.split("<")[0] and key in c]
+        if forms:
+            counters[key] = sum(forms)
+    return counters, kernel, os.path.relpath(path, ROOT)
 
 
-def traffic_of(c, launches):
+def traffic_of(c):
     """HBM bytes per step of the dominant kernel (fetch + write, each scaled by the copy calibration)."""
     try:
-        return launches * (c["FETCH_BYTES_PER_LAUNCH"] + c["WRITE_BYTES_PER_LAUNCH"])
+        return c["FETCH_BYTES_PER_LAUNCH"] + c["WRITE_BYTES_PER_LAUNCH"]
     except KeyError:
         return None
 
@@ -356,8 +362,7 @@ def main():
         roofline = {"bound": "mfma", "achieved": ach, "peak": PEAK_BF16_MFMA_TFLOPS, "unit": "TFLOP/s",
                     "frac": ach / PEAK_BF16_MFMA_TFLOPS, "algorithmic_flops": mflops}
     counters, profile_kernel, profile_file = read_profile("sweep_" + args.workload)
-    # the chunked path runs one launch per direction, both inside the probed interval; the summary holds one launch's mean
-    traffic = traffic_of(counters, 2 if ssd else 1)
+    traffic = traffic_of(counters)
     simds = 4 * torch.cuda.get_device_properties(0).multi_processor_count
     valu_busy, waves_per_simd = valu_busy_of(counters, simds)
     clock_ghz, valu_busy_own_clock = sustained_clock_of(counters, simds)
