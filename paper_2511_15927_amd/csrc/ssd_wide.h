@@ -1,4 +1,4 @@
-// The chunk walk of ssd_kernels.h for calls that fill the chip, dealt to short instruction streams of up to sixteen waves.
+// The chunk walk of ssd_kernels.h dealt to short instruction streams of up to sixteen waves.
 //
 // A wave issues at most one instruction every six to seven cycles whatever the instruction is, while a SIMD's vector
 // ALU accepts a 64-lane instruction every four, so a workgroup is as fast as its longest instruction stream, not as its
@@ -27,9 +27,9 @@
 // g is state 16*(g%2) + 8u + 4*(g/2) + e of a 32-state block, the order in which the state's accumulators publish it.
 //
 // The result one direction parks for the other crosses global memory as bf16: in the paper's precision (bf16 autocast,
-// App. A) each direction's output is a bf16 tensor before the two are added (eq. 6).
+// App. A) each direction's output is a bf16 tensor before the two are added (eq. 6).  In time parts it stays fp32.
 //
-// grid (H / HEADS, directions, batch).  Multi-chunk calls without time parts only; z / out token strides up to 2^24 elements (the host checks).
+// grid (H / HEADS, directions * parts, batch).  Calls of several chunks; z / out token strides up to 2^24 elements (the host checks).
 #pragma once
 #include "ssd_kernels.h"
 
