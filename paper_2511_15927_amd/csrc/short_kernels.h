@@ -4,8 +4,8 @@
 // of the second half of the walk and of what the other direction left for it, the commit.  Here everything a wave needs first is requested
 // before any of it is used, the token tiles are requested one ahead also across the meeting of the directions, B|C rows go to LDS as
 // fp32 once per workgroup (no copy per wave, no preparation launch), and what one direction leaves for the other stays in LDS.  16 x 32 tokens,
-// d_inner 4096, 16 states, committing: 23.9 -> 18.1 us against a walk by the long sweep's token loop with a copy of the rows per
-// wave and the partial sums in memory; 64 x 64 tokens 137 -> 97, 32 x 32 with 8 states 33.9 -> 22.5, 32 x 1 token 15.3 -> 12.6.
+// d_inner 4096, 16 states, committing: 23.9 -> 18.0 us against a walk by the long sweep's token loop with a copy of the rows per
+// wave and the partial sums in memory; 64 x 64 tokens 137 -> 93, 32 x 32 with 8 states 33.9 -> 22.5, 32 x 1 token 15.3 -> 12.6.
 //
 // A workgroup is four waves, the two directions of two adjacent tiles of 64 channels, as in kernels.h; the arithmetic of a token is
 // that of token_step there, with the output's dot product in two sums.
@@ -21,15 +21,16 @@ constexpr int kShortTile = 8;   // tokens whose loads are in flight while the ti
 constexpr int kShortAdd = 0, kShortAddRaw = 1, kShortSeparate = 2;
 
 // LDS of a workgroup, in floats: B|C rows [pair of waves, if their tiles may lie in two groups][direction, if they differ][L][2N], then
-// what the directions leave for each other, [pair][L][64].
+// what the directions leave for each other, [pair][L][64].  (A row to spare in front and one behind: the walk reads one ahead.)
 struct ShortLds {
-    int pair_rows, dir_rows, park, total;
+    int rows, pair_rows, dir_rows, park, total;
     __host__ __device__ ShortLds(int L, int N, bool two_sets, bool two_groups, bool separate)
     {
         dir_rows = two_sets ? L * 2 * N : 0;
         const int sets = L * 2 * N + dir_rows;
         pair_rows = two_groups ? sets : 0;
-        park = sets + pair_rows;
+        rows = 2 * N;
+        park = rows + sets + pair_rows + 2 * N;
         total = park + (separate ? 0 : 2 * L * 64);
     }
 };
@@ -46,7 +47,9 @@ template <int N, int AKIND, int KIND, typename IO>
 __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
 {
     using T = typename IO::T;
-    constexpr int TILE = kShortTile;
+    // (general decays of 16 states: half a tile, which leaves their factors room in the registers of three waves a SIMD; 64 x 64
+    // tokens, d_inner 4096: two waves 129 us, three with a whole tile's spills 131, so 119)
+    constexpr int TILE = AKIND == kAPerState && N >= 16 ? kShortTile / 2 : kShortTile;
     constexpr bool kSeparate = KIND == kShortSeparate, kRaw = KIND == kShortAddRaw;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int s = w & 1, b = blockIdx.z, L = a.L, last = L - 1;
@@ -99,7 +102,7 @@ __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
         const T* const from = (col < N ? (const T*)src.Braw.p + (size_t)b * src.Braw.sb : (const T*)src.Craw.p + (size_t)b * src.Craw.sb) +
                               grp * N + col % N;
         const long long st = col < N ? src.Braw.st : src.Craw.st;
-        float* const to = lds_all + pair * lds.pair_rows + set * lds.dir_rows + col;
+        float* const to = lds_all + lds.rows + pair * lds.pair_rows + set * lds.dir_rows + col;
         T v[kPer];
 #pragma unroll
         for (int k = 0; k < kPer; k++)
@@ -147,22 +150,28 @@ __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
     const bool sp = a.dt_softplus != 0;
     short_barrier();   // B|C rows
 
-    const float* const rows = lds_all + (w >> 1) * lds.pair_rows + s * lds.dir_rows + tstart * 2 * N;
-    float* const park = lds_all + lds.park + ((w >> 1) * L + tstart) * 64 + lane;
+    // (places in LDS as running byte offsets of the lane: an addition a token)
+    unsigned row_at = (unsigned)(lds.rows + (w >> 1) * lds.pair_rows + s * lds.dir_rows + tstart * 2 * N) * 4u;
+    unsigned park_at = (unsigned)(lds.park + ((w >> 1) * L + tstart) * 64 + lane) * 4u;
+    keep_narrow(row_at);
+    keep_narrow(park_at);
+    const unsigned row_step = (unsigned)(step * 2 * N * 4), park_step = (unsigned)(step * 64 * 4);
+    auto load_row = [&](BcRow<N>& r) { load_bc_lds<N, 1>(lane_elem((const float*)lds_all, row_at), 0, 0, r); };
     BcRow<N> row;
-    load_bc_lds<N, 1>(rows, 0, 0, row);
+    load_row(row);
     // One token of the walk: y before the gate.
-    auto token = [&](int j, T xraw, float delta) {
+    auto token = [&](T xraw, float delta) {
         asm volatile("" ::: "memory");   // one row of B|C ahead, not a tile of them: they would not fit the registers
         BcRow<N> row_next;
-        load_bc_lds<N, 1>(rows, step * min(j + 1, last), 0, row_next);
+        row_at += row_step;
+        load_row(row_next);
         const float x0 = IO::cvt(xraw);
         const float pre = fmaf(w4[3], x0, fmaf(w4[2], xh[0], fmaf(w4[1], xh[1], fmaf(w4[0], xh[2], cb))));
         xh[2] = xh[1];
         xh[1] = xh[0];
         xh[0] = x0;
         const float xc = silu(pre), u = delta * xc;
-        float y[2] = {dval * xc, 0.0f};
+        float y[2] = {dval * xc, 0.0f};   // (the second starts with a product)
         float an = 1.0f, ratio = 1.0f;
         if constexpr (AKIND != kAPerState) an = fast_exp2(delta * a2[0]);
         if constexpr (AKIND == kAProgression) ratio = fast_exp2(delta * d2);
@@ -170,18 +179,22 @@ __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
         for (int n = 0; n < N; n++) {
             if constexpr (AKIND == kAPerState) an = fast_exp2(delta * a2[n]);
             h[n] = fmaf(an, h[n], u * row.v[n]);
-            y[n & 1] = fmaf(row.v[N + n], h[n], y[n & 1]);
+            y[n & 1] = n == 1 ? row.v[N + n] * h[n] : fmaf(row.v[N + n], h[n], y[n & 1]);
             if constexpr (AKIND == kAProgression) an *= ratio;
         }
         row = row_next;
         return y[0] + y[1];
     };
-    auto leave = [&](int j, float y, T zraw) { park[step * j * 64] = kRaw ? y : y * silu(IO::cvt(zraw)); };
-    auto finish = [&](int j, float y, T zraw) {
+    auto leave = [&](float y, T zraw) {
+        *lane_elem(lds_all, park_at) = kRaw ? y : y * silu(IO::cvt(zraw));
+        park_at += park_step;
+    };
+    auto finish = [&](float y, T zraw) {
         const float zg = silu(IO::cvt(zraw));
         float v = kRaw ? 0.0f : y * zg;
         if constexpr (!kSeparate) {
-            const float part = park[step * j * 64];
+            const float part = *lane_elem(lds_all, park_at);
+            park_at += park_step;
             v = kRaw ? (y + part) * zg : v + part;
         }
         return v;
@@ -202,9 +215,9 @@ __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
             const TileRows<TILE> to = tile_rows<TILE>(ob + j * os, os);
 #pragma unroll
             for (int i = 0; i < TILE; i++) {
-                const float y = token(j + i, cur.x[i], delta[i]);
-                if constexpr (kFinal) IO::st_raw(to.range, ch_io, to.row(i), finish(j + i, y, cur.z[i]));
-                else leave(j + i, y, cur.z[i]);
+                const float y = token(cur.x[i], delta[i]);
+                if constexpr (kFinal) IO::st_raw(to.range, ch_io, to.row(i), finish(y, cur.z[i]));
+                else leave(y, cur.z[i]);
             }
         }
 #pragma unroll 1
@@ -213,9 +226,9 @@ __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
             const T zraw = kFinal || !kRaw ? *lane_elem(zb + j * zs, ch_io) : (T)0;
             float delta = IO::cvt(draw);
             if (sp) delta = softplus(delta + dtb);
-            const float y = token(j, xraw, delta);
-            if constexpr (kFinal) IO::st(lane_elem(ob + j * os, ch_io), finish(j, y, zraw));
-            else leave(j, y, zraw);
+            const float y = token(xraw, delta);
+            if constexpr (kFinal) IO::st(lane_elem(ob + j * os, ch_io), finish(y, zraw));
+            else leave(y, zraw);
         }
     };
     if constexpr (!kSeparate) {
@@ -240,9 +253,10 @@ __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
     }
 }
 
-// grid (ceil(ceil(Dn / 64) / 2), 1, batch), block 256, dynamic LDS ShortLds::total floats.
+// grid (ceil(ceil(Dn / 64) / 2), 1, batch), block 256, dynamic LDS ShortLds::total floats.  Three waves a SIMD: with the nine to twelve
+// registers more that the compiler would take, launches of many workgroups hold two (64 x 64 tokens 103 us, 64 x 16 43 -> 38).
 template <int N, int AKIND, int KIND, typename IO>
-__global__ __launch_bounds__(256) void short_kernel(const SweepArgs a)
+__global__ __launch_bounds__(256, 3) void short_kernel(const SweepArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) float short_lds[];
     if constexpr (AKIND == kAPerState && kProgressionEligible<N, IO>) {

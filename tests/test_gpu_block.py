@@ -295,7 +295,7 @@ def test_one_launch_short_calls(gpu, oracle, L, N, io, a_kind, own):
     states and tails committed in place."""
     from paper_2511_15927_amd import binding as bd
     cfg = synth.mixer_cfg(2, L, 192, d_state=N, n_heads=192 if L % 2 else 96, n_groups=3, io=io, a_kind=a_kind, dt_softplus=L // 2 % 2,
-                          combine=int(L in (2, 15, 64)))
+                          combine=int(L in (2, 15, 33)))   # (64 tokens, halves together, two groups and own B, C: the most LDS)
     if a_kind == 0 and L % 4 != 1:
         pf, pb = params(cfg, 60 + L)
     else:
