@@ -415,7 +415,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
         }
         if (sw < 2) scan_tables(sw);
         lds_barrier();   // the tables of the first two periods
-        score(0, HEADS == 1 ? 1 : -1);
+        score(0, HEADS == 1 ? min(1, nchunk - 1) : -1);
         publish_state(Head0{}, 0);
         if constexpr (HEADS == 2) publish_state(Head1{}, 1);
         lds_barrier();
