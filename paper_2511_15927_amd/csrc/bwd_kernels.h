@@ -201,8 +201,7 @@ __device__ __forceinline__ void bwd_wave_setup(const BwdArgs& a, BwdWave<N, IO>&
     const DirArgs& da = a.dir[w.s];
 #pragma unroll
     for (int n = 0; n < N; n++) w.a2[n] = da.A[(size_t)w.ch * N + n] * kLog2e;
-#pragma unroll
-    for (int i = 0; i < 4; i++) w.w4[3 - i] = i < a.K ? da.conv_w[(size_t)w.ch * a.K + (a.K - 1 - i)] : 0.0f;
+    load_taps(da.conv_w + (size_t)w.ch * a.K, a.K, w.w4);
     w.cb = da.conv_b ? da.conv_b[w.ch] : 0.0f;
     w.dval = da.D[w.ch];
     w.dtb = (a.dt_softplus && da.dt_bias) ? da.dt_bias[w.ch] : 0.0f;

@@ -1111,9 +1111,7 @@ __device__ __forceinline__ void sweep_body(const SweepArgs& a, float* lds_all, c
     c.sub = sub;
     // per-lane constants
     {
-        const int K = a.K;
-#pragma unroll
-        for (int i = 0; i < 4; i++) c.w4[3 - i] = i < K ? da.conv_w[(size_t)ch * K + (K - 1 - i)] : 0.0f;
+        load_taps(da.conv_w + (size_t)ch * a.K, a.K, c.w4);
         c.cb = da.conv_b ? da.conv_b[ch] : 0.0f;
         c.dval = da.D[a.d_per_head ? head : ch];
         c.dtb = (a.dt_softplus && da.dt_bias) ? da.dt_bias[head] : 0.0f;

@@ -400,9 +400,7 @@ __global__ __launch_bounds__(256, 4) void ssd_state_kernel(const SsdStatePair bo
     float w4[2][4], cbias[2];
 #pragma unroll
     for (int h2 = 0; h2 < 2; h2++) {
-#pragma unroll
-        for (int i = 0; i < 4; i++)
-            w4[h2][3 - i] = i < a.K ? a.conv_w[(size_t)(ch0 + 2 * cp + h2) * a.K + (a.K - 1 - i)] : 0.0f;
+        load_taps(a.conv_w + (size_t)(ch0 + 2 * cp + h2) * a.K, a.K, w4[h2]);
         cbias[h2] = a.conv_b ? a.conv_b[ch0 + 2 * cp + h2] : 0.0f;
     }
     const T* xb = (const T*)a.x.p + (size_t)b * a.x.sb + ch0 + 2 * cp;
