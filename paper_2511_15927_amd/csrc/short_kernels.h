@@ -4,7 +4,7 @@
 // of the second half of the walk and of what the other direction left for it, the commit.  Here everything a wave needs first is requested
 // before any of it is used, the token tiles are requested one ahead also across the meeting of the directions, B|C rows go to LDS as
 // fp32 once per workgroup (no copy per wave, no preparation launch), and what one direction leaves for the other stays in LDS.  16 x 32 tokens,
-// d_inner 4096, 16 states, committing: 23.9 -> 18.0 us against a walk by the long sweep's token loop with a copy of the rows per
+// d_inner 4096, 16 states, committing: 23.9 -> 17.8 us against a walk by the long sweep's token loop with a copy of the rows per
 // wave and the partial sums in memory; 64 x 64 tokens 137 -> 93, 32 x 32 with 8 states 33.9 -> 22.5, 32 x 1 token 15.3 -> 12.6.
 //
 // A workgroup is four waves, the two directions of two adjacent tiles of 64 channels, as in kernels.h; the arithmetic of a token is
