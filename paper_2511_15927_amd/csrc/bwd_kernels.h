@@ -536,26 +536,22 @@ struct BwdWalk {
     __device__ __forceinline__ void request(int k)
     {
         // (positions outside the sequence repeat its nearest token; rows as offsets from the chunk's lowest one, which the load
-        // instruction adds: a scalar multiplication a row)
+        // instruction adds: a scalar multiplication a row.  Seven rows of the widest token stride stay below 2^31 bytes.)
         const int first = w.j0 + k * CT;
         keep_narrow(lo_t);
-        const int ja = inside(first - 3), jb = inside(first + CT - 1), low = w.dir > 0 ? ja : a.L - 1 - jb;
+#pragma unroll
+        for (int e = 0; e < 3; e++) xbefore[e] = *(const T*)(w.at(w.x, inside(first - 3 + e)) + lo_t);
+        const int ja = inside(first), jb = inside(first + CT - 1), low = w.dir > 0 ? ja : a.L - 1 - jb;
         auto range_of = [&](const Walked& t) { return raw_range(t.base + (long long)low * t.stride); };
         const Rsrc rx = range_of(w.x), rd = range_of(w.dt), rz = range_of(w.z), rg = range_of(w.g);
+        static_assert(CT <= 8, "row offsets");
 #pragma unroll
-        for (int e = 0; e < CT + 3; e++) {
-            const int j = inside(first - 3 + e);
-            const unsigned row = (unsigned)(w.dir > 0 ? j - ja : jb - j);
-            auto load = [&](const Rsrc& r, const Walked& t) { return IO::ld_raw(r, lo_t, (int)(row * (unsigned)t.stride)); };
-            if (e < 3) {
-                xbefore[e < 3 ? e : 0] = load(rx, w.x);
-            } else {
-                const int i = e >= 3 ? e - 3 : 0;
-                xnext[i] = load(rx, w.x);
-                dnext[i] = load(rd, w.dt);
-                znext[i] = load(rz, w.z);
-                gnext[i] = load(rg, w.g);
-            }
+        for (int i = 0; i < CT; i++) {
+            const int j = inside(first + i), row = w.dir > 0 ? j - ja : jb - j;
+            xnext[i] = IO::ld_raw(rx, lo_t, row * w.x.stride);
+            dnext[i] = IO::ld_raw(rd, lo_t, row * w.dt.stride);
+            znext[i] = IO::ld_raw(rz, lo_t, row * w.z.stride);
+            gnext[i] = IO::ld_raw(rg, lo_t, row * w.g.stride);
         }
         load_block<N>(a.state + w.place(a, a.seg_chunks, k) * (64 * N), hnext, w.lane);
         wnext = a.state_w[w.place(a, a.seg_chunks, k) * 64 + w.lane];
