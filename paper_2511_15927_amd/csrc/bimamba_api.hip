@@ -184,10 +184,15 @@ bool enough_chains(const bimamba_desc* d, long long w) { return many_states(d) ?
 // launch): 20480 chains (batch * d_inner) 14.4 / 15.0 / 18.8 / 26.1 -> 8.8 / 10.1 / 14.3 / 22.6, 57344 chains 17.6 / 23.9 / 32.1 / 45.4 ->
 // 8.5 / 12.7 / 18.2 / 29.8, 262144 chains x 64 118 -> 97; general decays, fp32, halves apart alike.  Only while two lanes per chain make at most
 // one wave per SIMD (16384 chains) do more than 32 tokens favour them: 64 tokens 22.3 / 22.0 (one launch / two lanes), fp32 26.4 / 23.7,
-// halves apart 23.1 / 20.6.  (Fewer chains yet: the row form.)
+// halves apart 23.1 / 20.6.  (Fewer chains yet: the row form.)  And with the directions' halves apart two lanes win more than 48 tokens
+// from one to one and a half waves per SIMD, where one lane leaves some SIMDs two waves: 36000 chains x 64 tokens, per-state decays 43.8
+// (one launch) / 40.4, a decay per head 35.1 / 35.5; added up 41.7 / 41.4 and 33.1 / 36.3; 57344 chains 46.3 / 53.3.
 bool one_launch_fits(const bimamba_desc* d, long long w)
 {
-    return d->d_state <= 16 && !d->conv_bc && d->seqlen <= kShortCallTokens && (d->d_state < 16 || d->seqlen <= 32 || 2 * w > simds());
+    if (d->d_state > 16 || d->conv_bc || d->seqlen > kShortCallTokens) return false;
+    if (d->d_state < 16 || d->seqlen <= 32) return true;
+    const bool uneven = d->combine == BIMAMBA_COMBINE_SEPARATE && d->seqlen > 48 && w > simds() && 2 * w <= 3 * simds();
+    return 2 * w > simds() && !uneven;
 }
 
 int pick_split_general(const bimamba_desc* d)
@@ -472,7 +477,7 @@ bool short_call(const bimamba_desc* d, const Plan& plan)
 bool row_call(const bimamba_desc* d, const Plan& plan, RowForm* row)
 {
     return !plan.ssd && !d->conv_bc && d->time_chunks == 0 && d->state_split == 0 &&
-           row_form(d->batch, d->seqlen, d->d_inner, d->d_state, row);
+           row_form(d->batch, d->seqlen, d->d_inner, d->d_state, d->combine == BIMAMBA_COMBINE_SEPARATE, row);
 }
 
 void launch_scan(const bimamba_desc* d, int split, int short_call, const SweepArgs& sa, const CarryArgs& ca,

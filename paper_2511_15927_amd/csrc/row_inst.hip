@@ -15,26 +15,32 @@ namespace bm {
 //                         stop at 0.75 M channel tokens, the others at 1 M
 //   193 to 256 tokens     up to 0.4 M channel tokens 0.56 / 0.48 / 0.50, the worst call 0.81; beyond (bf16, 16 states) 1 x 212
 //                         tokens of 2688 channels 28.2 us / 32.6, 1 x 220 of 4112 37.1 / 56.4, 1 x 256 of 4096 34.6 / 37.8
-// Up to 64 tokens the other side is short_kernel, one launch too (short / row, us; 4, 16, 32 and 64 tokens, bf16):
+// Up to 64 tokens the other side is short_kernel, one launch too, or two lanes per chain (other / row, us; 4, 16, 32 and 64 tokens, bf16):
 //   16 states  12288 chains  8.4/8.7  9.9/9.6 14.1/11.6 22.0/17.3;  16384 chains  8.5/10.4 10.0/12.2 14.4/15.0
 //   8 states    8192 chains  8.7/9.2  8.2/8.4 11.2/9.7  16.8/13.5;  12288 chains  9.1/9.6  9.3/10.0 11.3/11.5 16.9/17.3
 //   4 states    8192 chains  8.3/8.4  8.4/8.8  9.7/9.4  14.4/13.3;  12288 chains  8.6/8.9  8.6/9.6   9.8/11.5 14.5/17.1
+// From 25 tokens on (fewer states: 17) the row form stays ahead for longer where the directions are added up (24, 32, 40 and 48 tokens, per-state decays):
+//   16 states, 16384 chains  added 14.9/14.8 17.4/15.4 22.0/18.3 21.5/18.7;  halves 14.7/17.4 17.8/18.6 18.6/23.0 21.3/23.8
+//   8 states, 9000 chains    added 12.1/11.1 12.6/11.3 15.6/13.5 16.3/14.5;  halves 11.5/13.0 13.2/13.1 15.3/15.4 17.1/16.2
+//   8 states, 12288 chains   added 12.0/11.9 12.3/12.1 15.2/14.5 16.1/14.7;  halves 11.1/13.5 13.1/13.7 15.0/16.3 16.8/17.0
 constexpr long long kRowMaxChainsShort = 3LL << 12, kRowMaxChainsShortFew = 8192;   // up to 64 tokens: 16 states, fewer
 constexpr long long kRowMaxChains = 16384, kRowMaxChainsFew = 3LL << 12, kRowMaxElements = 3LL << 18, kRowMaxElementsLong = 1LL << 20;
 constexpr long long kRowMaxElementsLongest = 3LL << 17;
-constexpr int kRowLongTokens = 128, kRowLongestTokens = 192;
+constexpr int kRowFewTokens = 24, kRowFewTokensFew = 16,   // 16 states, fewer
+              kRowLongTokens = 128, kRowLongestTokens = 192;
 constexpr size_t kRowLdsBytes = 160 * 1024;
 
-bool row_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f)
+bool row_form(int batch, int seqlen, int d_inner, int d_state, bool halves, RowForm* f)
 {
     if (d_state > 16 || seqlen < 1 || seqlen > kRowMaxTokens) return false;
     const long long chains = (long long)batch * d_inner;
     const long long most = seqlen > kRowLongestTokens                 ? kRowMaxElementsLongest
                            : seqlen > kRowLongTokens && d_state >= 8 ? kRowMaxElementsLong
                                                                      : kRowMaxElements;
-    const long long most_chains = seqlen <= kShortCallTokens ? (d_state < 16 ? kRowMaxChainsShortFew : kRowMaxChainsShort)
-                                  : d_state < 8              ? kRowMaxChainsFew
-                                                             : kRowMaxChains;
+    const bool few = seqlen <= kShortCallTokens && (halves || d_state < 8 || seqlen <= (d_state < 16 ? kRowFewTokensFew : kRowFewTokens));
+    const long long most_chains = few                                               ? (d_state < 16 ? kRowMaxChainsShortFew : kRowMaxChainsShort)
+                                  : d_state < (seqlen <= kShortCallTokens ? 16 : 8) ? kRowMaxChainsFew
+                                                                                    : kRowMaxChains;
     if (chains > most_chains || chains * seqlen > most) return false;
     const long long tiles = (long long)batch * ((d_inner + 3) / 4);
     const int groups = (seqlen + kRowTokens - 1) / kRowTokens;

@@ -59,7 +59,10 @@ def test_heads_groups_and_scalar_decay(gpu, oracle, L):
     (2, 64, 2045, 16, 2),        # four, two time segments
     (1, 100, 3001, 4, 4),        # two, two segments
     (1, 128, 2046, 16, 4),       # two, four segments
-    (2, 17, 8000, 16, 1)])       # four
+    (2, 17, 8000, 16, 1),        # four
+    (2, 33, 8000, 16, 4),        # four, added up; halves apart: two lanes per chain, not this form
+    (2, 17, 6144, 8, 4),         # four, added up; halves apart: one lane per chain
+    (1, 50, 33000, 16, 4)])      # not this form: one lane per chain added up, two lanes with the halves apart
 @pytest.mark.parametrize("io", ["f32", "bf16"])
 def test_several_channel_tiles_in_a_workgroup(gpu, oracle, batch, L, Dn, N, K, io):
     """Calls of 2048 chains or more put two or four channel tiles into a workgroup: full-sequence calls with the directions
