@@ -36,7 +36,8 @@
  *   - lane-per-chain kernels (every descriptor): one (direction, batch, channel) recurrence per lane group, all
  *     products and sums in fp32.  When a head's A[h, 0..N-1] is an arithmetic progression in n (checked on the
  *     device, bf16 I/O, d_state <= 32) the N decay factors of a token are formed as a_0 * r^n by repeated
- *     multiplication from two exponentials instead of N exponentials.  (bimamba_bwd, whose results are partly fp32
+ *     multiplication from two exponentials instead of N exponentials (up to 64 tokens and 16 states: none by
+ *     multiplication up to 16384 chains and 0.75 M channel tokens, below 61440 chains at most seven in a row).  (bimamba_bwd, whose results are partly fp32
  *     whatever the I/O dtype, evaluates every exponential.)
  *   - chunked matrix-core kernels (a_kind = SCALAR_PER_HEAD, bf16 I/O, d_state 64 or 128, 32 or 64 channels per
  *     head, time_chunks = state_split = 0): the recurrence over 64-token chunks as dense products on the MFMA

@@ -480,6 +480,17 @@ bool row_call(const bimamba_desc* d, const Plan& plan, RowForm* row)
            row_form(d->batch, d->seqlen, d->d_inner, d->d_state, d->combine == BIMAMBA_COMBINE_SEPARATE, row);
 }
 
+// Over how many states the decays of an arithmetic A may be products (SweepArgs::try_progression): no more than in the other forms that
+// are the choice for calls of the size.  The row form takes an exponential a state, and so do the calls of its sizes that
+// another form runs faster (by products over sixteen states what 13312 chains commit after 16 tokens is 8.1e-7 from 64 bits, this way
+// 1.3e-7); lane pairs hold eight states a lane.  One lane a chain is the choice of itself from 1.9 waves per SIMD on.
+int decay_run(const bimamba_desc* d)
+{
+    if (d->d_state > 16 || d->seqlen > kShortCallTokens) return 16;   // (the length matters to the short form only)
+    const bool row_size = !d->conv_bc && d->time_chunks == 0 && d->state_split == 0 && row_reach(d->batch, d->seqlen, d->d_inner);
+    return row_size ? 0 : enough_chains(d, waves_of(d, 1)) ? 16 : 8;
+}
+
 void launch_scan(const bimamba_desc* d, int split, int short_call, const SweepArgs& sa, const CarryArgs& ca,
                  hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
@@ -736,7 +747,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
         sa.separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
         sa.raw_partial = !sa.separate && same_tensor(in_f->z, in_b->z);
         sa.same_bc = same_tensor(in_f->B, in_b->B) && same_tensor(in_f->C, in_b->C);
-        sa.try_progression = 1;
+        sa.try_progression = decay_run(d);
         CarryArgs ca{};
         ca.carry = sa.carry; ca.sumdt = sa.sumdt; ca.A[0] = pf->A; ca.A[1] = pb->A;
         ca.h_in = sa.h_in; ca.h_out = sa.h_out;

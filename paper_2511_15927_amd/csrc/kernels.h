@@ -61,7 +61,8 @@ struct SweepArgs {
     int dt_softplus, d_per_head, separate;
     int same_bc;          // both directions read the same B and C (the short form asks)
     int raw_partial;      // both directions gate with the same z: park y ungated and gate once at the final store
-    int try_progression;  // let each wave test whether its chains' A rows are arithmetic in n (see sweep_kernel)
+    int try_progression;  // let each wave test whether its chains' A rows are arithmetic in n (see sweep_kernel); 0: an exponential a state;
+                          // the short form: over how many states the decays may be products
     int layer_wgs;        // workgroups the dispatcher places before a CU gets its next one (the CU count); set by the launcher
     int turn_mask;        // 0: leave wave priorities alone; 1 / 3: two / up to four waves share a SIMD and take turns
     void* tail_out;       // or null; written by the short form

@@ -62,6 +62,7 @@ struct RowForm {
 };
 struct RowArgs;
 bool row_form(int batch, int seqlen, int d_inner, int d_state, bool halves, RowForm* f);   // halves: the directions write halves of their own
+bool row_reach(int batch, int seqlen, int d_inner);   // whether a call is of a size that the row form takes for some state count and combine
 bool stack_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f);      // the same for a stack of layers (stack_kernels.h)
 struct StackArgs;
 hipError_t launch_stack(int io_bf16, const StackArgs& a, int batch, hipStream_t st);

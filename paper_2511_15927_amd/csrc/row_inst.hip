@@ -23,12 +23,21 @@ namespace bm {
 //   16 states, 16384 chains  added 14.9/14.8 17.4/15.4 22.0/18.3 21.5/18.7;  halves 14.7/17.4 17.8/18.6 18.6/23.0 21.3/23.8
 //   8 states, 9000 chains    added 12.1/11.1 12.6/11.3 15.6/13.5 16.3/14.5;  halves 11.5/13.0 13.2/13.1 15.3/15.4 17.1/16.2
 //   8 states, 12288 chains   added 12.0/11.9 12.3/12.1 15.2/14.5 16.1/14.7;  halves 11.1/13.5 13.1/13.7 15.0/16.3 16.8/17.0
+// An arithmetic A is no faster than that on the other side, which takes its exponentials in these sizes too (8, 16, 24 and 32 tokens; halves
+// read activations of their own): 16 states, 13312 chains, added 8.4/10.2 9.8/11.0 12.2/13.0, halves 8.3/11.4 10.0/13.0 12.5/15.3 15.3/15.8,
+// 40 and 48 tokens 16.6/19.5 18.0/20.7; 8 states, 9216 chains, halves 7.6/8.4 7.6/10.2 9.3/11.6 11.0/11.9, 48 and 64 tokens 14.3/14.3 17.6/21.2.
 constexpr long long kRowMaxChainsShort = 3LL << 12, kRowMaxChainsShortFew = 8192;   // up to 64 tokens: 16 states, fewer
 constexpr long long kRowMaxChains = 16384, kRowMaxChainsFew = 3LL << 12, kRowMaxElements = 3LL << 18, kRowMaxElementsLong = 1LL << 20;
 constexpr long long kRowMaxElementsLongest = 3LL << 17;
 constexpr int kRowFewTokens = 24, kRowFewTokensFew = 16,   // 16 states, fewer
               kRowLongTokens = 128, kRowLongestTokens = 192;
 constexpr size_t kRowLdsBytes = 160 * 1024;
+
+bool row_reach(int batch, int seqlen, int d_inner)
+{
+    const long long chains = (long long)batch * d_inner;
+    return chains <= kRowMaxChains && chains * seqlen <= kRowMaxElements;
+}
 
 bool row_form(int batch, int seqlen, int d_inner, int d_state, bool halves, RowForm* f)
 {

@@ -125,17 +125,27 @@ struct Tiled {
 };
 
 #if BM_S == 1 && BM_N <= 16
-template <int AKIND, int KIND, typename IO>
-static void launch_short(const SweepArgs& sa, int batch, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
+template <int AKIND, int KIND, typename IO, int RUN>
+static void launch_short_run(const SweepArgs& sa, int batch, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     static KernelFit fit;
-    const auto kernel = short_kernel<BM_N, AKIND, KIND, IO>;
+    const auto kernel = short_kernel<BM_N, AKIND, KIND, IO, RUN>;
     const dim3 grid((unsigned)(((sa.Dn + 63) / 64 + 1) / 2), 1, (unsigned)batch);
     const int need = ShortLds(sa.L, BM_N, !sa.same_bc, sa.G > 1, KIND == kShortSeparate).total * (int)sizeof(float);
     const unsigned lds = spread_lds(kernel, &fit, grid, need);
     if (ev_start) (void)hipEventRecord(ev_start, st);
     hipLaunchKernelGGL(kernel, grid, dim3(kBlock), lds, st, sa);
     if (ev_stop) (void)hipEventRecord(ev_stop, st);
+}
+
+template <int AKIND, int KIND, typename IO>
+static void launch_short(const SweepArgs& sa, int batch, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
+{
+    if constexpr (AKIND == kAPerState && kProgressionEligible<BM_N, IO>) {
+        if (BM_N > 8 && sa.try_progression > 8) return launch_short_run<AKIND, KIND, IO, BM_N>(sa, batch, st, ev_start, ev_stop);
+        if (sa.try_progression) return launch_short_run<AKIND, KIND, IO, (BM_N < 8 ? BM_N : 8)>(sa, batch, st, ev_start, ev_stop);
+    }
+    launch_short_run<AKIND, KIND, IO, 0>(sa, batch, st, ev_start, ev_stop);
 }
 #endif
 

@@ -4,7 +4,7 @@
 // of the second half of the walk and of what the other direction left for it, the commit.  Here everything a wave needs first is requested
 // before any of it is used, the token tiles are requested one ahead also across the meeting of the directions, B|C rows go to LDS as
 // fp32 once per workgroup (no copy per wave, no preparation launch), and what one direction leaves for the other stays in LDS.  16 x 32 tokens,
-// d_inner 4096, 16 states, committing: 23.9 -> 17.8 us against a walk by the long sweep's token loop with a copy of the rows per
+// d_inner 4096, 16 states, committing: 23.9 -> 17.3 us against a walk by the long sweep's token loop with a copy of the rows per
 // wave and the partial sums in memory; 64 x 64 tokens 137 -> 93, 32 x 32 with 8 states 33.9 -> 22.5, 32 x 1 token 15.3 -> 12.6.
 //
 // A workgroup is four waves, the two directions of two adjacent tiles of 64 channels, as in kernels.h; the arithmetic of a token is
@@ -43,13 +43,14 @@ __device__ __forceinline__ void short_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-template <int N, int AKIND, int KIND, typename IO>
+template <int N, int AKIND, int KIND, typename IO, int RUN>
 __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
 {
     using T = typename IO::T;
     // (general decays of 16 states: half a tile, which leaves their factors room in the registers of three waves a SIMD; 64 x 64
     // tokens, d_inner 4096: two waves 129 us, three with a whole tile's spills 131, so 119)
     constexpr int TILE = AKIND == kAPerState && N >= 16 ? kShortTile / 2 : kShortTile;
+    constexpr int kRun = RUN > 0 && RUN < N ? RUN : N;
     constexpr bool kSeparate = KIND == kShortSeparate, kRaw = KIND == kShortAddRaw;
     const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int s = w & 1, b = blockIdx.z, L = a.L, last = L - 1;
@@ -117,7 +118,7 @@ __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
         stage_set(1, 0);
         if (two_sets) stage_set(1, 1);
     }
-    float w4[4], h[N], a2[AKIND == kAPerState ? N : 1], d2 = 0.0f;
+    float w4[4], h[N], a2[AKIND == kAPerState ? N : AKIND == kAProgression ? N / kRun : 1], d2 = 0.0f;
     load_taps(da.conv_w + (size_t)ch * a.K, a.K, w4);
     const float cb = da.conv_b ? da.conv_b[ch] : 0.0f;
     const float dval = da.D[a.d_per_head ? head : ch];
@@ -126,7 +127,8 @@ __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
 #pragma unroll
         for (int n = 0; n < N; n++) a2[n] = da.A[(size_t)head * N + n] * kLog2e;
     } else if constexpr (AKIND == kAProgression) {
-        a2[0] = da.A[(size_t)head * N] * kLog2e;
+#pragma unroll
+        for (int n = 0; n < N; n += kRun) a2[n / kRun] = da.A[(size_t)head * N + n] * kLog2e;
         d2 = (da.A[(size_t)head * N + 1] - da.A[(size_t)head * N]) * kLog2e;
     } else {
         a2[0] = da.A[head] * kLog2e;
@@ -173,14 +175,15 @@ __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
         const float xc = silu(pre), u = delta * xc;
         float y[2] = {dval * xc, 0.0f};   // (the second starts with a product)
         float an = 1.0f, ratio = 1.0f;
-        if constexpr (AKIND != kAPerState) an = fast_exp2(delta * a2[0]);
+        if constexpr (AKIND == kAScalar) an = fast_exp2(delta * a2[0]);
         if constexpr (AKIND == kAProgression) ratio = fast_exp2(delta * d2);
 #pragma unroll
         for (int n = 0; n < N; n++) {
             if constexpr (AKIND == kAPerState) an = fast_exp2(delta * a2[n]);
+            if (AKIND == kAProgression && n % kRun == 0) an = fast_exp2(delta * a2[n / kRun]);
             h[n] = fmaf(an, h[n], u * row.v[n]);
             y[n & 1] = n == 1 ? row.v[N + n] * h[n] : fmaf(row.v[N + n], h[n], y[n & 1]);
-            if constexpr (AKIND == kAProgression) an *= ratio;
+            if (AKIND == kAProgression && (n + 1) % kRun != 0) an *= ratio;
         }
         row = row_next;
         return y[0] + y[1];
@@ -255,26 +258,29 @@ __device__ __forceinline__ void short_walk(const SweepArgs& a, float* lds_all)
 
 // grid (ceil(ceil(Dn / 64) / 2), 1, batch), block 256, dynamic LDS ShortLds::total floats.  Three waves a SIMD: with the nine to twelve
 // registers more that the compiler would take, launches of many workgroups hold two (64 x 64 tokens 103 us, 64 x 16 43 -> 38).
-template <int N, int AKIND, int KIND, typename IO>
+//
+// RUN: how many states the decays of an arithmetic A are products over before the next exponential; 0: an exponential each, whatever
+// A.  The ratio's own rounding grows with the run.  Relative error of the committed state against 64 bits, 20480 chains of 16 states, 16 / 32
+// / 64 tokens: runs of sixteen 8.2 / 12.7 / 17.6e-7, of eight 4.6 / 7.6 / 12.0e-7, none 1.3 / 1.8 / 2.8e-7; 16 x 32 tokens, d_inner 4096:
+// 17.3, 17.7 and 20.7 us.  A call takes no longer run than the other forms of its size do (decay_run in bimamba_api.hip).
+template <int N, int AKIND, int KIND, typename IO, int RUN>
 __global__ __launch_bounds__(256, 3) void short_kernel(const SweepArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) float short_lds[];
-    if constexpr (AKIND == kAPerState && kProgressionEligible<N, IO>) {
-        if (a.try_progression) {   // the two-exponential form if all of a wave's chains qualify, as in sweep_kernel
-            const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-            const int ch = min(tile_of_wave<1>(w, a.Dn) * 64 + (int)(threadIdx.x & 63), a.Dn - 1);
-            const float* row = a.dir[w & 1].A + (size_t)(ch / a.P) * N;
-            const float first = row[0], step = row[1] - row[0];
-            bool ok = true;
+    if constexpr (RUN > 0) {   // the progression form if all of a wave's chains qualify, as in sweep_kernel
+        const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+        const int ch = min(tile_of_wave<1>(w, a.Dn) * 64 + (int)(threadIdx.x & 63), a.Dn - 1);
+        const float* row = a.dir[w & 1].A + (size_t)(ch / a.P) * N;
+        const float first = row[0], step = row[1] - row[0];
+        bool ok = true;
 #pragma unroll
-            for (int n = 0; n < N; n++) ok &= row[n] == fmaf((float)n, step, first);
-            if (__all(ok)) {
-                short_walk<N, kAProgression, KIND, IO>(a, short_lds);
-                return;
-            }
+        for (int n = 0; n < N; n++) ok &= row[n] == fmaf((float)n, step, first);
+        if (__all(ok)) {
+            short_walk<N, kAProgression, KIND, IO, RUN>(a, short_lds);
+            return;
         }
     }
-    short_walk<N, AKIND, KIND, IO>(a, short_lds);
+    short_walk<N, AKIND, KIND, IO, 0>(a, short_lds);
 }
 
 }  // namespace bm
