@@ -270,29 +270,32 @@ __device__ __forceinline__ void load_block(const float* src, float (&v)[N], int 
 
 // The walk of bwd_state_kernel.  WITH_D: the dh sum is wanted (some segment precedes this one in scan order).
 template <int N, typename IO, bool WITH_D>
-__device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N, IO>& w)
+__device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N, IO>& w, float4* ds)
 {
     using T = typename IO::T;
     constexpr int CT = kBwdChunk / 2, kSteps = kBwdChunk / CT;   // half a chunk at a time: what is requested ahead fits beside the sums
     const bool sp = a.dt_softplus != 0;
     const bool end_wanted = w.j1 < a.L;                   // some segment follows in scan order
     unsigned lo = (unsigned)(w.ch * sizeof(T));
-    float h[N], ds[WITH_D ? N : 1];
-    // exp(A W_t) of the dh sum, by the decays that the states take anyway: a multiplication each where an exponential of its own takes
-    // a multiplication and two issue slots more (state pass of 8 x 8192 tokens, 4096 channels: 3.19 -> 2.65 ms).  Formed anew every
-    // half chunk, so that no more than four roundings meet: products over the whole segment took the error of dDelta against 64
-    // bits from 3.3e-7 to 4.3e-7 (fp32, 4 x 2048 x 1024, 64 tokens a segment), these leave it.
-    float pd[WITH_D ? N : 1];
+    float h[N];
+    // The dh sum by chunks: exp(A W) at the chunk's start, an exponential, times what its tokens add up to with the decays counted
+    // from there, products of those that the states take anyway: a multiplication where an exponential of its own takes a
+    // multiplication and two issue slots more (state pass of 8 x 8192 tokens, 4096 channels: 3.19 -> 2.4 ms with the rest of its
+    // steps).  The sum then rounds once a chunk, which is more than the products' roundings cost: relative error against 64 bits of dB just
+    // before a segment's 29 tokens 1.45e-7 term by term with an exponential each, 1.52e-7 with products and one sum, 1.21e-7 so.
+    float pd[WITH_D ? N : 1], part[WITH_D ? N : 1];       // ds: the sum, in LDS (N / 4 places, 64 lanes apart), which 128 registers do not hold too
 #pragma unroll
     for (int n = 0; n < N; n++) h[n] = 0.0f;
     if constexpr (WITH_D) {
 #pragma unroll
         for (int n = 0; n < N; n++) {
-            ds[n] = 0.0f;
+            part[n] = 0.0f;
             pd[n] = 1.0f;
         }
+#pragma unroll
+        for (int q = 0; q < N / 4; q++) ds[q * 64] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     }
-    float wsum = 0.0f, dsum = 0.0f;
+    float wsum = 0.0f, dsum = 0.0f, d0 = 0.0f;            // Delta so far: the segment's, the window's, the window's up to the chunk
     float xh[3];                                          // raw x one, two, three tokens back in scan order
 #pragma unroll
     for (int e = 0; e < 3; e++) xh[e] = w.j0 - 1 - e >= 0 ? IO::cvt(*(const T*)(w.at(w.x, max(w.j0 - 1 - e, 0)) + lo)) : 0.0f;
@@ -321,7 +324,24 @@ __device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N
     auto add_to_d = [&](int n, float an, float dy, float c) {
         const int i = WITH_D ? n : 0;
         pd[i] *= an;
-        ds[i] = fmaf(pd[i], dy * c, ds[i]);
+        part[i] = fmaf(pd[i], dy * c, part[i]);
+    };
+    auto fold_part = [&]() {
+        float sum[N];
+#pragma unroll
+        for (int q = 0; q < N / 4; q++) {
+            const float4 v = ds[q * 64];
+            sum[4 * q] = v.x; sum[4 * q + 1] = v.y; sum[4 * q + 2] = v.z; sum[4 * q + 3] = v.w;
+        }
+        for_each_decay<N>(w, d0, [&](int n, float p) {
+            const int i = WITH_D ? n : 0;
+            sum[n] = fmaf(p, part[i], sum[n]);
+            part[i] = 0.0f;
+            pd[i] = 1.0f;
+        });
+#pragma unroll
+        for (int q = 0; q < N / 4; q++) ds[q * 64] = make_float4(sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]);
+        d0 = dsum;
     };
     // a token's B and C, requested as soon as the values of the token before have had their last use
     // (8 x 8192 tokens of 4096 channels, the whole call 9.70 -> 9.50 ms, 4 x 771 x 1536 261 -> 257 us)
@@ -348,7 +368,6 @@ __device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N
             dst_w += (size_t)a.tiles * 64;
             if (k == (w.k1 - 1) * kSteps && !end_wanted && !WITH_D) return;    // what is left feeds nothing
         }
-        if constexpr (WITH_D) for_each_decay<N>(w, dsum, [&](int n, float p) { pd[n] = p; });
         float x[CT], delta[CT];
         RawPair<IO> zg[WITH_D ? CT : 1];
 #pragma unroll
@@ -392,7 +411,7 @@ __device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N
 #pragma unroll
                 for (int n = 0; n < N; n++) {   // (a token at a time: more at once than the registers hold)
                     settle(h[n]);
-                    settle(ds[n]);
+                    settle(part[n]);
                     settle(pd[n]);
                 }
                 dsum += in_window ? delta[i] : 0.0f;
@@ -401,6 +420,7 @@ __device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N
                     for (int n = 0; n < N; n++) pd[n] = 1.0f;
                 }
             }
+            if (WITH_D && i == CT - 1 && k % kSteps == kSteps - 1) fold_part();   // (waiting for LDS would wait for a row requested before)
             request_row(first + i + 1);
         }
     }
@@ -415,13 +435,16 @@ __device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N
             dsum += delta;
             for_each_decay<N>(w, delta, [&](int n, float an) { add_to_d(n, an, dy, c[n]); });
         }
+        fold_part();
     }
     if (w.exists) {
         store_block<N>(a.seg_h + w.place(a, 1, 0) * (64 * N), h, w.lane);
         a.seg_w[w.place(a, 1, 0) * 64 + w.lane] = wsum;
         if constexpr (WITH_D) {
             const size_t half = (size_t)2 * gridDim.z * a.nseg * a.tiles * 64;
-            store_block<N>(a.seg_d + w.place(a, 1, 0) * (64 * N), ds, w.lane);
+            float* const to = a.seg_d + w.place(a, 1, 0) * (64 * N);
+#pragma unroll
+            for (int q = 0; q < N / 4; q++) *reinterpret_cast<float4*>(to + (q * 64 + w.lane) * 4) = ds[q * 64];
             a.seg_w[half + w.place(a, 1, 0) * 64 + w.lane] = dsum;
         }
     }
@@ -432,12 +455,14 @@ __device__ __forceinline__ void bwd_state_walk(const BwdArgs& a, const BwdWave<N
 template <int N, typename IO>
 __global__ __launch_bounds__(256, 4) void bwd_state_kernel(const BwdArgs a)
 {
+    __shared__ float4 sums[4][N / 4][64];   // (a lane reads what it wrote itself: no barrier)
     BwdWave<N, IO> w;
     bwd_wave_setup<N, IO>(a, w);
     if (!w.exists) return;
+    float4* const ds = &sums[threadIdx.x >> 6][0][w.lane];
     const bool with_d = w.j0 > 0;   // some segment precedes this one in scan order
-    if (with_d) bwd_state_walk<N, IO, true>(a, w);
-    else bwd_state_walk<N, IO, false>(a, w);
+    if (with_d) bwd_state_walk<N, IO, true>(a, w, ds);
+    else bwd_state_walk<N, IO, false>(a, w, ds);
 }
 
 // One thread per (direction, batch, tile, N / 4, lane, 4): the state entering each segment in scan order, and against

@@ -337,3 +337,40 @@ def test_headline_width_sampled(gpu, oracle):
     got = gpu.gpu_bwd(cfg, pf, pb, inp, None, dout)
     ref = oracle.bimamba_bwd(cfg, to_np(pf), to_np(pb), to_np(inp), None, dout[..., sel], sel=sel)
     compare(cfg, got, ref, sel=sel)
+
+
+def test_sum_over_a_segment_rounds_no_more_than_term_by_term(gpu, oracle):
+    """What a segment's tokens add to the dh of the tokens before it.  With an output gradient in the last 29 of 64 tokens only (a segment of
+    32 whose sum starts three tokens in) dB of the four tokens before the segment is that sum, a few decays and a product, of one
+    channel and here of gates and conv outputs that no rounding touches (SiLU of 20 and more).  It is no further from 64 bits than the
+    same in fp32 with the sum formed term by term and every exponential correctly rounded."""
+    batch, L, N, seg = 1024, 64, 16, 35
+    cfg = synth.mixer_cfg(batch, L, 1, d_state=N, io="f32", d_conv=1)
+    pf, pb = synth.make_params(cfg, 5, 0), synth.make_params(cfg, 5, 1)
+    inp, inp_b = synth.make_inputs(cfg, 5), synth.make_inputs(cfg, 6)
+    for p in (pf, pb):
+        p["conv_w"].fill_(1.0)
+        p["conv_b"].zero_()
+    g = torch.Generator().manual_seed(5)
+    for i in (inp, inp_b):
+        for k in ("x", "z"):
+            i[k].uniform_(20.0, 40.0, generator=g)
+    # (one channel: the batch elements bring the spread of rates that channels have)
+    inp["dt"] *= torch.exp(2.0 * torch.rand(batch, 1, 1, generator=g) - 1.0)
+    dout = np.zeros((batch, L, 1), dtype=np.float32)
+    dout[:, seg:] = np.random.default_rng(5).standard_normal((batch, L - seg, 1))
+    got = gpu.gpu_bwd(cfg, pf, pb, inp, inp_b, dout)[0]["dB"][:, 28:32, 0]
+    ref = oracle.bimamba_bwd(cfg, to_np(pf), to_np(pb), to_np(inp), to_np(inp_b), dout)[0]["dB"][:, 28:32, 0]
+    x, z, dt, C = (inp[k].numpy().reshape(batch, L, -1) for k in ("x", "z", "dt", "C"))
+    a2 = (pf["A"].numpy()[0] * np.float32(np.log2(np.e))).astype(np.float32)
+    decay = lambda w: np.exp2((w * a2).astype(np.float64)).astype(np.float32)
+    dh, w = np.zeros((batch, N), np.float32), np.zeros((batch, 1), np.float32)
+    for t in range(seg, L):
+        w = w + dt[:, t]
+        dh = ((dout[:, t] * z[:, t] * decay(w)).astype(np.float64) * C[:, t] + dh).astype(np.float32)
+    plain = np.empty_like(got)
+    for t in range(seg - 1, 27, -1):
+        if t < 32:
+            plain[:, t - 28] = dh * (dt[:, t] * x[:, t])
+        dh = dh * decay(dt[:, t])
+    assert rel_all(got, ref) < rel_all(plain, ref), (rel_all(got, ref), rel_all(plain, ref))
