@@ -491,18 +491,16 @@ int decay_run(const bimamba_desc* d)
     return row_size ? 0 : enough_chains(d, waves_of(d, 1)) ? 16 : 8;
 }
 
-void launch_scan(const bimamba_desc* d, int split, int short_call, const SweepArgs& sa, const CarryArgs& ca,
-                 hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
+hipError_t launch_scan(const bimamba_desc* d, int split, int short_call, const SweepArgs& sa, const CarryArgs& ca,
+                       hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     const int scalar_a = d->a_kind == BIMAMBA_A_SCALAR_PER_HEAD, bf16 = d->io_dtype == BIMAMBA_BF16;
 #define BM_CASE(n, s) \
-    case (n) * 8 + (s):                                                                                          \
-        launch_scan_n##n##_s##s(scalar_a, bf16, sa, ca, d->batch, short_call, st, ev_start, ev_stop);              \
-        break;
+    case (n) * 8 + (s): return launch_scan_n##n##_s##s(scalar_a, bf16, sa, ca, d->batch, short_call, st, ev_start, ev_stop);
     switch (d->d_state * 8 + split) {
         BM_CASE(4, 1) BM_CASE(8, 1) BM_CASE(16, 1) BM_CASE(16, 2) BM_CASE(16, 4) BM_CASE(32, 1) BM_CASE(32, 2)
         BM_CASE(32, 4) BM_CASE(64, 1) BM_CASE(64, 4) BM_CASE(128, 1) BM_CASE(128, 4)
-        default: break;
+        default: return hipErrorInvalidValue;
     }
 #undef BM_CASE
 }
@@ -637,7 +635,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
             ba.dt_softplus = d->dt_softplus; ba.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD; ba.conv_bc = d->conv_bc;
             ba.separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
             ba.shared = same_tensor(in_f->x, in_b->x) && same_tensor(in_f->z, in_b->z);
-            launch_ssd_block_prep(d->d_state, ba, st);
+            if (launch_ssd_block_prep(d->d_state, ba, st) != hipSuccess) return BIMAMBA_ERR_HIP;   // (nothing is committed)
             if (probe_start) (void)hipEventRecord(probe_start, st);
             launch_ssd_block(d->d_state, ba, st);
             if (probe_stop) (void)hipEventRecord(probe_stop, st);
@@ -661,7 +659,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                 pa.L = d->seqlen; pa.G = d->n_groups; pa.dir = s == 0 ? 1 : -1;
                 pa.wide = wide;
             }
-            launch_ssd_prep(d->d_state, pp, plan.ssd_chunks, d->batch, st);
+            if (launch_ssd_prep(d->d_state, pp, plan.ssd_chunks, d->batch, st) != hipSuccess) return BIMAMBA_ERR_HIP;
             if (probe_start) (void)hipEventRecord(probe_start, st);
             auto scan_args = [&](int s) {
                 const bimamba_inputs* in = s == 0 ? in_f : in_b;
@@ -712,10 +710,10 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                 sp.dir[1] = scan_args(1);
                 if (!separate) {   // (the forward direction adds what the reverse one parked)
                     sp.dir[0] = sp.dir[1];
-                    launch_ssd_scan(d->d_state, head_width, sp, 1, d->batch, st);
+                    if (launch_ssd_scan(d->d_state, head_width, sp, 1, d->batch, st) != hipSuccess) return BIMAMBA_ERR_HIP;
                 }
                 sp.dir[0] = scan_args(0);
-                launch_ssd_scan(d->d_state, head_width, sp, separate ? 2 : 1, d->batch, st);
+                if (launch_ssd_scan(d->d_state, head_width, sp, separate ? 2 : 1, d->batch, st) != hipSuccess) return BIMAMBA_ERR_HIP;
             }
             if (probe_stop) (void)hipEventRecord(probe_stop, st);
         } else {
@@ -752,7 +750,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
         ca.carry = sa.carry; ca.sumdt = sa.sumdt; ca.A[0] = pf->A; ca.A[1] = pb->A;
         ca.h_in = sa.h_in; ca.h_out = sa.h_out;
         ca.batch = d->batch; ca.nseg = plan.nseg; ca.Dn = d->d_inner; ca.P = sa.P;
-        launch_scan(d, plan.split, one_launch, sa, ca, st, probe_start, probe_stop);
+        if (launch_scan(d, plan.split, one_launch, sa, ca, st, probe_start, probe_stop) != hipSuccess) return BIMAMBA_ERR_HIP;
         }
         }
     } else if (block_variant && d->batch > 0 && h_out && h_out != h_in) {

@@ -25,23 +25,15 @@ private:
     std::atomic<bool> raised_[kMaxDevices] = {};
 };
 
-// For the kernels whose limit is raised without a check: idempotent, done once per (kernel, device).
-constexpr int kMaxSeenDevices = 64;
-inline bool first_use_on_current_device(std::atomic<bool>* seen)
-{
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxSeenDevices) return true;
-    return !seen[dev].exchange(true);
-}
-
 // Compute units of the current device (256 when no device answers), asked once per device; defined in bimamba_api.hip
 // and used by the host-side plan and by every launcher, so that all of them size a launch for the same chip.
 int cu_count();
 
+// Launchers that return an error have launched nothing, or nothing but what writes the call's workspace.
 #define BM_DECLARE_SCAN(n, s)                                                                                      \
-    void launch_scan_n##n##_s##s(int a_scalar_per_head, int io_bf16, const SweepArgs& sa, const CarryArgs& ca,     \
-                                 int batch, int short_call, hipStream_t st, hipEvent_t ev_start,                   \
-                                 hipEvent_t ev_stop);
+    hipError_t launch_scan_n##n##_s##s(int a_scalar_per_head, int io_bf16, const SweepArgs& sa, const CarryArgs& ca, \
+                                       int batch, int short_call, hipStream_t st, hipEvent_t ev_start,             \
+                                       hipEvent_t ev_stop);
 BM_DECLARE_SCAN(4, 1)
 BM_DECLARE_SCAN(8, 1)
 BM_DECLARE_SCAN(16, 1)
@@ -73,16 +65,16 @@ struct SsdArgs;
 struct SsdCarryArgs;
 struct SsdStatePair;
 bool ssd_supported(int d_state, int headdim);
-void launch_ssd_prep(int d_state, const SsdPrepPair& pa, int nchunk, int batch, hipStream_t st);
-void launch_ssd_scan(int d_state, int headdim, const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
+hipError_t launch_ssd_prep(int d_state, const SsdPrepPair& pa, int nchunk, int batch, hipStream_t st);   // (an error: nothing was launched)
+hipError_t launch_ssd_scan(int d_state, int headdim, const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
 // (the many-wave form of the scan; defined in ssd_wide_inst.hip, one object per (d_state, head width))
-void launch_ssd_wide_n128_p64(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
-void launch_ssd_wide_n128_p32(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
-void launch_ssd_wide_n64_p64(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
-void launch_ssd_wide_n64_p32(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
+hipError_t launch_ssd_wide_n128_p64(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
+hipError_t launch_ssd_wide_n128_p32(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
+hipError_t launch_ssd_wide_n64_p64(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
+hipError_t launch_ssd_wide_n64_p32(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
 void launch_ssd_carry(int d_state, const SsdCarryArgs& ca, hipStream_t st);
 struct SsdBlockArgs;
-void launch_ssd_block_prep(int d_state, const SsdBlockArgs& a, hipStream_t st);   // (calls of one chunk: ssd_block.h)
+hipError_t launch_ssd_block_prep(int d_state, const SsdBlockArgs& a, hipStream_t st);   // (calls of one chunk: ssd_block.h)
 void launch_ssd_block(int d_state, const SsdBlockArgs& a, hipStream_t st);
 void launch_ssd_state(int d_state, int headdim, const SsdStatePair& sp, int subs, int batch, hipStream_t st);
 

@@ -126,26 +126,32 @@ struct Tiled {
 
 #if BM_S == 1 && BM_N <= 16
 template <int AKIND, int KIND, typename IO, int RUN>
-static void launch_short_run(const SweepArgs& sa, int batch, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
+static hipError_t launch_short_run(const SweepArgs& sa, int batch, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     static KernelFit fit;
     const auto kernel = short_kernel<BM_N, AKIND, KIND, IO, RUN>;
     const dim3 grid((unsigned)(((sa.Dn + 63) / 64 + 1) / 2), 1, (unsigned)batch);
     const int need = ShortLds(sa.L, BM_N, !sa.same_bc, sa.G > 1, KIND == kShortSeparate).total * (int)sizeof(float);
+    if (need > 64 * 1024) {
+        static LdsLimit limit;
+        const hipError_t err = limit.raise(reinterpret_cast<const void*>(kernel), kLdsPerCu);
+        if (err != hipSuccess) return err;
+    }
     const unsigned lds = spread_lds(kernel, &fit, grid, need);
     if (ev_start) (void)hipEventRecord(ev_start, st);
     hipLaunchKernelGGL(kernel, grid, dim3(kBlock), lds, st, sa);
     if (ev_stop) (void)hipEventRecord(ev_stop, st);
+    return hipSuccess;
 }
 
 template <int AKIND, int KIND, typename IO>
-static void launch_short(const SweepArgs& sa, int batch, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
+static hipError_t launch_short(const SweepArgs& sa, int batch, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     if constexpr (AKIND == kAPerState && kProgressionEligible<BM_N, IO>) {
         if (BM_N > 8 && sa.try_progression > 8) return launch_short_run<AKIND, KIND, IO, BM_N>(sa, batch, st, ev_start, ev_stop);
         if (sa.try_progression) return launch_short_run<AKIND, KIND, IO, (BM_N < 8 ? BM_N : 8)>(sa, batch, st, ev_start, ev_stop);
     }
-    launch_short_run<AKIND, KIND, IO, 0>(sa, batch, st, ev_start, ev_stop);
+    return launch_short_run<AKIND, KIND, IO, 0>(sa, batch, st, ev_start, ev_stop);
 }
 #endif
 
@@ -153,15 +159,14 @@ static void launch_short(const SweepArgs& sa, int batch, hipStream_t st, hipEven
 // SIMD holds few waves, the shallow one needs fewer registers, so more waves are resident at once.  The shallow tile
 // is taken when it gets the launch through in fewer rounds of resident workgroups.
 template <int AKIND, typename IO>
-static void launch_one(const SweepArgs& sa, const CarryArgs& ca, int batch, int short_call, hipStream_t st,
+static hipError_t launch_one(const SweepArgs& sa, const CarryArgs& ca, int batch, int short_call, hipStream_t st,
                        hipEvent_t ev_start, hipEvent_t ev_stop)
 {
 #if BM_S == 1 && BM_N <= 16
     if (short_call) {
-        if (sa.separate) launch_short<AKIND, kShortSeparate, IO>(sa, batch, st, ev_start, ev_stop);
-        else if (sa.raw_partial) launch_short<AKIND, kShortAddRaw, IO>(sa, batch, st, ev_start, ev_stop);
-        else launch_short<AKIND, kShortAdd, IO>(sa, batch, st, ev_start, ev_stop);
-        return;
+        if (sa.separate) return launch_short<AKIND, kShortSeparate, IO>(sa, batch, st, ev_start, ev_stop);
+        if (sa.raw_partial) return launch_short<AKIND, kShortAddRaw, IO>(sa, batch, st, ev_start, ev_stop);
+        return launch_short<AKIND, kShortAdd, IO>(sa, batch, st, ev_start, ev_stop);
     }
 #endif
     (void)short_call;
@@ -172,10 +177,11 @@ static void launch_one(const SweepArgs& sa, const CarryArgs& ca, int batch, int 
     const int dev = current_device();
     if (rounds(per_cu, Shallow::fit_sweep.ask(Shallow::sweep, dev)) < rounds(per_cu, Deep::fit_sweep.ask(Deep::sweep, dev))) {
         Shallow::launch(sa, ca, batch, st, ev_start, ev_stop);
-        return;
+        return hipSuccess;
     }
 #endif
     Deep::launch(sa, ca, batch, st, ev_start, ev_stop);
+    return hipSuccess;
 }
 
 }  // namespace
@@ -183,16 +189,15 @@ static void launch_one(const SweepArgs& sa, const CarryArgs& ca, int batch, int 
 #define BM_CAT4(a, b, c, d) a##b##c##d
 #define BM_NAME(n, s) BM_CAT4(launch_scan_n, n, _s, s)
 
-void BM_NAME(BM_N, BM_S)(int a_scalar_per_head, int io_bf16, const SweepArgs& sa, const CarryArgs& ca, int batch,
-                         int short_call, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
+hipError_t BM_NAME(BM_N, BM_S)(int a_scalar_per_head, int io_bf16, const SweepArgs& sa, const CarryArgs& ca, int batch,
+                               int short_call, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop)
 {
     if (a_scalar_per_head) {
-        if (io_bf16) launch_one<1, IoBF16>(sa, ca, batch, short_call, st, ev_start, ev_stop);
-        else launch_one<1, IoF32>(sa, ca, batch, short_call, st, ev_start, ev_stop);
-    } else {
-        if (io_bf16) launch_one<0, IoBF16>(sa, ca, batch, short_call, st, ev_start, ev_stop);
-        else launch_one<0, IoF32>(sa, ca, batch, short_call, st, ev_start, ev_stop);
+        if (io_bf16) return launch_one<1, IoBF16>(sa, ca, batch, short_call, st, ev_start, ev_stop);
+        return launch_one<1, IoF32>(sa, ca, batch, short_call, st, ev_start, ev_stop);
     }
+    if (io_bf16) return launch_one<0, IoBF16>(sa, ca, batch, short_call, st, ev_start, ev_stop);
+    return launch_one<0, IoF32>(sa, ca, batch, short_call, st, ev_start, ev_stop);
 }
 
 }  // namespace bm

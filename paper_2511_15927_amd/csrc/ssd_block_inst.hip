@@ -2,19 +2,20 @@
 #include "ssd_block.h"
 #include "launch.h"
 
-#include <atomic>
-
 namespace bm {
 
 template <int N, int BLOCKS>
-static void prep_one(const SsdBlockArgs& a, hipStream_t st)
+static hipError_t prep_one(const SsdBlockArgs& a, hipStream_t st)
 {
-    static std::atomic<bool> seen[kMaxSeenDevices];
+    static LdsLimit limit;
     constexpr size_t lds = ssd_block_prep_lds<N, BLOCKS>();
     auto prep = ssd_block_prep_kernel<N, BLOCKS>;
-    if (lds > 64 * 1024 && first_use_on_current_device(seen))
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(prep), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (lds > 64 * 1024) {
+        const hipError_t err = limit.raise(reinterpret_cast<const void*>(prep), lds);
+        if (err != hipSuccess) return err;
+    }
     hipLaunchKernelGGL(prep, dim3((unsigned)a.G, 2, (unsigned)a.batch), dim3(1024), lds, st, a);
+    return hipSuccess;
 }
 
 template <int N, int BLOCKS>
@@ -30,10 +31,10 @@ static void launch_one(const SsdBlockArgs& a, hipStream_t st)
     }
 }
 
-void launch_ssd_block_prep(int d_state, const SsdBlockArgs& a, hipStream_t st)
+hipError_t launch_ssd_block_prep(int d_state, const SsdBlockArgs& a, hipStream_t st)
 {
-    if (d_state == 128) a.L <= 32 ? prep_one<128, 1>(a, st) : prep_one<128, 2>(a, st);
-    else a.L <= 32 ? prep_one<64, 1>(a, st) : prep_one<64, 2>(a, st);
+    if (d_state == 128) return a.L <= 32 ? prep_one<128, 1>(a, st) : prep_one<128, 2>(a, st);
+    return a.L <= 32 ? prep_one<64, 1>(a, st) : prep_one<64, 2>(a, st);
 }
 
 void launch_ssd_block(int d_state, const SsdBlockArgs& a, hipStream_t st)

@@ -2,62 +2,57 @@
 #include "ssd_kernels.h"
 #include "launch.h"
 
-#include <atomic>
-
 namespace bm {
 
 template <int N, int THREADS>
-static void prep_variant(const SsdPrepPair& pa, int nchunk, int batch, hipStream_t st)
+static hipError_t prep_variant(const SsdPrepPair& pa, int nchunk, int batch, hipStream_t st)
 {
-    static std::atomic<bool> seen[kMaxSeenDevices];
+    static LdsLimit limit;
     constexpr size_t lds = ssd_prep_lds_bytes<N, THREADS>();
     auto kernel = ssd_prep_kernel<N, THREADS>;
-    if (first_use_on_current_device(seen))
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (lds > 64 * 1024) {
+        const hipError_t err = limit.raise(reinterpret_cast<const void*>(kernel), lds);
+        if (err != hipSuccess) return err;
+    }
     hipLaunchKernelGGL(kernel, dim3((unsigned)nchunk, (unsigned)pa.dir[0].G, 2u * (unsigned)batch), dim3(THREADS), lds, st, pa);
+    return hipSuccess;
 }
 
 template <int N, int P>
-static void scan_variant(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
+static hipError_t scan_variant(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    static std::atomic<bool> seen[kMaxSeenDevices];
+    static LdsLimit limit;
     constexpr size_t lds = SsdLds<N, P>::bytes();
     auto kernel = ssd_kernel<N, P>;
-    if (first_use_on_current_device(seen))
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t err = limit.raise(reinterpret_cast<const void*>(kernel), lds);
+    if (err != hipSuccess) return err;
     hipLaunchKernelGGL(kernel, dim3((unsigned)sp.dir[0].H, (unsigned)dirs, (unsigned)batch), dim3(4 * P + 256), lds, st, sp);
+    return hipSuccess;
 }
 
 template <int N, int P>
-static void launch_ssd_wide(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
+static hipError_t launch_ssd_wide(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    if constexpr (N == 128 && P == 64) launch_ssd_wide_n128_p64(sp, dirs, batch, st);
-    else if constexpr (N == 128) launch_ssd_wide_n128_p32(sp, dirs, batch, st);
-    else if constexpr (P == 64) launch_ssd_wide_n64_p64(sp, dirs, batch, st);
-    else launch_ssd_wide_n64_p32(sp, dirs, batch, st);
+    if constexpr (N == 128 && P == 64) return launch_ssd_wide_n128_p64(sp, dirs, batch, st);
+    else if constexpr (N == 128) return launch_ssd_wide_n128_p32(sp, dirs, batch, st);
+    else if constexpr (P == 64) return launch_ssd_wide_n64_p64(sp, dirs, batch, st);
+    else return launch_ssd_wide_n64_p32(sp, dirs, batch, st);
 }
 
 template <int N, int P>
-static void scan_one(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
+static hipError_t scan_one(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    const SsdArgs& sa = sp.dir[0];
-    if (sa.wide) launch_ssd_wide<N, P>(sp, dirs, batch, st);
-    else scan_variant<N, P>(sp, dirs, batch, st);
+    return sp.dir[0].wide ? launch_ssd_wide<N, P>(sp, dirs, batch, st) : scan_variant<N, P>(sp, dirs, batch, st);
 }
 
 bool ssd_supported(int d_state, int headdim) { return (d_state == 64 || d_state == 128) && (headdim == 32 || headdim == 64); }
 
 // Launches that give a CU at most one workgroup take the sixteen-wave form: their duration is one workgroup's chain.
-void launch_ssd_prep(int d_state, const SsdPrepPair& pa, int nchunk, int batch, hipStream_t st)
+hipError_t launch_ssd_prep(int d_state, const SsdPrepPair& pa, int nchunk, int batch, hipStream_t st)
 {
     const bool wide = 2LL * nchunk * pa.dir[0].G * batch <= cu_count();
-    if (d_state == 128) {
-        if (wide) prep_variant<128, 1024>(pa, nchunk, batch, st);
-        else prep_variant<128, 256>(pa, nchunk, batch, st);
-    } else {
-        if (wide) prep_variant<64, 1024>(pa, nchunk, batch, st);
-        else prep_variant<64, 256>(pa, nchunk, batch, st);
-    }
+    if (d_state == 128) return wide ? prep_variant<128, 1024>(pa, nchunk, batch, st) : prep_variant<128, 256>(pa, nchunk, batch, st);
+    return wide ? prep_variant<64, 1024>(pa, nchunk, batch, st) : prep_variant<64, 256>(pa, nchunk, batch, st);
 }
 
 void launch_ssd_carry(int d_state, const SsdCarryArgs& ca, hipStream_t st)
@@ -82,12 +77,13 @@ void launch_ssd_state(int d_state, int headdim, const SsdStatePair& sp, int subs
 // dirs 1: the direction sp.dir[0]; dirs 2: both in one launch, for calls whose directions write halves of their own.  A
 // workgroup holds a CU and a call's time is its longest chain of chunks, so two launches that each leave CUs empty take
 // twice as long as one: 120 heads x 32, N 128, 1 x 1024 tokens 72.2 -> 38.1 us a call.
-void launch_ssd_scan(int d_state, int headdim, const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
+hipError_t launch_ssd_scan(int d_state, int headdim, const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    if (d_state == 128 && headdim == 64) scan_one<128, 64>(sp, dirs, batch, st);
-    else if (d_state == 128 && headdim == 32) scan_one<128, 32>(sp, dirs, batch, st);
-    else if (d_state == 64 && headdim == 64) scan_one<64, 64>(sp, dirs, batch, st);
-    else if (d_state == 64 && headdim == 32) scan_one<64, 32>(sp, dirs, batch, st);
+    if (d_state == 128 && headdim == 64) return scan_one<128, 64>(sp, dirs, batch, st);
+    if (d_state == 128 && headdim == 32) return scan_one<128, 32>(sp, dirs, batch, st);
+    if (d_state == 64 && headdim == 64) return scan_one<64, 64>(sp, dirs, batch, st);
+    if (d_state == 64 && headdim == 32) return scan_one<64, 32>(sp, dirs, batch, st);
+    return hipErrorInvalidValue;
 }
 
 }  // namespace bm

@@ -2,26 +2,27 @@
 #include "ssd_wide.h"
 #include "launch.h"
 
-#include <atomic>
-
 namespace bm {
 
 template <int HEADS, int MODE, bool PARTS>
-static void variant(const SsdStatePair& sp, int batch, hipStream_t st)
+static hipError_t variant(const SsdStatePair& sp, int batch, hipStream_t st)
 {
-    static std::atomic<bool> seen[kMaxSeenDevices];
+    static LdsLimit limit;
     using W = SsdWide<BM_N, BM_P, HEADS>;
     auto kernel = ssd_wide_kernel<BM_N, BM_P, HEADS, MODE, PARTS>;
-    if (first_use_on_current_device(seen))
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)W::bytes());
+    if (W::bytes() > 64 * 1024) {
+        const hipError_t err = limit.raise(reinterpret_cast<const void*>(kernel), W::bytes());
+        if (err != hipSuccess) return err;
+    }
     const unsigned parts = PARTS ? (unsigned)sp.dir[0].parts : 1u;
     const dim3 grid((unsigned)(sp.dir[0].H / HEADS), MODE == kSsdFinalOnly ? 2u * parts : parts, (unsigned)batch), block(W::kThreads);
     if constexpr (MODE == kSsdFinalOnly) hipLaunchKernelGGL(kernel, grid, block, W::bytes(), st, sp);
     else hipLaunchKernelGGL(kernel, grid, block, W::bytes(), st, sp.dir[0]);
+    return hipSuccess;
 }
 
 template <int HEADS, bool PARTS>
-static void launch(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
+static hipError_t launch(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     if (dirs == 2) return variant<HEADS, kSsdFinalOnly, PARTS>(sp, batch, st);
     switch (sp.dir[0].mode) {
@@ -36,12 +37,12 @@ static void launch(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 #define BM_NAME(n, p) BM_NAME2(n, p)
 
 // Two heads to a workgroup once one head each would not fit the chip at once: they share the tiles of their group.
-void BM_NAME(BM_N, BM_P)(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
+hipError_t BM_NAME(BM_N, BM_P)(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     const SsdArgs& sa = sp.dir[0];
-    if (sa.parts > 1) launch<1, true>(sp, dirs, batch, st);
-    else if (sa.HG % 2 == 0 && (long long)sa.H * batch * dirs > cu_count()) launch<2, false>(sp, dirs, batch, st);
-    else launch<1, false>(sp, dirs, batch, st);
+    if (sa.parts > 1) return launch<1, true>(sp, dirs, batch, st);
+    if (sa.HG % 2 == 0 && (long long)sa.H * batch * dirs > cu_count()) return launch<2, false>(sp, dirs, batch, st);
+    return launch<1, false>(sp, dirs, batch, st);
 }
 
 }  // namespace bm

@@ -1,9 +1,10 @@
 // Host program of test_first_use_threads.py: calls libbimamba.so with the HIP runtime's entry points replaced by the ones
 // below (the executable's symbols come first in the lookup order), so no GPU is needed.  They model one rule of the real
 // ones: a launch with more than 64 KB of dynamic LDS is refused until the kernel's limit has been raised.
-//   race fwd|bwd   a second host thread makes its first call while the first one is inside the raising
-//   fail fwd|bwd   the raising fails on the first call only
-// Prints the two calls' return codes, the launches and the refused launches.
+//   race CALL     a second host thread makes its first call while the first one is inside the raising
+//   fail CALL N   the N-th raising (from 1) fails
+// CALL: fwd, bwd, block (short calls of lane-per-chain kernels), m2 (chunked Mamba-2, several chunks), m2_block (one chunk).
+// Prints the two calls' return codes, the launches, the refused launches and the launches of the first call ("fail" only).
 #include "bimamba.h"
 
 #include <dlfcn.h>
@@ -11,6 +12,7 @@
 #include <atomic>
 #include <chrono>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <map>
 #include <mutex>
@@ -22,7 +24,7 @@ struct dim3 {
 
 static std::mutex g_lock;
 static std::map<const void*, int> g_limit;
-static std::atomic<int> g_raising{0}, g_launches{0}, g_refused{0}, g_failures_left{0};
+static std::atomic<int> g_raising{0}, g_launches{0}, g_refused{0}, g_fails{0};
 static bool g_slow = false;
 static thread_local struct {
     dim3 grid, block;
@@ -33,12 +35,13 @@ static thread_local struct {
 extern "C" {
 int hipGetDevice(int* dev) { *dev = 0; return 0; }
 int hipDeviceGetAttribute(int* v, int, int) { *v = 256; return 0; }
+int hipFuncGetAttributes(void*, const void*) { return 1; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 3; return 0; }
 int hipPeekAtLastError() { return 0; }
 int hipGetLastError() { return 0; }
 int hipFuncSetAttribute(const void* fn, int, int value)
 {
-    g_raising++;
-    if (g_failures_left.fetch_sub(1) > 0) return 1;
+    if (++g_raising == g_fails) return 1;
     if (g_slow) std::this_thread::sleep_for(std::chrono::milliseconds(300));
     std::lock_guard<std::mutex> hold(g_lock);
     g_limit[fn] = value;
@@ -68,7 +71,7 @@ int hipLaunchKernel(const void* fn, dim3, dim3, void**, size_t lds, void*)
 
 int main(int argc, char** argv)
 {
-    if (argc != 4) return 2;
+    if (argc < 4) return 2;
     void* lib = dlopen(argv[1], RTLD_NOW);
     if (!lib) {
         fprintf(stderr, "%s\n", dlerror());
@@ -76,18 +79,29 @@ int main(int argc, char** argv)
     }
     auto fwd = (decltype(&bimamba_fwd))dlsym(lib, "bimamba_fwd");
     auto bwd = (decltype(&bimamba_bwd))dlsym(lib, "bimamba_bwd");
-    const bool forward = !strcmp(argv[3], "fwd");
-    // 256 tokens with activations per direction: 74 KB of B and C rows; the gradient walk takes 80 KB for 16 states
+    auto block = (decltype(&bimamba_block_fwd))dlsym(lib, "bimamba_block_fwd");
+    auto is = [&](const char* call) { return !strcmp(argv[3], call); };
+    // fwd, bwd: 256 tokens with activations per direction: 74 KB of B and C rows; the gradient walk takes 80 KB for 16 states
     bimamba_desc d{};
     d.struct_size = sizeof d;
     d.batch = 1; d.seqlen = 256; d.d_inner = 64; d.d_state = 16; d.n_heads = 64; d.n_groups = 1; d.d_conv = 4;
     d.io_dtype = BIMAMBA_BF16;
+    if (is("block")) {   // 65 KB: four sets of B and C rows and what the directions leave for each other
+        d.seqlen = 64; d.d_inner = d.n_heads = 128; d.n_groups = 2; d.state_split = 1;
+    } else if (is("m2") || is("m2_block")) {   // the preparation takes up to 118 KB, the walk of several chunks 115
+        d.seqlen = is("m2") ? 128 : 64;
+        d.d_inner = 128; d.n_heads = 2; d.d_state = 128;
+        d.a_kind = BIMAMBA_A_SCALAR_PER_HEAD; d.d_kind = BIMAMBA_D_PER_HEAD; d.dt_softplus = d.conv_bc = 1;
+    }
     uintptr_t next = 1 << 20;      // addresses that nothing reads
     auto place = [&] { return (void*)(next += 1 << 20); };
-    auto view = [&](int64_t ch) { return bimamba_tensor{place(), 256 * ch, ch}; };
-    auto inputs = [&] { return bimamba_inputs{view(64), view(64), view(64), view(16), view(16)}; };
+    auto view = [&](int64_t ch) { return bimamba_tensor{place(), d.seqlen * ch, ch}; };
+    const int gn = d.n_groups * d.d_state;
+    auto inputs = [&] { return bimamba_inputs{view(d.d_inner), view(d.d_inner), view(d.n_heads), view(gn), view(gn)}; };
     const bimamba_inputs f = inputs(), b = inputs();
-    const bimamba_tensor out = view(64);
+    const bimamba_tensor out = view(d.d_inner);
+    float* const state = (float*)place();
+    void* const tail = place();
     const float* any = (const float*)place();
     const bimamba_params p{any, any, any, any, nullptr};
     const bimamba_input_grads gf{view(64), view(64), view(64), (float*)place(), (float*)place()};
@@ -95,10 +109,11 @@ int main(int argc, char** argv)
     const bimamba_param_grads qf{(float*)place(), nullptr, (float*)place(), (float*)place(), nullptr}, qb = qf;
     void* ws = place();
     auto call = [&] {
-        return forward ? fwd(&d, &p, &p, &f, &b, &out, ws, (size_t)1 << 40, nullptr)
-                       : bwd(&d, &p, &p, &f, &b, &out, &gf, &gb, &qf, &qb, ws, (size_t)1 << 40, nullptr);
+        if (is("fwd")) return fwd(&d, &p, &p, &f, &b, &out, ws, (size_t)1 << 40, nullptr);
+        if (is("bwd")) return bwd(&d, &p, &p, &f, &b, &out, &gf, &gb, &qf, &qb, ws, (size_t)1 << 40, nullptr);
+        return block(&d, &p, &p, &f, &b, state, tail, state, tail, &out, ws, (size_t)1 << 40, nullptr);   // commits in place
     };
-    int first = 0, second = 0;
+    int first = 0, second = 0, of_first = 0;
     if (!strcmp(argv[2], "race")) {
         g_slow = true;
         std::thread t([&] { first = call(); });
@@ -106,10 +121,11 @@ int main(int argc, char** argv)
         second = call();
         t.join();
     } else {
-        g_failures_left = 1;
+        g_fails = atoi(argv[4]);
         first = call();
+        of_first = g_launches;
         second = call();
     }
-    printf("%d %d %d %d\n", first, second, g_launches.load(), g_refused.load());
+    printf("%d %d %d %d %d\n", first, second, g_launches.load(), g_refused.load(), of_first);
     return 0;
 }

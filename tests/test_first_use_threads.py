@@ -17,20 +17,22 @@ def program(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-rdynamic", "-pthread", "-I", os.path.join(os.path.dirname(HERE), "include"),
                     os.path.join(HERE, "first_use_threads.cpp"), "-o", exe, "-ldl"], check=True)
 
-    def run(mode, entry):
-        r = subprocess.run([exe, bd.LIB_PATH, mode, entry], stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=120)
+    def run(*args):
+        r = subprocess.run([exe, bd.LIB_PATH, *map(str, args)], stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=120)
         assert r.returncode == 0, r.stderr
         return [int(v) for v in r.stdout.split()]
     return run
 
 
-@pytest.mark.parametrize("entry", ["fwd", "bwd"])
+@pytest.mark.parametrize("entry", ["fwd", "bwd", "block", "m2", "m2_block"])
 def test_a_second_thread_does_not_launch_under_a_limit_still_being_raised(program, entry):
-    first, second, launches, refused = program("race", entry)
+    first, second, launches, refused, _ = program("race", entry)
     assert (first, second, refused) == (0, 0, 0) and launches >= 2
 
 
-@pytest.mark.parametrize("entry", ["fwd", "bwd"])
-def test_a_failed_raising_is_reported_and_tried_again(program, entry):
-    first, second, launches, refused = program("fail", entry)
-    assert (first, second, refused) == (ERR_HIP, 0, 0) and launches >= 1
+# (the raising that fails, and what was launched before it: the preparations and the direction that parks, into the workspace)
+@pytest.mark.parametrize("entry,failing,before", [("fwd", 1, 0), ("bwd", 1, 1), ("block", 1, 0), ("m2_block", 1, 0),
+                                                  ("m2", 1, 0), ("m2", 2, 1), ("m2", 3, 2)])
+def test_a_failed_raising_is_reported_and_tried_again(program, entry, failing, before):
+    first, second, launches, refused, of_first = program("fail", entry, failing)
+    assert (first, second, refused, of_first) == (ERR_HIP, 0, 0, before) and launches > of_first
