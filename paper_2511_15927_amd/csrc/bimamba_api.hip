@@ -13,7 +13,6 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
-#include <cstdlib>
 
 // Device memory of bimamba_block_fwd_static, the entry point for callers that cannot allocate: one copy per GPU, held
 // until the process ends.  In host code this name only identifies the symbol; the address a kernel can use is asked
@@ -529,13 +528,11 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
     // the chunked kernels read x two channels at a time and the carried state four states at a time
     if (plan.ssd && !(pairs_readable(in_f->x) && pairs_readable(in_b->x) && is_aligned(h_in, 16) && is_aligned(h_out, 16)))
         plan.ssd = false;
-    // the many-wave walk addresses a chunk's gate and output rows with 32-bit byte offsets, the state pass of the time parts
-    // its rows of x; parts come with both
-    constexpr int64_t kMaxWideStride = 1 << 24;
-    const bool wide = plan.ssd && plan.ssd_chunks >= 2 && in_f->z.stride_token <= kMaxWideStride &&
-                      in_b->z.stride_token <= kMaxWideStride && out->stride_token <= kMaxWideStride && !getenv("BIMAMBA_NO_WIDE");
-    if (plan.ssd && plan.ssd_parts > 1 &&
-        (!wide || in_f->x.stride_token > kMaxWideStride || in_b->x.stride_token > kMaxWideStride)) {
+    // the state pass of the time parts addresses a chunk's rows of x with 32-bit byte offsets, the walk its rows of z and out
+    // (where it can: SsdArgs::far)
+    constexpr int64_t kMaxNearStride = 1 << 24;
+    const bool far = in_f->z.stride_token > kMaxNearStride || in_b->z.stride_token > kMaxNearStride || out->stride_token > kMaxNearStride;
+    if (plan.ssd && plan.ssd_parts > 1 && (in_f->x.stride_token > kMaxNearStride || in_b->x.stride_token > kMaxNearStride)) {
         plan.ssd_parts = plan.ssd_subs = plan.ssd_part_subs = 1;
         plan.ssd_part_chunks = plan.ssd_sub_chunks = plan.ssd_chunks;
     }
@@ -657,7 +654,6 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                 pa.b_t = reinterpret_cast<__bf16*>(ws + plan.off_bt[s]);
                 pa.score_op = reinterpret_cast<float*>(ws + plan.off_score[s]);
                 pa.L = d->seqlen; pa.G = d->n_groups; pa.dir = s == 0 ? 1 : -1;
-                pa.wide = wide;
             }
             if (launch_ssd_prep(d->d_state, pp, plan.ssd_chunks, d->batch, st) != hipSuccess) return BIMAMBA_ERR_HIP;
             if (probe_start) (void)hipEventRecord(probe_start, st);
@@ -679,14 +675,15 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                 sa.G = d->n_groups; sa.K = d->d_conv; sa.tail_ch = tail_ch; sa.nchunk = plan.ssd_chunks;
                 sa.parts = plan.ssd_parts; sa.part_chunks = plan.ssd_part_chunks;
                 sa.part_subs = plan.ssd_part_subs; sa.sub_chunks = plan.ssd_sub_chunks;
-                sa.part_state = reinterpret_cast<float*>(ws + plan.off_pstate[s]);
+                // (a call in one part enters it with the caller's state)
+                sa.part_state = plan.ssd_parts > 1 ? reinterpret_cast<float*>(ws + plan.off_pstate[s]) : const_cast<float*>(sa.h_in);
                 sa.part_decay = reinterpret_cast<float*>(ws + plan.off_pdecay[s]);
                 sa.dir = s == 0 ? 1 : -1;
                 sa.mode = separate ? kSsdFinalOnly
                                    : s == 1 ? (raw ? kSsdPartialRaw : kSsdPartial) : (raw ? kSsdFinalAddRaw : kSsdFinalAdd);
                 sa.out_ch_off = separate ? s * d->d_inner : 0;
                 sa.dt_softplus = d->dt_softplus; sa.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD;
-                sa.wide = wide;
+                sa.far = far;
                 return sa;
             };
             if (plan.ssd_parts > 1) {

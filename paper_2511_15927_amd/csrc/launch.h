@@ -67,7 +67,7 @@ struct SsdStatePair;
 bool ssd_supported(int d_state, int headdim);
 hipError_t launch_ssd_prep(int d_state, const SsdPrepPair& pa, int nchunk, int batch, hipStream_t st);   // (an error: nothing was launched)
 hipError_t launch_ssd_scan(int d_state, int headdim, const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
-// (the many-wave form of the scan; defined in ssd_wide_inst.hip, one object per (d_state, head width))
+// (defined in ssd_wide_inst.hip, one object per (d_state, head width))
 hipError_t launch_ssd_wide_n128_p64(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
 hipError_t launch_ssd_wide_n128_p32(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);
 hipError_t launch_ssd_wide_n64_p64(const SsdStatePair& sp, int dirs, int batch, hipStream_t st);

@@ -339,7 +339,7 @@ __global__ __launch_bounds__(256, BLOCKS == 1 ? 4 : COMMIT ? 2 : 3) void ssd_blo
     bool separable[2];
     float decay_q = 1.0f;
     {
-        // separable decay exp(l_i - l_j) = e_i f_j around the block's middle unless it decays too fast (as in ssd_walk)
+        // separable decay exp(l_i - l_j) = e_i f_j around the block's middle unless it decays too fast (as in ssd_wide.h)
         if constexpr (BLOCKS == 1) {
             const int s = lane >> 5, t = s == 0 ? lane : kTok - 1 - (lane - 32);
             float dl = IoBF16::cvt(dtraw[0]);

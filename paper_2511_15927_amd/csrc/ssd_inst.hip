@@ -18,33 +18,6 @@ static hipError_t prep_variant(const SsdPrepPair& pa, int nchunk, int batch, hip
     return hipSuccess;
 }
 
-template <int N, int P>
-static hipError_t scan_variant(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
-{
-    static LdsLimit limit;
-    constexpr size_t lds = SsdLds<N, P>::bytes();
-    auto kernel = ssd_kernel<N, P>;
-    const hipError_t err = limit.raise(reinterpret_cast<const void*>(kernel), lds);
-    if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(kernel, dim3((unsigned)sp.dir[0].H, (unsigned)dirs, (unsigned)batch), dim3(4 * P + 256), lds, st, sp);
-    return hipSuccess;
-}
-
-template <int N, int P>
-static hipError_t launch_ssd_wide(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
-{
-    if constexpr (N == 128 && P == 64) return launch_ssd_wide_n128_p64(sp, dirs, batch, st);
-    else if constexpr (N == 128) return launch_ssd_wide_n128_p32(sp, dirs, batch, st);
-    else if constexpr (P == 64) return launch_ssd_wide_n64_p64(sp, dirs, batch, st);
-    else return launch_ssd_wide_n64_p32(sp, dirs, batch, st);
-}
-
-template <int N, int P>
-static hipError_t scan_one(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
-{
-    return sp.dir[0].wide ? launch_ssd_wide<N, P>(sp, dirs, batch, st) : scan_variant<N, P>(sp, dirs, batch, st);
-}
-
 bool ssd_supported(int d_state, int headdim) { return (d_state == 64 || d_state == 128) && (headdim == 32 || headdim == 64); }
 
 // Launches that give a CU at most one workgroup take the sixteen-wave form: their duration is one workgroup's chain.
@@ -79,10 +52,10 @@ void launch_ssd_state(int d_state, int headdim, const SsdStatePair& sp, int subs
 // twice as long as one: 120 heads x 32, N 128, 1 x 1024 tokens 72.2 -> 38.1 us a call.
 hipError_t launch_ssd_scan(int d_state, int headdim, const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    if (d_state == 128 && headdim == 64) return scan_one<128, 64>(sp, dirs, batch, st);
-    if (d_state == 128 && headdim == 32) return scan_one<128, 32>(sp, dirs, batch, st);
-    if (d_state == 64 && headdim == 64) return scan_one<64, 64>(sp, dirs, batch, st);
-    if (d_state == 64 && headdim == 32) return scan_one<64, 32>(sp, dirs, batch, st);
+    if (d_state == 128 && headdim == 64) return launch_ssd_wide_n128_p64(sp, dirs, batch, st);
+    if (d_state == 128 && headdim == 32) return launch_ssd_wide_n128_p32(sp, dirs, batch, st);
+    if (d_state == 64 && headdim == 64) return launch_ssd_wide_n64_p64(sp, dirs, batch, st);
+    if (d_state == 64 && headdim == 32) return launch_ssd_wide_n64_p32(sp, dirs, batch, st);
     return hipErrorInvalidValue;
 }
 

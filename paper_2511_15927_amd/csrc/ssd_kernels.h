@@ -8,11 +8,10 @@
 // (direction, batch, head) and walks the chunks in scan order with H in accumulator registers (fp32 for the whole
 // sequence).  Decay factors are formed in fp32; only MFMA operands (xc, B, C, the masked score tile, a copy of H) are
 // rounded to bf16.  ssd_prep_kernel builds, once per (direction, batch, chunk, group) and shared by all heads, the
-// score tile C B^T, the bf16 C rows and the transposed bf16 B tile.
+// score tile C B^T, C and the transposed B in bf16, all in the order in which the walk's matrix products take them.
 //
-// Kernels in this file: ssd_prep_kernel (above); ssd_kernel, the chunk walk of one direction (ssd_walk); ssd_state_kernel and ssd_carry_kernel, which find the state
-// entering each time part when a call has too few (batch, head) items to fill the chip.  Calls of one chunk run on ssd_block.h,
-// calls of several on ssd_wide.h; the walk here is for rows too far apart for 32-bit offsets.
+// Kernels in this file: ssd_prep_kernel (above); ssd_state_kernel and ssd_carry_kernel, which find the state entering each time part
+// when a call has too few (batch, head) items to fill the chip.  The chunk walk is in ssd_wide.h, calls of one chunk in ssd_block.h.
 //
 // Lane layouts of the 32x32x16 MFMA (checked on hardware): operand A lane l holds row l%32, k = 8*(l/32)..+7;
 // operand B lane l holds column l%32, same k; accumulator register r of lane l is row 8*(r/4) + 4*(l/32) + r%4,
@@ -43,20 +42,19 @@ struct SsdPrepArgs {
     const float* conv_w;  // full [conv_ch][K] table of this direction (rows Dn.. are B|C) when conv_bc
     const float* conv_b;  // or null
     const void* tail_in;  // bf16 [batch][K-1][tail_ch] or null (causal direction of the block variant)
-    __bf16* c_rows;    // [batch][Lpad][G][N], scan order
-    __bf16* b_t;       // [batch][nchunk][G][N][64], scan order inside the chunk
+    __bf16* c_rows;    // [batch][nchunk][G][64 x N], MFMA operand order (see the kernel)
+    __bf16* b_t;       // the same
     float* score_op;   // [batch][nchunk][G][kScoreOp]: B_j . C_i for j, i in the chunk, MFMA operand order (see the kernel)
     int L, G, K, Dn, tail_ch, conv_bc;
     int dir;           // +1: scan position tau is token tau; -1: token L-1-tau
-    int wide;          // operand tiles in the order of ssd_wide_kernel (ssd_wide.h)
 };
 
 struct SsdPrepPair {
     SsdPrepArgs dir[2];   // forward, reverse: one launch prepares both
 };
 
-// LDS of ssd_prep_kernel: the chunk's B and C rows after the conv, each value as a bf16 head and the bf16 rest of it.  (The wide
-// form adds the partial score accumulators of the waves that share a block: [12][64][16] floats.)
+// LDS of ssd_prep_kernel: the chunk's B and C rows after the conv, each value as a bf16 head and the bf16 rest of it.  (The form
+// of sixteen waves adds the partial score accumulators of the waves that share a block: [12][64][16] floats.)
 constexpr int kPrepPad = 8;
 template <int N, int THREADS>
 constexpr size_t ssd_prep_lds_bytes()
@@ -69,7 +67,7 @@ constexpr size_t ssd_prep_lds_bytes()
 // thread, applies the short conv + SiLU along the scan direction when they pass through it, and leaves the result in LDS split the
 // way the score product takes it, so that every operand below is read in pieces of eight or sixteen bytes (fp32 columns, read
 // one by one and split by every wave that needs them: 61.4 us for 8 x 8192 tokens, N 128; this: 41.5; 1 x 1024 tokens, sixteen waves,
-// 9.3 -> 7.5).  B^T pieces of the wide operand order are a column's consecutive positions: they go out from registers.  The form
+// 9.3 -> 7.5).  B^T pieces are a column's consecutive positions: they go out from registers.  The form
 // of sixteen waves is for launches of few workgroups (short sequences), whose duration is one workgroup's chain of phases.
 template <int N, int THREADS = 256>
 __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair both)
@@ -83,7 +81,6 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
     __bf16(*const split)[kQ][kRow] = reinterpret_cast<__bf16(*)[kQ][kRow]>(ssd_prep_lds);   // B head, B rest, C head, C rest
     const int c = blockIdx.x, g = blockIdx.y, b = blockIdx.z % batch, tid = threadIdx.x;
     const int nchunk = gridDim.x;
-    const size_t Lpad = (size_t)nchunk * kQ;
     const size_t tile = ((size_t)b * nchunk + c) * a.G + g;
     constexpr int kParts = THREADS / N, kLen = kQ / kParts;   // positions of a thread
     constexpr bool kFromRegisters = kLen >= 8;
@@ -157,7 +154,7 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
                 *reinterpret_cast<bf16x2*>(&split[2 * which][r][n]) = bf16x2{head[0], head[1]};
                 *reinterpret_cast<bf16x2*>(&split[2 * which + 1][r][n]) = bf16x2{rest[0], rest[1]};
                 if constexpr (kFromRegisters) {
-                    if (i % 8 == 7 && a.wide && which == 0) {
+                    if (i % 8 == 7 && which == 0) {
                         // B^T as [32 states][16 positions][lane]: lane l holds state l%32, positions 8 (l/32) .. + 7
                         const int j0 = r - 7;
 #pragma unroll
@@ -179,35 +176,24 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
         for (int e = 0; e < 8; e++) v[e] = split[0][j0 + e][n];
         return v;
     };
-    if (a.wide) {
-        // C as [row block of 16][32 states][lane of an MFMA operand], with the states in the order the state's accumulators publish them
-        for (int idx = tid; idx < kQ * N / 8; idx += THREADS) {
-            const int ln = idx % 64, f = idx / 64;
-            const int i = (f / (N / 32)) * 16 + ln % 16, n0 = (f % (N / 32)) * 32 + 16 * ((ln / 16) % 2) + 4 * (ln / 32);
-            const bf16x4 lo = *reinterpret_cast<const bf16x4*>(&split[2][i][n0]), hi = *reinterpret_cast<const bf16x4*>(&split[2][i][n0 + 8]);
-            *reinterpret_cast<bf16x8*>(&a.c_rows[(tile * kQ * N / 8 + idx) * 8]) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            if constexpr (!kFromRegisters) {
-                const int n2 = (f / 4) * 32 + ln % 32, j0 = (f % 4) * 16 + 8 * (ln / 32);
-                *reinterpret_cast<bf16x8*>(&a.b_t[(tile * kQ * N / 8 + idx) * 8]) = b_column(n2, j0);
-            }
-        }
-    } else
-    // bf16 C rows and the transposed bf16 B tile, written as 16-byte pieces (8 states of a row, 8 positions of a state)
+    // C as [row block of 16][32 states][lane of an MFMA operand], with the states in the order the state's accumulators publish them
     for (int idx = tid; idx < kQ * N / 8; idx += THREADS) {
-        const int j = idx / (N / 8), n8 = idx % (N / 8);
-        const int n2 = idx / (kQ / 8), j8 = idx % (kQ / 8);
-        *reinterpret_cast<bf16x8*>(&a.c_rows[(((size_t)b * Lpad + c * kQ + j) * a.G + g) * N + 8 * n8]) =
-            *reinterpret_cast<const bf16x8*>(&split[2][j][8 * n8]);
-        *reinterpret_cast<bf16x8*>(&a.b_t[((((size_t)b * nchunk + c) * a.G + g) * N + n2) * kQ + 8 * j8]) = b_column(n2, 8 * j8);
+        const int ln = idx % 64, f = idx / 64;
+        const int i = (f / (N / 32)) * 16 + ln % 16, n0 = (f % (N / 32)) * 32 + 16 * ((ln / 16) % 2) + 4 * (ln / 32);
+        const bf16x4 lo = *reinterpret_cast<const bf16x4*>(&split[2][i][n0]), hi = *reinterpret_cast<const bf16x4*>(&split[2][i][n0 + 8]);
+        *reinterpret_cast<bf16x8*>(&a.c_rows[(tile * kQ * N / 8 + idx) * 8]) = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+        if constexpr (!kFromRegisters) {
+            const int n2 = (f / 4) * 32 + ln % 32, j0 = (f % 4) * 16 + 8 * (ln / 32);
+            *reinterpret_cast<bf16x8*>(&a.b_t[(tile * kQ * N / 8 + idx) * 8]) = b_column(n2, j0);
+        }
     }
     // Score tile B_j . C_i on the matrix cores, one 32 x 32 block per wave; only the three blocks on or below the
     // diagonal are kept.  Each fp32 operand is split into a bf16 head and a bf16 remainder and the three significant
     // cross products are accumulated in fp32, which keeps about 16 bits of the products.  With B rows as operand A
     // and C rows as operand B, accumulator register r of lane l is row j%32 = 8*(r/4) + 4*(l/32) + r%4 of column
-    // i%32 = l%32: exactly the order in which the scan kernel feeds the tile to its MFMA as operand A,
-    // [block pair (0,0), (1,0), (1,1)][k-block r/8][lane][r%8].
+    // i%32 = l%32, block pairs (0,0), (1,0), (1,1).
     const int wave = tid / 64, lane = tid % 64;
-    // The wide form deals a block's N / 16 contraction steps to four waves and adds their accumulators through LDS.
+    // Sixteen waves deal a block's N / 16 contraction steps to four waves and adds their accumulators through LDS.
     constexpr int kSplit = THREADS > 256 ? 4 : 1;
     constexpr int kSteps = N / 16 / kSplit;
     const int blk = wave / kSplit, kpart = wave % kSplit;
@@ -243,7 +229,7 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
             }
         }
     }
-    if (blk < 3 && kpart == 0 && a.wide) {
+    if (blk < 3 && kpart == 0) {
         // [block][16 rows i][lane][8]: slot 4t + e of lane l holds row i = l%16 of column j = 16t + 4(l/16) + e; zero above the diagonal
         float* const dst = a.score_op + tile * kScoreOp;
 #pragma unroll
@@ -254,17 +240,10 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
             const int sl = (2 * (q % 2) + lane / 32) * 16 + lane % 16;
             *reinterpret_cast<float4*>(dst + ((blk * 2 + (lane / 16) % 2) * 64 + sl) * 8 + 4 * (q / 2)) = make_float4(v[0], v[1], v[2], v[3]);
         }
-    } else if (blk < 3 && kpart == 0) {
-        float* dst = a.score_op + (((size_t)b * nchunk + c) * a.G + g) * kScoreOp + ((size_t)(blk * 2) * 64 + lane) * 8;
-#pragma unroll
-        for (int kb = 0; kb < 2; kb++) {
-            *reinterpret_cast<float4*>(dst + kb * 64 * 8) = make_float4(acc[8 * kb], acc[8 * kb + 1], acc[8 * kb + 2], acc[8 * kb + 3]);
-            *reinterpret_cast<float4*>(dst + kb * 64 * 8 + 4) = make_float4(acc[8 * kb + 4], acc[8 * kb + 5], acc[8 * kb + 6], acc[8 * kb + 7]);
-        }
     }
 }
 
-// Output modes of ssd_kernel.
+// Output modes of the chunk walk (ssd_wide.h).
 enum { kSsdFinalOnly = 0, kSsdPartial = 1, kSsdPartialRaw = 2, kSsdFinalAdd = 3, kSsdFinalAddRaw = 4 };
 
 struct SsdArgs {
@@ -281,7 +260,7 @@ struct SsdArgs {
     const void* tail_in;  // bf16 [batch][K-1][tail_ch] or null (causal direction only)
     int L, Dn, H, HG, G, K, tail_ch, nchunk;
     int dir, mode, out_ch_off, dt_softplus, d_per_head;
-    int wide;             // run on ssd_wide_kernel (ssd_wide.h): both directions of a call agree, the parked result is bf16
+    int far;              // z or out rows are too far apart for a chunk's 32-bit row offsets (a form of ssd_wide_kernel has none)
     // Time parts (calls with too few (batch, head) items to fill the chip): the chunks are dealt to `parts` workgroups
     // per item, part_chunks each, in scan order.  A part is part_subs sub-parts of sub_chunks chunks;
     // ssd_state_kernel leaves every sub-part's end state from a zero start and the product of its chunk decays (all
@@ -321,24 +300,6 @@ __global__ __launch_bounds__(256) void ssd_carry_kernel(const SsdCarryArgs a)
         }
     }
 }
-
-// LDS of ssd_kernel: two buffers of per-chunk tiles (filled by the producer waves one chunk ahead of the consumer
-// waves) and two copies of the state in MFMA operand form.
-template <int N, int P>
-struct SsdLds {
-    static constexpr int kRowC = N + kPadK, kRowT = kQ + kPadK;
-    static constexpr int kC = kQ * kRowC;    // C rows of the chunk               [kQ][kRowC] bf16
-    static constexpr int kBT = N * kRowT;    // B transposed                      [N][kRowT]  bf16
-    static constexpr int kX = P * kRowT;     // conv + SiLU output, transposed    [P][kRowT]  bf16 (two of them)
-    static constexpr int kM = 2 * 2 * 2 * 64 * 8;   // masked, decayed score tile as MFMA operands [iblk][jblk][kb][lane][8]
-    static constexpr int kTileElems = kC + kBT + 2 * kX + kM;
-    static constexpr int kHT = (N / 32) * (P / 32) * 2 * 64 * 8;   // state operand copy, bf16
-    static constexpr int kProducerWaves = 4;
-    static constexpr int kBufs = 2;
-    static constexpr int kScanTables = kProducerWaves;
-    // + exp(l_i) per buffer, + per scan table: cumulative log2 decay, Delta, end-of-chunk weight of each position
-    static constexpr size_t bytes() { return (size_t)(kBufs * kTileElems + kBufs * kHT) * sizeof(__bf16) + (kBufs + 3 * kScanTables) * kQ * sizeof(float); }
-};
 
 // LDS-only barrier: waits for this wave's LDS traffic, not for global loads that were issued ahead on purpose.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -564,497 +525,6 @@ __global__ __launch_bounds__(256, 4) void ssd_state_kernel(const SsdStatePair bo
                     make_float4(hacc[o][4 * q], hacc[o][4 * q + 1], hacc[o][4 * q + 2], hacc[o][4 * q + 3]);
         }
     }
-}
-
-// grid (H, 1, batch), block 4*P + 256, dynamic LDS SsdLds<N, P>::bytes().  x is read as pairs of channels: its pointer
-// must be 4-byte aligned and its strides even (the host checks).
-// The first P/16 waves are consumers: wave w owns output rows iblk*32.. and channels pblk*32.. of every chunk and N/64
-// of the 32x32 blocks of H; they run the MFMAs, gate, combine and store.  The last four waves are producers: one
-// chunk ahead they compute Delta and the cumulative decay, build the masked decayed score operand, run conv + SiLU,
-// and stage the C / B^T tiles, with the global loads of the chunk after that already in flight.  One LDS barrier per
-// chunk.  (The producers' per-head work does not shrink with the head width, so their count does not either.)
-// Block: 4*P + 256 threads.
-template <int N, int P>
-__device__ __forceinline__ void ssd_walk(const SsdArgs& a)
-{
-    using Lds = SsdLds<N, P>;
-    constexpr int kPB = P / 32;       // channel blocks
-    constexpr int kNB = N / 32;       // state blocks
-    constexpr int kHB = kNB / 2;      // state blocks owned per consumer wave
-    constexpr int kConsThreads = 4 * P;   // one consumer wave per 32 x 32 block of a chunk's output
-    constexpr int kProdThreads = 256;
-    constexpr int kRowC = Lds::kRowC, kRowT = Lds::kRowT;
-    constexpr int kCopy = kQ * N / 8 / kProdThreads;   // 16-byte pieces of each tile per producer thread
-    constexpr int kHS = 2 * 3 * 2 * 64 / kProdThreads;   // half operand slots (4 values) of the lower-triangular score blocks per producer thread
-    using T = unsigned short;
-    extern __shared__ __attribute__((aligned(16))) unsigned char ssd_lds[];
-    __bf16* const tiles = reinterpret_cast<__bf16*>(ssd_lds);
-    __bf16* const sHT = tiles + Lds::kBufs * Lds::kTileElems;
-    float* const scal = reinterpret_cast<float*>(sHT + Lds::kBufs * Lds::kHT);   // [kBufs][kQ]: exp(l_i), decay from the chunk start
-    auto sC = [&](int buf) { return tiles + buf * Lds::kTileElems; };
-    auto sBT = [&](int buf) { return tiles + buf * Lds::kTileElems + Lds::kC; };
-    auto sXc = [&](int buf) { return tiles + buf * Lds::kTileElems + Lds::kC + Lds::kBT; };
-    auto sXw = [&](int buf) { return tiles + buf * Lds::kTileElems + Lds::kC + Lds::kBT + Lds::kX; };
-    auto sM = [&](int buf) { return tiles + buf * Lds::kTileElems + Lds::kC + Lds::kBT + 2 * Lds::kX; };
-
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const bool producer = wave >= kConsThreads / 64;
-    // Workgroups go to the 8 XCDs round-robin by linear id and each XCD has its own L2.  All heads of a batch element
-    // read the same C / B^T / score tiles, so the (batch, head) items are dealt out such that an XCD receives a
-    // contiguous, batch-major run of them and fetches each tile from HBM once instead of once per XCD.
-    int head = blockIdx.x, b = blockIdx.z;
-    {
-        const unsigned total = gridDim.x * gridDim.z, id = blockIdx.x + gridDim.x * blockIdx.z;
-        if (total % 8 == 0) {
-            const unsigned item = (id % 8) * (total / 8) + id / 8;
-            head = (int)(item % gridDim.x);
-            b = (int)(item / gridDim.x);
-        }
-    }
-    const int grp = head / a.HG;
-    const int ch0 = head * P;
-    const size_t Lpad = (size_t)a.nchunk * kQ;
-    // this workgroup's chunks [c_first, c_stop) and the states it starts from / leaves
-    constexpr int c_first = 0;
-    const int c_stop = a.nchunk;
-    const float* const state_in = a.h_in;
-    float* const state_out = a.h_out;
-    const int last = a.L - 1;
-    auto token_of = [&](int tau) { return a.dir > 0 ? tau : last - tau; };   // scan position -> token index
-
-    if (producer) {
-        // ------------------------------------------------------------------ producers
-        constexpr int kCP = P / 2;                 // channel pairs of the head
-        constexpr int kPos = kQ * kCP / kProdThreads;   // chunk positions per thread in the conv role (8 or 4)
-        const int ptid = tid - kConsThreads;
-        const int pwave = wave - kConsThreads / 64;
-        const int cp = ptid % kCP, tg = ptid / kCP;   // conv role: channels 2cp, 2cp+1; positions kPos*tg .. of each chunk
-        // wave-private, written and read by this wave only
-        float* const pw_l2 = scal + Lds::kBufs * kQ + pwave * 3 * kQ;
-        float* const pw_dl = pw_l2 + kQ;
-        float* const pw_wgt = pw_dl + kQ;
-        const float a2 = a.A[head] * kLog2e;
-        const float dtb = (a.dt_softplus && a.dt_bias) ? a.dt_bias[head] : 0.0f;
-        float w4[2][4], cbias[2];
-#pragma unroll
-        for (int h2 = 0; h2 < 2; h2++) {
-#pragma unroll
-            for (int i = 0; i < 4; i++)
-                w4[h2][3 - i] = i < a.K ? a.conv_w[(size_t)(ch0 + 2 * cp + h2) * a.K + (a.K - 1 - i)] : 0.0f;
-            cbias[h2] = a.conv_b ? a.conv_b[ch0 + 2 * cp + h2] : 0.0f;
-        }
-        const T* xb = (const T*)a.x.p + (size_t)b * a.x.sb + ch0 + 2 * cp;
-        const T* dtp = (const T*)a.dt.p + (size_t)b * a.dt.sb + head;
-        const long long xstep = a.dir * a.x.st;
-        // this thread's 16-byte pieces of the C and B^T tiles: offsets inside a chunk (global) and inside the LDS tiles
-        unsigned c_src[kCopy], b_src[kCopy], c_dst[kCopy], b_dst[kCopy];
-#pragma unroll
-        for (int i = 0; i < kCopy; i++) {
-            const int idx = i * kProdThreads + ptid;
-            c_src[i] = (unsigned)(idx / (N / 8)) * a.G * N + (idx % (N / 8)) * 8;
-            b_src[i] = (idx / (kQ / 8)) * kQ + (idx % (kQ / 8)) * 8;
-            c_dst[i] = (idx / (N / 8)) * kRowC + (idx % (N / 8)) * 8;
-            b_dst[i] = (idx / (kQ / 8)) * kRowT + (idx % (kQ / 8)) * 8;
-        }
-
-        unsigned xraw[kPos + 3];   // channel pair at positions kPos*tg - 3 .. kPos*tg + kPos - 1
-        T dtraw;
-        bf16x8 ctile[kCopy], btile[kCopy];
-        float4 gt[kHS];
-        // Score operand half-slot hs = m*kProdThreads + ptid: slot hs/2 is block pair (iblk, jblk) = (0,0), (1,0), (1,1)
-        // for hs / 256, k-block (hs / 128) % 2, operand lane (hs / 2) % 64; the half hs % 2 holds column
-        // i = iblk*32 + lane%32 of rows j = jblk*32 + 16*kb + 8*(hs%2) + 4*(lane/32) + 0..3 (the accumulator-register
-        // order, see the header comment).
-        auto edge_chunk = [&](int c) { return c == 0 || c * kQ + kQ - 1 > last; };
-        // The global loads of a chunk, one group per stage of `finish` (clamped positions: every address is valid).
-        auto issue_dt = [&](int c) { dtraw = dtp[(long long)token_of(min(c * kQ + lane, last)) * a.dt.st]; };
-        auto issue_score = [&](int c) {
-            const float4* sc = reinterpret_cast<const float4*>(a.score_op + (((size_t)b * a.nchunk + c) * a.G + grp) * kScoreOp);
-#pragma unroll
-            for (int m = 0; m < kHS; m++) gt[m] = sc[m * kProdThreads + ptid];
-        };
-        auto issue_x = [&](int c) {
-            const int tau0 = c * kQ + kPos * tg - 3;
-            if (!edge_chunk(c)) {
-                const T* xp = xb + (long long)token_of(tau0) * a.x.st;
-#pragma unroll
-                for (int q = 0; q < kPos + 3; q++) xraw[q] = *reinterpret_cast<const unsigned*>(xp + q * xstep);
-            } else {
-#pragma unroll
-                for (int q = 0; q < kPos + 3; q++)
-                    xraw[q] = *reinterpret_cast<const unsigned*>(xb + (long long)token_of(min(max(tau0 + q, 0), last)) * a.x.st);
-            }
-        };
-        auto issue_tiles = [&](int c) {
-            const __bf16* csrc = a.c_rows + (((size_t)b * Lpad + (size_t)c * kQ) * a.G + grp) * N;
-            const __bf16* bsrc = a.b_t + ((((size_t)b * a.nchunk + c) * a.G + grp) * N) * kQ;
-#pragma unroll
-            for (int i = 0; i < kCopy; i++) {
-                ctile[i] = *reinterpret_cast<const bf16x8*>(csrc + c_src[i]);
-                btile[i] = *reinterpret_cast<const bf16x8*>(bsrc + b_src[i]);
-            }
-        };
-        // Turn the data requested for chunk c into its tiles in buffer buf.  Each stage, once it has taken its inputs
-        // out of the load registers, requests the same data of chunk cn (the chunk this wave handles next), so every
-        // load has a whole chunk period to arrive.
-        auto finish = [&](int c, int buf, int cn) {
-            // Delta, inclusive cumulative log2-decay and end-of-chunk weight of position `lane` (every producer wave
-            // computes them for itself; the first one publishes exp(l) for the consumers)
-            float dl = IoBF16::cvt(dtraw);
-            issue_dt(cn);
-            if (a.dt_softplus) dl = softplus(dl + dtb);
-            if (c * kQ + lane > last) dl = 0.0f;
-            const float l2 = wave_inclusive_sum(dl * a2);
-            const float l2_end = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), 63));
-            // The decay exp(l_i - l_j) of a score element is separable, e_i f_j with e_i = exp(l_i - l_mid) and
-            // f_j = exp(l_mid - l_j): two exponentials per position instead of one per element.  Both factors stay
-            // well inside the fp32 range as long as the chunk's total decay does (2^-100 here); a chunk that decays
-            // faster keeps the per-element form.
-            const float l2_first = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), 0));
-            const float l2_mid = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(l2), kQ / 2 - 1));
-            const bool separable = l2_first - l2_end <= 100.0f;
-            if (separable) {
-                pw_l2[lane] = fast_exp2(l2 - l2_mid);          // e_i
-                pw_dl[lane] = fast_exp2(l2_mid - l2) * dl;     // f_j Delta_j
-            } else {
-                pw_l2[lane] = l2;
-                pw_dl[lane] = dl;
-            }
-            if (pwave == 0) scal[buf * kQ + lane] = fast_exp2(l2);
-            pw_wgt[lane] = fast_exp2(l2_end - l2) * dl;
-            __builtin_amdgcn_wave_barrier();
-            // masked score operand: (B_j . C_i) exp(l_i - l_j) Delta_j for j <= i, else 0
-            float sv[kHS][4];
-#pragma unroll
-            for (int m = 0; m < kHS; m++) { sv[m][0] = gt[m].x; sv[m][1] = gt[m].y; sv[m][2] = gt[m].z; sv[m][3] = gt[m].w; }
-            asm volatile("" ::: "memory");   // the re-issue below must not move above the reads of gt
-            issue_score(cn);
-#pragma unroll
-            for (int m = 0; m < kHS; m++) {
-                const int hs = m * kProdThreads + ptid;
-                const int bp = hs / 256, kb = (hs / 128) % 2, sl = (hs / 2) % 64, hi = hs % 2;
-                const int iblk = bp > 0, jblk = bp > 1;
-                const int i = iblk * 32 + sl % 32;
-                const int jb = jblk * 32 + 16 * kb + 8 * hi + 4 * (sl / 32);
-                const bool diagonal = iblk == jblk;    // only the diagonal blocks hold elements with j > i
-                const float l2i = pw_l2[i];
-                const float4 da = *reinterpret_cast<const float4*>(&pw_dl[jb]);
-                const float dj[4] = {da.x, da.y, da.z, da.w};
-                bf16x4 v;
-                if (separable) {
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        const float val = sv[m][e] * l2i * dj[e];
-                        v[e] = (__bf16)((diagonal && jb + e > i) ? 0.0f : val);
-                    }
-                } else {
-                    const float4 la = *reinterpret_cast<const float4*>(&pw_l2[jb]);
-                    const float lj[4] = {la.x, la.y, la.z, la.w};
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        const float val = sv[m][e] * fast_exp2(l2i - lj[e]) * dj[e];
-                        v[e] = (__bf16)((diagonal && jb + e > i) ? 0.0f : val);
-                    }
-                }
-                *reinterpret_cast<bf16x4*>(&sM(buf)[(((iblk * 2 + jblk) * 2 + kb) * 64 + sl) * 8 + 4 * hi]) = v;
-            }
-            // conv + SiLU of two channels at kPos positions
-            float xr[2][kPos + 3];
-#pragma unroll
-            for (int q = 0; q < kPos + 3; q++) {
-                xr[0][q] = __uint_as_float(xraw[q] << 16);
-                xr[1][q] = __uint_as_float(xraw[q] & 0xffff0000u);
-            }
-            asm volatile("" ::: "memory");
-            issue_x(cn);
-            if (edge_chunk(c)) {
-#pragma unroll
-                for (int q = 0; q < kPos + 3; q++) {
-                    const int tau = c * kQ + kPos * tg + q - 3;
-                    if (tau < 0 || tau > last) xr[0][q] = xr[1][q] = 0.0f;
-                }
-                if (c == 0 && a.dir > 0 && a.tail_in && tg == 0 && a.K > 1) {
-                    // requested together from clamped rows (a tap beyond the conv width has a zero weight)
-                    T cached[3][2];
-#pragma unroll
-                    for (int q = 0; q < 3; q++) {   // 3 - q tokens before the block
-                        const T* tp = (const T*)a.tail_in + ((size_t)b * (a.K - 1) + max(a.K - 1 - (3 - q), 0)) * a.tail_ch + ch0 + 2 * cp;
-                        cached[q][0] = tp[0];
-                        cached[q][1] = tp[1];
-                    }
-#pragma unroll
-                    for (int q = 0; q < 3; q++) {
-                        if (3 - q <= a.K - 1) {
-                            xr[0][q] = IoBF16::cvt(cached[q][0]);
-                            xr[1][q] = IoBF16::cvt(cached[q][1]);
-                        }
-                    }
-                }
-            }
-            float wq[kPos];
-#pragma unroll
-            for (int q = 0; q < kPos; q += 4) {
-                const float4 w = *reinterpret_cast<const float4*>(&pw_wgt[kPos * tg + q]);
-                wq[q] = w.x; wq[q + 1] = w.y; wq[q + 2] = w.z; wq[q + 3] = w.w;
-            }
-#pragma unroll
-            for (int h2 = 0; h2 < 2; h2++) {
-                typedef __attribute__((__vector_size__(kPos * sizeof(__bf16)))) __bf16 bf16run;
-                bf16run vx, vw;
-#pragma unroll
-                for (int q = 0; q < kPos; q++) {
-                    float pre = cbias[h2];
-                    pre = fmaf(w4[h2][0], xr[h2][q], pre);
-                    pre = fmaf(w4[h2][1], xr[h2][q + 1], pre);
-                    pre = fmaf(w4[h2][2], xr[h2][q + 2], pre);
-                    pre = fmaf(w4[h2][3], xr[h2][q + 3], pre);
-                    const float xc = silu(pre);
-                    vx[q] = (__bf16)xc;
-                    vw[q] = (__bf16)(xc * wq[q]);
-                }
-                *reinterpret_cast<bf16run*>(&sXc(buf)[(2 * cp + h2) * kRowT + kPos * tg]) = vx;
-                *reinterpret_cast<bf16run*>(&sXw(buf)[(2 * cp + h2) * kRowT + kPos * tg]) = vw;
-            }
-#pragma unroll
-            for (int i = 0; i < kCopy; i++) {
-                *reinterpret_cast<bf16x8*>(&sC(buf)[c_dst[i]]) = ctile[i];
-                *reinterpret_cast<bf16x8*>(&sBT(buf)[b_dst[i]]) = btile[i];
-            }
-            asm volatile("" ::: "memory");
-            issue_tiles(cn);
-            __builtin_amdgcn_wave_barrier();   // the next chunk's scan results overwrite pw_* only after these reads
-        };
-        issue_dt(c_first);
-        issue_score(c_first);
-        issue_tiles(c_first);
-        issue_x(c_first);
-        finish(c_first, 0, min(c_first + 1, c_stop - 1));
-        lds_barrier();
-        for (int c = c_first; c < c_stop; c++) {
-            if (c + 1 < c_stop) finish(c + 1, (c + 1 - c_first) & 1, min(c + 2, c_stop - 1));
-            lds_barrier();
-        }
-        return;
-    }
-
-    // ---------------------------------------------------------------------- consumers
-    // The output mode is fixed per launch; the walk is compiled once per mode so that the per-chunk code has no
-    // mode branches (gfx9 counts loads and stores on one counter: a load awaited while a store is in flight costs
-    // the store's full round trip, so every chunk first consumes its prefetched gate data, then stores).
-    auto walk = [&](auto mode_c) {
-        constexpr int kMode = decltype(mode_c)::value;
-        constexpr bool need_z = kMode != kSsdPartialRaw;
-        constexpr bool adds_parked = kMode == kSsdFinalAdd || kMode == kSsdFinalAddRaw;
-        constexpr bool parks = kMode == kSsdPartialRaw || kMode == kSsdPartial;
-        const int iblk = wave / kPB, pblk = wave % kPB;
-        const int cl = lane & 31, half = lane >> 5;
-        const int po = pblk * 32 + cl;             // this lane's channel within the head
-        const int icol = iblk * 32 + cl;           // this lane's output row, as the score tile's column
-        const int i0 = iblk * 32 + 4 * half;       // output row of accumulator register 0; register r: i0 + row_k(r)
-        auto row_k = [](int r) { return 8 * (r / 4) + (r % 4); };
-        const float dval = a.D[a.d_per_head ? head : ch0 + po];
-        const T* zb = (const T*)a.z.p + (size_t)b * a.z.sb + ch0 + po;
-        float* const pbase = a.partial + (size_t)b * a.L * a.Dn + ch0 + po;
-        T* const obase = (T*)a.out + (size_t)b * a.out_sb + a.out_ch_off + ch0 + po;
-        // signed element steps from one scan position to the next
-        const long long zstep = a.dir * a.z.st, pstep = (long long)a.dir * a.Dn, ostep = a.dir * a.out_st;
-
-        f32x16 hacc[kHB];
-#pragma unroll
-        for (int hb = 0; hb < kHB; hb++) {
-            const int nblk = iblk * kHB + hb;
-#pragma unroll
-            for (int r = 0; r < 16; r++) hacc[hb][r] = 0.0f;
-            if (state_in) {   // registers 4q .. 4q+3 hold four adjacent states: 16-byte pieces (the host checks alignment)
-                const float* hrow = state_in + ((size_t)b * a.Dn + ch0 + po) * N + nblk * 32 + 4 * half;
-#pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    const float4 v = *reinterpret_cast<const float4*>(hrow + 8 * q);
-                    hacc[hb][4 * q] = v.x; hacc[hb][4 * q + 1] = v.y; hacc[hb][4 * q + 2] = v.z; hacc[hb][4 * q + 3] = v.w;
-                }
-            }
-        }
-        auto publish_state = [&](int which) {
-#pragma unroll
-            for (int hb = 0; hb < kHB; hb++) {
-                const int nblk = iblk * kHB + hb;
-#pragma unroll
-                for (int kb = 0; kb < 2; kb++) {
-                    bf16x8 v;
-#pragma unroll
-                    for (int e = 0; e < 8; e++) v[e] = (__bf16)hacc[hb][8 * kb + e];
-                    *reinterpret_cast<bf16x8*>(&sHT[which * Lds::kHT + (((nblk * kPB + pblk) * 2 + kb) * 64 + lane) * 8]) = v;
-                }
-            }
-        };
-        // gate and parked partial of one chunk, requested a whole chunk before they are used.  A chunk that ends
-        // inside the sequence addresses its rows as one base plus constant multiples of the step; the ragged last
-        // chunk clamps every position instead.
-        T zraw[16];
-        float part[16];
-        auto issue_gate = [&](int c) {
-            const int tau0 = c * kQ + i0;
-            if (c * kQ + kQ - 1 <= last) {
-                const long long t0 = token_of(tau0);
-                const T* zp = zb + t0 * a.z.st;
-                const float* pp = pbase + t0 * a.Dn;
-#pragma unroll
-                for (int r = 0; r < 16; r++) {
-                    if constexpr (need_z) zraw[r] = zp[row_k(r) * zstep];
-                    if constexpr (adds_parked) part[r] = pp[row_k(r) * pstep];
-                }
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; r++) {
-                    const long long t = token_of(min(tau0 + row_k(r), last));
-                    if constexpr (need_z) zraw[r] = zb[t * a.z.st];
-                    if constexpr (adds_parked) part[r] = pbase[t * a.Dn];
-                }
-            }
-        };
-        publish_state(0);
-        bool state_nonzero = state_in != nullptr;
-        issue_gate(c_first);
-        lds_barrier();
-
-        for (int c = c_first; c < c_stop; c++) {
-            const int buf = (c - c_first) & 1;
-            const float* el = scal + buf * kQ;
-            const __bf16* xc_t = sXc(buf);
-            // ---- intra-chunk product with the masked, decayed score operand the producers prepared
-            f32x16 y1 = {0}, y2 = {0};
-#pragma unroll
-            for (int jblk = 0; jblk < 2; jblk++) {
-                if (jblk > iblk) break;
-#pragma unroll
-                for (int kb = 0; kb < 2; kb++) {
-                    const bf16x8 am = *reinterpret_cast<const bf16x8*>(&sM(buf)[(((iblk * 2 + jblk) * 2 + kb) * 64 + lane) * 8]);
-                    bf16x8 bx;
-#pragma unroll
-                    for (int jj = 0; jj < 2; jj++) {
-                        const bf16x4 v = *reinterpret_cast<const bf16x4*>(&xc_t[po * kRowT + jblk * 32 + 16 * kb + 8 * jj + 4 * half]);
-#pragma unroll
-                        for (int e = 0; e < 4; e++) bx[4 * jj + e] = v[e];
-                    }
-                    y1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bx, y1, 0, 0, 0);
-                }
-            }
-            // ---- inter-chunk product with the state entering the chunk
-            if (state_nonzero) {
-                const __bf16* c_t = sC(buf);
-                const __bf16* h_t = sHT + buf * Lds::kHT;
-#pragma unroll
-                for (int nblk = 0; nblk < kNB; nblk++) {
-#pragma unroll
-                    for (int kb = 0; kb < 2; kb++) {
-                        bf16x8 ac;
-#pragma unroll
-                        for (int jj = 0; jj < 2; jj++) {
-                            const bf16x4 v = *reinterpret_cast<const bf16x4*>(&c_t[icol * kRowC + nblk * 32 + 16 * kb + 8 * jj + 4 * half]);
-#pragma unroll
-                            for (int e = 0; e < 4; e++) ac[4 * jj + e] = v[e];
-                        }
-                        const bf16x8 bh = *reinterpret_cast<const bf16x8*>(&h_t[(((nblk * kPB + pblk) * 2 + kb) * 64 + lane) * 8]);
-                        y2 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ac, bh, y2, 0, 0, 0);
-                    }
-                }
-            }
-            // ---- state update of the blocks this wave owns (the state after the last chunk matters only if it is
-            // committed)
-            const bool state_needed = c + 1 < c_stop || state_out != nullptr;
-            if (state_needed) {
-                const __bf16* b_t = sBT(buf);
-                const __bf16* xw_t = sXw(buf);
-                const float decay_q = el[kQ - 1];
-#pragma unroll
-                for (int hb = 0; hb < kHB; hb++) {
-                    const int nblk = iblk * kHB + hb;
-#pragma unroll
-                    for (int r = 0; r < 16; r++) hacc[hb][r] *= decay_q;
-#pragma unroll
-                    for (int kb = 0; kb < 4; kb++) {
-                        const bf16x8 ab = *reinterpret_cast<const bf16x8*>(&b_t[(nblk * 32 + cl) * kRowT + 16 * kb + 8 * half]);
-                        const bf16x8 bw = *reinterpret_cast<const bf16x8*>(&xw_t[po * kRowT + 16 * kb + 8 * half]);
-                        hacc[hb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ab, bw, hacc[hb], 0, 0, 0);
-                    }
-                }
-            }
-            // ---- epilogue: inter-chunk term, skip term, gate, combine; all 16 results first, then the stores
-            {
-                float res[16];
-#pragma unroll
-                for (int q = 0; q < 4; q++) {
-                    const float4 e4 = *reinterpret_cast<const float4*>(&el[i0 + 8 * q]);
-                    const bf16x4 x4 = *reinterpret_cast<const bf16x4*>(&xc_t[po * kRowT + i0 + 8 * q]);
-                    const float ev[4] = {e4.x, e4.y, e4.z, e4.w};
-#pragma unroll
-                    for (int e = 0; e < 4; e++) {
-                        const int r = 4 * q + e;
-                        const float y = y1[r] + ev[e] * y2[r] + dval * (float)x4[e];
-                        if constexpr (!need_z) res[r] = y;
-                        else {
-                            const float zg = silu(IoBF16::cvt(zraw[r]));
-                            res[r] = kMode == kSsdFinalAddRaw ? (y + part[r]) * zg : adds_parked ? y * zg + part[r] : y * zg;
-                        }
-                    }
-                }
-                {
-                    const int tau0 = c * kQ + i0;
-                    if (c * kQ + kQ - 1 <= last) {
-                        const long long t0 = token_of(tau0);
-                        float* pp = pbase + t0 * a.Dn;
-                        T* op = obase + t0 * a.out_st;
-#pragma unroll
-                        for (int r = 0; r < 16; r++) {
-                            if constexpr (parks) pp[row_k(r) * pstep] = res[r];
-                            else IoBF16::st(op + row_k(r) * ostep, res[r]);
-                        }
-                    } else {
-#pragma unroll
-                        for (int r = 0; r < 16; r++) {
-                            const int tau = tau0 + row_k(r);
-                            if (tau <= last) {
-                                const long long t = token_of(tau);
-                                if constexpr (parks) pbase[t * a.Dn] = res[r];
-                                else IoBF16::st(obase + t * a.out_st, res[r]);
-                            }
-                        }
-                    }
-                }
-            }
-            if (c + 1 < c_stop) {
-                issue_gate(c + 1);
-                publish_state(buf ^ 1);
-            }
-            state_nonzero = true;
-            lds_barrier();
-        }
-        if (state_out) {
-#pragma unroll
-            for (int hb = 0; hb < kHB; hb++) {
-                const int nblk = iblk * kHB + hb;
-                float* hrow = state_out + ((size_t)b * a.Dn + ch0 + po) * N + nblk * 32 + 4 * half;
-#pragma unroll
-                for (int q = 0; q < 4; q++)
-                    *reinterpret_cast<float4*>(hrow + 8 * q) =
-                        make_float4(hacc[hb][4 * q], hacc[hb][4 * q + 1], hacc[hb][4 * q + 2], hacc[hb][4 * q + 3]);
-            }
-        }
-    };
-    switch (a.mode) {
-        case kSsdFinalOnly: walk(std::integral_constant<int, kSsdFinalOnly>{}); break;
-        case kSsdPartial: walk(std::integral_constant<int, kSsdPartial>{}); break;
-        case kSsdPartialRaw: walk(std::integral_constant<int, kSsdPartialRaw>{}); break;
-        case kSsdFinalAdd: walk(std::integral_constant<int, kSsdFinalAdd>{}); break;
-        default: walk(std::integral_constant<int, kSsdFinalAddRaw>{}); break;
-    }
-}
-
-template <int N, int P>
-__global__ __launch_bounds__(4 * P + 256, 1) void ssd_kernel(const SsdStatePair launch)
-{
-    ssd_walk<N, P>(launch.dir[blockIdx.y]);   // blockIdx.y: the direction, where a launch has both
 }
 
 }  // namespace bm

@@ -29,7 +29,7 @@
 // The result one direction parks for the other crosses global memory as bf16: in the paper's precision (bf16 autocast,
 // App. A) each direction's output is a bf16 tensor before the two are added (eq. 6).  In time parts it stays fp32.
 //
-// grid (H / HEADS, directions * parts, batch).  Calls of several chunks; z / out token strides up to 2^24 elements (the host checks).
+// grid (H / HEADS, directions * parts, batch).  Calls of several chunks; without PARTS, z / out token strides up to 2^24 elements (the host checks).
 #pragma once
 #include "ssd_kernels.h"
 
@@ -52,7 +52,9 @@ struct SsdWide {
 // both directions in one launch (see launch_ssd_scan), the others one.
 // PARTS: the launch deals every item's chunks to several workgroups in scan order (blockIdx.y: the part, then the direction), each from
 // the state that ssd_state_kernel and ssd_carry_kernel left for it, and what one direction parks for the other stays fp32.
-// Against the eight-wave walk of ssd_kernels.h, calls of 64 heads x 64, N 128: 1 x 32768 tokens 953 -> 890 us, 1 x 8192 279 -> 255, 2 x 8192
+// Calls whose z or out rows lie too far apart for 32-bit offsets within a chunk (a.far; SsdArgs) take this form too, also with one part: it
+// asks per chunk whether the offsets serve and addresses every row by itself where they do not.
+// Against one walk of eight waves a part, calls of 64 heads x 64, N 128: 1 x 32768 tokens 953 -> 890 us, 1 x 8192 279 -> 255, 2 x 8192
 // 476 -> 440, 1 x 2048 103 -> 90; 64 heads x 32, N 64, 1 x 16384 340 -> 258.
 template <int N, int P, int HEADS, int MODE, bool PARTS>
 __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_kernel(const std::conditional_t<(MODE > 0), SsdArgs, SsdStatePair> launch)
@@ -78,7 +80,9 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // (batch, head) items dealt to the XCDs batch-major, as in ssd_walk: the heads of a batch element share their tiles
+    // Workgroups go to the 8 XCDs round-robin by linear id and each XCD has its own L2.  All heads of a batch element read the same
+    // C / B^T / score tiles, so the (batch, head) items are dealt out such that an XCD receives a contiguous, batch-major run of
+    // them and fetches each tile from HBM once instead of once per XCD.
     int head = blockIdx.x, b = blockIdx.z;
     {
         const unsigned total = gridDim.x * gridDim.z, id = blockIdx.x + gridDim.x * blockIdx.z;
@@ -500,7 +504,8 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
     Park* const phead = (Park*)a.partial + (size_t)b * a.L * a.Dn + my_ch0;
     T* const ohead = (T*)a.out + (size_t)b * a.out_sb + a.out_ch_off + my_ch0;
     auto chunk_low_token = [&](int c) { return (long long)(fwd ? q0 + c * kQ : last - (q0 + c * kQ + kQ - 1)); };
-    auto inside = [&](int c) { return q0 + c * kQ + kQ - 1 <= last; };
+    const int last_near = PARTS && a.far ? -1 : last;
+    auto inside = [&](int c) { return q0 + c * kQ + kQ - 1 <= last_near; };
     auto token_at = [&](int c, int k) { return (long long)token_of(min(q0 + c * kQ + i0 + 16 * (k / 4) + k % 4, last)); };
 
     typedef unsigned __attribute__((ext_vector_type(2))) uint2v;

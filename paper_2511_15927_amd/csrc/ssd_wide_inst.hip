@@ -40,7 +40,7 @@ static hipError_t launch(const SsdStatePair& sp, int dirs, int batch, hipStream_
 hipError_t BM_NAME(BM_N, BM_P)(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     const SsdArgs& sa = sp.dir[0];
-    if (sa.parts > 1) return launch<1, true>(sp, dirs, batch, st);
+    if (sa.parts > 1 || sa.far) return launch<1, true>(sp, dirs, batch, st);
     if (sa.HG % 2 == 0 && (long long)sa.H * batch * dirs > cu_count()) return launch<2, false>(sp, dirs, batch, st);
     return launch<1, false>(sp, dirs, batch, st);
 }

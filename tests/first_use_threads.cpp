@@ -2,8 +2,9 @@
 // below (the executable's symbols come first in the lookup order), so no GPU is needed.  They model one rule of the real
 // ones: a launch with more than 64 KB of dynamic LDS is refused until the kernel's limit has been raised.
 //   race CALL     a second host thread makes its first call while the first one is inside the raising
-//   fail CALL N   the N-th raising (from 1) fails
-// CALL: fwd, bwd, block (short calls of lane-per-chain kernels), m2 (chunked Mamba-2, several chunks), m2_block (one chunk).
+//   fail CALL N   the N-th raising (from 1; 0: none) fails
+// CALL: fwd, bwd, block (short calls of lane-per-chain kernels), m2 (chunked Mamba-2, several chunks), m2_block (one chunk), m2_far,
+// m2_far_x (time parts, z and out, or x, with rows more than 2^24 elements apart).
 // Prints the two calls' return codes, the launches, the refused launches and the launches of the first call ("fail" only).
 #include "bimamba.h"
 
@@ -88,8 +89,8 @@ int main(int argc, char** argv)
     d.io_dtype = BIMAMBA_BF16;
     if (is("block")) {   // 65 KB: four sets of B and C rows and what the directions leave for each other
         d.seqlen = 64; d.d_inner = d.n_heads = 128; d.n_groups = 2; d.state_split = 1;
-    } else if (is("m2") || is("m2_block")) {   // the preparation takes up to 118 KB, the walk of several chunks 115
-        d.seqlen = is("m2") ? 128 : 64;
+    } else if (!strncmp(argv[3], "m2", 2)) {   // the preparation takes up to 118 KB, the walk of several chunks 115
+        d.seqlen = is("m2") ? 128 : is("m2_block") ? 64 : 1030;
         d.d_inner = 128; d.n_heads = 2; d.d_state = 128;
         d.a_kind = BIMAMBA_A_SCALAR_PER_HEAD; d.d_kind = BIMAMBA_D_PER_HEAD; d.dt_softplus = d.conv_bc = 1;
     }
@@ -98,8 +99,16 @@ int main(int argc, char** argv)
     auto view = [&](int64_t ch) { return bimamba_tensor{place(), d.seqlen * ch, ch}; };
     const int gn = d.n_groups * d.d_state;
     auto inputs = [&] { return bimamba_inputs{view(d.d_inner), view(d.d_inner), view(d.n_heads), view(gn), view(gn)}; };
-    const bimamba_inputs f = inputs(), b = inputs();
-    const bimamba_tensor out = view(d.d_inner);
+    bimamba_inputs f = inputs(), b = inputs();
+    bimamba_tensor out = view(d.d_inner);
+    auto far = [&](bimamba_tensor& t) { t = bimamba_tensor{(void*)(next <<= 1), d.seqlen * ((int64_t)1 << 25), (1 << 24) + 2}; };
+    if (is("m2_far")) {
+        far(f.z);
+        next = (uintptr_t)1 << 42;   // (an output may overlap no input)
+        far(out);
+    } else if (is("m2_far_x")) {
+        far(f.x);
+    }
     float* const state = (float*)place();
     void* const tail = place();
     const float* any = (const float*)place();

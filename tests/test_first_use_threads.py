@@ -1,5 +1,5 @@
-"""The first calls of several host threads that need a kernel's dynamic-LDS limit raised, and a raising that fails: the
-library against stand-ins for the HIP runtime's entry points (tests/first_use_threads.cpp), on the CPU."""
+"""The first calls of several host threads that need a kernel's dynamic-LDS limit raised, a raising that fails, and which
+launches a call makes: the library against stand-ins for the HIP runtime's entry points (tests/first_use_threads.cpp), on the CPU."""
 import os
 import subprocess
 
@@ -36,3 +36,10 @@ def test_a_second_thread_does_not_launch_under_a_limit_still_being_raised(progra
 def test_a_failed_raising_is_reported_and_tried_again(program, entry, failing, before):
     first, second, launches, refused, of_first = program("fail", entry, failing)
     assert (first, second, refused, of_first) == (ERR_HIP, 0, 0, before) and launches > of_first
+
+
+def test_time_parts_are_kept_where_only_z_and_out_rows_are_far_apart(program):
+    """The preparation, the state pass, its carry and a walk per direction; with x rows as far apart the call runs in one part.  (And the
+    conv tail's commit.)"""
+    assert program("fail", "m2_far", 0) == [0, 0, 12, 0, 6]
+    assert program("fail", "m2_far_x", 0) == [0, 0, 8, 0, 4]

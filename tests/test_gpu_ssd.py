@@ -227,7 +227,8 @@ def test_ssd_time_parts_down_to_one_short_chunk(gpu, oracle, N, headdim, combine
 
 
 def test_ssd_rows_too_far_apart_for_time_parts(gpu, oracle):
-    """z as a view with a token stride beyond 2^24 elements: the call runs without parts and without the many-wave walk."""
+    """z as a view with a token stride beyond 2^24 elements, the widest whose rows in a chunk 32-bit offsets reach: in time parts like
+    any other call, every row addressed by itself."""
     from paper_2511_15927_amd import binding as bd
     L, token_stride = 1030, (1 << 24) + 2
     cfg = synth.m2_cfg(1, L, 256, headdim=64, d_state=64)
@@ -246,6 +247,47 @@ def test_ssd_rows_too_far_apart_for_time_parts(gpu, oracle):
     del big, wide, dinp
     torch.cuda.empty_cache()
     assert_close(got, ref, gpu.TOL["bf16"])
+
+
+@pytest.mark.parametrize("L,combine,views", [(1030, 0, ("out",)), (2050, 0, ("z", "x")), (150, 0, ("z",)), (131, 1, ("out", "z")), (150, 0, ("z", "x", "out"))])
+def test_ssd_block_call_with_rows_far_apart(gpu, oracle, L, combine, views):
+    """z, out or x as views with token strides beyond 2^24 elements, with and without time parts (x that far apart: none), as a block call
+    from a cached state and tail, which it commits; activations per direction, so that one of them is near."""
+    from paper_2511_15927_amd import binding as bd
+    stride = (1 << 24) + 2
+    cfg = synth.m2_cfg(1, L, 128, headdim=64, d_state=64, combine=combine)
+    pf, pb, inp = case(cfg, 4300 + L)
+    inp_b = synth.make_inputs(cfg, 4400 + L)
+    K, Dn, N = cfg["d_conv"], cfg["d_inner"], cfg["d_state"]
+    g = torch.Generator().manual_seed(L)
+    h0 = (0.2 * torch.randn(1, Dn, N, generator=g)).float()
+    tail0 = synth.round_io(torch.randn(1, K - 1, synth.conv_channels(cfg), generator=g), "bf16")
+    ref, h_ref, t_ref = oracle.bimamba_block_fwd(cfg, to_np(pf), to_np(pb), to_np(inp), to_np(inp_b), h_in=h0.numpy(), tail_in=tail0.numpy())
+    desc = bd.make_desc(cfg)
+    dpf, dpb, dinp, dinp_b = bd.to_device(pf), bd.to_device(pb), bd.to_device(inp, cfg), bd.to_device(inp_b, cfg)
+    # one buffer, the views beside each other in its rows
+    big = torch.empty((L - 1) * stride + 1024, dtype=torch.bfloat16, device="cuda")
+    out, place = bd.alloc_out(cfg), 0
+    for v in views:
+        t = out if v == "out" else dinp[v]
+        wide = big.as_strided(t.shape, (0, stride, 1), place)
+        place += t.shape[2]
+        if v == "out":
+            out = wide
+        else:
+            wide.copy_(t)
+            dinp[v] = wide
+    h, tail = h0.cuda(), tail0.to(torch.bfloat16).cuda()
+    ws = bd.alloc_workspace(desc, 1)
+    bd.bimamba_block_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp), bd.make_inputs(dinp_b), h, tail, h, tail,
+                         bd.make_tensor(out), ws)
+    torch.cuda.synchronize()
+    got = out.float().cpu().numpy()
+    del big, out, dinp
+    torch.cuda.empty_cache()
+    assert_close(got.reshape(ref.shape), ref, gpu.TOL["bf16"])
+    assert rel_l2(h.cpu().numpy(), h_ref) < 1e-2
+    assert np.array_equal(tail.float().cpu().numpy(), t_ref)
 
 
 @pytest.mark.parametrize("name,batch", [("cfg2_m2", 1), ("headline_m2", 1), ("headline_m2", 2)])
@@ -285,7 +327,7 @@ def test_ssd_block_call_at_benchmark_size_sampled(gpu, oracle):
 @pytest.mark.parametrize("wide_z", [False, True])
 def test_ssd_both_directions_in_one_launch(gpu, oracle, L, batch, heads, headdim, N, wide_z):
     """Output halves kept apart, activations per direction: both directions walk in one launch, with and without time
-    parts; a z token stride beyond 2^24 elements takes the eight-wave form of the walk."""
+    parts; a z token stride beyond 2^24 elements takes the form that addresses every row by itself."""
     from paper_2511_15927_amd import binding as bd
     cfg = synth.m2_cfg(batch, L, heads * headdim, headdim=headdim, d_state=N, combine=synth.COMBINE_SEPARATE)
     pf, pb, inp = case(cfg, 2100 + L)
