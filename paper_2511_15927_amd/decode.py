@@ -41,6 +41,7 @@ class BlockDecodeLoop:
         self._step_flat = [torch.zeros(Bt * G * sum(widths.values()), dtype=io, device=device) for _ in range(self.n_steps)]
         self.step_inputs = [{k: t.view(Bt, G, n) for (k, n), t in zip(widths.items(), flat.split([Bt * G * n for n in widths.values()]))}
                             for flat in self._step_flat]
+        self._step_views = [dict(views) for views in self.step_inputs]
         width = Dn * (2 if cfg["combine"] == bd.COMBINE_SEPARATE else 1)
         assert width == Dn, "layers chain out -> x, which needs the additive combine"
         n_act = self.n_steps * self.n_layers if keep_layer_outputs else 2
@@ -63,9 +64,9 @@ class BlockDecodeLoop:
         flat, dsts = self._step_flat[step], self.step_inputs[step]
         own = flat.untyped_storage().data_ptr()
 
-        def plain(k, dst):   # of the buffer's kind, and no part of it
+        def plain(k, dst):   # into the buffer's own place (the caller may have put another tensor there), of its kind, and no part of it
             t = inputs[k]
-            return (t.device == flat.device and t.dtype == flat.dtype and t.numel() == dst.numel() and not t.requires_grad and
+            return (dst is self._step_views[step][k] and t.device == flat.device and t.dtype == flat.dtype and t.numel() == dst.numel() and not t.requires_grad and
                     t.untyped_storage().data_ptr() != own)
         if all(plain(k, dst) for k, dst in dsts.items()):
             # one launch instead of five (24 layers x 8 steps of 32 tokens at batch 1: 530 -> 486 us a block)
