@@ -238,3 +238,55 @@ def test_step_inputs_refreshed_together_or_one_by_one(kind):
     for k, v in want.items():
         assert torch.equal(loop.step_inputs[0][k], v.reshape(loop.step_inputs[0][k].shape)), k
     assert all(t.count_nonzero() == 0 for t in loop.step_inputs[1].values())
+
+
+@pytest.mark.parametrize("replaced", [("x",), ("dt", "C"), ("x", "z", "dt", "B", "C")])
+def test_step_inputs_go_to_the_tensors_that_stand_there(replaced):
+    """step_inputs is the caller's to read and to fill: the calls take what stands in it, so that is what is written."""
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    cfg = synth.mixer_cfg(2, 8, 12, d_state=4)
+    loop = BlockDecodeLoop(cfg, [(synth.make_params(cfg, 1, 0), synth.make_params(cfg, 1, 1))], 2, device="cpu")
+    for k in replaced:
+        loop.step_inputs[0][k] = torch.zeros_like(loop.step_inputs[0][k])
+    given = {k: v.to(torch.bfloat16) for k, v in synth.make_inputs(cfg, 3).items()}
+    loop.set_step_inputs(0, given)
+    for k, t in loop.step_inputs[0].items():
+        assert torch.equal(t, given[k].reshape(t.shape)), k
+    assert all(t.count_nonzero() == 0 for t in loop.step_inputs[1].values())
+
+
+def test_stack_errors_are_decided_on_the_host():
+    """bimamba_block_stack: 2 layers x 2 steps; every argument error, and outputs that overlap an input of any step (those that share
+    a projection's rows with the inputs without overlapping pass the check and are not reached here: they would launch)."""
+    L, Dn, N = 32, 64, 16
+    desc = bd.make_desc(synth.mixer_cfg(1, L, Dn))
+    at = lambda i: 0x100000 * (i + 1)      # nothing is read
+    view = lambda p, ch, st=None: bd.Tensor(p, L * (st or ch), st or ch)
+    params = bd.Params(at(0), at(0), at(0), at(0), None)
+    layer = bd.StackLayer(params, params, at(1), at(2))
+    step = lambda i: bd.Inputs(view(at(i), Dn), view(at(i + 1), Dn), view(at(i + 2), Dn), view(at(i + 3), N), view(at(i + 4), N))
+    fake = lambda p: type("T", (), dict(data_ptr=lambda self: p))()
+
+    def call(layers=(layer, layer), steps=(step(3), step(8)), outs=(None, None, None, at(20)), desc=desc, counts=(2, 2), host=True, dev=0x1000):
+        table = C.create_string_buffer(bd.make_stack_table(layers, steps, [None if o is None else fake(o) for o in outs]))
+        return bd.lib().bimamba_block_stack(C.byref(desc), *counts, C.addressof(table) if host is True else host, dev, None)
+
+    assert call(host=None) == -1 and call(dev=None) == -1
+    assert call(dev=0x1004) == -4
+    assert call(counts=(-1, 2)) == -2 and call(counts=(2, -1)) == -2
+    assert call(counts=(0, 2)) == 0 and call(counts=(2, 0)) == 0          # nothing to do
+    for over in (dict(time_chunks=1), dict(state_split=1), dict(combine=1), dict(d_state=32), dict(conv_bc=1), dict(seqlen=257), dict(batch=0)):
+        assert call(desc=bd.make_desc(synth.mixer_cfg(1, L, Dn), **over)) == -3, over
+    no_a, odd_a = bd.Params(at(0), at(0), None, at(0), None), bd.Params(at(0), at(0), at(0) + 2, at(0), None)
+    for bad, code in ((bd.StackLayer(params, no_a, at(1), at(2)), -1), (bd.StackLayer(odd_a, params, at(1), at(2)), -4),
+                      (bd.StackLayer(params, params, at(1) + 2, at(2)), -4), (bd.StackLayer(params, params, at(1), at(2) + 1), -4)):
+        assert call(layers=(layer, bad)) == code
+    good_step = step(8)
+    for field, bad, code in (("z", bd.Tensor(None, L * Dn, Dn), -1), ("dt", view(at(3) + 1, Dn), -4), ("B", view(at(3), N, N - 1), -2),
+                             ("x", view(at(3), Dn, (1 << 26) + 1), -3)):
+        other = bd.Inputs(*[bad if f == field else getattr(good_step, f) for f, _ in bd.Inputs._fields_])
+        assert call(steps=(step(3), other)) == code, field
+    assert call(outs=(None, at(20) + 1, None, at(21))) == -4
+    assert call(outs=(at(3), None, None, at(20))) == -8                    # in place over the first step's x
+    assert call(outs=(at(10) + 2 * Dn * (L - 1), None, None, at(20))) == -8   # the last row of the second step's dt, by a first-step output
+    assert call(outs=(None, None, None, at(12) - 2 * Dn * L + 2)) == -8    # ends in the first value of the second step's C

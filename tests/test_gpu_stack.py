@@ -71,3 +71,48 @@ def test_stack_refuses_what_it_cannot_take(oracle):
     for over in (dict(time_chunks=1), dict(state_split=2), dict(combine=1), dict(d_state=32), dict(seqlen=257)):
         assert bd.bimamba_block_stack_form(bd.make_desc(dict(small, **over))) == 0, over
     assert bd.bimamba_block_stack_form(bd.make_desc(synth.m2_cfg(1, 32, 64, headdim=32, d_state=64))) == 0
+
+
+@pytest.mark.parametrize("batch,L,Dn,io", [(1, 32, 260, "bf16"), (2, 17, 130, "f32"), (1, 100, 2048, "bf16")])
+def test_stack_with_outputs_not_wanted(batch, L, Dn, io):
+    """Layer outputs that nobody asked for, all but the last layer's or some of them: what is asked for and what is committed are
+    the same bits as with all of them."""
+    from paper_2511_15927_amd import binding as bd
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    layers, steps = 3, 2
+    cfg = synth.mixer_cfg(batch, L, Dn, io=io)
+    params = [(synth.make_params(cfg, 90 + l, 0), synth.make_params(cfg, 90 + l, 1)) for l in range(layers)]
+    inputs = [synth.make_inputs(cfg, 95 + s) for s in range(steps)]
+    got = []
+    for keep, wanted in ((True, None), (False, None), (True, {1, 3, 5})):     # places s * layers + l
+        loop = BlockDecodeLoop(cfg, params, steps, keep_layer_outputs=keep)
+        g = torch.Generator(device="cuda").manual_seed(7)
+        for l in range(layers):
+            loop.h[l].normal_(generator=g)
+            loop.tail[l].normal_(generator=g)
+        for s in range(steps):
+            loop.set_step_inputs(s, inputs[s])
+        outs = [[loop.layer_output(s, l) if keep else loop.out[s] if l == layers - 1 else None for l in range(layers)] for s in range(steps)]
+        for row in outs:
+            for o in row:
+                if o is not None:
+                    o.fill_(7.0)
+        if wanted is None:
+            loop.run_block_eager()
+        else:
+            stack = [bd.StackLayer(pf, pb, h.data_ptr(), t.data_ptr()) for (pf, pb), h, t in zip(loop._params, loop.h, loop.tail)]
+            flat = [o if i in wanted else None for i, o in enumerate(o for row in outs for o in row)]
+            table = bd.make_stack_table(stack, [bd.make_inputs(i) for i in loop.step_inputs], flat)
+            table_dev = torch.frombuffer(bytearray(table), dtype=torch.uint8).cuda()
+            bd.bimamba_block_stack(loop.desc, layers, steps, table, table_dev)
+        torch.cuda.synchronize()
+        got.append((outs, loop.h, loop.tail))
+    (every, h_all, tail_all), rest = got[0], got[1:]
+    for (outs, h, tail), wanted in zip(rest, ({2, 5}, {1, 3, 5})):
+        for l in range(layers):
+            assert torch.equal(h[l], h_all[l]) and torch.equal(tail[l], tail_all[l]), l
+            for s in range(steps):
+                if s * layers + l in wanted:
+                    assert torch.equal(outs[s][l], every[s][l]), (s, l)
+                elif outs[s][l] is not None:
+                    assert bool((outs[s][l] == 7.0).all()), (s, l)
