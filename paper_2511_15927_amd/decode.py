@@ -53,7 +53,10 @@ class BlockDecodeLoop:
         self._graph = None
         # few enough chains: the whole block is one launch (bimamba_block_stack), whose table of pointers sits on the device
         self._one_launch = self.n_layers > 0 and self.n_steps > 0 and bd.bimamba_block_stack_form(self.desc) == 1
-        self._table, self._table_dev = None, None
+        # (uploaded here: under a caller's own capture, which the first run may be, it could not be)
+        self._table, self._table_dev, self._captured = None, None, []
+        if self._one_launch:
+            self._upload(self._stack_table())
 
     def layer_output(self, step, layer):
         assert self.keep
@@ -89,26 +92,40 @@ class BlockDecodeLoop:
             bd.bimamba_block_fwd(*a, self.ws, stream=stream)
 
     def _stack_table(self):
-        """The pointers bimamba_block_stack works from, on the host and on the device; uploaded anew (into memory of its own: a
-        captured block keeps its copy) when one of them has changed."""
+        """The pointers bimamba_block_stack works from."""
         has_tail = self.tail[0].shape[1] > 0
         layers = [bd.StackLayer(pf, pb, h.data_ptr(), t.data_ptr() if has_tail else None)
                   for (pf, pb), h, t in zip(self._params, self.h, self.tail)]
         steps = [bd.make_inputs(s) for s in self.step_inputs]
         outs = [self.out[s] if l == self.n_layers - 1 else self._act[s * self.n_layers + l] if self.keep else None
                 for s in range(self.n_steps) for l in range(self.n_layers)]
-        table = bd.make_stack_table(layers, steps, outs)
+        return bd.make_stack_table(layers, steps, outs)
+
+    def _upload(self, table):
+        dev = torch.frombuffer(bytearray(table), dtype=torch.uint8).to(self.out[0].device)
+        if self._table_dev is not None:
+            torch.cuda.synchronize()   # (launches that read the one before have run)
+        self._table, self._table_dev = table, dev
+
+    def _run_stack(self, stream):
+        """The whole block in one launch.  False: the tensors have changed since the table was uploaded, and a stream that is being
+        captured cannot upload it anew."""
+        table = self._stack_table()
+        with torch.cuda.stream(stream):
+            capturing = torch.cuda.is_current_stream_capturing()
         if table != self._table:
-            self._table_dev = torch.frombuffer(bytearray(table), dtype=torch.uint8).to(self.out[0].device)
-            torch.cuda.synchronize()
-            self._table = table
-        return self._table, self._table_dev
+            if capturing:
+                return False
+            self._upload(table)
+        if capturing and not any(t is self._table_dev for t in self._captured):
+            self._captured.append(self._table_dev)   # the captured launch reads it at every replay
+        bd.bimamba_block_stack(self.desc, self.n_layers, self.n_steps, self._table, self._table_dev, stream=stream)
+        return True
 
     def run_block_eager(self, stream=None):
         """All steps of one block, call by call (in one launch where the library can); the last step commits every layer's
         state and conv tail in place."""
-        if self._one_launch:
-            bd.bimamba_block_stack(self.desc, self.n_layers, self.n_steps, *self._stack_table(), stream=stream)
+        if self._one_launch and self._run_stack(stream):
             return
         for step in range(self.n_steps):
             commit = step == self.n_steps - 1
@@ -135,7 +152,6 @@ class BlockDecodeLoop:
         self._graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(self._graph):
             self.run_block_eager()
-        self._graph_table = self._table_dev   # (the captured launch reads it)
         # the capture itself does not run the kernels: the cache is untouched
         return self
 

@@ -290,3 +290,30 @@ def test_stack_errors_are_decided_on_the_host():
     assert call(outs=(at(3), None, None, at(20))) == -8                    # in place over the first step's x
     assert call(outs=(at(10) + 2 * Dn * (L - 1), None, None, at(20))) == -8   # the last row of the second step's dt, by a first-step output
     assert call(outs=(None, None, None, at(12) - 2 * Dn * L + 2)) == -8    # ends in the first value of the second step's C
+
+
+def test_a_block_can_be_captured_without_a_run_before(monkeypatch):
+    """run_block_eager under a caller's own capture: nothing is uploaded and nothing waited for.  Tensors replaced since the upload are read
+    call by call there, and by the next launch outside; the table that a captured launch reads is kept."""
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    cfg = synth.mixer_cfg(2, 8, 12, d_state=4)
+    layer = (synth.make_params(cfg, 1, 0), synth.make_params(cfg, 1, 1))
+    loop = BlockDecodeLoop(cfg, [layer, layer], 2, device="cpu")
+    state, launches, calls, waits = dict(capturing=True), [], [], []
+    monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: state["capturing"])
+    monkeypatch.setattr(torch.cuda, "synchronize", lambda *a: waits.append(state["capturing"]))
+    monkeypatch.setattr(bd, "bimamba_block_stack", lambda desc, nl, ns, table, dev, stream=None: launches.append((table, dev)))
+    monkeypatch.setattr(bd, "bimamba_block_fwd", lambda *a, stream=None: calls.append(a[3].x.ptr))
+    loop.run_block_eager()
+    assert len(launches) == 1 and not calls and not waits
+    first = launches[0]
+    assert first[1].numpy().tobytes() == first[0]
+    loop.step_inputs[0]["x"] = torch.zeros_like(loop.step_inputs[0]["x"])
+    loop.run_block_eager()
+    assert len(launches) == 1 and len(calls) == 4 and calls[0] == loop.step_inputs[0]["x"].data_ptr() and not waits
+    state["capturing"] = False
+    loop.run_block_eager()
+    loop.run_block_eager()
+    assert len(launches) == 3 and launches[1][1] is launches[2][1] is not first[1] and waits == [False] and len(calls) == 4
+    assert launches[1][0] == launches[1][1].numpy().tobytes() != first[0]
+    assert [t is first[1] for t in loop._captured] == [True]

@@ -1,7 +1,8 @@
 """The block-diffusion decode loop (Sec. 4.3): n_layers x n_steps block calls per block, captured once as a HIP graph
 and replayed per block.  Every layer call of every step is checked against the fp64 oracle fed that call's own input
 (layer by layer), the committed caches against the oracle's chain, and graph replays against eager runs bit for bit
-(several replays, with eager work and synchronisation between them)."""
+(several replays, with eager work and synchronisation between them).  Blocks of few chains are one launch (bimamba_block_stack),
+which needs no workspace; the same blocks are run call by call too."""
 import numpy as np
 import pytest
 import torch
@@ -12,8 +13,8 @@ from paper_2511_15927_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("layout,G,static", [("selective", 32, False), ("selective", 64, True), ("selective_sweep", 32, False),
-                                             ("selective_sweep", 96, True), ("mamba2", 32, False), ("mamba2", 128, False)])
+@pytest.mark.parametrize("layout,G,static", [("selective", 32, False), ("selective", 64, True), ("selective_calls", 32, False), ("selective_calls", 64, True),
+                                             ("selective_sweep", 32, False), ("selective_sweep", 96, True), ("mamba2", 32, False), ("mamba2", 128, False)])
 def test_decode_loop_graph_matches_oracle_layer_by_layer(oracle, layout, G, static):
     from paper_2511_15927_amd import binding as bd
     from paper_2511_15927_amd.decode import BlockDecodeLoop
@@ -26,6 +27,9 @@ def test_decode_loop_graph_matches_oracle_layer_by_layer(oracle, layout, G, stat
     Bt, Dn, N, K = cfg["batch"], cfg["d_inner"], cfg["d_state"], cfg["d_conv"]
     params = [(synth.make_params(cfg, 3000 + l, 0), synth.make_params(cfg, 3000 + l, 1)) for l in range(n_layers)]
     loop = BlockDecodeLoop(cfg, params, n_steps, keep_layer_outputs=True, static_scratch=static)
+    assert loop._one_launch == (layout in ("selective", "selective_calls"))
+    if layout == "selective_calls":
+        loop._one_launch = False
     g = torch.Generator().manual_seed(G)
     h_ref, tail_ref = [], []
     for l in range(n_layers):        # a cache as some earlier blocks might have left it
@@ -46,7 +50,7 @@ def test_decode_loop_graph_matches_oracle_layer_by_layer(oracle, layout, G, stat
         torch.cuda.synchronize()
         got = [[loop.layer_output(s, l).float().cpu().numpy() for l in range(n_layers)] for s in range(n_steps)]
         cache = [(h.clone(), t.clone()) for h, t in zip(loop.h, loop.tail)]
-        # the same block, launch by launch, from the same cache: bit-identical outputs and caches
+        # the same block, eagerly, from the same cache: bit-identical outputs and caches
         for (h0, t0), h, t in zip(saved, loop.h, loop.tail):
             h.copy_(h0)
             t.copy_(t0)
@@ -95,3 +99,80 @@ def test_decode_loop_prefill_then_blocks_equals_full_forward_scan(oracle):
     _, h_full = oracle.one_direction(dict(cfg, seqlen=77 + 3 * 32), to_np(pf), whole, +1)
     assert rel_l2(loop.h[0].cpu().numpy(), h_full) < 1e-5
     assert np.array_equal(loop.tail[0].float().cpu().numpy(), whole["x"][:, -3:])
+
+
+@pytest.mark.parametrize("batch,G,Dn,N,keep", [(2, 32, 192, 16, True), (1, 37, 260, 8, False), (1, 100, 1030, 4, True)])
+def test_block_in_one_launch_equals_its_calls(batch, G, Dn, N, keep):
+    """The one launch against the chain of calls that it stands for, from one cache: fp32 I/O, so that nothing is rounded between the
+    layers.  Each side is within 1e-5 of the oracle at every layer (the library's fp32 bound); five layers feed each other."""
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    n_layers, n_steps = 5, 3
+    cfg = synth.mixer_cfg(batch, G, Dn, d_state=N, io="f32")
+    params = [(synth.make_params(cfg, 3400 + l, 0), synth.make_params(cfg, 3400 + l, 1)) for l in range(n_layers)]
+    inputs = [synth.make_inputs(cfg, 3450 + s) for s in range(n_steps)]
+    results = []
+    for one_launch in (True, False):
+        loop = BlockDecodeLoop(cfg, params, n_steps, keep_layer_outputs=keep)
+        assert loop._one_launch
+        loop._one_launch = one_launch
+        g = torch.Generator().manual_seed(G)
+        for h, t in zip(loop.h, loop.tail):
+            h.copy_(0.2 * torch.randn(h.shape, generator=g))
+            t.copy_(torch.randn(t.shape, generator=g))
+        for s in range(n_steps):
+            loop.set_step_inputs(s, inputs[s])
+        loop.run_block_eager()
+        torch.cuda.synchronize()
+        outs = [loop.layer_output(s, l) for s in range(n_steps) for l in range(n_layers)] if keep else loop.out
+        results.append(([t.cpu().numpy() for t in outs + loop.h], [t.cpu() for t in loop.tail]))
+    (a, tails_a), (b, tails_b) = results
+    for i, (x, y) in enumerate(zip(a, b)):
+        assert rel_l2(x, y) < 1e-5 * 2 * n_layers, i
+    assert torch.equal(tails_a[0], tails_b[0])                          # the first layer's x is the same
+    for x, y in zip(tails_a[1:], tails_b[1:]):
+        assert rel_l2(x.numpy(), y.numpy()) < 1e-5 * 2 * n_layers
+
+
+def test_block_in_a_callers_own_graph():
+    """run_block_eager captured without a run before, and again after a step's tensor was replaced: the replays of either graph are the block
+    of the tensors that stood there at its capture, whatever ran between."""
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    cfg = synth.mixer_cfg(2, 32, 192)
+    params = [(synth.make_params(cfg, 3500 + l, 0), synth.make_params(cfg, 3500 + l, 1)) for l in range(3)]
+    loop = BlockDecodeLoop(cfg, params, 2)
+    assert loop._one_launch
+    for s in range(2):
+        loop.set_step_inputs(s, synth.make_inputs(cfg, 3550 + s))
+    h0 = [torch.full_like(h, 0.1) for h in loop.h]
+    t0 = [torch.zeros_like(t) for t in loop.tail]
+
+    def run(fn):
+        for old, new in ((loop.h, h0), (loop.tail, t0)):
+            for a, b in zip(old, new):
+                a.copy_(b)
+        fn()
+        torch.cuda.synchronize()
+        return [t.clone() for t in loop.out + loop.h + loop.tail]
+
+    def capture():
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            loop.run_block_eager()
+        return graph
+
+    same = lambda a, b: all(torch.equal(x, y) for x, y in zip(a, b))
+    old_x = loop.step_inputs[0]["x"]
+    first = capture()
+    want_first = run(loop.run_block_eager)
+    assert same(run(first.replay), want_first)
+    loop.step_inputs[0]["x"] = torch.ones_like(old_x)
+    second = capture()                       # (call by call)
+    want_second = run(loop.run_block_eager)  # (uploads the table anew)
+    loop._one_launch = False
+    want_calls = run(loop.run_block_eager)
+    loop._one_launch = True
+    for _ in range(3):
+        assert same(run(first.replay), want_first)
+        assert same(run(second.replay), want_calls)
+        assert same(run(loop.run_block_eager), want_second)
+    assert not torch.equal(want_first[0], want_second[0])
