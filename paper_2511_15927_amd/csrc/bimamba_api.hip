@@ -529,7 +529,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
     if (plan.ssd && !(pairs_readable(in_f->x) && pairs_readable(in_b->x) && is_aligned(h_in, 16) && is_aligned(h_out, 16)))
         plan.ssd = false;
     // the state pass of the time parts addresses a chunk's rows of x with 32-bit byte offsets, the walk its rows of z and out
-    // (where it can: SsdArgs::far)
+    // (but in kSsdFarParts)
     constexpr int64_t kMaxNearStride = 1 << 24;
     const bool far = in_f->z.stride_token > kMaxNearStride || in_b->z.stride_token > kMaxNearStride || out->stride_token > kMaxNearStride;
     if (plan.ssd && plan.ssd_parts > 1 && (in_f->x.stride_token > kMaxNearStride || in_b->x.stride_token > kMaxNearStride)) {

@@ -245,6 +245,8 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
 
 // Output modes of the chunk walk (ssd_wide.h).
 enum { kSsdFinalOnly = 0, kSsdPartial = 1, kSsdPartialRaw = 2, kSsdFinalAdd = 3, kSsdFinalAddRaw = 4 };
+// Its forms.
+constexpr int kSsdWhole = 0, kSsdParts = 1, kSsdFarParts = 2;
 
 struct SsdArgs {
     TensorArg x, z, dt;
@@ -254,13 +256,13 @@ struct SsdArgs {
     const float* score_op;
     void* out;
     long long out_sb, out_st;
-    float* partial;       // [batch][L][Dn] fp32
+    void* partial;        // [batch][L][Dn]: bf16 where an item is walked whole, fp32 in the form for time parts (ssd_wide.h)
     const float* h_in;    // [batch][Dn][N] or null
     float* h_out;         // or null
     const void* tail_in;  // bf16 [batch][K-1][tail_ch] or null (causal direction only)
     int L, Dn, H, HG, G, K, tail_ch, nchunk;
     int dir, mode, out_ch_off, dt_softplus, d_per_head;
-    int far;              // z or out rows are too far apart for a chunk's 32-bit row offsets (a form of ssd_wide_kernel has none)
+    int far;              // z or out rows are too far apart for a chunk's 32-bit row offsets (kSsdFarParts)
     // Time parts (calls with too few (batch, head) items to fill the chip): the chunks are dealt to `parts` workgroups
     // per item, part_chunks each, in scan order.  A part is part_subs sub-parts of sub_chunks chunks;
     // ssd_state_kernel leaves every sub-part's end state from a zero start and the product of its chunk decays (all

@@ -29,7 +29,7 @@
 // The result one direction parks for the other crosses global memory as bf16: in the paper's precision (bf16 autocast,
 // App. A) each direction's output is a bf16 tensor before the two are added (eq. 6).  In time parts it stays fp32.
 //
-// grid (H / HEADS, directions * parts, batch).  Calls of several chunks; without PARTS, z / out token strides up to 2^24 elements (the host checks).
+// grid (H / HEADS, directions * parts, batch).  Calls of several chunks; z / out token strides up to 2^24 elements but in the form for rows far apart.
 #pragma once
 #include "ssd_kernels.h"
 
@@ -50,20 +50,22 @@ struct SsdWide {
 
 // MODE: the output mode, compiled apart (the registers of one mode are not held through another's loop); kSsdFinalOnly walks
 // both directions in one launch (see launch_ssd_scan), the others one.
-// PARTS: the launch deals every item's chunks to several workgroups in scan order (blockIdx.y: the part, then the direction), each from
-// the state that ssd_state_kernel and ssd_carry_kernel left for it, and what one direction parks for the other stays fp32.
-// Calls whose z or out rows lie too far apart for 32-bit offsets within a chunk (a.far; SsdArgs) take this form too, also with one part: it
-// asks per chunk whether the offsets serve and addresses every row by itself where they do not.
+// FORM: kSsdWhole: a workgroup walks an item's chunks.  kSsdParts: the launch deals them to several in scan order (blockIdx.y: the part,
+// then the direction), each from the state that ssd_state_kernel and ssd_carry_kernel left for it, and what one direction parks for
+// the other stays fp32.  kSsdFarParts: the same, one part or more, every row addressed by itself, for calls whose z or out rows lie
+// too far apart for 32-bit offsets within a chunk.  (A form of its own: asked per chunk in the other, whether the offsets serve
+// cost calls whose rows are near 1.6 %, 64 heads x 32, N 64, 1 x 16384 tokens.)
 // Against one walk of eight waves a part, calls of 64 heads x 64, N 128: 1 x 32768 tokens 953 -> 890 us, 1 x 8192 279 -> 255, 2 x 8192
 // 476 -> 440, 1 x 2048 103 -> 90; 64 heads x 32, N 64, 1 x 16384 340 -> 258.
-template <int N, int P, int HEADS, int MODE, bool PARTS>
+template <int N, int P, int HEADS, int MODE, int FORM>
 __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_kernel(const std::conditional_t<(MODE > 0), SsdArgs, SsdStatePair> launch)
 {
+    constexpr bool kParts = FORM != kSsdWhole;
     // (the parameter's type names no enumerator: those of an unnamed enumeration are spelt differently in a kernel's host and device name)
     static_assert(kSsdFinalOnly == 0);
     const SsdArgs& a = [&]() -> const SsdArgs& {
         if constexpr (MODE != kSsdFinalOnly) return launch;
-        else return launch.dir[PARTS ? (int)blockIdx.y >= launch.dir[0].parts : blockIdx.y];
+        else return launch.dir[kParts ? (int)blockIdx.y >= launch.dir[0].parts : blockIdx.y];
     }();
     using W = SsdWide<N, P, HEADS>;
     constexpr int kPB = W::kPB, kNB = W::kNB;
@@ -96,10 +98,10 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
     const int grp = head / a.HG;
     const int ch0 = head * P;
     // this workgroup's chunks [c0, c0 + nchunk), below by their place in it; period p: chunk p / HEADS, head p % HEADS
-    const int part = !PARTS ? 0 : (int)blockIdx.y - ((int)blockIdx.y >= a.parts ? a.parts : 0), c0 = !PARTS ? 0 : part * a.part_chunks;
-    const int nchunk = !PARTS ? a.nchunk : min(a.nchunk - c0, a.part_chunks), periods = nchunk * HEADS, q0 = c0 * kQ;
-    const float* const state_in = !PARTS ? a.h_in : a.part_state + (size_t)part * a.part_subs * gridDim.z * a.Dn * N;
-    float* const state_out = !PARTS || part == a.parts - 1 ? a.h_out : nullptr;
+    const int part = !kParts ? 0 : (int)blockIdx.y - ((int)blockIdx.y >= a.parts ? a.parts : 0), c0 = !kParts ? 0 : part * a.part_chunks;
+    const int nchunk = !kParts ? a.nchunk : min(a.nchunk - c0, a.part_chunks), periods = nchunk * HEADS, q0 = c0 * kQ;
+    const float* const state_in = !kParts ? a.h_in : a.part_state + (size_t)part * a.part_subs * gridDim.z * a.Dn * N;
+    float* const state_out = !kParts || part == a.parts - 1 ? a.h_out : nullptr;
     const int last = a.L - 1;
     auto token_of = [&](int tau) { return a.dir > 0 ? tau : last - tau; };
     // the prepared tiles of (chunk c, this group)
@@ -480,7 +482,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
     // the lane is group[rt] (in the lane offset) plus step[r] (a scalar offset): no vector address arithmetic
     const int fwd = a.dir > 0;
     const unsigned zs = (unsigned)a.z.st * 2u, os = (unsigned)a.out_st * 2u;
-    using Park = std::conditional_t<PARTS, float, T>;   // what one direction leaves for the other: bf16 where a call is walked whole
+    using Park = std::conditional_t<kParts, float, T>;   // what one direction leaves for the other: bf16 where a call is walked whole
     const unsigned ps = (unsigned)a.Dn * (unsigned)sizeof(Park);
     unsigned zoff[2], ooff[2], poff[2];
 #pragma unroll
@@ -504,12 +506,11 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
     Park* const phead = (Park*)a.partial + (size_t)b * a.L * a.Dn + my_ch0;
     T* const ohead = (T*)a.out + (size_t)b * a.out_sb + a.out_ch_off + my_ch0;
     auto chunk_low_token = [&](int c) { return (long long)(fwd ? q0 + c * kQ : last - (q0 + c * kQ + kQ - 1)); };
-    const int last_near = PARTS && a.far ? -1 : last;
-    auto inside = [&](int c) { return q0 + c * kQ + kQ - 1 <= last_near; };
+    auto inside = [&](int c) { return FORM != kSsdFarParts && q0 + c * kQ + kQ - 1 <= last; };
     auto token_at = [&](int c, int k) { return (long long)token_of(min(q0 + c * kQ + i0 + 16 * (k / 4) + k % 4, last)); };
 
     typedef unsigned __attribute__((ext_vector_type(2))) uint2v;
-    using ParkPair = std::conditional_t<PARTS, uint2v, unsigned>;
+    using ParkPair = std::conditional_t<kParts, uint2v, unsigned>;
     unsigned zraw[8];   // register k: row 16 (k / 4) + k % 4 of the lane, a channel pair
     ParkPair praw[8];
     auto issue_z = [&](int c) {
@@ -532,7 +533,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
             const Rsrc pr = raw_range(phead + chunk_low_token(c) * a.Dn);
 #pragma unroll
             for (int k = 0; k < 8; k++) {
-                if constexpr (PARTS) praw[k] = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(pr, poff[k / 4], pstep[k % 4], 0));
+                if constexpr (kParts) praw[k] = __builtin_bit_cast(uint2v, __builtin_amdgcn_raw_buffer_load_b64(pr, poff[k / 4], pstep[k % 4], 0));
                 else praw[k] = __builtin_amdgcn_raw_buffer_load_b32(pr, poff[k / 4], pstep[k % 4], 0);
             }
         } else {
@@ -621,7 +622,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
 #pragma unroll
             for (int ct = 0; ct < 2; ct++) {
                 float pv = 0.0f;
-                if constexpr (need_p && PARTS) pv = __uint_as_float(praw[k][ct]);
+                if constexpr (need_p && kParts) pv = __uint_as_float(praw[k][ct]);
                 else if constexpr (need_p) pv = ct == 0 ? lo(praw[k]) : hi(praw[k]);
                 if constexpr (!need_z) v[ct] = y[k][ct];
                 else {
@@ -629,7 +630,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
                     v[ct] = MODE == kSsdFinalAddRaw ? (y[k][ct] + pv) * zg : need_p ? y[k][ct] * zg + pv : y[k][ct] * zg;
                 }
             }
-            if constexpr (parks && PARTS) {
+            if constexpr (parks && kParts) {
                 res[k] = Result{__float_as_uint(v[0]), __float_as_uint(v[1])};
             } else {
                 const bf16x2 pair = {(__bf16)v[0], (__bf16)v[1]};
@@ -641,7 +642,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
             const Rsrc orr = raw_range(parks ? (const void*)(phead + t0 * a.Dn) : (const void*)(ohead + t0 * a.out_st));
 #pragma unroll
             for (int k = 0; k < 8; k++) {
-                if constexpr (parks && PARTS) __builtin_amdgcn_raw_buffer_store_b64(res[k], orr, poff[k / 4], pstep[k % 4], 0);
+                if constexpr (parks && kParts) __builtin_amdgcn_raw_buffer_store_b64(res[k], orr, poff[k / 4], pstep[k % 4], 0);
                 else if constexpr (parks) __builtin_amdgcn_raw_buffer_store_b32(res[k], orr, poff[k / 4], pstep[k % 4], 0);
                 else __builtin_amdgcn_raw_buffer_store_b32(res[k], orr, ooff[k / 4], ostep[k % 4], 0);
             }

@@ -4,32 +4,32 @@
 
 namespace bm {
 
-template <int HEADS, int MODE, bool PARTS>
+template <int HEADS, int MODE, int FORM>
 static hipError_t variant(const SsdStatePair& sp, int batch, hipStream_t st)
 {
     static LdsLimit limit;
     using W = SsdWide<BM_N, BM_P, HEADS>;
-    auto kernel = ssd_wide_kernel<BM_N, BM_P, HEADS, MODE, PARTS>;
+    auto kernel = ssd_wide_kernel<BM_N, BM_P, HEADS, MODE, FORM>;
     if (W::bytes() > 64 * 1024) {
         const hipError_t err = limit.raise(reinterpret_cast<const void*>(kernel), W::bytes());
         if (err != hipSuccess) return err;
     }
-    const unsigned parts = PARTS ? (unsigned)sp.dir[0].parts : 1u;
+    const unsigned parts = FORM != kSsdWhole ? (unsigned)sp.dir[0].parts : 1u;
     const dim3 grid((unsigned)(sp.dir[0].H / HEADS), MODE == kSsdFinalOnly ? 2u * parts : parts, (unsigned)batch), block(W::kThreads);
     if constexpr (MODE == kSsdFinalOnly) hipLaunchKernelGGL(kernel, grid, block, W::bytes(), st, sp);
     else hipLaunchKernelGGL(kernel, grid, block, W::bytes(), st, sp.dir[0]);
     return hipSuccess;
 }
 
-template <int HEADS, bool PARTS>
+template <int HEADS, int FORM>
 static hipError_t launch(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    if (dirs == 2) return variant<HEADS, kSsdFinalOnly, PARTS>(sp, batch, st);
+    if (dirs == 2) return variant<HEADS, kSsdFinalOnly, FORM>(sp, batch, st);
     switch (sp.dir[0].mode) {
-        case kSsdPartial: return variant<HEADS, kSsdPartial, PARTS>(sp, batch, st);
-        case kSsdPartialRaw: return variant<HEADS, kSsdPartialRaw, PARTS>(sp, batch, st);
-        case kSsdFinalAdd: return variant<HEADS, kSsdFinalAdd, PARTS>(sp, batch, st);
-        default: return variant<HEADS, kSsdFinalAddRaw, PARTS>(sp, batch, st);
+        case kSsdPartial: return variant<HEADS, kSsdPartial, FORM>(sp, batch, st);
+        case kSsdPartialRaw: return variant<HEADS, kSsdPartialRaw, FORM>(sp, batch, st);
+        case kSsdFinalAdd: return variant<HEADS, kSsdFinalAdd, FORM>(sp, batch, st);
+        default: return variant<HEADS, kSsdFinalAddRaw, FORM>(sp, batch, st);
     }
 }
 
@@ -40,9 +40,10 @@ static hipError_t launch(const SsdStatePair& sp, int dirs, int batch, hipStream_
 hipError_t BM_NAME(BM_N, BM_P)(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     const SsdArgs& sa = sp.dir[0];
-    if (sa.parts > 1 || sa.far) return launch<1, true>(sp, dirs, batch, st);
-    if (sa.HG % 2 == 0 && (long long)sa.H * batch * dirs > cu_count()) return launch<2, false>(sp, dirs, batch, st);
-    return launch<1, false>(sp, dirs, batch, st);
+    if (sa.far) return launch<1, kSsdFarParts>(sp, dirs, batch, st);
+    if (sa.parts > 1) return launch<1, kSsdParts>(sp, dirs, batch, st);
+    if (sa.HG % 2 == 0 && (long long)sa.H * batch * dirs > cu_count()) return launch<2, kSsdWhole>(sp, dirs, batch, st);
+    return launch<1, kSsdWhole>(sp, dirs, batch, st);
 }
 
 }  // namespace bm
