@@ -9,6 +9,7 @@ bounded sample of the same workload.
 import argparse
 import json
 import os
+import subprocess
 import sys
 import time
 
@@ -43,10 +44,21 @@ def parse():
     return ap.parse_args()
 
 
+def library_kernels():
+    """The kernels that the built library holds, as rocprofv3 names them."""
+    lib = os.path.join(ROOT, "paper_2511_15927_amd", "libbimamba.so")
+    try:
+        out = subprocess.run(["nm", "-DC", lib], stdout=subprocess.PIPE, stderr=subprocess.DEVNULL, text=True).stdout
+    except OSError:
+        return set()
+    return {line.split(" ", 2)[2] for line in out.splitlines() if line.count(" ") >= 2}
+
+
 def read_profile(kernel_key):
     """The committed rocprofv3 --pmc summary of this workload's dominant kernel (profiles/<key>_pmc.txt, written by
     paper_2511_15927_amd.profile_summary): counters as floats, plus the kernel name and the file the values come from.
-    These are STORED values of an earlier run of this same command, not measurements of the present run."""
+    These are STORED values of an earlier run of this same command, not measurements of the present run; kernels that the
+    library no longer has count for nothing."""
     path = os.path.join(ROOT, "profiles", kernel_key + "_pmc.txt")
     sections, kernel, shared = {}, None, {}
     try:
@@ -59,22 +71,25 @@ def read_profile(kernel_key):
                 (sections[kernel] if kernel else shared)[k.strip()] = float(v.strip())
     except Exception:
         return {}, None, None
-    ours = {k: v for k, v in sections.items() if "bm::" in k}
+    built = library_kernels()
+    ours = {k: v for k, v in sections.items() if "bm::" in k and k in built}
     if not ours:
         return {}, None, None
     # the dominant kernel of the step: the one with the longest dispatch
     kernel = max(ours, key=lambda k: ours[k].get("DURATION_NS_UNDER_PMC", 0.0))
     counters = dict(shared, **ours[kernel])
-    # bytes of a step: of all forms of that kernel (the chunked path launches one per direction)
-    for key in ("FETCH_BYTES_PER_LAUNCH", "WRITE_BYTES_PER_LAUNCH"):
-        forms = [c[key] for k, c in ours.items() if k.split("<")[0] == kernel.split("<")[0] and key in c]
-        if forms:
-            counters[key] = sum(forms)
+    # the chunked walk is a launch and a form per direction: a step's bytes are those of both
+    if "ssd_wide_kernel" in kernel:
+        for key in ("FETCH_BYTES_PER_LAUNCH", "WRITE_BYTES_PER_LAUNCH"):
+            forms = [c[key] for k, c in ours.items() if k.split("<")[0] == kernel.split("<")[0] and key in c]
+            if forms:
+                counters[key] = sum(forms)
     return counters, kernel, os.path.relpath(path, ROOT)
 
 
 def traffic_of(c):
-    """HBM bytes per step of the dominant kernel (fetch + write, each scaled by the copy calibration)."""
+    """HBM bytes per step of the dominant kernel, both launches of one that has a launch per direction (fetch + write, each
+    scaled by the copy calibration)."""
     try:
         return c["FETCH_BYTES_PER_LAUNCH"] + c["WRITE_BYTES_PER_LAUNCH"]
     except KeyError:

@@ -36,3 +36,28 @@ def test_algorithmic_bytes_and_flops_of_the_headline():
     assert shapes.algorithmic_bytes(cfg) == tokens * (3 * 4096 + 2 * 16 + 4096) * 2     # 8 B per token-channel + B, C
     assert shapes.algorithmic_flops(cfg) == tokens * 4096 * (2 * (22 + 7 * 16) + 1)
     assert synth.conv_channels(synth.CONFIGS["paper_1p3b"]) == 4096
+
+
+def test_stored_counters_count_only_for_kernels_that_exist(tmp_path, monkeypatch):
+    """bench.py's stored counters: of a kernel that the library has, summed over the directions' launches of the chunked walk only, and
+    nothing from a profile of a kernel that is gone."""
+    import bench
+    have = sorted(k for k in bench.library_kernels() if "bm::sweep_kernel<16, 2, 0, bm::IoBF16" in k)
+    walk = sorted(k for k in bench.library_kernels() if "bm::ssd_wide_kernel<128, 64, 2" in k)
+    assert len(have) == 2 and len(walk) >= 4
+    (tmp_path / "profiles").mkdir()
+
+    def stored(*sections):
+        text = "".join("# kernel: %s\nDURATION_NS_UNDER_PMC=%d\nFETCH_BYTES_PER_LAUNCH=%d\nWRITE_BYTES_PER_LAUNCH=1\n" % s for s in sections)
+        (tmp_path / "profiles" / "k_pmc.txt").write_text(text)
+        return bench.read_profile("k")
+
+    built = bench.library_kernels()
+    monkeypatch.setattr(bench, "library_kernels", lambda: built)
+    monkeypatch.setattr(bench, "ROOT", str(tmp_path))
+    gone = have[0].replace("<16, 2,", "<16, 2, 0,")
+    assert stored((gone, 9, 100)) == ({}, None, None)
+    counters, kernel, _ = stored((gone, 9, 100), (have[0], 5, 10), (have[1], 4, 20))
+    assert kernel == have[0] and bench.traffic_of(counters) == 11
+    counters, kernel, _ = stored((walk[0], 5, 10), (walk[1], 4, 20))
+    assert kernel == walk[0] and bench.traffic_of(counters) == 32
