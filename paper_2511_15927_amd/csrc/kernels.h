@@ -890,8 +890,8 @@ __device__ __forceinline__ void run_range(const SweepArgs& a, Chain<N, S, AKIND,
                 const float* next = kBcScalarAhead<N, S> ? (done + i + 1 < count ? c.bcrow + c.bcs : c.bcrow) : nullptr;
                 if constexpr (kBcScalarAhead<N, S> && !kRefill) {
                     // scalar loads return in any order, so waiting for one waits for all: this token's row, requested a token
-                    // ago, before the next request (16 x 2048 tokens of 4096 channels 995 -> 933 us, 8 x 2048 814 -> 725).  The
-                    // shorter tokens of fewer states do not cover a request: every second one waiting costs them 1 to 3 % less.
+                    // ago, before the next request (24 x 2048 tokens of 4096 channels 1184 -> 1160 us).  The shorter tokens of fewer
+                    // states do not cover a request: every second one waiting costs them 1 to 3 % less.
                     if constexpr (N == 16) asm volatile("" ::"s"(row.v[0]), "s"(row.v[2 * NS - 1]));
                     load_bc_scalar<N>(next, row_next);
                     __builtin_amdgcn_sched_barrier(0);

@@ -1,4 +1,4 @@
-// Mamba-2 calls of up to 64 tokens (block-diffusion steps), both directions, without a barrier.
+// Mamba-2 calls of up to 64 tokens (block-diffusion steps), both directions, without a barrier between the phases of a wave.
 //
 // Such a call is 1500 vector instructions and 46 KB of memory traffic an item (batch, head) at 32 tokens of 64 channels: what it
 // costs is the length of its chains of loads and phases.  Here a wave owns 16 channels over the whole block and does all phases
@@ -9,6 +9,10 @@
 // a call of 16 x 32 tokens, 64 heads x 64, 128 states took 26.2 us, most of it address and tag cycles; 18.8 now, the bytes alone
 // 9).  The score tiles and operands that all heads of a group share come from ssd_block_prep_kernel, one workgroup per (direction,
 // group, batch element).  (Before: a workgroup an item with producer and consumer waves, one direction after the other, 39.9.)
+//
+// The barriers of the walk are those of the sharing: the first before the convs, which read x and the score operands that all four
+// waves have put into LDS; the last before the output's rows are read back from the y columns that the waves have left there.  With
+// more than 32 tokens y lies over x and the operands, and one more orders their last reads before it.
 //
 // Both directions work in token order: the reverse direction's operands hold j >= i.  MFMA 16x16x32: operand A lane l holds row
 // l%16, B column l%16, eight contraction slots of group g = l/16; accumulator register r of lane l is row 4g + r, column l%16.
