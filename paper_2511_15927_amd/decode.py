@@ -12,7 +12,7 @@ The n_steps x n_layers calls of a block are captured ONCE into a HIP graph (torc
 the library's launches, which contain no memset nodes) and replayed per block; the caller refreshes the static step
 inputs between replays.  Nothing on this path mixes channels, so with few enough chains the whole block is one launch in which a
 workgroup takes a few channels through every layer of every step (bimamba_block_stack; at batch 1, 24 layers x 8 steps of 32
-tokens 1.44 -> 0.55 ms).  Otherwise the state of all layers (n_layers x batch x d_inner x d_state fp32, 100 MB at batch 16)
+tokens 1.44 -> 0.49 ms with the refresh of the step inputs).  Otherwise the state of all layers (n_layers x batch x d_inner x d_state fp32, 100 MB at batch 16)
 lives in HBM/L2 between calls and a call reads it once (4 MB per layer call against 8 MB of activations).
 """
 import torch
@@ -72,7 +72,7 @@ class BlockDecodeLoop:
             return (dst is self._step_views[step][k] and t.device == flat.device and t.dtype == flat.dtype and t.numel() == dst.numel() and not t.requires_grad and
                     t.untyped_storage().data_ptr() != own)
         if all(plain(k, dst) for k, dst in dsts.items()):
-            # one launch instead of five (24 layers x 8 steps of 32 tokens at batch 1: 530 -> 486 us a block)
+            # one launch instead of five (24 layers x 8 steps of 32 tokens at batch 1: 530 -> 486 us a block, refresh included)
             torch.cat([inputs[k].reshape(-1) for k in dsts], out=flat)
             return
         for k, dst in dsts.items():
