@@ -23,7 +23,8 @@ from . import synth
 
 class BlockDecodeLoop:
     def __init__(self, cfg, layer_params, n_steps, keep_layer_outputs=False, static_scratch=False, device="cuda"):
-        """cfg: block config (seqlen = G); layer_params: list of (params_f, params_b) dicts of CPU float32 tensors."""
+        """cfg: block config (seqlen = G); layer_params: list of (params_f, params_b) dicts of CPU float32 tensors.
+        static_scratch: the calls take the library's fixed scratch, not a workspace (a block in one launch needs neither)."""
         self.cfg, self.n_layers, self.n_steps = dict(cfg), len(layer_params), int(n_steps)
         self.desc = bd.make_desc(cfg)
         Bt, G, Dn, N, K = cfg["batch"], cfg["seqlen"], cfg["d_inner"], cfg["d_state"], cfg["d_conv"]
