@@ -35,7 +35,7 @@ def newest_dep(src, newest_all):
     """Modification time an object must beat: its source and the headers that source includes."""
     text = open(src).read()
     deps = [src, os.path.join(ROOT, "include", "bimamba.h")]
-    for h in ("kernels.h", "short_kernels.h", "launch.h", "ssd_kernels.h", "ssd_wide.h", "ssd_block.h", "bwd_kernels.h", "row_kernels.h", "stack_kernels.h"):
+    for h in ("kernels.h", "short_kernels.h", "launch.h", "ssd_kernels.h", "ssd_wide.h", "ssd_block.h", "bwd_kernels.h", "row_kernels.h", "stack_kernels.h", "stack_quad.h"):
         if h in text or (h == "kernels.h"):
             deps.append(os.path.join(CSRC, h))
     return max(os.path.getmtime(p) for p in deps)

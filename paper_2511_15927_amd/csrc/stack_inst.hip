@@ -1,6 +1,9 @@
 // Choice and launch of the one-launch form of a stack of layers (stack_kernels.h).
-#include "stack_kernels.h"
+#include "stack_quad.h"
 #include "launch.h"
+
+#include <algorithm>
+#include <cmath>
 
 namespace bm {
 
@@ -58,8 +61,61 @@ static hipError_t launch_io(const StackArgs& a, int batch, hipStream_t st)
     return launch_outputs<IO, 4>(a, batch, st);
 }
 
+// Steps side by side in the quad form, 0: the row form is the choice.  Clocks of a layer for all steps of a block, from what a SIMD's
+// waves issue: alone on its SIMD a wave issues an instruction every seven clocks, several share the vector pipe at 4.6 a slot.
+//   quad   34 / 22 / 16 slots a token and lane (16 / 8 / 4 states); a workgroup to a CU, side / 2 waves a SIMD; 2500 a layer
+//   row    14.5 instructions, 11.3 slots; time segments walk their tokens 1.6 times; 1300 a layer, one step after the other
+// Measured, us a layer and step, quad / row (bf16; layers feed each other):
+//   16 states, 32 tokens, 8 steps   512 chains 1.19/1.92, 4096 1.21/2.34, 8192 2.50/3.35, 16384 5.28/6.92, 32768 10.4/13.2, 45056 15.1/19.4
+//   4096 chains x 32, 1 / 2 / 3 / 4 steps   5.63/3.22  2.63/2.56  2.20/2.63  1.58/2.42
+//   2 x 16 tokens of 2856, 3 steps 1.84/2.14
+//   64 tokens    4096 chains, 8 steps 2.89/5.09, 1024 chains, 4 steps 2.91/3.07, 16384 chains, 8 steps 12.0/12.1
+//   128 tokens   1024 chains, 4 steps 8.88/3.88
+//   8 states     4096 chains x 32, 8 steps 0.93/2.47, 24576 6.22/10.9, 2616 x 64, 4 steps 2.08/4.80
+static int quad_steps(const StackArgs& a, int batch)
+{
+    const size_t bytes = (size_t)QuadLds(a.L, a.N).total * sizeof(float);
+    const int most = (int)std::min<size_t>(kQuadMaxSteps, kStackLdsBytes / bytes);
+    if (most < 1) return 0;
+    const int rounds = (a.n_steps + most - 1) / most, side = (a.n_steps + rounds - 1) / rounds;
+    const double cus = cu_count(), slots = a.N == 16 ? 34.0 : a.N == 8 ? 22.0 : 16.0;
+    const double quads = std::ceil((double)((a.Dn + kQuadChannels - 1) / kQuadChannels) * batch / cus);
+    const double quad = rounds * (a.L * slots * std::max(7.0, 4.6 * quads * side / 2) + 2500.0);
+    const double waves = (double)batch * ((a.Dn + 3) / 4) * 2 * a.nseg / (4 * cus);
+    const double tokens = a.nseg > 1 ? 1.6 * a.seg_len : a.L;
+    const double row = a.n_steps * (tokens * std::max(7.0 * 14.5, 4.6 * 11.3 * waves) + 1300.0);
+    return quad < row ? side : 0;
+}
+
+template <typename IO, int N>
+static hipError_t launch_quad(const StackArgs& a, int side, int batch, hipStream_t st)
+{
+    static LdsLimit limit;
+    auto kernel = stack_quad_kernel<IO, N>;
+    const size_t lds = (size_t)side * QuadLds(a.L, N).total * sizeof(float);
+    if (lds > 64 * 1024) {
+        const hipError_t err = limit.raise(reinterpret_cast<const void*>(kernel), kStackLdsBytes);
+        if (err != hipSuccess) return err;
+    }
+    const dim3 grid((unsigned)((a.Dn + kQuadChannels - 1) / kQuadChannels), 1, (unsigned)batch);
+    hipLaunchKernelGGL(kernel, grid, dim3(128u * (unsigned)side), lds, st, a, side);
+    return hipSuccess;
+}
+
+template <typename IO>
+static hipError_t launch_quad_io(const StackArgs& a, int side, int batch, hipStream_t st)
+{
+    switch (a.N) {
+        case 4: return launch_quad<IO, 4>(a, side, batch, st);
+        case 8: return launch_quad<IO, 8>(a, side, batch, st);
+        default: return launch_quad<IO, 16>(a, side, batch, st);
+    }
+}
+
 hipError_t launch_stack(int io_bf16, const StackArgs& a, int batch, hipStream_t st)
 {
+    if (const int side = quad_steps(a, batch); side > 0)
+        return io_bf16 ? launch_quad_io<IoBF16>(a, side, batch, st) : launch_quad_io<IoF32>(a, side, batch, st);
     return io_bf16 ? launch_io<IoBF16>(a, batch, st) : launch_io<IoF32>(a, batch, st);
 }
 

@@ -116,3 +116,65 @@ def test_stack_with_outputs_not_wanted(batch, L, Dn, io):
                     assert torch.equal(outs[s][l], every[s][l]), (s, l)
                 elif outs[s][l] is not None:
                     assert bool((outs[s][l] == 7.0).all()), (s, l)
+
+
+@pytest.mark.parametrize("batch,L,Dn,N,K,io,layers,steps,kw", [
+    (1, 1, 17, 16, 4, "f32", 2, 3, {}),                            # shorter than the tail and than a group; a ragged tile of channels
+    (2, 7, 16, 8, 3, "bf16", 1, 8, dict(dt_softplus=1)),           # one layer: committed and read in successive blocks
+    (1, 8, 5, 4, 2, "f32", 3, 5, {}),
+    (2, 9, 40, 16, 1, "f32", 2, 9, dict(dt_softplus=1)),           # two rounds of steps, the second with an idle slot; no tail
+    (1, 33, 130, 4, 4, "bf16", 2, 8, {}),
+    (1, 64, 64, 16, 4, "f32", 2, 8, dict(n_heads=4, n_groups=1, a_kind=1, d_kind=1)),   # four steps of eight fit the LDS
+    (3, 30, 128, 8, 4, "f32", 2, 4, dict(n_heads=16, n_groups=2)),
+])
+def test_stack_steps_side_by_side(oracle, batch, L, Dn, N, K, io, layers, steps, kw):
+    """Four lanes per chain, the steps of a block in one workgroup: every layer's output of every step and the committed caches of two
+    blocks, at block lengths around the groups of four and eight tokens, with and without a last round that is not full."""
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    cfg = synth.mixer_cfg(batch, L, Dn, d_state=N, d_conv=K, io=io, **kw)
+    params = [(synth.make_params(cfg, 170 + l, 0), synth.make_params(cfg, 170 + l, 1)) for l in range(layers)]
+    loop = BlockDecodeLoop(cfg, params, steps, keep_layer_outputs=True)
+    assert loop._one_launch
+    g = torch.Generator().manual_seed(L)
+    for h, t in zip(loop.h, loop.tail):
+        h.copy_(0.2 * torch.randn(h.shape, generator=g))
+        t.copy_(synth.round_io(torch.randn(t.shape, generator=g), io))
+    h_ref = [h.cpu().numpy().astype(np.float64) for h in loop.h]
+    tail_ref = [t.float().cpu().numpy().astype(np.float64) for t in loop.tail]
+    tol = 1e-5 if io == "f32" else 2e-2
+    for block in range(2):
+        inputs = [synth.make_inputs(cfg, 180 + 10 * block + s) for s in range(steps)]
+        for s in range(steps):
+            loop.set_step_inputs(s, inputs[s])
+        loop.run_block_eager()
+        torch.cuda.synchronize()
+        for s in range(steps):
+            for l in range(layers):
+                x = inputs[s]["x"].numpy() if l == 0 else loop.layer_output(s, l - 1).float().cpu().numpy()
+                ref, h_new, t_new = oracle.bimamba_block_fwd(cfg, to_np(params[l][0]), to_np(params[l][1]), dict(to_np(inputs[s]), x=x),
+                                                             h_in=h_ref[l], tail_in=tail_ref[l] if K > 1 else None)
+                assert_close(loop.layer_output(s, l).float().cpu().numpy(), ref, tol, (block, s, l))
+                if s == steps - 1:
+                    h_ref[l] = h_new
+                    if K > 1:
+                        tail_ref[l] = t_new
+        for l in range(layers):
+            assert rel_l2(loop.h[l].cpu().numpy(), h_ref[l]) < 1e-5, (block, l)
+            if K > 1:
+                assert np.array_equal(loop.tail[l].float().cpu().numpy().astype(np.float64), tail_ref[l]), (block, l)
+
+
+def test_stack_steps_do_not_reach_each_other():
+    """A step whose activations are infinite, beside others in a workgroup: theirs and the state that the last one commits stay finite."""
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    cfg = synth.mixer_cfg(1, 16, 32, io="f32")
+    loop = BlockDecodeLoop(cfg, [(synth.make_params(cfg, 190, 0), synth.make_params(cfg, 190, 1))], 3)
+    for s in range(3):
+        inputs = synth.make_inputs(cfg, 191 + s)
+        if s == 1:
+            inputs["x"][:, 6] = float("inf")
+        loop.set_step_inputs(s, inputs)
+    loop.run_block_eager()
+    torch.cuda.synchronize()
+    assert all(bool(torch.isfinite(loop.out[s]).all()) for s in (0, 2)) and bool(torch.isfinite(loop.h[0]).all())
+    assert not bool(torch.isfinite(loop.out[1][:, 6]).any())
