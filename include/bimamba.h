@@ -213,6 +213,12 @@ int bimamba_block_stack(const bimamba_desc* desc, int n_layers, int n_steps, con
                         void* hip_stream);
 int bimamba_block_stack_form(const bimamba_desc* desc);
 
+/*
+ * A call's x, z, dt, B and C into buffers of the caller, in one launch: a decode loop refreshes the fixed inputs of a captured step with
+ * it.  Both sides are views as for bimamba_fwd; the buffers must not overlap the sources or each other (BIMAMBA_ERR_ALIAS).
+ */
+int bimamba_copy_inputs(const bimamba_desc* desc, const bimamba_inputs* from, const bimamba_inputs* to, void* hip_stream);
+
 /* Gradients with respect to the activations one direction read.  dx, dz [batch, L, d_inner] and ddt [batch, L, n_heads]
  * are views in io_dtype like the inputs (written, one rounding each); dB, dC are contiguous fp32
  * [batch, L, n_groups, d_state] device arrays (sums over the channels of a group, formed in fp32 in a fixed order;

@@ -5,6 +5,7 @@ HIP library.  There is no fallback: if libbimamba.so has not been built, loading
 """
 import ctypes as C
 import os
+import struct
 
 import torch
 
@@ -21,8 +22,8 @@ STATUS = {0: "BIMAMBA_OK", -1: "BIMAMBA_ERR_NULL_POINTER", -2: "BIMAMBA_ERR_BAD_
           -7: "BIMAMBA_ERR_SCRATCH_EXCEEDED", -8: "BIMAMBA_ERR_ALIAS"}
 STATIC_SCRATCH_BYTES = 64 << 20
 
-EXPORTS = ("bimamba_fwd", "bimamba_block_fwd", "bimamba_block_fwd_static", "bimamba_block_stack", "bimamba_block_stack_form", "bimamba_bwd", "bimamba_workspace_bytes",
-           "bimamba_bwd_workspace_bytes", "bimamba_time_chunks", "bimamba_profile_next_call", "bimamba_status_string",
+EXPORTS = ("bimamba_fwd", "bimamba_block_fwd", "bimamba_block_fwd_static", "bimamba_block_stack", "bimamba_block_stack_form", "bimamba_copy_inputs", "bimamba_bwd",
+           "bimamba_workspace_bytes",           "bimamba_bwd_workspace_bytes", "bimamba_time_chunks", "bimamba_profile_next_call", "bimamba_status_string",
            "bimamba_version")
 
 
@@ -89,6 +90,8 @@ def lib():
         L.bimamba_block_stack.argtypes = [C.POINTER(Desc), C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p]
         L.bimamba_block_stack_form.restype = C.c_int
         L.bimamba_block_stack_form.argtypes = [C.POINTER(Desc)]
+        L.bimamba_copy_inputs.restype = C.c_int
+        L.bimamba_copy_inputs.argtypes = [C.POINTER(Desc), C.POINTER(Inputs), C.POINTER(Inputs), C.c_void_p]
         L.bimamba_bwd.restype = C.c_int
         L.bimamba_bwd.argtypes = [C.POINTER(Desc), C.POINTER(Params), C.POINTER(Params), C.POINTER(Inputs),
                                   C.POINTER(Inputs), C.POINTER(Tensor), C.POINTER(InputGrads), C.POINTER(InputGrads),
@@ -258,6 +261,23 @@ def bimamba_block_stack(desc, n_layers, n_steps, table, table_dev, stream=None, 
     rc = lib().bimamba_block_stack(C.byref(desc), n_layers, n_steps, table, C.c_void_p(table_dev.data_ptr()), _stream_ptr(stream))
     if check and rc != 0:
         raise BimambaError(rc, "bimamba_block_stack")
+    return rc
+
+
+_INPUT_WORDS = struct.Struct("=" + "Qqq" * 5)
+assert _INPUT_WORDS.size == C.sizeof(Inputs)
+
+
+def input_words(words):
+    """Inputs from pointer, batch stride and token stride of x, z, dt, B and C, in that order."""
+    return Inputs.from_buffer_copy(_INPUT_WORDS.pack(*words))
+
+
+def bimamba_copy_inputs(desc, src, dst, stream=None, check=True):
+    """Enqueue the copy of a call's inputs into buffers of the caller.  src, dst: Inputs structs."""
+    rc = lib().bimamba_copy_inputs(C.byref(desc), C.byref(src), C.byref(dst), _stream_ptr(stream))
+    if check and rc != 0:
+        raise BimambaError(rc, "bimamba_copy_inputs")
     return rc
 
 

@@ -89,6 +89,35 @@ __global__ __launch_bounds__(256) void zero_fill_kernel(float* p, long long n)
     if (i < n) p[i] = 0.0f;
 }
 
+// A call's five inputs into buffers of the caller, in one launch: grid (pieces of 256 threads, 1, the tensors).  A thread moves eight
+// elements of a row, 16 or 32 bytes at a time where both sides are aligned to that.
+struct CopyArgs {
+    struct Side {
+        char* p;
+        long long sb, st;   // bytes
+    } from[5], to[5];
+    int width[5], vector[5];   // elements of a row
+    int batch, L;
+};
+template <typename T>
+__global__ __launch_bounds__(256) void copy_inputs_kernel(const CopyArgs a)
+{
+    constexpr int kPiece = 8;
+    struct __attribute__((aligned(16))) Piece { T v[kPiece]; };
+    const int i = blockIdx.z, pieces = (a.width[i] + kPiece - 1) / kPiece;
+    const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= (long long)a.batch * a.L * pieces) return;
+    const long long row = idx / pieces;
+    const int first = (int)(idx - row * pieces) * kPiece, b = (int)(row / a.L), t = (int)(row - (long long)b * a.L);
+    const T* const from = reinterpret_cast<const T*>(a.from[i].p + b * a.from[i].sb + t * a.from[i].st) + first;
+    T* const to = reinterpret_cast<T*>(a.to[i].p + b * a.to[i].sb + t * a.to[i].st) + first;
+    if (a.vector[i] && first + kPiece <= a.width[i]) {
+        *reinterpret_cast<Piece*>(to) = *reinterpret_cast<const Piece*>(from);
+    } else {
+        for (int e = 0; e < kPiece && first + e < a.width[i]; e++) to[e] = from[e];
+    }
+}
+
 bool split_supported(int d_state, int split)
 {
     switch (d_state * 8 + split) {
@@ -832,6 +861,43 @@ int run_stack(const bimamba_desc* d, int n_layers, int n_steps, const void* tabl
     return now == hipSuccess || now == pending ? BIMAMBA_OK : BIMAMBA_ERR_HIP;
 }
 
+int copy_inputs(const bimamba_desc* d, const bimamba_inputs* from, const bimamba_inputs* to, void* hip_stream)
+{
+    int rc = check_desc(d);
+    if (rc) return rc;
+    const size_t elem = d->io_dtype == BIMAMBA_BF16 ? 2 : 4;
+    if ((rc = check_inputs(from, d, elem))) return rc;
+    if ((rc = check_inputs(to, d, elem))) return rc;
+    if (d->batch == 0 || d->seqlen == 0) return BIMAMBA_OK;
+    const int gn = d->n_groups * d->d_state;
+    const bimamba_tensor src[5] = {from->x, from->z, from->dt, from->B, from->C}, dst[5] = {to->x, to->z, to->dt, to->B, to->C};
+    const int width[5] = {d->d_inner, d->d_inner, d->n_heads, gn, gn};
+    CopyArgs a{};
+    a.batch = d->batch; a.L = d->seqlen;
+    long long most = 0;
+    for (int i = 0; i < 5; i++) {
+        for (int j = 0; j < 5; j++)
+            if (may_overlap(dst[i], width[i], src[j], width[j], elem, d) || (i != j && may_overlap(dst[i], width[i], dst[j], width[j], elem, d)))
+                return BIMAMBA_ERR_ALIAS;
+        auto side = [&](const bimamba_tensor& t) {
+            return CopyArgs::Side{static_cast<char*>(t.ptr), (long long)(t.stride_batch * elem), (long long)(t.stride_token * elem)};
+        };
+        a.from[i] = side(src[i]);
+        a.to[i] = side(dst[i]);
+        a.width[i] = width[i];
+        auto aligned = [&](const CopyArgs::Side& s) { return is_aligned(s.p, 16) && (s.sb | s.st) % 16 == 0; };
+        a.vector[i] = aligned(a.from[i]) && aligned(a.to[i]);
+        most = std::max(most, (long long)d->batch * d->seqlen * ((width[i] + 7) / 8));
+    }
+    const hipError_t pending = hipPeekAtLastError();
+    hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
+    const dim3 grid((unsigned)((most + 255) / 256), 1, 5);
+    if (elem == 2) hipLaunchKernelGGL(copy_inputs_kernel<unsigned short>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(copy_inputs_kernel<float>, grid, dim3(256), 0, st, a);
+    const hipError_t now = hipPeekAtLastError();
+    return now == hipSuccess || now == pending ? BIMAMBA_OK : BIMAMBA_ERR_HIP;
+}
+
 constexpr int kMaxScratchDevices = 64;
 std::atomic<void*> g_scratch_addr[kMaxScratchDevices];   // per device: each GPU holds its own copy of the array
 
@@ -1056,6 +1122,11 @@ int bimamba_block_stack_form(const bimamba_desc* desc)
 {
     RowForm row;
     return check_desc(desc) == BIMAMBA_OK && stack_call(desc, &row);
+}
+
+int bimamba_copy_inputs(const bimamba_desc* desc, const bimamba_inputs* from, const bimamba_inputs* to, void* hip_stream)
+{
+    return copy_inputs(desc, from, to, hip_stream);
 }
 
 int bimamba_time_chunks(const bimamba_desc* desc)

@@ -12,7 +12,7 @@ The n_steps x n_layers calls of a block are captured ONCE into a HIP graph (torc
 the library's launches, which contain no memset nodes) and replayed per block; the caller refreshes the static step
 inputs between replays.  Nothing on this path mixes channels, so with few enough chains the whole block is one launch in which a
 workgroup takes a few channels through every layer of every step (bimamba_block_stack; at batch 1, 24 layers x 8 steps of 32
-tokens 1.44 -> 0.49 ms with the refresh of the step inputs).  Otherwise the state of all layers (n_layers x batch x d_inner x d_state fp32, 100 MB at batch 16)
+tokens 1.44 -> 0.26 ms with the refresh of the step inputs).  Otherwise the state of all layers (n_layers x batch x d_inner x d_state fp32, 100 MB at batch 16)
 lives in HBM/L2 between calls and a call reads it once (4 MB per layer call against 8 MB of activations).
 """
 import torch
@@ -37,12 +37,15 @@ class BlockDecodeLoop:
                      for _ in range(self.n_layers)]
         H, GN = cfg["n_heads"], cfg["n_groups"] * N
         # static inputs of each step (the caller writes the block's current tokens here before a block runs)
-        # A step's tensors lie one behind the other, so that one launch can refresh all of them.
+        # A step's tensors lie one behind the other.
         widths = dict(x=Dn, z=Dn, dt=H, B=GN, C=GN)
         self._step_flat = [torch.zeros(Bt * G * sum(widths.values()), dtype=io, device=device) for _ in range(self.n_steps)]
         self.step_inputs = [{k: t.view(Bt, G, n) for (k, n), t in zip(widths.items(), flat.split([Bt * G * n for n in widths.values()]))}
                             for flat in self._step_flat]
         self._step_views = [dict(views) for views in self.step_inputs]
+        self._row_strides = {k: (G * n, n) for k, n in widths.items()}
+        self._step_places = [bd.make_inputs(views) for views in self.step_inputs]
+        self._device = self._step_flat[0].get_device() if self.n_steps else -1   # (-1: host memory)
         width = Dn * (2 if cfg["combine"] == bd.COMBINE_SEPARATE else 1)
         assert width == Dn, "layers chain out -> x, which needs the additive combine"
         n_act = self.n_steps * self.n_layers if keep_layer_outputs else 2
@@ -65,17 +68,26 @@ class BlockDecodeLoop:
 
     def set_step_inputs(self, step, inputs):
         """inputs: dict of tensors x, z [Bt,G,Dn]; dt [Bt,G,H]; B, C [Bt,G,G*N] or [Bt,G,groups,N] (any device)."""
-        flat, dsts = self._step_flat[step], self.step_inputs[step]
-        own = flat.untyped_storage().data_ptr()
-
-        def plain(k, dst):   # into the buffer's own place (the caller may have put another tensor there), of its kind, and no part of it
-            t = inputs[k]
-            return (dst is self._step_views[step][k] and t.device == flat.device and t.dtype == flat.dtype and t.numel() == dst.numel() and not t.requires_grad and
-                    t.untyped_storage().data_ptr() != own)
-        if all(plain(k, dst) for k, dst in dsts.items()):
-            # one launch instead of five (24 layers x 8 steps of 32 tokens at batch 1: 530 -> 486 us a block, refresh included)
-            torch.cat([inputs[k].reshape(-1) for k in dsts], out=flat)
-            return
+        dsts = self.step_inputs[step]
+        # one launch where the tensors are of the buffer's kind, rows of whole channels and no part of it (the library checks the last two;
+        # 24 layers x 8 steps of 32 tokens at batch 1: 57 us of host time a step with one concatenation, 12 so)
+        if self._device >= 0 and self._device == torch.cuda.current_device():
+            flat, views, words = self._step_flat[step], self._step_views[step], []
+            for k, dst in dsts.items():
+                t = inputs[k]
+                if (dst is not views[k] or type(t) is not torch.Tensor or t.get_device() != self._device or t.dtype is not flat.dtype or
+                        t.requires_grad or t.is_neg()):
+                    break
+                if t.is_contiguous() and t.numel() == dst.numel():
+                    words += (t.data_ptr(), *self._row_strides[k])
+                elif t.dim() == 3 and t.shape == dst.shape and t.stride(2) == 1:
+                    words += (t.data_ptr(), t.stride(0), t.stride(1))
+                else:
+                    break
+            else:
+                if bd.bimamba_copy_inputs(self.desc, bd.input_words(words), self._step_places[step], check=False) == 0:
+                    torch.autograd.graph.increment_version(flat)
+                    return
         for k, dst in dsts.items():
             dst.copy_(inputs[k].reshape(dst.shape))
 
