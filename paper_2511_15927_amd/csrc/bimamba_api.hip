@@ -661,9 +661,24 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
             ba.dt_softplus = d->dt_softplus; ba.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD; ba.conv_bc = d->conv_bc;
             ba.separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
             ba.shared = same_tensor(in_f->x, in_b->x) && same_tensor(in_f->z, in_b->z);
-            if (launch_ssd_block_prep(d->d_state, ba, st) != hipSuccess) return BIMAMBA_ERR_HIP;   // (nothing is committed)
+            ba.tiles = ssd_block_tiles(d->d_state, ba);
+            if (ba.tiles && ba.conv_bc && ba.tail_in && ba.tail_out) {
+                // every workgroup of a batch element reads B's and C's part of the tail: where it is committed in place, after them
+                const size_t bytes = (size_t)d->batch * (d->d_conv - 1) * tail_ch * sizeof(__bf16);
+                const uintptr_t from = reinterpret_cast<uintptr_t>(ba.tail_in), to = reinterpret_cast<uintptr_t>(ba.tail_out);
+                if (from < to + bytes && to < from + bytes) {
+                    // (the launch for it, 2 us, costs four tiles a workgroup what they save: 16 x 32 tokens of 64 heads x 64 23.8 against
+                    // 23.4 us; two tiles or one 11.4 against 13.8, 1 x 32, and 15.8 against 17.0, 32 x 32 of 16 heads)
+                    if (ba.tiles == 4) ba.tiles = 0;
+                    else {
+                        tail_out = ba.tail_out;
+                        ba.tail_out = nullptr;
+                    }
+                }
+            }
+            if (!ba.tiles && launch_ssd_block_prep(d->d_state, ba, st) != hipSuccess) return BIMAMBA_ERR_HIP;   // (nothing is committed)
             if (probe_start) (void)hipEventRecord(probe_start, st);
-            launch_ssd_block(d->d_state, ba, st);
+            if (launch_ssd_block(d->d_state, ba, st) != hipSuccess) return BIMAMBA_ERR_HIP;
             if (probe_stop) (void)hipEventRecord(probe_stop, st);
         } else if (plan.ssd) {
             // 2'. chunked matrix-core path: per-direction operand tiles, then the reverse scan parks its result and the

@@ -75,7 +75,8 @@ hipError_t launch_ssd_wide_n64_p32(const SsdStatePair& sp, int dirs, int batch, 
 void launch_ssd_carry(int d_state, const SsdCarryArgs& ca, hipStream_t st);
 struct SsdBlockArgs;
 hipError_t launch_ssd_block_prep(int d_state, const SsdBlockArgs& a, hipStream_t st);   // (calls of one chunk: ssd_block.h)
-void launch_ssd_block(int d_state, const SsdBlockArgs& a, hipStream_t st);
+hipError_t launch_ssd_block(int d_state, const SsdBlockArgs& a, hipStream_t st);   // (an error: nothing was launched)
+int ssd_block_tiles(int d_state, const SsdBlockArgs& a);   // SsdBlockArgs::tiles of a call that goes in one launch, else 0
 void launch_ssd_state(int d_state, int headdim, const SsdStatePair& sp, int subs, int batch, hipStream_t st);
 
 struct BwdArgs;

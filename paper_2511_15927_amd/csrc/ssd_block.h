@@ -6,9 +6,14 @@
 // 32 tokens), forms the masked, decayed score operands, the conv + SiLU of its channels right in operand layout and the bf16 operand
 // of its entry state, and multiplies.  Four waves share x, z and the output, which cross global memory in whole rows of 64 channels
 // through LDS, and the score operands of a head, made by its waves in shares (with 2-byte accesses and operands of each wave's own
-// a call of 16 x 32 tokens, 64 heads x 64, 128 states took 26.2 us, most of it address and tag cycles; 18.8 now, the bytes alone
-// 9).  The score tiles and operands that all heads of a group share come from ssd_block_prep_kernel, one workgroup per (direction,
-// group, batch element).  (Before: a workgroup an item with producer and consumer waves, one direction after the other, 39.9.)
+// a call of 16 x 32 tokens, 64 heads x 64, 128 states took 26.2 us, most of it address and tag cycles; 18.8 then, the bytes alone
+// 9).  (Before: a workgroup an item with producer and consumer waves, one direction after the other, 39.9.)
+//
+// The operands that all heads of a group share (scores, C, B^T) are 4350 vector instructions a batch element at 32 tokens.  Where
+// the chip holds the call at once, workgroups of sixteen waves make them for themselves (WHOLE), while the state and x that the
+// waves have requested are on their way: a launch of one workgroup per (direction, group, batch element) before the walk
+// (ssd_block_prep_kernel) costs 5 us whatever it does.  16 x 32 tokens of 64 heads x 64 18.7 -> 16.2 us, 1 x 32 10.8 -> 8.0, with
+// the state committed 23.7 -> 20.4 and 13.9 -> 9.2.  Longer blocks and calls of more workgroups take the two launches.
 //
 // The barriers of the walk are those of the sharing: the first before the convs, which read x and the score operands that all four
 // waves have put into LDS; the last before the output's rows are read back from the y columns that the waves have left there.  With
@@ -41,10 +46,12 @@ struct SsdBlockArgs {
     const float* h_in;    // [batch][Dn][N] or null
     float* h_out;         // or null; may alias h_in
     const void* tail_in;  // bf16 [batch][K-1][tail_ch] or null
-    void* tail_out;       // or null; may alias tail_in: x's part is written by whoever reads it there, B's and C's by the preparation
+    void* tail_out;       // or null; may alias tail_in (not in one launch where B and C have a part: every workgroup reads that of its
+                          // group): x's part is written by whoever reads it there, B's and C's by the preparation or a group's first workgroup
     int batch, L, Dn, H, P, HG, G, K, tail_ch;
     int dt_softplus, d_per_head, conv_bc, separate;
     int shared;           // both directions read the same x and the same z
+    int tiles;            // one launch: 64-channel tiles of a workgroup
 };
 
 // Eight channels of one token.
@@ -212,28 +219,197 @@ __device__ __forceinline__ float half_wave_inclusive_sum(float v)
 }
 __device__ __forceinline__ float lane_value(float v, int l) { return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l)); }
 
+// One launch (up to 32 tokens): LDS of ssd_block_kernel<.., WHOLE>.  B and C rows of both directions as bf16 head and rest, over
+// which the outputs lie once the operands have been made; scores; B^T of the forward direction; then the tiles' own parts.
+template <int N, bool COMMIT, bool SHARED>
+struct SsdBlockLds {
+    static constexpr int kRow = N + kPrepPad;
+    static constexpr size_t kSplit = 2 * 4 * 32 * (size_t)kRow * sizeof(__bf16), kY = 2 * 32 * 68 * sizeof(float);
+    static constexpr size_t kScore = 2 * 1024 * sizeof(float), kBt = COMMIT ? 32 * (size_t)N * sizeof(__bf16) : 0;
+    static constexpr size_t kTab = 4 * 6 * 32 * sizeof(float), kX = (SHARED ? 1 : 2) * 38 * 68 * sizeof(unsigned short), kM = 2 * 4 * 64 * 16;
+    static constexpr size_t kTile = kTab + kX + kM;
+    static constexpr size_t front(int tiles) { return kSplit > tiles * kY ? kSplit : tiles * kY; }
+    static constexpr size_t bytes(int tiles) { return front(tiles) + kScore + kBt + tiles * kTile; }
+};
+
+// B and C of one (group, batch element) after conv + SiLU, both directions, from the first 8 N threads of the workgroup: two columns
+// and eight tokens a thread, as in ssd_prep_kernel but in token order.  split[direction][B head, B rest, C head, C rest][token].
+template <int N, bool COMMIT>
+struct SsdBlockRows {
+    using T = unsigned short;
+    int s, part, n, which, row, last, t0;   // direction, run of eight tokens, first column of B or C, its conv channel
+    bf16_pair raw[11];
+    float w4[2][4], bias[2];                // w4[.][3] on the current position
+    bool from_tail, writes_tail;
+
+    __device__ __forceinline__ void request(const SsdBlockArgs& a, int g, int b, int tid, bool tail_writer)
+    {
+        s = __builtin_amdgcn_readfirstlane(tid / (4 * N));
+        part = __builtin_amdgcn_readfirstlane(tid / N % 4);
+        n = 2 * (tid % (N / 2));
+        last = a.L - 1;
+        which = tid % N / (N / 2);
+        if constexpr (N == 128) which = __builtin_amdgcn_readfirstlane(which);
+        const SsdBlockDir& d = a.dir[s];
+        const TensorArg& src = which ? d.C : d.B;
+        const T* const base = (const T*)src.p + (size_t)b * src.sb + g * N + n;
+        row = a.Dn + which * a.G * N + g * N + n;
+        t0 = part * 8 - (s == 0 ? 3 : 0);   // first token of the run and its halo (behind it in scan order)
+#pragma unroll
+        for (int q = 0; q < 11; q++) raw[q] = *(const bf16_pair*)(base + (long long)min(max(t0 + q, 0), last) * src.st);
+        const bool before = s == 0 && part == 0 && a.conv_bc && a.K > 1;
+        from_tail = before && a.tail_in;
+        if (from_tail) {
+#pragma unroll
+            for (int q = 0; q < 3; q++)   // 3 - q tokens before the block, from clamped rows (a tap beyond the conv width has a zero weight)
+                raw[q] = *(const bf16_pair*)((const T*)a.tail_in + ((size_t)b * (a.K - 1) + max(a.K - 1 - (3 - q), 0)) * a.tail_ch + row);
+        }
+        writes_tail = COMMIT && before && tail_writer && a.tail_out;
+        if (a.conv_bc) {
+#pragma unroll
+            for (int k = 0; k < 2; k++) {
+                load_taps(d.conv_w + (size_t)(row + k) * a.K, a.K, w4[k]);
+                bias[k] = d.conv_b ? d.conv_b[row + k] : 0.0f;
+            }
+        }
+    }
+
+    __device__ __forceinline__ float column(int q, int k) const { return __uint_as_float(k ? raw[q] & 0xffff0000u : raw[q] << 16); }
+
+    template <bool CONV, bool REVERSE>
+    __device__ __forceinline__ void rows(__bf16 (*const split)[4][32][N + kPrepPad], bf16x8* const bt)
+    {
+        bf16x8 piece[2];
+#pragma unroll
+        for (int i = 0; i < 8; i++) {
+            const int t = part * 8 + i;
+            __bf16 head[2], rest[2];
+#pragma unroll
+            for (int k = 0; k < 2; k++) {
+                float v = column(REVERSE ? i : i + 3, k);
+                if constexpr (CONV) {
+                    float pre = bias[k];
+#pragma unroll
+                    for (int w = 0; w < 4; w++) pre = fmaf(w4[k][w], column(REVERSE ? i + 3 - w : i + w, k), pre);
+                    v = silu(pre);
+                }
+                v = t <= last ? v : 0.0f;
+                head[k] = (__bf16)v;
+                rest[k] = (__bf16)(v - (float)head[k]);
+                piece[k][i] = head[k];
+            }
+            *reinterpret_cast<bf16x2*>(&split[s][2 * which][t][n]) = bf16x2{head[0], head[1]};
+            *reinterpret_cast<bf16x2*>(&split[s][2 * which + 1][t][n]) = bf16x2{rest[0], rest[1]};
+        }
+        if constexpr (COMMIT && !REVERSE) {   // B^T as the state update takes it: [16 states][lane][8]
+            if (which == 0)
+#pragma unroll
+                for (int k = 0; k < 2; k++) bt[(n / 16) * 64 + part * 16 + n % 16 + k] = piece[k];
+        }
+    }
+
+    __device__ __forceinline__ void finish(const SsdBlockArgs& a, int b, __bf16 (*const split)[4][32][N + kPrepPad], bf16x8* const bt)
+    {
+#pragma unroll
+        for (int q = 0; q < 11; q++) {
+            const bool there = (t0 + q >= 0 || (from_tail && 3 - q <= a.K - 1)) && t0 + q <= last;
+            raw[q] = there ? raw[q] : 0u;
+        }
+        if (writes_tail) {   // the last K - 1 raw tokens of (tail_in || block)
+            const SsdBlockDir& d = a.dir[0];
+            const TensorArg& src = which ? d.C : d.B;
+            const T* const base = (const T*)src.p + (size_t)b * src.sb + (row - a.Dn - which * a.G * N);
+            bf16_pair end_raw[3];
+#pragma unroll
+            for (int q = 0; q < 3; q++) end_raw[q] = *(const bf16_pair*)(base + (long long)max(a.L - 3 + q, 0) * src.st);
+#pragma unroll
+            for (int q = 0; q < 3; q++) {
+                const int n_out = q - 3 + (a.K - 1), pos = a.L - 3 + q;   // row of the tail, token of the block (negative: before it)
+                bf16_pair v = end_raw[q];
+#pragma unroll
+                for (int e = 0; e < 3; e++)
+                    if (pos + 3 == e) v = raw[e];
+                if (n_out >= 0) *(bf16_pair*)((T*)a.tail_out + ((size_t)b * (a.K - 1) + n_out) * a.tail_ch + row) = v;
+            }
+        }
+        if (s == 0) a.conv_bc ? rows<true, false>(split, bt) : rows<false, false>(split, bt);
+        else a.conv_bc ? rows<true, true>(split, bt) : rows<false, true>(split, bt);
+    }
+};
+
+// Scores of both directions, a 16 x 16 tile a wave (eight waves): [direction][16 rows i][lane][8], zero where they are masked.
+template <int N>
+__device__ __forceinline__ void ssd_block_scores_of(int wave, int lane, const __bf16 (*const split)[4][32][N + kPrepPad], float* score)
+{
+    const int s = wave / 4, it = wave % 4 / 2, jt = wave % 2, g4 = lane / 16, c16 = lane % 16;
+    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (s == 0 ? jt <= it : jt >= it) {
+#pragma unroll
+        for (int ks = 0; ks < N / 32; ks++) {
+            const int k0 = ks * 32 + 8 * g4;
+            const bf16x8 ah = *reinterpret_cast<const bf16x8*>(&split[s][0][jt * 16 + c16][k0]), al = *reinterpret_cast<const bf16x8*>(&split[s][1][jt * 16 + c16][k0]);
+            const bf16x8 bh = *reinterpret_cast<const bf16x8*>(&split[s][2][it * 16 + c16][k0]), bl = *reinterpret_cast<const bf16x8*>(&split[s][3][it * 16 + c16][k0]);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, acc, 0, 0, 0);
+        }
+    }
+    const int i = it * 16 + c16, j0 = jt * 16 + 4 * g4;
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+        if (s == 0 ? j0 + r > i : j0 + r < i) acc[r] = 0.0f;
+    *reinterpret_cast<f32x4*>(&score[s * 1024 + ((it * 64 + (2 * jt + g4 / 2) * 16 + c16) * 8 + 4 * (g4 % 2))]) = acc;
+}
+
 // grid (ceil(Dn / 64), 1, batch), block 256: wave w owns channels 16 (4 blockIdx.x + w) .. of one batch element.  COMMIT: h_out is
 // written; SHARED: both directions read the same x and the same z (the registers of the other cases are not held here).
-template <int N, int BLOCKS, bool COMMIT, bool SHARED>
-__global__ __launch_bounds__(256, BLOCKS == 1 ? 4 : COMMIT ? 2 : 3) void ssd_block_kernel(const SsdBlockArgs a)
+// WHOLE: grid (ceil(Dn / 64 / tiles), 1, batch), block 1024, dynamic LDS SsdBlockLds::bytes(tiles): the workgroup makes the operands
+// for itself, and its waves own up to four such tiles of one group.
+template <int N, int BLOCKS, bool COMMIT, bool SHARED, bool WHOLE = false>
+__global__ __launch_bounds__(WHOLE ? 1024 : 256, WHOLE ? 4 : BLOCKS == 1 ? 4 : COMMIT ? 2 : 3) void ssd_block_kernel(const SsdBlockArgs a)
 {
+    static_assert(!WHOLE || BLOCKS == 1, "one launch: up to 32 tokens");
     using T = unsigned short;
     constexpr int kTok = 32 * BLOCKS, kRT = 2 * BLOCKS, kNB = N / 32, kScores = ssd_block_scores<BLOCKS>();
     // wave-private tables by token: forward e_i, f_j Delta_j, exp(l_i), end weight; reverse e_i, f_j Delta_j
-    __shared__ __attribute__((aligned(16))) float s_tab[4][6][kTok];
+    constexpr int kTabBytes = 4 * 6 * kTok * (int)sizeof(float);
     // raw x by row (row r: token r - 3; zeros outside the block and its cached tail), and the outputs before the gate
     constexpr int kRows = kTok + 6, kXPitch = 68, kYPitch = 68;
-    // and the score operands, made once per head: [head of the workgroup][direction, block, 16 rows][lane].  With 64 tokens the
-    // outputs lie over x and the operands.
+    // and the score operands, made once per head: [head of the tile][direction, block, 16 rows][lane].  With 64 tokens the
+    // outputs lie over x and the operands, in one launch over the rows of B and C.
     constexpr int kXBytes = (SHARED ? 1 : 2) * kRows * kXPitch * (int)sizeof(T), kUnits = 2 * kScores * 2;
     constexpr int kMAt = (kXBytes + 15) / 16 * 16, kMBytes = 2 * kUnits * 64 * 16, kYBytes = 2 * kTok * kYPitch * 4;
     constexpr int kYAt = BLOCKS == 1 ? kMAt + kMBytes : 0, kAll = BLOCKS == 1 ? kYAt + kYBytes : kMAt + kMBytes > kYBytes ? kMAt + kMBytes : kYBytes;
-    __shared__ __attribute__((aligned(16))) unsigned char s_all[kAll];
+    const int tid = WHOLE ? threadIdx.x & 255 : threadIdx.x, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int tile = WHOLE ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 8) : 0, tiles = WHOLE ? a.tiles : 1;
+    unsigned char *s_all, *s_yall;
+    float(*tab)[kTok];
+    using Lds = SsdBlockLds<N, COMMIT, SHARED>;
+    __bf16(*split)[4][32][N + kPrepPad] = nullptr;
+    float* s_score = nullptr;
+    bf16x8* s_bt = nullptr;
+    if constexpr (WHOLE) {
+        static_assert(Lds::kY == kYBytes && Lds::kTab == kTabBytes && Lds::kX == kMAt && Lds::kM == kMBytes, "the parts of a tile");
+        extern __shared__ __attribute__((aligned(16))) unsigned char ssd_block_lds[];
+        unsigned char* const after = ssd_block_lds + Lds::front(tiles);
+        unsigned char* const own = after + Lds::kScore + Lds::kBt + tile * Lds::kTile;
+        split = reinterpret_cast<__bf16(*)[4][32][N + kPrepPad]>(ssd_block_lds);
+        s_score = reinterpret_cast<float*>(after);
+        s_bt = reinterpret_cast<bf16x8*>(after + Lds::kScore);
+        tab = reinterpret_cast<float(*)[kTok]>(own) + wave * 6;
+        s_all = own + kTabBytes;
+        s_yall = ssd_block_lds + tile * kYBytes;
+    } else {
+        __shared__ __attribute__((aligned(16))) unsigned char s_tab[kTabBytes];
+        __shared__ __attribute__((aligned(16))) unsigned char s_own[kAll];
+        tab = reinterpret_cast<float(*)[kTok]>(s_tab) + wave * 6;
+        s_all = s_own;
+        s_yall = s_own + kYAt;
+    }
     auto* const s_x = reinterpret_cast<T(*)[kRows][kXPitch]>(s_all);
     auto* const s_m = reinterpret_cast<bf16x8*>(s_all + kMAt);
-    auto* const s_y = reinterpret_cast<float(*)[kTok][kYPitch]>(s_all + kYAt);
-    const int tid = threadIdx.x, lane = tid & 63, c16 = lane & 15, g4 = lane >> 4;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    auto* const s_y = reinterpret_cast<float(*)[kTok][kYPitch]>(s_yall);
     // workgroups dealt to the XCDs batch-major: the heads of a batch element share its operands
     int wg = blockIdx.x, b = blockIdx.z;
     {
@@ -244,13 +420,29 @@ __global__ __launch_bounds__(256, BLOCKS == 1 ? 4 : COMMIT ? 2 : 3) void ssd_blo
             b = (int)(item / gridDim.x);
         }
     }
-    const int wg_ch0 = wg * 64;
+    const int wg_ch0 = (wg * tiles + tile) * 64;
+    // (one launch) the rows of B and C are requested first and worked on when everything else has been requested
+    SsdBlockRows<N, COMMIT> bc;
+    const bool has_rows = threadIdx.x < 8 * N;
+    if constexpr (WHOLE) {
+        const int g = wg * tiles * 64 / (a.HG * a.P);
+        if (has_rows) bc.request(a, g, b, threadIdx.x, wg * tiles * 64 == g * a.HG * a.P);
+        if (tile >= tiles || wg_ch0 >= a.Dn) {   // waves without channels: rows, the scores of the first eight waves, the barriers
+            if (has_rows) bc.finish(a, b, split, s_bt);
+            __syncthreads();
+            const int w = tile * 4 + wave;
+            if (w < 8) ssd_block_scores_of<N>(w, lane, split, s_score);
+            __syncthreads();
+            __syncthreads();
+            __syncthreads();
+            return;
+        }
+    }
     // (waves past the last channel shadow the last tile: they join the barriers and store nothing)
     const bool active = wg_ch0 + wave * 16 < a.Dn;
     const int ch0 = active ? wg_ch0 + wave * 16 : a.Dn - 16;
     const int head = ch0 / a.P, grp = head / a.HG, ch = ch0 + c16, last = a.L - 1;
     const size_t item = (size_t)b * a.G + grp;
-    float(*const tab)[kTok] = s_tab[wave];
 
     // ---- everything the wave reads
     T dtraw[BLOCKS];
@@ -312,21 +504,34 @@ __global__ __launch_bounds__(256, BLOCKS == 1 ? 4 : COMMIT ? 2 : 3) void ssd_blo
     const int head_waves = a.P / 16, hw = wave % head_waves;
     bf16x8* const m_ops = s_m + (wave / head_waves) * (kUnits * 64) + lane;
     f32x4 sc[kUnits / 2][2];
+    auto scores = [&](const float* fwd, const float* rev) {
 #pragma unroll
-    for (int k = 0; k < kUnits / 2; k++) {
-        const int u = hw + k * head_waves, us = u / (2 * kScores), v = u - us * (2 * kScores);
-        if (u < kUnits) {
-            const float* const src = (us == 0 ? a.score[0] : a.score[1]) + item * (kScores * 1024) + (v * 64 + lane) * 8;
-            sc[k][0] = *reinterpret_cast<const f32x4*>(src);
-            sc[k][1] = *reinterpret_cast<const f32x4*>(src + 4);
+        for (int k = 0; k < kUnits / 2; k++) {
+            const int u = hw + k * head_waves, us = u / (2 * kScores), v = u - us * (2 * kScores);
+            if (u < kUnits) {
+                const float* const src = (us == 0 ? fwd : rev) + (v * 64 + lane) * 8;
+                sc[k][0] = *reinterpret_cast<const f32x4*>(src);
+                sc[k][1] = *reinterpret_cast<const f32x4*>(src + 4);
+            }
         }
+    };
+    if constexpr (!WHOLE) scores(a.score[0] + item * (kScores * 1024), a.score[1] + item * (kScores * 1024));
+    auto request_z = [&] {
+#pragma unroll
+        for (int s = 0; s < (kTwoX ? 2 : 1); s++)
+#pragma unroll
+            for (int k = 0; k < BLOCKS; k++)
+                zraw[s][k] = *reinterpret_cast<const Piece*>((const T*)a.dir[s].z.p + (size_t)b * a.dir[s].z.sb +
+                                                             (long long)min((tid >> 3) + 32 * k, last) * a.dir[s].z.st + piece_ch);
+    };
+    constexpr bool kLateZ = WHOLE && COMMIT && !SHARED && N == 128;   // (for which there are no registers beside the rows')
+    if constexpr (!kLateZ) request_z();
+    if constexpr (WHOLE) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (has_rows) bc.finish(a, b, split, s_bt);
+        __builtin_amdgcn_sched_barrier(0);
     }
-#pragma unroll
-    for (int s = 0; s < (kTwoX ? 2 : 1); s++)
-#pragma unroll
-        for (int k = 0; k < BLOCKS; k++)
-            zraw[s][k] = *reinterpret_cast<const Piece*>((const T*)a.dir[s].z.p + (size_t)b * a.dir[s].z.sb +
-                                                         (long long)min((tid >> 3) + 32 * k, last) * a.dir[s].z.st + piece_ch);
+    if constexpr (kLateZ) request_z();
 #pragma unroll
     for (int s = 0; s < (kTwoX ? 2 : 1); s++)
 #pragma unroll
@@ -386,6 +591,45 @@ __global__ __launch_bounds__(256, BLOCKS == 1 ? 4 : COMMIT ? 2 : 3) void ssd_blo
         __builtin_amdgcn_wave_barrier();
     }
 
+    if constexpr (WHOLE) {
+        __syncthreads();                                   // the rows of B and C
+        const int w = tile * 4 + wave;
+        if (w < 8) ssd_block_scores_of<N>(w, lane, split, s_score);
+    }
+    // ---- inter-block term of the forward direction: exp(l_i) C_i H
+    f32x4 y[2][kRT];
+#pragma unroll
+    for (int rt = 0; rt < kRT; rt++) y[0][rt] = y[1][rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    if (a.h_in) {
+        auto c_op = [&](int nb, int rt) -> bf16x8 {
+            if constexpr (WHOLE) {
+                const __bf16* const row = &split[0][2][16 * rt + c16][32 * nb + 4 * g4];
+                const bf16x4 lo = *reinterpret_cast<const bf16x4*>(row), hi = *reinterpret_cast<const bf16x4*>(row + 16);
+                return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            } else {
+                return reinterpret_cast<const bf16x8*>(a.c_op)[item * (kTok * N / 8) + (nb * kRT + rt) * 64 + lane];
+            }
+        };
+#pragma unroll
+        for (int nb = 0; nb < kNB; nb++) {
+            bf16x8 hb;
+#pragma unroll
+            for (int e = 0; e < 8; e++) hb[e] = (__bf16)h[nb][e / 4][e % 4];
+#pragma unroll
+            for (int rt = 0; rt < kRT; rt++)
+                y[0][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c_op(nb, rt), hb, y[0][rt], 0, 0, 0);
+        }
+#pragma unroll
+        for (int rt = 0; rt < kRT; rt++) {
+            const float4 e4 = *reinterpret_cast<const float4*>(&tab[2][16 * rt + 4 * g4]);
+            y[0][rt][0] *= e4.x; y[0][rt][1] *= e4.y; y[0][rt][2] *= e4.z; y[0][rt][3] *= e4.w;
+        }
+    }
+
+    if constexpr (WHOLE) {
+        __syncthreads();                                   // the scores
+        scores(s_score, s_score + 1024);
+    }
     // ---- the head's masked, decayed score operands
 #pragma unroll
     for (int k = 0; k < kUnits / 2; k++) {
@@ -417,28 +661,6 @@ __global__ __launch_bounds__(256, BLOCKS == 1 ? 4 : COMMIT ? 2 : 3) void ssd_blo
                 }
             }
             m_ops[u * 64] = op;
-        }
-    }
-
-    // ---- inter-block term of the forward direction: exp(l_i) C_i H
-    f32x4 y[2][kRT];
-#pragma unroll
-    for (int rt = 0; rt < kRT; rt++) y[0][rt] = y[1][rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    if (a.h_in) {
-        const bf16x8* const c_op = reinterpret_cast<const bf16x8*>(a.c_op) + item * (kTok * N / 8) + lane;
-#pragma unroll
-        for (int nb = 0; nb < kNB; nb++) {
-            bf16x8 hb;
-#pragma unroll
-            for (int e = 0; e < 8; e++) hb[e] = (__bf16)h[nb][e / 4][e % 4];
-#pragma unroll
-            for (int rt = 0; rt < kRT; rt++)
-                y[0][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c_op[(nb * kRT + rt) * 64], hb, y[0][rt], 0, 0, 0);
-        }
-#pragma unroll
-        for (int rt = 0; rt < kRT; rt++) {
-            const float4 e4 = *reinterpret_cast<const float4*>(&tab[2][16 * rt + 4 * g4]);
-            y[0][rt][0] *= e4.x; y[0][rt][1] *= e4.y; y[0][rt][2] *= e4.z; y[0][rt][3] *= e4.w;
         }
     }
 
@@ -495,7 +717,7 @@ __global__ __launch_bounds__(256, BLOCKS == 1 ? 4 : COMMIT ? 2 : 3) void ssd_blo
 
     // ---- the committed state
     if constexpr (COMMIT) {
-        const bf16x8* const b_op = reinterpret_cast<const bf16x8*>(a.b_op) + item * (kTok * N / 8) + lane;
+        const bf16x8* const b_op = (WHOLE ? s_bt : reinterpret_cast<const bf16x8*>(a.b_op) + item * (kTok * N / 8)) + lane;
 #pragma unroll
         for (int nb = 0; nb < kNB; nb++)
 #pragma unroll

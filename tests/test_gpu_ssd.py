@@ -447,3 +447,54 @@ def test_ssd_one_chunk_calls(gpu, oracle, L, N, P, heads, groups, kw):
     assert_close(big[:, :, 1:1 + Dn].float().cpu().numpy(), ref, gpu.TOL["bf16"])
     assert rel_l2(h.cpu().numpy(), h_ref) < 1e-2
     assert torch.all(big[:, :, :1] == 0) and torch.all(big[:, :, 1 + Dn:] == 0)
+
+
+@pytest.mark.parametrize("batch,heads,headdim,N,groups,L,kw", [
+    (2, 5, 32, 64, 1, 1, {}),                        # one tile a workgroup; a width of two and a half tiles; shorter than the conv's reach
+    (3, 3, 64, 128, 1, 32, {}),                      # the longest block
+    (2, 8, 64, 128, 2, 31, dict(d_conv=3)),          # two groups
+    (70, 8, 64, 64, 2, 7, {}),                       # three tiles a workgroup do not make up a group of four: two launches
+    (50, 8, 64, 64, 2, 5, {}),                       # two groups, two tiles a workgroup
+    (130, 3, 64, 64, 1, 2, {}),                      # two tiles a workgroup, the last of which has one
+    (100, 3, 64, 128, 3, 2, {}),                     # groups of one tile, two a workgroup: two launches
+    (129, 6, 32, 64, 1, 33, {}),                     # more than 32 tokens: two launches
+    (100, 5, 64, 128, 1, 9, dict(conv_bc=0)),        # three tiles a workgroup, B and C as they come
+    (85, 10, 64, 64, 1, 3, dict(d_conv=2)),          # four tiles, the last workgroup with two; in place: two launches
+    (65, 16, 64, 64, 1, 4, dict(dt_softplus=0)),     # more than four tiles each: two launches
+])
+def test_ssd_block_forms_agree(gpu, oracle, batch, heads, headdim, N, groups, L, kw):
+    """Block calls of every number of tiles a workgroup and those that take two launches, from a cached state and tail and from
+    nothing, with the state committed, the tail committed to a buffer of its own and in place, and neither."""
+    from paper_2511_15927_amd import binding as bd
+    cfg = synth.m2_cfg(batch, L, heads * headdim, headdim=headdim, d_state=N, n_groups=groups, **kw)
+    pf, pb, inp = case(cfg, 4100 + L + N)
+    g = torch.Generator().manual_seed(L + heads)
+    K, Dn = cfg["d_conv"], cfg["d_inner"]
+    h0 = (0.2 * torch.randn(batch, Dn, N, generator=g)).float()
+    tail0 = synth.round_io(torch.randn(batch, K - 1, synth.conv_channels(cfg), generator=g), "bf16")
+    sel = sorted({0, headdim - 1, Dn // 2, Dn - 1} | set(np.random.default_rng(L).choice(Dn, size=12, replace=False).tolist()))
+    inp_b = synth.make_inputs(cfg, 4200 + L)
+    for combine, other, cached in ((0, None, True), (1, inp_b, True), (0, None, False)):
+        c = dict(cfg, combine=combine)
+        ref, h_ref, t_ref = oracle.bimamba_block_fwd(c, to_np(pf), to_np(pb), to_np(inp), None if other is None else to_np(other),
+                                                     h_in=h0.numpy() if cached else None, tail_in=tail0.numpy() if cached else None, sel=sel)
+        args = dict(h_in=h0 if cached else None, tail_in=tail0 if cached else None)
+        out, h, tail = gpu.gpu_block_fwd(c, pf, pb, inp, other, **args)
+        assert_close(out[..., sel], ref, gpu.TOL["bf16"], (combine, cached))
+        assert rel_l2(h[:, sel, :], h_ref[:, sel, :]) < 1e-2
+        assert np.array_equal(tail, t_ref)
+        plain, _, _ = gpu.gpu_block_fwd(c, pf, pb, inp, other, commit=False, **args)
+        assert_close(plain[..., sel], ref, gpu.TOL["bf16"], (combine, cached))
+        if not cached:
+            continue
+        desc = bd.make_desc(c)
+        dpf, dpb, dinp = bd.to_device(pf), bd.to_device(pb), bd.to_device(inp, c)
+        dinp_b = None if other is None else bd.to_device(other, c)
+        state, kept = h0.cuda(), tail0.cuda().to(torch.bfloat16)
+        res, ws = bd.alloc_out(c), bd.alloc_workspace(desc, 1)
+        bd.bimamba_block_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp),
+                             None if dinp_b is None else bd.make_inputs(dinp_b), state, kept, state, kept, bd.make_tensor(res), ws)
+        torch.cuda.synchronize()
+        assert_close(res.float().cpu().numpy().astype(np.float64).reshape(out.shape)[..., sel], ref, gpu.TOL["bf16"], (combine, "in place"))
+        assert rel_l2(state.cpu().numpy()[:, sel, :], h_ref[:, sel, :]) < 1e-2
+        assert np.array_equal(kept.float().cpu().numpy(), t_ref)
