@@ -53,10 +53,12 @@ bool row_form(int batch, int seqlen, int d_inner, int d_state, bool halves, RowF
     if (chains > most_chains || chains * seqlen > most) return false;
     const long long tiles = (long long)batch * ((d_inner + 3) / 4);
     const int groups = (seqlen + kRowTokens - 1) / kRowTokens;
-    // Time segments of two groups or more while that leaves the chip at most four waves per SIMD (a segment walked twice
-    // costs 1.6 times the work); then as many channel tiles beside each other as keep every CU busy.
+    // Time segments of one and a half groups or more on average while that leaves the chip at most four waves per SIMD (a segment
+    // walked twice costs 1.3 times the work, one of more than kRowHeld groups 1.6); then as many channel tiles beside each other as
+    // keep every CU busy.  (Segments of two groups or more: 200 tokens of 512 channels 12.6 us against 10.5, 40 of 1024 6.6 / 5.6, 192 of
+    // 256 9.4 / 8.2; of one or more: 32 tokens of 4096 7.1 against 6.1, 128 of 512 7.9 / 6.9.)
     int nseg = 1;
-    while (nseg < kRowMaxWaves / 2 && groups >= 4 * nseg && tiles * 4 * nseg <= 16LL * cu_count()) nseg *= 2;
+    while (nseg < kRowMaxWaves / 2 && groups >= 3 * nseg && tiles * 4 * nseg <= 16LL * cu_count()) nseg *= 2;
     f->seg_len = (groups + nseg - 1) / nseg * kRowTokens;
     f->nseg = (seqlen + f->seg_len - 1) / f->seg_len;
     f->tw = 1;
@@ -65,13 +67,16 @@ bool row_form(int batch, int seqlen, int d_inner, int d_state, bool halves, RowF
     return fits(f->tw);
 }
 
+// Segments that a wave's registers hold twice over are walked so: 256 tokens of 512 channels 10.7 us (every segment walked anew, fp32)
+// -> 9.7, 128 of 2048 10.8 -> 9.7, 64 of 512 6.1 -> 5.75.  A kernel of its own: its 102 registers (against 75) leave a SIMD five waves
+// at most, and calls of one segment bring up to eight.
 static size_t lds_bytes(const RowArgs& a) { return (size_t)RowLds(a.L, a.same_bc ? 1 : 2, a.tw, a.nseg, a.seg_len).total * sizeof(float); }
 
-template <typename IO>
+template <typename IO, bool HELD>
 static hipError_t launch_io(const RowArgs& a, int batch, hipStream_t st)
 {
     static LdsLimit limit;
-    auto kernel = row_kernel<IO>;
+    auto kernel = row_kernel<IO, HELD>;
     const size_t lds = lds_bytes(a);
     if (lds > 64 * 1024) {
         const hipError_t err = limit.raise(reinterpret_cast<const void*>(kernel), kRowLdsBytes);
@@ -84,7 +89,8 @@ static hipError_t launch_io(const RowArgs& a, int batch, hipStream_t st)
 
 hipError_t launch_row(int io_bf16, const RowArgs& a, int batch, hipStream_t st)
 {
-    return io_bf16 ? launch_io<IoBF16>(a, batch, st) : launch_io<IoF32>(a, batch, st);
+    if (a.nseg > 1 && a.seg_len <= kRowHeld * kRowTokens) return io_bf16 ? launch_io<IoBF16, true>(a, batch, st) : launch_io<IoF32, true>(a, batch, st);
+    return io_bf16 ? launch_io<IoBF16, false>(a, batch, st) : launch_io<IoF32, false>(a, batch, st);
 }
 
 }  // namespace bm

@@ -117,6 +117,16 @@ __device__ __forceinline__ float row_reduce_scatter(float (&p)[16], int n)
     return b0 ? q1 : q0;
 }
 
+// f(integral_constant<int, i>) for the sixteen tokens of a group.
+template <typename F>
+__device__ __forceinline__ void for_each_row_token(F&& f)
+{
+    f(std::integral_constant<int, 0>{}); f(std::integral_constant<int, 1>{}); f(std::integral_constant<int, 2>{}); f(std::integral_constant<int, 3>{});
+    f(std::integral_constant<int, 4>{}); f(std::integral_constant<int, 5>{}); f(std::integral_constant<int, 6>{}); f(std::integral_constant<int, 7>{});
+    f(std::integral_constant<int, 8>{}); f(std::integral_constant<int, 9>{}); f(std::integral_constant<int, 10>{}); f(std::integral_constant<int, 11>{});
+    f(std::integral_constant<int, 12>{}); f(std::integral_constant<int, 13>{}); f(std::integral_constant<int, 14>{}); f(std::integral_constant<int, 15>{});
+}
+
 // The recurrence of a wave's four chains over `groups` groups of sixteen tokens, from state h: (u, Delta, D xc) of the tokens from
 // `ud` (STRIDE floats a group), B|C rows of the call from `bc` (in token order: a group's are sixteen constant offsets from its
 // lowest-address one).  sink(j, y) takes the output of scan position j + n.
@@ -136,20 +146,58 @@ __device__ __forceinline__ void row_walk(float& h, float a2, const float* ud, co
             h = fmaf(an, h, row_lane<i>(u) * row.x);
             if (OUTPUT) p[i] = row.y * h;
         };
-        token(std::integral_constant<int, 0>{}); token(std::integral_constant<int, 1>{});
-        token(std::integral_constant<int, 2>{}); token(std::integral_constant<int, 3>{});
-        token(std::integral_constant<int, 4>{}); token(std::integral_constant<int, 5>{});
-        token(std::integral_constant<int, 6>{}); token(std::integral_constant<int, 7>{});
-        token(std::integral_constant<int, 8>{}); token(std::integral_constant<int, 9>{});
-        token(std::integral_constant<int, 10>{}); token(std::integral_constant<int, 11>{});
-        token(std::integral_constant<int, 12>{}); token(std::integral_constant<int, 13>{});
-        token(std::integral_constant<int, 14>{}); token(std::integral_constant<int, 15>{});
+        for_each_row_token(token);
         if constexpr (OUTPUT) sink(j, row_reduce_scatter(p, n) + ud[g * STRIDE + 128 + lane]);
     }
 }
 
+// A segment of up to kRowHeld groups walked twice: the first time from a zero state for its end state, keeping every token's decay
+// and input, which the second time, from the state entering it, takes an exponential, two products and half of the reads less.
+constexpr int kRowHeld = 2;
+struct RowSteps {
+    float an[kRowHeld][16], ub[kRowHeld][16];
+};
+template <int DIR>
+__device__ __forceinline__ void row_steps(float& h, RowSteps& st, float a2, const float* ud, const float2* bc, int groups, int j0, int last, int lane)
+{
+#pragma unroll
+    for (int g = 0; g < kRowHeld; g++) {
+        if (g < groups) {
+            const float u = ud[g * 192 + lane], delta = ud[g * 192 + 64 + lane];
+            const int j = j0 + g * kRowTokens;
+            const float2* const rows = bc + (DIR > 0 ? j : last - j - (kRowTokens - 1)) * 16;
+            auto token = [&](auto ic) {
+                constexpr int i = decltype(ic)::value;
+                st.an[g][i] = fast_exp2(row_lane<i>(delta) * a2);
+                st.ub[g][i] = row_lane<i>(u) * rows[(DIR > 0 ? i : kRowTokens - 1 - i) * 16].x;
+                h = fmaf(st.an[g][i], h, st.ub[g][i]);
+            };
+            for_each_row_token(token);
+        }
+    }
+}
+template <int DIR, typename Sink>
+__device__ __forceinline__ void row_walk_held(float& h, const RowSteps& st, const float* ud, const float2* bc, int groups, int j0, int last, int lane,
+                                              int n, Sink&& sink)
+{
+#pragma unroll
+    for (int g = 0; g < kRowHeld; g++) {
+        if (g < groups) {
+            float p[16];
+            const int j = j0 + g * kRowTokens;
+            const float2* const rows = bc + (DIR > 0 ? j : last - j - (kRowTokens - 1)) * 16;
+#pragma unroll
+            for (int i = 0; i < 16; i++) {
+                h = fmaf(st.an[g][i], h, st.ub[g][i]);
+                p[i] = rows[(DIR > 0 ? i : kRowTokens - 1 - i) * 16].y * h;
+            }
+            sink(j, row_reduce_scatter(p, n) + ud[g * 192 + 128 + lane]);
+        }
+    }
+}
+
 // grid (ceil(Dn / (4 tw)), 1, batch), block 128 * nseg * tw, dynamic LDS RowLds::total floats.
-template <typename IO>
+template <typename IO, bool HELD>
 __global__ __launch_bounds__(64 * kRowMaxWaves, 1) void row_kernel(const RowArgs a)
 {
     using T = typename IO::T;
@@ -264,22 +312,17 @@ __global__ __launch_bounds__(64 * kRowMaxWaves, 1) void row_kernel(const RowArgs
 
     // the recurrence over the segment
     const float2* const bc = reinterpret_cast<const float2*>(row_lds + lds.bc) + ((a.same_bc ? 0 : s) * set_rows + kRowTokens) * 16 + n;
+    auto leave = [&](int j, float y) {
+        if (j + n < j1) row_lds[lds.y + (s * a.L + token_of(j + n)) * width + tile * 4 + (lane >> 4)] = y;
+    };
     auto walk = [&](auto with_output, auto direction) {
         constexpr bool kOutput = decltype(with_output)::value;
         constexpr int kDir = decltype(direction)::value;
-        row_walk<kOutput, kDir, 192>(h, a2, ud, bc, groups, j0, last, lane, n, [&](int j, float y) {
-            if (j + n < j1) row_lds[lds.y + (s * a.L + token_of(j + n)) * width + tile * 4 + (lane >> 4)] = y;
-        });
+        row_walk<kOutput, kDir, 192>(h, a2, ud, bc, groups, j0, last, lane, n, leave);
     };
     using Up = std::integral_constant<int, 1>;
     using Down = std::integral_constant<int, -1>;
-    if (a.nseg > 1) {
-        const float h0 = h;
-        h = 0.0f;
-        if (seg + 1 < a.nseg) {                          // (nothing starts from the scan-last segment's end)
-            if (s == 0) walk(std::false_type{}, Up{});
-            else walk(std::false_type{}, Down{});
-        }
+    auto fold = [&](float h0) {                          // the state entering the segment, from the end states before it
         row_lds[lds.sum + wave * 128 + lane] = h;
         row_lds[lds.sum + wave * 128 + 64 + lane] = row_total(dsum);
         __syncthreads();
@@ -288,9 +331,28 @@ __global__ __launch_bounds__(64 * kRowMaxWaves, 1) void row_kernel(const RowArgs
             const float* from = row_lds + lds.sum + (((tile * a.nseg + e) << 1) + s) * 128 + lane;
             h = fmaf(fast_exp2(from[64] * a2), h, from[0]);
         }
+    };
+    const float h0 = h;
+    if constexpr (HELD) {
+        RowSteps st;
+        h = 0.0f;
+        if (s == 0) row_steps<1>(h, st, a2, ud, bc, groups, j0, last, lane);
+        else row_steps<-1>(h, st, a2, ud, bc, groups, j0, last, lane);
+        fold(h0);
+        if (s == 0) row_walk_held<1>(h, st, ud, bc, groups, j0, last, lane, n, leave);
+        else row_walk_held<-1>(h, st, ud, bc, groups, j0, last, lane, n, leave);
+    } else {
+        if (a.nseg > 1) {
+            h = 0.0f;
+            if (seg + 1 < a.nseg) {                      // (nothing starts from the scan-last segment's end)
+                if (s == 0) walk(std::false_type{}, Up{});
+                else walk(std::false_type{}, Down{});
+            }
+            fold(h0);
+        }
+        if (s == 0) walk(std::true_type{}, Up{});
+        else walk(std::true_type{}, Down{});
     }
-    if (s == 0) walk(std::true_type{}, Up{});
-    else walk(std::true_type{}, Down{});
     if (s == 0 && a.h_out && valid && state && j1 == a.L && j1 > j0) a.h_out[h_at] = h;
     __syncthreads();                                     // both directions' outputs
 
