@@ -139,19 +139,34 @@ def make_tensor(t):
     return Tensor(t.data_ptr(), t.stride(0), t.stride(1))
 
 
+_INPUT_WORDS = struct.Struct("=" + "Qqq" * 5)
+assert _INPUT_WORDS.size == C.sizeof(Inputs)
+
+
+def input_words(words):
+    """Inputs from pointer, batch stride and token stride of x, z, dt, B and C, in that order."""
+    return Inputs.from_buffer_copy(_INPUT_WORDS.pack(*words))
+
+
 def make_inputs(i):
     """i: dict of device tensors x, z [Bt,L,Dn]; dt [Bt,L,H]; B, C [Bt,L,G,N] or [Bt,L,G*N]."""
-    def three(t):
-        if t.dim() == 3:
-            return t
-        assert t.dim() == 4 and (t.shape[2] == 1 or t.stride(2) == t.shape[3] * t.stride(3)), "B/C groups must be adjacent"
-        return t.as_strided((t.shape[0], t.shape[1], t.shape[2] * t.shape[3]), (t.stride(0), t.stride(1), t.stride(3)))
-    return Inputs(*[make_tensor(three(i[k])) for k in ("x", "z", "dt", "B", "C")])
+    # (the host's share of a call counts: 256 tokens of 512 channels run in 9.7 us and took 12.6 with a struct a tensor and a stream object)
+    words = []
+    for k in ("x", "z", "dt", "B", "C"):
+        t = i[k]
+        strides = t.stride()
+        if len(strides) == 4:
+            assert t.shape[2] == 1 or strides[2] == t.shape[3] * strides[3], "B/C groups must be adjacent"
+        else:
+            assert len(strides) == 3, "channel dimension must be contiguous"
+        assert strides[-1] == 1 or t.numel() == 0 or t.shape[2:].numel() == 1, "channel dimension must be contiguous"
+        words += (t.data_ptr(), strides[0], strides[1])
+    return input_words(words)
 
 
 def _stream_ptr(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return C.c_void_p(stream.cuda_stream)
 
 
@@ -262,15 +277,6 @@ def bimamba_block_stack(desc, n_layers, n_steps, table, table_dev, stream=None, 
     if check and rc != 0:
         raise BimambaError(rc, "bimamba_block_stack")
     return rc
-
-
-_INPUT_WORDS = struct.Struct("=" + "Qqq" * 5)
-assert _INPUT_WORDS.size == C.sizeof(Inputs)
-
-
-def input_words(words):
-    """Inputs from pointer, batch stride and token stride of x, z, dt, B and C, in that order."""
-    return Inputs.from_buffer_copy(_INPUT_WORDS.pack(*words))
 
 
 def bimamba_copy_inputs(desc, src, dst, stream=None, check=True):

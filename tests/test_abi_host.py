@@ -317,3 +317,19 @@ def test_a_block_can_be_captured_without_a_run_before(monkeypatch):
     assert len(launches) == 3 and launches[1][1] is launches[2][1] is not first[1] and waits == [False] and len(calls) == 4
     assert launches[1][0] == launches[1][1].numpy().tobytes() != first[0]
     assert [t is first[1] for t in loop._captured] == [True]
+
+
+def test_inputs_struct_holds_each_view_as_it_is():
+    """Rows, column slices, separate B/C groups, one channel at any stride and empty tensors; a strided channel is refused."""
+    base = torch.zeros(3, 7, 40, dtype=torch.bfloat16)
+    views = dict(x=base[:, :, 4:20], z=base[:, ::2, 20:36], dt=base[1:, :, 39:], B=base[:, :, :16].unflatten(2, (2, 8)),
+                 C=base.transpose(0, 1)[:, :, 8:12].unsqueeze(2))
+    got = bd.make_inputs(views)
+    for k, t in views.items():
+        v = getattr(got, k)
+        assert (v.ptr, v.stride_batch, v.stride_token) == (t.data_ptr(), t.stride(0), t.stride(1)), k
+    assert bd.make_inputs(dict(views, dt=base[:, :, ::40])).dt.stride_token == 40   # one channel
+    assert bd.make_inputs(dict(views, x=base[:0, :, ::2])).x.stride_batch == base.stride(0)
+    for bad in (dict(x=base[:, :, ::2]), dict(z=base[0]), dict(B=base[:, :, :32].unflatten(2, (2, 16))[..., :8]), dict(C=base.unflatten(2, (8, 5)).transpose(2, 3))):
+        with pytest.raises(AssertionError):
+            bd.make_inputs(dict(views, **bad))
