@@ -6,8 +6,8 @@
 //
 // The four lanes of a chain hold a quarter of its states each and deal its tokens among themselves, four at a time, as in kernels.h:
 // the token's owner evaluates conv, SiLU and softplus, the others read Delta and u out of its registers through quad-permute operands.
-// That is 34 vector slots a lane and token at 16 states, 136 a chain's token; one lane per state takes 180.  24 layers x 8 steps of 32
-// tokens at batch 1, d_inner 4096, 16 states: 450 -> 232 us (by count the vector pipes are 85 to 90 % busy).  The directions meet in
+// That is 33 vector instructions a lane and token at 16 states, 132 a chain's token; one lane per state takes 180.  24 layers x 8 steps
+// of 32 tokens at batch 1, d_inner 4096, 16 states: 450 -> 221 us.  The directions meet in
 // the middle: in the first half of its walk a wave leaves its outputs in LDS, in the second it adds what the other one left, gates,
 // rounds and puts the result where the next layer reads its x.  Two barriers a layer.
 #pragma once
@@ -35,6 +35,11 @@ struct QuadLds {
         total = delta + kQuadChannels * pitch;
     }
 };
+
+__device__ __forceinline__ float quad_other_pair(float v)   // quad_perm [2,3,0,1]
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x4E, 0xF, 0xF, true));
+}
 
 // grid (ceil(Dn / 16), 1, batch), block 128 * side, dynamic LDS side * QuadLds::total floats; side: steps side by side.
 template <typename IO, int N>
@@ -195,7 +200,7 @@ __global__ __launch_bounds__(64 * 2 * kQuadMaxSteps, 1) void stack_quad_kernel(c
                     if (a.dt_softplus) delta = softplus(delta + p.dtb);
                     if (t >= a.L) delta = xc = 0.0f;     // a token that does not exist leaves the state as it is
                     const float u = delta * xc;
-                    float y = 0.0f;
+                    float ys[4];
 #pragma unroll
                     for (int j = 0; j < 4; j++) {
                         const float* const row = bc_l + (t0 + (kUp ? j : 3 - j)) * (2 * N);
@@ -205,17 +210,23 @@ __global__ __launch_bounds__(64 * 2 * kQuadMaxSteps, 1) void stack_quad_kernel(c
                             bv[n] = row[n];
                             cv[n] = row[NS + n];
                         }
-                        const float dj = chain_lane_pick<4>(delta, j), uj = chain_lane_pick<4>(u, j);
+                        float dj = chain_lane_pick<4>(delta, j), uj = chain_lane_pick<4>(u, j);
+                        // (values of their own, not permuted operands, which halve an instruction's rate: four of them cost what two
+                        // moves and eight products do not; 24 layers x 8 steps of 32 tokens 225.5 -> 220.8 us)
+                        if constexpr (NS > 1) asm volatile("" : "+v"(dj), "+v"(uj));
                         float yj = 0.0f;
 #pragma unroll
                         for (int n = 0; n < NS; n++) {
                             h[n] = fmaf(fast_exp2(dj * a2[n]), h[n], uj * bv[n]);
                             yj = n == 0 ? cv[n] * h[n] : fmaf(cv[n], h[n], yj);
                         }
-                        yj = sum_over_chain_lanes<4>(yj);
-                        y = sub == j ? yj : y;
+                        ys[j] = sum_over_chain_lanes<2>(yj);
                     }
-                    y = fmaf(p.dval, xc, y);
+                    // each lane its own token's sum over the quad: pairs, then what the other pair has of the tokens alike (six permuted
+                    // additions and three selects where a sum in every lane takes eight and four: 232.8 -> 225.5 us, the same bits)
+                    const float even = (sub & 1) ? ys[1] : ys[0], odd = (sub & 1) ? ys[3] : ys[2];
+                    const float y01 = even + quad_other_pair(even), y23 = odd + quad_other_pair(odd);
+                    const float y = fmaf(p.dval, xc, (sub & 2) ? y23 : y01);
                     if constexpr (!kFinal) {
                         at[to_y] = y;
                     } else {
