@@ -338,7 +338,9 @@ struct Plan {
     int ssd_chunks;
     int ssd_parts, ssd_part_chunks;  // time parts of the matrix-core path (1: every (batch, head) item is one workgroup)
     int ssd_subs, ssd_part_subs, ssd_sub_chunks;  // sub-parts the state pass walks: in all, per part, chunks of each
-    size_t off_bc[2], off_partial, off_carry, off_sumdt, off_crows[2], off_bt[2], off_score[2], off_pstate[2], off_pdecay[2], total;
+    int ssd_share;  // what bimamba_time_chunks says: the parts that the call's items leave CUs for
+    bool ssd_meet;  // both directions walk at once and meet in the middle (kSsdMeet)
+    size_t off_meet[2], off_bc[2], off_partial, off_carry, off_sumdt, off_crows[2], off_bt[2], off_score[2], off_pstate[2], off_pdecay[2], total;
 };
 
 // The chunked matrix-core path covers bf16 I/O with one decay rate per head, d_state 64 or 128 and heads of 32 or
@@ -349,6 +351,13 @@ bool use_ssd(const bimamba_desc* d)
            d->state_split == 0 && ssd_supported(d->d_state, d->d_inner / d->n_heads) &&
            d->batch <= 32767;   // the preparation kernel's grid holds both directions of every batch element
 }
+
+constexpr size_t kScratch = BIMAMBA_STATIC_SCRATCH_BYTES;
+
+// Prepared tiles of the chunked matrix-core path: C (or B^T) and scores of a direction, all of them.
+size_t ssd_rows_bytes(const bimamba_desc* d, int chunks) { return align_up((size_t)d->batch * chunks * kQ * d->n_groups * d->d_state * sizeof(__bf16), 256); }
+size_t ssd_score_bytes(const bimamba_desc* d, int chunks) { return align_up((size_t)d->batch * chunks * d->n_groups * kScoreOp * sizeof(float), 256); }
+size_t ssd_tile_bytes(const bimamba_desc* d, int chunks) { return 2 * (2 * ssd_rows_bytes(d, chunks) + ssd_score_bytes(d, chunks)); }
 
 Plan plan_of(const bimamba_desc* d, bool inputs_shared, bool coarse)
 {
@@ -380,7 +389,7 @@ Plan plan_of(const bimamba_desc* d, bool inputs_shared, bool coarse)
     // chunks to several workgroups (at least 8 chunks each, at most 16 parts); a first, cheaper pass then finds the
     // state entering each part.  That pass runs light workgroups, four to a CU, so it cuts the parts further into
     // sub-parts (at least 4 chunks each) until both directions together bring about that many.
-    p.ssd_parts = p.ssd_subs = p.ssd_part_subs = 1;
+    p.ssd_parts = p.ssd_subs = p.ssd_part_subs = p.ssd_share = 1;
     p.ssd_part_chunks = p.ssd_sub_chunks = p.ssd_chunks;
     if (p.ssd) {
         // (directions with an output half of their own share a launch: twice the items in flight)
@@ -389,6 +398,22 @@ Plan plan_of(const bimamba_desc* d, bool inputs_shared, bool coarse)
         long long parts = items > 0 ? cus / items : 1;
         if (parts > p.ssd_chunks / 8) parts = p.ssd_chunks / 8;
         if (parts > 16) parts = 16;
+        // Both directions at once, to meet in the middle, where they fit the chip: the walk of two parts an item without the state
+        // pass.  More parts, which the state pass lets start anywhere, are ahead when they save more chunks of the walk than that
+        // pass, which follows the items, costs.  us, parts / meeting, (heads x channels, states) x tokens, batch 1:
+        //   120 x 32, 128   66 18.7/18.0  512 31.8/27.0  1024 56.5/37.1  2048 88.0/55.3  4096 134/91.5  16384 525/387
+        //   64 x 64, 128    66 21.2/22.0  130 24.0/24.7  300 29.7/28.0  1024 66.7/45.8  1536 74.5/56.7  2048 83/67.7  4096 124/113  16384 450/513
+        //   64 x 32, 64     300 22.6/19.0  1024 45.0/30.2  2048 54.0/46.6  4096 78.0/77.7  16384 248/290
+        //   24 x 32, 128    300 24.1/21.0  1024 44.0/32.5  1536 47.7/42.3  2048 50.5/51.4  4096 60.4/84.0;  batch 2, 64 x 64 x 2048 119/77
+        p.ssd_meet = d->combine == BIMAMBA_COMBINE_ADD && p.ssd_chunks >= (d->d_inner / d->n_heads > 32 ? 4 : 2) && items > 0 && 2 * items <= cus &&
+                     p.ssd_chunks * (parts - 2) <= parts * (4 + items / 2);
+        if (p.ssd_meet && parts < 2) {
+            // the states it meets with must not take a block call out of the fixed scratch that holds it without them
+            // (by the size for separate activations)
+            const size_t states = 2 * align_up((size_t)d->batch * d->d_inner * d->d_state * sizeof(float), 256);
+            const size_t without = off + (p.two_bc ? 0 : bc_bytes) + ssd_tile_bytes(d, p.ssd_chunks);
+            if (without <= kScratch && without + states > kScratch) p.ssd_meet = false;
+        }
         if (parts >= 2) {
             const int part_chunks = (int)((p.ssd_chunks + parts - 1) / parts);
             const long long items_both = 2LL * d->n_heads * d->batch;
@@ -402,15 +427,24 @@ Plan plan_of(const bimamba_desc* d, bool inputs_shared, bool coarse)
             p.ssd_parts = (p.ssd_chunks + p.ssd_part_chunks - 1) / p.ssd_part_chunks;
             p.ssd_subs = (p.ssd_chunks + p.ssd_sub_chunks - 1) / p.ssd_sub_chunks;
         }
+        p.ssd_share = p.ssd_parts;
+        if (p.ssd_meet) {
+            p.ssd_parts = p.ssd_subs = p.ssd_part_subs = 1;
+            p.ssd_part_chunks = p.ssd_sub_chunks = p.ssd_chunks;
+        }
     }
     if (p.ssd) {
-        const size_t rows = align_up((size_t)d->batch * p.ssd_chunks * kQ * d->n_groups * d->d_state * sizeof(__bf16), 256);
-        const size_t score = align_up((size_t)d->batch * p.ssd_chunks * d->n_groups * kScoreOp * sizeof(float), 256);
+        const size_t rows = ssd_rows_bytes(d, p.ssd_chunks), score = ssd_score_bytes(d, p.ssd_chunks);
         for (int s = 0; s < 2; s++) {
             p.off_crows[s] = off; off += rows;
             p.off_bt[s] = off; off += rows;
             p.off_score[s] = off; off += score;
         }
+        if (p.ssd_meet)
+            for (int s = 0; s < 2; s++) {   // the states the directions meet with
+                p.off_meet[s] = off;
+                off += align_up((size_t)d->batch * d->d_inner * d->d_state * sizeof(float), 256);
+            }
         for (int s = 0; s < 2; s++) {
             p.off_pstate[s] = p.off_pdecay[s] = off;
             if (p.ssd_parts > 1) {
@@ -431,7 +465,6 @@ Plan plan_of(const bimamba_desc* d, bool inputs_shared, bool coarse)
 // (Decided on the size for separate activations: a call must not plan more than bimamba_workspace_bytes said.)
 Plan make_plan(const bimamba_desc* d, bool inputs_shared, bool block_variant, size_t bytes)
 {
-    constexpr size_t kScratch = BIMAMBA_STATIC_SCRATCH_BYTES;
     const Plan fine = plan_of(d, inputs_shared, false);
     if (!block_variant && bytes >= fine.total) return fine;
     const bool fits_coarse_only = plan_of(d, false, false).total > kScratch && plan_of(d, false, true).total <= kScratch;
@@ -685,6 +718,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
             // forward scan adds, gates and stores (or each writes its own half)
             const bool separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
             const bool raw = !separate && same_tensor(in_f->z, in_b->z);
+            const bool meet = plan.ssd_meet && !far;
             SsdPrepPair pp{};
             for (int s = 0; s < 2; s++) {
                 SsdPrepArgs& pa = pp.dir[s];
@@ -698,6 +732,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                 pa.b_t = reinterpret_cast<__bf16*>(ws + plan.off_bt[s]);
                 pa.score_op = reinterpret_cast<float*>(ws + plan.off_score[s]);
                 pa.L = d->seqlen; pa.G = d->n_groups; pa.dir = s == 0 ? 1 : -1;
+                pa.lead = meet && s == 1 ? plan.ssd_chunks * kQ - d->seqlen : 0;
             }
             if (launch_ssd_prep(d->d_state, pp, plan.ssd_chunks, d->batch, st) != hipSuccess) return BIMAMBA_ERR_HIP;
             if (probe_start) (void)hipEventRecord(probe_start, st);
@@ -728,9 +763,30 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                 sa.out_ch_off = separate ? s * d->d_inner : 0;
                 sa.dt_softplus = d->dt_softplus; sa.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD;
                 sa.far = far;
+                sa.meet = meet; sa.lead = pp.dir[s].lead;
                 return sa;
             };
-            if (plan.ssd_parts > 1) {
+            if (meet) {   // both directions at once: the halves they scan first, then, from the states left, the others' halves
+                const int half = (plan.ssd_chunks + 1) / 2;   // the forward direction's chunks of the first launch
+                SsdStatePair sp;
+                for (int s = 0; s < 2; s++) {
+                    sp.dir[s] = scan_args(s);
+                    sp.dir[s].mode = raw ? kSsdPartialRaw : kSsdPartial;
+                    sp.dir[s].first_chunk = 0;
+                    sp.dir[s].part_chunks = s == 0 ? half : plan.ssd_chunks - half;
+                    sp.dir[s].h_out = reinterpret_cast<float*>(ws + plan.off_meet[s]);
+                }
+                if (launch_ssd_scan(d->d_state, d->d_inner / d->n_heads, sp, 2, d->batch, st) != hipSuccess) return BIMAMBA_ERR_HIP;
+                for (int s = 0; s < 2; s++) {
+                    sp.dir[s] = scan_args(s);
+                    sp.dir[s].mode = raw ? kSsdFinalAddRaw : kSsdFinalAdd;
+                    sp.dir[s].first_chunk = s == 0 ? half : plan.ssd_chunks - half;
+                    sp.dir[s].part_chunks = plan.ssd_chunks - sp.dir[s].first_chunk;
+                    sp.dir[s].h_in = reinterpret_cast<const float*>(ws + plan.off_meet[s]);
+                }
+                if (launch_ssd_scan(d->d_state, d->d_inner / d->n_heads, sp, 2, d->batch, st) != hipSuccess) return BIMAMBA_ERR_HIP;
+            }
+            if (!meet && plan.ssd_parts > 1) {
                 // time parts: every sub-part's end state from a zero start, then the states entering them
                 SsdStatePair sp;
                 SsdCarryArgs ca{};
@@ -745,7 +801,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                 ca.parts = plan.ssd_subs;
                 launch_ssd_carry(d->d_state, ca, st);
             }
-            {
+            if (!meet) {
                 const int head_width = d->d_inner / d->n_heads;
                 SsdStatePair sp;
                 sp.dir[1] = scan_args(1);
@@ -1149,7 +1205,7 @@ int bimamba_time_chunks(const bimamba_desc* desc)
     if (check_desc(desc)) return 0;
     const Plan p = make_plan(desc, true, false, SIZE_MAX);
     RowForm row;
-    return p.ssd ? p.ssd_parts : row_call(desc, p, &row) ? 1 : p.nseg;
+    return p.ssd ? p.ssd_share : row_call(desc, p, &row) ? 1 : p.nseg;
 }
 
 void bimamba_profile_next_call(void* ev_start, void* ev_stop)

@@ -47,6 +47,7 @@ struct SsdPrepArgs {
     float* score_op;   // [batch][nchunk][G][kScoreOp]: B_j . C_i for j, i in the chunk, MFMA operand order (see the kernel)
     int L, G, K, Dn, tail_ch, conv_bc;
     int dir;           // +1: scan position tau is token tau; -1: token L-1-tau
+    int lead;          // positions before the sequence that the first chunk starts with (kSsdMeet)
 };
 
 struct SsdPrepPair {
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
         const T* const base = (const T*)src.p + (size_t)b * src.sb + g * N;
         const int last = a.L - 1;
         const int row = a.Dn + which * a.G * N + g * N + n;   // the first column's conv channel
-        const int tau0 = c * kQ + seg * kLen - 3;
+        const int tau0 = c * kQ + seg * kLen - 3 - a.lead;
         bf16_pair raw[kLen + 3];
         {   // (positions outside the sequence repeat its nearest row)
             const int first = min(max(tau0, 0), last);
@@ -127,7 +128,7 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
         // positions before the sequence (or the cached tail) and past its end are zeros
         const int front = from_tail ? 4 - a.K : max(-tau0, 0), end = last - tau0;
 #pragma unroll
-        for (int q = 0; q < kLen + 3; q++) raw[q] = ((q >= 3 || q >= front) & (q <= end)) ? raw[q] : 0u;
+        for (int q = 0; q < kLen + 3; q++) raw[q] = ((q >= front) & (q <= end)) ? raw[q] : 0u;
         auto column = [&](int q, int k) -> float { return __uint_as_float(k ? raw[q] & 0xffff0000u : raw[q] << 16); };
         bf16x8 piece[2];
         auto rows = [&](auto conv) {
@@ -145,7 +146,7 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
                         pre = fmaf(w4[k][3], column(i + 3, k), pre);
                         v = silu(pre);
                     }
-                    v = i + 3 <= end ? v : 0.0f;
+                    v = ((i + 3 >= front) & (i + 3 <= end)) ? v : 0.0f;
                     head[k] = (__bf16)v;
                     rest[k] = (__bf16)(v - (float)head[k]);
                     if constexpr (kFromRegisters) piece[k][i % 8] = head[k];
@@ -246,7 +247,7 @@ __global__ __launch_bounds__(THREADS) void ssd_prep_kernel(const SsdPrepPair bot
 // Output modes of the chunk walk (ssd_wide.h).
 enum { kSsdFinalOnly = 0, kSsdPartial = 1, kSsdPartialRaw = 2, kSsdFinalAdd = 3, kSsdFinalAddRaw = 4 };
 // Its forms.
-constexpr int kSsdWhole = 0, kSsdParts = 1, kSsdFarParts = 2;
+constexpr int kSsdWhole = 0, kSsdParts = 1, kSsdFarParts = 2, kSsdMeet = 3;
 
 struct SsdArgs {
     TensorArg x, z, dt;
@@ -271,6 +272,9 @@ struct SsdArgs {
     int parts, part_chunks, part_subs, sub_chunks;
     float* part_state;    // [subs][batch][Dn][N]
     float* part_decay;    // [subs][batch][H]
+    // Directions that meet in the middle (kSsdMeet): the launch walks part_chunks chunks from first_chunk on, from h_in to h_out.
+    int meet, first_chunk;
+    int lead;             // positions before the sequence that the first chunk starts with: both directions' chunks hold the same tokens
 };
 
 struct SsdCarryArgs {

@@ -55,16 +55,23 @@ struct SsdWide {
 // the other stays fp32.  kSsdFarParts: the same, one part or more, every row addressed by itself, for calls whose z or out rows lie
 // too far apart for 32-bit offsets within a chunk.  (A form of its own: asked per chunk in the other, whether the offsets serve
 // cost calls whose rows are near 1.6 %, 64 heads x 32, N 64, 1 x 16384 tokens.)
+// kSsdMeet: calls that leave at least half of the CUs empty and have directions to add, in two launches of both directions.  In the
+// first each walks the half of the chunks that it scans first, parks its results and leaves its state, in the second each takes the
+// other half from there and adds what the other direction parked there.  The reverse direction's chunks start before the sequence
+// where that is ragged, so that both directions' chunks hold the same tokens (positions that do not exist have Delta = 0 and are not
+// stored).
 // Against one walk of eight waves a part, calls of 64 heads x 64, N 128: 1 x 32768 tokens 953 -> 890 us, 1 x 8192 279 -> 255, 2 x 8192
 // 476 -> 440, 1 x 2048 103 -> 90; 64 heads x 32, N 64, 1 x 16384 340 -> 258.
 template <int N, int P, int HEADS, int MODE, int FORM>
-__global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_kernel(const std::conditional_t<(MODE > 0), SsdArgs, SsdStatePair> launch)
+__global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_kernel(const std::conditional_t<(MODE > 0 && FORM != 3), SsdArgs, SsdStatePair> launch)
 {
-    constexpr bool kParts = FORM != kSsdWhole;
+    constexpr bool kParts = FORM != kSsdWhole, kMeet = FORM == kSsdMeet;
+    static_assert(kSsdMeet == 3);
     // (the parameter's type names no enumerator: those of an unnamed enumeration are spelt differently in a kernel's host and device name)
     static_assert(kSsdFinalOnly == 0);
     const SsdArgs& a = [&]() -> const SsdArgs& {
-        if constexpr (MODE != kSsdFinalOnly) return launch;
+        if constexpr (kMeet) return launch.dir[blockIdx.y];
+        else if constexpr (MODE != kSsdFinalOnly) return launch;
         else return launch.dir[kParts ? (int)blockIdx.y >= launch.dir[0].parts : blockIdx.y];
     }();
     using W = SsdWide<N, P, HEADS>;
@@ -98,10 +105,12 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
     const int grp = head / a.HG;
     const int ch0 = head * P;
     // this workgroup's chunks [c0, c0 + nchunk), below by their place in it; period p: chunk p / HEADS, head p % HEADS
-    const int part = !kParts ? 0 : (int)blockIdx.y - ((int)blockIdx.y >= a.parts ? a.parts : 0), c0 = !kParts ? 0 : part * a.part_chunks;
-    const int nchunk = !kParts ? a.nchunk : min(a.nchunk - c0, a.part_chunks), periods = nchunk * HEADS, q0 = c0 * kQ;
-    const float* const state_in = !kParts ? a.h_in : a.part_state + (size_t)part * a.part_subs * gridDim.z * a.Dn * N;
-    float* const state_out = !kParts || part == a.parts - 1 ? a.h_out : nullptr;
+    const int part = !kParts || kMeet ? 0 : (int)blockIdx.y - ((int)blockIdx.y >= a.parts ? a.parts : 0);
+    const int c0 = kMeet ? a.first_chunk : !kParts ? 0 : part * a.part_chunks;
+    const int nchunk = kMeet ? a.part_chunks : !kParts ? a.nchunk : min(a.nchunk - c0, a.part_chunks), periods = nchunk * HEADS;
+    const int q0 = c0 * kQ - (kMeet ? a.lead : 0);
+    const float* const state_in = !kParts || kMeet ? a.h_in : a.part_state + (size_t)part * a.part_subs * gridDim.z * a.Dn * N;
+    float* const state_out = !kParts || kMeet || part == a.parts - 1 ? a.h_out : nullptr;
     const int last = a.L - 1;
     auto token_of = [&](int tau) { return a.dir > 0 ? tau : last - tau; };
     // the prepared tiles of (chunk c, this group)
@@ -126,7 +135,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
             }
         const T* xb = (const T*)a.x.p + (size_t)b * a.x.sb + ch0 + 2 * cp;
         const long long xstep = a.dir * a.x.st;
-        const auto edge_chunk = [&](int c) { return c0 + c == 0 || q0 + c * kQ + kQ - 1 > last; };
+        const auto edge_chunk = [&](int c) { return (kMeet ? q0 + c * kQ < 3 : c0 + c == 0) || q0 + c * kQ + kQ - 1 > last; };
         unsigned xraw[2][kPos + 3];   // of the periods of either parity, requested two periods ahead
         auto issue_x = [&](int c, int hd, unsigned (&xraw)[kPos + 3]) {
             const int tau0 = q0 + c * kQ + kPos * tg - 3;
@@ -279,7 +288,10 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
         const float dtb = (a.dt_softplus && a.dt_bias) ? a.dt_bias[scan_head] : 0.0f;
         const T* dtp = (const T*)a.dt.p + (size_t)b * a.dt.sb + scan_head;
         T dtraw;
-        auto issue_dt = [&](int p) { dtraw = dtp[(long long)token_of(min(q0 + p / HEADS * kQ + lane, last)) * a.dt.st]; };
+        auto issue_dt = [&](int p) {
+            const int tau = min(q0 + p / HEADS * kQ + lane, last);
+            dtraw = dtp[(long long)token_of(kMeet ? max(tau, 0) : tau) * a.dt.st];
+        };
         // A period's scan: Delta; the inclusive cumulative log2-decay; what the waves read of them.  With two heads a wave does these
         // in successive periods (whole, it lengthens one wave's stream in every period: 0.8 % at 8 x 8192 tokens); with one head's
         // shorter periods the branches cost more than that (2 % at 1 x 1024).
@@ -288,7 +300,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
             dl = IoBF16::cvt(dtraw);
             issue_dt(p + 4);   // (clamped to the sequence)
             if (a.dt_softplus) dl = softplus(dl + dtb);
-            if (q0 + p / HEADS * kQ + lane > last) dl = 0.0f;
+            if (q0 + p / HEADS * kQ + lane > last || (kMeet && q0 + p / HEADS * kQ + lane < 0)) dl = 0.0f;
         };
         auto scan_decay = [&]() { l2 = wave_inclusive_sum(dl * a2); };
         auto scan_tables = [&](int p) {
@@ -506,8 +518,11 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
     Park* const phead = (Park*)a.partial + (size_t)b * a.L * a.Dn + my_ch0;
     T* const ohead = (T*)a.out + (size_t)b * a.out_sb + a.out_ch_off + my_ch0;
     auto chunk_low_token = [&](int c) { return (long long)(fwd ? q0 + c * kQ : last - (q0 + c * kQ + kQ - 1)); };
-    auto inside = [&](int c) { return FORM != kSsdFarParts && q0 + c * kQ + kQ - 1 <= last; };
-    auto token_at = [&](int c, int k) { return (long long)token_of(min(q0 + c * kQ + i0 + 16 * (k / 4) + k % 4, last)); };
+    auto inside = [&](int c) { return FORM != kSsdFarParts && q0 + c * kQ + kQ - 1 <= last && (!kMeet || q0 + c * kQ >= 0); };
+    auto token_at = [&](int c, int k) {
+        const int tau = min(q0 + c * kQ + i0 + 16 * (k / 4) + k % 4, last);
+        return (long long)token_of(kMeet ? max(tau, 0) : tau);
+    };
 
     typedef unsigned __attribute__((ext_vector_type(2))) uint2v;
     using ParkPair = std::conditional_t<kParts, uint2v, unsigned>;
@@ -650,7 +665,7 @@ __global__ __launch_bounds__((SsdWide<N, P, HEADS>::kThreads)) void ssd_wide_ker
 #pragma unroll
             for (int k = 0; k < 8; k++) {
                 const int tau = q0 + c * kQ + i0 + 16 * (k / 4) + k % 4;
-                if (tau <= last) {
+                if (tau <= last && (!kMeet || tau >= 0)) {
                     const long long t = token_of(tau);
                     if constexpr (parks) *reinterpret_cast<Result*>(phead + t * a.Dn + po) = res[k];
                     else {

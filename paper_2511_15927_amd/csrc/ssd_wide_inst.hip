@@ -14,9 +14,9 @@ static hipError_t variant(const SsdStatePair& sp, int batch, hipStream_t st)
         const hipError_t err = limit.raise(reinterpret_cast<const void*>(kernel), W::bytes());
         if (err != hipSuccess) return err;
     }
-    const unsigned parts = FORM != kSsdWhole ? (unsigned)sp.dir[0].parts : 1u;
+    const unsigned parts = FORM == kSsdMeet ? 2u : FORM != kSsdWhole ? (unsigned)sp.dir[0].parts : 1u;
     const dim3 grid((unsigned)(sp.dir[0].H / HEADS), MODE == kSsdFinalOnly ? 2u * parts : parts, (unsigned)batch), block(W::kThreads);
-    if constexpr (MODE == kSsdFinalOnly) hipLaunchKernelGGL(kernel, grid, block, W::bytes(), st, sp);
+    if constexpr (MODE == kSsdFinalOnly || FORM == kSsdMeet) hipLaunchKernelGGL(kernel, grid, block, W::bytes(), st, sp);
     else hipLaunchKernelGGL(kernel, grid, block, W::bytes(), st, sp.dir[0]);
     return hipSuccess;
 }
@@ -24,7 +24,8 @@ static hipError_t variant(const SsdStatePair& sp, int batch, hipStream_t st)
 template <int HEADS, int FORM>
 static hipError_t launch(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
-    if (dirs == 2) return variant<HEADS, kSsdFinalOnly, FORM>(sp, batch, st);
+    if constexpr (FORM != kSsdMeet)
+        if (dirs == 2) return variant<HEADS, kSsdFinalOnly, FORM>(sp, batch, st);
     switch (sp.dir[0].mode) {
         case kSsdPartial: return variant<HEADS, kSsdPartial, FORM>(sp, batch, st);
         case kSsdPartialRaw: return variant<HEADS, kSsdPartialRaw, FORM>(sp, batch, st);
@@ -40,6 +41,7 @@ static hipError_t launch(const SsdStatePair& sp, int dirs, int batch, hipStream_
 hipError_t BM_NAME(BM_N, BM_P)(const SsdStatePair& sp, int dirs, int batch, hipStream_t st)
 {
     const SsdArgs& sa = sp.dir[0];
+    if (sa.meet) return launch<1, kSsdMeet>(sp, dirs, batch, st);
     if (sa.far) return launch<1, kSsdFarParts>(sp, dirs, batch, st);
     if (sa.parts > 1) return launch<1, kSsdParts>(sp, dirs, batch, st);
     if (sa.HG % 2 == 0 && (long long)sa.H * batch * dirs > cu_count()) return launch<2, kSsdWhole>(sp, dirs, batch, st);

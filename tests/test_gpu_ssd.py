@@ -498,3 +498,44 @@ def test_ssd_block_forms_agree(gpu, oracle, batch, heads, headdim, N, groups, L,
         assert_close(res.float().cpu().numpy().astype(np.float64).reshape(out.shape)[..., sel], ref, gpu.TOL["bf16"], (combine, "in place"))
         assert rel_l2(state.cpu().numpy()[:, sel, :], h_ref[:, sel, :]) < 1e-2
         assert np.array_equal(kept.float().cpu().numpy(), t_ref)
+
+
+@pytest.mark.parametrize("L,batch,heads,headdim,N,kw", [
+    (65, 2, 4, 32, 64, {}),                     # two chunks; the reverse direction's first one holds one token
+    (128, 1, 8, 32, 128, {}),                   # two whole chunks
+    (66, 1, 3, 32, 64, dict(conv_bc=0)),        # its second chunk's conv window begins before the sequence
+    (129, 3, 5, 32, 64, dict(d_conv=3)),        # three chunks: halves of two and one
+    (193, 2, 2, 64, 128, {}),                   # four, heads of 64 channels
+    (319, 1, 6, 64, 64, dict(n_groups=2)),      # five
+    (1111, 1, 3, 64, 128, dict(dt_softplus=0)), # eighteen
+    (190, 1, 120, 32, 128, {}),                 # the most heads of 32 channels that the 1.3B layer has
+    (250, 2, 64, 64, 64, {}),                   # as many items as there may be
+    (129, 1, 4, 64, 64, {}),                    # three chunks, heads of 64 channels: one direction after the other
+    (1601, 1, 4, 32, 64, {}),                   # so few items that three time parts are taken instead
+])
+def test_ssd_directions_meet_in_the_middle(gpu, oracle, L, batch, heads, headdim, N, kw):
+    """Directions that are added, few (batch, head) items: gated once and gated each, from nothing and, as a block call, from a cached
+    state and tail, with both committed in place."""
+    from paper_2511_15927_amd import binding as bd
+    cfg = synth.m2_cfg(batch, L, heads * headdim, headdim=headdim, d_state=N, **kw)
+    pf, pb, inp = case(cfg, 5100 + L + N)
+    Dn, K = cfg["d_inner"], cfg["d_conv"]
+    g = torch.Generator().manual_seed(L)
+    h0 = (0.2 * torch.randn(batch, Dn, N, generator=g)).float()
+    tail0 = synth.round_io(torch.randn(batch, K - 1, synth.conv_channels(cfg), generator=g), "bf16")
+    sel = sorted({0, headdim - 1, Dn // 2, Dn - 1} | set(np.random.default_rng(L).choice(Dn, size=24, replace=False).tolist()))
+    for other in (None, dict(inp, z=synth.make_inputs(cfg, 5300 + L)["z"])):
+        both = (to_np(pf), to_np(pb), to_np(inp), None if other is None else to_np(other))
+        assert_close(gpu.gpu_fwd(cfg, pf, pb, inp, other)[..., sel], oracle.bimamba_fwd(cfg, *both, sel=sel), gpu.TOL["bf16"], other is None)
+        ref, h_ref, t_ref = oracle.bimamba_block_fwd(cfg, *both, h_in=h0.numpy(), tail_in=tail0.numpy(), sel=sel)
+        desc = bd.make_desc(cfg)
+        dpf, dpb, dinp = bd.to_device(pf), bd.to_device(pb), bd.to_device(inp, cfg)
+        dother = None if other is None else bd.to_device(other, cfg)
+        state, kept, res, ws = h0.cuda(), tail0.cuda().to(torch.bfloat16), bd.alloc_out(cfg), bd.alloc_workspace(desc, 1)
+        ws.fill_(255)   # (NaN, if anything is read that the call has not written)
+        bd.bimamba_block_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp),
+                             None if dother is None else bd.make_inputs(dother), state, kept, state, kept, bd.make_tensor(res), ws)
+        torch.cuda.synchronize()
+        assert_close(res.float().cpu().numpy().astype(np.float64)[..., sel], ref, gpu.TOL["bf16"], (other is None, "block"))
+        assert rel_l2(state.cpu().numpy()[:, sel, :], h_ref[:, sel, :]) < 1e-2
+        assert np.array_equal(kept.float().cpu().numpy(), t_ref)
