@@ -338,9 +338,8 @@ struct Plan {
     int ssd_chunks;
     int ssd_parts, ssd_part_chunks;  // time parts of the matrix-core path (1: every (batch, head) item is one workgroup)
     int ssd_subs, ssd_part_subs, ssd_sub_chunks;  // sub-parts the state pass walks: in all, per part, chunks of each
-    int ssd_share;  // what bimamba_time_chunks says: the parts that the call's items leave CUs for
-    bool ssd_meet;  // both directions walk at once and meet in the middle (kSsdMeet)
-    size_t off_meet[2], off_bc[2], off_partial, off_carry, off_sumdt, off_crows[2], off_bt[2], off_score[2], off_pstate[2], off_pdecay[2], total;
+    bool ssd_meet;  // both directions walk at once and meet in the middle (kSsdMeet), not in time parts, unless rows are far apart
+    size_t off_bc[2], off_partial, off_carry, off_sumdt, off_crows[2], off_bt[2], off_score[2], off_pstate[2], off_pdecay[2], total;
 };
 
 // The chunked matrix-core path covers bf16 I/O with one decay rate per head, d_state 64 or 128 and heads of 32 or
@@ -389,7 +388,7 @@ Plan plan_of(const bimamba_desc* d, bool inputs_shared, bool coarse)
     // chunks to several workgroups (at least 8 chunks each, at most 16 parts); a first, cheaper pass then finds the
     // state entering each part.  That pass runs light workgroups, four to a CU, so it cuts the parts further into
     // sub-parts (at least 4 chunks each) until both directions together bring about that many.
-    p.ssd_parts = p.ssd_subs = p.ssd_part_subs = p.ssd_share = 1;
+    p.ssd_parts = p.ssd_subs = p.ssd_part_subs = 1;
     p.ssd_part_chunks = p.ssd_sub_chunks = p.ssd_chunks;
     if (p.ssd) {
         // (directions with an output half of their own share a launch: twice the items in flight)
@@ -427,11 +426,6 @@ Plan plan_of(const bimamba_desc* d, bool inputs_shared, bool coarse)
             p.ssd_parts = (p.ssd_chunks + p.ssd_part_chunks - 1) / p.ssd_part_chunks;
             p.ssd_subs = (p.ssd_chunks + p.ssd_sub_chunks - 1) / p.ssd_sub_chunks;
         }
-        p.ssd_share = p.ssd_parts;
-        if (p.ssd_meet) {
-            p.ssd_parts = p.ssd_subs = p.ssd_part_subs = 1;
-            p.ssd_part_chunks = p.ssd_sub_chunks = p.ssd_chunks;
-        }
     }
     if (p.ssd) {
         const size_t rows = ssd_rows_bytes(d, p.ssd_chunks), score = ssd_score_bytes(d, p.ssd_chunks);
@@ -440,13 +434,10 @@ Plan plan_of(const bimamba_desc* d, bool inputs_shared, bool coarse)
             p.off_bt[s] = off; off += rows;
             p.off_score[s] = off; off += score;
         }
-        if (p.ssd_meet)
-            for (int s = 0; s < 2; s++) {   // the states the directions meet with
-                p.off_meet[s] = off;
-                off += align_up((size_t)d->batch * d->d_inner * d->d_state * sizeof(float), 256);
-            }
         for (int s = 0; s < 2; s++) {
             p.off_pstate[s] = p.off_pdecay[s] = off;
+            // (the states that directions meet with: in the place of those of the parts, of which there are two or more)
+            if (p.ssd_meet && p.ssd_parts == 1) off += align_up((size_t)d->batch * d->d_inner * d->d_state * sizeof(float), 256);
             if (p.ssd_parts > 1) {
                 off += align_up((size_t)p.ssd_subs * d->batch * d->d_inner * d->d_state * sizeof(float), 256);
                 p.off_pdecay[s] = off;
@@ -594,7 +585,8 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
     // (but in kSsdFarParts)
     constexpr int64_t kMaxNearStride = 1 << 24;
     const bool far = in_f->z.stride_token > kMaxNearStride || in_b->z.stride_token > kMaxNearStride || out->stride_token > kMaxNearStride;
-    if (plan.ssd && plan.ssd_parts > 1 && (in_f->x.stride_token > kMaxNearStride || in_b->x.stride_token > kMaxNearStride)) {
+    const bool meet = plan.ssd && plan.ssd_meet && !far;
+    if (meet || (plan.ssd && plan.ssd_parts > 1 && (in_f->x.stride_token > kMaxNearStride || in_b->x.stride_token > kMaxNearStride))) {
         plan.ssd_parts = plan.ssd_subs = plan.ssd_part_subs = 1;
         plan.ssd_part_chunks = plan.ssd_sub_chunks = plan.ssd_chunks;
     }
@@ -718,7 +710,6 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
             // forward scan adds, gates and stores (or each writes its own half)
             const bool separate = d->combine == BIMAMBA_COMBINE_SEPARATE;
             const bool raw = !separate && same_tensor(in_f->z, in_b->z);
-            const bool meet = plan.ssd_meet && !far;
             SsdPrepPair pp{};
             for (int s = 0; s < 2; s++) {
                 SsdPrepArgs& pa = pp.dir[s];
@@ -774,7 +765,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                     sp.dir[s].mode = raw ? kSsdPartialRaw : kSsdPartial;
                     sp.dir[s].first_chunk = 0;
                     sp.dir[s].part_chunks = s == 0 ? half : plan.ssd_chunks - half;
-                    sp.dir[s].h_out = reinterpret_cast<float*>(ws + plan.off_meet[s]);
+                    sp.dir[s].h_out = reinterpret_cast<float*>(ws + plan.off_pstate[s]);
                 }
                 if (launch_ssd_scan(d->d_state, d->d_inner / d->n_heads, sp, 2, d->batch, st) != hipSuccess) return BIMAMBA_ERR_HIP;
                 for (int s = 0; s < 2; s++) {
@@ -782,7 +773,7 @@ int run(const bimamba_desc* d, const bimamba_params* pf, const bimamba_params* p
                     sp.dir[s].mode = raw ? kSsdFinalAddRaw : kSsdFinalAdd;
                     sp.dir[s].first_chunk = s == 0 ? half : plan.ssd_chunks - half;
                     sp.dir[s].part_chunks = plan.ssd_chunks - sp.dir[s].first_chunk;
-                    sp.dir[s].h_in = reinterpret_cast<const float*>(ws + plan.off_meet[s]);
+                    sp.dir[s].h_in = reinterpret_cast<const float*>(ws + plan.off_pstate[s]);
                 }
                 if (launch_ssd_scan(d->d_state, d->d_inner / d->n_heads, sp, 2, d->batch, st) != hipSuccess) return BIMAMBA_ERR_HIP;
             }
@@ -1205,7 +1196,7 @@ int bimamba_time_chunks(const bimamba_desc* desc)
     if (check_desc(desc)) return 0;
     const Plan p = make_plan(desc, true, false, SIZE_MAX);
     RowForm row;
-    return p.ssd ? p.ssd_share : row_call(desc, p, &row) ? 1 : p.nseg;
+    return p.ssd ? p.ssd_parts : row_call(desc, p, &row) ? 1 : p.nseg;
 }
 
 void bimamba_profile_next_call(void* ev_start, void* ev_stop)
