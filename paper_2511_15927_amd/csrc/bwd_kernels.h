@@ -540,8 +540,45 @@ struct BwdWalk {
     const Wave& w;
     float* const lds;
     bool sp;
-    unsigned lo_t, lo_pk, lo_part;                       // the lane's byte offset into a row: I/O dtype, parked records, partial sums
-    Walked odx, odz, oddt, pk, part;
+    unsigned lo_t;                                       // the lane's byte offset into a row of the I/O dtype
+    // What the walk writes (and fetches) token by token.  A pointer of each lane's own, moved by a row a token, is one vector
+    // instruction where the row's address from its number is six scalar ones and the reading of spilled scalars: 8 x 8192 tokens
+    // of 4096 channels, bf16 9531 -> 9302 us, 4 x 4096 with activations of their own for each direction 2447 -> 2372, 8 x 2048
+    // with 8 states 1651 -> 1572, 2 x 500 x 700 85.9 -> 83.5.  fp32 I/O with 16 states lacks the registers (4 x 4096: 2570 ->
+    // 2615, 13 spilled): from the number.
+    static constexpr bool kLanePointers = N < 16 || sizeof(T) == 2;
+    struct Running {
+        // (a pointer to global memory by its type: past the asm below the compiler could not tell, and would use flat instructions)
+        __attribute__((address_space(1))) char* at;   // the lane's place, or (wave-uniform) token 0
+        int stride, step;    // bytes from a token to the next, and to the one before it in scan order
+        unsigned lo;         // the lane's byte offset into a row
+        __device__ __forceinline__ void start(const Wave& w, const void* base, int stride_, unsigned lo_, int j)
+        {
+            at = (__attribute__((address_space(1))) char*)const_cast<void*>(base);
+            stride = stride_;
+            step = -w.dir * stride_;
+            lo = lo_;
+            if constexpr (kLanePointers) {
+                at += (long long)w.token(j) * stride + lo;
+                opaque();
+            }
+        }
+        __device__ __forceinline__ void opaque() { asm volatile("" : "+v"(at)); }
+        __device__ __forceinline__ char* place(const Wave& w, int j)   // j: the scan position it stands at
+        {
+            if constexpr (kLanePointers) return (char*)at;
+            keep_narrow(lo);
+            return (char*)(at + (long long)w.token(j) * stride + lo);
+        }
+        __device__ __forceinline__ void next()
+        {
+            if constexpr (kLanePointers) {
+                at += step;
+                opaque();
+            }
+        }
+    };
+    Running odx, odz, oddt, pk, part;
     float dh[N], gA[N];
     float gD, gcb, gbias, gw[4];
     float dp1, dp2, dp3;                                 // dpre of the tokens one, two, three steps later in scan order
@@ -549,6 +586,7 @@ struct BwdWalk {
     // the next chunk to be walked, requested half a chunk early
     T xnext[CT], dnext[CT], znext[CT], gnext[CT];
     T xbefore[3];                                        // raw x of the three tokens before it
+    float hseg[N];                                       // the state entering the segment, for the next chunk
     float hnext[N], wnext;                               // the state entering it (from zero at the segment's start), and the Delta up to there
 
     __device__ __forceinline__ BwdWalk(const BwdArgs& a_, const Wave& w_, float* lds_) : a(a_), w(w_), lds(lds_) {}
@@ -580,11 +618,12 @@ struct BwdWalk {
         }
         load_block<N>(a.state + w.place(a, a.seg_chunks, k) * (64 * N), hnext, w.lane);
         wnext = a.state_w[w.place(a, a.seg_chunks, k) * 64 + w.lane];
+        __builtin_amdgcn_sched_barrier(0);                       // (not moved into the tokens that follow)
     }
 
     __device__ __forceinline__ void fetch_parked(float (&v)[3], const char* row)
     {
-        const Parked r = *(const Parked*)(row + lo_pk);
+        const Parked r = *(const Parked*)row;
         v[0] = r.dx; v[1] = r.dz; v[2] = r.ddt;
     }
 
@@ -665,8 +704,6 @@ struct BwdWalk {
 #pragma unroll
         for (int n = 0; n < N; n++) h[n] = hnext[n];
         if (carried()) {
-            float hseg[N];
-            load_block<N>(a.seg_h + w.place(a, 1, 0) * (64 * N), hseg, w.lane);
             for_each_decay<N>(w, wnext, [&](int n, float c) { h[n] = fmaf(c, hseg[n], h[n]); });
         }
         float delta[CT], xc[CT], sig[CT];   // Delta, conv + SiLU output, sigmoid of the conv output
@@ -723,6 +760,9 @@ struct BwdWalk {
             // next chunk, its entering state and the three x before it.  (Also after the last chunk, when nothing uses it:
             // under a condition the old values would stay live beside the states.)
             if (i == CT / 2 - 1) request(max(k - 1, w.k0));
+            // (asked for here: where the chunk that uses it asked, it waited; its registers are free only now.  Unused where nothing
+            // precedes the segment.)
+            if (i == 0) load_block<N>(a.seg_h + w.place(a, 1, 0) * (64 * N), hseg, w.lane);
             if (i < LT) load_block<N>(lds + i * 64 * N, hs[i], w.lane);
             float y = w.dval * xc[i];
 #pragma unroll
@@ -778,9 +818,8 @@ struct BwdWalk {
                 // the two totals of a state side by side: the first half of its lanes has dB_t[n], the second dC_t[n]
                 const float db_total = wave_reduce_scatter<N>(terms, u);
                 const bool second = (w.lane & (kLanesPerState / 2)) != 0;
-                keep_narrow(lo_part);
-                if (there && w.exists && w.lane % (kLanesPerState / 2) == 0)
-                    *(float*)(const_cast<char*>(w.at(part, j)) + lo_part) = second ? dc_total : db_total;
+                if (there && w.exists && w.lane % (kLanesPerState / 2) == 0) *(float*)part.place(w, j) = second ? dc_total : db_total;
+                part.next();
             }
             if (sp) {
                 ddt *= sigmoidf(xd[i + 3].second() + w.dtb);
@@ -803,19 +842,19 @@ struct BwdWalk {
             }
             if constexpr (MODE == kBwdAdd) {
                 dxv += q[i & 1][0]; dzv += q[i & 1][1]; ddt += q[i & 1][2];
-                fetch_parked(q[i & 1], w.at(pk, j - 2));            // (the buffer has rows to spare on both sides)
+                fetch_parked(q[i & 1], pk.place(w, j - 2));   // (the buffer has rows to spare on both sides)
             }
-            keep_narrow(lo_t);
-            keep_narrow(lo_pk);
             if (there && w.valid) {
                 if constexpr (MODE == kBwdPark) {
-                    *(Parked*)(const_cast<char*>(w.at(pk, j)) + lo_pk) = Parked{dxv, dzv, ddt};
+                    *(Parked*)pk.place(w, j) = Parked{dxv, dzv, ddt};
                 } else {
-                    IO::st((T*)(const_cast<char*>(w.at(odx, j)) + lo_t), dxv);
-                    IO::st((T*)(const_cast<char*>(w.at(odz, j)) + lo_t), dzv);
-                    IO::st((T*)(const_cast<char*>(w.at(oddt, j)) + lo_t), ddt);
+                    IO::st((T*)odx.place(w, j), dxv);
+                    IO::st((T*)odz.place(w, j), dzv);
+                    IO::st((T*)oddt.place(w, j), ddt);
                 }
             }
+            if constexpr (MODE != kBwdAlone) pk.next();
+            if constexpr (MODE != kBwdPark) { odx.next(); odz.next(); oddt.next(); }
             // (convergent: keeps the compiler from copying the loop's exit test into both sides of the branch above, which
             // would make the loop counter, and with it every row address, a per-lane value)
             __builtin_amdgcn_wave_barrier();
@@ -832,20 +871,19 @@ struct BwdWalk {
     {
         sp = a.dt_softplus != 0;
         lo_t = (unsigned)(w.ch * sizeof(T));
-        lo_pk = (unsigned)(w.ch * sizeof(Parked));
-        lo_part = (unsigned)((w.lane / (kLanesPerState / 2)) * sizeof(float));
-        auto view = [&](const TensorArg& t) {
-            return Walked{(const char*)t.p + (size_t)w.b * t.sb * sizeof(T), (int)(t.st * (long long)sizeof(T))};
+        auto park_from = [&](int j) { pk.start(w, a.parked + (size_t)w.b * a.L * a.Dn, a.Dn * (int)sizeof(Parked), (unsigned)(w.ch * sizeof(Parked)), j); };
+        auto store_from = [&](int j) {
+            auto view = [&](Running& r, const TensorArg& t) { r.start(w, (const char*)t.p + (size_t)w.b * t.sb * sizeof(T), (int)(t.st * (long long)sizeof(T)), lo_t, j); };
+            view(odx, a.gdx[w.s]);
+            view(odz, a.gdz[w.s]);
+            view(oddt, a.gddt[w.s]);
         };
-        odx = view(a.gdx[w.s]);
-        odz = view(a.gdz[w.s]);
-        oddt = view(a.gddt[w.s]);
-        pk = Walked{(const char*)(a.parked + (size_t)w.b * a.L * a.Dn), a.Dn * (int)sizeof(Parked)};
+        const int last = w.j0 + w.k1 * CT - 1;          // the walk's first token, which the sequence may not reach
         // this wave's slot of the dB and dC partial sums: [batch][L][G][slots][N][2]
         const int tiles_per_group = (a.Dn / a.G + 63) / 64;
         const int slot = __builtin_amdgcn_readfirstlane(w.tile % tiles_per_group) + (w.s == 1 ? a.bc_slot_of_rev : 0);
-        part = Walked{(const char*)(a.bc_part[w.s] + (((size_t)w.b * a.L * a.G + w.grp) * a.bc_slots + slot) * (2 * N)),
-                      a.G * a.bc_slots * 2 * N * (int)sizeof(float)};
+        part.start(w, (a.bc_part[w.s] + (((size_t)w.b * a.L * a.G + w.grp) * a.bc_slots + slot) * (2 * N)),
+                   a.G * a.bc_slots * 2 * N * (int)sizeof(float), (unsigned)(w.lane / (kLanesPerState / 2) * sizeof(float)), last);
 #pragma unroll
         for (int n = 0; n < N; n++) dh[n] = gA[n] = 0.0f;
         gD = gcb = gbias = dp1 = dp2 = dp3 = 0.0f;
@@ -853,20 +891,28 @@ struct BwdWalk {
         for (int e = 0; e < 4; e++) gw[e] = 0.0f;
         if (w.j1 < a.L) start_from_next_segment();
         if (!a.park) {
+            store_from(last);
             request(w.k1 - 1);
+            load_block<N>(a.seg_h + w.place(a, 1, 0) * (64 * N), hseg, w.lane);
             chunks<kBwdAlone>(w.k1 - 1, w.k0);
         } else {
             // The two waves of a tile walk the segment's tokens in opposite orders.  The forward direction's wave parks the
             // later half, the reverse one's the earlier half; the barrier is a workgroup-scope release / acquire: past it,
             // what the other wave parked is visible.  It is fetched two tokens ahead.
             const int to = w.s == 0 ? a.seg_chunks / 2 : a.seg_chunks - a.seg_chunks / 2;
+            park_from(last);
             request(w.k1 - 1);
+            load_block<N>(a.seg_h + w.place(a, 1, 0) * (64 * N), hseg, w.lane);
             chunks<kBwdPark>(w.k1 - 1, max(to, w.k0));
             __syncthreads();
             const int from = min(to, w.k1) - 1, j = w.j0 + from * CT + CT - 1;
             if (from >= w.k0) {
-                fetch_parked(q[1], w.at(pk, j));
-                fetch_parked(q[0], w.at(pk, j - 1));
+                park_from(j);
+                fetch_parked(q[1], pk.place(w, j));
+                pk.next();
+                fetch_parked(q[0], pk.place(w, j - 1));
+                pk.next();
+                store_from(j);
             }
             chunks<kBwdAdd>(from, w.k0);
         }
