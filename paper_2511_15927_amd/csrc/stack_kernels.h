@@ -78,8 +78,10 @@ __global__ __launch_bounds__(64 * kRowMaxWaves, 1) void stack_kernel(const Stack
         const float* h;
         const T* tail;
     };
+    // (the tables of layers and steps by scalar loads: pointers read through them are known to be global memory)
+    typedef const __attribute__((address_space(4))) bimamba_stack_layer* uniform_layer;
+    typedef const __attribute__((address_space(4))) bimamba_inputs* uniform_inputs;
     auto places = [&](int l) {
-        typedef const __attribute__((address_space(4))) bimamba_stack_layer* uniform_layer;
         const uniform_layer ly = (uniform_layer)(a.layers + l);
         auto p = s == 0 ? &ly->f : &ly->b;
         return Places{p->conv_w, p->conv_b, p->A, p->D, p->dt_bias, s == 0 ? ly->h : nullptr, s == 0 && seg == 0 ? (const T*)ly->tail : nullptr};
@@ -112,30 +114,30 @@ __global__ __launch_bounds__(64 * kRowMaxWaves, 1) void stack_kernel(const Stack
 
     for (int step = 0; step < a.n_steps; step++) {
         // ---- what the layers of a step share: x of the first one, B|C rows as fp32, Delta, the gates
-        const bimamba_inputs& in = a.steps[step];
-        const T* const zb = (const T*)in.z.ptr + (size_t)b * in.z.stride_batch;
-        const T* const xb = (const T*)in.x.ptr + (size_t)b * in.x.stride_batch;
-        const T* const db = (const T*)in.dt.ptr + (size_t)b * in.dt.stride_batch + head;
+        const uniform_inputs in = (uniform_inputs)(a.steps + step);
+        const T* const zb = (const T*)in->z.ptr + (size_t)b * in->z.stride_batch;
+        const T* const xb = (const T*)in->x.ptr + (size_t)b * in->x.stride_batch;
+        const T* const db = (const T*)in->dt.ptr + (size_t)b * in->dt.stride_batch + head;
         T xr[OUTPUTS], zr[OUTPUTS];
 #pragma unroll
         for (int k = 0; k < OUTPUTS; k++) {
             if (k * threads < outputs) {
                 const int i = min(tid + k * threads, outputs - 1), t = i >> shift, chan = min(ch0 + (i & (width - 1)), a.Dn - 1);
-                xr[k] = xb[(long long)t * in.x.stride_token + chan];
-                zr[k] = zb[(long long)t * in.z.stride_token + chan];
+                xr[k] = xb[(long long)t * in->x.stride_token + chan];
+                zr[k] = zb[(long long)t * in->z.stride_token + chan];
             }
         }
-        for (int g = 0; g < groups; g++) ud[g * 256 + 192 + lane] = IO::cvt(db[place(j0 + g * kRowTokens + n) * in.dt.stride_token]);
+        for (int g = 0; g < groups; g++) ud[g * 256 + 192 + lane] = IO::cvt(db[place(j0 + g * kRowTokens + n) * in->dt.stride_token]);
         {
             constexpr int kFlight = 8;
             const int m = tid & 15, which = (tid >> 4) & 1, rows = threads >> 5;
-            const bimamba_tensor& src = which ? in.C : in.B;
-            const T* const col = (const T*)src.ptr + (size_t)b * src.stride_batch + grp * a.N + min(m, a.N - 1);
+            const long long col_token = which ? in->C.stride_token : in->B.stride_token;
+            const T* const col = (which ? (const T*)in->C.ptr : (const T*)in->B.ptr) + (size_t)b * (which ? in->C.stride_batch : in->B.stride_batch) + grp * a.N + min(m, a.N - 1);
             float* const dst = row_lds + lds.bc + (kRowTokens * 16 + m) * 2 + which;
             for (int t0 = tid >> 5; t0 < a.L; t0 += kFlight * rows) {
                 T v[kFlight];
 #pragma unroll
-                for (int k = 0; k < kFlight; k++) v[k] = col[(long long)min(t0 + k * rows, last) * src.stride_token];
+                for (int k = 0; k < kFlight; k++) v[k] = col[(long long)min(t0 + k * rows, last) * col_token];
 #pragma unroll
                 for (int k = 0; k < kFlight; k++)
                     if (t0 + k * rows < a.L) dst[(t0 + k * rows) * 32] = m < a.N ? IO::cvt(v[k]) : 0.0f;
@@ -194,11 +196,11 @@ __global__ __launch_bounds__(64 * kRowMaxWaves, 1) void stack_kernel(const Stack
                 ud[g * 256 + 128 + lane] = p.dval * xc;
             }
             // the committed tail: the last K - 1 raw tokens of (tail || block), by the wave that holds the old one
-            if (commit && a.K > 1 && s == 0 && seg == 0 && a.layers[l].tail) {
+            if (commit && a.K > 1 && s == 0 && seg == 0 && ((uniform_layer)(a.layers + l))->tail) {
                 const int pos = a.L + n - (a.K - 1);     // token of the block, or (negative) of the cached tail: lane pos + 16 holds that
                 const float old = __shfl(IO::cvt(p.tail), (lane & 48) | ((pos + kRowTokens) & 15));
                 if (n < a.K - 1 && valid)
-                    ((T*)a.layers[l].tail)[((size_t)b * (a.K - 1) + n) * a.Dn + ch] = io_value<IO>(pos >= 0 ? xc_row[pos] : old);
+                    ((T*)((uniform_layer)(a.layers + l))->tail)[((size_t)b * (a.K - 1) + n) * a.Dn + ch] = io_value<IO>(pos >= 0 ? xc_row[pos] : old);
             }
             // ---- the recurrence over the segment
             float h = p.h;
@@ -229,7 +231,8 @@ __global__ __launch_bounds__(64 * kRowMaxWaves, 1) void stack_kernel(const Stack
             }
             if (s == 0) walk(std::true_type{}, Up{});
             else walk(std::true_type{}, Down{});
-            if (commit && s == 0 && a.layers[l].h && valid && state && j1 == a.L && j1 > j0) a.layers[l].h[state_at] = h;
+            float* const h_out = ((uniform_layer)(a.layers + l))->h;
+            if (commit && s == 0 && h_out && valid && state && j1 == a.L && j1 > j0) h_out[state_at] = h;
             __syncthreads();                             // both directions' outputs
             // ---- gate, combine, round: channels across the lanes; the result is the next layer's x
 #pragma unroll
