@@ -63,13 +63,14 @@ static hipError_t launch_io(const StackArgs& a, int batch, hipStream_t st)
 
 // Steps side by side in the quad form, 0: the row form is the choice.  Clocks of a layer for all steps of a block, from what a SIMD's
 // waves issue: alone on its SIMD a wave issues an instruction every seven clocks, several share the vector pipe at 4.6 a slot.
-//   quad   34 / 22 / 16 slots a token and lane (16 / 8 / 4 states); a workgroup to a CU, side / 2 waves a SIMD; 2500 a layer
+//   quad   34 / 22 / 16 slots a token and lane (16 / 8 / 4 states); a workgroup to a CU, side / 2 waves a SIMD (the
+//          fullest one sets the pace of all at a layer's barriers); 2500 a layer
 //   row    14.5 instructions, 11.3 slots; time segments walk their tokens 1.6 times; 1300 a layer, one step after the other
 // Measured, us a layer and step, quad / row (bf16; layers feed each other):
 //   16 states, 32 tokens, 8 steps   512 chains 1.19/1.92, 4096 1.21/2.34, 8192 2.50/3.35, 16384 5.28/6.92, 32768 10.4/13.2, 45056 15.1/19.4
 //   4096 chains x 32, 1 / 2 / 3 / 4 steps   5.63/3.22  2.63/2.56  2.20/2.63  1.58/2.42
 //   2 x 16 tokens of 2856, 3 steps 1.84/2.14
-//   64 tokens    4096 chains, 8 steps 2.89/5.09, 1024 chains, 4 steps 2.91/3.07, 16384 chains, 8 steps 12.0/12.1
+//   64 tokens    1640 chains, 3 steps 3.4/3.2, 4096 chains, 8 steps 2.89/5.09, 1024 chains, 4 steps 2.91/3.07, 16384 chains, 8 steps 12.0/12.1
 //   128 tokens   1024 chains, 4 steps 8.88/3.88
 //   8 states     4096 chains x 32, 8 steps 0.93/2.47, 24576 6.22/10.9, 2616 x 64, 4 steps 2.08/4.80
 static int quad_steps(const StackArgs& a, int batch)
@@ -80,7 +81,7 @@ static int quad_steps(const StackArgs& a, int batch)
     const int rounds = (a.n_steps + most - 1) / most, side = (a.n_steps + rounds - 1) / rounds;
     const double cus = cu_count(), slots = a.N == 16 ? 34.0 : a.N == 8 ? 22.0 : 16.0;
     const double quads = std::ceil((double)((a.Dn + kQuadChannels - 1) / kQuadChannels) * batch / cus);
-    const double quad = rounds * (a.L * slots * std::max(7.0, 4.6 * quads * side / 2) + 2500.0);
+    const double quad = rounds * (a.L * slots * std::max(7.0, 4.6 * std::ceil(quads * side / 2)) + 2500.0);
     const double waves = (double)batch * ((a.Dn + 3) / 4) * 2 * a.nseg / (4 * cus);
     const double tokens = a.nseg > 1 ? 1.6 * a.seg_len : a.L;
     const double row = a.n_steps * (tokens * std::max(7.0 * 14.5, 4.6 * 11.3 * waves) + 1300.0);
