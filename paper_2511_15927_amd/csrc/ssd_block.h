@@ -46,8 +46,9 @@ struct SsdBlockArgs {
     const float* h_in;    // [batch][Dn][N] or null
     float* h_out;         // or null; may alias h_in
     const void* tail_in;  // bf16 [batch][K-1][tail_ch] or null
-    void* tail_out;       // or null; may alias tail_in (not in one launch where B and C have a part: every workgroup reads that of its
-                          // group): x's part is written by whoever reads it there, B's and C's by the preparation or a group's first workgroup
+    void* tail_out;       // or null; may alias tail_in: x's part is written by whoever reads it there, B's and C's by the preparation, or, in
+                          // one launch that commits the state, by a group's first workgroup (there not aliasing, since every workgroup of the
+                          // group reads it; a launch that does not commit the state writes no part of B and C)
     int batch, L, Dn, H, P, HG, G, K, tail_ch;
     int dt_softplus, d_per_head, conv_bc, separate;
     int shared;           // both directions read the same x and the same z

@@ -317,3 +317,51 @@ def test_one_launch_short_calls(gpu, oracle, L, N, io, a_kind, own):
     assert_close(out.float().cpu().numpy().reshape(ref.shape), ref, gpu.TOL[io])
     assert rel_l2(dh.cpu().numpy(), h_ref) < 1e-5
     assert np.array_equal(dt.float().cpu().numpy().astype(np.float64), t_ref)
+
+
+@pytest.mark.parametrize("form,cfg", [
+    ("row", synth.mixer_cfg(1, 17, 68, io="f32")),
+    ("one launch", synth.mixer_cfg(2, 9, 192, state_split=1, time_chunks=1)),
+    ("sweep", synth.mixer_cfg(2, 75, 192, time_chunks=1)),
+    ("m2, lane per chain", synth.m2_cfg(2, 6, 128, headdim=32, d_state=16)),
+    ("m2, one launch", synth.m2_cfg(3, 32, 192, headdim=64, d_state=128)),
+    ("m2, one launch, shorter than the tail", synth.m2_cfg(2, 2, 256, headdim=32, d_state=64, n_groups=2)),
+    ("m2, one launch, conv of three", synth.m2_cfg(1, 31, 96, headdim=32, d_state=128, d_conv=3)),
+    ("m2, one launch, two tiles a workgroup", synth.m2_cfg(50, 5, 512, headdim=64, d_state=64, n_groups=2)),
+    ("m2, four tiles a workgroup", synth.m2_cfg(85, 3, 640, headdim=64, d_state=64)),
+    ("m2, two launches", synth.m2_cfg(2, 33, 192, headdim=64, d_state=128)),
+    ("m2, chunks", synth.m2_cfg(2, 129, 128, headdim=64, d_state=64)),
+])
+@pytest.mark.parametrize("cached", [True, False])
+def test_state_and_tail_are_committed_each_by_itself(gpu, oracle, form, cfg, cached):
+    """h_out and tail_out do not depend on each other: either, both or neither, from a cached state and tail and from none, with the
+    directions' activations shared and apart; what is committed is written whole (its buffers hold NaN before)."""
+    from paper_2511_15927_amd import binding as bd
+    pf, pb = synth.make_params(cfg, 70, 0), synth.make_params(cfg, 70, 1)
+    inp, inp_b = synth.make_inputs(cfg, 71), synth.make_inputs(cfg, 72)
+    Bt, Dn, N, K, ch = cfg["batch"], cfg["d_inner"], cfg["d_state"], cfg["d_conv"], synth.conv_channels(cfg)
+    g = torch.Generator().manual_seed(73)
+    h0 = (0.2 * torch.randn(Bt, Dn, N, generator=g)).float() if cached else None
+    tail0 = synth.round_io(torch.randn(Bt, K - 1, ch, generator=g), cfg["io"]) if cached else None
+    desc, dpf, dpb = bd.make_desc(cfg), bd.to_device(pf), bd.to_device(pb)
+    dinp, ws = bd.to_device(inp, cfg), bd.alloc_workspace(desc, 1)
+    h_tol = 1e-2 if form.startswith("m2") and cfg["d_state"] >= 64 else 1e-5     # (the matrix-core path takes the state from bf16 operands)
+    for other in (None, inp_b):
+        ref, h_ref, t_ref = oracle.bimamba_block_fwd(cfg, to_np(pf), to_np(pb), to_np(inp), None if other is None else to_np(other),
+                                                     h_in=None if h0 is None else h0.numpy(), tail_in=None if tail0 is None else tail0.numpy())
+        dother = None if other is None else bd.to_device(other, cfg)
+        for with_h in (False, True):
+            for with_tail in (False, True):
+                h = torch.full((Bt, Dn, N), float("nan"), device="cuda") if with_h else None
+                tail = torch.full((Bt, K - 1, ch), float("nan"), dtype=bd.io_dtype(cfg), device="cuda") if with_tail else None
+                out = bd.alloc_out(cfg)
+                bd.bimamba_block_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp),
+                                     None if dother is None else bd.make_inputs(dother), None if h0 is None else h0.cuda(),
+                                     None if tail0 is None else tail0.to(device="cuda", dtype=bd.io_dtype(cfg)), h, tail, bd.make_tensor(out), ws)
+                torch.cuda.synchronize()
+                what = (other is not None, with_h, with_tail)
+                assert_close(out.float().cpu().numpy(), ref, gpu.TOL[cfg["io"]], what)
+                if with_h:
+                    assert rel_l2(h.cpu().numpy(), h_ref) < h_tol, what
+                if with_tail:
+                    assert np.array_equal(tail.float().cpu().numpy().astype(np.float64), t_ref), what
