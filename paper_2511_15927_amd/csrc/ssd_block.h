@@ -362,6 +362,49 @@ __device__ __forceinline__ void ssd_block_scores_of(int wave, int lane, const __
     *reinterpret_cast<f32x4*>(&score[s * 1024 + ((it * 64 + (2 * jt + g4 / 2) * 16 + c16) * 8 + 4 * (g4 % 2))]) = acc;
 }
 
+// What the walk's two forms do in different places, as functions of values.  A closure that holds the kernel's arguments by reference, anywhere
+// in its body, changes how the compiler orders their loads in all of it: calls in two launches whose directions have x and z of their own
+// lose by it (16 x 64 tokens of 64 heads x 64, state committed, 49.4 us without and 50.5 with), those that share them gain (state not
+// committed 28.9 and 28.4; 9 x 64 of 640 channels 22.6 and 22.2), so there the last of these takes one.
+template <int BLOCKS>
+__device__ __forceinline__ void ssd_block_rows(Piece (&to)[BLOCKS], const unsigned short* from, long long stride, int t, int last)
+{
+#pragma unroll
+    for (int k = 0; k < BLOCKS; k++) to[k] = *reinterpret_cast<const Piece*>(from + (long long)min(t + 32 * k, last) * stride);
+}
+// A wave's share of the score units of its head: first, first + step, ..
+template <int SCORES, int SHARES>
+__device__ __forceinline__ void ssd_block_score_units(f32x4 (&sc)[SHARES][2], const float* fwd, const float* rev, size_t at, int first, int step, int lane)
+{
+#pragma unroll
+    for (int k = 0; k < SHARES; k++) {
+        const int u = first + k * step, us = u / (2 * SCORES), v = u - us * (2 * SCORES);
+        if (u < 2 * SHARES) {
+            const float* const src = (us == 0 ? fwd : rev) + at + (v * 64 + lane) * 8;
+            sc[k][0] = *reinterpret_cast<const f32x4*>(src);
+            sc[k][1] = *reinterpret_cast<const f32x4*>(src + 4);
+        }
+    }
+}
+// Inter-block term of the forward direction: exp(l_i) C_i H.
+template <int NB, int RT, typename COp>
+__device__ __forceinline__ void ssd_block_inter(f32x4 (&y)[RT], const f32x4 (&h)[NB][2], const float* exp_l, int g4, COp c_op)
+{
+#pragma unroll
+    for (int nb = 0; nb < NB; nb++) {
+        bf16x8 hb;
+#pragma unroll
+        for (int e = 0; e < 8; e++) hb[e] = (__bf16)h[nb][e / 4][e % 4];
+#pragma unroll
+        for (int rt = 0; rt < RT; rt++) y[rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c_op(nb, rt), hb, y[rt], 0, 0, 0);
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; rt++) {
+        const float4 e4 = *reinterpret_cast<const float4*>(&exp_l[16 * rt + 4 * g4]);
+        y[rt][0] *= e4.x; y[rt][1] *= e4.y; y[rt][2] *= e4.z; y[rt][3] *= e4.w;
+    }
+}
+
 // grid (ceil(Dn / 64), 1, batch), block 256: wave w owns channels 16 (4 blockIdx.x + w) .. of one batch element.  COMMIT: h_out is
 // written; SHARED: both directions read the same x and the same z (the registers of the other cases are not held here).
 // WHOLE: grid (ceil(Dn / 64 / tiles), 1, batch), block 1024, dynamic LDS SsdBlockLds::bytes(tiles): the workgroup makes the operands
@@ -505,34 +548,23 @@ __global__ __launch_bounds__(WHOLE ? 1024 : 256, WHOLE ? 4 : BLOCKS == 1 ? 4 : C
     const int head_waves = a.P / 16, hw = wave % head_waves;
     bf16x8* const m_ops = s_m + (wave / head_waves) * (kUnits * 64) + lane;
     f32x4 sc[kUnits / 2][2];
-    auto scores = [&](const float* fwd, const float* rev) {
-#pragma unroll
-        for (int k = 0; k < kUnits / 2; k++) {
-            const int u = hw + k * head_waves, us = u / (2 * kScores), v = u - us * (2 * kScores);
-            if (u < kUnits) {
-                const float* const src = (us == 0 ? fwd : rev) + (v * 64 + lane) * 8;
-                sc[k][0] = *reinterpret_cast<const f32x4*>(src);
-                sc[k][1] = *reinterpret_cast<const f32x4*>(src + 4);
-            }
-        }
-    };
-    if constexpr (!WHOLE) scores(a.score[0] + item * (kScores * 1024), a.score[1] + item * (kScores * 1024));
-    auto request_z = [&] {
+    if constexpr (!WHOLE) ssd_block_score_units<kScores>(sc, a.score[0], a.score[1], item * (kScores * 1024), hw, head_waves, lane);
+    constexpr bool kLateZ = WHOLE && COMMIT && !SHARED && N == 128;   // (for which there are no registers beside the rows')
+    if constexpr (!kLateZ) {
 #pragma unroll
         for (int s = 0; s < (kTwoX ? 2 : 1); s++)
-#pragma unroll
-            for (int k = 0; k < BLOCKS; k++)
-                zraw[s][k] = *reinterpret_cast<const Piece*>((const T*)a.dir[s].z.p + (size_t)b * a.dir[s].z.sb +
-                                                             (long long)min((tid >> 3) + 32 * k, last) * a.dir[s].z.st + piece_ch);
-    };
-    constexpr bool kLateZ = WHOLE && COMMIT && !SHARED && N == 128;   // (for which there are no registers beside the rows')
-    if constexpr (!kLateZ) request_z();
+            ssd_block_rows(zraw[s], (const T*)a.dir[s].z.p + (size_t)b * a.dir[s].z.sb + piece_ch, a.dir[s].z.st, tid >> 3, last);
+    }
     if constexpr (WHOLE) {
         __builtin_amdgcn_sched_barrier(0);
         if (has_rows) bc.finish(a, b, split, s_bt);
         __builtin_amdgcn_sched_barrier(0);
     }
-    if constexpr (kLateZ) request_z();
+    if constexpr (kLateZ) {
+#pragma unroll
+        for (int s = 0; s < (kTwoX ? 2 : 1); s++)
+            ssd_block_rows(zraw[s], (const T*)a.dir[s].z.p + (size_t)b * a.dir[s].z.sb + piece_ch, a.dir[s].z.st, tid >> 3, last);
+    }
 #pragma unroll
     for (int s = 0; s < (kTwoX ? 2 : 1); s++)
 #pragma unroll
@@ -602,37 +634,15 @@ __global__ __launch_bounds__(WHOLE ? 1024 : 256, WHOLE ? 4 : BLOCKS == 1 ? 4 : C
     f32x4 y[2][kRT];
 #pragma unroll
     for (int rt = 0; rt < kRT; rt++) y[0][rt] = y[1][rt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    auto inter_block = [&] {
-        if (!a.h_in) return;
-        auto c_op = [&](int nb, int rt) -> bf16x8 {
-            if constexpr (WHOLE) {
+    if constexpr (WHOLE) {
+        if (a.h_in)
+            ssd_block_inter(y[0], h, tab[2], g4, [=](int nb, int rt) -> bf16x8 {
                 const __bf16* const row = &split[0][2][16 * rt + c16][32 * nb + 4 * g4];
                 const bf16x4 lo = *reinterpret_cast<const bf16x4*>(row), hi = *reinterpret_cast<const bf16x4*>(row + 16);
                 return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-            } else {
-                return reinterpret_cast<const bf16x8*>(a.c_op)[item * (kTok * N / 8) + (nb * kRT + rt) * 64 + lane];
-            }
-        };
-#pragma unroll
-        for (int nb = 0; nb < kNB; nb++) {
-            bf16x8 hb;
-#pragma unroll
-            for (int e = 0; e < 8; e++) hb[e] = (__bf16)h[nb][e / 4][e % 4];
-#pragma unroll
-            for (int rt = 0; rt < kRT; rt++)
-                y[0][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c_op(nb, rt), hb, y[0][rt], 0, 0, 0);
-        }
-#pragma unroll
-        for (int rt = 0; rt < kRT; rt++) {
-            const float4 e4 = *reinterpret_cast<const float4*>(&tab[2][16 * rt + 4 * g4]);
-            y[0][rt][0] *= e4.x; y[0][rt][1] *= e4.y; y[0][rt][2] *= e4.z; y[0][rt][3] *= e4.w;
-        }
-    };
-    if constexpr (WHOLE) inter_block();
-
-    if constexpr (WHOLE) {
+            });
         __syncthreads();                                   // the scores
-        scores(s_score, s_score + 1024);
+        ssd_block_score_units<kScores>(sc, s_score, s_score + 1024, 0, hw, head_waves, lane);
     }
     // ---- the head's masked, decayed score operands
 #pragma unroll
@@ -668,7 +678,17 @@ __global__ __launch_bounds__(WHOLE ? 1024 : 256, WHOLE ? 4 : BLOCKS == 1 ? 4 : C
         }
     }
 
-    if constexpr (!WHOLE) inter_block();
+    if constexpr (!WHOLE) {
+        if constexpr (SHARED) {   // (by reference: see ssd_block_rows)
+            if (a.h_in)
+                ssd_block_inter(y[0], h, tab[2], g4, [&](int nb, int rt) {
+                    return reinterpret_cast<const bf16x8*>(a.c_op)[item * (kTok * N / 8) + (nb * kRT + rt) * 64 + lane];
+                });
+        } else if (a.h_in) {
+            const bf16x8* const c_op = reinterpret_cast<const bf16x8*>(a.c_op) + item * (kTok * N / 8) + lane;
+            ssd_block_inter(y[0], h, tab[2], g4, [=](int nb, int rt) { return c_op[(nb * kRT + rt) * 64]; });
+        }
+    }
 
     __syncthreads();                                       // x and the score operands
     // ---- conv + SiLU of the lane's runs, as contraction operands, and (forward) weighted to the block's end
