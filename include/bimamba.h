@@ -205,13 +205,20 @@ typedef struct bimamba_stack_layer {
  *               layer l of step s (place s * n_layers + l) leaves its output, io_dtype [batch, seqlen, d_inner] contiguous, or
  *               NULL (not wanted).
  *   table_dev   a copy of it in device memory, 8-byte aligned; it stays until the work has run.
- * Outputs must not overlap any step's inputs.  Only for descriptors bimamba_block_stack_form answers 1 to: few enough chains that
+ * Outputs must not overlap any step's inputs.  Among themselves they may share memory, whole tokens apart: what a later step, or layer,
+ * leaves there stays.  (A table whose steps share outputs, or whose layers share a state or a tail, is walked one step after the
+ * other.)  Only for descriptors bimamba_block_stack_form answers 1 to: few enough chains that
  * a workgroup takes a few channels through the whole stack, since channels are mixed nowhere.  Nothing is allocated, no scratch is
  * used.
  */
 int bimamba_block_stack(const bimamba_desc* desc, int n_layers, int n_steps, const void* table, const void* table_dev,
                         void* hip_stream);
 int bimamba_block_stack_form(const bimamba_desc* desc);
+
+/* How many of a stack's n_steps steps bimamba_block_stack takes side by side, four lanes to a chain; 0: one after the other, a row of
+ * lanes to a chain (and for every descriptor that bimamba_block_stack_form answers 0 to).  For tables that share no outputs between
+ * steps and no state or tail between layers; the others take their steps one after the other.  Pure host code. */
+int bimamba_block_stack_side_by_side(const bimamba_desc* desc, int n_steps);
 
 /*
  * A call's x, z, dt, B and C into buffers of the caller, in one launch: a decode loop refreshes the fixed inputs of a captured step with

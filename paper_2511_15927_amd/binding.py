@@ -22,9 +22,9 @@ STATUS = {0: "BIMAMBA_OK", -1: "BIMAMBA_ERR_NULL_POINTER", -2: "BIMAMBA_ERR_BAD_
           -7: "BIMAMBA_ERR_SCRATCH_EXCEEDED", -8: "BIMAMBA_ERR_ALIAS"}
 STATIC_SCRATCH_BYTES = 64 << 20
 
-EXPORTS = ("bimamba_fwd", "bimamba_block_fwd", "bimamba_block_fwd_static", "bimamba_block_stack", "bimamba_block_stack_form", "bimamba_copy_inputs", "bimamba_bwd",
-           "bimamba_workspace_bytes",           "bimamba_bwd_workspace_bytes", "bimamba_time_chunks", "bimamba_profile_next_call", "bimamba_status_string",
-           "bimamba_version")
+EXPORTS = ("bimamba_fwd", "bimamba_block_fwd", "bimamba_block_fwd_static", "bimamba_block_stack", "bimamba_block_stack_form",
+           "bimamba_block_stack_side_by_side", "bimamba_copy_inputs", "bimamba_bwd", "bimamba_workspace_bytes",
+           "bimamba_bwd_workspace_bytes", "bimamba_time_chunks", "bimamba_profile_next_call", "bimamba_status_string", "bimamba_version")
 
 
 class Desc(C.Structure):
@@ -90,6 +90,8 @@ def lib():
         L.bimamba_block_stack.argtypes = [C.POINTER(Desc), C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p]
         L.bimamba_block_stack_form.restype = C.c_int
         L.bimamba_block_stack_form.argtypes = [C.POINTER(Desc)]
+        L.bimamba_block_stack_side_by_side.restype = C.c_int
+        L.bimamba_block_stack_side_by_side.argtypes = [C.POINTER(Desc), C.c_int]
         L.bimamba_copy_inputs.restype = C.c_int
         L.bimamba_copy_inputs.argtypes = [C.POINTER(Desc), C.POINTER(Inputs), C.POINTER(Inputs), C.c_void_p]
         L.bimamba_bwd.restype = C.c_int
@@ -261,6 +263,10 @@ def bimamba_block_fwd_static(desc, pf, pb, in_f, in_b, h_in, tail_in, h_out, tai
 
 def bimamba_block_stack_form(desc):
     return int(lib().bimamba_block_stack_form(C.byref(desc)))
+
+
+def bimamba_block_stack_side_by_side(desc, n_steps):
+    return int(lib().bimamba_block_stack_side_by_side(C.byref(desc), n_steps))
 
 
 def make_stack_table(layers, steps, outs):

@@ -13,6 +13,8 @@
 #include <algorithm>
 #include <atomic>
 #include <cmath>
+#include <memory>
+#include <new>
 
 // Device memory of bimamba_block_fwd_static, the entry point for callers that cannot allocate: one copy per GPU, held
 // until the process ends.  In host code this name only identifies the symbol; the address a kernel can use is asked
@@ -876,6 +878,56 @@ bool stack_call(const bimamba_desc* d, RowForm* row)
            d->batch > 0 && stack_form(d->batch, d->seqlen, d->d_inner, d->d_state, row);
 }
 
+StackArgs stack_args(const bimamba_desc* d, const RowForm& row, int n_layers, int n_steps)
+{
+    StackArgs sa{};
+    sa.n_layers = n_layers; sa.n_steps = n_steps;
+    sa.L = d->seqlen; sa.Dn = d->d_inner; sa.P = d->d_inner / d->n_heads; sa.HG = d->n_heads / d->n_groups;
+    sa.G = d->n_groups; sa.N = d->d_state; sa.K = d->d_conv;
+    sa.dt_softplus = d->dt_softplus; sa.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD;
+    sa.a_scalar = d->a_kind == BIMAMBA_A_SCALAR_PER_HEAD;
+    sa.tw = row.tw; sa.tw_log2 = row.tw == 4 ? 2 : row.tw == 2 ? 1 : 0; sa.nseg = row.nseg; sa.seg_len = row.seg_len;
+    return sa;
+}
+
+// Buffers of one size, each with its owner: whether no two owners' overlap.
+struct Owned {
+    uintptr_t at;
+    int owner;
+};
+bool owners_apart(Owned* r, int n, size_t bytes)
+{
+    std::sort(r, r + n, [](const Owned& x, const Owned& y) { return x.at < y.at; });
+    int nearest = -1, other = -1;   // of what lies before: the last buffer, and the last one of another owner than its
+    for (int i = 0; i < n; i++) {
+        if (nearest >= 0 && r[nearest].owner != r[i].owner) other = nearest;
+        nearest = i;
+        if (other >= 0 && r[i].at - r[other].at < bytes) return false;
+    }
+    return true;
+}
+
+// Whether a stack's steps may go in any order beside each other: outputs of different steps, and states and tails of different layers,
+// lie apart.
+bool steps_apart(const bimamba_desc* d, const bimamba_stack_layer* layers, int n_layers, void* const* outs, int n_steps)
+{
+    const size_t elem = d->io_dtype == BIMAMBA_BF16 ? 2 : 4, channels = (size_t)d->batch * d->d_inner;
+    const std::unique_ptr<Owned[]> r(new (std::nothrow) Owned[std::max((size_t)n_layers, (size_t)n_steps * n_layers)]);
+    if (!r) return false;
+    int n = 0;
+    auto take = [&](const void* p, int owner) {
+        if (p) r[n++] = Owned{reinterpret_cast<uintptr_t>(p), owner};
+    };
+    for (int i = 0; i < n_steps * n_layers; i++) take(outs[i], i / n_layers);
+    if (!owners_apart(r.get(), n, channels * d->seqlen * elem)) return false;
+    n = 0;
+    for (int l = 0; l < n_layers; l++) take(layers[l].h, l);
+    if (!owners_apart(r.get(), n, channels * d->d_state * sizeof(float))) return false;
+    n = 0;
+    for (int l = 0; l < n_layers; l++) take(d->d_conv > 1 ? layers[l].tail : nullptr, l);
+    return owners_apart(r.get(), n, channels * (d->d_conv - 1) * elem);
+}
+
 int run_stack(const bimamba_desc* d, int n_layers, int n_steps, const void* table, const void* table_dev, void* hip_stream)
 {
     int rc = check_desc(d);
@@ -910,17 +962,12 @@ int run_stack(const bimamba_desc* d, int n_layers, int n_steps, const void* tabl
         }
     }
     const hipError_t pending = hipPeekAtLastError();
-    StackArgs sa{};
+    StackArgs sa = stack_args(d, row, n_layers, n_steps);
     sa.layers = static_cast<const bimamba_stack_layer*>(table_dev);
     sa.steps = reinterpret_cast<const bimamba_inputs*>(sa.layers + n_layers);
     sa.outs = reinterpret_cast<void* const*>(sa.steps + n_steps);
-    sa.n_layers = n_layers; sa.n_steps = n_steps;
-    sa.L = d->seqlen; sa.Dn = d->d_inner; sa.P = d->d_inner / d->n_heads; sa.HG = d->n_heads / d->n_groups;
-    sa.G = d->n_groups; sa.N = d->d_state; sa.K = d->d_conv;
-    sa.dt_softplus = d->dt_softplus; sa.d_per_head = d->d_kind == BIMAMBA_D_PER_HEAD;
-    sa.a_scalar = d->a_kind == BIMAMBA_A_SCALAR_PER_HEAD;
-    sa.tw = row.tw; sa.tw_log2 = row.tw == 4 ? 2 : row.tw == 2 ? 1 : 0; sa.nseg = row.nseg; sa.seg_len = row.seg_len;
-    if (launch_stack(d->io_dtype == BIMAMBA_BF16, sa, d->batch, reinterpret_cast<hipStream_t>(hip_stream)) != hipSuccess) return BIMAMBA_ERR_HIP;
+    const bool apart = steps_apart(d, layers, n_layers, outs, n_steps);
+    if (launch_stack(d->io_dtype == BIMAMBA_BF16, sa, d->batch, apart, reinterpret_cast<hipStream_t>(hip_stream)) != hipSuccess) return BIMAMBA_ERR_HIP;
     const hipError_t now = hipPeekAtLastError();
     return now == hipSuccess || now == pending ? BIMAMBA_OK : BIMAMBA_ERR_HIP;
 }
@@ -1186,6 +1233,13 @@ int bimamba_block_stack_form(const bimamba_desc* desc)
 {
     RowForm row;
     return check_desc(desc) == BIMAMBA_OK && stack_call(desc, &row);
+}
+
+int bimamba_block_stack_side_by_side(const bimamba_desc* desc, int n_steps)
+{
+    RowForm row;
+    if (check_desc(desc) != BIMAMBA_OK || n_steps < 1 || !stack_call(desc, &row)) return 0;
+    return bm::stack_side_by_side(stack_args(desc, row, 1, n_steps), desc->batch);
 }
 
 int bimamba_copy_inputs(const bimamba_desc* desc, const bimamba_inputs* from, const bimamba_inputs* to, void* hip_stream)

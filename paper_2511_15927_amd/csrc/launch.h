@@ -57,7 +57,9 @@ bool row_form(int batch, int seqlen, int d_inner, int d_state, bool halves, RowF
 bool row_reach(int batch, int seqlen, int d_inner);   // whether a call is of a size that the row form takes for some state count and combine
 bool stack_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f);      // the same for a stack of layers (stack_kernels.h)
 struct StackArgs;
-hipError_t launch_stack(int io_bf16, const StackArgs& a, int batch, hipStream_t st);
+// apart: no two steps have outputs, no two layers states or tails in the same memory
+hipError_t launch_stack(int io_bf16, const StackArgs& a, int batch, bool apart, hipStream_t st);
+int stack_side_by_side(const StackArgs& a, int batch);   // steps side by side of such a stack, 0: one after the other (stack_kernels.h)
 hipError_t launch_row(int io_bf16, const RowArgs& a, int batch, hipStream_t st);   // (an error: nothing was launched)
 
 struct SsdPrepPair;

@@ -73,7 +73,7 @@ static hipError_t launch_io(const StackArgs& a, int batch, hipStream_t st)
 //   64 tokens    1640 chains, 3 steps 3.4/3.2, 4096 chains, 8 steps 2.89/5.09, 1024 chains, 4 steps 2.91/3.07, 16384 chains, 8 steps 12.0/12.1
 //   128 tokens   1024 chains, 4 steps 8.88/3.88
 //   8 states     4096 chains x 32, 8 steps 0.93/2.47, 24576 6.22/10.9, 2616 x 64, 4 steps 2.08/4.80
-static int quad_steps(const StackArgs& a, int batch)
+int stack_side_by_side(const StackArgs& a, int batch)
 {
     const size_t bytes = (size_t)QuadLds(a.L, a.N).total * sizeof(float);
     const int most = (int)std::min<size_t>(kQuadMaxSteps, kStackLdsBytes / bytes);
@@ -113,9 +113,11 @@ static hipError_t launch_quad_io(const StackArgs& a, int side, int batch, hipStr
     }
 }
 
-hipError_t launch_stack(int io_bf16, const StackArgs& a, int batch, hipStream_t st)
+// (steps side by side store their outputs in no order, and a layer's state and tail are replaced while they may still read those of a
+// later layer: what shares memory goes one step after the other, so that the last one's values stay)
+hipError_t launch_stack(int io_bf16, const StackArgs& a, int batch, bool apart, hipStream_t st)
 {
-    if (const int side = quad_steps(a, batch); side > 0)
+    if (const int side = apart ? stack_side_by_side(a, batch) : 0; side > 0)
         return io_bf16 ? launch_quad_io<IoBF16>(a, side, batch, st) : launch_quad_io<IoF32>(a, side, batch, st);
     return io_bf16 ? launch_io<IoBF16>(a, batch, st) : launch_io<IoF32>(a, batch, st);
 }

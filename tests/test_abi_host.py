@@ -333,3 +333,12 @@ def test_inputs_struct_holds_each_view_as_it_is():
     for bad in (dict(x=base[:, :, ::2]), dict(z=base[0]), dict(B=base[:, :, :32].unflatten(2, (2, 16))[..., :8]), dict(C=base.unflatten(2, (8, 5)).transpose(2, 3))):
         with pytest.raises(AssertionError):
             bd.make_inputs(dict(views, **bad))
+
+
+def test_stack_form_of_a_table_is_decided_on_the_host():
+    """Steps side by side: as many as fit the LDS, in rounds as even as they go; none for a single step, for a descriptor that takes no stack."""
+    side = lambda n, *a, **kw: bd.bimamba_block_stack_side_by_side(bd.make_desc(synth.mixer_cfg(*a, **kw)), n)
+    assert [side(n, 1, 32, 4096) for n in (-1, 0, 1, 2, 4, 8, 9, 16)] == [0, 0, 0, 0, 4, 8, 5, 8]
+    assert side(8, 2, 64, 2045) == 4          # 64 tokens: six steps' LDS, two rounds
+    assert side(4, 1, 128, 256) == 0          # long blocks of few channels: time segments
+    assert side(8, 1, 32, 64, d_state=32) == side(8, 1, 32, 64, combine=1) == side(8, 0, 32, 64) == 0

@@ -178,3 +178,61 @@ def test_stack_steps_do_not_reach_each_other():
     torch.cuda.synchronize()
     assert all(bool(torch.isfinite(loop.out[s]).all()) for s in (0, 2)) and bool(torch.isfinite(loop.h[0]).all())
     assert not bool(torch.isfinite(loop.out[1][:, 6]).any())
+
+
+@pytest.mark.parametrize("shared", ["the same", "a token further", "two in turn", "states and tails"])
+def test_steps_and_layers_that_share_memory(shared):
+    """A table whose steps leave outputs in the same memory, or whose layers share a cache: what an earlier step left or read is what it is
+    when the steps follow each other, at a size whose steps otherwise go side by side."""
+    from paper_2511_15927_amd import binding as bd
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    layers, steps, L, Dn = 4, 8, 32, 130
+    cfg = synth.mixer_cfg(1, L, Dn, io="f32")
+    assert bd.bimamba_block_stack_side_by_side(bd.make_desc(cfg), steps) == 8
+    params = [(synth.make_params(cfg, 210 + l, 0), synth.make_params(cfg, 210 + l, 1)) for l in range(layers)]
+    inputs = [synth.make_inputs(cfg, 220 + s) for s in range(steps)]
+
+    def run(outs_of, caches):
+        loop = BlockDecodeLoop(cfg, params, steps, keep_layer_outputs=True)
+        for s in range(steps):
+            loop.set_step_inputs(s, inputs[s])
+        g = torch.Generator().manual_seed(5)
+        for i in range(2):       # the caches of layers 0 and 1; those of 2 and 3 are the same values
+            loop.h[i].copy_(0.2 * torch.randn(loop.h[i].shape, generator=g))
+            loop.tail[i].copy_(torch.randn(loop.tail[i].shape, generator=g))
+            loop.h[i + 2].copy_(loop.h[i])
+            loop.tail[i + 2].copy_(loop.tail[i])
+        stack = [bd.StackLayer(*loop._params[l], loop.h[caches[l]].data_ptr(), loop.tail[caches[l]].data_ptr()) for l in range(layers)]
+        outs = outs_of(loop)
+        table = bd.make_stack_table(stack, [bd.make_inputs(i) for i in loop.step_inputs], outs)
+        table_dev = torch.frombuffer(bytearray(table), dtype=torch.uint8).cuda()
+        bd.bimamba_block_stack(loop.desc, layers, steps, table, table_dev)
+        torch.cuda.synchronize()
+        return [o.clone() for o in outs], [h.clone() for h in loop.h]
+
+    own = lambda loop: [loop.layer_output(s, l) for s in range(steps) for l in range(layers)]
+    apart, h_apart = run(own, range(layers))
+    tol = 1e-5 * 2 * layers      # (fp32: either form is within 1e-5 of the oracle at each of the layers that feed each other)
+    close = lambda a, b: rel_l2(a.cpu().numpy(), b.cpu().numpy()) < tol
+    last = [apart[s * layers + layers - 1] for s in range(steps)]
+    assert not any(close(last[s], last[-1]) for s in range(steps - 1))
+    if shared == "states and tails":
+        outs, h = run(own, (0, 1, 0, 1))
+        for i in range((steps - 1) * layers):      # every step but the last reads the caches as they were
+            assert close(outs[i], apart[i]), divmod(i, layers)
+        assert close(outs[(steps - 1) * layers], apart[(steps - 1) * layers])
+        return
+    if shared == "the same":
+        one = torch.zeros(1, L, Dn, device="cuda")
+        outs, h = run(lambda loop: [one] * (steps * layers), range(layers))
+        assert close(outs[-1], last[-1])
+    elif shared == "a token further":
+        run_of = torch.zeros(L + steps - 1, Dn, device="cuda")
+        outs, h = run(lambda loop: [run_of[s:s + L].unsqueeze(0) for s in range(steps) for l in range(layers)], range(layers))
+        want = torch.cat([last[s][:, :1] for s in range(steps - 1)] + [last[-1]], dim=1)
+        assert close(run_of.unsqueeze(0), want)
+    else:
+        two = [torch.zeros(1, L, Dn, device="cuda") for _ in range(2)]
+        outs, h = run(lambda loop: [two[l & 1] for s in range(steps) for l in range(layers)], range(layers))
+        assert close(two[1], last[-1]) and close(two[0], apart[-2])
+    assert all(close(a, b) for a, b in zip(h, h_apart))
