@@ -282,8 +282,9 @@ size_t bimamba_workspace_bytes(const bimamba_desc* desc, int block_variant);
  * workgroups and joined through a carry pass (>= 1; 0 on an invalid descriptor): the time segments of the
  * lane-per-chain kernels (1 for short calls with few chains, which one workgroup walks from end to end, in whatever
  * pieces), or the time parts of the chunked matrix-core kernels, which are 1 unless a call has so few (batch, head)
- * pairs that they would leave half of the chip empty (where two or few parts are all there would be, a call whose directions are
- * added walks from both ends at once instead, in two launches that meet in the middle, without a carry pass).  Pure host code. */
+ * pairs that they would leave half of the chip empty.  1 too for such calls whose directions are added and which would have few parts:
+ * they walk from both ends at once, in two launches that meet in the middle, without a carry pass (but where z or out has a token
+ * stride beyond 2^24 elements, which the answer does not know of: those take the parts).  Pure host code. */
 int bimamba_time_chunks(const bimamba_desc* desc);
 
 /* Benchmark diagnostics: arm a one-shot probe on the calling host thread.  The next bimamba_fwd or

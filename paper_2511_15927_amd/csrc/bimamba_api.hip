@@ -1252,7 +1252,7 @@ int bimamba_time_chunks(const bimamba_desc* desc)
     if (check_desc(desc)) return 0;
     const Plan p = make_plan(desc, true, false, SIZE_MAX);
     RowForm row;
-    return p.ssd ? p.ssd_parts : row_call(desc, p, &row) ? 1 : p.nseg;
+    return p.ssd ? (p.ssd_meet ? 1 : p.ssd_parts) : row_call(desc, p, &row) ? 1 : p.nseg;
 }
 
 void bimamba_profile_next_call(void* ev_start, void* ev_stop)

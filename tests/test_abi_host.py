@@ -168,16 +168,18 @@ def test_narrow_sequences_are_cut_into_segments(batch, L, Dn, N):
 
 
 def test_time_parts_of_the_matrix_core_path():
-    # 64 heads: batch 1 leaves 3/4 of the CUs empty -> 4 parts; batch 2 -> 2; batch 4 fills the chip -> 1.
+    # 64 heads: batch 1 leaves 3/4 of the CUs empty -> 4 parts; batch 2 would have 2 and meets in the middle; batch 4 fills the chip -> 1.
     parts = {b: bd.bimamba_time_chunks(bd.make_desc(synth.m2_cfg(b, 8192, 4096))) for b in (1, 2, 3, 4, 8)}
-    assert parts == {1: 4, 2: 2, 3: 1, 4: 1, 8: 1}, parts
+    assert parts == {1: 4, 2: 1, 3: 1, 4: 1, 8: 1}, parts
+    # directions kept apart share a launch anyway: twice the items, never met in the middle
+    parts = {b: bd.bimamba_time_chunks(bd.make_desc(synth.m2_cfg(b, 8192, 4096, combine=1))) for b in (1, 2, 4)}
+    assert parts == {1: 2, 2: 1, 4: 1}, parts
     # 8 heads: 16 parts at most, and no part shorter than 8 chunks of 64 tokens
     assert bd.bimamba_time_chunks(bd.make_desc(synth.m2_cfg(1, 32768, 512))) == 16
     assert bd.bimamba_time_chunks(bd.make_desc(synth.m2_cfg(1, 2048, 512))) == 4
-    assert bd.bimamba_time_chunks(bd.make_desc(synth.m2_cfg(1, 1023, 512))) == 2
-    assert bd.bimamba_time_chunks(bd.make_desc(synth.m2_cfg(1, 960, 512))) == 1
-    # parts of ceil(chunks / parts) chunks: 17 chunks in 2 parts of 9
-    assert bd.bimamba_time_chunks(bd.make_desc(synth.m2_cfg(1, 17 * 64, 512))) == 2
+    for L, apart in ((1023, 2), (960, 1), (17 * 64, 2)):     # parts of ceil(chunks / parts) chunks: 17 chunks in 2 parts of 9
+        assert bd.bimamba_time_chunks(bd.make_desc(synth.m2_cfg(1, L, 512, combine=1))) == apart
+        assert bd.bimamba_time_chunks(bd.make_desc(synth.m2_cfg(1, L, 512))) == 1     # (two parts at most: met in the middle)
     # the part states live in the workspace
     one = bd.bimamba_workspace_bytes(bd.make_desc(synth.m2_cfg(4, 8192, 4096))) / 4
     assert bd.bimamba_workspace_bytes(bd.make_desc(synth.m2_cfg(1, 8192, 4096))) > one

@@ -162,15 +162,15 @@ def test_ssd_state_not_16_byte_aligned_falls_back(gpu, oracle):
     assert float(buf_out[0]) == 0.0
 
 
-@pytest.mark.parametrize("L,batch,N,kw", [(1100, 1, 128, {}), (2117, 2, 64, dict(combine=1)),
-                                          (1030, 1, 64, dict(conv_bc=0, dt_softplus=0, d_kind=0))])
-def test_ssd_time_parts(gpu, oracle, L, batch, N, kw):
+@pytest.mark.parametrize("L,batch,N,parts,kw", [(1550, 1, 128, 3, {}), (2117, 2, 64, 4, dict(combine=1)), (1100, 1, 128, 2, dict(combine=1)),
+                                                (1481, 1, 64, 3, dict(conv_bc=0, dt_softplus=0, d_kind=0))])
+def test_ssd_time_parts(gpu, oracle, L, batch, N, parts, kw):
     """Few (batch, head) items and many chunks: each item's chunks are dealt to several workgroups (a state-only pass,
     a carry over the parts, then the output pass).  Ragged last part, both combines, and the block variant: the parts
     start from the cached state and the committed state is the last part's."""
     from paper_2511_15927_amd import binding as bd
     cfg = synth.m2_cfg(batch, L, 256, headdim=64, d_state=N, **kw)
-    assert bd.bimamba_time_chunks(bd.make_desc(cfg)) > 1
+    assert bd.bimamba_time_chunks(bd.make_desc(cfg)) == parts
     pf, pb, inp = case(cfg, 1900 + L)
     ref = oracle.bimamba_fwd(cfg, to_np(pf), to_np(pb), to_np(inp))
     assert_close(gpu.gpu_fwd(cfg, pf, pb, inp), ref, gpu.TOL["bf16"])
@@ -180,7 +180,7 @@ def test_ssd_time_parts(gpu, oracle, L, batch, N, kw):
     blk = {k: v[:, m:].contiguous() for k, v in inp.items()}
     _, h_pre, tail_pre = oracle.bimamba_block_fwd(dict(cfg, seqlen=m), to_np(pf), to_np(pb), to_np(pre))
     cb = dict(cfg, seqlen=L - m)
-    assert bd.bimamba_time_chunks(bd.make_desc(cb)) > 1
+    assert bd.bimamba_time_chunks(bd.make_desc(cb)) == parts
     ref_b, h_ref, tail_ref = oracle.bimamba_block_fwd(cb, to_np(pf), to_np(pb), to_np(blk), h_in=h_pre.astype(np.float32), tail_in=tail_pre)
     out, h, tail = gpu.gpu_block_fwd(cb, pf, pb, blk, h_in=h_pre.astype(np.float32), tail_in=tail_pre)
     assert_close(out, ref_b, gpu.TOL["bf16"])
@@ -189,13 +189,15 @@ def test_ssd_time_parts(gpu, oracle, L, batch, N, kw):
 
 
 @pytest.mark.parametrize("token_stride", [1 << 24, (1 << 24) + 2])
-def test_ssd_time_parts_with_a_wide_x_stride(gpu, oracle, token_stride):
+@pytest.mark.parametrize("combine", [0, 1])
+def test_ssd_time_parts_with_a_wide_x_stride(gpu, oracle, token_stride, combine):
     """x as a view with a token stride of 2^24 elements, the widest for which the state pass of the time parts may
-    address a chunk's rows with 32-bit offsets, and just beyond it, where the call runs without parts."""
+    address a chunk's rows with 32-bit offsets, and just beyond it, where the call runs without parts.  (Directions kept apart: those that
+    are added meet in the middle, whatever the stride.)"""
     from paper_2511_15927_amd import binding as bd
     L = 1030
-    cfg = synth.m2_cfg(1, L, 256, headdim=64, d_state=64)
-    assert bd.bimamba_time_chunks(bd.make_desc(cfg)) > 1
+    cfg = synth.m2_cfg(1, L, 256, headdim=64, d_state=64, combine=combine)
+    assert bd.bimamba_time_chunks(bd.make_desc(cfg)) == 1 + combine
     pf, pb, inp = case(cfg, 4242)
     ref = oracle.bimamba_fwd(cfg, to_np(pf), to_np(pb), to_np(inp))
     desc = bd.make_desc(cfg)
@@ -207,7 +209,7 @@ def test_ssd_time_parts_with_a_wide_x_stride(gpu, oracle, token_stride):
     out, ws = bd.alloc_out(cfg), bd.alloc_workspace(desc)
     bd.bimamba_fwd(desc, bd.make_params(dpf), bd.make_params(dpb), bd.make_inputs(dinp), None, bd.make_tensor(out), ws)
     torch.cuda.synchronize()
-    got = out.float().cpu().numpy()
+    got = out.float().cpu().numpy().reshape(ref.shape)
     del big, wide, dinp
     torch.cuda.empty_cache()
     assert_close(got, ref, gpu.TOL["bf16"])
@@ -290,13 +292,14 @@ def test_ssd_block_call_with_rows_far_apart(gpu, oracle, L, combine, views):
     assert np.array_equal(tail.float().cpu().numpy(), t_ref)
 
 
-@pytest.mark.parametrize("name,batch", [("cfg2_m2", 1), ("headline_m2", 1), ("headline_m2", 2)])
-def test_ssd_time_parts_at_benchmark_size_sampled(gpu, oracle, name, batch):
+@pytest.mark.parametrize("name,batch,combine,parts", [("cfg2_m2", 1, 0, 4), ("headline_m2", 1, 0, 4), ("headline_m2", 1, 1, 2), ("headline_m2", 2, 0, 1)])
+def test_ssd_time_parts_at_benchmark_size_sampled(gpu, oracle, name, batch, combine, parts):
     """The time-part path (state pass over sub-parts, carry, concurrent output pass) at the benchmark's own sizes, in the
-    launch configuration the benchmark times; the oracle runs on sampled channels."""
+    launch configuration the benchmark times; with two parts at most the added directions meet in the middle instead.  The oracle
+    runs on sampled channels."""
     from paper_2511_15927_amd import binding as bd
-    cfg = dict(synth.CONFIGS[name], batch=batch)
-    assert bd.bimamba_time_chunks(bd.make_desc(cfg)) > 1
+    cfg = dict(synth.CONFIGS[name], batch=batch, combine=combine)
+    assert bd.bimamba_time_chunks(bd.make_desc(cfg)) == parts
     pf, pb, inp = case(cfg, 1700 + batch)
     sel = sorted(np.random.default_rng(5).choice(cfg["d_inner"], size=24, replace=False).tolist())
     ref = oracle.bimamba_fwd(cfg, to_np(pf), to_np(pb), to_np(inp), sel=sel)
