@@ -45,7 +45,9 @@ class BlockDecodeLoop:
         self._step_views = [dict(views) for views in self.step_inputs]
         self._row_strides = {k: (G * n, n) for k, n in widths.items()}
         self._step_places = [bd.make_inputs(views) for views in self.step_inputs]
+        self._step_ptrs = [{k: t.data_ptr() for k, t in views.items()} for views in self.step_inputs]
         self._device = self._step_flat[0].get_device() if self.n_steps else -1   # (-1: host memory)
+        self._copies_at_once = self._device >= 0
         width = Dn * (2 if cfg["combine"] == bd.COMBINE_SEPARATE else 1)
         assert width == Dn, "layers chain out -> x, which needs the additive combine"
         n_act = self.n_steps * self.n_layers if keep_layer_outputs else 2
@@ -68,28 +70,45 @@ class BlockDecodeLoop:
 
     def set_step_inputs(self, step, inputs):
         """inputs: dict of tensors x, z [Bt,G,Dn]; dt [Bt,G,H]; B, C [Bt,G,G*N] or [Bt,G,groups,N] (any device)."""
+        if self._copies_at_once and self._device != torch.cuda.current_device():
+            with torch.cuda.device(self._device):
+                return self.set_step_inputs(step, inputs)
         dsts = self.step_inputs[step]
-        # one launch where the tensors are of the buffer's kind, rows of whole channels and no part of it (the library checks the last two;
-        # 24 layers x 8 steps of 32 tokens at batch 1: 57 us of host time a step with one concatenation, 12 so)
-        if self._device >= 0 and self._device == torch.cuda.current_device():
-            flat, views, words = self._step_flat[step], self._step_views[step], []
+        if not self._copies_at_once or not self._copy_at_once(step, dsts, inputs):
             for k, dst in dsts.items():
-                t = inputs[k]
-                if (dst is not views[k] or type(t) is not torch.Tensor or t.get_device() != self._device or t.dtype is not flat.dtype or
-                        t.requires_grad or t.is_neg()):
-                    break
-                if t.is_contiguous() and t.numel() == dst.numel():
-                    words += (t.data_ptr(), *self._row_strides[k])
-                elif t.dim() == 3 and t.shape == dst.shape and t.stride(2) == 1:
-                    words += (t.data_ptr(), t.stride(0), t.stride(1))
-                else:
-                    break
-            else:
-                if bd.bimamba_copy_inputs(self.desc, bd.input_words(words), self._step_places[step], check=False) == 0:
-                    torch.autograd.graph.increment_version(flat)
-                    return
+                dst.copy_(inputs[k].reshape(dst.shape))
+
+    def _copy_at_once(self, step, dsts, inputs):
+        """A step's tensors in one launch, where they are of the buffer's kind and no part of it and it stands where it was made; one that
+        does not lie in rows of whole channels is copied into such rows before.  False: nothing was written.  (24 layers x 8 steps of 32
+        tokens at batch 1: 57 us of host time a step with one concatenation, 12 so.)"""
+        flat, views, places, words, held = self._step_flat[step], self._step_views[step], self._step_ptrs[step], [], []
+        if flat.is_inference() and not torch.is_inference_mode_enabled():
+            return False   # (a write that torch refuses)
+
+        def in_rows(t, dst):
+            return (t.dim() == 3 and t.shape == dst.shape and t.stride(2) == 1 and t.stride(1) >= t.shape[2] and
+                    (t.shape[0] == 1 or t.stride(0) >= (t.shape[1] - 1) * t.stride(1) + t.shape[2]))
+
         for k, dst in dsts.items():
-            dst.copy_(inputs[k].reshape(dst.shape))
+            t = inputs[k]
+            if (dst is not views[k] or dst.data_ptr() != places[k] or type(t) not in (torch.Tensor, torch.nn.Parameter) or t.get_device() != self._device or
+                    t.dtype is not flat.dtype or t.numel() != dst.numel() or t.requires_grad or t.is_neg()):
+                return False
+            if t.is_contiguous():
+                words += (t.data_ptr(), *self._row_strides[k])
+                continue
+            if not in_rows(t, dst):
+                if t.untyped_storage().data_ptr() == flat.untyped_storage().data_ptr():
+                    return False   # (to be read after the tensors before it are written)
+                t = t.reshape(dst.shape)
+                t = t if in_rows(t, dst) else t.contiguous()
+                held.append(t)
+            words += (t.data_ptr(), t.stride(0), t.stride(1))
+        if bd.bimamba_copy_inputs(self.desc, bd.input_words(words), self._step_places[step], check=False) != 0:
+            return False   # (a part of the buffer among them)
+        torch.autograd.graph.increment_version(flat)
+        return True
 
     def _call(self, layer, step, x, out, commit, stream):
         pf, pb = self._params[layer]

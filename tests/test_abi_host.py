@@ -218,13 +218,33 @@ def test_status_strings():
 
 
 @pytest.mark.parametrize("kind", ["same", "strided", "other_dtype", "own", "grad"])
-def test_step_inputs_refreshed_together_or_one_by_one(kind):
-    """A step's tensors are refreshed in one go where they are of the buffer's kind, one by one otherwise: the same values at odd sizes."""
+@pytest.mark.parametrize("at_once", [False, True])
+def test_step_inputs_refreshed_together_or_one_by_one(kind, at_once, monkeypatch):
+    """A step's tensors are refreshed in one go where they are of the buffer's kind, one by one otherwise and in host memory: the same
+    values at odd sizes.  (One go: as on a GPU, the library's copy stood in for by one of its places in host memory.)"""
     from paper_2511_15927_amd.decode import BlockDecodeLoop
     cfg = synth.mixer_cfg(2, 3, 5, d_state=4)
     layer = (synth.make_params(cfg, 1, 0), synth.make_params(cfg, 1, 1))
     loop = BlockDecodeLoop(cfg, [layer], 2, device="cpu")
     want = {k: v.to(torch.bfloat16) for k, v in synth.make_inputs(cfg, 3).items()}
+    statuses = []
+
+    def copy(desc, src, dst, stream=None, check=True):
+        flat = loop._step_flat[0]
+        widths = dict(x=5, z=5, dt=5, B=4, C=4)
+        inside = lambda p: flat.data_ptr() <= p < flat.data_ptr() + flat.numel() * 2
+        statuses.append(-8 if any(inside(getattr(src, k).ptr) for k in widths) else 0)
+        if statuses[-1] == 0:
+            for k, n in widths.items():
+                s, d = getattr(src, k), getattr(dst, k)
+                for b in range(2):
+                    for t in range(3):
+                        C.memmove(d.ptr + 2 * (b * d.stride_batch + t * d.stride_token), s.ptr + 2 * (b * s.stride_batch + t * s.stride_token), 2 * n)
+        return statuses[-1]
+    if at_once:
+        monkeypatch.setattr(bd, "bimamba_copy_inputs", copy)
+        monkeypatch.setattr(torch.cuda, "current_device", lambda: -1)
+        loop._copies_at_once = True
     given = dict(want)
     if kind == "strided":
         given["x"] = want["x"].transpose(0, 1).contiguous().transpose(0, 1)
@@ -235,11 +255,15 @@ def test_step_inputs_refreshed_together_or_one_by_one(kind):
         given = dict(loop.step_inputs[0])
     elif kind == "grad":
         given["dt"] = want["dt"].clone().requires_grad_()
+    statuses.clear()
+    version = loop._step_flat[0]._version
     with torch.no_grad():
         loop.set_step_inputs(0, given)
     for k, v in want.items():
         assert torch.equal(loop.step_inputs[0][k], v.reshape(loop.step_inputs[0][k].shape)), k
     assert all(t.count_nonzero() == 0 for t in loop.step_inputs[1].values())
+    assert statuses == ([] if not at_once else {"same": [0], "strided": [0], "own": [-8]}.get(kind, []))
+    assert loop._step_flat[0]._version > version
 
 
 @pytest.mark.parametrize("replaced", [("x",), ("dt", "C"), ("x", "z", "dt", "B", "C")])
@@ -344,3 +368,49 @@ def test_stack_form_of_a_table_is_decided_on_the_host():
     assert side(8, 2, 64, 2045) == 4          # 64 tokens: six steps' LDS, two rounds
     assert side(4, 1, 128, 256) == 0          # long blocks of few channels: time segments
     assert side(8, 1, 32, 64, d_state=32) == side(8, 1, 32, 64, combine=1) == side(8, 0, 32, 64) == 0
+
+
+def test_copy_inputs_errors_are_decided_on_the_host():
+    """bimamba_copy_inputs: missing and narrow views on either side, a place that overlaps a source or another place.  (Legal copies would
+    launch: the GPU tests have those.)"""
+    Bt, L, Dn, N = 2, 64, 128, 16
+    desc = bd.make_desc(synth.mixer_cfg(Bt, L, Dn))
+    at = lambda i: 0x1000000 * (i + 1)      # nothing is read
+    widths = dict(x=Dn, z=Dn, dt=Dn, B=N, C=N)
+    side = lambda i, **over: bd.Inputs(*[over.get(k, bd.Tensor(at(i + j), L * n, n)) for j, (k, n) in enumerate(widths.items())])
+
+    def call(src, dst, desc=desc):
+        return bd.lib().bimamba_copy_inputs(C.byref(desc), None if src is None else C.byref(src), None if dst is None else C.byref(dst), None)
+
+    assert call(None, side(5)) == call(side(0), None) == -1
+    for k, n in widths.items():
+        for bad, code in ((bd.Tensor(None, L * n, n), -1), (bd.Tensor(at(20) + 1, L * n, n), -4), (bd.Tensor(at(20), L * n, n - 1), -2),
+                          (bd.Tensor(at(20), L * n - 1, n), -2), (bd.Tensor(at(20), L << 27, 1 << 27), -3)):
+            assert call(side(0, **{k: bad}), side(5)) == code, (k, code)
+            assert call(side(0), side(5, **{k: bad})) == code, (k, code)
+    last = 2 * (Bt * L * Dn - 1)     # the last element of x, in bytes
+    for where in (at(0), at(0) + last, at(1), at(3)):      # x's place over x, its end, z, B as they come
+        assert call(side(0), side(5, x=bd.Tensor(where, L * Dn, Dn))) == -8, hex(where)
+    assert call(side(0), side(5, C=bd.Tensor(at(5) + last, L * N, N))) == -8                   # C's place at the end of x's
+    assert call(side(0), side(5, B=bd.Tensor(at(6) - 2 * Bt * L * N + 2, L * N, N))) == -8     # B's place reaches into z's
+    assert call(side(0), side(0)) == -8
+    assert call(side(0), side(0), bd.make_desc(synth.mixer_cfg(0, L, Dn))) == 0                # nothing to do
+
+
+def test_step_inputs_of_a_loop_made_in_inference_mode(monkeypatch):
+    """Refused outside that mode, as torch refuses every write to such tensors, with nothing written; taken inside it."""
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    cfg = synth.mixer_cfg(1, 4, 8, d_state=4)
+    calls = []
+    monkeypatch.setattr(bd, "bimamba_copy_inputs", lambda *a, **kw: calls.append(a) or 0)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: -1)
+    with torch.inference_mode():
+        loop = BlockDecodeLoop(cfg, [(synth.make_params(cfg, 1, 0), synth.make_params(cfg, 1, 1))], 1, device="cpu")
+    loop._copies_at_once = True
+    given = {k: v.to(torch.bfloat16) for k, v in synth.make_inputs(cfg, 3).items()}
+    with pytest.raises(RuntimeError):
+        loop.set_step_inputs(0, given)
+    assert not calls
+    with torch.inference_mode():
+        loop.set_step_inputs(0, given)
+    assert len(calls) == 1

@@ -176,3 +176,104 @@ def test_block_in_a_callers_own_graph():
         assert same(run(second.replay), want_calls)
         assert same(run(loop.run_block_eager), want_second)
     assert not torch.equal(want_first[0], want_second[0])
+
+
+@pytest.mark.parametrize("io", ["bf16", "f32"])
+@pytest.mark.parametrize("batch,L,Dn,kw", [
+    (1, 1, 5, dict(d_state=4)),                                  # rows shorter than a piece of eight
+    (3, 7, 8, dict(d_state=8)),                                  # one piece each
+    (2, 33, 130, {}),                                            # a remainder of two
+    (1, 32, 4096, {}),                                           # several workgroups
+    (2, 5, 192, dict(n_heads=24, n_groups=3, d_state=8)),        # B and C of three groups, few dt columns
+])
+def test_copy_inputs_rows_at_any_place(io, batch, L, Dn, kw):
+    """bimamba_copy_inputs bit for bit, between contiguous tensors and column slices at 16-byte and at odd places on either side, batch strides
+    of their own; what lies around the places stays."""
+    from paper_2511_15927_amd import binding as bd
+    cfg = synth.mixer_cfg(batch, L, Dn, io=io, **kw)
+    desc, dtype, GN = bd.make_desc(cfg), bd.io_dtype(cfg), cfg["n_groups"] * cfg["d_state"]
+    widths = dict(x=Dn, z=Dn, dt=cfg["n_heads"], B=GN, C=GN)
+    g = torch.Generator(device="cuda").manual_seed(L + Dn)
+
+    def sides(pad, at):      # one buffer a tensor: `at` columns in front, so many in all that rows are `pad` apart modulo 8, a batch element to spare
+        whole = {k: torch.randn(batch, L + 1, (n + at + 7) // 8 * 8 + pad, device="cuda", generator=g).to(dtype) for k, n in widths.items()}
+        return whole, {k: w[:, :L, at:at + widths[k]] for k, w in whole.items()}
+
+    plain = {k: torch.randn(batch, L, n, device="cuda", generator=g).to(dtype) for k, n in widths.items()}
+    for src in (plain, sides(0, 8)[1], sides(8, 0)[1], sides(3, 1)[1]):
+        for pad, at in ((0, 0), (8, 16), (0, 1), (5, 2)):
+            whole, dst = sides(pad, at)
+            kept = {k: w.clone() for k, w in whole.items()}
+            for k, n in widths.items():
+                kept[k][:, :L, at:at + n] = src[k]
+            four = {k: v if k in "xz" or k == "dt" else v.unflatten(2, (cfg["n_groups"], -1)) for k, v in src.items()}
+            bd.bimamba_copy_inputs(desc, bd.make_inputs(four), bd.make_inputs(dst))
+            torch.cuda.synchronize()
+            for k in widths:
+                assert torch.equal(whole[k], kept[k]), (k, pad, at)
+
+
+@pytest.mark.parametrize("kind,at_once", [("same", 1), ("columns", 1), ("odd columns", 1), ("transposed", 1), ("flat rows", 1), ("groups apart", 1), ("one row", 1),
+                                          ("parameter", 1), ("own", 0), ("own, turned", 0), ("other dtype", 0), ("host", 0), ("grad", 0), ("replaced", 0), ("moved", 0)])
+def test_step_inputs_refreshed_in_one_launch(kind, at_once, monkeypatch):
+    """set_step_inputs with tensors on the device: the values asked for, in one launch of the library where they are of the buffer's kind, and
+    the other step as it was."""
+    from paper_2511_15927_amd import binding as bd
+    from paper_2511_15927_amd.decode import BlockDecodeLoop
+    cfg = synth.mixer_cfg(2, 9, 128, n_groups=2, n_heads=16, d_state=4)
+    loop = BlockDecodeLoop(cfg, [(synth.make_params(cfg, 1, 0), synth.make_params(cfg, 1, 1))], 2)
+    real, statuses = bd.bimamba_copy_inputs, []
+
+    def counted(*a, **kw):
+        statuses.append(real(*a, **kw))
+        return statuses[-1]
+    monkeypatch.setattr(bd, "bimamba_copy_inputs", counted)
+    want = {k: v.to("cuda", torch.bfloat16).reshape(2, 9, -1) for k, v in synth.make_inputs(cfg, 3).items()}
+    given = dict(want)
+    if kind in ("columns", "odd columns"):
+        at = 8 if kind == "columns" else 3
+        wide = torch.randn(2, 9, 128 + 128 + 16 + 8 + 8 + at, device="cuda").to(torch.bfloat16)
+        for k in given:
+            n = want[k].shape[2]
+            wide[:, :, at:at + n] = want[k]
+            given[k] = wide[:, :, at:at + n]
+            at += n
+    elif kind == "transposed":
+        given["x"] = want["x"].transpose(0, 1).contiguous().transpose(0, 1)
+        given["z"] = want["z"].transpose(1, 2).contiguous().transpose(1, 2)
+    elif kind == "flat rows":
+        given["dt"] = torch.cat([want["dt"], want["dt"]], dim=2).reshape(18, 32)[:, :16]
+    elif kind == "groups apart":
+        given["B"] = torch.stack([want["B"].unflatten(2, (2, 4))] * 2, dim=3)[:, :, :, 1]
+        given["C"] = want["C"].unflatten(2, (2, 4))
+    elif kind == "one row":
+        want["dt"] = want["dt"][:1, :1].expand(2, 9, 16)
+        given["dt"] = want["dt"]
+    elif kind == "parameter":
+        given["x"] = torch.nn.Parameter(want["x"], requires_grad=False)
+    elif kind == "own":
+        loop.set_step_inputs(0, dict(want, x=want["z"]))
+        given["z"] = loop.step_inputs[0]["x"]       # (read after x has been written)
+        want["z"] = want["x"]
+    elif kind == "own, turned":      # 128 rows of nine of the buffer of x, which hold the new x by then
+        given["z"] = loop.step_inputs[0]["x"].flatten(1).unflatten(1, (128, 9)).transpose(1, 2)
+        want["z"] = want["x"].flatten(1).unflatten(1, (128, 9)).transpose(1, 2)
+    elif kind == "other dtype":
+        given["z"] = want["z"].float()
+    elif kind == "host":
+        given["z"] = want["z"].cpu()
+    elif kind == "grad":
+        given["dt"] = want["dt"].clone().requires_grad_()
+    elif kind == "replaced":
+        loop.step_inputs[0]["x"] = torch.zeros_like(loop.step_inputs[0]["x"])
+    elif kind == "moved":
+        loop.step_inputs[0]["x"].data = torch.zeros_like(loop.step_inputs[0]["x"])
+    statuses.clear()
+    version = loop._step_flat[0]._version
+    with torch.no_grad():
+        loop.set_step_inputs(0, given)
+    torch.cuda.synchronize()
+    for k, v in want.items():
+        assert torch.equal(loop.step_inputs[0][k], v), k
+    assert all(t.count_nonzero() == 0 for t in loop.step_inputs[1].values())
+    assert statuses.count(0) == at_once and loop._step_flat[0]._version > version
