@@ -26,7 +26,8 @@ bool stack_form(int batch, int seqlen, int d_inner, int d_state, RowForm* f)
     if (chains * seqlen > (d_state > 4 ? kStackMaxElements : kStackMaxElements4)) return false;
     const long long tiles = (long long)batch * ((d_inner + 3) / 4);
     const int groups = (seqlen + kRowTokens - 1) / kRowTokens;
-    int nseg = 1;   // segments and tiles as row_form takes them
+    // tiles as row_form takes them; segments of two groups or more (of one and a half there, whose segments are held for the second walk)
+    int nseg = 1;
     while (nseg < kRowMaxWaves / 2 && groups >= 4 * nseg && tiles * 4 * nseg <= 16LL * cu_count()) nseg *= 2;
     f->seg_len = (groups + nseg - 1) / nseg * kRowTokens;
     f->nseg = (seqlen + f->seg_len - 1) / f->seg_len;

@@ -1,5 +1,5 @@
-"""GPU parity of a stack of layers in one launch (bimamba_block_stack through BlockDecodeLoop): every layer's output of every
-step and the committed caches against the fp64 oracle fed that layer's own input, at block lengths around the groups of 16
+"""GPU parity of a stack of layers in one launch (bimamba_block_stack through BlockDecodeLoop), in either of its forms: every layer's output of
+every step and the committed caches against the fp64 oracle fed that layer's own input, at block lengths around the groups of 16
 tokens and the outputs a thread holds, for every conv width, state counts below a row's width, ragged channel tiles."""
 import numpy as np
 import pytest
@@ -11,25 +11,26 @@ from paper_2511_15927_amd import synth
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("batch,L,Dn,N,K,io,layers,kw", [
-    (1, 1, 72, 16, 4, "f32", 2, {}),                               # a block shorter than the conv tail
-    (2, 2, 5, 4, 3, "bf16", 3, dict(dt_softplus=1)),
-    (2, 16, 130, 8, 1, "f32", 1, {}),                              # no tail; one layer
-    (1, 17, 257, 16, 2, "bf16", 2, dict(dt_softplus=1)),
-    (3, 33, 1366, 16, 4, "f32", 2, {}),                            # several tiles of four channels in a workgroup, a ragged last one
-    (1, 32, 4098, 16, 4, "bf16", 3, {}),
-    (2, 64, 2045, 16, 4, "bf16", 2, dict(dt_softplus=1)),          # two outputs a thread or two time segments
-    (1, 65, 515, 8, 3, "f32", 2, {}),
-    (1, 100, 4096, 16, 4, "bf16", 2, {}),                          # four outputs a thread
-    (1, 128, 256, 16, 4, "f32", 2, dict(n_heads=32, n_groups=2, d_kind=1)),
-    (1, 200, 64, 16, 4, "f32", 2, dict(n_heads=4, a_kind=1)),
+@pytest.mark.parametrize("steps", [2, 1])
+@pytest.mark.parametrize("batch,L,Dn,N,K,io,layers,side,kw", [     # side: steps side by side, of two; a single one takes the row form
+    (1, 1, 72, 16, 4, "f32", 2, 2, {}),                               # a block shorter than the conv tail
+    (2, 2, 5, 4, 3, "bf16", 3, 2, dict(dt_softplus=1)),
+    (2, 16, 130, 8, 1, "f32", 1, 2, {}),                              # no tail; one layer
+    (1, 17, 257, 16, 2, "bf16", 2, 0, dict(dt_softplus=1)),
+    (3, 33, 1366, 16, 4, "f32", 2, 0, {}),                            # several tiles of four channels in a workgroup, a ragged last one
+    (1, 32, 4098, 16, 4, "bf16", 3, 0, {}),
+    (2, 64, 2045, 16, 4, "bf16", 2, 2, dict(dt_softplus=1)),          # (row form) two outputs a thread or two time segments
+    (1, 65, 515, 8, 3, "f32", 2, 2, {}),
+    (1, 100, 4096, 16, 4, "bf16", 2, 2, {}),                          # (row form) four outputs a thread
+    (1, 128, 256, 16, 4, "f32", 2, 0, dict(n_heads=32, n_groups=2, d_kind=1)),
+    (1, 200, 64, 16, 4, "f32", 2, 0, dict(n_heads=4, a_kind=1)),
 ])
-def test_stack_matches_oracle_layer_by_layer(oracle, batch, L, Dn, N, K, io, layers, kw):
+def test_stack_matches_oracle_layer_by_layer(oracle, batch, L, Dn, N, K, io, layers, side, kw, steps):
     from paper_2511_15927_amd import binding as bd
     from paper_2511_15927_amd.decode import BlockDecodeLoop
     cfg = synth.mixer_cfg(batch, L, Dn, d_state=N, d_conv=K, io=io, **kw)
     assert bd.bimamba_block_stack_form(bd.make_desc(cfg)) == 1
-    steps = 2
+    assert bd.bimamba_block_stack_side_by_side(bd.make_desc(cfg), steps) == (side if steps == 2 else 0)
     params = [(synth.make_params(cfg, 70 + l, 0), synth.make_params(cfg, 70 + l, 1)) for l in range(layers)]
     loop = BlockDecodeLoop(cfg, params, steps, keep_layer_outputs=True)
     g = torch.Generator().manual_seed(L)
@@ -73,14 +74,16 @@ def test_stack_refuses_what_it_cannot_take(oracle):
     assert bd.bimamba_block_stack_form(bd.make_desc(synth.m2_cfg(1, 32, 64, headdim=32, d_state=64))) == 0
 
 
+@pytest.mark.parametrize("steps", [2, 4])
 @pytest.mark.parametrize("batch,L,Dn,io", [(1, 32, 260, "bf16"), (2, 17, 130, "f32"), (1, 100, 2048, "bf16")])
-def test_stack_with_outputs_not_wanted(batch, L, Dn, io):
+def test_stack_with_outputs_not_wanted(batch, L, Dn, io, steps):
     """Layer outputs that nobody asked for, all but the last layer's or some of them: what is asked for and what is committed are
     the same bits as with all of them."""
     from paper_2511_15927_amd import binding as bd
     from paper_2511_15927_amd.decode import BlockDecodeLoop
-    layers, steps = 3, 2
+    layers = 3
     cfg = synth.mixer_cfg(batch, L, Dn, io=io)
+    assert bd.bimamba_block_stack_side_by_side(bd.make_desc(cfg), steps) == (4 if steps == 4 and L < 100 else 0)
     params = [(synth.make_params(cfg, 90 + l, 0), synth.make_params(cfg, 90 + l, 1)) for l in range(layers)]
     inputs = [synth.make_inputs(cfg, 95 + s) for s in range(steps)]
     got = []
@@ -108,7 +111,7 @@ def test_stack_with_outputs_not_wanted(batch, L, Dn, io):
         torch.cuda.synchronize()
         got.append((outs, loop.h, loop.tail))
     (every, h_all, tail_all), rest = got[0], got[1:]
-    for (outs, h, tail), wanted in zip(rest, ({2, 5}, {1, 3, 5})):
+    for (outs, h, tail), wanted in zip(rest, ({s * layers + layers - 1 for s in range(steps)}, {1, 3, 5})):
         for l in range(layers):
             assert torch.equal(h[l], h_all[l]) and torch.equal(tail[l], tail_all[l]), l
             for s in range(steps):
@@ -130,8 +133,10 @@ def test_stack_with_outputs_not_wanted(batch, L, Dn, io):
 def test_stack_steps_side_by_side(oracle, batch, L, Dn, N, K, io, layers, steps, kw):
     """Four lanes per chain, the steps of a block in one workgroup: every layer's output of every step and the committed caches of two
     blocks, at block lengths around the groups of four and eight tokens, with and without a last round that is not full."""
+    from paper_2511_15927_amd import binding as bd
     from paper_2511_15927_amd.decode import BlockDecodeLoop
     cfg = synth.mixer_cfg(batch, L, Dn, d_state=N, d_conv=K, io=io, **kw)
+    assert bd.bimamba_block_stack_side_by_side(bd.make_desc(cfg), steps) == {9: 5}.get(steps, 4 if L == 64 else steps)
     params = [(synth.make_params(cfg, 170 + l, 0), synth.make_params(cfg, 170 + l, 1)) for l in range(layers)]
     loop = BlockDecodeLoop(cfg, params, steps, keep_layer_outputs=True)
     assert loop._one_launch
