@@ -58,7 +58,7 @@ def read_profile(kernel_key):
     """The committed rocprofv3 --pmc summary of this workload's dominant kernel (profiles/<key>_pmc.txt, written by
     paper_2511_15927_amd.profile_summary): counters as floats, plus the kernel name and the file the values come from.
     These are STORED values of an earlier run of this same command, not measurements of the present run; kernels that the
-    library no longer has count for nothing."""
+    library no longer has count for nothing, and nor do the others in their place."""
     path = os.path.join(ROOT, "profiles", kernel_key + "_pmc.txt")
     sections, kernel, shared = {}, None, {}
     try:
@@ -72,11 +72,16 @@ def read_profile(kernel_key):
     except Exception:
         return {}, None, None
     built = library_kernels()
-    ours = {k: v for k, v in sections.items() if "bm::" in k and k in built}
+    sections = {k: v for k, v in sections.items() if "bm::" in k}
+    ours = {k: v for k, v in sections.items() if k in built}
     if not ours:
         return {}, None, None
-    # the dominant kernel of the step: the one with the longest dispatch
-    kernel = max(ours, key=lambda k: ours[k].get("DURATION_NS_UNDER_PMC", 0.0))
+    # the dominant kernel of the step: the one with the longest dispatch, of the template that had it when the values were stored
+    def longest(kernels):
+        return max(kernels, key=lambda k: kernels[k].get("DURATION_NS_UNDER_PMC", 0.0))
+    kernel = longest(ours)
+    if kernel.split("<")[0] != longest(sections).split("<")[0]:
+        return {}, None, None
     counters = dict(shared, **ours[kernel])
     # the chunked walk is a launch and a form per direction: a step's bytes are those of both
     if "ssd_wide_kernel" in kernel:

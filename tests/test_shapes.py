@@ -61,3 +61,16 @@ def test_stored_counters_count_only_for_kernels_that_exist(tmp_path, monkeypatch
     assert kernel == have[0] and bench.traffic_of(counters) == 11
     counters, kernel, _ = stored((walk[0], 5, 10), (walk[1], 4, 20))
     assert kernel == walk[0] and bench.traffic_of(counters) == 32
+    # (a preparation kernel is not the dominant one because the walk has gone)
+    prep = next(k for k in built if "bm::ssd_prep_kernel<128, 256>" in k and "stub" not in k)
+    assert stored((prep, 1, 10), (walk[0].replace("<128, 64, 2,", "<128, 64, 9,"), 5, 10)) == ({}, None, None)
+
+
+def test_stored_counters_are_of_kernels_of_the_library():
+    """The committed counters that bench.py prints name kernels that are built, the one that takes longest among them."""
+    import bench
+    for workload, dominant, launches in (("headline", "bm::sweep_kernel<16, 2, 0, bm::IoBF16, 0,", 1), ("headline_m2", "bm::ssd_wide_kernel<128, 64, 2,", 2)):
+        counters, kernel, _ = bench.read_profile("sweep_" + workload)
+        assert dominant in kernel
+        # more than the output alone, which each of a call's launches writes or parks in two bytes
+        assert bench.traffic_of(counters) > launches * 2 * 8 * 8192 * 4096
