@@ -13,7 +13,9 @@
 // the chip holds the call at once, workgroups of sixteen waves make them for themselves (WHOLE), while the state and x that the
 // waves have requested are on their way: a launch of one workgroup per (direction, group, batch element) before the walk
 // (ssd_block_prep_kernel) costs 5 us whatever it does.  16 x 32 tokens of 64 heads x 64 18.7 -> 16.2 us, 1 x 32 10.8 -> 8.0, with
-// the state committed 23.7 -> 20.4 and 13.9 -> 9.2.  Longer blocks and calls of more workgroups take the two launches.
+// state and tail committed to places of their own 23.7 -> 20.4 and 13.9 -> 9.2.  (Committed in place, as a decode loop does, the tail of
+// B and C takes a launch of its own behind, 11.4 for the second call; calls with four tiles a workgroup, the first one, keep to two
+// launches then, 23.4.)  So do longer blocks and calls of more workgroups.
 //
 // The barriers of the walk are those of the sharing: the first before the convs, which read x and the score operands that all four
 // waves have put into LDS; the last before the output's rows are read back from the y columns that the waves have left there.  With
